@@ -270,7 +270,8 @@ template <bool TRAIN>
 mpzch_status_t launch_discover(const Params &p, int grid, hipStream_t s)
 {
     if (TRAIN) {
-        if (p.num_tables > 1) hipLaunchKernelGGL(k_discover_tables, dim3(grid), dim3(kBlock), 0, s, p);
+        if (p.num_tables > 1 && p.all_records) hipLaunchKernelGGL(k_discover_tables_records, dim3(grid), dim3(kBlock), 0, s, p);
+        else if (p.num_tables > 1) hipLaunchKernelGGL(k_discover_tables, dim3(grid), dim3(kBlock), 0, s, p);
         else if (p.t0.sh) hipLaunchKernelGGL(k_discover_records, dim3(grid), dim3(kBlock), 0, s, p);
         else if (p.t0.N >= kStreamingSlots) hipLaunchKernelGGL(k_discover_streaming, dim3(grid), dim3(kBlock), 0, s, p);
         else hipLaunchKernelGGL(k_discover, dim3(grid), dim3(kBlock), 0, s, p);
@@ -1025,6 +1026,7 @@ mpzch_status_t mpzch_remap_jagged_feature_ttl(mpzch_group_t *g, int64_t *const *
         if (!any) return MPZCH_ERR_INVALID_ARG;          // no table of the group uses retention times
     }
     int32_t max_p = 1, max_p_lru = 0;
+    bool all_records = true;
     std::vector<TableDesc> descs((size_t)T);
     for (int f = 0; f < T; ++f) {
         if (!identities[f] || !metadata[f]) return MPZCH_ERR_INVALID_ARG;
@@ -1033,6 +1035,7 @@ mpzch_status_t mpzch_remap_jagged_feature_ttl(mpzch_group_t *g, int64_t *const *
         if (cap < 0 || evicted_offsets[f] < 0) return MPZCH_ERR_INVALID_ARG;
         if (cap > 0 && !out_evicted_slots) return MPZCH_ERR_INVALID_ARG;
         descs[f] = make_desc(g->cfgs[f], identities[f], metadata[f], evicted_offsets[f], cap);
+        all_records = all_records && descs[f].sh == 1;
         if (descs[f].P > max_p) max_p = descs[f].P;
         if (descs[f].evict == 2 && descs[f].P > max_p_lru) max_p_lru = descs[f].P;
     }
@@ -1053,6 +1056,7 @@ mpzch_status_t mpzch_remap_jagged_feature_ttl(mpzch_group_t *g, int64_t *const *
     p.num_tables = T;
     p.out_slots = out_slots;
     p.descs = g->train.dev;
+    p.all_records = all_records ? 1 : 0;
     p.offsets = feature_offsets;
     p.t0 = descs[0];
     p.out_evicted = out_evicted_slots;

@@ -38,6 +38,7 @@
 namespace mpzch {
 
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+typedef uint32_t u32x3 __attribute__((ext_vector_type(3)));
 
 constexpr int kWave = 64;
 constexpr int kBlock = 256;
@@ -114,6 +115,7 @@ struct Params {
     int64_t g_stride;              // bytes between rows
     int32_t g_chunks;              // 16-byte (g_wide) or 4-byte pieces per row
     int32_t g_wide;
+    int32_t all_records;           // several tables: every one of them is kept as records
     int32_t g_shift;               // log2(g_chunks) when that is a power of two, else -1
     // training remap that also resets the rows of the slots it evicts (one table; geometry in g_num_rows,
     // g_stride, g_chunks, g_wide, g_shift): rows[slot mod num_rows, :] <- init row, or zero bits
@@ -446,9 +448,10 @@ constexpr int kWhereAddrBits = 48;
 // that exist below its own -- its own slot when its round exists, else the first slot (r < r_lo) or the one after
 // the last (r >= r_hi): valid addresses in or next to the line that is fetched anyway.  Slots past the end of the
 // table go on at slot 0.
-// NT: the loads are marked non-temporal (see k_discover_streaming).
-template <int G, bool NT>
-__device__ __forceinline__ void probe_loads(const Tab &d, const ProbeReq *s_req, int64_t (&v)[G])
+// NT: the loads are marked non-temporal (see k_discover_streaming).  REC: a table of records, read with the
+// metadata (12 bytes per lane, the same line): what comes back besides the id is the slot's metadata.
+template <int G, bool NT, bool REC>
+__device__ __forceinline__ void probe_loads(const Tab &d, const ProbeReq *s_req, int64_t (&v)[G], int32_t (&m)[G])
 {
     constexpr int IPI = kWave / G;
     const int lane = lane_id();
@@ -463,8 +466,15 @@ __device__ __forceinline__ void probe_loads(const Tab &d, const ProbeReq *s_req,
         const uint32_t k = (uint32_t)__popc((uint32_t)(where >> kWhereAddrBits) & below);
         uint64_t a = (where & ((1ull << kWhereAddrBits) - 1ull)) + (uint64_t)(k << sh3);
         if (a >= table_end) a -= table_bytes;
-        if constexpr (NT) v[t] = __builtin_nontemporal_load((global_ptr<int64_t>)(uintptr_t)a);
-        else v[t] = *(global_ptr<int64_t>)(uintptr_t)a;
+        if constexpr (REC) {
+            const u32x3 rec = *(global_ptr<u32x3>)(uintptr_t)a;
+            v[t] = (int64_t)(((uint64_t)rec.y << 32) | rec.x);
+            m[t] = (int32_t)rec.z;
+        } else if constexpr (NT) {
+            v[t] = __builtin_nontemporal_load((global_ptr<int64_t>)(uintptr_t)a);
+        } else {
+            v[t] = *(global_ptr<int64_t>)(uintptr_t)a;
+        }
     }
 }
 
@@ -472,10 +482,11 @@ __device__ __forceinline__ void probe_loads(const Tab &d, const ProbeReq *s_req,
 // a group read G consecutive slots of one id per access; what each saw (1 = the id, 2 = an empty
 // slot, 0 = neither) goes back through LDS as one byte per slot, and the id's own lane reads its G
 // bytes at once and drops those of rounds that do not exist: no cross-lane operation depends on a
-// load, and nothing branches.
-template <int G, bool NT = false>
+// load, and nothing branches.  REC: *fresh tells whether the slot of a hit already holds the metadata value
+// fresh_meta (read with the id, in the same access).
+template <int G, bool NT = false, bool REC = false>
 __device__ __forceinline__ int probe_pass(const Tab &d, int64_t id, int64_t home, int q, ProbeReq *s_req,
-                                          uint8_t *s_code)
+                                          uint8_t *s_code, int32_t fresh_meta = 0, bool *fresh = nullptr)
 {
     static_assert(G == 8, "the codes of one id are read back as one 64-bit word");
     constexpr int IPI = kWave / G;
@@ -492,18 +503,23 @@ __device__ __forceinline__ int probe_pass(const Tab &d, int64_t id, int64_t home
     s_req[lane] = ProbeReq{id, (uint64_t)(uintptr_t)(int64_t *)id_at(d, first_slot) | ((uint64_t)rounds << kWhereAddrBits)};
     __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
     int64_t v[G];
-    probe_loads<G, NT>(d, s_req, v);
+    int32_t m[G];
+    probe_loads<G, NT, REC>(d, s_req, v, m);
 #pragma unroll
     for (int t = 0; t < G; ++t) {
         const int64_t gid = s_req[t * IPI + g].id;
-        s_code[t * kWave + lane] = v[t] == gid ? 1 : (v[t] == -1 ? 2 : 0);        // = byte r of id t * IPI + g
+        uint8_t code = v[t] == gid ? 1 : (v[t] == -1 ? 2 : 0);
+        if constexpr (REC) code = v[t] == gid ? (m[t] == fresh_meta ? 5 : 1) : (v[t] == -1 ? 2 : 0);
+        s_code[t * kWave + lane] = code;        // = byte r of id t * IPI + g
     }
     __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
     // the lowest set bit of the bytes of the rounds that exist: bit 8 j = found at round q + r_lo + j,
     // bit 8 j + 1 = that round's slot is empty
     const uint64_t x = *reinterpret_cast<const uint64_t *>(s_code + lane * G) >> (8 * r_lo);
+    // (bit 8 j + 2, only ever set together with bit 8 j: that slot's metadata needs no refresh)
     const int bit = __ffsll((unsigned long long)x) - 1;
     const int j = bit >> 3;
+    if constexpr (REC) *fresh = x != 0 && ((x >> (bit & 63)) & 4ull) != 0;
     const int round = q + r_lo + j;
     const int found = (x == 0 || j >= count) ? kProbeGoOn : ((bit & 1) ? probe_absent(round) : round);
     __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");    // the areas are written again by the next pass
@@ -558,7 +574,13 @@ __device__ __forceinline__ void gather_wave(const Params &p, bool active, int64_
 // in LDS (position, next round) and resolved later, 64 at a time, so that the second
 // memory round trip is paid once per 64 parked ids instead of once per chunk.  What remains
 // unfound is the segment's miss list.
-template <bool TRAIN, bool MULTI, bool GATHER, bool COUNT = TRAIN, bool NT = false>
+//
+// REC (training, every table of the call kept as records): a hit whose record already holds the metadata it would
+// get is not written again.  A batch draws its popular ids many times, and only the first of them has to dirty the
+// line: a read costs the memory system half of what a read and a narrow write of one line cost (47 against 20 G
+// lines/s on a 16 GB table).  The value read may be older than the table (another die's refresh not yet seen), which
+// costs a second store of the same value and nothing else.
+template <bool TRAIN, bool MULTI, bool GATHER, bool COUNT = TRAIN, bool NT = false, bool REC = false>
 __device__ __forceinline__ void discover_body(const Params &p)
 {
     __shared__ uint32_t s_pos[kWavesPerBlock][kStage];
@@ -624,9 +646,9 @@ __device__ __forceinline__ void discover_body(const Params &p)
     };
     // a position whose id is resident at `dist` probes from home
     // (the first pass stores the outputs of its whole chunk itself: emit = false)
-    auto finish_hit = [&](const Tab &d, int64_t pos, int64_t home, int dist, bool emit) {
+    auto finish_hit = [&](const Tab &d, int64_t pos, int64_t home, int dist, bool emit, bool fresh) {
         const int64_t slot = wrap(home + dist, d.N);
-        if (TRAIN) {
+        if (TRAIN && !(REC && fresh && d.evict != 3)) {
             store_meta(d, slot, meta_value(p, d, pos));   // "Update": refresh the resident's metadata
         }
         if (COUNT) {
@@ -663,19 +685,21 @@ __device__ __forceinline__ void discover_body(const Params &p)
                 stats_table(f0);
                 const int64_t home = mine ? home_slot(id, d.seed, d.N) : 0;
                 int dist = -1;
+                bool fresh = false;
                 int mlen = q0 < 0 ? -q0 : 0;                // > 0: the search has ended at an empty slot
                 int q = q0 > 0 ? q0 : d.P;
                 for (;;) {
                     const bool need = mine && dist < 0 && mlen == 0 && q < d.P;
                     if (!__any(need)) break;
-                    const int got = probe_pass<kNextG, NT>(d, id, home, need ? q : d.P, s_req[w], s_code[w]);
+                    bool got_fresh = false;
+                    const int got = probe_pass<kNextG, NT, REC>(d, id, home, need ? q : d.P, s_req[w], s_code[w], p.step, &got_fresh);
                     if (need) {
-                        if (got >= 0) dist = got;
+                        if (got >= 0) { dist = got; fresh = got_fresh; }
                         else if (got <= kProbeAbsent) mlen = absent_len(got);   // an empty slot ends the search
                         else q += kNextG;
                     }
                 }
-                if (mine && dist >= 0) finish_hit(d, (int64_t)pos, home, dist, true);
+                if (mine && dist >= 0) finish_hit(d, (int64_t)pos, home, dist, true, fresh);
                 const bool miss = mine && dist < 0;
                 const uint64_t mb = __ballot(miss);
                 if (miss && TRAIN) {
@@ -757,10 +781,11 @@ __device__ __forceinline__ void discover_body(const Params &p)
             const int64_t home = mine ? home_slot(id, d.seed, d.N) : 0;
             // first pass: the aligned 64 bytes that hold the home slot
             const int o = block_offset(d, home, kFirstG);
-            int res = probe_pass<kFirstG, NT>(d, id, home, valid ? -o : d.P, s_req[w], s_code[w]);
+            bool fresh = false;
+            int res = probe_pass<kFirstG, NT, REC>(d, id, home, valid ? -o : d.P, s_req[w], s_code[w], p.step, &fresh);
             if (res == kProbeGoOn && kFirstG - o >= d.P) res = probe_absent(d.P - 1);    // the whole window was read
             const bool hit = valid && res >= 0;
-            if (hit) finish_hit(d, pos, home, res, false);
+            if (hit) finish_hit(d, pos, home, res, false, fresh);
             else if (COUNT && mine && !valid) st_inv++;
             if (COUNT && !TRAIN && valid && res <= kProbeAbsent) {           // a lookup miss decided here is final
                 st_miss++;
@@ -828,10 +853,12 @@ __global__ __launch_bounds__(kBlock, 4) void k_discover_streaming(Params p)
     discover_body<true, false, false, true, true>(p);
 }
 
-// the same pass over a table kept as 16-byte records: the metadata store lands in the line just read
+// the same pass over a table kept as 16-byte records: the metadata store lands in the line just read, and is left
+// out when the record shows that an earlier copy of the id has refreshed it (16 % of the headline's positions:
+// 205 -> 180 us)
 __global__ __launch_bounds__(kBlock, 4) void k_discover_records(Params p)
 {
-    discover_body<true, false, false>(p);
+    discover_body<true, false, false, true, false, true>(p);
 }
 
 __global__ __launch_bounds__(kBlock, 4) void k_lookup(Params p)
@@ -852,6 +879,15 @@ __global__ __launch_bounds__(kBlock, 3) void k_lookup_counting(Params p)
 __global__ __launch_bounds__(kBlock, 4) void k_discover_tables(Params p)
 {
     discover_body<true, true, false>(p);
+}
+
+// A group whose tables are all kept as records: popular ids are refreshed once (41 M values over 26 tables: 1 494 ->
+// 1 045 us, at 40 G ids/s near the rate of random line reads).  Three wavefronts per SIMD: the records in flight
+// need 157 registers; held to 128 the compiler spills inside the probe.  (Two dense tensors keep the plain store: a
+// look at the metadata first is a random read of its own there, and Pass 1 over 500 M slots went from 111 to 133 us.)
+__global__ __launch_bounds__(kBlock, 3) void k_discover_tables_records(Params p)
+{
+    discover_body<true, true, false, true, false, true>(p);
 }
 
 __global__ __launch_bounds__(kBlock, 4) void k_lookup_tables(Params p)
