@@ -108,7 +108,7 @@ def mpzch_status_string(status: int) -> str:
 
 
 def _check(status: int, what: str):
-    if status != 0:
+    if status:
         raise MpzchError(status, what)
 
 
@@ -120,11 +120,13 @@ def _ptr(t, dtype=None):
     assert t.is_cuda and (t.is_contiguous() or (t.dim() == 1 and t.stride(0) in (2, 4))), "device, dense tensors only"
     if dtype is not None:
         assert t.dtype == dtype, (t.dtype, dtype)
-    return ctypes.c_void_p(t.data_ptr())
+    return t.data_ptr()
 
 
 def _stream():
-    return ctypes.c_void_p(torch.cuda.current_stream().cuda_stream)
+    """Torch's current stream on the current device, as an address.  (torch.cuda.current_stream() builds a Stream
+    object around the same number: 2.8 us of the 8 us that a small lookup spends on the host, against 0.2.)"""
+    return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
 
 
 # ----------------------------------------------------------------------------- C-ABI names
@@ -188,9 +190,9 @@ def mpzch_remap_reset(handle, identities, metadata, ids, step: int, out_slots, o
     _check(load_library().mpzch_remap_reset(handle, _ptr(identities, torch.int64), _ptr(metadata, torch.int32),
                                             _ptr(ids, torch.int64), n, step, _ptr(out_slots, torch.int64),
                                             _ptr(out_evicted_slots, torch.int64), cap, _ptr(out_num_evicted, torch.int64),
-                                            _ptr(out_stats, torch.int64), ctypes.c_void_p(rows.data_ptr()), nrows,
+                                            _ptr(out_stats, torch.int64), rows.data_ptr(), nrows,
                                             row_bytes, stride,
-                                            None if init_row is None else ctypes.c_void_p(init_row.data_ptr()),
+                                            None if init_row is None else init_row.data_ptr(),
                                             _stream()), "mpzch_remap_reset")
 
 
@@ -238,8 +240,8 @@ def mpzch_reset_rows(slots, num_slots_dev, rows, init_row=None, num_rows: int | 
     if init_row is not None:
         assert init_row.is_cuda and init_row.is_contiguous() and init_row.numel() * init_row.element_size() == row_bytes
     _check(load_library().mpzch_reset_rows(_ptr(slots, torch.int64), _ptr(num_slots_dev, torch.int64), slots.numel(),
-                                           ctypes.c_void_p(rows.data_ptr()), nrows, row_bytes, stride,
-                                           None if init_row is None else ctypes.c_void_p(init_row.data_ptr()),
+                                           rows.data_ptr(), nrows, row_bytes, stride,
+                                           None if init_row is None else init_row.data_ptr(),
                                            _stream()), "mpzch_reset_rows")
 
 
@@ -263,8 +265,8 @@ def mpzch_lookup_gather(handle, identities, ids, rows, out_rows, out_slots=None,
     n, rb, st = _row_geometry(rows)
     assert out_rows.is_contiguous() and out_rows.numel() * out_rows.element_size() == ids.numel() * rb
     _check(load_library().mpzch_lookup_gather(handle, _ptr(identities, torch.int64), _ptr(ids, torch.int64), ids.numel(),
-                                              ctypes.c_void_p(rows.data_ptr()), n, rb, st,
-                                              ctypes.c_void_p(out_rows.data_ptr()), _ptr(out_slots, torch.int64),
+                                              rows.data_ptr(), n, rb, st,
+                                              out_rows.data_ptr(), _ptr(out_slots, torch.int64),
                                               _ptr(out_found, torch.uint8), _stream()), "mpzch_lookup_gather")
 
 
@@ -279,14 +281,14 @@ def mpzch_gather_rows(slots, count_dev, rows, out_rows):
     n, rb, st = _row_geometry(rows)
     assert out_rows.is_contiguous()
     _check(load_library().mpzch_gather_rows(_ptr(slots, torch.int64), _ptr(count_dev, torch.int64), slots.numel(),
-                                            ctypes.c_void_p(rows.data_ptr()), n, rb, st,
-                                            ctypes.c_void_p(out_rows.data_ptr()), _stream()), "mpzch_gather_rows")
+                                            rows.data_ptr(), n, rb, st,
+                                            out_rows.data_ptr(), _stream()), "mpzch_gather_rows")
 
 
 def mpzch_apply_delta(identities, slots, ids, count_dev, rows=None, delta_rows=None):
     if rows is not None:
         n, rb, st = _row_geometry(rows)
-        rp, dp = ctypes.c_void_p(rows.data_ptr()), ctypes.c_void_p(delta_rows.data_ptr())
+        rp, dp = rows.data_ptr(), delta_rows.data_ptr()
     else:
         n, rb, st, rp, dp = 0, 0, 0, None, None
     _check(load_library().mpzch_apply_delta(_ptr(identities, torch.int64), identities.numel(), _ptr(slots, torch.int64),
