@@ -283,8 +283,7 @@ mpzch_status_t launch_discover(const Params &p, int grid, hipStream_t s)
     return MPZCH_OK;
 }
 
-// max_p: largest min(max_probe, num_slots) of the tables involved; max_p_lru: the same over the LRU
-// tables, 0 when there is none
+// max_p_lru: largest min(max_probe, num_slots) of the LRU tables involved, 0 when there is none
 template <bool MULTI>
 void launch_allocate_lru(int32_t max_p_lru, const Params &p, int grid, hipStream_t s)
 {
@@ -297,23 +296,22 @@ void launch_allocate_lru(int32_t max_p_lru, const Params &p, int grid, hipStream
     else hipLaunchKernelGGL((k_allocate_lru<64, MULTI>), dim3(grid), dim3(kWave), 0, s, p);
 }
 
-mpzch_status_t launch_allocate(int32_t max_p, int32_t max_p_lru, const Params &p, int num_cus, hipStream_t s)
+mpzch_status_t launch_allocate(int32_t max_p_lru, const Params &p, int num_cus, hipStream_t s)
 {
-    // one wavefront per workgroup, one segment per workgroup pass; the lane phase covers the first
-    // 8 or 16 slots of every window, longer windows continue in the wave phase
+    // one wavefront per workgroup, one segment per workgroup pass
     const int grid = grid_for((int64_t)p.num_segs, 1, num_cus, 4 * group_blocks_per_cu());
     if (p.num_tables > 1) {
         // several tables: TTL / no-eviction claimants first (this also writes every hint), then
         // the claimants of LRU tables
-        if (max_p <= 8) hipLaunchKernelGGL((k_allocate<8, true>), dim3(grid), dim3(kWave), 0, s, p);
-        else hipLaunchKernelGGL((k_allocate<16, true>), dim3(grid), dim3(kWave), 0, s, p);
+        if (p.all_records) hipLaunchKernelGGL((k_allocate<true, true>), dim3(grid), dim3(kWave), 0, s, p);
+        else hipLaunchKernelGGL((k_allocate<true, false>), dim3(grid), dim3(kWave), 0, s, p);
         LAUNCH_CHECK();
         if (max_p_lru > 0) launch_allocate_lru<true>(max_p_lru, p, grid, s);
     } else if (max_p_lru > 0) {
         launch_allocate_lru<false>(max_p_lru, p, grid, s);
     } else {
-        if (max_p <= 8) hipLaunchKernelGGL((k_allocate<8, false>), dim3(grid), dim3(kWave), 0, s, p);
-        else hipLaunchKernelGGL((k_allocate<16, false>), dim3(grid), dim3(kWave), 0, s, p);
+        if (p.t0.sh) hipLaunchKernelGGL((k_allocate<false, true>), dim3(grid), dim3(kWave), 0, s, p);
+        else hipLaunchKernelGGL((k_allocate<false, false>), dim3(grid), dim3(kWave), 0, s, p);
     }
     LAUNCH_CHECK();
     return MPZCH_OK;
@@ -321,7 +319,8 @@ mpzch_status_t launch_allocate(int32_t max_p, int32_t max_p_lru, const Params &p
 
 mpzch_status_t launch_finalize(const Params &p, int grid, hipStream_t s)
 {
-    hipLaunchKernelGGL(k_finalize, dim3(grid), dim3(kBlock), 0, s, p);
+    if (p.num_tables > 1) hipLaunchKernelGGL((k_finalize<true>), dim3(grid), dim3(kBlock), 0, s, p);
+    else hipLaunchKernelGGL((k_finalize<false>), dim3(grid), dim3(kBlock), 0, s, p);
     LAUNCH_CHECK();
     return MPZCH_OK;
 }
@@ -342,23 +341,23 @@ mpzch_status_t fill64(int64_t *dst, int64_t count, long long value, hipStream_t 
 mpzch_status_t fill32(int32_t *dst, int64_t count, int32_t value, hipStream_t s);
 
 // The launch sequence of one training remap (single table or group).
-mpzch_status_t launch_remap(Scratch &sc, Timing &tm, Params p, int32_t max_p, int32_t max_p_lru, hipStream_t s);
+mpzch_status_t launch_remap(Scratch &sc, Timing &tm, Params p, int32_t max_p_lru, hipStream_t s);
 
 // Every call leaves the scratch set empty and the counter block zeroed -- unless its launch
 // sequence was cut short by a HIP error; the next call then clears both before it starts.
-mpzch_status_t run_remap(Scratch &sc, Timing &tm, const Params &p, int32_t max_p, int32_t max_p_lru, hipStream_t s)
+mpzch_status_t run_remap(Scratch &sc, Timing &tm, const Params &p, int32_t max_p_lru, hipStream_t s)
 {
     if (sc.dirty) {
         TRY(fill32((int32_t *)sc.set_slot, 2 * sc.cap_n, -1, s));
         TRY(fill64((int64_t *)sc.ctl, (int64_t)(sizeof(Control) / sizeof(int64_t)), 0, s));
     }
     sc.dirty = true;
-    const mpzch_status_t st = launch_remap(sc, tm, p, max_p, max_p_lru, s);
+    const mpzch_status_t st = launch_remap(sc, tm, p, max_p_lru, s);
     if (st == MPZCH_OK) sc.dirty = false;
     return st;
 }
 
-mpzch_status_t launch_remap(Scratch &sc, Timing &tm, Params p, int32_t max_p, int32_t max_p_lru, hipStream_t s)
+mpzch_status_t launch_remap(Scratch &sc, Timing &tm, Params p, int32_t max_p_lru, hipStream_t s)
 {
     p.list = sc.list;
     p.ent = sc.ent;
@@ -378,7 +377,7 @@ mpzch_status_t launch_remap(Scratch &sc, Timing &tm, Params p, int32_t max_p, in
     const int g_grp = grid_for((int64_t)p.num_segs, kWavesPerBlock, sc.num_cus, group_blocks_per_cu());
 
     TIMED(tm, KDiscover, s, (launch_discover<true>(p, g_disc, s)));
-    TIMED(tm, KAllocate, s, launch_allocate(max_p, max_p_lru, p, sc.num_cus, s));
+    TIMED(tm, KAllocate, s, launch_allocate(max_p_lru, p, sc.num_cus, s));
     TIMED(tm, KFinalize, s, launch_finalize(p, g_grp, s));
     return MPZCH_OK;
 }
@@ -657,7 +656,7 @@ mpzch_status_t remap_one(mpzch_table_t *t, int64_t *identities, int32_t *metadat
         for (int b = 0; b < 31; ++b)
             if (g.chunks == ((int64_t)1 << b)) p.g_shift = b;
     }
-    return run_remap(t->sc, t->tm, p, p.t0.P, p.t0.evict == 2 ? p.t0.P : 0, s);
+    return run_remap(t->sc, t->tm, p, p.t0.evict == 2 ? p.t0.P : 0, s);
 }
 }  // namespace
 
@@ -732,7 +731,7 @@ mpzch_status_t mpzch_remap_noalloc(const mpzch_table_t *t, int64_t *identities, 
     p.out_num_evicted = out_num_evicted;
     p.out_stats = out_stats;
     Timing off;                                  // never enabled: records nothing, creates no event
-    return run_remap(*sc, off, p, p.t0.P, p.t0.evict == 2 ? p.t0.P : 0, s);
+    return run_remap(*sc, off, p, p.t0.evict == 2 ? p.t0.P : 0, s);
 }
 
 mpzch_status_t mpzch_lookup(const mpzch_table_t *t, const int64_t *identities,
@@ -1025,7 +1024,7 @@ mpzch_status_t mpzch_remap_jagged_feature_ttl(mpzch_group_t *g, int64_t *const *
         for (int f = 0; f < T; ++f) any = any || g->cfgs[f].kind == MPZCH_EVICT_TTL_EXPIRY;
         if (!any) return MPZCH_ERR_INVALID_ARG;          // no table of the group uses retention times
     }
-    int32_t max_p = 1, max_p_lru = 0;
+    int32_t max_p_lru = 0;
     bool all_records = true;
     std::vector<TableDesc> descs((size_t)T);
     for (int f = 0; f < T; ++f) {
@@ -1036,7 +1035,6 @@ mpzch_status_t mpzch_remap_jagged_feature_ttl(mpzch_group_t *g, int64_t *const *
         if (cap > 0 && !out_evicted_slots) return MPZCH_ERR_INVALID_ARG;
         descs[f] = make_desc(g->cfgs[f], identities[f], metadata[f], evicted_offsets[f], cap);
         all_records = all_records && descs[f].sh == 1;
-        if (descs[f].P > max_p) max_p = descs[f].P;
         if (descs[f].evict == 2 && descs[f].P > max_p_lru) max_p_lru = descs[f].P;
     }
     hipStream_t s = (hipStream_t)stream;
@@ -1064,7 +1062,7 @@ mpzch_status_t mpzch_remap_jagged_feature_ttl(mpzch_group_t *g, int64_t *const *
     p.out_stats = out_stats;
     // a group of one table still goes through the descriptor path
     if (T == 1) p.num_tables = 1;
-    return run_remap(g->sc, g->tm, p, max_p, max_p_lru, s);
+    return run_remap(g->sc, g->tm, p, max_p_lru, s);
 }
 
 mpzch_status_t mpzch_remap_jagged(mpzch_group_t *g, int64_t *const *identities, int32_t *const *metadata,

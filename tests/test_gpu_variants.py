@@ -45,3 +45,68 @@ def test_groups_of_records_refreshed_once(records):
             jp.step(vals, offsets, step, tt)
     jp.check_state()
     jp.close()
+
+
+# ---- ids with a chosen home slot: the hash is a bijection, so it can be run backwards
+def ids_at(homes, num_slots, seed, rng):
+    """One valid id per entry of `homes` (int64), hashing to that home slot."""
+    homes = np.asarray(homes)
+    out = np.empty(homes.size, dtype=np.int64)
+    todo = np.arange(homes.size)
+    u = np.uint64
+    with np.errstate(over="ignore"):
+        while todo.size:
+            # a random hash value whose high product with num_slots is the home: home * 2^64 / N + a bit less than 2^64 / N
+            width = (1 << 64) // num_slots
+            h = np.array([-(-(int(x) << 64) // num_slots) for x in homes[todo]], dtype=np.uint64)
+            h = h + rng.integers(0, max(1, width - 2), size=todo.size, dtype=np.uint64)
+
+            def unshift(z, s):
+                r = z
+                for _ in range(64 // s + 1):
+                    r = z ^ (r >> u(s))
+                return r
+            z = unshift(h, 31) * u(pow(0x94D049BB133111EB, -1, 1 << 64))
+            z = unshift(z, 27) * u(pow(0xBF58476D1CE4E5B9, -1, 1 << 64))
+            z = unshift(z, 30) - u(0x9E3779B97F4A7C15)
+            ids = (z ^ u(seed)).astype(np.int64)
+            ok = ids >= 0
+            out[todo[ok]] = ids[ok]
+            todo = todo[~ok]
+    return out
+
+
+def test_ids_at_gives_the_home_asked_for():
+    rng = rng_for(903)
+    for n_slots in (7, 5_000, 34_000_001):
+        homes = rng.integers(0, n_slots, size=200)
+        ids = ids_at(homes, n_slots, 99, rng)
+        t = Pair(n_slots, 1, 0, True, 99)
+        so, fo = t.lookup(ids)                    # an empty table: every lookup returns the home
+        assert np.array_equal(so, homes) and not fo.any()
+        t.close()
+
+
+# ---- windows of every length over crowded stretches of the table: shared-out blocks of the later passes, displaced
+# claimants, windows that run over the end of the table; blocks aligned (tables beyond 256 MB) or not
+@pytest.mark.parametrize("layout", ["separate", "records"])
+@pytest.mark.parametrize("slots,probe", [(5, 8), (8, 8), (1_000, 9), (4_099, 17), (4_099, 40), (4_099, 65), (4_099, 300),
+                                         (34_000_001, 16), (34_000_001, 33), (34_000_001, 130)])
+@pytest.mark.parametrize("evict", [True, "expiry", False])
+def test_crowded_windows(slots, probe, layout, evict):
+    rng = rng_for(904 + slots + probe)
+    t = Pair(slots, probe, 1, evict, 5, layout=layout)
+    span = min(slots, 700)
+    for step, n in [(0, 64), (1, span // 2 + 1), (2, span), (4, span), (5, 3 * span), (7, 9)]:
+        # homes within `span` slots around the end of the table, a third of them on a handful of slots
+        at = slots - span // 2 + rng.integers(0, span, size=n)
+        hot = slots - 3 + rng.integers(0, 5, size=n)
+        homes = np.where(rng.random(n) < 0.33, hot, at) % slots
+        ids = ids_at(homes, slots, 5, rng)
+        if n > 20:
+            ids[rng.integers(0, n, size=n // 5)] = ids[rng.integers(0, n, size=n // 5)]      # copies
+        t.step(ids, step, check_state=slots < 10_000_000)
+        t.lookup(ids)
+        t.step(ids[: n // 2 + 1], step, check_state=slots < 10_000_000)
+    t.check_state()
+    t.close()
