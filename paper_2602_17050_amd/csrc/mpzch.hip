@@ -2,7 +2,7 @@
 // kernel launches on the caller's stream.  No call here synchronises with the host except
 // where the header says so (scratch growth, descriptor upload, timing read-out, destroy).
 #include "../../include/mpzch.h"
-#include "mpzch_kernels.hpp"
+#include "mpzch_chunk_kernels.hpp"
 
 #include <cstdlib>
 #include <cstring>
@@ -101,8 +101,9 @@ struct Timing {
 // ---- device scratch -----------------------------------------------------------------------
 // Grid caps in workgroups per compute unit.  8 is the measured best for Pass 1 (4 and 16 are within a few
 // per cent) and for the kernels that walk the miss lists; scratch is sized for up to kDiscoverBlocksPerCuMax.
-const int kDiscoverBlocksPerCuMax = 16;
+constexpr int kDiscoverBlocksPerCuMax = 16;
 constexpr int discover_blocks_per_cu() { return 8; }
+static_assert(3 * sizeof(uint64_t) * discover_blocks_per_cu() <= sizeof(uint32_t) * kDiscoverBlocksPerCuMax * kWavesPerBlock, "the counter words of the workgroups of a one-chunk call fit seg_cnt");
 constexpr int group_blocks_per_cu() { return 8; }
 
 // Compute units of the current device, asked once per device and process (no handle state: read-only
@@ -357,6 +358,25 @@ mpzch_status_t run_remap(Scratch &sc, Timing &tm, const Params &p, int32_t max_p
     return st;
 }
 
+// One chunk per wavefront (mpzch_chunk_kernels.hpp): grid = workgroups of 256 positions.
+mpzch_status_t launch_remap_chunks(Timing &tm, const Params &p, int grid, hipStream_t s)
+{
+    const bool rec = p.t0.sh != 0;
+    if (!tm.begin(KDiscover, s)) return MPZCH_ERR_HIP;
+    if (rec) hipLaunchKernelGGL((k_discover_chunk<true>), dim3(grid), dim3(kBlock), 0, s, p);
+    else hipLaunchKernelGGL((k_discover_chunk<false>), dim3(grid), dim3(kBlock), 0, s, p);
+    LAUNCH_CHECK();
+    if (!tm.end(s) || !tm.begin(KAllocate, s)) return MPZCH_ERR_HIP;
+    if (rec) hipLaunchKernelGGL((k_allocate_chunk<true>), dim3(grid), dim3(kBlock), 0, s, p);
+    else hipLaunchKernelGGL((k_allocate_chunk<false>), dim3(grid), dim3(kBlock), 0, s, p);
+    LAUNCH_CHECK();
+    if (!tm.end(s) || !tm.begin(KFinalize, s)) return MPZCH_ERR_HIP;
+    hipLaunchKernelGGL(k_finalize_chunk, dim3(grid), dim3(kBlock), 0, s, p);
+    LAUNCH_CHECK();
+    if (!tm.end(s)) return MPZCH_ERR_HIP;
+    return MPZCH_OK;
+}
+
 mpzch_status_t launch_remap(Scratch &sc, Timing &tm, Params p, int32_t max_p_lru, hipStream_t s)
 {
     p.list = sc.list;
@@ -367,6 +387,14 @@ mpzch_status_t launch_remap(Scratch &sc, Timing &tm, Params p, int32_t max_p_lru
     p.seg_cnt = sc.seg_cnt;
     p.set_slot = sc.set_slot;
     p.ctl = sc.ctl;
+
+    p.place = sc.first_of;
+    p.wg_words = (uint64_t *)sc.seg_cnt;
+
+    // one table, and no wavefront of Pass 1 has more than one chunk
+    const int64_t groups = (p.n + kBlock - 1) / kBlock;
+    if (p.num_tables == 1 && max_p_lru == 0 && groups <= (int64_t)sc.num_cus * discover_blocks_per_cu())
+        return launch_remap_chunks(tm, p, (int)groups, s);
 
     const int64_t num_chunks = (p.n + kWave - 1) / kWave;
     // k_discover: every wavefront owns one segment of seg_chunks 64-position chunks

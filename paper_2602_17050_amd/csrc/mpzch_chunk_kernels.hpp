@@ -1,0 +1,304 @@
+// The training remap of batches that give every wavefront at most one chunk of 64 positions (one table; up to
+// about half a million positions on 256 compute units).
+//
+// Such a call is bound by latency: every kernel is a chain of dependent round trips to memory (0.6 to 1 us each),
+// and the kernels wait for each other.  The kernels of mpzch_kernels.hpp compact the missed positions into lists, add
+// their counters to shared words and let the workgroup that finishes last publish them; none of that pays here.
+// In these kernels lane L of wavefront W works on position 64 W + L in all three phases, what one phase leaves for the
+// next is stored by position, and counters are stored per workgroup and summed by the last kernel: no shared
+// counter, no arrival word, no list.
+//   k_discover_chunk   Pass 1; the whole window of every id is looked at in registers (nothing is parked); missed
+//                      ids enter the scratch set.
+//   k_allocate_chunk   claims.  The first block of every window is requested together with the election of the
+//                      first occurrence.  A slot that is claimed for the first time is an insert or an eviction
+//                      whatever displacements follow, so the outcome is counted here, and the evicted slots are left for
+//                      the last kernel, per workgroup.  Where a claimant ends up is kept in place[position]: rounds only
+//                      grow while a claimant is displaced, so an atomic maximum makes the word final when the
+//                      kernel ends, and the last kernel need not look at the table at all.
+//   k_finalize_chunk   ids and metadata of the placed claimants, outputs, evicted list (its place in the list
+//                      comes from the counts of the workgroups before), row reset, counters.
+#pragma once
+#include "mpzch_kernels.hpp"
+
+namespace mpzch {
+
+constexpr uint32_t kNoEntry = 0xFFFFFFFFu;       // ent[pos]: the position did not miss
+constexpr uint32_t kPlaceNone = 0xFFFFFFFFu;     // place[pos]: displaced and out of slots.  0: never placed.  Else round + 1.
+
+// Sum over the wavefront of 32-bit values whose total fits 32 bits, in every lane.
+__device__ __forceinline__ uint32_t wave_sum32(uint32_t x)
+{
+    x += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x111, 0xF, 0xF, false);      // row_shr:1
+    x += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x112, 0xF, 0xF, false);      // row_shr:2
+    x += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x114, 0xF, 0xF, false);      // row_shr:4
+    x += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x118, 0xF, 0xF, false);      // row_shr:8
+    x += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x142, 0xA, 0xF, false);      // row_bcast:15
+    x += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x143, 0xC, 0xF, false);      // row_bcast:31
+    return (uint32_t)__builtin_amdgcn_readlane((int)x, kWave - 1);
+}
+
+// counters of one workgroup, three words: positions (hit, miss, invalid), probe lengths (hits, misses), outcomes
+// (distinct ids, inserts, evictions)
+__device__ __forceinline__ uint64_t pack3(uint32_t a, uint32_t b, uint32_t c)
+{
+    return (uint64_t)a | ((uint64_t)b << 16) | ((uint64_t)c << 32);
+}
+__device__ __forceinline__ uint32_t unpack3(uint64_t w, int k) { return (uint32_t)(w >> (16 * k)) & 0xFFFFu; }
+
+template <bool REC>
+__global__ __launch_bounds__(kBlock, 4) void k_discover_chunk(Params p)
+{
+    __shared__ ProbeReq s_req[kWavesPerBlock][kWave];
+    __shared__ __attribute__((aligned(16))) uint8_t s_code[kWavesPerBlock][kWave * kFirstG];
+    __shared__ uint32_t s_red[kWavesPerBlock][5];
+
+    const int lane = lane_id(), w = threadIdx.x / kWave;
+    const int64_t pos = (int64_t)blockIdx.x * kBlock + threadIdx.x;
+    const bool in = pos < p.n;
+    const Tab d = view(p.t0);
+    const int64_t id = in ? p.ids[pos] : -1;
+    const bool valid = in && id >= 0;
+    const int64_t home = home_slot(id, d.seed, d.N);
+    // first block: the aligned one, or in a table that the caches hold the 8 slots from the home slot on (k_allocate)
+    const int o = (d.N << (3 + d.sh)) > kCachedTableBytes ? block_offset(d, home, kFirstG) : 0;
+    bool fresh = false;
+    int res = probe_pass<kFirstG, false, REC>(d, id, home, valid ? -o : d.P, s_req[w], s_code[w], p.step, &fresh);
+    int q = kFirstG - o;
+    for (;;) {
+        const bool need = valid && res == kProbeGoOn && q < d.P;
+        if (!__any(need)) break;
+        bool f = false;
+        const int got = probe_more<false, REC>(d, id, home, q, need, s_req[w], s_code[w], p.step, &f);
+        if (need) { res = got; fresh = f; }
+    }
+    const bool hit = valid && res >= 0, miss = valid && res < 0;
+    uint32_t e = kNoEntry;
+    if (miss) e = set_insert(p, id, (uint32_t)pos, 0, 2ull * (uint64_t)p.n);
+    const int64_t slot = hit ? wrap(home + res, d.N) : home;
+    if (hit && !(REC && fresh && d.evict != 3)) store_meta(d, slot, meta_value(p, d, pos));
+    if (in) {
+        p.out_slots[pos] = slot;
+        p.ent[pos] = e;
+        p.place[pos] = 0;
+    }
+    if (p.out_stats) {
+        const uint32_t hits = (uint32_t)__popcll(__ballot(hit)), misses = (uint32_t)__popcll(__ballot(miss));
+        const uint32_t invalid = (uint32_t)__popcll(__ballot(in && !valid));
+        const uint32_t hit_len = wave_sum32(hit ? (uint32_t)res + 1u : 0u);
+        const uint32_t miss_len = wave_sum32(miss ? (uint32_t)(res <= kProbeAbsent ? absent_len(res) : d.P) : 0u);
+        if (lane == 0) {
+            s_red[w][0] = hits;
+            s_red[w][1] = misses;
+            s_red[w][2] = invalid;
+            s_red[w][3] = hit_len;
+            s_red[w][4] = miss_len;
+        }
+        __syncthreads();
+        if (threadIdx.x == 0) {
+            uint32_t t[5] = {0, 0, 0, 0, 0};
+            for (int i = 0; i < kWavesPerBlock; ++i)
+                for (int k = 0; k < 5; ++k) t[k] += s_red[i][k];
+            p.wg_words[3 * blockIdx.x] = pack3(t[0], t[1], t[2]);
+            p.wg_words[3 * blockIdx.x + 1] = (uint64_t)t[3] | ((uint64_t)t[4] << 32);
+        }
+    }
+}
+
+// What the lanes of a workgroup leave for k_finalize_chunk: which evicted which slot (evicted: lanes with a slot in
+// `slot`), and the workgroup's outcome counts.  Reached by all threads.
+__device__ __forceinline__ void leave_outcomes(const Params &p, bool agent, bool inserted, bool evicted, int64_t slot,
+                                               uint32_t (*s_red)[3])
+{
+    const int lane = lane_id(), w = threadIdx.x / kWave;
+    const uint64_t em = __ballot(evicted);
+    const uint32_t agents = (uint32_t)__popcll(__ballot(agent)), ins = (uint32_t)__popcll(__ballot(inserted));
+    if (lane == 0) {
+        s_red[w][0] = agents;
+        s_red[w][1] = ins;
+        s_red[w][2] = (uint32_t)__popcll(em);
+    }
+    __syncthreads();
+    uint32_t before = 0;
+    for (int i = 0; i < w; ++i) before += s_red[i][2];
+    if (evicted) p.homes[(int64_t)blockIdx.x * kBlock + before + __popcll(em & ((1ull << lane) - 1ull))] = slot;
+    if (threadIdx.x == 0) {
+        uint32_t t[3] = {0, 0, 0};
+        for (int i = 0; i < kWavesPerBlock; ++i)
+            for (int k = 0; k < 3; ++k) t[k] += s_red[i][k];
+        p.wg_words[3 * blockIdx.x + 2] = pack3(t[0], t[1], t[2]);
+    }
+}
+
+__device__ __forceinline__ void note_place(const Params &p, uint32_t pos, uint32_t place)
+{
+    __hip_atomic_fetch_max(&p.place[pos], place, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
+template <bool REC>
+__global__ __launch_bounds__(kBlock, 4) void k_allocate_chunk(Params p)
+{
+    __shared__ __attribute__((aligned(16))) uint8_t s_code[kWavesPerBlock][kWave * kAllocG];
+    __shared__ ClaimReq s_req[kWavesPerBlock][kWave];
+    __shared__ uint32_t s_red[kWavesPerBlock][3];
+
+    const int w = threadIdx.x / kWave;
+    const int64_t pos = (int64_t)blockIdx.x * kBlock + threadIdx.x;
+    const bool in = pos < p.n;
+    const Tab d = view(p.t0);
+    const uint32_t e = in ? p.ent[pos] : kNoEntry;
+    const int64_t id = in ? p.ids[pos] : -1;
+    const bool have = e != kNoEntry;
+    uint32_t first = 0;
+    if (have) first = p.set_slot[e];
+
+    Claimant c;
+    c.active = have;                                 // the first blocks are requested before the election is known
+    c.pos = (uint32_t)pos;
+    c.home = home_slot(id, d.seed, d.N);
+    c.q = 0;
+    const int32_t bound = expiry_bound(d, p.step);
+    const bool aligned = (d.N << (3 + d.sh)) > kCachedTableBytes;
+    bool agent = false, inserted = false, evicted = false;
+    int64_t slot = 0;
+    for (bool later = false;; later = true) {
+        const uint64_t am = __ballot(c.active);
+        if (!am) break;
+        const int m = later ? blocks_shift(__popcll(am), d.P) : 0;
+        const int row = claim_blocks<false, REC>(d, d, c, am, m, bound, aligned, s_code[w], s_req[w]);
+        if (!later) {
+            agent = have && first == (uint32_t)pos;  // else: a later copy of the id
+            c.active = agent;
+            if (have) p.list[pos] = first;
+        }
+        bool moved = false;
+        if (c.active) {
+            int64_t old;
+            const int64_t at = claim_walk(d, c, m, row, s_code[w], s_req[w], old);
+            if (at >= 0) {
+                note_place(p, c.pos, (uint32_t)c.q + 1u);
+                c.active = false;
+                inserted = old == -1;
+                evicted = old >= 0;
+                slot = at;
+                if (is_tag(old)) {
+                    // the displaced claimant goes on from its next round (same table: same slot)
+                    c.pos = tag_pos(old);
+                    c.q = (int32_t)tag_round(old) + 1;
+                    c.active = moved = c.q < d.P;
+                    if (!moved) note_place(p, c.pos, kPlaceNone);
+                }
+            } else if (c.q >= d.P) {                 // window exhausted: falls back at finalize
+                c.active = false;
+                if (c.pos != (uint32_t)pos) note_place(p, c.pos, kPlaceNone);
+            }
+        }
+        if (moved) c.home = home_slot(p.ids[c.pos], d.seed, d.N);
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");   // s_code and s_req are written again
+    }
+    leave_outcomes(p, agent, inserted, evicted, slot, s_red);
+}
+
+// Sum over the workgroup, in every thread.  s_sum: one word per wavefront; to be reached by all threads.
+__device__ __forceinline__ unsigned long long block_sum(unsigned long long x, unsigned long long *s_sum)
+{
+    const unsigned long long t = wave_sum(x);
+    __syncthreads();                                 // s_sum may still be read from an earlier sum
+    if (lane_id() == 0) s_sum[threadIdx.x / kWave] = t;
+    __syncthreads();
+    unsigned long long v = 0;
+    for (int i = 0; i < kWavesPerBlock; ++i) v += s_sum[i];
+    return v;
+}
+
+// The call's counters, from the words of all workgroups: three tasks, taken by the first workgroups.
+__device__ __forceinline__ void publish_words(const Params &p, int task, unsigned long long *s_sum)
+{
+    if (task < 2 && !p.out_stats) return;
+    unsigned long long a = 0, b = 0, c = 0;
+    for (int i = threadIdx.x; i < (int)gridDim.x; i += kBlock) {
+        const uint64_t v = p.wg_words[3 * i + task];
+        if (task == 1) {
+            a += (uint32_t)v;
+            b += v >> 32;
+        } else {
+            a += unpack3(v, 0);
+            b += unpack3(v, 1);
+            c += unpack3(v, 2);
+        }
+    }
+    a = block_sum(a, s_sum);
+    b = block_sum(b, s_sum);
+    c = block_sum(c, s_sum);
+    if (threadIdx.x != 0) return;
+    if (task == 0) {
+        p.out_stats[kHitPos] = (int64_t)a;
+        p.out_stats[kMissPos] = (int64_t)b;
+        p.out_stats[kInvalidPos] = (int64_t)c;
+    } else if (task == 1) {
+        p.out_stats[kHitProbeSum] = (int64_t)a;
+        p.out_stats[kMissProbeSum] = (int64_t)b;
+    } else {
+        p.out_num_evicted[0] = (int64_t)c;
+        if (p.out_stats) {
+            p.out_stats[kDistinctMiss] = (int64_t)a;
+            p.out_stats[kInserts] = (int64_t)b;
+            p.out_stats[kEvictions] = (int64_t)c;
+            p.out_stats[kCollisions] = (int64_t)(a - b - c);
+        }
+    }
+}
+
+__global__ __launch_bounds__(kBlock, 8) void k_finalize_chunk(Params p)
+{
+    __shared__ int64_t s_row[kBlock];
+    __shared__ unsigned long long s_sum[kWavesPerBlock];
+
+    const int64_t pos = (int64_t)blockIdx.x * kBlock + threadIdx.x;
+    const bool in = pos < p.n;
+    const Tab d = view(p.t0);
+    const uint32_t e = in ? p.ent[pos] : kNoEntry;
+    const int64_t id = in ? p.ids[pos] : -1;
+    uint32_t first = 0, place = 0;
+    if (in) {
+        first = p.list[pos];                         // (left over from an earlier call where the position did not miss)
+        place = p.place[pos];
+    }
+    const int evicted = (int)unpack3(p.wg_words[3 * blockIdx.x + 2], 2);
+    const bool have = e != kNoEntry;
+    if (have) {
+        const bool agent = first == (uint32_t)pos;
+        if (!agent) place = p.place[first];
+        p.set_slot[e] = kSetEmpty;                   // the scratch set is left empty again
+        const bool placed = place != 0 && place != kPlaceNone;
+        const int64_t home = home_slot(id, d.seed, d.N);
+        const int64_t slot = placed ? wrap(home + (int64_t)(place - 1u), d.N) : home;
+        // the claim becomes the id, metadata gets its value (Algorithm 1, Pass 2); without a claim: Case 3, the home
+        // slot's metadata is refreshed; with per-feature retention a later copy may ask for a later expiry step
+        if (agent && placed) *id_at(d, slot) = id;
+        if (agent || (p.ttls && d.evict == 3)) store_meta(d, slot, meta_value(p, d, pos));
+        p.out_slots[pos] = slot;
+    }
+    if (evicted > 0) {
+        // where this workgroup's part of the list begins: the evictions of the workgroups before
+        unsigned long long base = 0;
+        for (int i = threadIdx.x; i < (int)blockIdx.x; i += kBlock) base += unpack3(p.wg_words[3 * i + 2], 2);
+        base = block_sum(base, s_sum);
+        if ((int)threadIdx.x < evicted) {
+            const int64_t s = p.homes[(int64_t)blockIdx.x * kBlock + threadIdx.x];
+            const int64_t at = (int64_t)base + threadIdx.x;
+            if (at < p.t0.ev_cap) p.out_evicted[at] = s;
+            if (p.r_rows) s_row[threadIdx.x] = s >= p.g_num_rows ? s % p.g_num_rows : s;
+        }
+        if (p.r_rows) {
+            __syncthreads();
+            // every wavefront resets a quarter of the rows
+            const int per = (evicted + kWavesPerBlock - 1) / kWavesPerBlock, w = threadIdx.x / kWave;
+            const int lo = w * per < evicted ? w * per : evicted;
+            const int hi = lo + per < evicted ? lo + per : evicted;
+            reset_staged_rows(p, s_row + lo, hi - lo);
+        }
+    }
+    for (int task = blockIdx.x; task < 3; task += gridDim.x) publish_words(p, task, s_sum);
+}
+
+}  // namespace mpzch

@@ -98,6 +98,10 @@ struct Params {
     uint8_t *hint;                 // by batch position: round at which k_allocate placed the claim of the id
                                    // elected there (written for elected positions only)
     uint32_t *seg_cnt;
+    // one chunk per wavefront (mpzch_chunk_kernels.hpp): by batch position, where the claim of the id elected there
+    // ended up; and three words of counters per workgroup
+    uint32_t *place;
+    uint64_t *wg_words;
     int32_t seg_chunks;
     int32_t num_segs;
     uint32_t *set_slot;            // scratch hash set of batch positions, empty = 0xFFFFFFFF
@@ -1037,25 +1041,124 @@ __device__ __forceinline__ int32_t expiry_bound(const Tab &d, int32_t step)
     return (int32_t)0x80000000;
 }
 
-// One wavefront serves the segments vblock, vblock + vgrid, ...; s_code and s_req are its own areas of LDS.  REC: every
-// table of the call is kept as records (identity and metadata come with one load).
-// The blocks are aligned: a claimant placed in the block of its home slot -- nearly every one, in a table with room
+// Blocks.  They are aligned: a claimant placed in the block of its home slot -- nearly every one, in a table with room
 // or with expired ids -- costs the memory system one line (8 slots counted from the home slot straddle two in seven
-// of eight cases; 1 B slots of records, 345 K claimants: 51.5 -> 37 us).  In a table that the memory-side cache holds, lines are cheap
-// and round trips are what counts: there a block is simply the next 8 slots.
+// of eight cases; 1 B slots of records, 345 K claimants: 51.5 -> 37 us).  In a table that the memory-side cache holds,
+// lines are cheap and round trips are what counts: there a block is simply the next 8 slots.
 constexpr int64_t kCachedTableBytes = (int64_t)256 << 20;
 constexpr int kAllocG = 8;                           // slots of a block = lanes that read one block together
 
+// A claimant on its way: its position, home slot and next round.
+struct Claimant {
+    bool active;
+    uint32_t pos;
+    int32_t q;
+    int64_t home;
+};
+
+// One stage: reads the next 1 << m blocks of every active claimant's window (am: who is active) and leaves in s_code
+// what may be claimed, in rows `row` (returned) and following of 8 bytes each.  d: the table of this lane's
+// claimant; d0: any table of the call.
+template <bool MULTI, bool REC>
+__device__ __forceinline__ int claim_blocks(const Tab &d, const Tab &d0, const Claimant &c, uint64_t am, int m, int32_t bound,
+                                            bool aligned, uint8_t *s_code, ClaimReq *s_req)
+{
+    constexpr int G = kAllocG;
+    constexpr int APL = kWave / G;                   // blocks served by one load instruction
+    constexpr int NT = kWave / APL;                  // load instructions per stage
+    const int lane = lane_id();
+    const int g = lane / G, r = lane % G;
+    const int row = m == 0 ? lane : __popcll(am & ((1ull << lane) - 1ull)) << m;
+    if (m > 0 || !c.active)
+        s_req[lane] = ClaimReq{(uint64_t)(uintptr_t)(int64_t *)d.I, (uint64_t)(uintptr_t)(int32_t *)d.M, bound, 0, 0, 0};
+    if (m > 0) __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    if (c.active) {
+        int qj = c.q;
+        for (int j = 0; j < (1 << m); ++j) {
+            // the slots from round qj on that lie in one block, in the window and before the table's end
+            const int64_t s0 = qj < d.P ? wrap(c.home + qj, d.N) : 0;
+            int count = aligned ? G - block_offset(d, s0, G) : G;
+            if (count > d.P - qj) count = d.P - qj;
+            if ((int64_t)count > d.N - s0) count = (int)(d.N - s0);
+            s_req[row + j] = ClaimReq{(uint64_t)(uintptr_t)(int64_t *)id_at(d, s0) | ((uint64_t)(uint32_t)count << kWhereAddrBits) |
+                                          ((uint64_t)(uint32_t)d.sh << (kWhereAddrBits + 4)),
+                                      (uint64_t)(uintptr_t)(int32_t *)meta_at(d, s0), bound, c.pos, (uint32_t)qj, 0};
+            qj += count;
+        }
+    }
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    int64_t vi[NT];
+    int32_t vm[NT];
+#pragma unroll
+    for (int t = 0; t < NT; ++t) {
+        const ClaimReq &rq = s_req[t * APL + g];
+        const uint64_t first_slot = rq.first;
+        // lanes without a slot to look at read the block's first one
+        const uint64_t k = r < (int)((first_slot >> kWhereAddrBits) & 15u) ? (uint64_t)r : 0ull;
+        const uint64_t a = first_slot & ((1ull << kWhereAddrBits) - 1ull);
+        if constexpr (REC) {
+            const u32x3 rec = *(global_ptr<u32x3>)(uintptr_t)(a + k * 16);
+            vi[t] = (int64_t)(((uint64_t)rec.y << 32) | rec.x);
+            vm[t] = (int32_t)rec.z;
+        } else {
+            const int sh = MULTI ? (int)(first_slot >> (kWhereAddrBits + 4)) & 1 : d0.sh;
+            vi[t] = *(global_ptr<int64_t>)(uintptr_t)(a + (k << (3 + sh)));
+            vm[t] = *(global_ptr<int32_t>)(uintptr_t)(rq.meta + (k << (2 + 2 * sh)));
+        }
+    }
+    // what the claimant's lane needs to know of a slot, one byte: 1 = it may be claimed (empty, holds an
+    // expired id, or a worse claim), 2 = it held an id when the call began
+#pragma unroll
+    for (int t = 0; t < NT; ++t) {
+        const ClaimReq &rq = s_req[t * APL + g];
+        const int64_t v = vi[t];
+        uint32_t occ = v >= 0 ? 1u : 0u;
+        bool cand = v < 0 || vm[t] < (MULTI ? rq.bound : bound);
+        if (is_tag(v)) {
+            occ = tag_occ(v);
+            cand = v > make_tag(rq.round + (uint32_t)r, rq.pos, occ);
+        }
+        const bool in = r < (int)((rq.first >> kWhereAddrBits) & 15u);
+        s_code[(t * APL + g) * G + r] = (uint8_t)(in && cand ? 1u | (occ << 1) : 0u);
+    }
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    return row;
+}
+
+// The claimant's lane walks the blocks of the stage.  Returns the slot it claimed (c.q: the round; old: what the slot
+// held, a tag when a worse claim was displaced), or -1 when it went past the blocks (c.q is moved on).
+__device__ __forceinline__ int64_t claim_walk(const Tab &d, Claimant &c, int m, int row, const uint8_t *s_code,
+                                              const ClaimReq *s_req, int64_t &old)
+{
+    constexpr int G = kAllocG;
+    for (int j = 0; j < (1 << m); ++j) {
+        uint64_t x = *reinterpret_cast<const uint64_t *>(s_code + (row + j) * G);
+        const uint64_t rq = s_req[row + j].first;
+        const uint64_t a = rq & ((1ull << kWhereAddrBits) - 1ull);
+        while (x) {
+            const int bit = __ffsll((unsigned long long)x) - 1;      // 8 k: the bytes of slots that may not be claimed are 0
+            const int k = bit >> 3;
+            const uint32_t occ = (uint32_t)(x >> (bit + 1)) & 1u;
+            x &= ~(0xFFull << bit);
+            const int64_t mine = make_tag((uint32_t)(c.q + k), c.pos, occ);
+            old = __hip_atomic_fetch_min((global_ptr<int64_t>)(uintptr_t)(a + ((uint64_t)k << (3 + d.sh))), mine, __ATOMIC_RELAXED,
+                                         __HIP_MEMORY_SCOPE_AGENT);
+            if (is_tag(old) && old < mine) continue;                 // a better claim got there first
+            c.q += k;
+            return wrap(c.home + c.q, d.N);
+        }
+        c.q += (int)(rq >> kWhereAddrBits) & 15;
+    }
+    return -1;
+}
+
+// One wavefront serves the segments vblock, vblock + vgrid, ...; s_code and s_req are its own areas of LDS.  REC: every
+// table of the call is kept as records (identity and metadata come with one load).
 template <bool MULTI, bool REC>
 __device__ __forceinline__ void allocate_body(const Params &p, int64_t vblock, int64_t vgrid,
                                               uint8_t *s_code, ClaimReq *s_req)
 {
-    constexpr int G = kAllocG;
-    constexpr int APL = kWave / G;                   // claimants served by one load instruction
-    constexpr int NT = kWave / APL;                  // load instructions per stage
-
     const int lane = lane_id();
-    const int g = lane / G, r = lane % G;
     const Tab d0 = view(p.t0);
     const int64_t lane_offset = MULTI ? table_offsets(p.offsets, p.num_tables) : 0;
     for (int64_t seg = vblock; seg < p.num_segs; seg += vgrid) {
@@ -1097,107 +1200,40 @@ __device__ __forceinline__ void allocate_body(const Params &p, int64_t vblock, i
             const int32_t bound = expiry_bound(d, p.step);
             const bool aligned = (d.N << (3 + d.sh)) > kCachedTableBytes;
             uint32_t hint = kHintUnplaced;
-            // the claimant this lane carries: its position, home slot and next round
-            bool active = agent, own = true;
-            uint32_t cpos = pos;
-            int32_t q = 0;
+            // the claimant this lane carries
+            Claimant c;
+            c.active = agent;
+            c.pos = pos;
+            c.q = 0;
+            c.home = home;
+            bool own = true;
             for (bool later = false;; later = true) {
-                const uint64_t am = __ballot(active);
+                const uint64_t am = __ballot(c.active);
                 if (!am) break;
                 // the 64 blocks of a stage are shared out among the claimants that are left (but one block each is
                 // what nearly every claimant needs at first)
                 const int m = later ? blocks_shift(__popcll(am), !MULTI ? d0.P : seg_one ? seg_d.P : 64) : 0;
-                const int row = m == 0 ? lane : __popcll(am & ((1ull << lane) - 1ull)) << m;
-                if (m > 0 || !active)
-                    s_req[lane] = ClaimReq{(uint64_t)(uintptr_t)(int64_t *)d.I, (uint64_t)(uintptr_t)(int32_t *)d.M, bound, 0, 0, 0};
-                if (m > 0) __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-                if (active) {
-                    int qj = q;
-                    for (int j = 0; j < (1 << m); ++j) {
-                        // the slots from round qj on that lie in one block, in the window and before the table's end
-                        const int64_t s0 = qj < d.P ? wrap(home + qj, d.N) : 0;
-                        int count = aligned ? G - block_offset(d, s0, G) : G;
-                        if (count > d.P - qj) count = d.P - qj;
-                        if ((int64_t)count > d.N - s0) count = (int)(d.N - s0);
-                        s_req[row + j] = ClaimReq{(uint64_t)(uintptr_t)(int64_t *)id_at(d, s0) |
-                                                      ((uint64_t)(uint32_t)count << kWhereAddrBits) |
-                                                      ((uint64_t)(uint32_t)d.sh << (kWhereAddrBits + 4)),
-                                                  (uint64_t)(uintptr_t)(int32_t *)meta_at(d, s0), bound, cpos, (uint32_t)qj, 0};
-                        qj += count;
-                    }
-                }
-                __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-                int64_t vi[NT];
-                int32_t vm[NT];
-#pragma unroll
-                for (int t = 0; t < NT; ++t) {
-                    const ClaimReq &rq = s_req[t * APL + g];
-                    const uint64_t first_slot = rq.first;
-                    // lanes without a slot to look at read the block's first one
-                    const uint64_t k = r < (int)((first_slot >> kWhereAddrBits) & 15u) ? (uint64_t)r : 0ull;
-                    const uint64_t a = first_slot & ((1ull << kWhereAddrBits) - 1ull);
-                    if constexpr (REC) {
-                        const u32x3 rec = *(global_ptr<u32x3>)(uintptr_t)(a + k * 16);
-                        vi[t] = (int64_t)(((uint64_t)rec.y << 32) | rec.x);
-                        vm[t] = (int32_t)rec.z;
-                    } else {
-                        const int sh = (int)(first_slot >> (kWhereAddrBits + 4)) & 1;
-                        vi[t] = *(global_ptr<int64_t>)(uintptr_t)(a + (k << (3 + sh)));
-                        vm[t] = *(global_ptr<int32_t>)(uintptr_t)(rq.meta + (k << (2 + 2 * sh)));
-                    }
-                }
-                // what the claimant's lane needs to know of a slot, one byte: 1 = it may be claimed (empty, holds an
-                // expired id, or a worse claim), 2 = it held an id when the call began
-#pragma unroll
-                for (int t = 0; t < NT; ++t) {
-                    const ClaimReq &rq = s_req[t * APL + g];
-                    const int64_t v = vi[t];
-                    uint32_t occ = v >= 0 ? 1u : 0u;
-                    bool cand = v < 0 || vm[t] < (MULTI ? rq.bound : bound);
-                    if (is_tag(v)) {
-                        occ = tag_occ(v);
-                        cand = v > make_tag(rq.round + (uint32_t)r, rq.pos, occ);
-                    }
-                    const bool in = r < (int)((rq.first >> kWhereAddrBits) & 15u);
-                    s_code[(t * APL + g) * G + r] = (uint8_t)(in && cand ? 1u | (occ << 1) : 0u);
-                }
-                __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-                // every lane walks the blocks of its own claimant
+                const int row = claim_blocks<MULTI, REC>(d, d0, c, am, m, bound, aligned, s_code, s_req);
                 bool moved = false;
-                if (active) {
-                    bool placed = false;
-                    for (int j = 0; j < (1 << m) && !placed; ++j) {
-                        uint64_t x = *reinterpret_cast<const uint64_t *>(s_code + (row + j) * G);
-                        const uint64_t rq = s_req[row + j].first;
-                        const uint64_t a = rq & ((1ull << kWhereAddrBits) - 1ull);
-                        while (x) {
-                            const int bit = __ffsll((unsigned long long)x) - 1;      // 8 k: slots that may not be claimed are 0
-                            const int k = bit >> 3;
-                            const uint32_t occ = (uint32_t)(x >> (bit + 1)) & 1u;
-                            x &= ~(0xFFull << bit);
-                            const int64_t mine = make_tag((uint32_t)(q + k), cpos, occ);
-                            const int64_t old = __hip_atomic_fetch_min((global_ptr<int64_t>)(uintptr_t)(a + ((uint64_t)k << (3 + d.sh))),
-                                                                       mine, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                            if (is_tag(old) && old < mine) continue;      // a better claim got there first
-                            placed = true;
-                            const uint32_t at = q + k < (int32_t)kHintUnknown ? (uint32_t)(q + k) : kHintUnknown;
-                            if (own) hint = at;
-                            else p.hint[cpos] = (uint8_t)at;
-                            active = false;
-                            if (is_tag(old) && (int32_t)tag_round(old) + 1 < d.P) {
-                                // the displaced claimant goes on from its next round (same table: same slot)
-                                active = moved = true;
-                                own = false;
-                                cpos = tag_pos(old);
-                                q = (int32_t)tag_round(old) + 1;
-                            }
-                            break;
+                if (c.active) {
+                    int64_t old;
+                    if (claim_walk(d, c, m, row, s_code, s_req, old) >= 0) {
+                        const uint32_t at = c.q < (int32_t)kHintUnknown ? (uint32_t)c.q : kHintUnknown;
+                        if (own) hint = at;
+                        else p.hint[c.pos] = (uint8_t)at;
+                        c.active = false;
+                        if (is_tag(old) && (int32_t)tag_round(old) + 1 < d.P) {
+                            // the displaced claimant goes on from its next round (same table: same slot)
+                            c.active = moved = true;
+                            own = false;
+                            c.pos = tag_pos(old);
+                            c.q = (int32_t)tag_round(old) + 1;
                         }
-                        if (!placed) q += (int)(rq >> kWhereAddrBits) & 15;
+                    } else {
+                        c.active = c.q < d.P;                        // window exhausted: falls back at finalize
                     }
-                    if (!placed) active = q < d.P;                       // window exhausted: falls back at finalize
                 }
-                if (moved) home = home_slot(p.ids[cpos], d.seed, d.N);
+                if (moved) c.home = home_slot(p.ids[c.pos], d.seed, d.N);
                 __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");   // s_code and s_req are written again
             }
             if (agent) p.hint[pos] = (uint8_t)hint;           // for the copies of the id
