@@ -393,7 +393,8 @@ mpzch_status_t launch_remap(Scratch &sc, Timing &tm, Params p, int32_t max_p_lru
 
     // one table, and no wavefront of Pass 1 has more than one chunk
     const int64_t groups = (p.n + kBlock - 1) / kBlock;
-    if (p.num_tables == 1 && max_p_lru == 0 && groups <= (int64_t)sc.num_cus * discover_blocks_per_cu())
+    if (p.num_tables == 1 && max_p_lru == 0 && groups <= (int64_t)sc.num_cus * discover_blocks_per_cu() &&
+        p.n < ((int64_t)1 << kChunkPosBits))
         return launch_remap_chunks(tm, p, (int)groups, s);
 
     const int64_t num_chunks = (p.n + kWave - 1) / kWave;

@@ -25,6 +25,39 @@ namespace mpzch {
 constexpr uint32_t kNoEntry = 0xFFFFFFFFu;       // ent[pos]: the position did not miss
 constexpr uint32_t kPlaceNone = 0xFFFFFFFFu;     // place[pos]: displaced and out of slots.  0: never placed.  Else round + 1.
 
+// Scratch set of these calls: an entry is the batch position with 12 bits of the id's hash above it, so that two ids that
+// meet in one entry tell each other apart without a look at the batch (a round trip per collision; with every
+// id missed and half of the set full, that was 8 of 40 us for 262 144 ids).  Otherwise as set_insert.
+constexpr int kChunkPosBits = 20;                // n < 2^20
+constexpr uint32_t kChunkPosMask = (1u << kChunkPosBits) - 1u;
+
+__device__ __forceinline__ uint32_t set_insert_chunk(const Params &p, int64_t id, uint32_t pos)
+{
+    const uint64_t h = mix64((uint64_t)id ^ kSetSeed);
+    const uint32_t size = 2u * (uint32_t)p.n;
+    const uint32_t mine = ((uint32_t)h << kChunkPosBits) | pos;
+    uint32_t e = (uint32_t)__umul64hi(h, (uint64_t)size);
+    for (;;) {
+        uint32_t expected = kSetEmpty;
+        if (__hip_atomic_compare_exchange_strong(&p.set_slot[e], &expected, mine, __ATOMIC_RELAXED, __ATOMIC_RELAXED,
+                                                 __HIP_MEMORY_SCOPE_AGENT))
+            break;                                            // first of its id so far
+        if (((expected ^ mine) & ~kChunkPosMask) == 0) {
+            const uint32_t other = expected & kChunkPosMask;
+            if ((int64_t)other < p.n && p.ids[other] == id) {
+                if (mine < expected) __hip_atomic_fetch_min(&p.set_slot[e], mine, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                break;
+            }
+        }
+        if (++e == size) e = 0;
+    }
+    return e;
+}
+
+// hint[pos] of a missed position: the first round at which its id may find a slot to claim, as far as Pass 1 can tell
+// (without eviction: the first empty slot), at most kStartMax; kStartNever: there is none in its window.
+constexpr uint32_t kStartMax = 0xFE, kStartNever = 0xFF;
+
 // Sum over the wavefront of 32-bit values whose total fits 32 bits, in every lane.
 __device__ __forceinline__ uint32_t wave_sum32(uint32_t x)
 {
@@ -73,13 +106,21 @@ __global__ __launch_bounds__(kBlock, 4) void k_discover_chunk(Params p)
     }
     const bool hit = valid && res >= 0, miss = valid && res < 0;
     uint32_t e = kNoEntry;
-    if (miss) e = set_insert(p, id, (uint32_t)pos, 0, 2ull * (uint64_t)p.n);
+    if (miss) e = set_insert_chunk(p, id, (uint32_t)pos);
     const int64_t slot = hit ? wrap(home + res, d.N) : home;
     if (hit && !(REC && fresh && d.evict != 3)) store_meta(d, slot, meta_value(p, d, pos));
     if (in) {
         p.out_slots[pos] = slot;
         p.ent[pos] = e;
         p.place[pos] = 0;
+    }
+    if (miss) {
+        uint32_t start = 0;
+        if (d.evict == 0) {
+            const uint32_t r = (uint32_t)(absent_len(res) - 1);
+            start = res > kProbeAbsent ? kStartNever : r < kStartMax ? r : kStartMax;
+        }
+        p.hint[pos] = (uint8_t)start;
     }
     if (p.out_stats) {
         const uint32_t hits = (uint32_t)__popcll(__ballot(hit)), misses = (uint32_t)__popcll(__ballot(miss));
@@ -147,55 +188,42 @@ __global__ __launch_bounds__(kBlock, 4) void k_allocate_chunk(Params p)
     const Tab d = view(p.t0);
     const uint32_t e = in ? p.ent[pos] : kNoEntry;
     const int64_t id = in ? p.ids[pos] : -1;
+    uint32_t start = in ? (uint32_t)p.hint[pos] : kStartNever;   // (anything where the position did not miss)
     const bool have = e != kNoEntry;
     uint32_t first = 0;
-    if (have) first = p.set_slot[e];
+    if (have) first = p.set_slot[e] & kChunkPosMask;
+    else start = kStartNever;
 
     Claimant c;
-    c.active = have;                                 // the first blocks are requested before the election is known
+    c.active = start != kStartNever;                 // the first blocks are requested before the election is known
     c.pos = (uint32_t)pos;
     c.home = home_slot(id, d.seed, d.N);
-    c.q = 0;
+    c.q = (int32_t)start;
     const int32_t bound = expiry_bound(d, p.step);
     const bool aligned = (d.N << (3 + d.sh)) > kCachedTableBytes;
-    bool agent = false, inserted = false, evicted = false;
+    bool inserted = false, evicted = false;
     int64_t slot = 0;
     for (bool later = false;; later = true) {
         const uint64_t am = __ballot(c.active);
         if (!am) break;
         const int m = later ? blocks_shift(__popcll(am), d.P) : 0;
         const int row = claim_blocks<false, REC>(d, d, c, am, m, bound, aligned, s_code[w], s_req[w]);
-        if (!later) {
-            agent = have && first == (uint32_t)pos;  // else: a later copy of the id
-            c.active = agent;
-            if (have) p.list[pos] = first;
-        }
-        bool moved = false;
-        if (c.active) {
-            int64_t old;
-            const int64_t at = claim_walk(d, c, m, row, s_code[w], s_req[w], old);
-            if (at >= 0) {
-                note_place(p, c.pos, (uint32_t)c.q + 1u);
-                c.active = false;
-                inserted = old == -1;
-                evicted = old >= 0;
-                slot = at;
-                if (is_tag(old)) {
-                    // the displaced claimant goes on from its next round (same table: same slot)
-                    c.pos = tag_pos(old);
-                    c.q = (int32_t)tag_round(old) + 1;
-                    c.active = moved = c.q < d.P;
-                    if (!moved) note_place(p, c.pos, kPlaceNone);
-                }
-            } else if (c.q >= d.P) {                 // window exhausted: falls back at finalize
-                c.active = false;
-                if (c.pos != (uint32_t)pos) note_place(p, c.pos, kPlaceNone);
-            }
-        }
-        if (moved) c.home = home_slot(p.ids[c.pos], d.seed, d.N);
+        if (!later) c.active = c.active && first == (uint32_t)pos;      // else: a later copy of the id
+        if (c.active)
+            claim_walk(d, c, m, row, s_code[w], s_req[w],
+                       [&](uint32_t who, int32_t round, int64_t at, int64_t old) {
+                           note_place(p, who, (uint32_t)round + 1u);
+                           inserted = old == -1;     // (a lane's last claim: only it meets a slot not claimed before)
+                           evicted = old >= 0;
+                           slot = at;
+                       },
+                       [&](uint32_t who) {
+                           if (who != (uint32_t)pos) note_place(p, who, kPlaceNone);
+                       });
         __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");   // s_code and s_req are written again
     }
-    leave_outcomes(p, agent, inserted, evicted, slot, s_red);
+    if (have) p.list[pos] = first;
+    leave_outcomes(p, have && first == (uint32_t)pos, inserted, evicted, slot, s_red);
 }
 
 // Sum over the workgroup, in every thread.  s_sum: one word per wavefront; to be reached by all threads.

@@ -1103,11 +1103,12 @@ __device__ __forceinline__ int claim_blocks(const Tab &d, const Tab &d0, const C
         } else {
             const int sh = MULTI ? (int)(first_slot >> (kWhereAddrBits + 4)) & 1 : d0.sh;
             vi[t] = *(global_ptr<int64_t>)(uintptr_t)(a + (k << (3 + sh)));
-            vm[t] = *(global_ptr<int32_t>)(uintptr_t)(rq.meta + (k << (2 + 2 * sh)));
+            vm[t] = 0;
+            if (MULTI || d0.evict != 0) vm[t] = *(global_ptr<int32_t>)(uintptr_t)(rq.meta + (k << (2 + 2 * sh)));
         }
     }
     // what the claimant's lane needs to know of a slot, one byte: 1 = it may be claimed (empty, holds an
-    // expired id, or a worse claim), 2 = it held an id when the call began
+    // expired id, or a worse claim), 2 = it held an id when the call began, 4 = it is claimed already
 #pragma unroll
     for (int t = 0; t < NT; ++t) {
         const ClaimReq &rq = s_req[t * APL + g];
@@ -1119,37 +1120,57 @@ __device__ __forceinline__ int claim_blocks(const Tab &d, const Tab &d0, const C
             cand = v > make_tag(rq.round + (uint32_t)r, rq.pos, occ);
         }
         const bool in = r < (int)((rq.first >> kWhereAddrBits) & 15u);
-        s_code[(t * APL + g) * G + r] = (uint8_t)(in && cand ? 1u | (occ << 1) : 0u);
+        s_code[(t * APL + g) * G + r] = (uint8_t)(in ? (cand ? 1u : 0u) | (occ << 1) | (is_tag(v) ? 4u : 0u) : 0u);
     }
     __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
     return row;
 }
 
-// The claimant's lane walks the blocks of the stage.  Returns the slot it claimed (c.q: the round; old: what the slot
-// held, a tag when a worse claim was displaced), or -1 when it went past the blocks (c.q is moved on).
-__device__ __forceinline__ int64_t claim_walk(const Tab &d, Claimant &c, int m, int row, const uint8_t *s_code,
-                                              const ClaimReq *s_req, int64_t &old)
+// The claimant's lane walks the blocks of the stage and claims.  A claimant that it displaces is carried on at once, from
+// the next slot of the same blocks (its next round is that slot: displaced at round r of slot s its home is s - r, and
+// what the block says of empty and expired slots holds for it too; claimed ones it tries) -- a displacement costs the
+// round trip of its atomic and no other.  placed(pos, round, slot, old) is called for every claim that stands, old being
+// what the slot held before; lost(pos) for a claimant that has run out of slots.  On return c is the claimant to go on
+// with, if c.active.
+template <typename Placed, typename Lost>
+__device__ __forceinline__ void claim_walk(const Tab &d, Claimant &c, int m, int row, const uint8_t *s_code,
+                                           const ClaimReq *s_req, Placed placed, Lost lost)
 {
     constexpr int G = kAllocG;
+    constexpr uint64_t kOnes = 0x0101010101010101ull;
+    bool carried = false;
     for (int j = 0; j < (1 << m); ++j) {
-        uint64_t x = *reinterpret_cast<const uint64_t *>(s_code + (row + j) * G);
+        const uint64_t word = *reinterpret_cast<const uint64_t *>(s_code + (row + j) * G);
         const uint64_t rq = s_req[row + j].first;
         const uint64_t a = rq & ((1ull << kWhereAddrBits) - 1ull);
+        uint64_t x = (carried ? word | (word >> 2) : word) & kOnes;
         while (x) {
-            const int bit = __ffsll((unsigned long long)x) - 1;      // 8 k: the bytes of slots that may not be claimed are 0
+            const int bit = __ffsll((unsigned long long)x) - 1;
             const int k = bit >> 3;
-            const uint32_t occ = (uint32_t)(x >> (bit + 1)) & 1u;
-            x &= ~(0xFFull << bit);
-            const int64_t mine = make_tag((uint32_t)(c.q + k), c.pos, occ);
-            old = __hip_atomic_fetch_min((global_ptr<int64_t>)(uintptr_t)(a + ((uint64_t)k << (3 + d.sh))), mine, __ATOMIC_RELAXED,
-                                         __HIP_MEMORY_SCOPE_AGENT);
+            x &= x - 1;
+            const int32_t round = c.q + k;                           // c.q: the round of the block's first slot
+            if (round >= d.P) break;
+            const int64_t mine = make_tag((uint32_t)round, c.pos, (uint32_t)(word >> (bit + 1)) & 1u);
+            const int64_t old = __hip_atomic_fetch_min((global_ptr<int64_t>)(uintptr_t)(a + ((uint64_t)k << (3 + d.sh))), mine,
+                                                       __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
             if (is_tag(old) && old < mine) continue;                 // a better claim got there first
-            c.q += k;
-            return wrap(c.home + c.q, d.N);
+            const int64_t slot = wrap(c.home + round, d.N);
+            placed(c.pos, round, slot, old);
+            if (!is_tag(old)) { c.active = false; return; }
+            c.pos = tag_pos(old);
+            c.home = slot - (int64_t)tag_round(old);
+            if (c.home < 0) c.home += d.N;
+            c.q = (int32_t)tag_round(old) - k;
+            carried = true;
+            x = ((word | (word >> 2)) & kOnes) & ~((1ull << bit) | ((1ull << bit) - 1ull));
         }
         c.q += (int)(rq >> kWhereAddrBits) & 15;
+        if (c.q >= d.P) break;
     }
-    return -1;
+    if (c.q >= d.P) {
+        c.active = false;
+        lost(c.pos);
+    }
 }
 
 // One wavefront serves the segments vblock, vblock + vgrid, ...; s_code and s_req are its own areas of LDS.  REC: every
@@ -1206,7 +1227,6 @@ __device__ __forceinline__ void allocate_body(const Params &p, int64_t vblock, i
             c.pos = pos;
             c.q = 0;
             c.home = home;
-            bool own = true;
             for (bool later = false;; later = true) {
                 const uint64_t am = __ballot(c.active);
                 if (!am) break;
@@ -1214,26 +1234,14 @@ __device__ __forceinline__ void allocate_body(const Params &p, int64_t vblock, i
                 // what nearly every claimant needs at first)
                 const int m = later ? blocks_shift(__popcll(am), !MULTI ? d0.P : seg_one ? seg_d.P : 64) : 0;
                 const int row = claim_blocks<MULTI, REC>(d, d0, c, am, m, bound, aligned, s_code, s_req);
-                bool moved = false;
-                if (c.active) {
-                    int64_t old;
-                    if (claim_walk(d, c, m, row, s_code, s_req, old) >= 0) {
-                        const uint32_t at = c.q < (int32_t)kHintUnknown ? (uint32_t)c.q : kHintUnknown;
-                        if (own) hint = at;
-                        else p.hint[c.pos] = (uint8_t)at;
-                        c.active = false;
-                        if (is_tag(old) && (int32_t)tag_round(old) + 1 < d.P) {
-                            // the displaced claimant goes on from its next round (same table: same slot)
-                            c.active = moved = true;
-                            own = false;
-                            c.pos = tag_pos(old);
-                            c.q = (int32_t)tag_round(old) + 1;
-                        }
-                    } else {
-                        c.active = c.q < d.P;                        // window exhausted: falls back at finalize
-                    }
-                }
-                if (moved) c.home = home_slot(p.ids[c.pos], d.seed, d.N);
+                if (c.active)
+                    claim_walk(d, c, m, row, s_code, s_req,
+                               [&](uint32_t who, int32_t round, int64_t, int64_t) {
+                                   const uint32_t at = round < (int32_t)kHintUnknown ? (uint32_t)round : kHintUnknown;
+                                   if (who == pos) hint = at;
+                                   else p.hint[who] = (uint8_t)at;
+                               },
+                               [](uint32_t) {});
                 __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");   // s_code and s_req are written again
             }
             if (agent) p.hint[pos] = (uint8_t)hint;           // for the copies of the id
