@@ -78,12 +78,44 @@ __device__ __forceinline__ uint64_t pack3(uint32_t a, uint32_t b, uint32_t c)
 }
 __device__ __forceinline__ uint32_t unpack3(uint64_t w, int k) { return (uint32_t)(w >> (16 * k)) & 0xFFFFu; }
 
+// store_meta_wave over the workgroup (all threads reach it; barriers only where metadata is expiry steps).
+constexpr int kMergeCells = 512;
+struct MergeArea {
+    int64_t slot[kBlock];
+    int32_t value[kBlock];
+    uint16_t winner[kMergeCells];
+};
+__device__ __forceinline__ void store_meta_block(const Tab &d, bool active, int64_t slot, int32_t value, MergeArea &s_m)
+{
+    if (d.evict != 3) {
+        if (active) *meta_at(d, slot) = value;
+        return;
+    }
+    const int t = threadIdx.x;
+    const int cell = (int)((uint32_t)slot * 0x9E3779B1u >> 23);
+    s_m.slot[t] = active ? slot : -1;
+    s_m.value[t] = value;
+    if (active) s_m.winner[cell] = (uint16_t)t;
+    __syncthreads();
+    bool store = active;
+    if (active) {
+        const int o = s_m.winner[cell];
+        if (o != t && s_m.slot[o] == slot) {
+            __hip_atomic_fetch_max(&s_m.value[o], value, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+            store = false;
+        }
+    }
+    __syncthreads();
+    if (store) __hip_atomic_fetch_max(meta_at(d, slot), s_m.value[t], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
 template <bool REC>
 __global__ __launch_bounds__(kBlock, 4) void k_discover_chunk(Params p)
 {
     __shared__ ProbeReq s_req[kWavesPerBlock][kWave];
     __shared__ __attribute__((aligned(16))) uint8_t s_code[kWavesPerBlock][kWave * kFirstG];
     __shared__ uint32_t s_red[kWavesPerBlock][5];
+    __shared__ MergeArea s_merge;
 
     const int lane = lane_id(), w = threadIdx.x / kWave;
     const int64_t pos = (int64_t)blockIdx.x * kBlock + threadIdx.x;
@@ -108,7 +140,7 @@ __global__ __launch_bounds__(kBlock, 4) void k_discover_chunk(Params p)
     uint32_t e = kNoEntry;
     if (miss) e = set_insert_chunk(p, id, (uint32_t)pos);
     const int64_t slot = hit ? wrap(home + res, d.N) : home;
-    if (hit && !(REC && fresh && d.evict != 3)) store_meta(d, slot, meta_value(p, d, pos));
+    store_meta_block(d, hit && !(REC && fresh && d.evict != 3), slot, hit ? meta_value(p, d, pos) : 0, s_merge);
     if (in) {
         p.out_slots[pos] = slot;
         p.ent[pos] = e;
@@ -280,6 +312,7 @@ __global__ __launch_bounds__(kBlock, 8) void k_finalize_chunk(Params p)
 {
     __shared__ int64_t s_row[kBlock];
     __shared__ unsigned long long s_sum[kWavesPerBlock];
+    __shared__ MergeArea s_merge;
 
     const int64_t pos = (int64_t)blockIdx.x * kBlock + threadIdx.x;
     const bool in = pos < p.n;
@@ -293,19 +326,22 @@ __global__ __launch_bounds__(kBlock, 8) void k_finalize_chunk(Params p)
     }
     const int evicted = (int)unpack3(p.wg_words[3 * blockIdx.x + 2], 2);
     const bool have = e != kNoEntry;
+    bool refresh = false;
+    int64_t slot = 0;
     if (have) {
         const bool agent = first == (uint32_t)pos;
         if (!agent) place = p.place[first];
         p.set_slot[e] = kSetEmpty;                   // the scratch set is left empty again
         const bool placed = place != 0 && place != kPlaceNone;
         const int64_t home = home_slot(id, d.seed, d.N);
-        const int64_t slot = placed ? wrap(home + (int64_t)(place - 1u), d.N) : home;
+        slot = placed ? wrap(home + (int64_t)(place - 1u), d.N) : home;
         // the claim becomes the id, metadata gets its value (Algorithm 1, Pass 2); without a claim: Case 3, the home
         // slot's metadata is refreshed; with per-feature retention a later copy may ask for a later expiry step
         if (agent && placed) *id_at(d, slot) = id;
-        if (agent || (p.ttls && d.evict == 3)) store_meta(d, slot, meta_value(p, d, pos));
+        refresh = agent || (p.ttls && d.evict == 3);
         p.out_slots[pos] = slot;
     }
+    store_meta_block(d, refresh, slot, refresh ? meta_value(p, d, pos) : 0, s_merge);
     if (evicted > 0) {
         // where this workgroup's part of the list begins: the evictions of the workgroups before
         unsigned long long base = 0;

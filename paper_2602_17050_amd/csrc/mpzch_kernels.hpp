@@ -602,6 +602,43 @@ __device__ __forceinline__ int probe_more(const Tab &d, int64_t id, int64_t home
     return found;
 }
 
+// store_meta for the lanes with `active` set, of which many may hold the same slot (the copies of a popular id).  With
+// expiry steps every store is an atomic maximum, and those on one address follow each other at some 12 ns: 20 011
+// positions of which the most popular id holds a tenth spent 20 of 24 us on it.  So lanes of one slot first agree on
+// their maximum in LDS: of the lanes that write their number into one of 64 (or, over a workgroup, 512) words the
+// winner collects the values of those that share its slot; a lane that lost to another slot stores for itself.
+struct MetaMerge {
+    int64_t slot;
+    int32_t value;
+    uint32_t winner;
+};
+static_assert(sizeof(MetaMerge) == sizeof(ProbeReq), "a wavefront's requests lie idle meanwhile");
+
+__device__ __forceinline__ void store_meta_wave(const Tab &d, bool active, int64_t slot, int32_t value, MetaMerge *s_m)
+{
+    if (d.evict != 3) {
+        if (active) *meta_at(d, slot) = value;
+        return;
+    }
+    const int lane = lane_id();
+    const int cell = (int)((uint32_t)slot * 0x9E3779B1u >> 26);
+    s_m[lane].slot = active ? slot : -1;
+    s_m[lane].value = value;
+    if (active) s_m[cell].winner = (uint32_t)lane;
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    bool store = active;
+    if (active) {
+        const uint32_t o = s_m[cell].winner;
+        if (o != (uint32_t)lane && s_m[o].slot == slot) {
+            __hip_atomic_fetch_max(&s_m[o].value, value, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+            store = false;
+        }
+    }
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    if (store) __hip_atomic_fetch_max(meta_at(d, slot), s_m[lane].value, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+}
+
 // out[pos, :] <- rows[slot mod num_rows, :] for the positions of the active lanes (Sec. 3.7: the lookup
 // fused with the embedding gather).  The 64 rows are copied by the whole wavefront, consecutive lanes
 // moving consecutive 16-byte (or 4-byte) pieces of a row, several loads in flight per lane.
@@ -735,11 +772,13 @@ __device__ __forceinline__ void discover_body(const Params &p)
     };
     // a position whose id is resident at `dist` probes from home
     // (the first pass stores the outputs of its whole chunk itself: emit = false)
-    auto finish_hit = [&](const Tab &d, int64_t pos, int64_t home, int dist, bool emit, bool fresh) {
+    // (called by all lanes; `active`: the lane's position is a hit)
+    auto finish_hit = [&](const Tab &d, bool active, int64_t pos, int64_t home, int dist, bool emit, bool fresh) {
         const int64_t slot = wrap(home + dist, d.N);
-        if (TRAIN && !(REC && fresh && d.evict != 3)) {
-            store_meta(d, slot, meta_value(p, d, pos));   // "Update": refresh the resident's metadata
-        }
+        if (TRAIN)            // "Update": refresh the resident's metadata
+            store_meta_wave(d, active && !(REC && fresh && d.evict != 3), slot, active ? meta_value(p, d, pos) : 0,
+                            reinterpret_cast<MetaMerge *>(s_req[w]));
+        if (!active) return;
         if (COUNT) st_probe += (unsigned long long)(dist + 1);
         if (emit) {
             if (!GATHER || p.out_slots) p.out_slots[pos] = slot;
@@ -784,7 +823,7 @@ __device__ __forceinline__ void discover_body(const Params &p)
                         else if (got <= kProbeAbsent) mlen = absent_len(got);   // an empty slot ends the search
                     }
                 }
-                if (mine && dist >= 0) finish_hit(d, (int64_t)pos, home, dist, true, fresh);
+                finish_hit(d, mine && dist >= 0, (int64_t)pos, home, dist, true, fresh);
                 const bool miss = mine && dist < 0;
                 const uint64_t mb = __ballot(miss);
                 if (miss && TRAIN) {
@@ -870,7 +909,7 @@ __device__ __forceinline__ void discover_body(const Params &p)
             int res = probe_pass<kFirstG, NT, REC>(d, id, home, valid ? -o : d.P, s_req[w], s_code[w], p.step, &fresh);
             if (res == kProbeGoOn && kFirstG - o >= d.P) res = probe_absent(d.P - 1);    // the whole window was read
             const bool hit = valid && res >= 0;
-            if (hit) finish_hit(d, pos, home, res, false, fresh);
+            finish_hit(d, hit, pos, home, res, false, fresh);
             if (COUNT) {
                 st_hit += __popcll(__ballot(hit));
                 st_inv += __popcll(__ballot(mine && !valid));

@@ -134,3 +134,17 @@ def test_batches_around_the_largest_one_chunk_call(n):
     for step in (0, 1, 2):
         t.step(wl.zipf_ids(rng, n, 1.02, 600_000), step)
     t.close()
+
+
+# ---- expiry steps: the copies of a popular id agree on their maximum in LDS before they store it
+@pytest.mark.parametrize("layout", ["separate", "records"])
+@pytest.mark.parametrize("n", [3, 64, 100, 257, 20_011, 530_000])
+def test_expiry_steps_of_popular_ids(n, layout):
+    rng = rng_for(907 + n)
+    t = Pair(max(8, n // 2), 16, 3, "expiry", 31, layout=layout)
+    for step in (0, 2, 2, 9):
+        ids = wl.zipf_ids(rng, n, 1.3, max(4, n))
+        ids[rng.random(n) < 0.3] = 77 + step % 2          # one id at a third of the positions, new every other time
+        t.step(ids, step, ttls=rng.integers(0, 1_000, size=n).astype(np.int32))
+        t.step(ids, step)
+    t.close()
