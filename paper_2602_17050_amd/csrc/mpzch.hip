@@ -2,7 +2,7 @@
 // kernel launches on the caller's stream.  No call here synchronises with the host except
 // where the header says so (scratch growth, descriptor upload, timing read-out, destroy).
 #include "../../include/mpzch.h"
-#include "mpzch_chunk_kernels.hpp"
+#include "mpzch_block_kernel.hpp"
 
 #include <cstdlib>
 #include <cstring>
@@ -341,6 +341,19 @@ mpzch_status_t launch_finalize(const Params &p, int grid, hipStream_t s)
 mpzch_status_t fill64(int64_t *dst, int64_t count, long long value, hipStream_t s);
 mpzch_status_t fill32(int32_t *dst, int64_t count, int32_t value, hipStream_t s);
 
+// One workgroup (mpzch_block_kernel.hpp).  Timed as Pass 1.
+bool one_block(const Params &p) { return p.num_tables == 1 && p.t0.evict != 2 && p.n <= kOneBlock; }
+mpzch_status_t launch_remap_block(Timing &tm, const Params &p, hipStream_t s)
+{
+    const int threads = (int)((p.n + kWave - 1) / kWave) * kWave;
+    if (!tm.begin(KDiscover, s)) return MPZCH_ERR_HIP;
+    if (p.t0.sh) hipLaunchKernelGGL((k_remap_block<true>), dim3(1), dim3(threads), 0, s, p);
+    else hipLaunchKernelGGL((k_remap_block<false>), dim3(1), dim3(threads), 0, s, p);
+    LAUNCH_CHECK();
+    if (!tm.end(s)) return MPZCH_ERR_HIP;
+    return MPZCH_OK;
+}
+
 // The launch sequence of one training remap (single table or group).
 mpzch_status_t launch_remap(Scratch &sc, Timing &tm, Params p, int32_t max_p_lru, hipStream_t s);
 
@@ -348,6 +361,7 @@ mpzch_status_t launch_remap(Scratch &sc, Timing &tm, Params p, int32_t max_p_lru
 // sequence was cut short by a HIP error; the next call then clears both before it starts.
 mpzch_status_t run_remap(Scratch &sc, Timing &tm, const Params &p, int32_t max_p_lru, hipStream_t s)
 {
+    if (one_block(p)) return launch_remap_block(tm, p, s);        // uses no scratch
     if (sc.dirty) {
         TRY(fill32((int32_t *)sc.set_slot, 2 * sc.cap_n, -1, s));
         TRY(fill64((int64_t *)sc.ctl, (int64_t)(sizeof(Control) / sizeof(int64_t)), 0, s));

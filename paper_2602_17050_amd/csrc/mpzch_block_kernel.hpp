@@ -1,0 +1,163 @@
+// The training remap of the smallest batches: one workgroup, one launch.
+//
+// Three launches cost the host some 12 us and the GPU two waits of 1.6 us between kernels, which is most of a step of
+// a thousand ids.  One workgroup of up to 1 024 threads has barriers instead of launches, and what the phases hand to
+// each other (scratch set, places, counters, evicted rows) stays in LDS, so the call needs no scratch memory.  The
+// phases are those of mpzch_chunk_kernels.hpp.  Remap with row reset, us per call, against three launches: 64 to 512
+// positions 14 to 17.5 -> 7 to 9, 1 024 positions 13.8 to 17.7 -> 7.0 to 12.4; with two positions per thread (2 048) the
+// one compute unit took as long as three launches do (10.8 to 21.8 against 13.8 to 19.2), so the line is drawn at 1 024.
+#pragma once
+#include "mpzch_chunk_kernels.hpp"
+
+namespace mpzch {
+
+constexpr int kOneBlock = 1024;
+constexpr int kOneBlockWaves = kOneBlock / kWave;
+
+struct OneBlockArea {
+    ClaimReq req[kOneBlockWaves][kWave];                     // (Pass 1: the requests of its probes)
+    alignas(16) uint8_t code[kOneBlockWaves][kWave * kAllocG];
+    int64_t id[kOneBlock];                              // later: the rows to reset
+    uint32_t set[2 * kOneBlock];
+    uint32_t place[kOneBlock];
+    uint32_t count[kStatCount];                              // (probe lengths of 1 024 positions fit 32 bits)
+    MergeArea<kOneBlock, 2 * kOneBlock> merge;
+};
+
+template <bool REC>
+__global__ __launch_bounds__(kOneBlock) void k_remap_block(Params p)
+{
+    __shared__ OneBlockArea s;
+    const int lane = lane_id(), w = threadIdx.x / kWave, t = threadIdx.x, threads = blockDim.x;
+    const int n = (int)p.n;
+    const Tab d = view(p.t0);
+    ProbeReq *const s_probe = reinterpret_cast<ProbeReq *>(s.req[w]);
+
+    const bool in = t < n;
+    const uint32_t pos = (uint32_t)t;
+    const int64_t id = in ? p.ids[t] : -1;
+    const bool valid = in && id >= 0;
+    const int64_t home = home_slot(id, d.seed, d.N);
+    for (int i = t; i < 2 * threads; i += threads) s.set[i] = kSetEmpty;
+    if (t < kStatCount) s.count[t] = 0;
+    s.id[t] = id;
+    s.place[t] = 0;
+    __syncthreads();
+
+    // Pass 1.  (Blocks of the next 8 slots: round trips count here, not lines.)
+    bool fresh = false;
+    int res = probe_pass<kFirstG, false, REC>(d, id, home, valid ? 0 : d.P, s_probe, s.code[w], p.step, &fresh);
+    int q = kFirstG;
+    for (;;) {
+        const bool need = valid && res == kProbeGoOn && q < d.P;
+        if (!__any(need)) break;
+        bool f = false;
+        const int got = probe_more<false, REC>(d, id, home, q, need, s_probe, s.code[w], p.step, &f);
+        if (need) { res = got; fresh = f; }
+    }
+    const bool hit = valid && res >= 0, miss = valid && res < 0;
+    int64_t slot = hit ? wrap(home + res, d.N) : home;
+    uint32_t e = kNoEntry;
+    if (miss) {
+        const uint32_t size = 2u * (uint32_t)threads;
+        uint32_t at = (uint32_t)__umul64hi(mix64((uint64_t)id ^ kSetSeed), (uint64_t)size);
+        for (;;) {
+            uint32_t expected = kSetEmpty;
+            if (__hip_atomic_compare_exchange_strong(&s.set[at], &expected, pos, __ATOMIC_RELAXED, __ATOMIC_RELAXED,
+                                                     __HIP_MEMORY_SCOPE_WORKGROUP))
+                break;
+            if (s.id[expected] == id) {
+                if (pos < expected)
+                    __hip_atomic_fetch_min(&s.set[at], pos, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+                break;
+            }
+            if (++at == size) at = 0;
+        }
+        e = at;
+    }
+    store_meta_block(d, hit && !(REC && fresh && d.evict != 3), slot, hit ? meta_value(p, d, pos) : 0, s.merge);
+    if (p.out_stats) {
+        const uint32_t hits = (uint32_t)__popcll(__ballot(hit)), misses = (uint32_t)__popcll(__ballot(miss));
+        const uint32_t invalid = (uint32_t)__popcll(__ballot(in && !valid));
+        const uint32_t hit_len = wave_sum32(hit ? (uint32_t)res + 1u : 0u);
+        const uint32_t miss_len = wave_sum32(miss ? (uint32_t)(res <= kProbeAbsent ? absent_len(res) : d.P) : 0u);
+        if (lane == 0) {
+            atomicAdd(&s.count[kHitPos], hits);
+            atomicAdd(&s.count[kMissPos], misses);
+            atomicAdd(&s.count[kInvalidPos], invalid);
+            atomicAdd(&s.count[kHitProbeSum], hit_len);
+            atomicAdd(&s.count[kMissProbeSum], miss_len);
+        }
+    }
+    // every id that was resident has been refreshed, every first occurrence is elected
+    __syncthreads();
+
+    // claims
+    const int32_t bound = expiry_bound(d, p.step);
+    const uint32_t first = e != kNoEntry ? s.set[e] : kNoEntry;
+    uint32_t outcome = 0;                                    // 1 = this lane's last claim was an insert, 2 = an eviction
+    int64_t claimed = 0;
+    Claimant cl;
+    cl.active = first == pos;
+    cl.pos = pos;
+    cl.q = 0;
+    cl.home = home;
+    for (bool later = false;; later = true) {
+        const uint64_t am = __ballot(cl.active);
+        if (!am) break;
+        const int m = later ? blocks_shift(__popcll(am), d.P) : 0;
+        const int row = claim_blocks<false, REC>(d, d, cl, am, m, bound, false, s.code[w], s.req[w]);
+        if (cl.active)
+            claim_walk(d, cl, m, row, s.code[w], s.req[w],
+                       [&](uint32_t who, int32_t round, int64_t at, int64_t old) {
+                           atomicMax(&s.place[who], (uint32_t)round + 1u);
+                           outcome = old == -1 ? 1u : old >= 0 ? 2u : 0u;
+                           claimed = at;
+                       },
+                       [&](uint32_t who) {
+                           if (who != pos) atomicMax(&s.place[who], kPlaceNone);
+                       });
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    }
+    const uint64_t em = __ballot(outcome == 2u);
+    const uint32_t agents = (uint32_t)__popcll(__ballot(first == pos)), ins = (uint32_t)__popcll(__ballot(outcome == 1u));
+    uint32_t base = 0;
+    if (lane == 0) {
+        atomicAdd(&s.count[kDistinctMiss], agents);
+        atomicAdd(&s.count[kInserts], ins);
+        base = atomicAdd(&s.count[kEvictions], (uint32_t)__popcll(em));
+    }
+    base = (uint32_t)__builtin_amdgcn_readfirstlane((int)base);
+    if (outcome == 2u) {
+        const uint32_t at = base + (uint32_t)__popcll(em & ((1ull << lane) - 1ull));
+        if ((int64_t)at < p.t0.ev_cap) p.out_evicted[at] = claimed;
+        // (the ids in LDS are not looked at any more: the displaced are known by their position)
+        if (p.r_rows) s.id[at] = claimed >= p.g_num_rows ? claimed % p.g_num_rows : claimed;
+    }
+    // every claim stands
+    __syncthreads();
+
+    bool refresh = false;
+    if (first != kNoEntry) {
+        const uint32_t place = s.place[first];
+        const bool placed = place != 0 && place != kPlaceNone, agent = first == pos;
+        if (placed) slot = wrap(home + (int64_t)(place - 1u), d.N);
+        if (agent && placed) *id_at(d, slot) = id;
+        refresh = agent || (p.ttls && d.evict == 3);
+    }
+    if (in) p.out_slots[pos] = slot;
+    store_meta_block(d, refresh, slot, refresh ? meta_value(p, d, pos) : 0, s.merge);
+    const int evicted = (int)s.count[kEvictions];
+    if (p.r_rows && evicted > 0) {
+        const int waves = (threads + kWave - 1) / kWave, per = (evicted + waves - 1) / waves;
+        const int lo = w * per < evicted ? w * per : evicted;
+        const int hi = lo + per < evicted ? lo + per : evicted;
+        reset_staged_rows(p, s.id + lo, hi - lo);
+    }
+    if (t == 0) p.out_num_evicted[0] = evicted;
+    if (p.out_stats && t < kStatCount)
+        p.out_stats[t] = t == kCollisions ? (int64_t)(s.count[kDistinctMiss] - s.count[kInserts] - s.count[kEvictions])
+                                          : (int64_t)s.count[t];
+}
+
+}  // namespace mpzch

@@ -79,20 +79,24 @@ __device__ __forceinline__ uint64_t pack3(uint32_t a, uint32_t b, uint32_t c)
 __device__ __forceinline__ uint32_t unpack3(uint64_t w, int k) { return (uint32_t)(w >> (16 * k)) & 0xFFFFu; }
 
 // store_meta_wave over the workgroup (all threads reach it; barriers only where metadata is expiry steps).
-constexpr int kMergeCells = 512;
+template <int THREADS, int CELLS>
 struct MergeArea {
-    int64_t slot[kBlock];
-    int32_t value[kBlock];
-    uint16_t winner[kMergeCells];
+    int64_t slot[THREADS];
+    int32_t value[THREADS];
+    uint16_t winner[CELLS];
 };
-__device__ __forceinline__ void store_meta_block(const Tab &d, bool active, int64_t slot, int32_t value, MergeArea &s_m)
+template <int THREADS, int CELLS>
+__device__ __forceinline__ void store_meta_block(const Tab &d, bool active, int64_t slot, int32_t value,
+                                                 MergeArea<THREADS, CELLS> &s_m)
 {
+    static_assert((CELLS & (CELLS - 1)) == 0 && CELLS >= 2, "cells by the high bits of a product");
     if (d.evict != 3) {
         if (active) *meta_at(d, slot) = value;
         return;
     }
     const int t = threadIdx.x;
-    const int cell = (int)((uint32_t)slot * 0x9E3779B1u >> 23);
+    const int cell = (int)((uint32_t)slot * 0x9E3779B1u >> (32 - __builtin_ctz(CELLS)));
+    __syncthreads();                                 // the area may still be read from the call before
     s_m.slot[t] = active ? slot : -1;
     s_m.value[t] = value;
     if (active) s_m.winner[cell] = (uint16_t)t;
@@ -115,7 +119,7 @@ __global__ __launch_bounds__(kBlock, 4) void k_discover_chunk(Params p)
     __shared__ ProbeReq s_req[kWavesPerBlock][kWave];
     __shared__ __attribute__((aligned(16))) uint8_t s_code[kWavesPerBlock][kWave * kFirstG];
     __shared__ uint32_t s_red[kWavesPerBlock][5];
-    __shared__ MergeArea s_merge;
+    __shared__ MergeArea<kBlock, 2 * kBlock> s_merge;
 
     const int lane = lane_id(), w = threadIdx.x / kWave;
     const int64_t pos = (int64_t)blockIdx.x * kBlock + threadIdx.x;
@@ -312,7 +316,7 @@ __global__ __launch_bounds__(kBlock, 8) void k_finalize_chunk(Params p)
 {
     __shared__ int64_t s_row[kBlock];
     __shared__ unsigned long long s_sum[kWavesPerBlock];
-    __shared__ MergeArea s_merge;
+    __shared__ MergeArea<kBlock, 2 * kBlock> s_merge;
 
     const int64_t pos = (int64_t)blockIdx.x * kBlock + threadIdx.x;
     const bool in = pos < p.n;

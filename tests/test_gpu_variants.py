@@ -112,14 +112,14 @@ def test_crowded_windows(slots, probe, layout, evict):
     t.close()
 
 
-# ---- one chunk per wavefront up to 256 x 8 workgroups of 256 positions (256 compute units); lists beyond that
+# ---- one workgroup up to 1 024 positions, one chunk per wavefront up to 256 x 8 workgroups of 256 positions (256 compute units); lists beyond that
 @pytest.mark.parametrize("layout", ["separate", "records"])
 @pytest.mark.parametrize("evict,fused", [(True, True), (True, False), ("expiry", False), (False, False)])
 def test_batches_around_workgroup_multiples(evict, fused, layout):
     rng = rng_for(905)
     emb = wl.embedding_pattern(7_001, 12, np.float32)
     t = Pair(20_000, 16, 1, evict, 17, emb, layout, fused)
-    for step, n in enumerate([1, 63, 64, 65, 255, 256, 257, 511, 513, 1_024, 4_095, 20_001, 20_000, 7]):
+    for step, n in enumerate([1, 63, 64, 65, 255, 256, 257, 511, 513, 1_023, 1_024, 1_025, 4_095, 20_001, 20_000, 7]):
         ids = wl.zipf_ids(rng, n, 1.05, 60_000)
         ids[rng.random(n) < 0.02] = -5
         t.step(ids, 2 * step, init_row=np.full(12, 3.5, np.float32) if step % 2 else None,
