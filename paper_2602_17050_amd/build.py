@@ -10,6 +10,7 @@ SRC = os.path.join(HERE, "csrc", "mpzch.hip")
 DEPS = [SRC, os.path.join(HERE, "csrc", "mpzch_kernels.hpp"),
         os.path.join(HERE, "csrc", "mpzch_chunk_kernels.hpp"),
         os.path.join(HERE, "csrc", "mpzch_block_kernel.hpp"),
+        os.path.join(HERE, "csrc", "mpzch_row_kernels.hpp"),
         os.path.join(os.path.dirname(HERE), "include", "mpzch.h")]
 LIB = os.path.join(HERE, "libmpzch.so")
 CEIL_SRC = os.path.join(HERE, "csrc", "memory_ceilings.hip")

@@ -3,6 +3,7 @@
 // where the header says so (scratch growth, descriptor upload, timing read-out, destroy).
 #include "../../include/mpzch.h"
 #include "mpzch_block_kernel.hpp"
+#include "mpzch_row_kernels.hpp"
 
 #include <cstdlib>
 #include <cstring>
@@ -635,10 +636,12 @@ RowGeom row_geom(const void *rows, int64_t row_bytes, int64_t row_stride_bytes, 
     g.ok = g.chunks <= 0x7FFFFFFF;
     return g;
 }
+// (the number of rows lives on the device: the grid is sized for the capacity of the list, at most eight workgroups on
+// each of 256 compute units, which is all that run at a time; the kernels stride)
 int row_grid(int64_t items)
 {
     int64_t want = (items + kBlock - 1) / kBlock;
-    if (want > 8192) want = 8192;
+    if (want > 2048) want = 2048;
     if (want < 1) want = 1;
     return (int)want;
 }
@@ -848,16 +851,13 @@ mpzch_status_t mpzch_reset_rows(const int64_t *slots, const int64_t *num_slots_d
                       !((uintptr_t)init_row & 15);
     const int64_t chunks = wide ? row_bytes / 16 : row_bytes / 4;
     if (chunks > 0x7FFFFFFF) return MPZCH_ERR_INVALID_ARG;
-    // the count lives on the device: size the grid for the capacity, bounded; the kernel strides
-    int64_t want = (slots_cap * chunks + kBlock - 1) / kBlock;
-    if (want > 8192) want = 8192;
-    if (want < 1) want = 1;
+    const int grid = row_grid(slots_cap * chunks);
     if (wide)
-        hipLaunchKernelGGL((k_reset_rows<u32x4>), dim3((int)want), dim3(kBlock), 0, s, slots, num_slots_dev, slots_cap,
-                           (char *)rows, num_rows, (int32_t)chunks, row_stride_bytes, (const u32x4 *)init_row);
+        hipLaunchKernelGGL((k_reset_rows<u32x4>), dim3(grid), dim3(kBlock), 0, s, slots, num_slots_dev, slots_cap,
+                           (char *)rows, row_mod(num_rows), (int32_t)chunks, row_stride_bytes, (const u32x4 *)init_row);
     else
-        hipLaunchKernelGGL((k_reset_rows<uint32_t>), dim3((int)want), dim3(kBlock), 0, s, slots, num_slots_dev,
-                           slots_cap, (char *)rows, num_rows, (int32_t)chunks, row_stride_bytes,
+        hipLaunchKernelGGL((k_reset_rows<uint32_t>), dim3(grid), dim3(kBlock), 0, s, slots, num_slots_dev,
+                           slots_cap, (char *)rows, row_mod(num_rows), (int32_t)chunks, row_stride_bytes,
                            (const uint32_t *)init_row);
     LAUNCH_CHECK();
     return MPZCH_OK;
@@ -884,7 +884,7 @@ mpzch_status_t mpzch_reset_rows_multi(const int64_t *slots, const int64_t *num_s
         const mpzch_rows_t &t = tensors[i];
         ds.t[i].rows = (char *)t.rows;
         ds.t[i].init_row = t.init_row;
-        ds.t[i].num_rows = t.num_rows;
+        ds.t[i].mod = row_mod(t.num_rows);
         ds.t[i].row_stride_bytes = t.row_stride_bytes;
         ds.t[i].chunks = (int32_t)(wide ? t.row_bytes / 16 : t.row_bytes / 4);
         total += ds.t[i].chunks;
@@ -915,10 +915,10 @@ mpzch_status_t mpzch_gather_rows(const int64_t *slots, const int64_t *count_dev,
     const int grid = row_grid(cap * g.chunks);
     if (g.wide)
         hipLaunchKernelGGL((k_gather_rows<u32x4>), dim3(grid), dim3(kBlock), 0, s, slots, count_dev, cap, (const char *)rows,
-                           num_rows, (int32_t)g.chunks, row_stride_bytes, (u32x4 *)out_rows);
+                           row_mod(num_rows), (int32_t)g.chunks, row_stride_bytes, (u32x4 *)out_rows);
     else
         hipLaunchKernelGGL((k_gather_rows<uint32_t>), dim3(grid), dim3(kBlock), 0, s, slots, count_dev, cap,
-                           (const char *)rows, num_rows, (int32_t)g.chunks, row_stride_bytes, (uint32_t *)out_rows);
+                           (const char *)rows, row_mod(num_rows), (int32_t)g.chunks, row_stride_bytes, (uint32_t *)out_rows);
     LAUNCH_CHECK();
     return MPZCH_OK;
 }
@@ -976,10 +976,17 @@ mpzch_status_t mpzch_collect_delta(const mpzch_table_t *t, const int64_t *identi
     int num_cus = 0;
     TRY(device_cus(&num_cus));
     TRY(fill64(out_count, 1, 0, s));
-    const int grid = grid_for(t->cfg.num_slots, 4 * kBlock, num_cus, 8);
-    hipLaunchKernelGGL(k_collect_delta, dim3(grid), dim3(kBlock), 0, s, identities, metadata,
-                       t->cfg.layout == MPZCH_LAYOUT_RECORDS ? 1 : 0, t->cfg.num_slots,
-                       since_step, out_slots, out_ids, cap, (unsigned long long *)out_count);
+    // every workgroup scans a whole number of steps
+    const int64_t steps = (t->cfg.num_slots + kDeltaSlots - 1) / kDeltaSlots;
+    const int64_t most = (int64_t)num_cus * kDeltaBlocksPerCu;
+    const int64_t per_block = (steps + most - 1) / most * kDeltaSlots;       // (below 2^32: num_slots <= MPZCH_MAX_SLOTS)
+    const int grid = (int)((t->cfg.num_slots + per_block - 1) / per_block);
+    if (t->cfg.layout == MPZCH_LAYOUT_RECORDS)
+        hipLaunchKernelGGL((k_collect_delta<true>), dim3(grid), dim3(kDeltaBlock), 0, s, identities, metadata, t->cfg.num_slots,
+                           per_block, since_step, out_slots, out_ids, cap, (unsigned long long *)out_count);
+    else
+        hipLaunchKernelGGL((k_collect_delta<false>), dim3(grid), dim3(kDeltaBlock), 0, s, identities, metadata, t->cfg.num_slots,
+                           per_block, since_step, out_slots, out_ids, cap, (unsigned long long *)out_count);
     LAUNCH_CHECK();
     return MPZCH_OK;
 }
@@ -1003,10 +1010,10 @@ mpzch_status_t mpzch_apply_delta(int64_t *identities, int64_t num_slots,
         const int grid = row_grid(cap * g.chunks);
         if (g.wide)
             hipLaunchKernelGGL((k_apply_delta_rows<u32x4>), dim3(grid), dim3(kBlock), 0, s, num_slots, slots, count_dev, cap,
-                               (char *)rows, num_rows, (int32_t)g.chunks, row_stride_bytes, (const u32x4 *)delta_rows);
+                               (char *)rows, row_mod(num_rows), (int32_t)g.chunks, row_stride_bytes, (const u32x4 *)delta_rows);
         else
             hipLaunchKernelGGL((k_apply_delta_rows<uint32_t>), dim3(grid), dim3(kBlock), 0, s, num_slots, slots, count_dev,
-                               cap, (char *)rows, num_rows, (int32_t)g.chunks, row_stride_bytes,
+                               cap, (char *)rows, row_mod(num_rows), (int32_t)g.chunks, row_stride_bytes,
                                (const uint32_t *)delta_rows);
         LAUNCH_CHECK();
     }
@@ -1174,7 +1181,7 @@ mpzch_status_t mpzch_reset_rows_jagged(mpzch_group_t *g, const int64_t *evicted_
         JagRows &d = descs[f];
         d.rows = (char *)t.rows;
         d.init_row = t.init_row;
-        d.num_rows = t.num_rows;
+        d.mod = row_mod(t.num_rows);
         d.row_stride_bytes = t.row_stride_bytes;
         d.ev_begin = evicted_offsets[f];
         d.ev_cap = cap;

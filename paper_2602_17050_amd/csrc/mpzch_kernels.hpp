@@ -1929,217 +1929,4 @@ __global__ __launch_bounds__(kBlock) void k_fill32(int32_t *dst, int64_t count, 
         dst[i] = value;
 }
 
-// rows[(slots[k] mod num_rows)] <- init (or zero bits).  One thread per VEC-byte chunk of a row,
-// so a row is written by consecutive lanes with full-width stores.
-
-template <typename VEC>
-__global__ __launch_bounds__(kBlock) void k_reset_rows(const int64_t *slots, const int64_t *count_dev, int64_t cap,
-                                                        char *rows, int64_t num_rows, int32_t chunks_per_row,
-                                                        int64_t row_stride_bytes, const VEC *init_row)
-{
-    int64_t count = *count_dev;
-    if (count > cap) count = cap;
-    if (count < 0) count = 0;
-    const int64_t total = count * chunks_per_row;
-    for (int64_t i = (int64_t)blockIdx.x * kBlock + threadIdx.x; i < total; i += (int64_t)gridDim.x * kBlock) {
-        const int64_t k = i / chunks_per_row;
-        const int32_t c = (int32_t)(i - k * chunks_per_row);
-        int64_t s = slots[k];
-        if (s < 0) continue;
-        if (s >= num_rows) s %= num_rows;
-        VEC v = VEC(0);
-        if (init_row) v = init_row[c];
-        VEC *dst = reinterpret_cast<VEC *>(rows + s * row_stride_bytes) + c;
-        __builtin_nontemporal_store(v, dst);
-    }
-}
-
-// rows[(slots[k] mod num_rows)] <- init for several tensors at once (embedding weights and
-// optimizer state, Sec. 3.4): one thread per VEC-byte chunk of a row of one tensor.
-struct RowsDesc {
-    char *rows;
-    const void *init_row;
-    int64_t num_rows;
-    int64_t row_stride_bytes;
-    int32_t chunks;          // VEC-sized chunks per row
-    int32_t pad_;
-};
-constexpr int kMaxResetTensors = 4;
-struct RowsDescs {
-    RowsDesc t[kMaxResetTensors];
-    int32_t count;
-    int32_t total_chunks;
-};
-
-template <typename VEC>
-__global__ __launch_bounds__(kBlock) void k_reset_rows_multi(const int64_t *slots, const int64_t *count_dev, int64_t cap,
-                                                              RowsDescs ds)
-{
-    int64_t count = *count_dev;
-    if (count > cap) count = cap;
-    if (count < 0) count = 0;
-    const int64_t total = count * ds.total_chunks;
-    for (int64_t i = (int64_t)blockIdx.x * kBlock + threadIdx.x; i < total; i += (int64_t)gridDim.x * kBlock) {
-        const int64_t k = i / ds.total_chunks;
-        int32_t c = (int32_t)(i - k * ds.total_chunks);
-        int which = 0;
-        while (which + 1 < ds.count && c >= ds.t[which].chunks) { c -= ds.t[which].chunks; ++which; }
-        const RowsDesc &t = ds.t[which];
-        int64_t s = slots[k];
-        if (s < 0) continue;
-        if (s >= t.num_rows) s %= t.num_rows;
-        VEC v = VEC(0);
-        if (t.init_row) v = reinterpret_cast<const VEC *>(t.init_row)[c];
-        __builtin_nontemporal_store(v, reinterpret_cast<VEC *>(t.rows + s * t.row_stride_bytes) + c);
-    }
-}
-
-// Row reset for a group of tables in one launch: table f's evicted slots are
-// slots[ev_begin .. ev_begin + min(counts[f], ev_cap)), its rows are reset as in k_reset_rows.
-struct JagRows {
-    char *rows;               // null: nothing to reset for this table
-    const void *init_row;
-    int64_t num_rows;
-    int64_t row_stride_bytes;
-    int64_t ev_begin;
-    int64_t ev_cap;
-    int32_t chunks;           // 16-byte (wide) or 4-byte chunks per row
-    int32_t wide;
-};
-
-__global__ __launch_bounds__(kBlock) void k_reset_rows_jagged(const int64_t *slots, const int64_t *counts,
-                                                               const JagRows *tables, int num_tables)
-{
-    for (int f = 0; f < num_tables; ++f) {
-        const JagRows t = tables[f];
-        if (!t.rows) continue;
-        int64_t count = counts[f];
-        if (count > t.ev_cap) count = t.ev_cap;
-        if (count < 0) count = 0;
-        const int64_t total = count * t.chunks;
-        for (int64_t i = (int64_t)blockIdx.x * kBlock + threadIdx.x; i < total; i += (int64_t)gridDim.x * kBlock) {
-            const int64_t k = i / t.chunks;
-            const int32_t c = (int32_t)(i - k * t.chunks);
-            int64_t s = slots[t.ev_begin + k];
-            if (s < 0) continue;
-            if (s >= t.num_rows) s %= t.num_rows;
-            char *row = t.rows + s * t.row_stride_bytes;
-            if (t.wide) {
-                u32x4 v = u32x4(0);
-                if (t.init_row) v = reinterpret_cast<const u32x4 *>(t.init_row)[c];
-                __builtin_nontemporal_store(v, reinterpret_cast<u32x4 *>(row) + c);
-            } else {
-                uint32_t v = 0u;
-                if (t.init_row) v = reinterpret_cast<const uint32_t *>(t.init_row)[c];
-                __builtin_nontemporal_store(v, reinterpret_cast<uint32_t *>(row) + c);
-            }
-        }
-    }
-}
-
-// out[k, :] <- rows[slots[k] mod num_rows, :]   (dense output rows of chunks * sizeof(VEC) bytes)
-template <typename VEC>
-__global__ __launch_bounds__(kBlock) void k_gather_rows(const int64_t *slots, const int64_t *count_dev, int64_t cap,
-                                                         const char *rows, int64_t num_rows, int32_t chunks,
-                                                         int64_t row_stride_bytes, VEC *out)
-{
-    int64_t count = count_dev ? *count_dev : cap;
-    if (count > cap) count = cap;
-    if (count < 0) count = 0;
-    const int64_t total = count * chunks;
-    for (int64_t i = (int64_t)blockIdx.x * kBlock + threadIdx.x; i < total; i += (int64_t)gridDim.x * kBlock) {
-        const int64_t k = i / chunks;
-        const int32_t c = (int32_t)(i - k * chunks);
-        int64_t s = slots[k];
-        VEC v = VEC(0);
-        if (s >= 0) {
-            if (s >= num_rows) s %= num_rows;
-            v = reinterpret_cast<const VEC *>(rows + s * row_stride_bytes)[c];
-        }
-        out[i] = v;
-    }
-}
-
-// Streaming delta, receiving side (Sec. 3.8): rows[slots[k] mod num_rows, :] <- delta_rows[k, :] in one launch
-// and identities[slots[k]] <- ids[k] in the next one on the same stream, so that every row of the delta
-// has landed before any identity points at it (a reader on another stream never finds a new id in
-// front of a row that is still partly old).
-template <typename VEC>
-__global__ __launch_bounds__(kBlock) void k_apply_delta_rows(int64_t num_slots, const int64_t *slots,
-                                                              const int64_t *count_dev, int64_t cap,
-                                                              char *rows, int64_t num_rows, int32_t chunks,
-                                                              int64_t row_stride_bytes, const VEC *delta_rows)
-{
-    int64_t count = count_dev ? *count_dev : cap;
-    if (count > cap) count = cap;
-    if (count < 0) count = 0;
-    const int64_t total = count * chunks;
-    for (int64_t i = (int64_t)blockIdx.x * kBlock + threadIdx.x; i < total; i += (int64_t)gridDim.x * kBlock) {
-        const int64_t k = i / chunks;
-        const int32_t c = (int32_t)(i - k * chunks);
-        const int64_t s = slots[k];
-        if (s < 0 || s >= num_slots) continue;
-        const int64_t r = s >= num_rows ? s % num_rows : s;
-        reinterpret_cast<VEC *>(rows + r * row_stride_bytes)[c] = delta_rows[i];
-    }
-}
-
-__global__ __launch_bounds__(kBlock) void k_apply_delta_ids(int64_t *identities, int64_t num_slots, const int64_t *slots,
-                                                             const int64_t *ids, const int64_t *count_dev, int64_t cap)
-{
-    int64_t count = count_dev ? *count_dev : cap;
-    if (count > cap) count = cap;
-    if (count < 0) count = 0;
-    for (int64_t k = (int64_t)blockIdx.x * kBlock + threadIdx.x; k < count; k += (int64_t)gridDim.x * kBlock) {
-        const int64_t s = slots[k];
-        if (s < 0 || s >= num_slots) continue;
-        __hip_atomic_store(&identities[s], ids[k], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    }
-}
-
-// Streaming delta, sending side (Sec. 3.8): every occupied slot whose metadata is >= since goes to the
-// list (slot, id), order unspecified.  A workgroup scans a contiguous range of slots, stages its finds in
-// LDS and appends them with one reservation per kDeltaStage finds.
-constexpr int kDeltaStage = 1024;
-constexpr int kDeltaPerThread = 4;     // slots a thread looks at between two workgroup barriers
-
-__global__ __launch_bounds__(kBlock) void k_collect_delta(const int64_t *identities, const int32_t *metadata, int sh,
-                                                          int64_t num_slots, int32_t since, int64_t *out_slots,
-                                                          int64_t *out_ids, int64_t cap, unsigned long long *out_count)
-{
-    __shared__ int64_t s_slot[kDeltaStage + kDeltaPerThread * kBlock];
-    __shared__ int s_n;
-    __shared__ unsigned long long s_base;
-    const int64_t per_block = (num_slots + gridDim.x - 1) / gridDim.x;
-    const int64_t lo = (int64_t)blockIdx.x * per_block;
-    const int64_t hi = lo + per_block < num_slots ? lo + per_block : num_slots;
-    if (threadIdx.x == 0) s_n = 0;
-    __syncthreads();
-    auto flush = [&]() {       // reached by all threads, with the staging complete and s_n at rest
-        const int n = s_n;
-        if (threadIdx.x == 0 && n) s_base = atomicAdd(out_count, (unsigned long long)n);
-        __syncthreads();       // everyone has read s_n and sees s_base
-        for (int i = threadIdx.x; i < n; i += kBlock) {
-            const int64_t at = (int64_t)s_base + i;
-            if (at < cap) { out_slots[at] = s_slot[i]; out_ids[at] = identities[s_slot[i] << sh]; }
-        }
-        if (threadIdx.x == 0) s_n = 0;
-        __syncthreads();       // the staging area is free again before anyone adds to it
-    };
-    for (int64_t base = lo; base < hi; base += kDeltaPerThread * kBlock) {
-#pragma unroll
-        for (int k = 0; k < kDeltaPerThread; ++k) {
-            const int64_t s = base + k * kBlock + threadIdx.x;
-            if (s < hi && identities[s << sh] >= 0 && metadata[s << (2 * sh)] >= since) s_slot[atomicAdd(&s_n, 1)] = s;
-        }
-        __syncthreads();
-        // The decision to flush is taken by all threads from the same value: s_n does not change
-        // between the barrier above and the one inside flush (or the one below).
-        const bool full = s_n > kDeltaStage;
-        if (full) flush();
-        else __syncthreads();  // nobody adds to s_n before everyone has looked at it
-    }
-    flush();
-}
-
 }  // namespace mpzch

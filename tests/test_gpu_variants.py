@@ -4,6 +4,7 @@ import numpy as np
 import pytest
 import torch
 
+from paper_2602_17050_amd import binding as mp
 from paper_2602_17050_amd import workloads as wl
 from gpu_common import Pair
 
@@ -147,4 +148,48 @@ def test_expiry_steps_of_popular_ids(n, layout):
         ids[rng.random(n) < 0.3] = 77 + step % 2          # one id at a third of the positions, new every other time
         t.step(ids, step, ttls=rng.integers(0, 1_000, size=n).astype(np.int32))
         t.step(ids, step)
+    t.close()
+
+
+# ---- the scan of the streaming delta in steps of 2 048 slots per workgroup, the row movers in pieces
+@pytest.mark.parametrize("layout", ["separate", "records"])
+@pytest.mark.parametrize("slots,rows,dim", [(1, 1, 1), (63, 7, 3), (2_047, 2_047, 4), (2_049, 1_000, 5), (300_001, 299_999, 12),
+                                            (2_098_177, 100_003, 20)])
+def test_delta_round_trip_at_edges(slots, rows, dim, layout):
+    """Collect, gather and apply at sizes around a step, a workgroup's range and a row's pieces (4 and 16 bytes)."""
+    rng = rng_for(907)
+    ids = np.where(rng.random(slots) < 0.6, rng.integers(0, 1 << 62, size=slots), -1).astype(np.int64)
+    meta = rng.integers(-1, 6, size=slots).astype(np.int32)
+    ids[-1], meta[-1] = 77, 5                                     # the last slot belongs to every delta
+    t = mp.MpzchTable(slots, 8, mp.EVICT_TTL, 1, 5, layout=mp.LAYOUT_RECORDS if layout == "records" else mp.LAYOUT_SEPARATE)
+    t.identities.copy_(torch.from_numpy(ids).cuda())
+    t.metadata.copy_(torch.from_numpy(meta).cuda())
+    emb = torch.from_numpy(wl.embedding_pattern(rows, dim, np.float32)).cuda()
+    count = torch.zeros(1, dtype=torch.int64, device="cuda")
+    for since in (-(1 << 31), 0, 5, 6):
+        d_slots = torch.full((slots,), -1, dtype=torch.int64, device="cuda")
+        d_ids = torch.full_like(d_slots, -1)
+        mp.mpzch_collect_delta(t.handle, t.identities, t.metadata, since, d_slots, d_ids, count)
+        want = np.flatnonzero((ids >= 0) & (meta >= since))
+        n = int(count.item())
+        got = d_slots[:n].cpu().numpy()
+        order = np.argsort(got)
+        assert np.array_equal(got[order], want) and np.array_equal(d_ids[:n].cpu().numpy()[order], ids[want])
+        payload = torch.full((slots, dim), 7.0, dtype=torch.float32, device="cuda")
+        mp.mpzch_gather_rows(d_slots, count, emb, payload)
+        assert torch.equal(payload[:n], emb[d_slots[:n] % rows]) and bool((payload[n:] == 7.0).all())
+        inf_ids = torch.full((slots,), -1, dtype=torch.int64, device="cuda")
+        inf_rows = torch.zeros_like(emb)
+        mp.mpzch_apply_delta(inf_ids, d_slots, d_ids, count, inf_rows, payload)
+        full = np.full(slots, -1, np.int64)
+        full[want] = ids[want]
+        assert np.array_equal(inf_ids.cpu().numpy(), full)
+        touched = torch.zeros(rows, dtype=torch.bool, device="cuda")
+        touched[d_slots[:n] % rows] = True
+        assert torch.equal(inf_rows, emb * touched[:, None])
+        mp.mpzch_reset_rows(d_slots, count, inf_rows)
+        assert not bool(inf_rows.any())
+        inf_rows.copy_(emb)
+        mp.mpzch_reset_rows_multi(d_slots, count, [inf_rows, inf_ids.view(slots, 1).view(torch.float32)])
+        assert torch.equal(inf_rows, emb * ~touched[:, None]) and not bool((inf_ids == torch.from_numpy(full).cuda())[d_slots[:n]].any())
     t.close()
