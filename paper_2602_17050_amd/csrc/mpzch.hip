@@ -286,16 +286,26 @@ mpzch_status_t launch_discover(const Params &p, int grid, hipStream_t s)
 }
 
 // max_p_lru: largest min(max_probe, num_slots) of the LRU tables involved, 0 when there is none
-template <bool MULTI>
+template <bool MULTI, bool REC>
 void launch_allocate_lru(int32_t max_p_lru, const Params &p, int grid, hipStream_t s)
 {
     // a group of 8, 16, 32 or 64 lanes per claimant, whichever holds its window; the whole wavefront
     // with several slots per lane for longer probe ranges
     if (max_p_lru > kWave) hipLaunchKernelGGL((k_allocate_lru_long<MULTI>), dim3(grid), dim3(kWave), 0, s, p);
-    else if (max_p_lru <= 8) hipLaunchKernelGGL((k_allocate_lru<8, MULTI>), dim3(grid), dim3(kWave), 0, s, p);
-    else if (max_p_lru <= 16) hipLaunchKernelGGL((k_allocate_lru<16, MULTI>), dim3(grid), dim3(kWave), 0, s, p);
-    else if (max_p_lru <= 32) hipLaunchKernelGGL((k_allocate_lru<32, MULTI>), dim3(grid), dim3(kWave), 0, s, p);
-    else hipLaunchKernelGGL((k_allocate_lru<64, MULTI>), dim3(grid), dim3(kWave), 0, s, p);
+    else if (max_p_lru <= 8) hipLaunchKernelGGL((k_allocate_lru<8, MULTI, REC>), dim3(grid), dim3(kWave), 0, s, p);
+    else if (max_p_lru <= 16) hipLaunchKernelGGL((k_allocate_lru<16, MULTI, REC>), dim3(grid), dim3(kWave), 0, s, p);
+    else if (max_p_lru <= 32) hipLaunchKernelGGL((k_allocate_lru<32, MULTI, REC>), dim3(grid), dim3(kWave), 0, s, p);
+    else hipLaunchKernelGGL((k_allocate_lru<64, MULTI, REC>), dim3(grid), dim3(kWave), 0, s, p);
+}
+
+// the same where every wavefront has one chunk (max_p_lru <= 64)
+template <bool REC>
+void launch_allocate_lru_chunk(int32_t max_p_lru, const Params &p, int grid, hipStream_t s)
+{
+    if (max_p_lru <= 8) hipLaunchKernelGGL((k_allocate_lru_chunk<8, REC>), dim3(grid), dim3(kLruBlock), 0, s, p);
+    else if (max_p_lru <= 16) hipLaunchKernelGGL((k_allocate_lru_chunk<16, REC>), dim3(grid), dim3(kLruBlock), 0, s, p);
+    else if (max_p_lru <= 32) hipLaunchKernelGGL((k_allocate_lru_chunk<32, REC>), dim3(grid), dim3(kLruBlock), 0, s, p);
+    else hipLaunchKernelGGL((k_allocate_lru_chunk<64, REC>), dim3(grid), dim3(kLruBlock), 0, s, p);
 }
 
 mpzch_status_t launch_allocate(int32_t max_p_lru, const Params &p, int num_cus, hipStream_t s)
@@ -308,9 +318,11 @@ mpzch_status_t launch_allocate(int32_t max_p_lru, const Params &p, int num_cus, 
         if (p.all_records) hipLaunchKernelGGL((k_allocate<true, true>), dim3(grid), dim3(kWave), 0, s, p);
         else hipLaunchKernelGGL((k_allocate<true, false>), dim3(grid), dim3(kWave), 0, s, p);
         LAUNCH_CHECK();
-        if (max_p_lru > 0) launch_allocate_lru<true>(max_p_lru, p, grid, s);
+        if (max_p_lru > 0 && p.all_records) launch_allocate_lru<true, true>(max_p_lru, p, grid, s);
+        else if (max_p_lru > 0) launch_allocate_lru<true, false>(max_p_lru, p, grid, s);
     } else if (max_p_lru > 0) {
-        launch_allocate_lru<false>(max_p_lru, p, grid, s);
+        if (p.t0.sh) launch_allocate_lru<false, true>(max_p_lru, p, grid, s);
+        else launch_allocate_lru<false, false>(max_p_lru, p, grid, s);
     } else {
         if (p.t0.sh) hipLaunchKernelGGL((k_allocate<false, true>), dim3(grid), dim3(kWave), 0, s, p);
         else hipLaunchKernelGGL((k_allocate<false, false>), dim3(grid), dim3(kWave), 0, s, p);
@@ -374,7 +386,7 @@ mpzch_status_t run_remap(Scratch &sc, Timing &tm, const Params &p, int32_t max_p
 }
 
 // One chunk per wavefront (mpzch_chunk_kernels.hpp): grid = workgroups of 256 positions.
-mpzch_status_t launch_remap_chunks(Timing &tm, const Params &p, int grid, hipStream_t s)
+mpzch_status_t launch_remap_chunks(Timing &tm, const Params &p, int32_t max_p_lru, int grid, hipStream_t s)
 {
     const bool rec = p.t0.sh != 0;
     if (!tm.begin(KDiscover, s)) return MPZCH_ERR_HIP;
@@ -382,7 +394,9 @@ mpzch_status_t launch_remap_chunks(Timing &tm, const Params &p, int grid, hipStr
     else hipLaunchKernelGGL((k_discover_chunk<false>), dim3(grid), dim3(kBlock), 0, s, p);
     LAUNCH_CHECK();
     if (!tm.end(s) || !tm.begin(KAllocate, s)) return MPZCH_ERR_HIP;
-    if (rec) hipLaunchKernelGGL((k_allocate_chunk<true>), dim3(grid), dim3(kBlock), 0, s, p);
+    if (max_p_lru > 0 && rec) launch_allocate_lru_chunk<true>(max_p_lru, p, grid, s);
+    else if (max_p_lru > 0) launch_allocate_lru_chunk<false>(max_p_lru, p, grid, s);
+    else if (rec) hipLaunchKernelGGL((k_allocate_chunk<true>), dim3(grid), dim3(kBlock), 0, s, p);
     else hipLaunchKernelGGL((k_allocate_chunk<false>), dim3(grid), dim3(kBlock), 0, s, p);
     LAUNCH_CHECK();
     if (!tm.end(s) || !tm.begin(KFinalize, s)) return MPZCH_ERR_HIP;
@@ -408,9 +422,10 @@ mpzch_status_t launch_remap(Scratch &sc, Timing &tm, Params p, int32_t max_p_lru
 
     // one table, and no wavefront of Pass 1 has more than one chunk
     const int64_t groups = (p.n + kBlock - 1) / kBlock;
-    if (p.num_tables == 1 && max_p_lru == 0 && groups <= (int64_t)sc.num_cus * discover_blocks_per_cu() &&
+    // (the LRU policy with windows of more than 64 slots gives a claimant the whole wavefront)
+    if (p.num_tables == 1 && max_p_lru <= kWave && groups <= (int64_t)sc.num_cus * discover_blocks_per_cu() &&
         p.n < ((int64_t)1 << kChunkPosBits))
-        return launch_remap_chunks(tm, p, (int)groups, s);
+        return launch_remap_chunks(tm, p, max_p_lru, (int)groups, s);
 
     const int64_t num_chunks = (p.n + kWave - 1) / kWave;
     // k_discover: every wavefront owns one segment of seg_chunks 64-position chunks

@@ -114,9 +114,7 @@ __global__ __launch_bounds__(kOneBlock) void k_remap_block(Params p)
                            outcome = old == -1 ? 1u : old >= 0 ? 2u : 0u;
                            claimed = at;
                        },
-                       [&](uint32_t who) {
-                           if (who != pos) atomicMax(&s.place[who], kPlaceNone);
-                       });
+                       [&](uint32_t who) { atomicMax(&s.place[who], kPlaceNone); });
         __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
     }
     const uint64_t em = __ballot(outcome == 2u);

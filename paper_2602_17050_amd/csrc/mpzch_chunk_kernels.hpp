@@ -23,7 +23,8 @@
 namespace mpzch {
 
 constexpr uint32_t kNoEntry = 0xFFFFFFFFu;       // ent[pos]: the position did not miss
-constexpr uint32_t kPlaceNone = 0xFFFFFFFFu;     // place[pos]: displaced and out of slots.  0: never placed.  Else round + 1.
+constexpr uint32_t kPlaceNone = 0xFFFFFFFFu;     // place[pos]: displaced and out of slots.  0: never placed.  Else round + 1;
+                                                 // under the LRU policy choice << 16 | round + 1
 
 // Scratch set of these calls: an entry is the batch position with 12 bits of the id's hash above it, so that two ids that
 // meet in one entry tell each other apart without a look at the batch (a round trip per collision; with every
@@ -183,8 +184,9 @@ __global__ __launch_bounds__(kBlock, 4) void k_discover_chunk(Params p)
 
 // What the lanes of a workgroup leave for k_finalize_chunk: which evicted which slot (evicted: lanes with a slot in
 // `slot`), and the workgroup's outcome counts.  Reached by all threads.
+template <int WAVES>
 __device__ __forceinline__ void leave_outcomes(const Params &p, bool agent, bool inserted, bool evicted, int64_t slot,
-                                               uint32_t (*s_red)[3])
+                                               uint32_t (&s_red)[WAVES][3])
 {
     const int lane = lane_id(), w = threadIdx.x / kWave;
     const uint64_t em = __ballot(evicted);
@@ -200,7 +202,7 @@ __device__ __forceinline__ void leave_outcomes(const Params &p, bool agent, bool
     if (evicted) p.homes[(int64_t)blockIdx.x * kBlock + before + __popcll(em & ((1ull << lane) - 1ull))] = slot;
     if (threadIdx.x == 0) {
         uint32_t t[3] = {0, 0, 0};
-        for (int i = 0; i < kWavesPerBlock; ++i)
+        for (int i = 0; i < WAVES; ++i)
             for (int k = 0; k < 3; ++k) t[k] += s_red[i][k];
         p.wg_words[3 * blockIdx.x + 2] = pack3(t[0], t[1], t[2]);
     }
@@ -253,13 +255,82 @@ __global__ __launch_bounds__(kBlock, 4) void k_allocate_chunk(Params p)
                            evicted = old >= 0;
                            slot = at;
                        },
-                       [&](uint32_t who) {
-                           if (who != (uint32_t)pos) note_place(p, who, kPlaceNone);
-                       });
+                       // (also for the lane's own: its chain may come back to it, in a table hardly longer than a window)
+                       [&](uint32_t who) { note_place(p, who, kPlaceNone); });
         __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");   // s_code and s_req are written again
     }
     if (have) p.list[pos] = first;
-    leave_outcomes(p, have && first == (uint32_t)pos, inserted, evicted, slot, s_red);
+    leave_outcomes<kWavesPerBlock>(p, have && first == (uint32_t)pos, inserted, evicted, slot, s_red);
+}
+
+// The claims under the LRU policy (max_probe <= G <= 64).  The workgroup first lists its claimants, so that its 512 / G
+// groups of lanes get them evenly: a wavefront of 64 positions has a handful, which it would serve one or two at a time
+// (300 007 positions, 10 % of them claimants with windows of 32 slots: 43 -> 16 us).
+constexpr int kLruBlock = 512;
+template <int G, bool REC>
+__global__ __launch_bounds__(kLruBlock, 8) void k_allocate_lru_chunk(Params p)
+{
+    constexpr int WAVES = kLruBlock / kWave, GROUPS = kLruBlock / G;
+    __shared__ __attribute__((aligned(16))) uint64_t s_key[kLruBlock];
+    __shared__ int64_t s_home[kBlock];
+    __shared__ int64_t s_slot[kBlock];               // of the claimant's chain of claims: the slot not claimed before
+    __shared__ uint32_t s_pos[kBlock];
+    __shared__ uint8_t s_outcome[kBlock];            // 0: none, 1: it was empty, 2: it held an id
+    __shared__ uint32_t s_red[WAVES][3];
+    const int lane = lane_id(), w = threadIdx.x / kWave;
+    const Tab d = view(p.t0);
+    const int64_t pos = (int64_t)blockIdx.x * kBlock + threadIdx.x;
+    const bool in = (int)threadIdx.x < kBlock && pos < p.n;
+    const uint32_t e = in ? p.ent[pos] : kNoEntry;
+    const int64_t id = in ? p.ids[pos] : -1;
+    const bool have = e != kNoEntry;
+    uint32_t first = 0;
+    if (have) {
+        first = p.set_slot[e] & kChunkPosMask;
+        p.list[pos] = first;
+    }
+    const bool agent = have && first == (uint32_t)pos;
+    const uint64_t am = __ballot(agent);
+    if (lane == 0) s_red[w][0] = (uint32_t)__popcll(am);
+    __syncthreads();
+    int at = __popcll(am & ((1ull << lane) - 1ull)), count = 0;
+    for (int i = 0; i < WAVES; ++i) {
+        if (i < w) at += (int)s_red[i][0];
+        count += (int)s_red[i][0];
+    }
+    if (agent) {
+        s_pos[at] = (uint32_t)pos;
+        s_home[at] = home_slot(id, d.seed, d.N);
+        s_outcome[at] = 0;
+    }
+    __syncthreads();
+    const int g = (int)threadIdx.x / G;
+    int i = g;
+    int64_t home = i < count ? s_home[i] : 0;
+    LruSlot x = load_lru_slot<G, REC>(d, i < count, home);
+    for (; __any(i < count); i += GROUPS) {
+        // the window of the next claimant is requested before this one is served
+        const bool more = i + GROUPS < count;
+        const int64_t home2 = more ? s_home[i + GROUPS] : 0;
+        const LruSlot x2 = load_lru_slot<G, REC>(d, more, home2);
+        claim_group_lru<G, REC>(p, d, i < count, i < count ? s_pos[i] : 0u, home, x, s_key + w * kWave,
+                                [&](uint32_t who, int32_t choice, int32_t round, int64_t slot, int64_t old) {
+                                    if (lane % G != 0) return;
+                                    note_place(p, who, (uint32_t)choice << 16 | (uint32_t)(round + 1));
+                                    if (is_tag(old)) return;
+                                    s_slot[i] = slot;
+                                    s_outcome[i] = old == -1 ? 1 : 2;
+                                },
+                                [&](uint32_t who) {
+                                    if (lane % G == 0) note_place(p, who, kPlaceNone);
+                                });
+        home = home2;
+        x = x2;
+    }
+    __syncthreads();
+    const bool mine = (int)threadIdx.x < count;
+    const int outcome = mine ? s_outcome[threadIdx.x] : 0;
+    leave_outcomes<WAVES>(p, mine, outcome == 1, outcome == 2, outcome == 2 ? s_slot[threadIdx.x] : 0, s_red);
 }
 
 // Sum over the workgroup, in every thread.  s_sum: one word per wavefront; to be reached by all threads.
@@ -338,6 +409,7 @@ __global__ __launch_bounds__(kBlock, 8) void k_finalize_chunk(Params p)
         p.set_slot[e] = kSetEmpty;                   // the scratch set is left empty again
         const bool placed = place != 0 && place != kPlaceNone;
         const int64_t home = home_slot(id, d.seed, d.N);
+        if (d.evict == 2) place &= 0xFFFFu;
         slot = placed ? wrap(home + (int64_t)(place - 1u), d.N) : home;
         // the claim becomes the id, metadata gets its value (Algorithm 1, Pass 2); without a claim: Case 3, the home
         // slot's metadata is refreshed; with per-feature retention a later copy may ask for a later expiry step

@@ -1307,91 +1307,111 @@ __global__ __launch_bounds__(kWave, MULTI ? 5 : 7) void k_allocate(Params p)
 // k_finalize.  The tag's round field carries the CHOICE number, so a slot ends with the claimant
 // of the lowest (choice, position).  A group of G lanes serves one claimant, one lane per slot of
 // its window (max_probe <= G <= 64; longer ranges: claim_wave_lru_long), so a wavefront works on
-// 64 / G claimants at a time; a
-// displaced claimant is carried on by the group that displaced it, from its next choice.
-// active, cpos and choice are uniform within a group.  Returns the probe round at which the
-// group's first claimant was placed, or -1.
-template <int G>
-__device__ __forceinline__ int32_t claim_group_lru(const Params &p, const Tab &d, bool active, uint32_t cpos,
-                                                   int32_t choice)
+// 64 / G claimants at a time; a displaced claimant is carried on by the group that displaced it, from its next choice.
+//
+// A claimant is a chain of two round trips, window and atomic.  What lies between them goes through LDS: every lane reads
+// the keys of its group's slots, 16 bytes at a time, and counts the smaller ones (by shuffles, two for each slot of
+// the window, the ranking took longer than the loads).
+
+// What a lane of a claimant's group has read of its slot of the window.
+struct LruSlot {
+    int64_t v;
+    int32_t m;
+};
+template <int G, bool REC>
+__device__ __forceinline__ LruSlot load_lru_slot(const Tab &d, bool active, int64_t home)
+{
+    const int r = lane_id() % G;
+    // (a lane without a slot reads one that is there)
+    const int64_t s = active && r < d.P ? wrap(home + r, d.N) : 0;
+    LruSlot x;
+    if constexpr (REC) {
+        const u32x3 rec = *(global_ptr<u32x3>)id_at(d, s);
+        x.v = (int64_t)(((uint64_t)rec.y << 32) | rec.x);
+        x.m = (int32_t)rec.z;
+    } else {
+        x.v = *id_at(d, s);
+        x.m = *meta_at(d, s);
+    }
+    return x;
+}
+
+// active, cpos and home are uniform within a group, x: what its lanes have read of the window; s_key: 64 words of LDS of
+// this wavefront.  placed(pos, choice, round, slot, old) is called for every claim that stands, old being what the slot
+// held before; lost(pos) for a claimant that has run out of slots; both by all lanes of the group.
+template <int G, bool REC, typename Placed, typename Lost>
+__device__ __forceinline__ void claim_group_lru(const Params &p, const Tab &d, bool active, uint32_t cpos, int64_t home,
+                                                LruSlot x, uint64_t *s_key, Placed placed, Lost lost)
 {
     const int lane = lane_id();
     const int r = lane % G, gbase = lane - r;
     const uint64_t gmask = G == kWave ? ~0ull : ((1ull << (G % kWave)) - 1ull) << gbase;
     const uint64_t below = (1ull << lane) - 1ull;
-    int32_t first_round = -1;
-    bool is_first = true;
+    int32_t choice = 0;
     while (__any(active)) {
         const bool in = active && r < d.P;
-        int64_t s = 0, v = 0;
-        int32_t m = 0;
-        if (in) {
-            s = wrap(home_slot(p.ids[cpos], d.seed, d.N) + r, d.N);
-            v = __hip_atomic_load(id_at(d, s), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            m = *meta_at(d, s);
-        }
-        const bool base_empty = in && (v == -1 || (is_tag(v) && !tag_occ(v)));
-        const bool evictable = in && (v >= 0 || (is_tag(v) && tag_occ(v))) && m != p.step;
+        const bool occ = is_tag(x.v) ? tag_occ(x.v) != 0 : x.v >= 0;      // the slot held an id when the call began
+        const bool base_empty = in && !occ;
+        const bool evictable = in && occ && x.m != p.step;
         const uint64_t emask = __ballot(base_empty) & gmask;
-        const uint64_t vmask = __ballot(evictable) & gmask;
         const int n_empty = __popcll(emask);
+        const int n_choices = n_empty + __popcll(__ballot(evictable) & gmask);
         // rank of this lane's slot in the claimant's preference list
+        const uint64_t key = evictable ? ((uint64_t)((uint32_t)x.m ^ 0x80000000u) << 32) | (uint32_t)r : ~0ull;
+        s_key[lane] = key;
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
         int older = 0;
-        for (int l = 0; l < G; ++l) {
-            const int32_t ml = __shfl(m, gbase + l);
-            const bool el = (vmask >> (gbase + l)) & 1ull;
-            if (el && (ml < m || (ml == m && l < r))) ++older;
+#pragma unroll 4
+        for (int l = 0; l < G; l += 2) {
+            const ulonglong2 k = *reinterpret_cast<const ulonglong2 *>(s_key + gbase + l);
+            older += k.x < key ? 1 : 0;
+            older += k.y < key ? 1 : 0;
         }
-        int rank = 0x7FFFFFFF;
-        if (base_empty) rank = __popcll(emask & below);
-        else if (evictable) rank = n_empty + older;
-        const int n_choices = n_empty + __popcll(vmask);
-        bool placed = false;
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+        const int rank = base_empty ? __popcll(emask & below) : evictable ? n_empty + older : 0x7FFFFFFF;
         int64_t displaced = 0;
         bool trying = active && choice < n_choices;
+        if (active && !trying) lost(cpos);
         while (__any(trying)) {
             const uint64_t wb = __ballot(trying && rank == choice) & gmask;
             const int who = __ffsll((unsigned long long)wb) - 1;      // exactly one lane of a trying group has this rank
-            int64_t old = 0, mine = 0;
-            if (lane == who) {
-                mine = make_tag((uint32_t)choice, cpos, base_empty ? 0u : 1u);
-                old = __hip_atomic_fetch_min(id_at(d, s), mine, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            }
             const int from = who >= 0 ? who : lane;
+            const int64_t mine = make_tag((uint32_t)choice, cpos, (emask >> from) & 1ull ? 0u : 1u);
+            const int64_t s = wrap(home + (from - gbase), d.N);
+            int64_t old = 0;
+            if (lane == who) old = __hip_atomic_fetch_min(id_at(d, s), mine, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
             old = shfl64(old, from);
-            mine = shfl64(mine, from);
             if (trying) {
                 if (is_tag(old) && old < mine) {
                     ++choice;                                           // a better claim holds this slot
                     trying = choice < n_choices;
+                    if (!trying) lost(cpos);
                 } else {
-                    placed = true;
+                    placed(cpos, choice, from - gbase, s, old);
                     displaced = is_tag(old) ? old : 0;
-                    if (is_first) first_round = who - gbase;
                     trying = false;
                 }
             }
         }
-        is_first = false;
+        active = active && displaced != 0;
         if (active) {
-            if (!placed || !displaced) {
-                active = false;
-            } else {
-                cpos = tag_pos(displaced);                               // same table: same slot
-                choice = (int32_t)tag_round(displaced) + 1;
-            }
+            cpos = tag_pos(displaced);                                   // same table: same slot
+            choice = (int32_t)tag_round(displaced) + 1;
+            home = home_slot(p.ids[cpos], d.seed, d.N);
         }
+        if (__any(active)) x = load_lru_slot<G, REC>(d, active, home);
     }
-    return first_round;
 }
 
 // One workgroup = one wavefront.  With several tables this kernel runs after k_allocate, which has
 // written the hints of every list entry and skipped the claimants of LRU tables; here only those
-// claimants are served and only their hints are written.
-template <int G, bool MULTI>
-__global__ __launch_bounds__(kWave) void k_allocate_lru(Params p)
+// claimants are served and only their hints are written.  The windows of the next claimants are requested before the
+// present ones are served.
+template <int G, bool MULTI, bool REC>
+__global__ __launch_bounds__(kWave, MULTI ? 5 : 6) void k_allocate_lru(Params p)
 {
     constexpr int NG = kWave / G;
+    __shared__ __attribute__((aligned(16))) uint64_t s_key[kWave];
     const int lane = threadIdx.x;
     const int g = lane / G;
     const Tab d0 = view(MULTI ? p.descs[0] : p.t0);
@@ -1403,11 +1423,13 @@ __global__ __launch_bounds__(kWave) void k_allocate_lru(Params p)
             const int64_t idx = seg_base + j0 + lane;
             const bool have = j0 + lane < cnt;
             uint32_t pos = 0, e = 0, first = 0;
+            int64_t home = 0;
             bool agent = false;
             int f = 0;
             if (have) {
                 pos = p.list[idx];
                 e = p.ent[idx];
+                home = p.homes[idx];
                 first = p.set_slot[e];
                 agent = first == pos;
                 if (MULTI && agent) {
@@ -1417,19 +1439,28 @@ __global__ __launch_bounds__(kWave) void k_allocate_lru(Params p)
             }
             uint32_t hint = kHintNone;
             uint64_t am = __ballot(agent);
-            while (am) {
-                // the next NG claimants, one per group of lanes
-                int src = -1;
-#pragma unroll
-                for (int k = 0; k < NG; ++k) {
-                    const int sk = am ? __ffsll((unsigned long long)am) - 1 : -1;
-                    am &= am - 1;                                         // 0 stays 0
-                    if (k == g) src = sk;
-                }
-                const uint32_t cpos = __shfl(pos, src >= 0 ? src : lane);
-                const int fs = __shfl(f, src >= 0 ? src : lane);
-                const Tab d = (MULTI && src >= 0) ? view(p.descs[fs]) : d0;
-                const int32_t fr = claim_group_lru<G>(p, d, src >= 0, cpos, 0);
+            // the next NG claimants, one per group of lanes: the lane that holds this group's one, or -1
+            int src = next_bits<G>(am, g);
+            uint32_t cpos = __shfl(pos, src >= 0 ? src : lane);
+            int64_t chome = shfl64(home, src >= 0 ? src : lane);
+            const int f1 = __shfl(f, src >= 0 ? src : lane);
+            Tab d = d0;
+            if (MULTI && src >= 0) d = view(p.descs[f1]);
+            LruSlot x = load_lru_slot<G, REC>(d, src >= 0, chome);
+            while (__any(src >= 0)) {
+                const int src2 = next_bits<G>(am, g);
+                const uint32_t cpos2 = __shfl(pos, src2 >= 0 ? src2 : lane);
+                const int64_t chome2 = shfl64(home, src2 >= 0 ? src2 : lane);
+                const int f2 = __shfl(f, src2 >= 0 ? src2 : lane);
+                Tab d2 = d0;
+                if (MULTI && src2 >= 0) d2 = view(p.descs[f2]);
+                const LruSlot x2 = load_lru_slot<G, REC>(d2, src2 >= 0, chome2);
+                int32_t fr = -1;
+                claim_group_lru<G, REC>(p, d, src >= 0, cpos, chome, x, s_key,
+                                        [&](uint32_t who, int32_t, int32_t round, int64_t, int64_t) {
+                                            if (who == cpos) fr = round;
+                                        },
+                                        [](uint32_t) {});
                 // the outcome goes to the lane that holds the claimant's list entry
 #pragma unroll
                 for (int k = 0; k < NG; ++k) {
@@ -1437,6 +1468,11 @@ __global__ __launch_bounds__(kWave) void k_allocate_lru(Params p)
                     const int32_t frk = __shfl(fr, k * G);
                     if (lane == sk) hint = frk < 0 ? kHintUnplaced : (uint32_t)frk;
                 }
+                src = src2;
+                cpos = cpos2;
+                chome = chome2;
+                d = d2;
+                x = x2;
             }
             if (agent) p.hint[pos] = (uint8_t)hint;
             if (agent) p.first_of[idx] = kAgentEntry | hint;

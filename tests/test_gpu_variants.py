@@ -193,3 +193,20 @@ def test_delta_round_trip_at_edges(slots, rows, dim, layout):
         mp.mpzch_reset_rows_multi(d_slots, count, [inf_rows, inf_ids.view(slots, 1).view(torch.float32)])
         assert torch.equal(inf_rows, emb * ~touched[:, None]) and not bool((inf_ids == torch.from_numpy(full).cuda())[d_slots[:n]].any())
     t.close()
+
+
+# ---- LRU claims: one group of lanes per claimant, listed per workgroup where every wavefront has one chunk
+@pytest.mark.parametrize("layout", ["separate", "records"])
+@pytest.mark.parametrize("slots,probe", [(3, 8), (700, 1), (900, 8), (3_001, 9), (3_001, 16), (5_003, 31), (5_003, 33), (5_003, 64),
+                                         (5_003, 65)])
+def test_lru_claims(slots, probe, layout):
+    """Batches from one position to several workgroups of claimants that contend for few slots; calls beyond the
+    largest one-chunk call too."""
+    rng = rng_for(908)
+    t = Pair(slots, probe, 0, "lru", 17, layout=layout)
+    for step, n in enumerate([1, 63, 257, 300, 1_025, 4_000, 4_000, 20_011, 2]):
+        t.step(wl.zipf_ids(rng, n, 1.02, 6 * slots), step)
+    t.step(wl.zipf_ids(rng, 530_000, 1.02, 3 * slots), 9)
+    t.step(rng.integers(0, 2 * slots, size=2_000), 9)
+    t.step(rng.integers(0, 9 * slots, size=2_000), 10)
+    t.close()
