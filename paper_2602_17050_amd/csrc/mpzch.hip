@@ -132,7 +132,7 @@ struct Scratch {
     uint32_t *list = nullptr;
     uint32_t *ent = nullptr;
     uint32_t *first_of = nullptr;
-    int64_t *homes = nullptr;
+    int64_t *list_id = nullptr;
     uint8_t *hint = nullptr;
     uint32_t *seg_cnt = nullptr;
     uint32_t *set_slot = nullptr;
@@ -153,7 +153,7 @@ struct Scratch {
     // Where each array sits inside an area that serves batches of up to n positions: 29 bytes per
     // position and a few small fixed areas.
     struct Layout {
-        size_t o_list, o_ent, o_first, o_homes, o_hint, o_seg, o_set, o_ctl, total;
+        size_t o_list, o_ent, o_first, o_list_id, o_hint, o_seg, o_set, o_ctl, total;
     };
     static Layout layout_for(int64_t n, int num_cus)
     {
@@ -163,8 +163,8 @@ struct Scratch {
         L.o_list = 0;
         L.o_ent = L.o_list + align_up(per_pos);
         L.o_first = L.o_ent + align_up(per_pos);
-        L.o_homes = L.o_first + align_up(per_pos);
-        L.o_hint = L.o_homes + align_up(2 * per_pos);
+        L.o_list_id = L.o_first + align_up(per_pos);
+        L.o_hint = L.o_list_id + align_up(2 * per_pos);
         L.o_seg = L.o_hint + align_up((size_t)n + kWave);
         L.o_set = L.o_seg + align_up(4 * max_blocks * kWavesPerBlock);
         L.o_ctl = L.o_set + align_up(8 * (size_t)n);
@@ -177,7 +177,7 @@ struct Scratch {
         list = (uint32_t *)(base + L.o_list);
         ent = (uint32_t *)(base + L.o_ent);
         first_of = (uint32_t *)(base + L.o_first);
-        homes = (int64_t *)(base + L.o_homes);
+        list_id = (int64_t *)(base + L.o_list_id);
         hint = (uint8_t *)(base + L.o_hint);
         seg_cnt = (uint32_t *)(base + L.o_seg);
         set_slot = (uint32_t *)(base + L.o_set);
@@ -333,8 +333,8 @@ mpzch_status_t launch_allocate(int32_t max_p_lru, const Params &p, int num_cus, 
 
 mpzch_status_t launch_finalize(const Params &p, int grid, hipStream_t s)
 {
-    if (p.num_tables > 1) hipLaunchKernelGGL((k_finalize<true>), dim3(grid), dim3(kBlock), 0, s, p);
-    else hipLaunchKernelGGL((k_finalize<false>), dim3(grid), dim3(kBlock), 0, s, p);
+    if (p.num_tables > 1) hipLaunchKernelGGL((k_finalize<true>), dim3(grid), dim3(kFinalizeBlock), 0, s, p);
+    else hipLaunchKernelGGL((k_finalize<false>), dim3(grid), dim3(kFinalizeBlock), 0, s, p);
     LAUNCH_CHECK();
     return MPZCH_OK;
 }
@@ -412,7 +412,8 @@ mpzch_status_t launch_remap(Scratch &sc, Timing &tm, Params p, int32_t max_p_lru
     p.ent = sc.ent;
     p.first_of = sc.first_of;
     p.hint = sc.hint;
-    p.homes = sc.homes;
+    p.list_id = sc.list_id;
+    p.evicted = sc.list_id;
     p.seg_cnt = sc.seg_cnt;
     p.set_slot = sc.set_slot;
     p.ctl = sc.ctl;
@@ -433,7 +434,7 @@ mpzch_status_t launch_remap(Scratch &sc, Timing &tm, Params p, int32_t max_p_lru
     p.num_segs = g_disc * kWavesPerBlock;
     p.seg_chunks = (int32_t)((num_chunks + p.num_segs - 1) / p.num_segs);
     // the other kernels walk the segments' miss lists, one segment per wavefront pass
-    const int g_grp = grid_for((int64_t)p.num_segs, kWavesPerBlock, sc.num_cus, group_blocks_per_cu());
+    const int g_grp = grid_for((int64_t)p.num_segs, kFinalizeWaves, sc.num_cus, 2);
 
     TIMED(tm, KDiscover, s, (launch_discover<true>(p, g_disc, s)));
     TIMED(tm, KAllocate, s, launch_allocate(max_p_lru, p, sc.num_cus, s));

@@ -199,7 +199,7 @@ __device__ __forceinline__ void leave_outcomes(const Params &p, bool agent, bool
     __syncthreads();
     uint32_t before = 0;
     for (int i = 0; i < w; ++i) before += s_red[i][2];
-    if (evicted) p.homes[(int64_t)blockIdx.x * kBlock + before + __popcll(em & ((1ull << lane) - 1ull))] = slot;
+    if (evicted) p.evicted[(int64_t)blockIdx.x * kBlock + before + __popcll(em & ((1ull << lane) - 1ull))] = slot;
     if (threadIdx.x == 0) {
         uint32_t t[3] = {0, 0, 0};
         for (int i = 0; i < WAVES; ++i)
@@ -271,7 +271,6 @@ template <int G, bool REC>
 __global__ __launch_bounds__(kLruBlock, 8) void k_allocate_lru_chunk(Params p)
 {
     constexpr int WAVES = kLruBlock / kWave, GROUPS = kLruBlock / G;
-    __shared__ __attribute__((aligned(16))) uint64_t s_key[kLruBlock];
     __shared__ int64_t s_home[kBlock];
     __shared__ int64_t s_slot[kBlock];               // of the claimant's chain of claims: the slot not claimed before
     __shared__ uint32_t s_pos[kBlock];
@@ -313,7 +312,7 @@ __global__ __launch_bounds__(kLruBlock, 8) void k_allocate_lru_chunk(Params p)
         const bool more = i + GROUPS < count;
         const int64_t home2 = more ? s_home[i + GROUPS] : 0;
         const LruSlot x2 = load_lru_slot<G, REC>(d, more, home2);
-        claim_group_lru<G, REC>(p, d, i < count, i < count ? s_pos[i] : 0u, home, x, s_key + w * kWave,
+        claim_group_lru<G, REC>(p, d, i < count, i < count ? s_pos[i] : 0u, home, x,
                                 [&](uint32_t who, int32_t choice, int32_t round, int64_t slot, int64_t old) {
                                     if (lane % G != 0) return;
                                     note_place(p, who, (uint32_t)choice << 16 | (uint32_t)(round + 1));
@@ -424,7 +423,7 @@ __global__ __launch_bounds__(kBlock, 8) void k_finalize_chunk(Params p)
         for (int i = threadIdx.x; i < (int)blockIdx.x; i += kBlock) base += unpack3(p.wg_words[3 * i + 2], 2);
         base = block_sum(base, s_sum);
         if ((int)threadIdx.x < evicted) {
-            const int64_t s = p.homes[(int64_t)blockIdx.x * kBlock + threadIdx.x];
+            const int64_t s = p.evicted[(int64_t)blockIdx.x * kBlock + threadIdx.x];
             const int64_t at = (int64_t)base + threadIdx.x;
             if (at < p.t0.ev_cap) p.out_evicted[at] = s;
             if (p.r_rows) s_row[threadIdx.x] = s >= p.g_num_rows ? s % p.g_num_rows : s;

@@ -76,6 +76,10 @@ struct Control {
 // k_finalize reports in by adding kArriveOne to `done`.  With one table the same atomic also reserves the
 // workgroup's part of the evicted list, whose length is kept in the low bits of `done` (num_evicted[0]
 // stays unused): one round trip to one address at the end of a workgroup instead of two to two.
+// Workgroups of 16 wavefronts: at 12 ns each the arrivals of 2 048 workgroups of four took 25 us, however little
+// there was to do (batch of 700 K positions 35 -> 19 us).
+constexpr int kFinalizeBlock = 1024;
+constexpr int kFinalizeWaves = kFinalizeBlock / kWave;
 constexpr int kArriveShift = 40;
 constexpr unsigned long long kArriveOne = 1ull << kArriveShift;
 constexpr unsigned long long kEvictedMask = kArriveOne - 1ull;
@@ -90,17 +94,18 @@ struct Params {
     uint8_t *out_found;            // lookup only, may be null
     // scratch.  Segment s (one wavefront of k_discover) covers the 64-position chunks
     // [s * seg_chunks, (s + 1) * seg_chunks); its missed positions are list[s * seg_chunks * 64 + k]
-    // for k < seg_cnt[s]; ent and first_of run parallel to list.
+    // for k < seg_cnt[s]; ent, list_id and first_of run parallel to list.
     uint32_t *list;
     uint32_t *ent;                 // entry of the position's id in the scratch set
-    int64_t *homes;                // home slot of the position's id
+    int64_t *list_id;              // the position's id (read back in one piece: in the batch it is one of a line of sixteen)
     uint32_t *first_of;            // position of the first occurrence of the position's id
     uint8_t *hint;                 // by batch position: round at which k_allocate placed the claim of the id
                                    // elected there (written for elected positions only)
     uint32_t *seg_cnt;
     // one chunk per wavefront (mpzch_chunk_kernels.hpp): by batch position, where the claim of the id elected there
-    // ended up; and three words of counters per workgroup
+    // ended up; by workgroup, the slots evicted by its claimants; and three words of counters per workgroup
     uint32_t *place;
+    int64_t *evicted;
     uint64_t *wg_words;
     int32_t seg_chunks;
     int32_t num_segs;
@@ -370,9 +375,10 @@ __device__ __forceinline__ unsigned long long *stat_word(const Params &p, int ta
 // Sums counters (each the wavefront's total) over the workgroup and adds them to this workgroup's copy of the call's
 // counters: one atomic per counter when all its wavefronts ended on the same table (the rule), one
 // per wavefront and counter otherwise.  Must be reached by all threads of the workgroup.
+template <int WAVES>
 __device__ __forceinline__ void block_stat_add(const Params &p, const int *idx, const unsigned long long *vals,
-                                               int count, int table, unsigned long long (*s_red)[kStatCount],
-                                               int *s_tab)
+                                               int count, int table, unsigned long long (&s_red)[WAVES][kStatCount],
+                                               int (&s_tab)[WAVES])
 {
     const int lane = lane_id(), w = threadIdx.x / kWave;
     if (lane == 0) {
@@ -383,13 +389,13 @@ __device__ __forceinline__ void block_stat_add(const Params &p, const int *idx, 
     if ((int)threadIdx.x < count) {
         const int k = idx[threadIdx.x];
         bool same = true;
-        for (int i = 1; i < kWavesPerBlock; ++i) same = same && s_tab[i] == s_tab[0];
+        for (int i = 1; i < WAVES; ++i) same = same && s_tab[i] == s_tab[0];
         if (same) {
             unsigned long long v = 0;
-            for (int i = 0; i < kWavesPerBlock; ++i) v += s_red[i][k];
+            for (int i = 0; i < WAVES; ++i) v += s_red[i][k];
             if (v) atomicAdd(stat_word(p, s_tab[0], k), v);
         } else {
-            for (int i = 0; i < kWavesPerBlock; ++i)
+            for (int i = 0; i < WAVES; ++i)
                 if (s_red[i][k]) atomicAdd(stat_word(p, s_tab[i], k), s_red[i][k]);
         }
     }
@@ -397,11 +403,12 @@ __device__ __forceinline__ void block_stat_add(const Params &p, const int *idx, 
 
 // Sums the kBins copies of the call's counters, writes out_num_evicted / out_stats and clears the block.
 // Run by the workgroup that finishes last (of k_finalize; of a counting lookup).
+template <int THREADS>
 __device__ __forceinline__ void publish_counters(const Params &p, unsigned long long (*s_bins)[kStatCount])
 {
     if (p.out_num_evicted) {
         if (p.num_tables > 1) {
-            for (int i = threadIdx.x; i < p.num_tables; i += kBlock)
+            for (int i = threadIdx.x; i < p.num_tables; i += THREADS)
                 p.out_num_evicted[i] =
                     (int64_t)__hip_atomic_load(&p.ctl->num_evicted[i], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         } else if (threadIdx.x == 0) {
@@ -411,7 +418,7 @@ __device__ __forceinline__ void publish_counters(const Params &p, unsigned long 
     }
     if (p.out_stats) {
         const int nbins = p.num_tables * kStatCount;
-        for (int i = threadIdx.x; i < nbins; i += kBlock) {
+        for (int i = threadIdx.x; i < nbins; i += THREADS) {
             unsigned long long v = 0;
             for (int b = 0; b < kBins; ++b)
                 v += __hip_atomic_load(&p.ctl->stats[b][i / kStatCount][i % kStatCount], __ATOMIC_RELAXED,
@@ -419,15 +426,15 @@ __device__ __forceinline__ void publish_counters(const Params &p, unsigned long 
             s_bins[i / kStatCount][i % kStatCount] = v;
         }
         __syncthreads();
-        for (int t = threadIdx.x; t < p.num_tables; t += kBlock)
+        for (int t = threadIdx.x; t < p.num_tables; t += THREADS)
             s_bins[t][kDistinctMiss] = s_bins[t][kInserts] + s_bins[t][kEvictions] + s_bins[t][kCollisions];
         __syncthreads();
-        for (int i = threadIdx.x; i < nbins; i += kBlock)
+        for (int i = threadIdx.x; i < nbins; i += THREADS)
             p.out_stats[i] = (int64_t)s_bins[i / kStatCount][i % kStatCount];
     }
     __syncthreads();
     unsigned long long *z = reinterpret_cast<unsigned long long *>(p.ctl);
-    for (int i = threadIdx.x; i < (int)(sizeof(Control) / sizeof(unsigned long long)); i += kBlock) z[i] = 0ull;
+    for (int i = threadIdx.x; i < (int)(sizeof(Control) / sizeof(unsigned long long)); i += THREADS) z[i] = 0ull;
 }
 
 // ------------------------------------------------------------------ Pass 1 (discovery)
@@ -844,32 +851,23 @@ __device__ __forceinline__ void discover_body(const Params &p)
         }
         if (TRAIN) {
             __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-            // (read through lane 0: as plain copies the compiler would fold them with the per-lane descriptor
-            // loads of the last branch below into loads through a selected pointer, which puts t_d in memory)
-            const uint64_t c_seed = (uint64_t)uniform64((int64_t)t_d.seed);
-            const int64_t c_n = uniform64(t_d.N);
             for (int j = lane; j < nmiss; j += kWave) {
                 const uint32_t pos = s_pos[w][j];
                 const int64_t id = s_id[w][j];
                 uint64_t sb, ss;
-                int64_t home;
                 if (!multi) {
                     sb = 0;
                     ss = 2ull * (uint64_t)p.n;
-                    home = home_slot(id, p.t0.seed, p.t0.N);
                 } else if (all_cached) {
                     sb = 2ull * (uint64_t)t_lo;
                     ss = 2ull * (uint64_t)(t_hi - t_lo);
-                    home = home_slot(id, c_seed, c_n);
                 } else {
                     set_region(p, (int64_t)pos, sb, ss);
-                    const int tf = find_table(p.offsets, p.num_tables, (int64_t)pos);
-                    home = home_slot(id, s_desc[tf].seed, s_desc[tf].N);
                 }
                 const uint32_t e = set_insert(p, id, pos, sb, ss);
                 p.list[seg_base + flushed + j] = pos;
                 p.ent[seg_base + flushed + j] = e;
-                p.homes[seg_base + flushed + j] = home;
+                p.list_id[seg_base + flushed + j] = id;
             }
             flushed += nmiss;
         }
@@ -959,7 +957,7 @@ __device__ __forceinline__ void discover_body(const Params &p)
         __syncthreads();
         if (threadIdx.x == 0) s_last = atomicAdd(&p.ctl->done, 1ull) == (unsigned long long)(gridDim.x - 1);
         __syncthreads();
-        if (s_last) publish_counters(p, s_bins);
+        if (s_last) publish_counters<kBlock>(p, s_bins);
     }
 }
 
@@ -1236,7 +1234,7 @@ __device__ __forceinline__ void allocate_body(const Params &p, int64_t vblock, i
             const int64_t idx = seg_base + j0 + lane;
             const uint32_t pos = p.list[idx];
             const uint32_t e = p.ent[idx];
-            int64_t home = p.homes[idx];
+            const int64_t id = p.list_id[idx];
             if (j0 >= cnt) break;
             const bool have = j0 + lane < cnt;
             bool agent = false;
@@ -1265,7 +1263,7 @@ __device__ __forceinline__ void allocate_body(const Params &p, int64_t vblock, i
             c.active = agent;
             c.pos = pos;
             c.q = 0;
-            c.home = home;
+            c.home = home_slot(id, d.seed, d.N);
             for (bool later = false;; later = true) {
                 const uint64_t am = __ballot(c.active);
                 if (!am) break;
@@ -1309,9 +1307,10 @@ __global__ __launch_bounds__(kWave, MULTI ? 5 : 7) void k_allocate(Params p)
 // its window (max_probe <= G <= 64; longer ranges: claim_wave_lru_long), so a wavefront works on
 // 64 / G claimants at a time; a displaced claimant is carried on by the group that displaced it, from its next choice.
 //
-// A claimant is a chain of two round trips, window and atomic.  What lies between them goes through LDS: every lane reads
-// the keys of its group's slots, 16 bytes at a time, and counts the smaller ones (by shuffles, two for each slot of
-// the window, the ranking took longer than the loads).
+// A claimant is a chain of two round trips, window and atomic, and with windows requested ahead what counts is the
+// number of instructions in between: the list is not ranked, its next choice is drawn when it is needed, which for nearly
+// every claimant is once (2 M positions, windows of 32, 220 K claimants: ranked by two shuffles per slot of the window
+// more than twice as long, ranked through LDS 78, drawn 56 us).
 
 // What a lane of a claimant's group has read of its slot of the window.
 struct LruSlot {
@@ -1336,61 +1335,72 @@ __device__ __forceinline__ LruSlot load_lru_slot(const Tab &d, bool active, int6
     return x;
 }
 
-// active, cpos and home are uniform within a group, x: what its lanes have read of the window; s_key: 64 words of LDS of
-// this wavefront.  placed(pos, choice, round, slot, old) is called for every claim that stands, old being what the slot
-// held before; lost(pos) for a claimant that has run out of slots; both by all lanes of the group.
+// Minimum over the G lanes of a group, in every lane of it.
+template <int CTRL>
+__device__ __forceinline__ int32_t min_with(int32_t x)
+{
+    const int32_t y = __builtin_amdgcn_update_dpp(x, x, CTRL, 0xF, 0xF, false);
+    return y < x ? y : x;
+}
+template <int G>
+__device__ __forceinline__ int32_t group_min(int32_t x)
+{
+    x = min_with<0xB1>(x);                           // quad_perm 1 0 3 2
+    x = min_with<0x4E>(x);                           // quad_perm 2 3 0 1
+    x = min_with<0x141>(x);                          // row_half_mirror: 8 lanes
+    if constexpr (G >= 16) x = min_with<0x140>(x);   // row_mirror: 16 lanes
+    for (int o = 16; o < G; o <<= 1) {
+        const int32_t y = __shfl_xor(x, o);
+        x = y < x ? y : x;
+    }
+    return x;
+}
+
+// active, cpos and home are uniform within a group, x: what its lanes have read of the window.  placed(pos, choice, round,
+// slot, old) is called for every claim that stands, old being what the slot held before; lost(pos) for a claimant that
+// has run out of slots; both by all lanes of the group.
 template <int G, bool REC, typename Placed, typename Lost>
 __device__ __forceinline__ void claim_group_lru(const Params &p, const Tab &d, bool active, uint32_t cpos, int64_t home,
-                                                LruSlot x, uint64_t *s_key, Placed placed, Lost lost)
+                                                LruSlot x, Placed placed, Lost lost)
 {
     const int lane = lane_id();
     const int r = lane % G, gbase = lane - r;
     const uint64_t gmask = G == kWave ? ~0ull : ((1ull << (G % kWave)) - 1ull) << gbase;
-    const uint64_t below = (1ull << lane) - 1ull;
     int32_t choice = 0;
     while (__any(active)) {
         const bool in = active && r < d.P;
         const bool occ = is_tag(x.v) ? tag_occ(x.v) != 0 : x.v >= 0;      // the slot held an id when the call began
-        const bool base_empty = in && !occ;
-        const bool evictable = in && occ && x.m != p.step;
-        const uint64_t emask = __ballot(base_empty) & gmask;
-        const int n_empty = __popcll(emask);
-        const int n_choices = n_empty + __popcll(__ballot(evictable) & gmask);
-        // rank of this lane's slot in the claimant's preference list
-        const uint64_t key = evictable ? ((uint64_t)((uint32_t)x.m ^ 0x80000000u) << 32) | (uint32_t)r : ~0ull;
-        s_key[lane] = key;
-        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-        int older = 0;
-#pragma unroll 4
-        for (int l = 0; l < G; l += 2) {
-            const ulonglong2 k = *reinterpret_cast<const ulonglong2 *>(s_key + gbase + l);
-            older += k.x < key ? 1 : 0;
-            older += k.y < key ? 1 : 0;
-        }
-        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-        const int rank = base_empty ? __popcll(emask & below) : evictable ? n_empty + older : 0x7FFFFFFF;
+        // what has not been drawn yet
+        uint64_t empties = __ballot(in && !occ) & gmask;
+        bool evictable = in && occ && x.m != p.step;
+        int32_t drawn = 0;
         int64_t displaced = 0;
-        bool trying = active && choice < n_choices;
-        if (active && !trying) lost(cpos);
+        bool trying = active;
         while (__any(trying)) {
-            const uint64_t wb = __ballot(trying && rank == choice) & gmask;
-            const int who = __ffsll((unsigned long long)wb) - 1;      // exactly one lane of a trying group has this rank
-            const int from = who >= 0 ? who : lane;
-            const int64_t mine = make_tag((uint32_t)choice, cpos, (emask >> from) & 1ull ? 0u : 1u);
-            const int64_t s = wrap(home + (from - gbase), d.N);
+            const int32_t oldest = group_min<G>(evictable ? x.m : 0x7FFFFFFF);
+            const uint64_t oldests = __ballot(evictable && x.m == oldest) & gmask;
+            const uint64_t from = empties ? empties : oldests;
+            const bool was_empty = empties != 0;
+            if (trying && !from) {
+                lost(cpos);
+                trying = false;
+            }
+            if (!trying) continue;
+            const int who = __ffsll((unsigned long long)from) - 1;
+            empties &= empties - 1;                                     // (0 stays 0)
+            if (!was_empty && lane == who) evictable = false;
+            if (drawn++ < choice) continue;
+            const int64_t mine = make_tag((uint32_t)choice, cpos, was_empty ? 0u : 1u);
+            const int64_t s = wrap(home + (who - gbase), d.N);
             int64_t old = 0;
             if (lane == who) old = __hip_atomic_fetch_min(id_at(d, s), mine, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            old = shfl64(old, from);
-            if (trying) {
-                if (is_tag(old) && old < mine) {
-                    ++choice;                                           // a better claim holds this slot
-                    trying = choice < n_choices;
-                    if (!trying) lost(cpos);
-                } else {
-                    placed(cpos, choice, from - gbase, s, old);
-                    displaced = is_tag(old) ? old : 0;
-                    trying = false;
-                }
+            old = shfl64(old, who);
+            if (is_tag(old) && old < mine) {
+                ++choice;                                               // a better claim holds this slot
+            } else {
+                placed(cpos, choice, who - gbase, s, old);
+                displaced = is_tag(old) ? old : 0;
+                trying = false;
             }
         }
         active = active && displaced != 0;
@@ -1408,10 +1418,9 @@ __device__ __forceinline__ void claim_group_lru(const Params &p, const Tab &d, b
 // claimants are served and only their hints are written.  The windows of the next claimants are requested before the
 // present ones are served.
 template <int G, bool MULTI, bool REC>
-__global__ __launch_bounds__(kWave, MULTI ? 5 : 6) void k_allocate_lru(Params p)
+__global__ __launch_bounds__(kWave, MULTI ? 5 : 8) void k_allocate_lru(Params p)
 {
     constexpr int NG = kWave / G;
-    __shared__ __attribute__((aligned(16))) uint64_t s_key[kWave];
     const int lane = threadIdx.x;
     const int g = lane / G;
     const Tab d0 = view(MULTI ? p.descs[0] : p.t0);
@@ -1429,12 +1438,16 @@ __global__ __launch_bounds__(kWave, MULTI ? 5 : 6) void k_allocate_lru(Params p)
             if (have) {
                 pos = p.list[idx];
                 e = p.ent[idx];
-                home = p.homes[idx];
+                const int64_t id = p.list_id[idx];
                 first = p.set_slot[e];
                 agent = first == pos;
                 if (MULTI && agent) {
                     f = find_table(p.offsets, p.num_tables, (int64_t)pos);
-                    agent = p.descs[f].evict == 2;
+                    const TableDesc &t = p.descs[f];
+                    agent = t.evict == 2;
+                    home = home_slot(id, t.seed, t.N);
+                } else {
+                    home = home_slot(id, d0.seed, d0.N);
                 }
             }
             uint32_t hint = kHintNone;
@@ -1456,7 +1469,7 @@ __global__ __launch_bounds__(kWave, MULTI ? 5 : 6) void k_allocate_lru(Params p)
                 if (MULTI && src2 >= 0) d2 = view(p.descs[f2]);
                 const LruSlot x2 = load_lru_slot<G, REC>(d2, src2 >= 0, chome2);
                 int32_t fr = -1;
-                claim_group_lru<G, REC>(p, d, src >= 0, cpos, chome, x, s_key,
+                claim_group_lru<G, REC>(p, d, src >= 0, cpos, chome, x,
                                         [&](uint32_t who, int32_t, int32_t round, int64_t, int64_t) {
                                             if (who == cpos) fr = round;
                                         },
@@ -1747,9 +1760,9 @@ __device__ __forceinline__ void finalize_account(const Params &p, FinalizeState 
 // before it reports in.  (A device-scope release fence here would also write back the die's whole L2,
 // once per workgroup.)
 __device__ __forceinline__ bool finalize_epilogue(const Params &p, FinalizeState &fs, int64_t (*s_ev)[kEvBuf],
-                                                  int64_t (*s_row)[kEvBuf], int *s_cnt, int *s_tab,
+                                                  int64_t (*s_row)[kEvBuf], int *s_cnt, int (&s_tab)[kFinalizeWaves],
                                                   unsigned long long *s_base, bool *s_last,
-                                                  unsigned long long (*s_red)[kStatCount], bool want_stats)
+                                                  unsigned long long (&s_red)[kFinalizeWaves][kStatCount], bool want_stats)
 {
     const int lane = lane_id(), w = threadIdx.x / kWave;
     const bool multi = p.num_tables > 1;
@@ -1758,7 +1771,7 @@ __device__ __forceinline__ bool finalize_epilogue(const Params &p, FinalizeState
     __syncthreads();
     int total = 0, before = 0, tab = -1;
     bool same = true;
-    for (int i = 0; i < kWavesPerBlock; ++i) {
+    for (int i = 0; i < kFinalizeWaves; ++i) {
         if (s_cnt[i] == 0) continue;
         if (tab < 0) tab = s_tab[i];
         else if (s_tab[i] != tab) same = false;
@@ -1797,7 +1810,6 @@ __device__ __forceinline__ bool finalize_epilogue(const Params &p, FinalizeState
         }
         for (int i = lane; i < fs.ev_cnt; i += kWave)
             if (base + i < ev_cap) p.out_evicted[ev_begin + base + i] = s_ev[w][i];
-        reset_staged_rows(p, s_row[w], fs.ev_cnt);
     }
     return *s_last;
 }
@@ -1812,19 +1824,19 @@ __device__ __forceinline__ bool finalize_epilogue(const Params &p, FinalizeState
 template <bool MULTI>
 __device__ __forceinline__ void finalize_body(const Params &p)
 {
-    __shared__ int64_t s_ev[kWavesPerBlock][kEvBuf];
-    __shared__ int64_t s_row[kWavesPerBlock][kEvBuf];              // fused row reset: the rows of the staged slots
-    __shared__ unsigned long long s_red[kWavesPerBlock][kStatCount];
+    __shared__ int64_t s_ev[kFinalizeWaves][kEvBuf];
+    __shared__ int64_t s_row[kFinalizeWaves][kEvBuf];              // fused row reset: the rows of the staged slots
+    __shared__ unsigned long long s_red[kFinalizeWaves][kStatCount];
     __shared__ unsigned long long s_bins[MULTI ? kMaxTables : 1][kStatCount];
-    __shared__ int s_cnt[kWavesPerBlock];
-    __shared__ int s_tab[kWavesPerBlock];
+    __shared__ int s_cnt[kFinalizeWaves];
+    __shared__ int s_tab[kFinalizeWaves];
     __shared__ unsigned long long s_base;
     __shared__ bool s_last;
 
     const int lane = lane_id();
     const int w = threadIdx.x / kWave;
-    const int64_t wave_global = ((int64_t)blockIdx.x * kBlock + threadIdx.x) / kWave;
-    const int64_t num_waves = (int64_t)gridDim.x * kWavesPerBlock;
+    const int64_t wave_global = ((int64_t)blockIdx.x * kFinalizeBlock + threadIdx.x) / kWave;
+    const int64_t num_waves = (int64_t)gridDim.x * kFinalizeWaves;
     constexpr bool multi = MULTI;
     const bool want_stats = p.out_stats != nullptr;
     FinalizeState fs;
@@ -1844,13 +1856,13 @@ __device__ __forceinline__ void finalize_body(const Params &p)
             const uint32_t pos = p.list[idx];
             const uint32_t word = p.first_of[idx];
             const uint32_t e = p.ent[idx];
-            const int64_t home = p.homes[idx];
+            const int64_t id = p.list_id[idx];
             if (j0 >= cnt) break;
             const bool have = j0 + lane < cnt;
             bool agent = false;
             uint32_t first = 0, h = kHintUnplaced;
             int outcome = 2, f = 0;
-            int64_t s_final = 0, id = 0;
+            int64_t s_final = 0, home = 0;
             Tab d = view(p.t0);
             int at = -1;
             uint32_t occ = 0;
@@ -1873,7 +1885,7 @@ __device__ __forceinline__ void finalize_body(const Params &p)
                         d = view(p.descs[f]);
                     }
                 }
-                id = p.ids[pos];
+                home = home_slot(id, d.seed, d.N);
                 if (h < kHintUnknown) {
                     const int64_t v = *id_at(d, wrap(home + (int)h, d.N));
                     if (is_claim_of(v, first, id)) { at = (int)h; occ = tag_occ(v); }
@@ -1917,11 +1929,15 @@ __device__ __forceinline__ void finalize_body(const Params &p)
                     // the claim becomes the id, metadata gets its value (Algorithm 1, Pass 2); without a
                     // claim: Case 3, the home slot's metadata is refreshed.  (The agent always meets its
                     // own tag: nobody else replaces it.)
-                    if (at >= 0) {
-                        *id_at(d, s_final) = id;
-                        outcome = (int)occ;
+                    if (at >= 0) outcome = (int)occ;
+                    const int32_t m = meta_value(p, d, pos);
+                    if (at >= 0 && d.sh == 1 && d.evict != 3) {
+                        // (one store for both)
+                        *(global_ptr<u32x3>)id_at(d, s_final) = u32x3{(uint32_t)(uint64_t)id, (uint32_t)((uint64_t)id >> 32), (uint32_t)m};
+                    } else {
+                        if (at >= 0) *id_at(d, s_final) = id;
+                        store_meta(d, s_final, m);
                     }
-                    store_meta(d, s_final, meta_value(p, d, pos));
                 } else if (p.ttls && d.evict == 3) {
                     // per-feature retention: a later copy may ask for a later expiry step than the first
                     store_meta(d, s_final, meta_value(p, d, pos));
@@ -1931,15 +1947,22 @@ __device__ __forceinline__ void finalize_body(const Params &p)
             finalize_account<MULTI>(p, fs, s_ev[w], s_row[w], agent, outcome, s_final, f, want_stats);
         }
     }
+    if constexpr (!MULTI) {
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+        reset_staged_rows(p, s_row[w], fs.ev_cnt);
+    }
     // the workgroup that finishes last publishes the call's counters
     const bool last = finalize_epilogue(p, fs, s_ev, s_row, s_cnt, s_tab, &s_base, &s_last, s_red, want_stats);
-    if (last) publish_counters(p, s_bins);
+    if (last) publish_counters<kFinalizeBlock>(p, s_bins);
 }
 
-// The single-table form is held to 8 wavefronts per SIMD (50 registers, 17 KB of LDS): its 8 192 wavefronts, each a
-// chain of three round trips, then run in one go (headline with the row reset: 60.5 -> 55 us; 63 at 7 per SIMD).
+// The single-table form is held to 8 wavefronts per SIMD (50 registers, 66 KB of LDS for 16 wavefronts): its 8 192
+// wavefronts, each a chain of three round trips, then run in one go.  A batch of 4 M positions, 10 % of them new, with
+// the row reset: 56 -> 46 us by the ids in the miss lists (a line read for each of them before), one store for id and
+// metadata of a record, and rows reset before the workgroup's barrier instead of behind it; 41 M values over 26 tables
+// 242 -> 178 us.
 template <bool MULTI>
-__global__ __launch_bounds__(kBlock, MULTI ? 6 : 8) void k_finalize(Params p)
+__global__ __launch_bounds__(kFinalizeBlock, MULTI ? 4 : 8) void k_finalize(Params p)
 {
     finalize_body<MULTI>(p);
 }
