@@ -12,9 +12,10 @@
 //   k_allocate_chunk   claims.  The first block of every window is requested together with the election of the
 //                      first occurrence.  A slot that is claimed for the first time is an insert or an eviction
 //                      whatever displacements follow, so the outcome is counted here, and the evicted slots are left for
-//                      the last kernel, per workgroup.  Where a claimant ends up is kept in place[position]: rounds only
-//                      grow while a claimant is displaced, so an atomic maximum makes the word final when the
-//                      kernel ends, and the last kernel need not look at the table at all.
+//                      the last kernel, per workgroup.  Where its own lane has placed a claimant is stored once; lanes
+//                      that carry on displaced ones note it in place[position], and since rounds only grow while a
+//                      claimant is displaced an atomic maximum makes the larger of the two words final when the
+//                      kernel ends.  So the last kernel need not look at the table at all.
 //   k_finalize_chunk   ids and metadata of the placed claimants, outputs, evicted list (its place in the list
 //                      comes from the counts of the workgroups before), row reset, counters.
 #pragma once
@@ -23,8 +24,12 @@
 namespace mpzch {
 
 constexpr uint32_t kNoEntry = 0xFFFFFFFFu;       // ent[pos]: the position did not miss
-constexpr uint32_t kPlaceNone = 0xFFFFFFFFu;     // place[pos]: displaced and out of slots.  0: never placed.  Else round + 1;
-                                                 // under the LRU policy choice << 16 | round + 1
+// Where a claimant ends up: round + 1 (under the LRU policy choice << 16 | round + 1), 0: nowhere so far, kPlaceNone:
+// displaced and out of slots.
+constexpr uint32_t kPlaceNone = 0x7FFFFFFEu;      // (with kOwnPlace it is not kNoEntry)
+constexpr uint32_t kOwnPlace = 0x80000000u;      // list[pos] of the first occurrence of a missed id: this bit and its place
+                                                 // as far as its own lane knows.  Of a later copy: the position of the
+                                                 // first; kNoEntry: the position did not miss
 
 // Scratch set of these calls: an entry is the batch position with 12 bits of the id's hash above it, so that two ids that
 // meet in one entry tell each other apart without a look at the batch (a round trip per collision; with every
@@ -114,6 +119,32 @@ __device__ __forceinline__ void store_meta_block(const Tab &d, bool active, int6
     if (store) __hip_atomic_fetch_max(meta_at(d, slot), s_m.value[t], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
+// set_insert_chunk for the lanes with `miss` set.  Copies of one id within the wavefront (those that find each other in
+// LDS) enter it once, with the smallest of their positions: an id that is new and popular at once -- the first batch of a
+// table, of a feature -- otherwise has thousands of atomics on one word, 12 ns each (65 536 positions, the most popular id
+// a fourteenth of them: 67 -> 27 us; over the workgroup instead, 14 us, but the barriers cost every other call 0.7).
+__device__ __forceinline__ uint32_t set_insert_wave(const Params &p, bool miss, int64_t id, uint32_t pos, MetaMerge *s_m)
+{
+    const int lane = lane_id();
+    const int cell = (int)((uint32_t)(mix64((uint64_t)id) >> 58));
+    s_m[lane].slot = miss ? id : -1;
+    s_m[lane].value = (int32_t)pos;
+    if (miss) s_m[cell].winner = (uint32_t)lane;
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    int from = lane;
+    if (miss) {
+        const int o = (int)s_m[cell].winner;
+        if (o != lane && s_m[o].slot == id) {
+            __hip_atomic_fetch_min(&s_m[o].value, (int32_t)pos, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+            from = o;
+        }
+    }
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    uint32_t e = kNoEntry;
+    if (miss && from == lane) e = set_insert_chunk(p, id, (uint32_t)s_m[lane].value);
+    return (uint32_t)__shfl((int)e, from);
+}
+
 template <bool REC>
 __global__ __launch_bounds__(kBlock, 4) void k_discover_chunk(Params p)
 {
@@ -142,8 +173,7 @@ __global__ __launch_bounds__(kBlock, 4) void k_discover_chunk(Params p)
         if (need) { res = got; fresh = f; }
     }
     const bool hit = valid && res >= 0, miss = valid && res < 0;
-    uint32_t e = kNoEntry;
-    if (miss) e = set_insert_chunk(p, id, (uint32_t)pos);
+    const uint32_t e = set_insert_wave(p, miss, id, (uint32_t)pos, reinterpret_cast<MetaMerge *>(s_req[w]));
     const int64_t slot = hit ? wrap(home + res, d.N) : home;
     store_meta_block(d, hit && !(REC && fresh && d.evict != 3), slot, hit ? meta_value(p, d, pos) : 0, s_merge);
     if (in) {
@@ -241,6 +271,7 @@ __global__ __launch_bounds__(kBlock, 4) void k_allocate_chunk(Params p)
     const bool aligned = (d.N << (3 + d.sh)) > kCachedTableBytes;
     bool inserted = false, evicted = false;
     int64_t slot = 0;
+    uint32_t own = 0;
     for (bool later = false;; later = true) {
         const uint64_t am = __ballot(c.active);
         if (!am) break;
@@ -250,16 +281,20 @@ __global__ __launch_bounds__(kBlock, 4) void k_allocate_chunk(Params p)
         if (c.active)
             claim_walk(d, c, m, row, s_code[w], s_req[w],
                        [&](uint32_t who, int32_t round, int64_t at, int64_t old) {
-                           note_place(p, who, (uint32_t)round + 1u);
+                           if (who == (uint32_t)pos) own = (uint32_t)round + 1u;
+                           else note_place(p, who, (uint32_t)round + 1u);
                            inserted = old == -1;     // (a lane's last claim: only it meets a slot not claimed before)
                            evicted = old >= 0;
                            slot = at;
                        },
                        // (also for the lane's own: its chain may come back to it, in a table hardly longer than a window)
-                       [&](uint32_t who) { note_place(p, who, kPlaceNone); });
+                       [&](uint32_t who) {
+                           if (who == (uint32_t)pos) own = kPlaceNone;
+                           else note_place(p, who, kPlaceNone);
+                       });
         __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");   // s_code and s_req are written again
     }
-    if (have) p.list[pos] = first;
+    if (in) p.list[pos] = !have ? kNoEntry : first == (uint32_t)pos ? kOwnPlace | own : first;
     leave_outcomes<kWavesPerBlock>(p, have && first == (uint32_t)pos, inserted, evicted, slot, s_red);
 }
 
@@ -274,6 +309,7 @@ __global__ __launch_bounds__(kLruBlock, 8) void k_allocate_lru_chunk(Params p)
     __shared__ int64_t s_home[kBlock];
     __shared__ int64_t s_slot[kBlock];               // of the claimant's chain of claims: the slot not claimed before
     __shared__ uint32_t s_pos[kBlock];
+    __shared__ uint32_t s_own[kBlock];               // its place
     __shared__ uint8_t s_outcome[kBlock];            // 0: none, 1: it was empty, 2: it held an id
     __shared__ uint32_t s_red[WAVES][3];
     const int lane = lane_id(), w = threadIdx.x / kWave;
@@ -284,11 +320,9 @@ __global__ __launch_bounds__(kLruBlock, 8) void k_allocate_lru_chunk(Params p)
     const int64_t id = in ? p.ids[pos] : -1;
     const bool have = e != kNoEntry;
     uint32_t first = 0;
-    if (have) {
-        first = p.set_slot[e] & kChunkPosMask;
-        p.list[pos] = first;
-    }
+    if (have) first = p.set_slot[e] & kChunkPosMask;
     const bool agent = have && first == (uint32_t)pos;
+    if (in && !agent) p.list[pos] = have ? first : kNoEntry;
     const uint64_t am = __ballot(agent);
     if (lane == 0) s_red[w][0] = (uint32_t)__popcll(am);
     __syncthreads();
@@ -300,6 +334,7 @@ __global__ __launch_bounds__(kLruBlock, 8) void k_allocate_lru_chunk(Params p)
     if (agent) {
         s_pos[at] = (uint32_t)pos;
         s_home[at] = home_slot(id, d.seed, d.N);
+        s_own[at] = 0;
         s_outcome[at] = 0;
     }
     __syncthreads();
@@ -315,19 +350,24 @@ __global__ __launch_bounds__(kLruBlock, 8) void k_allocate_lru_chunk(Params p)
         claim_group_lru<G, REC>(p, d, i < count, i < count ? s_pos[i] : 0u, home, x,
                                 [&](uint32_t who, int32_t choice, int32_t round, int64_t slot, int64_t old) {
                                     if (lane % G != 0) return;
-                                    note_place(p, who, (uint32_t)choice << 16 | (uint32_t)(round + 1));
+                                    const uint32_t place = (uint32_t)choice << 16 | (uint32_t)(round + 1);
+                                    if (who == s_pos[i]) s_own[i] = place;
+                                    else note_place(p, who, place);
                                     if (is_tag(old)) return;
                                     s_slot[i] = slot;
                                     s_outcome[i] = old == -1 ? 1 : 2;
                                 },
                                 [&](uint32_t who) {
-                                    if (lane % G == 0) note_place(p, who, kPlaceNone);
+                                    if (lane % G != 0) return;
+                                    if (who == s_pos[i]) s_own[i] = kPlaceNone;
+                                    else note_place(p, who, kPlaceNone);
                                 });
         home = home2;
         x = x2;
     }
     __syncthreads();
     const bool mine = (int)threadIdx.x < count;
+    if (mine) p.list[s_pos[threadIdx.x]] = kOwnPlace | s_own[threadIdx.x];
     const int outcome = mine ? s_outcome[threadIdx.x] : 0;
     leave_outcomes<WAVES>(p, mine, outcome == 1, outcome == 2, outcome == 2 ? s_slot[threadIdx.x] : 0, s_red);
 }
@@ -391,21 +431,24 @@ __global__ __launch_bounds__(kBlock, 8) void k_finalize_chunk(Params p)
     const int64_t pos = (int64_t)blockIdx.x * kBlock + threadIdx.x;
     const bool in = pos < p.n;
     const Tab d = view(p.t0);
-    const uint32_t e = in ? p.ent[pos] : kNoEntry;
+    const uint32_t word = in ? p.list[pos] : kNoEntry;
     const int64_t id = in ? p.ids[pos] : -1;
-    uint32_t first = 0, place = 0;
-    if (in) {
-        first = p.list[pos];                         // (left over from an earlier call where the position did not miss)
-        place = p.place[pos];
-    }
+    uint32_t moved = in ? p.place[pos] : 0;
+    // the scratch set is left empty again: n positions have 2 n entries (all of them, in one coalesced store, instead of
+    // those that were used, one at a time)
+    if (in) reinterpret_cast<uint64_t *>(p.set_slot)[pos] = ~0ull;
     const int evicted = (int)unpack3(p.wg_words[3 * blockIdx.x + 2], 2);
-    const bool have = e != kNoEntry;
+    const bool have = word != kNoEntry;
     bool refresh = false;
     int64_t slot = 0;
     if (have) {
-        const bool agent = first == (uint32_t)pos;
-        if (!agent) place = p.place[first];
-        p.set_slot[e] = kSetEmpty;                   // the scratch set is left empty again
+        const bool agent = (word & kOwnPlace) != 0;
+        uint32_t place = word & ~kOwnPlace;
+        if (!agent) {
+            moved = p.place[word];
+            place = p.list[word] & ~kOwnPlace;
+        }
+        place = moved > place ? moved : place;
         const bool placed = place != 0 && place != kPlaceNone;
         const int64_t home = home_slot(id, d.seed, d.N);
         if (d.evict == 2) place &= 0xFFFFu;

@@ -210,3 +210,17 @@ def test_lru_claims(slots, probe, layout):
     t.step(rng.integers(0, 2 * slots, size=2_000), 9)
     t.step(rng.integers(0, 9 * slots, size=2_000), 10)
     t.close()
+
+
+# ---- ids that are new and popular at once: copies enter the scratch set once per wavefront
+@pytest.mark.parametrize("evict", [True, "lru", False])
+@pytest.mark.parametrize("n", [1_025, 4_111, 65_536])
+def test_new_ids_with_many_copies(n, evict):
+    rng = rng_for(909)
+    t = Pair(2_003, 16, 1, evict, 19, layout="records")
+    for step in range(4):
+        hot = rng.integers(0, 1 << 40, size=5)
+        ids = np.where(rng.random(n) < 0.7, hot[rng.integers(0, 5, size=n)], rng.integers(0, 1 << 40, size=n))
+        ids[: n // 3] = hot[0]
+        t.step(ids[rng.permutation(n)], 2 * step)
+    t.close()
