@@ -222,7 +222,7 @@ mpzch_status_t mpzch_remap_reset(mpzch_table_t *t, int64_t *identities, int32_t 
  * area ready for the next one (set emptied, counters zeroed).
  */
 #define MPZCH_NOALLOC_MAX_BATCH ((int64_t)262144)
-#define MPZCH_NOALLOC_SCRATCH_BYTES (9u << 20) /* 9 MiB per GPU */
+#define MPZCH_NOALLOC_SCRATCH_BYTES (10u << 20) /* 10 MiB per GPU */
 mpzch_status_t mpzch_remap_noalloc(const mpzch_table_t *t, int64_t *identities, int32_t *metadata,
                                    const int64_t *ids, int64_t n, int32_t step,
                                    int64_t *out_slots,

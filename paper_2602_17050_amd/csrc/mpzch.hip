@@ -151,10 +151,15 @@ struct Scratch {
     }
 
     // Where each array sits inside an area that serves batches of up to n positions: 29 bytes per
-    // position and a few small fixed areas.
+    // position (37 for the first kChunkMaxBatch) and a few small fixed areas.
     struct Layout {
         size_t o_list, o_ent, o_first, o_list_id, o_hint, o_seg, o_set, o_ctl, total;
     };
+    static int64_t set_entries(int64_t n)
+    {
+        const int64_t chunk = kChunkSetEntries * (n < kChunkMaxBatch ? n : kChunkMaxBatch);
+        return 2 * n > chunk ? 2 * n : chunk;
+    }
     static Layout layout_for(int64_t n, int num_cus)
     {
         Layout L;
@@ -167,7 +172,7 @@ struct Scratch {
         L.o_hint = L.o_list_id + align_up(2 * per_pos);
         L.o_seg = L.o_hint + align_up((size_t)n + kWave);
         L.o_set = L.o_seg + align_up(4 * max_blocks * kWavesPerBlock);
-        L.o_ctl = L.o_set + align_up(8 * (size_t)n);
+        L.o_ctl = L.o_set + align_up(4 * (size_t)set_entries(n));
         L.total = L.o_ctl + align_up(sizeof(Control));
         return L;
     }
@@ -376,7 +381,7 @@ mpzch_status_t run_remap(Scratch &sc, Timing &tm, const Params &p, int32_t max_p
 {
     if (one_block(p)) return launch_remap_block(tm, p, s);        // uses no scratch
     if (sc.dirty) {
-        TRY(fill32((int32_t *)sc.set_slot, 2 * sc.cap_n, -1, s));
+        TRY(fill32((int32_t *)sc.set_slot, Scratch::set_entries(sc.cap_n), -1, s));
         TRY(fill64((int64_t *)sc.ctl, (int64_t)(sizeof(Control) / sizeof(int64_t)), 0, s));
     }
     sc.dirty = true;
@@ -425,7 +430,7 @@ mpzch_status_t launch_remap(Scratch &sc, Timing &tm, Params p, int32_t max_p_lru
     const int64_t groups = (p.n + kBlock - 1) / kBlock;
     // (the LRU policy with windows of more than 64 slots gives a claimant the whole wavefront)
     if (p.num_tables == 1 && max_p_lru <= kWave && groups <= (int64_t)sc.num_cus * discover_blocks_per_cu() &&
-        p.n < ((int64_t)1 << kChunkPosBits))
+        p.n <= kChunkMaxBatch)
         return launch_remap_chunks(tm, p, max_p_lru, (int)groups, s);
 
     const int64_t num_chunks = (p.n + kWave - 1) / kWave;

@@ -34,13 +34,19 @@ constexpr uint32_t kOwnPlace = 0x80000000u;      // list[pos] of the first occur
 // Scratch set of these calls: an entry is the batch position with 12 bits of the id's hash above it, so that two ids that
 // meet in one entry tell each other apart without a look at the batch (a round trip per collision; with every
 // id missed and half of the set full, that was 8 of 40 us for 262 144 ids).  Otherwise as set_insert.
-constexpr int kChunkPosBits = 20;                // n < 2^20
+//
+// Four entries per position: the GPU performs 26 G atomics/s, whatever they are and wherever they go, so where every id is
+// missed the lanes of all wavefronts queue 10 us for their first one, and every collision queues again (262 144 ids,
+// Pass 1: 36 -> SET4 us; two entries per position and 1.5 atomics per id took 27 of 36).
+constexpr int kChunkSetEntries = 4;              // per position
+constexpr int64_t kChunkMaxBatch = (int64_t)1 << 19;
+constexpr int kChunkPosBits = 20;
 constexpr uint32_t kChunkPosMask = (1u << kChunkPosBits) - 1u;
 
 __device__ __forceinline__ uint32_t set_insert_chunk(const Params &p, int64_t id, uint32_t pos)
 {
     const uint64_t h = mix64((uint64_t)id ^ kSetSeed);
-    const uint32_t size = 2u * (uint32_t)p.n;
+    const uint32_t size = (uint32_t)kChunkSetEntries * (uint32_t)p.n;
     const uint32_t mine = ((uint32_t)h << kChunkPosBits) | pos;
     uint32_t e = (uint32_t)__umul64hi(h, (uint64_t)size);
     for (;;) {
@@ -434,9 +440,10 @@ __global__ __launch_bounds__(kBlock, 8) void k_finalize_chunk(Params p)
     const uint32_t word = in ? p.list[pos] : kNoEntry;
     const int64_t id = in ? p.ids[pos] : -1;
     uint32_t moved = in ? p.place[pos] : 0;
-    // the scratch set is left empty again: n positions have 2 n entries (all of them, in one coalesced store, instead of
-    // those that were used, one at a time)
-    if (in) reinterpret_cast<uint64_t *>(p.set_slot)[pos] = ~0ull;
+    // the scratch set is left empty again (all of it, in one coalesced store, instead of the entries that were used, one at
+    // a time)
+    static_assert(kChunkSetEntries == 4, "cleared as one vector of four");
+    if (in) reinterpret_cast<u32x4 *>(p.set_slot)[pos] = u32x4(kSetEmpty);
     const int evicted = (int)unpack3(p.wg_words[3 * blockIdx.x + 2], 2);
     const bool have = word != kNoEntry;
     bool refresh = false;
