@@ -102,10 +102,10 @@ __global__ __launch_bounds__(kOneBlock) void k_remap_block(Params p)
     cl.pos = pos;
     cl.q = 0;
     cl.home = home;
-    for (bool later = false;; later = true) {
+    for (;;) {
         const uint64_t am = __ballot(cl.active);
         if (!am) break;
-        const int m = later ? blocks_shift(__popcll(am), d.P) : 0;
+        const int m = blocks_shift(__popcll(am), d.P);
         const int row = claim_blocks<false, REC>(d, d, cl, am, m, bound, false, s.code[w], s.req[w]);
         if (cl.active)
             claim_walk(d, cl, m, row, s.code[w], s.req[w],

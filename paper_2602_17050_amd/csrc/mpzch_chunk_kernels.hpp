@@ -37,7 +37,7 @@ constexpr uint32_t kOwnPlace = 0x80000000u;      // list[pos] of the first occur
 //
 // Four entries per position: the GPU performs 26 G atomics/s, whatever they are and wherever they go, so where every id is
 // missed the lanes of all wavefronts queue 10 us for their first one, and every collision queues again (262 144 ids,
-// Pass 1: 36 -> SET4 us; two entries per position and 1.5 atomics per id took 27 of 36).
+// Pass 1: 36 -> 24 us; two entries per position and 1.5 atomics per id took 27 of 36).
 constexpr int kChunkSetEntries = 4;              // per position
 constexpr int64_t kChunkMaxBatch = (int64_t)1 << 19;
 constexpr int kChunkPosBits = 20;
@@ -281,7 +281,7 @@ __global__ __launch_bounds__(kBlock, 4) void k_allocate_chunk(Params p)
     for (bool later = false;; later = true) {
         const uint64_t am = __ballot(c.active);
         if (!am) break;
-        const int m = later ? blocks_shift(__popcll(am), d.P) : 0;
+        const int m = later || !aligned ? blocks_shift(__popcll(am), d.P) : 0;
         const int row = claim_blocks<false, REC>(d, d, c, am, m, bound, aligned, s_code[w], s_req[w]);
         if (!later) c.active = c.active && first == (uint32_t)pos;      // else: a later copy of the id
         if (c.active)
