@@ -351,22 +351,6 @@ __device__ __forceinline__ int next_bits(uint64_t &amask, int g)
     return b;
 }
 
-// Region of the scratch set that serves the table owning `pos`: twice the number of positions
-// of that table, so it can never fill up.  The clamps keep the region inside [0, 2n) even if the
-// feature offsets break their contract.
-__device__ __forceinline__ void set_region(const Params &p, int64_t pos, uint64_t &base, uint64_t &size)
-{
-    if (p.num_tables <= 1) { base = 0; size = 2ull * (uint64_t)p.n; return; }
-    const int f = find_table(p.offsets, p.num_tables, pos);
-    int64_t lo = p.offsets[f], hi = p.offsets[f + 1];
-    if (f == p.num_tables - 1 || hi > p.n) hi = p.n;
-    if (hi <= pos) hi = pos + 1;
-    if (lo > pos) lo = pos;
-    if (lo < 0) lo = 0;
-    base = 2ull * (uint64_t)lo;
-    size = 2ull * (uint64_t)(hi - lo);
-}
-
 __device__ __forceinline__ unsigned long long *stat_word(const Params &p, int table, int k)
 {
     return &p.ctl->stats[blockIdx.x % kBins][table][k];
@@ -548,6 +532,59 @@ __device__ __forceinline__ int probe_pass(const Tab &d, int64_t id, int64_t home
     return found;
 }
 
+// The first pass of a large batch: the aligned block of 8 slots that holds the home slot.  Otherwise as probe_pass; next:
+// the round to go on with.  The lanes that load read the block as it lies, eight slots from its first one on (slot_step:
+// how far this lane's slot lies from it, in bytes), and only the id's own lane knows which of them are its rounds: two
+// instructions per load instead of fifteen.  An id whose block reaches out of the table leaves everything to the later
+// passes.  (Measured with the tables of a group looked at one at a time, see discover_body: 41 M values over 26 tables
+// 961 -> 882 us, lookup of 1 M ids 19.8 -> 18.4 us.)
+template <bool NT, bool REC>
+__device__ __forceinline__ int probe_first(const Tab &d, int64_t id, int64_t home, uint32_t slot_step, ProbeReq *s_req,
+                                           uint8_t *s_code, int32_t fresh_meta, bool *fresh, int *next)
+{
+    constexpr int G = kFirstG, IPI = kWave / G;
+    const int lane = lane_id();
+    const int g = lane / G;
+    const int o = block_offset(d, home, G);
+    const bool here = home >= o && home - o + G <= d.N;
+    s_req[lane] = ProbeReq{id, (uint64_t)(uintptr_t)(int64_t *)id_at(d, here ? home - o : 0)};
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    int64_t v[G];
+    int32_t m[G];
+#pragma unroll
+    for (int t = 0; t < G; ++t) {
+        const uint64_t a = s_req[t * IPI + g].where + slot_step;
+        if constexpr (REC) {
+            const u32x3 rec = *(global_ptr<u32x3>)(uintptr_t)a;
+            v[t] = (int64_t)(((uint64_t)rec.y << 32) | rec.x);
+            m[t] = (int32_t)rec.z;
+        } else if constexpr (NT) {
+            v[t] = __builtin_nontemporal_load((global_ptr<int64_t>)(uintptr_t)a);
+        } else {
+            v[t] = *(global_ptr<int64_t>)(uintptr_t)a;
+        }
+    }
+    __builtin_amdgcn_sched_barrier(0);          // (the ids are read again now, not kept meanwhile)
+#pragma unroll
+    for (int t = 0; t < G; ++t) {
+        const int64_t gid = s_req[t * IPI + g].id;
+        uint8_t code = v[t] == gid ? 1 : (v[t] == -1 ? 2 : 0);
+        if constexpr (REC) code = v[t] == gid ? (m[t] == fresh_meta ? 5 : 1) : (v[t] == -1 ? 2 : 0);
+        s_code[t * kWave + lane] = code;        // = byte (slot of the block) of id t * IPI + g
+    }
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    const uint64_t x = *reinterpret_cast<const uint64_t *>(s_code + lane * G) >> (8 * o);
+    const int bit = __ffsll((unsigned long long)x) - 1;
+    const int round = bit >> 3;
+    const int count = d.P < G - o ? d.P : G - o;
+    if constexpr (REC) *fresh = x != 0 && ((x >> (bit & 63)) & 4ull) != 0;
+    *next = here ? G - o : 0;
+    int found = (bit & 1) ? probe_absent(round) : round;
+    if (x == 0 || round >= count) found = count == d.P ? probe_absent(d.P - 1) : kProbeGoOn;   // (or: the whole window was read)
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");    // the areas are written again by the next pass
+    return here ? found : kProbeGoOn;
+}
+
 // How many blocks of 8 slots each of `count` lanes gets in one pass over 64 blocks, as a shift; no more than windows of
 // P slots have use for.
 __device__ __forceinline__ int blocks_shift(int count, int P)
@@ -704,7 +741,7 @@ template <bool TRAIN, bool MULTI, bool GATHER, bool COUNT = TRAIN, bool NT = fal
 __device__ __forceinline__ void discover_body(const Params &p)
 {
     __shared__ uint32_t s_pos[kWavesPerBlock][kStage];
-    __shared__ int32_t s_q[kWavesPerBlock][kStage];      // > 0: next round to look at; < 0: absent, -(slots read)
+    __shared__ int32_t s_q[kWavesPerBlock][kStage];      // >= 0: next round to look at; < 0: absent, -(slots read)
     __shared__ int64_t s_id[kWavesPerBlock][kStage];
     __shared__ unsigned long long s_red[kWavesPerBlock][kStatCount];
     __shared__ int s_tab[kWavesPerBlock];
@@ -724,7 +761,6 @@ __device__ __forceinline__ void discover_body(const Params &p)
 
     // counters of the table currently being processed: positions per wavefront, probe lengths per lane
     unsigned long long st_hit = 0, st_miss = 0, st_inv = 0, st_probe = 0, st_mlen = 0;
-    int st_table = 0;
     int staged = 0, flushed = 0;                 // wave-uniform: parked ids in LDS / misses already listed
 
     // Several tables: the table that owns the positions this wavefront is working through, with the
@@ -747,8 +783,20 @@ __device__ __forceinline__ void discover_body(const Params &p)
         for (int i = threadIdx.x; i < p.num_tables * (int)(sizeof(TableDesc) / 8); i += kBlock) dst[i] = src[i];
         __syncthreads();
     }
-    auto table_at = [&](int64_t upos) {
-        if (upos >= t_lo && upos < t_hi) return;
+    // hands the counters of the present table over (when the table changes inside this wavefront's range)
+    auto hand_over = [&]() {
+        if (!want_stats) return;
+        const unsigned long long y = wave_sum(st_probe), z = wave_sum(st_mlen);
+        if (lane == 0) {
+            if (st_hit) atomicAdd(stat_word(p, t_f, kHitPos), st_hit);
+            if (st_miss) atomicAdd(stat_word(p, t_f, kMissPos), st_miss);
+            if (st_inv) atomicAdd(stat_word(p, t_f, kInvalidPos), st_inv);
+            if (y) atomicAdd(stat_word(p, t_f, kHitProbeSum), y);
+            if (z) atomicAdd(stat_word(p, t_f, kMissProbeSum), z);
+        }
+        st_hit = st_miss = st_inv = st_probe = st_mlen = 0;
+    };
+    auto enter_table = [&](int64_t upos) {
         t_f = find_table_wave(lane_offset, upos);
         // the search skips empty features that share this offset; the clamps keep every loop
         // finite and every range inside the batch even if the offsets break their contract
@@ -760,22 +808,6 @@ __device__ __forceinline__ void discover_body(const Params &p)
         t_lo = uniform64(lo);
         t_hi = uniform64(hi);
         t_d = uniform(view(s_desc[t_f]));
-    };
-
-    // counters are kept for one table at a time
-    auto stats_table = [&](int f) {
-        if (!want_stats || f == st_table) return;
-        // table changed inside this wavefront's range (rare): hand the counters over
-        const unsigned long long y = wave_sum(st_probe), z = wave_sum(st_mlen);
-        if (lane == 0) {
-            if (st_hit) atomicAdd(stat_word(p, st_table, kHitPos), st_hit);
-            if (st_miss) atomicAdd(stat_word(p, st_table, kMissPos), st_miss);
-            if (st_inv) atomicAdd(stat_word(p, st_table, kInvalidPos), st_inv);
-            if (y) atomicAdd(stat_word(p, st_table, kHitProbeSum), y);
-            if (z) atomicAdd(stat_word(p, st_table, kMissProbeSum), z);
-        }
-        st_hit = st_miss = st_inv = st_probe = st_mlen = 0;
-        st_table = f;
     };
     // a position whose id is resident at `dist` probes from home
     // (the first pass stores the outputs of its whole chunk itself: emit = false)
@@ -793,77 +825,58 @@ __device__ __forceinline__ void discover_body(const Params &p)
         }
     };
 
-    // probes the parked ids until found or their window ends; enters the rest into the scratch set
+    // probes the parked ids (all of the present table) until found or their window ends; enters the rest into the
+    // scratch set
     auto resolve_stage = [&]() {
         // what the first pass stored comes before what any lane of this wavefront stores below
         __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+        const Tab d = t_d;
         int nmiss = 0;
-        bool all_cached = true;                 // wave-uniform: every parked position is of the cached table
         for (int e0 = 0; e0 < staged; e0 += kWave) {
             const bool have = e0 + lane < staged;
             const uint32_t pos = have ? s_pos[w][e0 + lane] : 0;
-            const int q0 = have ? s_q[w][e0 + lane] : 0;
+            const int q0 = have ? s_q[w][e0 + lane] : -1;
             const int64_t id = have ? s_id[w][e0 + lane] : -1;
-            // parked positions nearly always belong to the table of the chunks just read
-            const bool cached = !multi || __all(!have || ((int64_t)pos >= t_lo && (int64_t)pos < t_hi));
-            if (!cached) all_cached = false;
-            const int f = (have && !cached) ? find_table(p.offsets, p.num_tables, (int64_t)pos) : t_f;
-            bool todo = have;
-            while (__any(todo)) {
-                const int f0 = cached ? t_f : __shfl(f, __ffsll((unsigned long long)__ballot(todo)) - 1);
-                const bool mine = todo && f == f0;
-                Tab d = t_d;                                    // one table: t_d is the table
-                if (multi && !cached) d = uniform(view(s_desc[f0]));
-                stats_table(f0);
-                const int64_t home = mine ? home_slot(id, d.seed, d.N) : 0;
-                int dist = -1;
-                bool fresh = false;
-                int mlen = q0 < 0 ? -q0 : 0;                // > 0: the search has ended at an empty slot
-                int q = q0 > 0 ? q0 : d.P;
-                for (;;) {
-                    const bool need = mine && dist < 0 && mlen == 0 && q < d.P;
-                    if (!__any(need)) break;
-                    bool got_fresh = false;
-                    const int got = probe_more<NT, REC>(d, id, home, q, need, s_req[w], s_code[w], p.step, &got_fresh);
-                    if (need) {
-                        if (got >= 0) { dist = got; fresh = got_fresh; }
-                        else if (got <= kProbeAbsent) mlen = absent_len(got);   // an empty slot ends the search
-                    }
+            const int64_t home = have ? home_slot(id, d.seed, d.N) : 0;
+            int dist = -1;
+            bool fresh = false;
+            int mlen = q0 < 0 ? -q0 : 0;                // > 0: the search has ended at an empty slot
+            int q = q0;
+            for (;;) {
+                const bool need = have && dist < 0 && mlen == 0 && q < d.P;
+                if (!__any(need)) break;
+                bool got_fresh = false;
+                const int got = probe_more<NT, REC>(d, id, home, q, need, s_req[w], s_code[w], p.step, &got_fresh);
+                if (need) {
+                    if (got >= 0) { dist = got; fresh = got_fresh; }
+                    else if (got <= kProbeAbsent) mlen = absent_len(got);   // an empty slot ends the search
                 }
-                finish_hit(d, mine && dist >= 0, (int64_t)pos, home, dist, true, fresh);
-                const bool miss = mine && dist < 0;
-                const uint64_t mb = __ballot(miss);
-                if (miss && TRAIN) {
-                    const int at = nmiss + __popcll(mb & ((1ull << lane) - 1ull));      // slots already consumed
-                    s_pos[w][at] = pos;
-                    s_id[w][at] = id;
-                }
-                if (COUNT) {
-                    st_hit += __popcll(__ballot(mine && dist >= 0));
-                    st_miss += __popcll(mb);
-                    if (miss) st_mlen += (unsigned long long)(mlen ? mlen : d.P);
-                }
-                // lookup: the first pass has already stored home and "not found"
-                if (GATHER) gather_wave(p, mine, (int64_t)pos, dist >= 0 ? wrap(home + dist, d.N) : home);
-                nmiss += __popcll(mb);
-                todo = todo && !mine;
             }
+            finish_hit(d, have && dist >= 0, (int64_t)pos, home, dist, true, fresh);
+            const bool miss = have && dist < 0;
+            const uint64_t mb = __ballot(miss);
+            if (miss && TRAIN) {
+                const int at = nmiss + __popcll(mb & ((1ull << lane) - 1ull));      // slots already consumed
+                s_pos[w][at] = pos;
+                s_id[w][at] = id;
+            }
+            if (COUNT) {
+                st_hit += __popcll(__ballot(have && dist >= 0));
+                st_miss += __popcll(mb);
+                if (miss) st_mlen += (unsigned long long)(mlen ? mlen : d.P);
+            }
+            // lookup: the first pass has already stored home and "not found"
+            if (GATHER) gather_wave(p, have, (int64_t)pos, dist >= 0 ? wrap(home + dist, d.N) : home);
+            nmiss += __popcll(mb);
         }
         if (TRAIN) {
             __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+            // the region of the scratch set that serves this table: twice as many entries as the table has positions, so
+            // that it can never fill up
+            const uint64_t sb = multi ? 2ull * (uint64_t)t_lo : 0, ss = 2ull * (uint64_t)(multi ? t_hi - t_lo : p.n);
             for (int j = lane; j < nmiss; j += kWave) {
                 const uint32_t pos = s_pos[w][j];
                 const int64_t id = s_id[w][j];
-                uint64_t sb, ss;
-                if (!multi) {
-                    sb = 0;
-                    ss = 2ull * (uint64_t)p.n;
-                } else if (all_cached) {
-                    sb = 2ull * (uint64_t)t_lo;
-                    ss = 2ull * (uint64_t)(t_hi - t_lo);
-                } else {
-                    set_region(p, (int64_t)pos, sb, ss);
-                }
                 const uint32_t e = set_insert(p, id, pos, sb, ss);
                 p.list[seg_base + flushed + j] = pos;
                 p.ent[seg_base + flushed + j] = e;
@@ -875,79 +888,93 @@ __device__ __forceinline__ void discover_body(const Params &p)
         staged = 0;
     };
 
-    for (int64_t c = c_begin; c < c_end; ++c) {
-        const int64_t base = c * kWave;
-        const int64_t pos = base + lane;
-        const bool in_range = pos < p.n;
-        const int64_t id = id_next;
-        id_next = (c + 1 < c_end && pos + kWave < p.n) ? p.ids[pos + kWave] : -1;
-        bool todo = in_range;
-        // every pass handles the lanes that belong to one table (one pass unless the chunk
-        // straddles a feature boundary)
-        while (__any(todo)) {
-            Tab d;
-            int f = 0;
-            bool mine = todo;
+    // One step looks at the lanes of the present chunk that belong to one table (all of them unless the chunk straddles a
+    // feature boundary); parked ids are resolved when the stage is full, when the next lanes belong to another table and
+    // at the end.  (One place each for the two, or the code is there several times over and needs more registers.)
+    int64_t c = c_begin, id = -1;
+    bool todo = false;                           // lanes of chunk c that have not been looked at
+    bool fetch = true, done = c_begin >= c_end;
+    for (;;) {
+        bool resolve = done;
+        if (!done) {
+            const int64_t pos = c * kWave + lane;
+            if (fetch) {
+                id = id_next;
+                id_next = (c + 1 < c_end && pos + kWave < p.n) ? p.ids[pos + kWave] : -1;
+                todo = pos < p.n;
+                fetch = false;
+            }
             if (multi) {
-                const uint64_t tb = __ballot(todo);
-                table_at(base + __ffsll((unsigned long long)tb) - 1);
-                f = t_f;
-                d = t_d;
-                mine = todo && pos < t_hi;
-            } else {
-                d = view(p.t0);
+                const int64_t upos = c * kWave + __ffsll((unsigned long long)__ballot(todo)) - 1;
+                if (upos < t_lo || upos >= t_hi) {
+                    resolve = staged > 0;        // what is parked belongs to the table that is left
+                    if (!resolve) {
+                        hand_over();
+                        enter_table(upos);
+                    }
+                }
             }
-            stats_table(f);
-
-            const bool valid = mine && id >= 0;
-            const int64_t home = mine ? home_slot(id, d.seed, d.N) : 0;
-            // first pass: the aligned 64 bytes that hold the home slot
-            const int o = block_offset(d, home, kFirstG);
-            bool fresh = false;
-            int res = probe_pass<kFirstG, NT, REC>(d, id, home, valid ? -o : d.P, s_req[w], s_code[w], p.step, &fresh);
-            if (res == kProbeGoOn && kFirstG - o >= d.P) res = probe_absent(d.P - 1);    // the whole window was read
-            const bool hit = valid && res >= 0;
-            finish_hit(d, hit, pos, home, res, false, fresh);
-            if (COUNT) {
-                st_hit += __popcll(__ballot(hit));
-                st_inv += __popcll(__ballot(mine && !valid));
+            if (!resolve) {
+                const Tab d = t_d;
+                const bool mine = todo && (!multi || pos < t_hi);
+                const bool valid = mine && id >= 0;
+                const int64_t home = mine ? home_slot(id, d.seed, d.N) : 0;
+                // (tables of fewer than 8 slots have no block to read: every lane reads slot 0)
+                const uint32_t slot_step = d.N >= kFirstG ? (uint32_t)(lane % kFirstG) << (3 + d.sh) : 0u;
+                bool fresh = false;
+                int next = 0;
+                const int res = probe_first<NT, REC>(d, id, home, slot_step, s_req[w], s_code[w], p.step, &fresh, &next);
+                const bool hit = valid && res >= 0;
+                finish_hit(d, hit, pos, home, res, false, fresh);
+                if (COUNT) {
+                    st_hit += __popcll(__ballot(hit));
+                    st_inv += __popcll(__ballot(mine && !valid));
+                }
+                if (COUNT && !TRAIN) {                                       // a lookup miss decided here is final
+                    const bool final_miss = valid && res <= kProbeAbsent;
+                    st_miss += __popcll(__ballot(final_miss));
+                    if (final_miss) st_mlen += (unsigned long long)absent_len(res);
+                }
+                // One store for the whole chunk keeps the 64-byte sectors of the outputs complete (a
+                // sector written with holes leaves the cache as narrow writes).  A position that is
+                // not decided yet gets its home slot: final for a negative id (home of its bit
+                // pattern) and for a lookup miss, rewritten later otherwise.
+                const int64_t slot = hit ? wrap(home + res, d.N) : home;
+                if (mine) {
+                    // (non-temporal: the outputs are not read by this call; nine in ten are final here)
+                    if (!GATHER || p.out_slots) __builtin_nontemporal_store(slot, &p.out_slots[pos]);
+                    if (!TRAIN && p.out_found) p.out_found[pos] = hit ? 1 : 0;
+                }
+                // not found so far: parked when its window goes on, or (training) to be listed as a miss
+                const bool park = valid && (res == kProbeGoOn || (TRAIN && res <= kProbeAbsent));
+                const uint64_t pb = __ballot(park);
+                if (park) {
+                    const int at = staged + __popcll(pb & ((1ull << lane) - 1ull));
+                    s_pos[w][at] = (uint32_t)pos;
+                    s_id[w][at] = id;
+                    s_q[w][at] = res <= kProbeAbsent ? -absent_len(res) : next;
+                }
+                staged += __popcll(pb);
+                if (GATHER) gather_wave(p, mine && !park, pos, slot);
+                todo = todo && !mine;
+                if (!__any(todo)) {
+                    ++c;
+                    fetch = true;
+                    done = c >= c_end;
+                }
+                resolve = done || staged > kStage - kWave;
             }
-            if (COUNT && !TRAIN) {                                           // a lookup miss decided here is final
-                const bool final_miss = valid && res <= kProbeAbsent;
-                st_miss += __popcll(__ballot(final_miss));
-                if (final_miss) st_mlen += (unsigned long long)absent_len(res);
-            }
-            // One store for the whole chunk keeps the 64-byte sectors of the outputs complete (a
-            // sector written with holes leaves the cache as narrow writes).  A position that is
-            // not decided yet gets its home slot: final for a negative id (home of its bit
-            // pattern) and for a lookup miss, rewritten later otherwise.
-            const int64_t slot = hit ? wrap(home + res, d.N) : home;
-            if (mine) {
-                // (non-temporal: the outputs are not read by this call; nine in ten are final here)
-                if (!GATHER || p.out_slots) __builtin_nontemporal_store(slot, &p.out_slots[pos]);
-                if (!TRAIN && p.out_found) p.out_found[pos] = hit ? 1 : 0;
-            }
-            // not found so far: parked when its window goes on, or (training) to be listed as a miss
-            const bool park = valid && (res == kProbeGoOn || (TRAIN && res <= kProbeAbsent));
-            const uint64_t pb = __ballot(park);
-            if (park) {
-                const int at = staged + __popcll(pb & ((1ull << lane) - 1ull));
-                s_pos[w][at] = (uint32_t)pos;
-                s_id[w][at] = id;
-                s_q[w][at] = res <= kProbeAbsent ? -absent_len(res) : kFirstG - o;
-            }
-            staged += __popcll(pb);
-            if (GATHER) gather_wave(p, mine && !park, pos, slot);
-            todo = todo && !mine;
         }
-        if (staged > kStage - kWave) resolve_stage();
+        if (resolve) {
+            resolve_stage();
+            if (done) break;
+        }
     }
-    resolve_stage();
     if (TRAIN && lane == 0 && seg < p.num_segs) p.seg_cnt[seg] = (uint32_t)flushed;
     if (want_stats) {
         const int idx[5] = {kHitPos, kMissPos, kInvalidPos, kHitProbeSum, kMissProbeSum};
         const unsigned long long vals[5] = {st_hit, st_miss, st_inv, wave_sum(st_probe), wave_sum(st_mlen)};
-        block_stat_add(p, idx, vals, 5, st_table, s_red, s_tab);
+        block_stat_add(p, idx, vals, 5, t_f, s_red, s_tab);
     }
     if constexpr (COUNT && !TRAIN) {
         // a counting lookup publishes its own counters (see finalize_body for the training remap)
@@ -1009,10 +1036,10 @@ __global__ __launch_bounds__(kBlock, 4) void k_discover_tables(Params p)
 }
 
 // A group whose tables are all kept as records: popular ids are refreshed once (41 M values over 26 tables: 1 494 ->
-// 1 045 us, at 40 G ids/s near the rate of random line reads).  Three wavefronts per SIMD: the records in flight
-// need 157 registers; held to 128 the compiler spills inside the probe.  (Two dense tensors keep the plain store: a
+// 1 045 us, at 40 G ids/s near the rate of random line reads).
+// (Two dense tensors keep the plain store: a
 // look at the metadata first is a random read of its own there, and Pass 1 over 500 M slots went from 111 to 133 us.)
-__global__ __launch_bounds__(kBlock, 3) void k_discover_tables_records(Params p)
+__global__ __launch_bounds__(kBlock, 4) void k_discover_tables_records(Params p)
 {
     discover_body<true, true, false, true, false, true>(p);
 }
