@@ -751,7 +751,20 @@ __device__ __forceinline__ void discover_body(const Params &p)
 
     const int lane = lane_id();
     const int w = threadIdx.x / kWave;
-    const int64_t seg = (int64_t)blockIdx.x * kWavesPerBlock + w;       // this wavefront's segment
+    int block = blockIdx.x;
+    if constexpr (MULTI) {
+        // Which workgroup takes which part of the batch.  The dies take workgroups in turn; here each gets whole
+        // sixteenths of the batch, so that the popular ids of a feature are in the L2 of one or two dies instead of all
+        // eight (41 M values over 26 tables: lines read 23.1 M -> 16.3 M, 877 -> 848 us; eighths 855, for some dies then
+        // have the large tables, 32nds 852, 128ths 906).  With few values per part it is uneven and nothing else: 4 M
+        // values 99 -> 100 us; so from 32 chunks per wavefront on.
+        constexpr int kDies = 8, kParts = 16;
+        if (p.seg_chunks >= 32 && gridDim.x % kParts == 0) {
+            const int per = (int)gridDim.x / kParts, j = block / kDies;
+            block = (j / per * kDies + block % kDies) * per + j % per;
+        }
+    }
+    const int64_t seg = (int64_t)block * kWavesPerBlock + w;            // this wavefront's segment
     const int64_t num_chunks = (p.n + kWave - 1) / kWave;
     const int64_t c_begin = seg * p.seg_chunks;
     const int64_t c_end = c_begin + p.seg_chunks < num_chunks ? c_begin + p.seg_chunks : num_chunks;
