@@ -692,7 +692,7 @@ __device__ __forceinline__ void gather_rows_wave(const Params &p, uint64_t am, i
     constexpr int U = 4;
     const int lane = lane_id();
     const int C = p.g_chunks;
-    const int total = kWave * C;
+    const int total = (kWave - __clzll((long long)am)) * C;          // up to the last active lane (am is not 0)
     for (int i0 = 0; i0 < total; i0 += kWave * U) {
         VEC v[U];
         int64_t dst[U];
@@ -702,13 +702,14 @@ __device__ __forceinline__ void gather_rows_wave(const Params &p, uint64_t am, i
             const int idx = i0 + u * kWave + lane;
             const bool in = idx < total;
             const int src = in ? (p.g_shift >= 0 ? idx >> p.g_shift : idx / C) : 0;
-            const int c = idx - src * C;
+            const int c = in ? idx - src * C : 0;
             const int64_t srow = shfl64(row, src);
             const int64_t spos = shfl64(pos, src);
             ok[u] = in && ((am >> src) & 1ull);
             dst[u] = spos * C + c;
-            v[u] = VEC(0);
-            if (ok[u]) v[u] = reinterpret_cast<const VEC *>(p.g_rows + srow * p.g_stride)[c];
+            // (no branch between the loads: lanes without a piece read the first piece of a row, which is row 0 for
+            // positions that are not active)
+            v[u] = reinterpret_cast<const VEC *>(p.g_rows + srow * p.g_stride)[c];
         }
 #pragma unroll
         for (int u = 0; u < U; ++u)
