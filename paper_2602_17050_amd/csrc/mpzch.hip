@@ -100,10 +100,14 @@ struct Timing {
 };
 
 // ---- device scratch -----------------------------------------------------------------------
-// Grid caps in workgroups per compute unit.  8 is the measured best for Pass 1 (4 and 16 are within a few
-// per cent) and for the kernels that walk the miss lists; scratch is sized for up to kDiscoverBlocksPerCuMax.
+// Grid caps in workgroups per compute unit.  8 is the measured best for Pass 1 (4 M positions: 197 us; 4 and 16 per unit
+// 222 and 210) and for the kernels that walk the miss lists.  From 16 M positions on, where a wavefront has 32 chunks
+// and more, twice as many even the ends out (41 M values over 26 tables, Pass 1 743 -> 721, the other kernels 288 -> 278
+// us).  Scratch is sized for up to kDiscoverBlocksPerCuMax.
 constexpr int kDiscoverBlocksPerCuMax = 16;
 constexpr int discover_blocks_per_cu() { return 8; }
+constexpr int64_t kLongBatch = (int64_t)1 << 24;
+constexpr int train_blocks_per_cu(int64_t n) { return n < kLongBatch ? discover_blocks_per_cu() : kDiscoverBlocksPerCuMax; }
 static_assert(3 * sizeof(uint64_t) * discover_blocks_per_cu() <= sizeof(uint32_t) * kDiscoverBlocksPerCuMax * kWavesPerBlock, "the counter words of the workgroups of a one-chunk call fit seg_cnt");
 constexpr int group_blocks_per_cu() { return 8; }
 
@@ -435,7 +439,7 @@ mpzch_status_t launch_remap(Scratch &sc, Timing &tm, Params p, int32_t max_p_lru
 
     const int64_t num_chunks = (p.n + kWave - 1) / kWave;
     // k_discover: every wavefront owns one segment of seg_chunks 64-position chunks
-    const int g_disc = grid_for(p.n, kBlock, sc.num_cus, discover_blocks_per_cu());
+    const int g_disc = grid_for(p.n, kBlock, sc.num_cus, train_blocks_per_cu(p.n));
     p.num_segs = g_disc * kWavesPerBlock;
     p.seg_chunks = (int32_t)((num_chunks + p.num_segs - 1) / p.num_segs);
     // the other kernels walk the segments' miss lists, one segment per wavefront pass
@@ -976,7 +980,10 @@ mpzch_status_t mpzch_lookup_gather(const mpzch_table_t *t, const int64_t *identi
     p.g_shift = -1;
     for (int b = 0; b <= 20; ++b)
         if (g.chunks == ((int64_t)1 << b)) p.g_shift = b;
-    const int grid = grid_for(n, kBlock, num_cus, discover_blocks_per_cu());
+    // five workgroups of this kernel fit a compute unit: where every wavefront has several chunks anyway, a grid that runs
+    // in one go is better than one and a half turns (2 M ids with rows of 256 bytes: 208 -> 197 us)
+    const int full = num_cus * discover_blocks_per_cu() * kBlock;
+    const int grid = grid_for(n, kBlock, num_cus, n > full ? 4 : discover_blocks_per_cu());
     p.num_segs = grid * kWavesPerBlock;
     p.seg_chunks = (int32_t)(((n + kWave - 1) / kWave + p.num_segs - 1) / p.num_segs);
     if (!t->tm.begin(KLookup, s)) return MPZCH_ERR_HIP;

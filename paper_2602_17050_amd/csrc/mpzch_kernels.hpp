@@ -758,9 +758,9 @@ __device__ __forceinline__ void discover_body(const Params &p)
         // sixteenths of the batch, so that the popular ids of a feature are in the L2 of one or two dies instead of all
         // eight (41 M values over 26 tables: lines read 23.1 M -> 16.3 M, 877 -> 848 us; eighths 855, for some dies then
         // have the large tables, 32nds 852, 128ths 906).  With few values per part it is uneven and nothing else: 4 M
-        // values 99 -> 100 us; so from 32 chunks per wavefront on.
+        // values 99 -> 100 us; so from 16 chunks per wavefront on.
         constexpr int kDies = 8, kParts = 16;
-        if (p.seg_chunks >= 32 && gridDim.x % kParts == 0) {
+        if (p.seg_chunks >= 16 && gridDim.x % kParts == 0) {
             const int per = (int)gridDim.x / kParts, j = block / kDies;
             block = (j / per * kDies + block % kDies) * per + j % per;
         }
