@@ -1,18 +1,21 @@
-"""Thin ctypes binding over libmpzch.so (the C ABI of include/mpzch.h).
+"""Thin binding over libmpzch.so (the C ABI of include/mpzch.h).
 
 Argument marshalling only: torch tensors supply device memory and the current
-stream; every step of the path runs in the library's HIP kernels.  There is no
-fallback: if the library is missing, loading raises.
+stream; every step of the path runs in the library's HIP kernels.  The calls of a
+training or serving loop are marshalled in native code (_native.so, csrc/native_call.cpp),
+the others by ctypes.  There is no fallback: if either file is missing, loading raises.
 """
 from __future__ import annotations
 
 import ctypes
+import importlib
 import os
 
 import torch
 
 _HERE = os.path.dirname(os.path.abspath(__file__))
 _LIB_PATH = os.path.join(_HERE, "libmpzch.so")
+_NATIVE_PATH = os.path.join(_HERE, "_native.so")
 
 EVICT_NONE, EVICT_TTL, EVICT_LRU, EVICT_TTL_EXPIRY = 0, 1, 2, 3
 STAT_NAMES = ("hit_pos", "miss_pos", "distinct_miss", "inserts",
@@ -48,12 +51,19 @@ class _Rows(ctypes.Structure):
 
 
 _lib = None
+_native = None             # the module that marshals the repeated calls, bound to _lib
+_NATIVE_CALLS = (
+    "mpzch_init_tensors", "mpzch_remap", "mpzch_remap_noalloc", "mpzch_remap_reset", "mpzch_remap_feature_ttl", "mpzch_lookup",
+    "mpzch_lookup_stats", "mpzch_lookup_gather", "mpzch_reset_rows", "mpzch_reset_rows_multi", "mpzch_collect_delta",
+    "mpzch_gather_rows", "mpzch_apply_delta", "mpzch_remap_jagged_feature_ttl", "mpzch_lookup_jagged", "mpzch_reset_rows_jagged",
+)
 
 
 def load_library(path: str | None = None):
     """Loads the in-tree HIP library; fails loudly when it has not been built."""
-    global _lib
-    if _lib is not None and path is None:
+    global _lib, _native
+    own = path is None
+    if _lib is not None and own:
         return _lib
     path = path or os.environ.get("MPZCH_LIBRARY") or _LIB_PATH   # env override: another build of the same ABI
     if not os.path.exists(path):
@@ -98,9 +108,18 @@ def load_library(path: str | None = None):
     for name in EXPORTED:
         if name != "mpzch_status_string":
             getattr(lib, name).restype = ctypes.c_int32
-    if path == _LIB_PATH:
-        _lib = lib
+    if own:
+        if not os.path.exists(_NATIVE_PATH):
+            raise FileNotFoundError(f"{_NATIVE_PATH} is missing: build it with `python -m paper_2602_17050_amd.build`")
+        native = importlib.import_module(__package__ + "._native")
+        native.bind({name: ctypes.cast(getattr(lib, name), ctypes.c_void_p).value for name in _NATIVE_CALLS})
+        _lib, _native = lib, native
     return lib
+
+
+def _load_native():
+    load_library()
+    return _native
 
 
 def mpzch_status_string(status: int) -> str:
@@ -110,23 +129,6 @@ def mpzch_status_string(status: int) -> str:
 def _check(status: int, what: str):
     if status:
         raise MpzchError(status, what)
-
-
-def _ptr(t, dtype=None):
-    if t is None:
-        return None
-    # dense tensors, or the strided views of a table kept as 16-byte records (identities: every second
-    # int64, metadata: every fourth int32)
-    assert t.is_cuda and (t.is_contiguous() or (t.dim() == 1 and t.stride(0) in (2, 4))), "device, dense tensors only"
-    if dtype is not None:
-        assert t.dtype == dtype, (t.dtype, dtype)
-    return t.data_ptr()
-
-
-def _stream():
-    """Torch's current stream on the current device, as an address.  (torch.cuda.current_stream() builds a Stream
-    object around the same number: 2.8 us of the 8 us that a small lookup spends on the host, against 0.2.)"""
-    return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
 
 
 # ----------------------------------------------------------------------------- C-ABI names
@@ -162,138 +164,92 @@ def mpzch_reserve(handle, max_n: int):
 
 
 def mpzch_init_tensors(handle, identities, metadata=None):
-    _check(load_library().mpzch_init_tensors(handle, _ptr(identities, torch.int64), _ptr(metadata, torch.int32),
-                                             _stream()), "mpzch_init_tensors")
+    status = (_native or _load_native()).init_tensors(handle, identities, metadata)
+    if status:
+        raise MpzchError(status, "mpzch_init_tensors")
 
 
 def mpzch_remap(handle, identities, metadata, ids, step: int, out_slots, out_evicted_slots, out_num_evicted,
                 out_stats=None):
-    n = ids.numel()
-    cap = 0 if out_evicted_slots is None else out_evicted_slots.numel()
-    _check(load_library().mpzch_remap(handle, _ptr(identities, torch.int64), _ptr(metadata, torch.int32),
-                                      _ptr(ids, torch.int64), n, step, _ptr(out_slots, torch.int64),
-                                      _ptr(out_evicted_slots, torch.int64), cap, _ptr(out_num_evicted, torch.int64),
-                                      _ptr(out_stats, torch.int64), _stream()), "mpzch_remap")
+    status = (_native or _load_native()).remap(handle, identities, metadata, ids, step, out_slots, out_evicted_slots,
+                                               out_num_evicted, out_stats)
+    if status:
+        raise MpzchError(status, "mpzch_remap")
 
 
 def mpzch_remap_reset(handle, identities, metadata, ids, step: int, out_slots, out_evicted_slots, out_num_evicted,
                       out_stats, rows, init_row=None, num_rows: int | None = None):
     """mpzch_remap that also resets rows[slot mod num_rows] of every slot it evicts; rows: 2-D tensor (num_rows, dim)."""
-    n = ids.numel()
-    cap = 0 if out_evicted_slots is None else out_evicted_slots.numel()
-    assert rows.dim() == 2 and rows.stride(1) == 1 and rows.is_cuda
-    nrows = rows.shape[0] if num_rows is None else num_rows
-    row_bytes = rows.shape[1] * rows.element_size()
-    stride = rows.stride(0) * rows.element_size()
-    if init_row is not None:
-        assert init_row.is_cuda and init_row.is_contiguous() and init_row.numel() * init_row.element_size() == row_bytes
-    _check(load_library().mpzch_remap_reset(handle, _ptr(identities, torch.int64), _ptr(metadata, torch.int32),
-                                            _ptr(ids, torch.int64), n, step, _ptr(out_slots, torch.int64),
-                                            _ptr(out_evicted_slots, torch.int64), cap, _ptr(out_num_evicted, torch.int64),
-                                            _ptr(out_stats, torch.int64), rows.data_ptr(), nrows,
-                                            row_bytes, stride,
-                                            None if init_row is None else init_row.data_ptr(),
-                                            _stream()), "mpzch_remap_reset")
+    status = (_native or _load_native()).remap_reset(handle, identities, metadata, ids, step, out_slots, out_evicted_slots,
+                                                     out_num_evicted, out_stats, rows, init_row, num_rows)
+    if status:
+        raise MpzchError(status, "mpzch_remap_reset")
 
 
 def mpzch_remap_noalloc(handle, identities, metadata, ids, step: int, out_slots, out_evicted_slots, out_num_evicted,
                         out_stats=None):
-    n = ids.numel()
-    cap = 0 if out_evicted_slots is None else out_evicted_slots.numel()
-    _check(load_library().mpzch_remap_noalloc(handle, _ptr(identities, torch.int64), _ptr(metadata, torch.int32),
-                                              _ptr(ids, torch.int64), n, step, _ptr(out_slots, torch.int64),
-                                              _ptr(out_evicted_slots, torch.int64), cap,
-                                              _ptr(out_num_evicted, torch.int64), _ptr(out_stats, torch.int64),
-                                              _stream()), "mpzch_remap_noalloc")
+    status = (_native or _load_native()).remap_noalloc(handle, identities, metadata, ids, step, out_slots,
+                                                       out_evicted_slots, out_num_evicted, out_stats)
+    if status:
+        raise MpzchError(status, "mpzch_remap_noalloc")
 
 
 def mpzch_remap_feature_ttl(handle, identities, metadata, ids, ttls, step: int, out_slots, out_evicted_slots,
                             out_num_evicted, out_stats=None):
-    n = ids.numel()
-    cap = 0 if out_evicted_slots is None else out_evicted_slots.numel()
-    assert ttls is None or ttls.numel() == n
-    _check(load_library().mpzch_remap_feature_ttl(handle, _ptr(identities, torch.int64), _ptr(metadata, torch.int32),
-                                                  _ptr(ids, torch.int64), _ptr(ttls, torch.int32), n, step,
-                                                  _ptr(out_slots, torch.int64), _ptr(out_evicted_slots, torch.int64),
-                                                  cap, _ptr(out_num_evicted, torch.int64),
-                                                  _ptr(out_stats, torch.int64), _stream()), "mpzch_remap_feature_ttl")
+    status = (_native or _load_native()).remap_feature_ttl(handle, identities, metadata, ids, ttls, step, out_slots,
+                                                           out_evicted_slots, out_num_evicted, out_stats)
+    if status:
+        raise MpzchError(status, "mpzch_remap_feature_ttl")
 
 
 def mpzch_lookup(handle, identities, ids, out_slots, out_found=None):
-    _check(load_library().mpzch_lookup(handle, _ptr(identities, torch.int64), _ptr(ids, torch.int64), ids.numel(),
-                                       _ptr(out_slots, torch.int64), _ptr(out_found, torch.uint8), _stream()),
-           "mpzch_lookup")
+    status = (_native or _load_native()).lookup(handle, identities, ids, out_slots, out_found)
+    if status:
+        raise MpzchError(status, "mpzch_lookup")
 
 
 def mpzch_lookup_stats(handle, identities, ids, out_slots, out_found, out_stats):
-    _check(load_library().mpzch_lookup_stats(handle, _ptr(identities, torch.int64), _ptr(ids, torch.int64), ids.numel(),
-                                             _ptr(out_slots, torch.int64), _ptr(out_found, torch.uint8),
-                                             _ptr(out_stats, torch.int64), _stream()), "mpzch_lookup_stats")
+    status = (_native or _load_native()).lookup_stats(handle, identities, ids, out_slots, out_found, out_stats)
+    if status:
+        raise MpzchError(status, "mpzch_lookup_stats")
 
 
 def mpzch_reset_rows(slots, num_slots_dev, rows, init_row=None, num_rows: int | None = None):
     """rows: 2-D tensor (num_rows, dim); row = slot mod num_rows."""
-    assert rows.dim() == 2 and rows.stride(1) == 1
-    nrows = rows.shape[0] if num_rows is None else num_rows
-    row_bytes = rows.shape[1] * rows.element_size()
-    stride = rows.stride(0) * rows.element_size()
-    if init_row is not None:
-        assert init_row.is_cuda and init_row.is_contiguous() and init_row.numel() * init_row.element_size() == row_bytes
-    _check(load_library().mpzch_reset_rows(_ptr(slots, torch.int64), _ptr(num_slots_dev, torch.int64), slots.numel(),
-                                           rows.data_ptr(), nrows, row_bytes, stride,
-                                           None if init_row is None else init_row.data_ptr(),
-                                           _stream()), "mpzch_reset_rows")
-
-
-def _row_geometry(rows):
-    assert rows.dim() == 2 and rows.stride(1) == 1 and rows.is_cuda
-    return rows.shape[0], rows.shape[1] * rows.element_size(), rows.stride(0) * rows.element_size()
+    status = (_native or _load_native()).reset_rows(slots, num_slots_dev, rows, init_row, num_rows)
+    if status:
+        raise MpzchError(status, "mpzch_reset_rows")
 
 
 def mpzch_reset_rows_multi(slots, num_slots_dev, tensors, init_rows=None):
     """tensors: list of 2-D device tensors (weights, optimizer state, ...), reset in one launch."""
-    init_rows = init_rows or [None] * len(tensors)
-    arr = (_Rows * len(tensors))()
-    for k, (t, init) in enumerate(zip(tensors, init_rows)):
-        n, rb, st = _row_geometry(t)
-        arr[k] = _Rows(t.data_ptr(), n, rb, st, None if init is None else init.data_ptr())
-    _check(load_library().mpzch_reset_rows_multi(_ptr(slots, torch.int64), _ptr(num_slots_dev, torch.int64),
-                                                 slots.numel(), arr, len(tensors), _stream()), "mpzch_reset_rows_multi")
+    status = (_native or _load_native()).reset_rows_multi(slots, num_slots_dev, tensors, init_rows or [None] * len(tensors))
+    if status:
+        raise MpzchError(status, "mpzch_reset_rows_multi")
 
 
 def mpzch_lookup_gather(handle, identities, ids, rows, out_rows, out_slots=None, out_found=None):
-    n, rb, st = _row_geometry(rows)
-    assert out_rows.is_contiguous() and out_rows.numel() * out_rows.element_size() == ids.numel() * rb
-    _check(load_library().mpzch_lookup_gather(handle, _ptr(identities, torch.int64), _ptr(ids, torch.int64), ids.numel(),
-                                              rows.data_ptr(), n, rb, st,
-                                              out_rows.data_ptr(), _ptr(out_slots, torch.int64),
-                                              _ptr(out_found, torch.uint8), _stream()), "mpzch_lookup_gather")
+    status = (_native or _load_native()).lookup_gather(handle, identities, ids, rows, out_rows, out_slots, out_found)
+    if status:
+        raise MpzchError(status, "mpzch_lookup_gather")
 
 
 def mpzch_collect_delta(handle, identities, metadata, since_step: int, out_slots, out_ids, out_count):
-    _check(load_library().mpzch_collect_delta(handle, _ptr(identities, torch.int64), _ptr(metadata, torch.int32),
-                                              since_step, _ptr(out_slots, torch.int64), _ptr(out_ids, torch.int64),
-                                              out_slots.numel(), _ptr(out_count, torch.int64), _stream()),
-           "mpzch_collect_delta")
+    status = (_native or _load_native()).collect_delta(handle, identities, metadata, since_step, out_slots, out_ids, out_count)
+    if status:
+        raise MpzchError(status, "mpzch_collect_delta")
 
 
 def mpzch_gather_rows(slots, count_dev, rows, out_rows):
-    n, rb, st = _row_geometry(rows)
-    assert out_rows.is_contiguous()
-    _check(load_library().mpzch_gather_rows(_ptr(slots, torch.int64), _ptr(count_dev, torch.int64), slots.numel(),
-                                            rows.data_ptr(), n, rb, st,
-                                            out_rows.data_ptr(), _stream()), "mpzch_gather_rows")
+    status = (_native or _load_native()).gather_rows(slots, count_dev, rows, out_rows)
+    if status:
+        raise MpzchError(status, "mpzch_gather_rows")
 
 
 def mpzch_apply_delta(identities, slots, ids, count_dev, rows=None, delta_rows=None):
-    if rows is not None:
-        n, rb, st = _row_geometry(rows)
-        rp, dp = rows.data_ptr(), delta_rows.data_ptr()
-    else:
-        n, rb, st, rp, dp = 0, 0, 0, None, None
-    _check(load_library().mpzch_apply_delta(_ptr(identities, torch.int64), identities.numel(), _ptr(slots, torch.int64),
-                                            _ptr(ids, torch.int64), _ptr(count_dev, torch.int64), slots.numel(),
-                                            rp, n, rb, st, dp, _stream()), "mpzch_apply_delta")
+    status = (_native or _load_native()).apply_delta(identities, slots, ids, count_dev, rows, delta_rows)
+    if status:
+        raise MpzchError(status, "mpzch_apply_delta")
 
 
 def mpzch_group_create(handles):
@@ -315,54 +271,36 @@ def mpzch_remap_jagged_feature_ttl(group, identities, metadata, values, ttls, fe
                                    out_evicted_slots, evicted_offsets, out_num_evicted, out_stats=None):
     """identities / metadata: lists of device tensors; ttls: int32 per value or None;
     evicted_offsets: host list of ints."""
-    T = len(identities)
-    ip = (ctypes.c_void_p * T)(*[t.data_ptr() for t in identities])
-    mp = (ctypes.c_void_p * T)(*[t.data_ptr() for t in metadata])
-    eo = (ctypes.c_int64 * (T + 1))(*[int(x) for x in evicted_offsets])
-    _check(load_library().mpzch_remap_jagged_feature_ttl(
-        group, ip, mp, _ptr(values, torch.int64), _ptr(ttls, torch.int32), _ptr(feature_offsets, torch.int64),
-        values.numel(), step, _ptr(out_slots, torch.int64), _ptr(out_evicted_slots, torch.int64), eo,
-        _ptr(out_num_evicted, torch.int64), _ptr(out_stats, torch.int64), _stream()), "mpzch_remap_jagged_feature_ttl")
+    status = (_native or _load_native()).remap_jagged(group, identities, metadata, values, ttls, feature_offsets, step,
+                                                      out_slots, out_evicted_slots, evicted_offsets, out_num_evicted,
+                                                      out_stats)
+    if status:
+        raise MpzchError(status, "mpzch_remap_jagged_feature_ttl")
 
 
 def mpzch_remap_jagged(group, identities, metadata, values, feature_offsets, step: int, out_slots,
                        out_evicted_slots, evicted_offsets, out_num_evicted, out_stats=None):
     """identities / metadata: lists of device tensors; evicted_offsets: host list of ints."""
-    T = len(identities)
-    ip = (ctypes.c_void_p * T)(*[t.data_ptr() for t in identities])
-    mp = (ctypes.c_void_p * T)(*[t.data_ptr() for t in metadata])
-    eo = (ctypes.c_int64 * (T + 1))(*[int(x) for x in evicted_offsets])
-    _check(load_library().mpzch_remap_jagged(group, ip, mp, _ptr(values, torch.int64),
-                                             _ptr(feature_offsets, torch.int64), values.numel(), step,
-                                             _ptr(out_slots, torch.int64), _ptr(out_evicted_slots, torch.int64), eo,
-                                             _ptr(out_num_evicted, torch.int64), _ptr(out_stats, torch.int64),
-                                             _stream()), "mpzch_remap_jagged")
+    status = (_native or _load_native()).remap_jagged(group, identities, metadata, values, None, feature_offsets, step,
+                                                      out_slots, out_evicted_slots, evicted_offsets, out_num_evicted,
+                                                      out_stats)
+    if status:
+        raise MpzchError(status, "mpzch_remap_jagged")
 
 
 def mpzch_reset_rows_jagged(group, evicted_slots, evicted_offsets, num_evicted, tensors, init_rows=None):
     """tensors: one 2-D device tensor (or None) per table of the group; evicted_offsets: host list of ints."""
-    T = len(tensors)
-    init_rows = init_rows or [None] * T
-    arr = (_Rows * T)()
-    for k, (t, init) in enumerate(zip(tensors, init_rows)):
-        if t is None:
-            arr[k] = _Rows(None, 0, 0, 0, None)
-        else:
-            n, rb, st = _row_geometry(t)
-            arr[k] = _Rows(t.data_ptr(), n, rb, st, None if init is None else init.data_ptr())
-    eo = (ctypes.c_int64 * (T + 1))(*[int(x) for x in evicted_offsets])
-    _check(load_library().mpzch_reset_rows_jagged(group, _ptr(evicted_slots, torch.int64), eo,
-                                                  _ptr(num_evicted, torch.int64), arr, _stream()),
-           "mpzch_reset_rows_jagged")
+    status = (_native or _load_native()).reset_rows_jagged(group, evicted_slots, evicted_offsets, num_evicted, tensors,
+                                                           init_rows or [None] * len(tensors))
+    if status:
+        raise MpzchError(status, "mpzch_reset_rows_jagged")
 
 
 def mpzch_lookup_jagged(group, identities, values, feature_offsets, out_slots, out_found=None):
     """identities: list of device tensors, one per table of the group."""
-    T = len(identities)
-    ip = (ctypes.c_void_p * T)(*[t.data_ptr() for t in identities])
-    _check(load_library().mpzch_lookup_jagged(group, ip, _ptr(values, torch.int64), _ptr(feature_offsets, torch.int64),
-                                              values.numel(), _ptr(out_slots, torch.int64), _ptr(out_found, torch.uint8),
-                                              _stream()), "mpzch_lookup_jagged")
+    status = (_native or _load_native()).lookup_jagged(group, identities, values, feature_offsets, out_slots, out_found)
+    if status:
+        raise MpzchError(status, "mpzch_lookup_jagged")
 
 
 def _times(fn, handle):

@@ -13,6 +13,8 @@ DEPS = [SRC, os.path.join(HERE, "csrc", "mpzch_kernels.hpp"),
         os.path.join(HERE, "csrc", "mpzch_row_kernels.hpp"),
         os.path.join(os.path.dirname(HERE), "include", "mpzch.h")]
 LIB = os.path.join(HERE, "libmpzch.so")
+NATIVE_SRC = os.path.join(HERE, "csrc", "native_call.cpp")
+NATIVE = os.path.join(HERE, "_native.so")
 CEIL_SRC = os.path.join(HERE, "csrc", "memory_ceilings.hip")
 CEIL_BIN = os.path.join(HERE, "memory_ceilings.bin")
 
@@ -34,7 +36,26 @@ def build_library(verbose: bool = False) -> str:
         print(" ".join(cmd), flush=True)
     subprocess.check_call(cmd)
     os.replace(LIB + ".tmp", LIB)
+    build_native(verbose)
     return LIB
+
+
+def build_native(verbose: bool = False) -> str:
+    """The module that marshals the repeated calls of the binding (host code; torch's headers, for its tensors and streams)."""
+    import sysconfig
+    import torch
+    lib = os.path.join(os.path.dirname(torch.__file__), "lib")
+    rocm = os.path.dirname(os.path.dirname(hipcc())) if os.path.isabs(hipcc()) else "/opt/rocm"
+    cmd = [os.environ.get("CXX", "g++"), "-O2", "-std=c++17", "-fPIC", "-shared", "-Wall", "-fvisibility=hidden",
+           "-D__HIP_PLATFORM_AMD__", "-DUSE_ROCM",               # what torch's stream header asks of a plain host compiler
+           "-isystem", os.path.join(os.path.dirname(torch.__file__), "include"), "-isystem", os.path.join(rocm, "include"),
+           "-isystem", sysconfig.get_paths()["include"],
+           NATIVE_SRC, "-o", NATIVE + ".tmp", "-L" + lib, "-ltorch_python", "-ltorch_cpu", "-lc10", "-lc10_hip"]
+    if verbose:
+        print(" ".join(cmd), flush=True)
+    subprocess.check_call(cmd)
+    os.replace(NATIVE + ".tmp", NATIVE)
+    return NATIVE
 
 
 def build_memory_ceilings(verbose: bool = False) -> str:

@@ -451,11 +451,12 @@ mpzch_status_t launch_remap(Scratch &sc, Timing &tm, Params p, int32_t max_p_lru
     return MPZCH_OK;
 }
 
+int fill_grid(int64_t count) { return (int)((count + kBlock - 1) / kBlock < 4096 ? (count + kBlock - 1) / kBlock : 4096); }
+
 mpzch_status_t fill64(int64_t *dst, int64_t count, long long value, hipStream_t s)
 {
     if (count <= 0) return MPZCH_OK;
-    const int grid = (int)((count + kBlock - 1) / kBlock < 4096 ? (count + kBlock - 1) / kBlock : 4096);
-    hipLaunchKernelGGL(k_fill64, dim3(grid), dim3(kBlock), 0, s, (long long *)dst, count, value);
+    hipLaunchKernelGGL(k_fill64, dim3(fill_grid(count)), dim3(kBlock), 0, s, (long long *)dst, count, value);
     LAUNCH_CHECK();
     return MPZCH_OK;
 }
@@ -463,8 +464,7 @@ mpzch_status_t fill64(int64_t *dst, int64_t count, long long value, hipStream_t 
 mpzch_status_t fill32(int32_t *dst, int64_t count, int32_t value, hipStream_t s)
 {
     if (count <= 0) return MPZCH_OK;
-    const int grid = (int)((count + kBlock - 1) / kBlock < 4096 ? (count + kBlock - 1) / kBlock : 4096);
-    hipLaunchKernelGGL(k_fill32, dim3(grid), dim3(kBlock), 0, s, dst, count, value);
+    hipLaunchKernelGGL(k_fill32, dim3(fill_grid(count)), dim3(kBlock), 0, s, dst, count, value);
     LAUNCH_CHECK();
     return MPZCH_OK;
 }
@@ -638,13 +638,13 @@ mpzch_status_t mpzch_init_tensors(const mpzch_table_t *t, int64_t *identities, i
     if (t->cfg.layout == MPZCH_LAYOUT_RECORDS) {
         if (!records_ok(identities, metadata)) return MPZCH_ERR_INVALID_ARG;
         const int64_t count = t->cfg.num_slots;
-        const int grid = (int)((count + kBlock - 1) / kBlock < 4096 ? (count + kBlock - 1) / kBlock : 4096);
-        hipLaunchKernelGGL(k_init_records, dim3(grid), dim3(kBlock), 0, s, (u32x4 *)identities, count);
+        hipLaunchKernelGGL(k_init_records, dim3(fill_grid(count)), dim3(kBlock), 0, s, (u32x4 *)identities, count);
         LAUNCH_CHECK();
         return MPZCH_OK;
     }
-    TRY(fill64(identities, t->cfg.num_slots, -1, s));
-    if (metadata) TRY(fill32(metadata, t->cfg.num_slots, -1, s));
+    if (!metadata) return fill64(identities, t->cfg.num_slots, -1, s);
+    hipLaunchKernelGGL(k_init_tensors, dim3(fill_grid(t->cfg.num_slots)), dim3(kBlock), 0, s, (long long *)identities, metadata, t->cfg.num_slots);
+    LAUNCH_CHECK();
     return MPZCH_OK;
 }
 

@@ -2023,6 +2023,15 @@ __global__ __launch_bounds__(kBlock) void k_init_records(u32x4 *dst, int64_t cou
         dst[i] = v;
 }
 
+// initial state of a table kept as two tensors (one launch: a second one takes longer than a small table)
+__global__ __launch_bounds__(kBlock) void k_init_tensors(long long *ids, int32_t *metadata, int64_t count)
+{
+    for (int64_t i = (int64_t)blockIdx.x * kBlock + threadIdx.x; i < count; i += (int64_t)gridDim.x * kBlock) {
+        ids[i] = -1;
+        metadata[i] = -1;
+    }
+}
+
 __global__ __launch_bounds__(kBlock) void k_fill32(int32_t *dst, int64_t count, int32_t value)
 {
     for (int64_t i = (int64_t)blockIdx.x * kBlock + threadIdx.x; i < count; i += (int64_t)gridDim.x * kBlock)
