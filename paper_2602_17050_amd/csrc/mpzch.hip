@@ -294,6 +294,23 @@ mpzch_status_t launch_discover(const Params &p, int grid, hipStream_t s)
     return MPZCH_OK;
 }
 
+// A lookup of few ids (k_lookup_short).  max_p: the longest window of the tables involved.
+bool short_lookup(Params &p, int32_t max_p)
+{
+    p.short_shift = window_shift(max_p);
+    return p.n << p.short_shift <= kShortBlocks;
+}
+template <bool GATHER>
+mpzch_status_t launch_lookup_short(const Params &p, hipStream_t s)
+{
+    const int per_block = kBlock >> p.short_shift;
+    const int grid = (int)((p.n + per_block - 1) / per_block);
+    if (p.num_tables > 1) hipLaunchKernelGGL((k_lookup_short<true, GATHER>), dim3(grid), dim3(kBlock), 0, s, p);
+    else hipLaunchKernelGGL((k_lookup_short<false, GATHER>), dim3(grid), dim3(kBlock), 0, s, p);
+    LAUNCH_CHECK();
+    return MPZCH_OK;
+}
+
 // max_p_lru: largest min(max_probe, num_slots) of the LRU tables involved, 0 when there is none
 template <bool MULTI, bool REC>
 void launch_allocate_lru(int32_t max_p_lru, const Params &p, int grid, hipStream_t s)
@@ -824,6 +841,10 @@ mpzch_status_t mpzch_lookup(const mpzch_table_t *t, const int64_t *identities,
     p.out_slots = out_slots;
     p.out_found = out_found;
     p.t0 = make_desc(t->cfg, const_cast<int64_t *>(identities), nullptr, 0, 0);
+    if (short_lookup(p, p.t0.P)) {
+        TIMED(t->tm, KLookup, s, launch_lookup_short<false>(p, s));
+        return MPZCH_OK;
+    }
     const int grid = grid_for(n, kBlock, num_cus, discover_blocks_per_cu());
     p.num_segs = grid * kWavesPerBlock;
     p.seg_chunks = (int32_t)(((n + kWave - 1) / kWave + p.num_segs - 1) / p.num_segs);
@@ -980,6 +1001,10 @@ mpzch_status_t mpzch_lookup_gather(const mpzch_table_t *t, const int64_t *identi
     p.g_shift = -1;
     for (int b = 0; b <= 20; ++b)
         if (g.chunks == ((int64_t)1 << b)) p.g_shift = b;
+    if (short_lookup(p, p.t0.P)) {
+        TIMED(t->tm, KLookup, s, launch_lookup_short<true>(p, s));
+        return MPZCH_OK;
+    }
     // five workgroups of this kernel fit a compute unit: where every wavefront has several chunks anyway, a grid that runs
     // in one go is better than one and a half turns (2 M ids with rows of 256 bytes: 208 -> 197 us)
     const int full = num_cus * discover_blocks_per_cu() * kBlock;
@@ -1183,6 +1208,12 @@ mpzch_status_t mpzch_lookup_jagged(mpzch_group_t *g, const int64_t *const *ident
     p.offsets = feature_offsets;
     p.t0 = descs[0];
     if (T == 1) p.num_tables = 1;            // a group of one table: the single-table kernel, offsets unused
+    int32_t max_p = 1;
+    for (const TableDesc &d : descs) max_p = d.P > max_p ? d.P : max_p;
+    if (short_lookup(p, max_p)) {
+        TIMED(g->tm, KLookup, s, launch_lookup_short<false>(p, s));
+        return MPZCH_OK;
+    }
     const int grid = grid_for(total_values, kBlock, g->sc.num_cus, discover_blocks_per_cu());
     p.num_segs = grid * kWavesPerBlock;
     p.seg_chunks = (int32_t)(((total_values + kWave - 1) / kWave + p.num_segs - 1) / p.num_segs);

@@ -224,3 +224,26 @@ def test_new_ids_with_many_copies(n, evict):
         ids[: n // 3] = hot[0]
         t.step(ids[rng.permutation(n)], 2 * step)
     t.close()
+
+
+# ---- lookups of few ids: as many ids per wavefront as one pass holds the windows of
+@pytest.mark.parametrize("layout", ["separate", "records"])
+@pytest.mark.parametrize("slots,probe", [(5, 8), (300, 8), (300, 16), (4_099, 17), (4_099, 33), (4_099, 65), (4_099, 300)])
+def test_lookups_around_the_largest_short_one(slots, probe, layout):
+    rng = rng_for(910)
+    t = Pair(slots, probe, 1, True, 23, layout=layout)
+    for step in range(3):
+        t.step(wl.zipf_ids(rng, slots + 7, 1.02, 2 * slots), step)
+    shift = 0 if probe <= 8 else 1 if probe <= 16 else 2 if probe <= 32 else 3
+    edge = 32_768 >> min(shift, 0 if slots <= 8 else shift)
+    rows_np = wl.embedding_pattern(slots, 12, np.float32)
+    rows = torch.from_numpy(rows_np).cuda()
+    for n in (1, 7, 8, 9, 31, 33, 64, 65, 257, edge - 1, edge, edge + 1):
+        q = np.concatenate([wl.zipf_ids(rng, n, 1.02, 3 * slots)[: n - n // 10], rng.integers(-3, 1 << 40, size=n // 10)])
+        so, fo = t.o.lookup(q)
+        sg, fg = t.g.lookup(torch.from_numpy(q).cuda())
+        assert np.array_equal(sg.cpu().numpy(), so) and np.array_equal(fg.cpu().numpy(), fo), n
+        out = torch.full((n, 12), -1.0, dtype=torch.float32, device="cuda")
+        mp.mpzch_lookup_gather(t.g.handle, t.g.identities, torch.from_numpy(q).cuda(), rows, out)
+        assert np.array_equal(out.cpu().numpy(), rows_np[so % slots]), n
+    t.close()
