@@ -411,13 +411,20 @@ mpzch_status_t run_remap(Scratch &sc, Timing &tm, const Params &p, int32_t max_p
     return st;
 }
 
+template <int SHIFT>
+void launch_discover_chunk(const Params &p, int grid, hipStream_t s)
+{
+    if (p.t0.sh) hipLaunchKernelGGL((k_discover_chunk<true, SHIFT>), dim3(grid), dim3(kBlock << SHIFT), 0, s, p);
+    else hipLaunchKernelGGL((k_discover_chunk<false, SHIFT>), dim3(grid), dim3(kBlock << SHIFT), 0, s, p);
+}
+
 // One chunk per wavefront (mpzch_chunk_kernels.hpp): grid = workgroups of 256 positions.
 mpzch_status_t launch_remap_chunks(Timing &tm, const Params &p, int32_t max_p_lru, int grid, hipStream_t s)
 {
     const bool rec = p.t0.sh != 0;
     if (!tm.begin(KDiscover, s)) return MPZCH_ERR_HIP;
-    if (rec) hipLaunchKernelGGL((k_discover_chunk<true>), dim3(grid), dim3(kBlock), 0, s, p);
-    else hipLaunchKernelGGL((k_discover_chunk<false>), dim3(grid), dim3(kBlock), 0, s, p);
+    if (window_shift(p.t0.P) == 1 && 2 * p.n <= kShortBlocks) launch_discover_chunk<1>(p, grid, s);
+    else launch_discover_chunk<0>(p, grid, s);
     LAUNCH_CHECK();
     if (!tm.end(s) || !tm.begin(KAllocate, s)) return MPZCH_ERR_HIP;
     if (max_p_lru > 0 && rec) launch_allocate_lru_chunk<true>(max_p_lru, p, grid, s);

@@ -151,26 +151,34 @@ __device__ __forceinline__ uint32_t set_insert_wave(const Params &p, bool miss, 
     return (uint32_t)__shfl((int)e, from);
 }
 
-template <bool REC>
-__global__ __launch_bounds__(kBlock, 4) void k_discover_chunk(Params p)
+// SHIFT 1: a wavefront takes 32 positions, so that one pass holds the whole windows of up to 16 slots (see k_lookup_short;
+// while the call has no more than kShortBlocks blocks), and the workgroup's 256 positions have 512 threads.  65 536
+// positions per step, the 50-step pass 1 078 -> 1 056 us.  Longer windows gain nothing by it: what a look less saves, the
+// barriers of 1 024 threads and the copies of an id that no longer meet in one wavefront cost.
+template <bool REC, int SHIFT>
+__global__ __launch_bounds__(kBlock << SHIFT, 4) void k_discover_chunk(Params p)
 {
-    __shared__ ProbeReq s_req[kWavesPerBlock][kWave];
-    __shared__ __attribute__((aligned(16))) uint8_t s_code[kWavesPerBlock][kWave * kFirstG];
-    __shared__ uint32_t s_red[kWavesPerBlock][5];
-    __shared__ MergeArea<kBlock, 2 * kBlock> s_merge;
+    constexpr int THREADS = kBlock << SHIFT, WAVES = THREADS / kWave, PER = kWave >> SHIFT;
+    __shared__ ProbeReq s_req[WAVES][kWave];
+    __shared__ __attribute__((aligned(16))) uint8_t s_code[WAVES][kWave * kFirstG];
+    __shared__ uint32_t s_red[WAVES][5];
+    __shared__ MergeArea<THREADS, 2 * kBlock> s_merge;
 
     const int lane = lane_id(), w = threadIdx.x / kWave;
-    const int64_t pos = (int64_t)blockIdx.x * kBlock + threadIdx.x;
-    const bool in = pos < p.n;
+    const int64_t pos = (int64_t)blockIdx.x * kBlock + w * PER + lane;
+    const bool in = lane < PER && pos < p.n;
     const Tab d = view(p.t0);
     const int64_t id = in ? p.ids[pos] : -1;
     const bool valid = in && id >= 0;
     const int64_t home = home_slot(id, d.seed, d.N);
-    // first block: the aligned one, or in a table that the caches hold the 8 slots from the home slot on (k_allocate)
-    const int o = (d.N << (3 + d.sh)) > kCachedTableBytes ? block_offset(d, home, kFirstG) : 0;
     bool fresh = false;
-    int res = probe_pass<kFirstG, false, REC>(d, id, home, valid ? -o : d.P, s_req[w], s_code[w], p.step, &fresh);
-    int q = kFirstG - o;
+    int res = kProbeGoOn, q = 0;
+    if constexpr (SHIFT == 0) {
+        // first block: the aligned one, or in a table that the caches hold the 8 slots from the home slot on (k_allocate)
+        const int o = (d.N << (3 + d.sh)) > kCachedTableBytes ? block_offset(d, home, kFirstG) : 0;
+        res = probe_pass<kFirstG, false, REC>(d, id, home, valid ? -o : d.P, s_req[w], s_code[w], p.step, &fresh);
+        q = kFirstG - o;
+    }
     for (;;) {
         const bool need = valid && res == kProbeGoOn && q < d.P;
         if (!__any(need)) break;
@@ -210,7 +218,7 @@ __global__ __launch_bounds__(kBlock, 4) void k_discover_chunk(Params p)
         __syncthreads();
         if (threadIdx.x == 0) {
             uint32_t t[5] = {0, 0, 0, 0, 0};
-            for (int i = 0; i < kWavesPerBlock; ++i)
+            for (int i = 0; i < WAVES; ++i)
                 for (int k = 0; k < 5; ++k) t[k] += s_red[i][k];
             p.wg_words[3 * blockIdx.x] = pack3(t[0], t[1], t[2]);
             p.wg_words[3 * blockIdx.x + 1] = (uint64_t)t[3] | ((uint64_t)t[4] << 32);

@@ -1067,9 +1067,10 @@ __global__ __launch_bounds__(kBlock, 4) void k_lookup_tables(Params p)
 // Lookups of few ids.  The chip is idle and round trips are what counts, so a wavefront takes only as many ids as lets the
 // 64 blocks of one pass hold the whole window of each (32 ids with windows of 16 slots, 8 with 64; longer ones take
 // more passes): a lookup is ids, one look at the table, outputs.  Used while the blocks of a call are no more than
-// kShortBlocks, which the memory system serves in a microsecond (lookup of 5 000 ids, windows of 32 slots, 5.8 -> 3.9 us;
-// 10 K values over 26 tables 7.9 -> 5.6 us).
-constexpr int64_t kShortBlocks = 32768;
+// kShortBlocks (lookup of 5 000 ids, windows of 32 slots, 5.8 -> 3.9 us; 10 K values over 26 tables 7.9 -> 5.6 us; at the
+// limit, 128 000 ids with windows of 16 slots 5.2 -> 4.6, 32 000 with 64 7.0 -> 5.9; at twice as many blocks, 64 000 with
+// 64, 7.3 against 8.2).
+constexpr int64_t kShortBlocks = (int64_t)1 << 18;
 constexpr int window_shift(int P) { return P <= 8 ? 0 : P <= 16 ? 1 : P <= 32 ? 2 : 3; }
 
 template <bool MULTI, bool GATHER>

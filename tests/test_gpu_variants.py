@@ -235,7 +235,7 @@ def test_lookups_around_the_largest_short_one(slots, probe, layout):
     for step in range(3):
         t.step(wl.zipf_ids(rng, slots + 7, 1.02, 2 * slots), step)
     shift = 0 if probe <= 8 else 1 if probe <= 16 else 2 if probe <= 32 else 3
-    edge = 32_768 >> min(shift, 0 if slots <= 8 else shift)
+    edge = (1 << 18) >> (0 if slots <= 8 else shift)
     rows_np = wl.embedding_pattern(slots, 12, np.float32)
     rows = torch.from_numpy(rows_np).cuda()
     for n in (1, 7, 8, 9, 31, 33, 64, 65, 257, edge - 1, edge, edge + 1):
