@@ -6,6 +6,7 @@
 // phases are those of mpzch_chunk_kernels.hpp.  Remap with row reset, us per call, against three launches: 64 to 512
 // positions 14 to 17.5 -> 7 to 9, 1 024 positions 13.8 to 17.7 -> 7.0 to 12.4; with two positions per thread (2 048) the
 // one compute unit took as long as three launches do (10.8 to 21.8 against 13.8 to 19.2), so the line is drawn at 1 024.
+// The claimants listed and the first look without index arithmetic: the tiny 8-step pass 97.8 -> 93.2 us.
 #pragma once
 #include "mpzch_chunk_kernels.hpp"
 
@@ -17,7 +18,9 @@ constexpr int kOneBlockWaves = kOneBlock / kWave;
 struct OneBlockArea {
     ClaimReq req[kOneBlockWaves][kWave];                     // (Pass 1: the requests of its probes)
     alignas(16) uint8_t code[kOneBlockWaves][kWave * kAllocG];
-    int64_t id[kOneBlock];                              // later: the rows to reset
+    int64_t id[kOneBlock];
+    int64_t row[kOneBlock];                                  // rows to reset
+    uint16_t claimant[kOneBlock];                            // first occurrences of the missed ids
     uint32_t set[2 * kOneBlock];
     uint32_t place[kOneBlock];
     uint32_t count[kStatCount];                              // (probe lengths of 1 024 positions fit 32 bits)
@@ -46,8 +49,8 @@ __global__ __launch_bounds__(kOneBlock) void k_remap_block(Params p)
 
     // Pass 1.  (Blocks of the next 8 slots: round trips count here, not lines.)
     bool fresh = false;
-    int res = probe_pass<kFirstG, false, REC>(d, id, home, valid ? 0 : d.P, s_probe, s.code[w], p.step, &fresh);
-    int q = kFirstG;
+    int q = 0;
+    int res = probe_first<false, REC, false>(d, id, home, first_slot_step(d), s_probe, s.code[w], p.step, &fresh, &q);
     for (;;) {
         const bool need = valid && res == kProbeGoOn && q < d.P;
         if (!__any(need)) break;
@@ -92,16 +95,25 @@ __global__ __launch_bounds__(kOneBlock) void k_remap_block(Params p)
     // every id that was resident has been refreshed, every first occurrence is elected
     __syncthreads();
 
-    // claims
+    // claims.  (The one compute unit is busy with instructions, not waiting: the claimants are listed, so that they take
+    // up as few wavefronts as they can.)
     const int32_t bound = expiry_bound(d, p.step);
     const uint32_t first = e != kNoEntry ? s.set[e] : kNoEntry;
     uint32_t outcome = 0;                                    // 1 = this lane's last claim was an insert, 2 = an eviction
     int64_t claimed = 0;
+    {
+        const uint64_t am = __ballot(first == pos);
+        uint32_t at = 0;
+        if (lane == 0 && am) at = atomicAdd(&s.count[kDistinctMiss], (uint32_t)__popcll(am));
+        at = (uint32_t)__builtin_amdgcn_readfirstlane((int)at);
+        if (first == pos) s.claimant[at + (uint32_t)__popcll(am & ((1ull << lane) - 1ull))] = (uint16_t)pos;
+    }
+    __syncthreads();
     Claimant cl;
-    cl.active = first == pos;
-    cl.pos = pos;
+    cl.active = t < (int)s.count[kDistinctMiss];
+    cl.pos = cl.active ? s.claimant[t] : 0u;
     cl.q = 0;
-    cl.home = home;
+    cl.home = cl.active ? home_slot(s.id[cl.pos], d.seed, d.N) : 0;
     for (;;) {
         const uint64_t am = __ballot(cl.active);
         if (!am) break;
@@ -118,19 +130,15 @@ __global__ __launch_bounds__(kOneBlock) void k_remap_block(Params p)
         __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
     }
     const uint64_t em = __ballot(outcome == 2u);
-    const uint32_t agents = (uint32_t)__popcll(__ballot(first == pos)), ins = (uint32_t)__popcll(__ballot(outcome == 1u));
+    const uint32_t ins = (uint32_t)__popcll(__ballot(outcome == 1u));
     uint32_t base = 0;
-    if (lane == 0) {
-        atomicAdd(&s.count[kDistinctMiss], agents);
-        atomicAdd(&s.count[kInserts], ins);
-        base = atomicAdd(&s.count[kEvictions], (uint32_t)__popcll(em));
-    }
+    if (lane == 0 && ins) atomicAdd(&s.count[kInserts], ins);
+    if (lane == 0 && em) base = atomicAdd(&s.count[kEvictions], (uint32_t)__popcll(em));
     base = (uint32_t)__builtin_amdgcn_readfirstlane((int)base);
     if (outcome == 2u) {
         const uint32_t at = base + (uint32_t)__popcll(em & ((1ull << lane) - 1ull));
         if ((int64_t)at < p.t0.ev_cap) p.out_evicted[at] = claimed;
-        // (the ids in LDS are not looked at any more: the displaced are known by their position)
-        if (p.r_rows) s.id[at] = claimed >= p.g_num_rows ? claimed % p.g_num_rows : claimed;
+        if (p.r_rows) s.row[at] = claimed >= p.g_num_rows ? claimed % p.g_num_rows : claimed;
     }
     // every claim stands
     __syncthreads();
@@ -150,7 +158,7 @@ __global__ __launch_bounds__(kOneBlock) void k_remap_block(Params p)
         const int waves = (threads + kWave - 1) / kWave, per = (evicted + waves - 1) / waves;
         const int lo = w * per < evicted ? w * per : evicted;
         const int hi = lo + per < evicted ? lo + per : evicted;
-        reset_staged_rows(p, s.id + lo, hi - lo);
+        reset_staged_rows(p, s.row + lo, hi - lo);
     }
     if (t == 0) p.out_num_evicted[0] = evicted;
     if (p.out_stats && t < kStatCount)

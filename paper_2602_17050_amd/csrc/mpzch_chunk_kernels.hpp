@@ -175,9 +175,11 @@ __global__ __launch_bounds__(kBlock << SHIFT, 4) void k_discover_chunk(Params p)
     int res = kProbeGoOn, q = 0;
     if constexpr (SHIFT == 0) {
         // first block: the aligned one, or in a table that the caches hold the 8 slots from the home slot on (k_allocate)
-        const int o = (d.N << (3 + d.sh)) > kCachedTableBytes ? block_offset(d, home, kFirstG) : 0;
-        res = probe_pass<kFirstG, false, REC>(d, id, home, valid ? -o : d.P, s_req[w], s_code[w], p.step, &fresh);
-        q = kFirstG - o;
+        const uint32_t step = first_slot_step(d);
+        if ((d.N << (3 + d.sh)) > kCachedTableBytes)
+            res = probe_first<false, REC, true>(d, id, home, step, s_req[w], s_code[w], p.step, &fresh, &q);
+        else
+            res = probe_first<false, REC, false>(d, id, home, step, s_req[w], s_code[w], p.step, &fresh, &q);
     }
     for (;;) {
         const bool need = valid && res == kProbeGoOn && q < d.P;

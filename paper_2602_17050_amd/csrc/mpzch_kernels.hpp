@@ -3,7 +3,7 @@
 // Kernel sequence of one training remap (paper Sec. 3.2 / Algorithm 1, Sec. 3.4, Sec. 3.6):
 //   k_discover   Pass 1 for every position.  An 8-lane group reads the aligned block of 8 slots
 //                that holds the id's home slot with one coalesced access; ids and results travel
-//                between the id's lane and the lanes that load for it through LDS (probe_pass);
+//                between the id's lane and the lanes that load for it through LDS (probe_first);
 //                the few ids whose window continues are parked in LDS and scanned 8 slots at
 //                a time.  Hits store metadata = step and the output slot.  (k_lookup is the
 //                same body without writes, k_discover_tables / k_lookup_tables the bodies for
@@ -423,15 +423,13 @@ __device__ __forceinline__ void publish_counters(const Params &p, unsigned long 
 }
 
 // ------------------------------------------------------------------ Pass 1 (discovery)
-// One probe pass over the 64 ids held one per lane: the id of lane L is compared with the G
-// slots of rounds [q, q + G) of its window (q may be negative: rounds below 0 do not exist;
-// q >= d.P switches the lane off).  A G-lane group serves one id per access, so with q chosen
-// such that home + q is a multiple of G slots every access reads one aligned block of 8 G bytes.
-// All G accesses are issued before the first result is looked at; a lane without a slot to
-// look at re-reads the home slot (a valid address, same or neighbouring line; slot 0 if the id
-// is switched off or belongs to another table), so the loads carry no branch and stay in flight
-// together.  d is wave-uniform.  Returns the round of the match; kProbeGoOn when the id is not among
-// these slots; or, when in addition one of them is empty, a value <= kProbeAbsent that names the round
+// A probe pass compares the ids held one per lane with 8 consecutive slots each (or several times 8: probe_more).  Eight
+// lanes read the slots of one id with one access, eight ids per load instruction, and all loads of a pass are in flight
+// together.  What the lanes that load need to know goes through LDS (ProbeReq), what each saw (1 = the id, 2 = an empty
+// slot, 0 = neither; 4 added to 1 over records: the metadata is what the hit would store) goes back through LDS as one
+// byte per slot, and the id's own lane reads its bytes at once and drops those of rounds that do not exist: no
+// cross-lane operation depends on a load, and nothing branches.  A pass returns the round of the match; kProbeGoOn when
+// the id is not among these slots; or, when in addition one of them is empty, a value <= kProbeAbsent that names the round
 // of the first empty slot (probe_absent / absent_len): a slot never becomes empty again once it was
 // occupied, so no resident id lies beyond an empty slot of its window and the search can end there.
 constexpr int kFirstG = 8;             // slots looked at by the first pass: the aligned 64 bytes that hold the home slot
@@ -444,7 +442,7 @@ __device__ __forceinline__ int absent_len(int code) { return -code - 1; }
 
 // What the lane that holds an id leaves in LDS for the lanes that load for it: the id, and `where`
 // = address of the identity of the first slot to read (bits 0..47: device addresses have no more)
-// with, in bit 48 + r, whether round q + r exists (r < G).
+// with, for probe_more, in bit 48 + r whether round q + r exists (r < G).
 struct alignas(16) ProbeReq {
     int64_t id;
     uint64_t where;
@@ -452,9 +450,8 @@ struct alignas(16) ProbeReq {
 constexpr int kWhereAddrBits = 48;
 
 // the loads of one pass: lane r of a group reads slot number k(r) behind the first one, where k counts the rounds
-// that exist below its own -- its own slot when its round exists, else the first slot (r < r_lo) or the one after
-// the last (r >= r_hi): valid addresses in or next to the line that is fetched anyway.  Slots past the end of the
-// table go on at slot 0.
+// that exist below its own -- its own slot when its round exists, else the one after the last: a valid address in or next
+// to the line that is fetched anyway.  Slots past the end of the table go on at slot 0.
 // NT: the loads are marked non-temporal (see k_discover_streaming).  REC: a table of records, read with the
 // metadata (12 bytes per lane, the same line): what comes back besides the id is the slot's metadata.
 template <int G, bool NT, bool REC>
@@ -485,68 +482,27 @@ __device__ __forceinline__ void probe_loads(const Tab &d, const ProbeReq *s_req,
     }
 }
 
-// s_req: 64 requests, s_code: 64 * G bytes, both this wavefront's own areas of LDS.  The G lanes of
-// a group read G consecutive slots of one id per access; what each saw (1 = the id, 2 = an empty
-// slot, 0 = neither) goes back through LDS as one byte per slot, and the id's own lane reads its G
-// bytes at once and drops those of rounds that do not exist: no cross-lane operation depends on a
-// load, and nothing branches.  REC: *fresh tells whether the slot of a hit already holds the metadata value
-// fresh_meta (read with the id, in the same access).
-template <int G, bool NT = false, bool REC = false>
-__device__ __forceinline__ int probe_pass(const Tab &d, int64_t id, int64_t home, int q, ProbeReq *s_req,
-                                          uint8_t *s_code, int32_t fresh_meta = 0, bool *fresh = nullptr)
+// probe_first's slot_step (tables of fewer than 8 slots have no block to read: every lane reads slot 0)
+__device__ __forceinline__ uint32_t first_slot_step(const Tab &d)
 {
-    static_assert(G == 8, "the codes of one id are read back as one 64-bit word");
-    constexpr int IPI = kWave / G;
-    const int lane = lane_id();
-    const int g = lane / G;
-    // the rounds of [q, q + G) that exist are r_lo <= r < r_hi; none when the lane is switched off
-    const int r_lo = q < 0 ? -q : 0;
-    const int r_hi = d.P - q < G ? d.P - q : G;
-    const int count = r_hi - r_lo;
-    const bool on = count > 0;
-    const uint32_t rounds = on ? ((1u << r_hi) - 1u) & ~((1u << r_lo) - 1u) : 0u;
-    // the slots read for this id are first_slot .. first_slot + count (the last by lanes without a round)
-    const int64_t first_slot = on ? wrap(home + (q + r_lo), d.N) : 0;
-    s_req[lane] = ProbeReq{id, (uint64_t)(uintptr_t)(int64_t *)id_at(d, first_slot) | ((uint64_t)rounds << kWhereAddrBits)};
-    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-    int64_t v[G];
-    int32_t m[G];
-    probe_loads<G, NT, REC>(d, s_req, v, m);
-#pragma unroll
-    for (int t = 0; t < G; ++t) {
-        const int64_t gid = s_req[t * IPI + g].id;
-        uint8_t code = v[t] == gid ? 1 : (v[t] == -1 ? 2 : 0);
-        if constexpr (REC) code = v[t] == gid ? (m[t] == fresh_meta ? 5 : 1) : (v[t] == -1 ? 2 : 0);
-        s_code[t * kWave + lane] = code;        // = byte r of id t * IPI + g
-    }
-    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-    // the lowest set bit of the bytes of the rounds that exist: bit 8 j = found at round q + r_lo + j,
-    // bit 8 j + 1 = that round's slot is empty
-    const uint64_t x = *reinterpret_cast<const uint64_t *>(s_code + lane * G) >> (8 * r_lo);
-    // (bit 8 j + 2, only ever set together with bit 8 j: that slot's metadata needs no refresh)
-    const int bit = __ffsll((unsigned long long)x) - 1;
-    const int j = bit >> 3;
-    if constexpr (REC) *fresh = x != 0 && ((x >> (bit & 63)) & 4ull) != 0;
-    const int round = q + r_lo + j;
-    const int found = (x == 0 || j >= count) ? kProbeGoOn : ((bit & 1) ? probe_absent(round) : round);
-    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");    // the areas are written again by the next pass
-    return found;
+    return d.N >= kFirstG ? (uint32_t)(lane_id() % kFirstG) << (3 + d.sh) : 0u;
 }
 
-// The first pass of a large batch: the aligned block of 8 slots that holds the home slot.  Otherwise as probe_pass; next:
-// the round to go on with.  The lanes that load read the block as it lies, eight slots from its first one on (slot_step:
-// how far this lane's slot lies from it, in bytes), and only the id's own lane knows which of them are its rounds: two
-// instructions per load instead of fifteen.  An id whose block reaches out of the table leaves everything to the later
-// passes.  (Measured with the tables of a group looked at one at a time, see discover_body: 41 M values over 26 tables
+// The first pass: the aligned block of 8 slots that holds the home slot or, ALIGNED not set, the 8 slots from the home slot
+// on.  d is wave-uniform; s_req, s_code: this wavefront's own areas of LDS; next: the round to go on with; fresh: whether
+// the record of a hit holds fresh_meta already.  The lanes that load read the block as it lies, eight slots
+// from its first one on (slot_step: how far this lane's slot lies from it, in bytes), and only the id's own lane knows
+// which of them are its rounds: two instructions per load instead of fifteen.  An id whose block reaches out of the table
+// leaves everything to the later passes.  (Measured with the tables of a group looked at one at a time, see discover_body: 41 M values over 26 tables
 // 961 -> 882 us, lookup of 1 M ids 19.8 -> 18.4 us.)
-template <bool NT, bool REC>
+template <bool NT, bool REC, bool ALIGNED = true>
 __device__ __forceinline__ int probe_first(const Tab &d, int64_t id, int64_t home, uint32_t slot_step, ProbeReq *s_req,
                                            uint8_t *s_code, int32_t fresh_meta, bool *fresh, int *next)
 {
     constexpr int G = kFirstG, IPI = kWave / G;
     const int lane = lane_id();
     const int g = lane / G;
-    const int o = block_offset(d, home, G);
+    const int o = ALIGNED ? block_offset(d, home, G) : 0;
     const bool here = home >= o && home - o + G <= d.N;
     s_req[lane] = ProbeReq{id, (uint64_t)(uintptr_t)(int64_t *)id_at(d, here ? home - o : 0)};
     __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
@@ -598,7 +554,7 @@ __device__ __forceinline__ int blocks_shift(int count, int P)
 // A later pass: rounds q, q + 1, ... of the lanes with `need` set (the others' arguments are ignored).  The 64 blocks of
 // 8 slots that one pass reads are shared out among those lanes: the fewer are left, the more of its window each one
 // sees per round trip (8 slots, up to 64 when 8 lanes or fewer are left; a window at 95 % load is often longer than
-// 8 slots).  Returns as probe_pass; q is moved on past the slots that were looked at.
+// 8 slots).  q is moved on past the slots that were looked at.
 template <bool NT = false, bool REC = false>
 __device__ __forceinline__ int probe_more(const Tab &d, int64_t id, int64_t home, int &q, bool need, ProbeReq *s_req,
                                           uint8_t *s_code, int32_t fresh_meta = 0, bool *fresh = nullptr)
@@ -934,8 +890,7 @@ __device__ __forceinline__ void discover_body(const Params &p)
                 const bool mine = todo && (!multi || pos < t_hi);
                 const bool valid = mine && id >= 0;
                 const int64_t home = mine ? home_slot(id, d.seed, d.N) : 0;
-                // (tables of fewer than 8 slots have no block to read: every lane reads slot 0)
-                const uint32_t slot_step = d.N >= kFirstG ? (uint32_t)(lane % kFirstG) << (3 + d.sh) : 0u;
+                const uint32_t slot_step = first_slot_step(d);
                 bool fresh = false;
                 int next = 0;
                 const int res = probe_first<NT, REC>(d, id, home, slot_step, s_req[w], s_code[w], p.step, &fresh, &next);
