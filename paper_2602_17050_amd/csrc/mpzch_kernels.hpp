@@ -493,8 +493,9 @@ __device__ __forceinline__ uint32_t first_slot_step(const Tab &d)
 // the record of a hit holds fresh_meta already.  The lanes that load read the block as it lies, eight slots
 // from its first one on (slot_step: how far this lane's slot lies from it, in bytes), and only the id's own lane knows
 // which of them are its rounds: two instructions per load instead of fifteen.  An id whose block reaches out of the table
-// leaves everything to the later passes.  (Measured with the tables of a group looked at one at a time, see discover_body: 41 M values over 26 tables
-// 961 -> 882 us, lookup of 1 M ids 19.8 -> 18.4 us.)
+// leaves everything to the later passes.  (With the
+// tables of a group looked at one at a time, see discover_body: 41 M values over 26 tables 961 -> 882 us; lookup of 1 M ids
+// 19.8 -> 18.4 us.)
 template <bool NT, bool REC, bool ALIGNED = true>
 __device__ __forceinline__ int probe_first(const Tab &d, int64_t id, int64_t home, uint32_t slot_step, ProbeReq *s_req,
                                            uint8_t *s_code, int32_t fresh_meta, bool *fresh, int *next)
