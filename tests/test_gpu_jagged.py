@@ -199,6 +199,46 @@ def test_group_of_one_table_equals_plain_remap():
     jp.close()
 
 
+@pytest.mark.parametrize("evict,n", [(True, 700), (True, 1_024), (True, 1_025), ("expiry", 5_000), ("lru", 700), ("lru", 5_000),
+                                     (True, 524_289)])
+def test_evicted_list_of_a_group_of_one_table_starts_at_its_offset(evict, n):
+    """A group of one table runs the single-table kernels (one workgroup, one chunk per wavefront, lists, by n); its
+    evicted list starts at evicted_offsets[0] and ends at evicted_offsets[1] there too."""
+    spec = wl.TableSpec(n // 4, 16, 0, evict, 43)
+    jp = JaggedPair([spec])
+    rows_o = wl.embedding_pattern(97, 4, np.float32)
+    rows_g = torch.from_numpy(rows_o).cuda()
+    rng = np.random.Generator(np.random.Philox(key=5))
+    gap, tot = 37, 0
+    for step in range(0, 8, 2):
+        values = rng.integers(0, 8 * spec.num_slots, size=n).astype(np.int64)
+        offsets = np.array([0, n], np.int64)
+        room = 3 if step == 6 else n                           # the last list has room for three
+        out = torch.empty(n, dtype=torch.int64, device="cuda")
+        ev = torch.full((gap + n + 9,), -7, dtype=torch.int64, device="cuda")
+        nev = torch.zeros(1, dtype=torch.int64, device="cuda")
+        stats = torch.zeros(mp.STAT_COUNT, dtype=torch.int64, device="cuda")
+        mp.mpzch_remap_jagged(jp.group, jp.I, jp.M, torch.from_numpy(values).cuda(), torch.from_numpy(offsets).cuda(), step,
+                              out, ev, [gap, gap + room], nev, stats)
+        so, evs, sts = oracle.remap_jagged(jp.o, values, offsets, step)
+        assert np.array_equal(out.cpu().numpy(), so)
+        assert int(nev.item()) == len(evs[0]) and dict(zip(mp.STAT_NAMES, stats.tolist())) == sts[0]
+        listed = min(room, len(evs[0]))
+        got = ev.cpu().numpy()
+        assert (got[:gap] == -7).all() and (got[gap + listed:] == -7).all()
+        if listed == len(evs[0]):
+            assert np.array_equal(np.sort(got[gap: gap + listed]), np.sort(evs[0]))
+        else:
+            assert np.isin(got[gap: gap + listed], evs[0]).all() and len(set(got[gap: gap + listed])) == listed
+        mp.mpzch_reset_rows_jagged(jp.group, ev, [gap, gap + room], nev, [rows_g])
+        oracle.reset_rows(got[gap: gap + listed], rows_o)
+        assert np.array_equal(rows_g.cpu().numpy(), rows_o)
+        tot += len(evs[0])
+    assert tot > 0
+    jp.check_state()
+    jp.close()
+
+
 @pytest.mark.parametrize("kinds", [("lru",) * 4, (True, "lru", False, "expiry", "lru", True)],
                          ids=["all_lru", "mixed_policies"])
 def test_jagged_group_with_every_policy(kinds):
