@@ -76,9 +76,11 @@ int64_t number(PyObject *o)
 }
 int32_t number32(PyObject *o) { return (int32_t)number(o); }
 
-// a handle is a ctypes.c_void_p
-template <typename T>
-T *handle(PyObject *o)
+// A handle: a ctypes.c_void_p (what the create calls return), an address, None, or another pointer of ctypes.  (Not a text,
+// which ctypes would pass as the address of its characters.)
+PyObject *g_c_void_p = nullptr, *g_cast = nullptr;           // ctypes.c_void_p, ctypes.cast
+
+void *value_of(PyObject *o)
 {
     static PyObject *const name = PyUnicode_InternFromString("value");
     PyObject *v = PyObject_GetAttr(o, name);
@@ -86,8 +88,28 @@ T *handle(PyObject *o)
     void *p = v == Py_None ? nullptr : PyLong_AsVoidPtr(v);
     Py_DECREF(v);
     if (!p && PyErr_Occurred()) throw Failed{};
-    return (T *)p;
+    return p;
 }
+void *pointer(PyObject *o)
+{
+    if (o == Py_None) return nullptr;
+    if ((PyObject *)Py_TYPE(o) == g_c_void_p) return value_of(o);
+    if (PyLong_Check(o)) {
+        void *p = PyLong_AsVoidPtr(o);
+        if (!p && PyErr_Occurred()) throw Failed{};
+        return p;
+    }
+    if (!g_cast || PyUnicode_Check(o) || PyBytes_Check(o)) fail(PyExc_TypeError, "a handle is expected");
+    PyObject *v = PyObject_CallFunctionObjArgs(g_cast, o, g_c_void_p, nullptr);
+    if (!v) throw Failed{};
+    struct Release {
+        PyObject *o;
+        ~Release() { Py_DECREF(o); }
+    } release{v};
+    return value_of(v);
+}
+template <typename T>
+T *handle(PyObject *o) { return (T *)pointer(o); }
 
 void *stream() { return (void *)c10::hip::getCurrentHIPStream().stream(); }
 
@@ -310,6 +332,14 @@ PyObject *bind(PyObject *, PyObject *functions)
     }
     MPZCH_CALLS(F)
 #undef F
+    if (!g_cast) {
+        PyObject *ctypes = PyImport_ImportModule("ctypes");
+        if (!ctypes) return nullptr;
+        g_c_void_p = PyObject_GetAttrString(ctypes, "c_void_p");
+        g_cast = g_c_void_p ? PyObject_GetAttrString(ctypes, "cast") : nullptr;
+        Py_DECREF(ctypes);
+        if (!g_cast) return nullptr;
+    }
     Py_RETURN_NONE;
 }
 

@@ -1,0 +1,61 @@
+"""What the binding takes and refuses: the repeated calls are marshalled in native code, and accept what ctypes did."""
+import ctypes
+
+import pytest
+import torch
+
+from paper_2602_17050_amd import binding as mp
+
+pytestmark = pytest.mark.gpu
+INVALID_ARG = 1
+
+
+def dev(a, dtype=torch.int64):
+    return torch.tensor(a, dtype=dtype, device="cuda")
+
+
+def refused(status, fn, *args, **kw):
+    with pytest.raises(mp.MpzchError) as e:
+        fn(*args, **kw)
+    assert e.value.status == status
+
+
+# ---- handles: a ctypes.c_void_p or other pointer, an address, or None (which the library refuses, as for a table that has been closed)
+def test_handles_as_pointers_addresses_and_none():
+    t = mp.MpzchTable(100, 8, mp.EVICT_TTL, 1, 7, max_batch=64)
+    group = mp.mpzch_group_create([t.handle])
+    ids = dev([3, 5, 3])
+    out, found, stats = torch.empty_like(ids), torch.empty(3, dtype=torch.uint8, device="cuda"), torch.zeros(mp.STAT_COUNT, dtype=torch.int64, device="cuda")
+    ev, nev, off = torch.empty_like(ids), torch.zeros(1, dtype=torch.int64, device="cuda"), dev([0, 3])
+    rows = torch.ones((100, 4), device="cuda")
+    gathered = torch.empty((3, 4), device="cuda")
+    count = torch.zeros(1, dtype=torch.int64, device="cuda")
+    calls = {
+        "init_tensors": lambda h, g: mp.mpzch_init_tensors(h, t.identities, t.metadata),
+        "remap": lambda h, g: mp.mpzch_remap(h, t.identities, t.metadata, ids, 1, out, ev, nev, stats),
+        "noalloc": lambda h, g: mp.mpzch_remap_noalloc(h, t.identities, t.metadata, ids, 1, out, ev, nev, stats),
+        "feature_ttl": lambda h, g: mp.mpzch_remap_feature_ttl(h, t.identities, t.metadata, ids, None, 1, out, ev, nev, stats),
+        "reset": lambda h, g: mp.mpzch_remap_reset(h, t.identities, t.metadata, ids, 1, out, ev, nev, stats, rows),
+        "lookup": lambda h, g: mp.mpzch_lookup(h, t.identities, ids, out, found),
+        "lookup_stats": lambda h, g: mp.mpzch_lookup_stats(h, t.identities, ids, out, found, stats),
+        "gather": lambda h, g: mp.mpzch_lookup_gather(h, t.identities, ids, rows, gathered, out, found),
+        "delta": lambda h, g: mp.mpzch_collect_delta(h, t.identities, t.metadata, 1, out, ev, count),
+        "jagged": lambda h, g: mp.mpzch_remap_jagged(g, [t.identities], [t.metadata], ids, off, 1, out, ev, [0, 3], nev, stats),
+        "lookup_jagged": lambda h, g: mp.mpzch_lookup_jagged(g, [t.identities], ids, off, out, found),
+        "reset_jagged": lambda h, g: mp.mpzch_reset_rows_jagged(g, ev, [0, 3], nev, [rows]),
+    }
+    for name, call in calls.items():
+        call(t.handle, group)
+        call(t.handle.value, group.value)
+        call(ctypes.cast(t.handle, ctypes.POINTER(ctypes.c_char)), ctypes.cast(group, ctypes.POINTER(ctypes.c_char)))
+        refused(INVALID_ARG, call, None, None)
+        for other in (1.5, "handle", t):
+            with pytest.raises(Exception):
+                call(other, other)
+    out.fill_(-1)
+    mp.mpzch_lookup(t.handle.value, t.identities, ids, out, found)
+    assert bool(found.all()) and int(out[0]) == int(out[2])
+    mp.mpzch_group_destroy(group)
+    t.close()
+    refused(INVALID_ARG, t.remap, ids, 2)
+    refused(INVALID_ARG, t.lookup, ids)
