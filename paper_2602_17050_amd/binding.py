@@ -222,7 +222,8 @@ def mpzch_reset_rows(slots, num_slots_dev, rows, init_row=None, num_rows: int | 
 
 
 def mpzch_reset_rows_multi(slots, num_slots_dev, tensors, init_rows=None):
-    """tensors: list of 2-D device tensors (weights, optimizer state, ...), reset in one launch."""
+    """tensors: list of 2-D device tensors (weights, optimizer state, ...), reset in one launch; init_rows: one dense row
+    per tensor, on the device or in pinned host memory, or None."""
     status = (_native or _load_native()).reset_rows_multi(slots, num_slots_dev, tensors, init_rows or [None] * len(tensors))
     if status:
         raise MpzchError(status, "mpzch_reset_rows_multi")
@@ -289,7 +290,8 @@ def mpzch_remap_jagged(group, identities, metadata, values, feature_offsets, ste
 
 
 def mpzch_reset_rows_jagged(group, evicted_slots, evicted_offsets, num_evicted, tensors, init_rows=None):
-    """tensors: one 2-D device tensor (or None) per table of the group; evicted_offsets: host list of ints."""
+    """tensors: one 2-D device tensor (or None) per table of the group; evicted_offsets: host list of ints; init_rows: as
+    for mpzch_reset_rows_multi (tables beyond a shorter list are left alone)."""
     status = (_native or _load_native()).reset_rows_jagged(group, evicted_slots, evicted_offsets, num_evicted, tensors,
                                                            init_rows or [None] * len(tensors))
     if status:

@@ -113,8 +113,9 @@ T *handle(PyObject *o) { return (T *)pointer(o); }
 
 void *stream() { return (void *)c10::hip::getCurrentHIPStream().stream(); }
 
-// a 2-D device tensor whose rows are dense (where host memory that the device can reach will do too: pinned_too)
-mpzch_rows_t rows_of(PyObject *o, PyObject *init, bool pinned_too = false)
+// a 2-D device tensor whose rows are dense (where host memory that the device can reach will do too: pinned_too,
+// init_pinned_too)
+mpzch_rows_t rows_of(PyObject *o, PyObject *init, bool pinned_too = false, bool init_pinned_too = false)
 {
     const at::Tensor &t = tensor(o);
     if (t.dim() != 2 || t.stride(1) != 1 || !(t.is_cuda() || pinned_too)) fail(PyExc_AssertionError, "rows: 2-D device tensor with dense rows");
@@ -127,7 +128,7 @@ mpzch_rows_t rows_of(PyObject *o, PyObject *init, bool pinned_too = false)
     r.init_row = nullptr;
     if (init != Py_None) {
         const at::Tensor &i = tensor(init);
-        if (!i.is_cuda() || !i.is_contiguous() || i.numel() * (int64_t)i.element_size() != r.row_bytes)
+        if (!(i.is_cuda() || (init_pinned_too && i.is_pinned())) || !i.is_contiguous() || i.numel() * (int64_t)i.element_size() != r.row_bytes)
             fail(PyExc_AssertionError, "init_row: one dense row on the device");
         r.init_row = i.data_ptr();
     }
@@ -147,6 +148,19 @@ struct Sequence {
     Sequence(const Sequence &) = delete;
     Sequence &operator=(const Sequence &) = delete;
     PyObject *operator[](Py_ssize_t k) const { return PySequence_Fast_GET_ITEM(o, k); }
+};
+
+// Several tensors with the initial row of each.  The tensors beyond a list of initial rows that is shorter have no entry
+// (rows == NULL: the reset of several tensors refuses it, the one of a group leaves that table alone); what a longer
+// list holds beyond the tensors is not looked at.
+struct RowsList {
+    mpzch_rows_t v[MPZCH_MAX_GROUP_TABLES] = {};
+    RowsList(const Sequence &t, const Sequence &init, bool may_be_none)
+    {
+        if (t.n > MPZCH_MAX_GROUP_TABLES) fail(PyExc_ValueError, "more tensors than a group has tables");
+        for (Py_ssize_t k = 0; k < t.n && k < init.n; ++k)
+            if (!(may_be_none && t[k] == Py_None)) v[k] = rows_of(t[k], init[k], false, true);
+    }
 };
 
 // what the group calls take per table
@@ -247,11 +261,9 @@ PyObject *reset_rows(PyObject *const *a)
 PyObject *reset_rows_multi(PyObject *const *a)
 {
     const Sequence t(a[2]), init(a[3]);
-    if (t.n != init.n || t.n > MPZCH_MAX_GROUP_TABLES) fail(PyExc_ValueError, "one initial row per tensor");
-    mpzch_rows_t r[MPZCH_MAX_GROUP_TABLES];
-    for (Py_ssize_t k = 0; k < t.n; ++k) r[k] = rows_of(t[k], init[k]);
+    const RowsList r(t, init, false);
     return call(g_call.mpzch_reset_rows_multi, (const int64_t *)i64(a[0]), (const int64_t *)i64(a[1]), count(a[0]),
-                (const mpzch_rows_t *)r, (int32_t)t.n, stream());
+                (const mpzch_rows_t *)r.v, (int32_t)t.n, stream());
 }
 PyObject *collect_delta(PyObject *const *a)
 {
@@ -295,12 +307,10 @@ PyObject *lookup_jagged(PyObject *const *a)
 PyObject *reset_rows_jagged(PyObject *const *a)
 {
     const Sequence t(a[4]), init(a[5]);
-    if (t.n != init.n || t.n > MPZCH_MAX_GROUP_TABLES) fail(PyExc_ValueError, "one initial row per tensor");
-    mpzch_rows_t r[MPZCH_MAX_GROUP_TABLES];
-    for (Py_ssize_t k = 0; k < t.n; ++k) r[k] = t[k] == Py_None ? mpzch_rows_t{} : rows_of(t[k], init[k]);
+    const RowsList r(t, init, true);
     const Offsets evicted(a[2], t.n);
     return call(g_call.mpzch_reset_rows_jagged, handle<mpzch_group_t>(a[0]), (const int64_t *)i64(a[1]), (const int64_t *)evicted.v,
-                (const int64_t *)i64(a[3]), (const mpzch_rows_t *)r, stream());
+                (const int64_t *)i64(a[3]), (const mpzch_rows_t *)r.v, stream());
 }
 
 template <PyObject *(*FN)(PyObject *const *), int N>

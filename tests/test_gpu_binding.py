@@ -59,3 +59,36 @@ def test_handles_as_pointers_addresses_and_none():
     t.close()
     refused(INVALID_ARG, t.remap, ids, 2)
     refused(INVALID_ARG, t.lookup, ids)
+
+
+# ---- initial rows of several tensors: on the device or in pinned host memory; a list may be shorter or longer than the
+# tensors (several tensors of one table: refused when shorter; tables of a group: the rest is left alone)
+def test_initial_rows_of_several_tensors():
+    slots, count = dev([2, 7, 9, 4]), dev([3])
+    rows = lambda: torch.arange(80, dtype=torch.float32, device="cuda").view(10, 8).clone()
+    pinned = torch.full((8,), 2.5, pin_memory=True)
+    init = torch.full((8,), -1.5, device="cuda")
+    want = lambda v: torch.stack([torch.full((8,), v) if k in (2, 7, 9) else torch.arange(8 * k, 8 * k + 8).float() for k in range(10)])
+    a, b = rows(), rows()
+    mp.mpzch_reset_rows_multi(slots, count, [a, b], [pinned, init])
+    assert torch.equal(a.cpu(), want(2.5)) and torch.equal(b.cpu(), want(-1.5))
+    a, b = rows(), rows()
+    mp.mpzch_reset_rows_multi(slots, count, [a, b], [None, init, init])
+    assert torch.equal(a.cpu(), want(0.0)) and torch.equal(b.cpu(), want(-1.5))
+    refused(INVALID_ARG, mp.mpzch_reset_rows_multi, slots, count, [a, b], [init])
+    # a row of another size is refused
+    for other in (init[:7], torch.zeros(16, device="cuda"), torch.zeros((8, 2), device="cuda")[:, 0]):
+        with pytest.raises(AssertionError):
+            mp.mpzch_reset_rows_multi(slots, count, [a], [other])
+
+    tables = [mp.MpzchTable(10, 4, mp.EVICT_TTL, 1, 7) for _ in range(2)]
+    group = mp.mpzch_group_create([t.handle for t in tables])
+    jagged, counts, at = dev([2, 7, 9, 9, 7, 2]), dev([3, 3]), [0, 3, 6]
+    for inits, first, second in [([pinned, init], 2.5, -1.5), ([init], -1.5, None), ([None, pinned, init], 0.0, 2.5)]:
+        a, b = rows(), rows()
+        mp.mpzch_reset_rows_jagged(group, jagged, at, counts, [a, b], inits)
+        assert torch.equal(a.cpu(), want(first))
+        assert torch.equal(b.cpu(), rows().cpu() if second is None else want(second))
+    mp.mpzch_group_destroy(group)
+    for t in tables:
+        t.close()
