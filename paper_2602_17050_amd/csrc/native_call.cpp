@@ -60,19 +60,22 @@ int32_t *i32(PyObject *o) { return address<int32_t>(o, at::kInt); }
 uint8_t *u8(PyObject *o) { return address<uint8_t>(o, at::kByte); }
 int64_t count(PyObject *o) { return o == Py_None ? 0 : tensor(o).numel(); }
 
+// whole numbers as a ctypes parameter takes them (numpy integers and the like too; the low bits of what does not fit)
 int64_t number(PyObject *o)
 {
-    const long long v = PyLong_AsLongLong(o);
-    if (v == -1 && PyErr_Occurred()) {
-        PyErr_Clear();
-        PyObject *i = PyNumber_Index(o);             // numpy integers and the like
-        if (!i) throw Failed{};
-        const long long w = PyLong_AsLongLong(i);
-        Py_DECREF(i);
-        if (w == -1 && PyErr_Occurred()) throw Failed{};
-        return w;
-    }
-    return v;
+    const unsigned long long v = PyLong_AsUnsignedLongLongMask(o);
+    if (v == ~0ull && PyErr_Occurred()) throw Failed{};
+    return (int64_t)v;
+}
+// ... and as int() makes them
+int64_t number_of(PyObject *o)
+{
+    if (PyLong_CheckExact(o)) return number(o);
+    PyObject *i = PyNumber_Long(o);
+    if (!i) throw Failed{};
+    const unsigned long long v = PyLong_AsUnsignedLongLongMask(i);
+    Py_DECREF(i);
+    return (int64_t)v;
 }
 int32_t number32(PyObject *o) { return (int32_t)number(o); }
 
@@ -179,13 +182,14 @@ Py_ssize_t length(PyObject *list)
     if (n < 0) throw Failed{};
     return n;
 }
+// n + 1 of them; what a shorter list leaves out is zero
 struct Offsets {
-    int64_t v[MPZCH_MAX_GROUP_TABLES + 1];
+    int64_t v[MPZCH_MAX_GROUP_TABLES + 1] = {};
     Offsets(PyObject *list, Py_ssize_t n)
     {
         const Sequence s(list);
-        if (s.n < n + 1 || n > MPZCH_MAX_GROUP_TABLES) fail(PyExc_ValueError, "one offset per table of the group and one more");
-        for (Py_ssize_t k = 0; k <= n; ++k) v[k] = number(s[k]);
+        if (s.n > n + 1 || n > MPZCH_MAX_GROUP_TABLES) fail(PyExc_IndexError, "one offset per table of the group and one more");
+        for (Py_ssize_t k = 0; k < s.n; ++k) v[k] = number_of(s[k]);
     }
 };
 

@@ -1,6 +1,7 @@
 """What the binding takes and refuses: the repeated calls are marshalled in native code, and accept what ctypes did."""
 import ctypes
 
+import numpy as np
 import pytest
 import torch
 
@@ -89,6 +90,50 @@ def test_initial_rows_of_several_tensors():
         mp.mpzch_reset_rows_jagged(group, jagged, at, counts, [a, b], inits)
         assert torch.equal(a.cpu(), want(first))
         assert torch.equal(b.cpu(), rows().cpu() if second is None else want(second))
+    mp.mpzch_group_destroy(group)
+    for t in tables:
+        t.close()
+
+
+# ---- whole numbers: steps as ctypes takes them, offsets as int() does
+def test_steps_and_offsets():
+    tables = [mp.MpzchTable(64, 8, mp.EVICT_TTL, 0, 7 + f) for f in range(2)]
+    group = mp.mpzch_group_create([t.handle for t in tables])
+    I, M = [t.identities for t in tables], [t.metadata for t in tables]
+    ids, off = torch.arange(200, dtype=torch.int64, device="cuda"), dev([0, 120, 200])
+    out, nev = torch.empty_like(ids), torch.zeros(2, dtype=torch.int64, device="cuda")
+    rows = [torch.ones((64, 4), device="cuda") for _ in tables]
+    step = 0
+    for at in ([0, 120, 200], (0, 120, 200), [0.0, 120.0, 200.0], np.array([0, 120, 200], np.int32), np.array([0.0, 120.0, 200.0]),
+               torch.tensor([0, 120, 200]), torch.tensor([0.0, 120.0, 200.0]), off, iter([0, 120, 200])):
+        step += 2
+        ids += 200
+        again = [0, 120, 200] if hasattr(at, "__next__") else at
+        ev = torch.full((200,), -7, dtype=torch.int64, device="cuda")
+        mp.mpzch_remap_jagged(group, I, M, ids, off, np.int64(step), out, ev, at, nev)
+        n = nev.tolist()
+        assert step == 2 or min(n) > 0
+        assert bool((ev[: n[0]] >= 0).all()) and bool((ev[n[0]: 120] == -7).all())
+        assert bool((ev[120: 120 + n[1]] >= 0).all()) and bool((ev[120 + n[1]:] == -7).all())
+        for r in rows:
+            r.fill_(1.0)
+        mp.mpzch_reset_rows_jagged(group, ev, again, nev, rows)
+        for f, lo in enumerate((0, 120)):
+            want = torch.ones(64, device="cuda")
+            want[ev[lo: lo + n[f]]] = 0.0
+            assert torch.equal(rows[f], want[:, None].expand(64, 4))
+    # one too many is refused; what is left out counts as zero, which the library refuses unless all are
+    for fn in (lambda at: mp.mpzch_remap_jagged(group, I, M, ids, off, step, out, ev, at, nev),
+               lambda at: mp.mpzch_reset_rows_jagged(group, ev, at, nev, rows)):
+        with pytest.raises((ValueError, IndexError)):
+            fn([0, 120, 200, 200])
+        refused(INVALID_ARG, fn, [0, 120])
+        fn([0, 0])
+        with pytest.raises(TypeError):
+            fn([0, None, 200])
+    for bad in (1.0, "1", None):
+        with pytest.raises(Exception):
+            mp.mpzch_remap(tables[0].handle, I[0], M[0], ids, bad, out, ev, nev)
     mp.mpzch_group_destroy(group)
     for t in tables:
         t.close()
