@@ -58,7 +58,9 @@ T *address(PyObject *o, at::ScalarType type)
 int64_t *i64(PyObject *o) { return address<int64_t>(o, at::kLong); }
 int32_t *i32(PyObject *o) { return address<int32_t>(o, at::kInt); }
 uint8_t *u8(PyObject *o) { return address<uint8_t>(o, at::kByte); }
-int64_t count(PyObject *o) { return o == Py_None ? 0 : tensor(o).numel(); }
+// entries of a tensor that the call cannot do without, and of one that may be left out
+int64_t count(PyObject *o) { return tensor(o).numel(); }
+int64_t count_if_given(PyObject *o) { return o == Py_None ? 0 : tensor(o).numel(); }
 
 // whole numbers as a ctypes parameter takes them (numpy integers and the like too; the low bits of what does not fit)
 int64_t number(PyObject *o)
@@ -213,18 +215,18 @@ PyObject *init_tensors(PyObject *const *a)
 PyObject *remap(PyObject *const *a)
 {
     return call(g_call.mpzch_remap, handle<mpzch_table_t>(a[0]), i64(a[1]), i32(a[2]), (const int64_t *)i64(a[3]), count(a[3]),
-                number32(a[4]), i64(a[5]), i64(a[6]), count(a[6]), i64(a[7]), i64(a[8]), stream());
+                number32(a[4]), i64(a[5]), i64(a[6]), count_if_given(a[6]), i64(a[7]), i64(a[8]), stream());
 }
 PyObject *remap_noalloc(PyObject *const *a)
 {
     return call(g_call.mpzch_remap_noalloc, handle<const mpzch_table_t>(a[0]), i64(a[1]), i32(a[2]), (const int64_t *)i64(a[3]),
-                count(a[3]), number32(a[4]), i64(a[5]), i64(a[6]), count(a[6]), i64(a[7]), i64(a[8]), stream());
+                count(a[3]), number32(a[4]), i64(a[5]), i64(a[6]), count_if_given(a[6]), i64(a[7]), i64(a[8]), stream());
 }
 PyObject *remap_feature_ttl(PyObject *const *a)
 {
     if (a[4] != Py_None && count(a[4]) != count(a[3])) fail(PyExc_AssertionError, "one ttl per id");
     return call(g_call.mpzch_remap_feature_ttl, handle<mpzch_table_t>(a[0]), i64(a[1]), i32(a[2]), (const int64_t *)i64(a[3]),
-                (const int32_t *)i32(a[4]), count(a[3]), number32(a[5]), i64(a[6]), i64(a[7]), count(a[7]), i64(a[8]), i64(a[9]),
+                (const int32_t *)i32(a[4]), count(a[3]), number32(a[5]), i64(a[6]), i64(a[7]), count_if_given(a[7]), i64(a[8]), i64(a[9]),
                 stream());
 }
 PyObject *remap_reset(PyObject *const *a)
@@ -232,7 +234,7 @@ PyObject *remap_reset(PyObject *const *a)
     const mpzch_rows_t r = rows_of(a[9], a[10]);
     const int64_t num_rows = a[11] == Py_None ? r.num_rows : number(a[11]);
     return call(g_call.mpzch_remap_reset, handle<mpzch_table_t>(a[0]), i64(a[1]), i32(a[2]), (const int64_t *)i64(a[3]), count(a[3]),
-                number32(a[4]), i64(a[5]), i64(a[6]), count(a[6]), i64(a[7]), i64(a[8]), r.rows, num_rows, r.row_bytes,
+                number32(a[4]), i64(a[5]), i64(a[6]), count_if_given(a[6]), i64(a[7]), i64(a[8]), r.rows, num_rows, r.row_bytes,
                 r.row_stride_bytes, r.init_row, stream());
 }
 PyObject *lookup(PyObject *const *a)

@@ -137,3 +137,35 @@ def test_steps_and_offsets():
     mp.mpzch_group_destroy(group)
     for t in tables:
         t.close()
+
+
+# ---- a tensor that a call cannot do without is not an empty batch
+def test_missing_batches_are_refused():
+    t = mp.MpzchTable(64, 8, mp.EVICT_TTL, 0, 7, max_batch=64)
+    group = mp.mpzch_group_create([t.handle])
+    I, M = t.identities, t.metadata
+    ids, rows = dev([1, 2, 3]), torch.ones((64, 4), device="cuda")
+    out, ev, nev, off, found = torch.empty_like(ids), torch.empty_like(ids), dev([0]), dev([0, 3]), torch.zeros(3, dtype=torch.uint8, device="cuda")
+    stats = torch.zeros(mp.STAT_COUNT, dtype=torch.int64, device="cuda")
+    for call in (lambda: mp.mpzch_remap(t.handle, I, M, None, 1, out, ev, nev),
+                 lambda: mp.mpzch_remap_noalloc(t.handle, I, M, None, 1, out, ev, nev),
+                 lambda: mp.mpzch_remap_feature_ttl(t.handle, I, M, None, None, 1, out, ev, nev),
+                 lambda: mp.mpzch_remap_reset(t.handle, I, M, None, 1, out, ev, nev, stats, rows),
+                 lambda: mp.mpzch_lookup(t.handle, I, None, out, found),
+                 lambda: mp.mpzch_lookup_stats(t.handle, I, None, out, found, stats),
+                 lambda: mp.mpzch_lookup_gather(t.handle, I, None, rows, torch.empty((0, 4), device="cuda")),
+                 lambda: mp.mpzch_remap_jagged(group, [I], [M], None, off, 1, out, ev, [0, 3], nev),
+                 lambda: mp.mpzch_lookup_jagged(group, [I], None, off, out, found),
+                 lambda: mp.mpzch_reset_rows(None, nev, rows),
+                 lambda: mp.mpzch_reset_rows_multi(None, nev, [rows]),
+                 lambda: mp.mpzch_collect_delta(t.handle, I, M, 0, None, None, nev),
+                 lambda: mp.mpzch_gather_rows(None, nev, rows, torch.empty((0, 4), device="cuda")),
+                 lambda: mp.mpzch_apply_delta(I, None, None, nev),
+                 lambda: mp.mpzch_apply_delta(None, out, ids, nev)):
+        with pytest.raises((AttributeError, TypeError)):
+            call()
+    # the list of evicted slots and the retention times may be left out
+    t.remap(ids, 1)
+    mp.mpzch_remap(t.handle, I, M, ids, 2, out, None, nev)
+    mp.mpzch_group_destroy(group)
+    t.close()
