@@ -168,9 +168,10 @@ struct RowsList {
     }
 };
 
-// what the group calls take per table
+// what the group calls take per table.  The library reads as many as the group has tables, which may be more than the list
+// has: those are null, and it refuses them.
 struct Tables {
-    void *p[MPZCH_MAX_GROUP_TABLES];
+    void *p[MPZCH_MAX_GROUP_TABLES] = {};
     Tables(PyObject *list, Py_ssize_t n)
     {
         const Sequence s(list);

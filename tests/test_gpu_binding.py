@@ -169,3 +169,21 @@ def test_missing_batches_are_refused():
     mp.mpzch_remap(t.handle, I, M, ids, 2, out, None, nev)
     mp.mpzch_group_destroy(group)
     t.close()
+
+
+# ---- lists with fewer entries than the group has tables: what is missing is a null pointer, which the library refuses
+def test_lists_shorter_than_the_group():
+    tables = [mp.MpzchTable(64, 8, mp.EVICT_TTL, 0, 7 + f) for f in range(3)]
+    group = mp.mpzch_group_create([t.handle for t in tables])
+    I, M = [t.identities for t in tables], [t.metadata for t in tables]
+    ids, off, nev = dev([1, 2, 3]), dev([0, 1, 2, 3]), dev([1, 1, 1])
+    out, ev, rows = torch.full_like(ids, -7), dev([5, 6, 7]), [torch.ones((64, 4), device="cuda") for _ in tables]
+    for n in (0, 1, 2):
+        refused(INVALID_ARG, mp.mpzch_remap_jagged, group, I[:n], M[:n], ids, off, 1, out, ev, [0, 1, 2, 3][: n + 1], nev)
+        refused(INVALID_ARG, mp.mpzch_lookup_jagged, group, I[:n], ids, off, out)
+    refused(INVALID_ARG, mp.mpzch_reset_rows_jagged, group, ev, [0, 1, 2], nev, rows[:2])
+    mp.mpzch_reset_rows_jagged(group, ev, [0, 0], nev, rows[:1])
+    assert all(bool((r == 1.0).all()) for r in rows) and bool((out == -7).all())
+    mp.mpzch_group_destroy(group)
+    for t in tables:
+        t.close()
