@@ -7,11 +7,6 @@ import sys
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 SRC = os.path.join(HERE, "csrc", "mpzch.hip")
-DEPS = [SRC, os.path.join(HERE, "csrc", "mpzch_kernels.hpp"),
-        os.path.join(HERE, "csrc", "mpzch_chunk_kernels.hpp"),
-        os.path.join(HERE, "csrc", "mpzch_block_kernel.hpp"),
-        os.path.join(HERE, "csrc", "mpzch_row_kernels.hpp"),
-        os.path.join(os.path.dirname(HERE), "include", "mpzch.h")]
 LIB = os.path.join(HERE, "libmpzch.so")
 NATIVE_SRC = os.path.join(HERE, "csrc", "native_call.cpp")
 NATIVE = os.path.join(HERE, "_native.so")

@@ -952,7 +952,6 @@ mpzch_status_t mpzch_reset_rows_multi(const int64_t *slots, const int64_t *num_s
         total += ds.t[i].chunks;
     }
     if (total > 0x7FFFFFFF) return MPZCH_ERR_INVALID_ARG;
-    ds.count = num_tensors;
     ds.total_chunks = (int32_t)total;
     if (slots_cap == 0) return MPZCH_OK;
     if (!slots) return MPZCH_ERR_INVALID_ARG;

@@ -288,14 +288,6 @@ __device__ __forceinline__ void store_meta(const Tab &d, int64_t s, int32_t valu
     else *meta_at(d, s) = value;
 }
 
-// TTL test of Sec. 3.4 on metadata m of a slot that holds an id
-__device__ __forceinline__ bool is_expired(int32_t evict, int32_t ttl, int32_t step, int32_t m)
-{
-    if (evict == 1) return (int64_t)step - (int64_t)m > (int64_t)ttl;
-    if (evict == 3) return m < step;
-    return false;
-}
-
 // ------------------------------------------------------------------ scratch set
 constexpr uint64_t kSetSeed = 0x2545F4914F6CDD1Dull;
 constexpr uint32_t kSetEmpty = 0xFFFFFFFFu;
@@ -1093,12 +1085,6 @@ __device__ __forceinline__ bool segment_table(const Params &p, int64_t lane_offs
 }
 
 // ------------------------------------------------------------------ allocation
-// TTL test of Sec. 3.4 on a slot that holds an id
-__device__ __forceinline__ bool expired(const Tab &d, int32_t step, int64_t s)
-{
-    return is_expired(d.evict, d.ttl, step, *meta_at(d, s));
-}
-
 // One workgroup = one wavefront, every lane carries one claimant.  In one stage the next block of 8 slots of every
 // claimant's window (identities and metadata) is read cooperatively -- 8 lanes read the slots of one block with one
 // coalesced access, all accesses in flight together -- and what may be claimed goes through LDS to the claimant's own
@@ -1128,7 +1114,7 @@ struct alignas(16) ClaimReq {
     uint32_t unused;
 };
 
-// expired <=> metadata < bound
+// The TTL test of Sec. 3.4 on a slot that holds an id: expired <=> metadata < bound
 __device__ __forceinline__ int32_t expiry_bound(const Tab &d, int32_t step)
 {
     if (d.evict == 1) return step - d.ttl;

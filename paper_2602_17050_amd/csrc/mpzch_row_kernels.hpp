@@ -101,8 +101,7 @@ struct RowsDesc {
 };
 constexpr int kMaxResetTensors = 4;
 struct RowsDescs {
-    RowsDesc t[kMaxResetTensors];
-    int32_t count;
+    RowsDesc t[kMaxResetTensors];        // (0 pieces: none)
     int32_t total_chunks;
 };
 
