@@ -152,17 +152,25 @@ def test_config3_100m_slots_lookup(layout):
     g.close()
 
 
-def test_config5_26_tables_full_jagged_batch():
+@pytest.mark.parametrize("layout", ["separate", "records"])
+def test_config5_26_tables_full_jagged_batch(layout):
     """26 tables, slot counts log-uniform 1 K .. 1 B scaled to <= 1 B in total, 65 536 samples,
-    pooling 1..50: one mpzch_remap_jagged call per step, two steps."""
+    pooling 1..50: one mpzch_remap_jagged call per step, two steps.  Every table as two tensors, or every table as
+    records (a group of records has kernels of its own)."""
     spec = wl.c5_spec()
     total = sum(t.num_slots for t in spec.tables)
     say("c5 tables:", [t.num_slots for t in spec.tables], "total", total)
     assert total <= 1_000_000_000 + 26_000
-    handles = [mp.mpzch_create(t.num_slots, t.max_probe, (mp.EVICT_TTL, t.ttl), t.hash_seed) for t in spec.tables]
+    records = layout == "records"
+    handles = [mp.mpzch_create_with_layout(t.num_slots, t.max_probe, (mp.EVICT_TTL, t.ttl), t.hash_seed,
+                                           mp.LAYOUT_RECORDS if records else mp.LAYOUT_SEPARATE) for t in spec.tables]
     group = mp.mpzch_group_create(handles)
-    I = [torch.empty(t.num_slots, dtype=torch.int64, device="cuda") for t in spec.tables]
-    M = [torch.empty(t.num_slots, dtype=torch.int32, device="cuda") for t in spec.tables]
+    if records:
+        views = [mp.records_views(torch.empty(2 * t.num_slots, dtype=torch.int64, device="cuda"), t.num_slots) for t in spec.tables]
+        I, M = [v[0] for v in views], [v[1] for v in views]
+    else:
+        I = [torch.empty(t.num_slots, dtype=torch.int64, device="cuda") for t in spec.tables]
+        M = [torch.empty(t.num_slots, dtype=torch.int32, device="cuda") for t in spec.tables]
     for h, i, m in zip(handles, I, M):
         mp.mpzch_init_tensors(h, i, m)
     os_ = [oracle.Table(t.num_slots, t.max_probe, oracle.EVICT_TTL, t.ttl, t.hash_seed) for t in spec.tables]

@@ -48,6 +48,33 @@ def test_groups_of_records_refreshed_once(records):
     jp.close()
 
 
+# ---- large batches of a group: whole sixteenths per die from 16 chunks per wavefront on, twice as many wavefronts from
+# 2^24 values on
+@pytest.mark.parametrize("chunks,more,layout", [(15, 0, "records"), (15, 1, "records"), (15, 1, "separate"), (32, -1, "records"),
+                                                (32, 0, "records"), (32, 0, "separate")])
+def test_groups_around_the_lines_of_large_batches(chunks, more, layout):
+    from test_gpu_jagged import JaggedPair
+    rng = rng_for(911)
+    n = chunks * torch.cuda.get_device_properties(0).multi_processor_count * 8 * 256 + more
+    specs = [wl.TableSpec(1_003, 8, 1, True, 61), wl.TableSpec(50_000, 16, 1, True, 62), wl.TableSpec(7, 3, 1, True, 63),
+             wl.TableSpec(2_000_000, 16, 1, True, 64), wl.TableSpec(300_007, 24, 0, False, 65), wl.TableSpec(1_000_000, 16, 1, "expiry", 66)]
+    jp = JaggedPair(specs, range(len(specs)) if layout == "records" else ())
+    # six features of very different length, one of them empty; what the first, small batch brings in has expired later
+    share = np.array([0.21, 0.003, 0.0, 0.4, 0.137, 0.25])
+    tot = 0
+    for step, size in ((0, 1_000_003), (3, n)):
+        counts = (share * size).astype(np.int64)
+        counts[-1] = size - counts[:-1].sum()
+        vals = np.concatenate([wl.zipf_ids(rng, int(c), 1.05, 2 * s.num_slots) + step for c, s in zip(counts, specs)])
+        offsets = np.concatenate([[0], np.cumsum(counts)]).astype(np.int64)
+        tot += sum(s["evictions"] for s in jp.step(vals, offsets, step))
+    assert tot > 1_000
+    jp.check_state()
+    if chunks == 32:
+        jp.lookup(vals, offsets)
+    jp.close()
+
+
 # ---- ids with a chosen home slot: the hash is a bijection, so it can be run backwards
 def ids_at(homes, num_slots, seed, rng):
     """One valid id per entry of `homes` (int64), hashing to that home slot."""
