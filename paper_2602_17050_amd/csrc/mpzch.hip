@@ -1178,8 +1178,11 @@ mpzch_status_t mpzch_remap_jagged_feature_ttl(mpzch_group_t *g, int64_t *const *
     p.out_evicted = out_evicted_slots;
     p.out_num_evicted = out_num_evicted;
     p.out_stats = out_stats;
-    // a group of one table still goes through the descriptor path
-    if (T == 1) p.num_tables = 1;
+    // a group of one table runs the single-table kernels, whose list of evicted slots begins at out_evicted
+    if (T == 1 && p.t0.ev_cap > 0) {
+        p.out_evicted = out_evicted_slots + p.t0.ev_begin;
+        p.t0.ev_begin = 0;
+    }
     return run_remap(g->sc, g->tm, p, max_p_lru, s);
 }
 

@@ -137,7 +137,7 @@ __global__ __launch_bounds__(kOneBlock) void k_remap_block(Params p)
     base = (uint32_t)__builtin_amdgcn_readfirstlane((int)base);
     if (outcome == 2u) {
         const uint32_t at = base + (uint32_t)__popcll(em & ((1ull << lane) - 1ull));
-        if ((int64_t)at < p.t0.ev_cap) p.out_evicted[p.t0.ev_begin + at] = claimed;
+        if ((int64_t)at < p.t0.ev_cap) p.out_evicted[at] = claimed;
         if (p.r_rows) s.row[at] = claimed >= p.g_num_rows ? claimed % p.g_num_rows : claimed;
     }
     // every claim stands

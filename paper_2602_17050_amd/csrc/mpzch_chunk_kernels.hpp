@@ -485,8 +485,7 @@ __global__ __launch_bounds__(kBlock, 8) void k_finalize_chunk(Params p)
         if ((int)threadIdx.x < evicted) {
             const int64_t s = p.evicted[(int64_t)blockIdx.x * kBlock + threadIdx.x];
             const int64_t at = (int64_t)base + threadIdx.x;
-            // (a group of one table comes here too: its list need not begin the tensor)
-            if (at < p.t0.ev_cap) p.out_evicted[p.t0.ev_begin + at] = s;
+            if (at < p.t0.ev_cap) p.out_evicted[at] = s;
             if (p.r_rows) s_row[threadIdx.x] = s >= p.g_num_rows ? s % p.g_num_rows : s;
         }
         if (p.r_rows) {
