@@ -703,12 +703,15 @@ __device__ __forceinline__ void discover_body(const Params &p)
     const int lane = lane_id();
     const int w = threadIdx.x / kWave;
     int block = blockIdx.x;
-    if constexpr (MULTI) {
+    if constexpr (MULTI && TRAIN) {
         // Which workgroup takes which part of the batch.  The dies take workgroups in turn; here each gets whole
         // sixteenths of the batch, so that the popular ids of a feature are in the L2 of one or two dies instead of all
         // eight (41 M values over 26 tables: lines read 23.1 M -> 16.3 M, 877 -> 848 us; eighths 855, for some dies then
-        // have the large tables, 32nds 852, 128ths 906).  With few values per part it is uneven and nothing else: 4 M
-        // values 99 -> 100 us; so from 16 chunks per wavefront on.
+        // have the large tables, 32nds 852, 128ths 906).  Whole calls, dealt in turn against sixteenths, us: records 8.1 M
+        // values 268 / 252, 16.2 M 490 / 463, 28.6 M 772 / 727, 41.6 M 1 077 / 1 030; two tensors 332 / 323, 576 / 554,
+        // 992 / 937, 1 603 / 1 513.  The line at 16 chunks per wavefront is a cautious one: 4.1 M values 171 / 164 and
+        // 186 / 183.  Not for lookups, which do not write the lines they share: 12.2 M values 152 / 159, 16.2 M 201 / 210,
+        // 41.6 M 495 / 494.
         constexpr int kDies = 8, kParts = 16;
         if (p.seg_chunks >= 16 && gridDim.x % kParts == 0) {
             const int per = (int)gridDim.x / kParts, j = block / kDies;
