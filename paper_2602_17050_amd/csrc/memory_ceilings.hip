@@ -31,6 +31,58 @@ __global__ void k_copy(const uint4 *a, uint4 *b, uint64_t n)
     for (uint64_t i = blockIdx.x * (uint64_t)blockDim.x + threadIdx.x; i < n; i += (uint64_t)gridDim.x * blockDim.x) b[i] = a[i];
 }
 
+// The same with four 16-byte accesses under way per lane, past the caches; STORE = false: the array is only read.
+typedef unsigned v4u __attribute__((ext_vector_type(4)));
+template <bool STORE>
+__global__ void k_stream(const v4u *a, v4u *b, uint64_t n, unsigned *sink)
+{
+    unsigned acc = 0;
+    const uint64_t threads = (uint64_t)gridDim.x * blockDim.x;
+    for (uint64_t i = blockIdx.x * (uint64_t)blockDim.x + threadIdx.x; i < n; i += 4 * threads) {
+        v4u v[4];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) v[u] = __builtin_nontemporal_load(a + (i + u * threads < n ? i + u * threads : i));
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            if (STORE) {
+                if (i + u * threads < n) __builtin_nontemporal_store(v[u], b + i + u * threads);
+            } else {
+                acc += v[u].x ^ v[u].y ^ v[u].z ^ v[u].w;
+            }
+        }
+    }
+    if (!STORE && acc == 0x1234567) sink[0] = acc;
+}
+
+// As a probe pass reads: 8 lanes read one random aligned line, 16 bytes each, and every lane has the reads of eight lines
+// under way.  WHERE: nothing else (0), then a 4-byte store into the same line (1) or into a second array (2).
+template <int WHERE>
+__global__ void k_line8(v4u *t, int *m, uint64_t lines, uint64_t ops, unsigned *sink)
+{
+    unsigned acc = 0;
+    const uint64_t tid = blockIdx.x * (uint64_t)blockDim.x + threadIdx.x;
+    const uint64_t groups = ((uint64_t)gridDim.x * blockDim.x) >> 3;
+    const int r = tid & 7;
+    for (uint64_t i = tid >> 3; i < ops; i += groups * 8) {
+        v4u v[8];
+        uint64_t line[8];
+#pragma unroll
+        for (int u = 0; u < 8; ++u) {
+            line[u] = __umul64hi(mix64(i + u * groups), lines);
+            v[u] = t[line[u] * 8 + r];
+        }
+#pragma unroll
+        for (int u = 0; u < 8; ++u) {
+            acc += v[u].x;
+            if (WHERE != 0 && r == 7 && i + u * groups < ops) {
+                if (WHERE == 1) reinterpret_cast<int *>(t)[line[u] * 32 + 31] = (int)v[u].x | 7;
+                else m[line[u] * 16 + 15] = (int)v[u].x | 7;
+            }
+        }
+    }
+    if (acc == 0x1234567) sink[0] = acc;
+}
+
 // one 8-byte load per thread at a uniformly random slot
 __global__ void k_gather8(const long long *t, uint64_t n, uint64_t ops, long long *sink)
 {
@@ -245,12 +297,24 @@ int main(int argc, char **argv)
     TIME((k_copy<<<8192, 256>>>((const uint4 *)t, (uint4 *)(t + (n / 2)), cn)));
     std::printf("streaming copy moves %.3f GiB each way\n", copy_bytes / 1073741824.0);
     report("streaming copy (read + written)", (double)cn, 32.0);
+    TIME((k_stream<true><<<2048, 256>>>((const v4u *)t, (v4u *)(t + (n / 2)), n / 4, (unsigned *)c + 16)));
+    report("half of the array copied, 4 x 16 bytes under way per lane", (double)(n / 4), 32.0);
+    TIME((k_stream<false><<<2048, 256>>>((const v4u *)t, nullptr, n / 2, (unsigned *)c + 16)));
+    report("the whole array read, 4 x 16 bytes under way per lane", (double)(n / 2), 16.0);
+    TIME(CK(hipMemcpyAsync(t + (n / 2), t, n / 2 * 8, hipMemcpyDeviceToDevice, nullptr)));
+    report("half of the array copied by the runtime", (double)(n / 4), 32.0);
     TIME((k_gather8<<<8192, 256>>>(t, n, ops, (long long *)c + 8)));
     report("random 8-byte loads (one per lane)", (double)ops, 8.0);
     TIME((k_line<true><<<8192, 256>>>(t, n, ops, (long long *)c + 8)));
     report("random aligned 128-byte lines (16 lanes each)", (double)ops, 128.0);
     TIME((k_line<false><<<8192, 256>>>(t, n, ops, (long long *)c + 8)));
     report("random unaligned 128-byte windows (16 lanes each)", (double)ops, 128.0);
+    TIME((k_line8<0><<<2048, 256>>>((v4u *)t, m, n / 16, ops, (unsigned *)c + 16)));
+    report("eight 128-byte lines under way (8 lanes each)", (double)ops, 128.0);
+    TIME((k_line8<1><<<2048, 256>>>((v4u *)t, m, n / 16, ops, (unsigned *)c + 16)));
+    report("... then a 4-byte store into the same line", (double)ops, 132.0);
+    TIME((k_line8<2><<<2048, 256>>>((v4u *)t, m, n / 16, ops, (unsigned *)c + 16)));
+    report("... then a 4-byte store into a second array", (double)ops, 132.0);
     for (uint64_t buckets : {2048ull, 65536ull, 2097152ull}) {
         char name[96];
         TIME((k_line_bucketed<<<8192, 256>>>(t, n, ops, buckets, (long long *)c + 8)));
