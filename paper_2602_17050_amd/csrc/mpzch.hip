@@ -102,8 +102,10 @@ struct Timing {
 // ---- device scratch -----------------------------------------------------------------------
 // Grid caps in workgroups per compute unit.  8 is the measured best for Pass 1 (4 M positions: 197 us; 4 and 16 per unit
 // 222 and 210) and for the kernels that walk the miss lists.  From 16 M positions on, where a wavefront has 32 chunks
-// and more, twice as many even the ends out (41 M values over 26 tables, Pass 1 743 -> 721, the other kernels 288 -> 278
-// us).  Scratch is sized for up to kDiscoverBlocksPerCuMax.
+// and more, twice as many even the ends out: whole calls over 26 tables, 8 / 16 per unit, us: records 20.8 M values
+// 614 / 618, 28.6 M 727 / 727, 41.6 M 1 030 / 1 007; two tensors 763 / 751, 937 / 924, 1 513 / 1 466; below the line it
+// costs (12.2 M values 354 / 373 and 430 / 440).  One table, 8 to 40 M positions, either layout: no difference beyond
+// the runs' own.  Scratch is sized for up to kDiscoverBlocksPerCuMax.
 constexpr int kDiscoverBlocksPerCuMax = 16;
 constexpr int discover_blocks_per_cu() { return 8; }
 constexpr int64_t kLongBatch = (int64_t)1 << 24;
@@ -475,7 +477,8 @@ mpzch_status_t launch_remap(Scratch &sc, Timing &tm, Params p, int32_t max_p_lru
     const int g_disc = grid_for(p.n, kBlock, sc.num_cus, train_blocks_per_cu(p.n));
     p.num_segs = g_disc * kWavesPerBlock;
     p.seg_chunks = (int32_t)((num_chunks + p.num_segs - 1) / p.num_segs);
-    // the other kernels walk the segments' miss lists, one segment per wavefront pass
+    // the other kernels walk the segments' miss lists, one segment per wavefront pass.  (Two workgroups of 16 wavefronts
+    // per compute unit; of the form for several tables, with 66 registers, one is resident at a time.)
     const int g_grp = grid_for((int64_t)p.num_segs, kFinalizeWaves, sc.num_cus, 2);
 
     TIMED(tm, KDiscover, s, (launch_discover<true>(p, g_disc, s)));
@@ -1020,8 +1023,11 @@ mpzch_status_t mpzch_lookup_gather(const mpzch_table_t *t, const int64_t *identi
         TIMED(t->tm, KLookup, s, launch_lookup_short<true>(p, s));
         return MPZCH_OK;
     }
-    // five workgroups of this kernel fit a compute unit: where every wavefront has several chunks anyway, a grid that runs
-    // in one go is better than one and a half turns (2 M ids with rows of 256 bytes: 208 -> 197 us)
+    // Seven workgroups of this kernel are resident on a compute unit (22.5 KB of LDS, 72 registers): of eight per unit the
+    // last starts when another ends.  Where every wavefront has several chunks anyway, four per unit run in one go and
+    // have lines enough under way.  Eight / four per unit, us, rows of 256 bytes: 0.7 M ids 67 / 68, 1 M 103 / 98, 2 M
+    // 205 / 194, 4 M 417 / 381 (seven: 67, 104, 205, 389, for a wavefront more or less has one chunk more); rows of 64 bytes
+    // 29 / 28, 43 / 42, 89 / 88, 173 / 169.  Right above the line it costs: 530 K ids 43.8 / 46.4 and 22.3 / 21.9.
     const int full = num_cus * discover_blocks_per_cu() * kBlock;
     const int grid = grid_for(n, kBlock, num_cus, n > full ? 4 : discover_blocks_per_cu());
     p.num_segs = grid * kWavesPerBlock;

@@ -35,8 +35,9 @@ constexpr uint32_t kOwnPlace = 0x80000000u;      // list[pos] of the first occur
 // meet in one entry tell each other apart without a look at the batch (a round trip per collision; with every
 // id missed and half of the set full, that was 8 of 40 us for 262 144 ids).  Otherwise as set_insert.
 //
-// Four entries per position: the GPU performs 26 G atomics/s, whatever they are and wherever they go, so where every id is
-// missed the lanes of all wavefronts queue 10 us for their first one, and every collision queues again (262 144 ids,
+// Four entries per position: the GPU performs 27 G atomics/s on memory that its 256 MB cache holds, as it does this set of
+// 8 MB at most (17 to 18 G/s on gigabytes), so where every id is missed the lanes of all wavefronts queue 10 us for their
+// first one, and every collision queues again (262 144 ids,
 // Pass 1: 36 -> 24 us; two entries per position and 1.5 atomics per id took 27 of 36).
 constexpr int kChunkSetEntries = 4;              // per position
 constexpr int64_t kChunkMaxBatch = (int64_t)1 << 19;

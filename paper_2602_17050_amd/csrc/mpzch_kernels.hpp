@@ -685,8 +685,8 @@ __device__ __forceinline__ void gather_wave(const Params &p, bool active, int64_
 //
 // REC (training, every table of the call kept as records): a hit whose record already holds the metadata it would
 // get is not written again.  A batch draws its popular ids many times, and only the first of them has to dirty the
-// line: a read costs the memory system half of what a read and a narrow write of one line cost (47 against 20 G
-// lines/s on a 16 GB table).  The value read may be older than the table (another die's refresh not yet seen), which
+// line: a read costs the memory system half of what a read and a narrow write of one line cost (48 against 20 G
+// lines/s on tables of 8 to 24 GB).  The value read may be older than the table (another die's refresh not yet seen), which
 // costs a second store of the same value and nothing else.
 template <bool TRAIN, bool MULTI, bool GATHER, bool COUNT = TRAIN, bool NT = false, bool REC = false>
 __device__ __forceinline__ void discover_body(const Params &p)
@@ -954,10 +954,11 @@ __device__ __forceinline__ void discover_body(const Params &p)
     }
 }
 
-// The kernels around the one body.  At most four wavefronts per SIMD (the compiler then has 128 registers
-// and needs about 90): the pass is bound by memory, and measured within 2 % of its best from three to six
-// wavefronts for both table layouts; fewer hide the latency of the loads less well, more only add to the
-// queues of the memory system.
+// The kernels around the one body.  At least four wavefronts per SIMD are asked for (128 registers); with the 84 to 93
+// that training on one table needs five are resident, with the 116 and 125 of a group four, and of the lookups (64 and 72)
+// the seven that their LDS leaves room for.  The pass is bound by memory, and measured within 2 % of its best from three
+// to six wavefronts for both table layouts; fewer hide the latency of the loads less well, more only add to the queues of
+// the memory system.
 __global__ __launch_bounds__(kBlock, 4) void k_discover(Params p)
 {
     discover_body<true, false, false>(p);
@@ -965,16 +966,16 @@ __global__ __launch_bounds__(kBlock, 4) void k_discover(Params p)
 
 // The same pass with the identities read by non-temporal loads, for a two-tensor table far larger than the
 // caches: a line of identities is not used again before it is evicted anyway, and not keeping it leaves the L2
-// to the lines of metadata that the hits write into (headline with two tensors: 0.295 -> 0.253 ms).  Not for
+// to the lines of metadata that the hits write into (1 B slots, 4 M ids: 0.295 -> 0.253 ms).  Not for
 // records -- there the refresh goes into the very line the probe has fetched (0.218 -> 0.277 ms with such
-// loads) -- and not for lookups, whose repeated ids do hit in the L2 (config 3: 0.029 -> 0.034 ms).
+// loads) -- and not for lookups, whose repeated ids do hit in the L2 (100 M slots, 1 M ids: 0.029 -> 0.034 ms).
 __global__ __launch_bounds__(kBlock, 4) void k_discover_streaming(Params p)
 {
     discover_body<true, false, false, true, true>(p);
 }
 
 // the same pass over a table kept as 16-byte records: the metadata store lands in the line just read, and is left
-// out when the record shows that an earlier copy of the id has refreshed it (16 % of the headline's positions:
+// out when the record shows that an earlier copy of the id has refreshed it (16 % of 4 M positions, 1 B slots:
 // 205 -> 202 us)
 __global__ __launch_bounds__(kBlock, 4) void k_discover_records(Params p)
 {
@@ -2004,7 +2005,8 @@ __device__ __forceinline__ void finalize_body(const Params &p)
 }
 
 // The single-table form is held to 8 wavefronts per SIMD (50 registers, 66 KB of LDS for 16 wavefronts): its 8 192
-// wavefronts, each a chain of three round trips, then run in one go.  A batch of 4 M positions, 10 % of them new, with
+// wavefronts, each a chain of three round trips, then run in one go.  (The form for several tables has 66 registers, seven
+// wavefronts per SIMD, so that one workgroup of 16 is resident per compute unit and the grid runs in two turns.)  A batch of 4 M positions, 10 % of them new, with
 // the row reset: 56 -> 46 us by the ids in the miss lists (a line read for each of them before), one store for id and
 // metadata of a record, and rows reset before the workgroup's barrier instead of behind it; 41 M values over 26 tables
 // 242 -> 178 us.

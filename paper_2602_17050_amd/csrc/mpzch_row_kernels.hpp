@@ -290,8 +290,8 @@ __global__ __launch_bounds__(kBlock) void k_apply_delta_ids(int64_t *identities,
 // list (slot, id), order unspecified.  Finds are staged in LDS and appended with one reservation per kDeltaStage finds or
 // more (reservations follow each other at 12 ns).
 //
-// Bound by reading the table: non-temporal loads (6.7 instead of 6.0 TB/s) and few instructions, some 60 for a step of
-// 4 slots per lane.  Records: 16 bytes per lane and slot (50 M slots: 217 -> 130 us, of which 120 are the reads).  Two
+// Bound by reading the table: non-temporal loads and few instructions, some 60 for a step of 4 slots per lane.  Records:
+// 16 bytes per lane and slot (50 M slots: 217 -> 130 us, 6.1 TB/s, which is the rate of large reads).  Two
 // tensors: the metadata decides nearly always, so identities are read only where it lets a slot pass.  The next step is
 // requested before this one is looked at, and what a wavefront has found is known to the others by one barrier per
 // step: its counts alternate between two places.
