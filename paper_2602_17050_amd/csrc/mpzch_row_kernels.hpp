@@ -28,8 +28,23 @@ __device__ __forceinline__ int64_t row_of(const RowMod &m, int64_t slot)
 // 256 MB).  With plain accesses the caches end up full of written rows, whose write-back the next kernel pays for.  A
 // delta of 0.6 M rows of 256 bytes out of 50 M slots of records, collect + gather + apply rows + apply ids, us: 243 + 60 +
 // 64 + 29 before; non-temporal scan alone 131 + 106 + 76 + 29; rows read that way 131 + 79 + 89 + 32; rows written that
-// way too 130 + 65 + 57 + 17; the payload as well 131 + 71 + 75 + 11.
+// way too 130 + 65 + 57 + 17; the payload as well 131 + 71 + 75 + 11.  (The gather alone is slower for it where a row is
+// half a line: 0.6 M rows of 64 bytes 20 -> 23, and gather + apply 59 -> 50.)
 constexpr int kPieces = 4;
+
+// How the pieces of a list are shared out: to as many workgroups as have `each` for each thread, of those that the grid has
+// (it is sized for the list's capacity).  A thread with fewer than kPieces reads the first one again for what is missing,
+// which with one each took 5.9 -> 7.4 us for 28 000 rows of 256 bytes.
+struct Share {
+    int64_t first, stride;
+    __device__ __forceinline__ explicit Share(int64_t total, int each = kPieces)
+    {
+        const int64_t need = (total + kBlock * each - 1) / (kBlock * each);
+        const int64_t blocks = need < (int64_t)gridDim.x ? need : (int64_t)gridDim.x;
+        stride = blocks * kBlock;
+        first = (int64_t)blockIdx.x < blocks ? (int64_t)blockIdx.x * kBlock + threadIdx.x : total;
+    }
+};
 struct PieceWalk {
     int64_t k, dk;               // row
     uint32_t c, dc, chunks;      // piece of it
@@ -66,7 +81,8 @@ __global__ __launch_bounds__(kBlock) void k_reset_rows(const int64_t *slots, con
                                                         int64_t row_stride_bytes, const VEC *init_row)
 {
     const int64_t total = listed(count_dev, cap) * chunks_per_row;
-    const int64_t first = (int64_t)blockIdx.x * kBlock + threadIdx.x, stride = (int64_t)gridDim.x * kBlock;
+    const Share share(total);
+    const int64_t first = share.first, stride = share.stride;
     if (first >= total) return;
     PieceWalk at(first, stride, chunks_per_row);
     for (int64_t i = first; i < total; i += kPieces * stride) {
@@ -90,7 +106,11 @@ __global__ __launch_bounds__(kBlock) void k_reset_rows(const int64_t *slots, con
     }
 }
 
-// The same for several tensors at once (embedding weights and optimizer state, Sec. 3.4).
+// The same for several tensors at once (embedding weights and optimizer state, Sec. 3.4).  One piece at a time per thread
+// and a grid of up to 8 192 workgroups: with 2 048 the last of them end late (two tensors, 0.6 M rows of 256 bytes 81 ->
+// 67 us, of 64 bytes 27.5 -> 24.0); four pieces under way gain nothing beside that.  Short lists do not use them all (28 000
+// rows of 256 bytes, 3 500 workgroups 7.3 us, half of them 6.4).
+constexpr int kPiecesMulti = 2;
 struct RowsDesc {
     char *rows;
     const void *init_row;
@@ -110,7 +130,8 @@ __global__ __launch_bounds__(kBlock) void k_reset_rows_multi(const int64_t *slot
                                                               RowsDescs ds)
 {
     const int64_t total = listed(count_dev, cap) * ds.total_chunks;
-    const int64_t first = (int64_t)blockIdx.x * kBlock + threadIdx.x, stride = (int64_t)gridDim.x * kBlock;
+    const Share share(total, kPiecesMulti);
+    const int64_t first = share.first, stride = share.stride;
     if (first >= total) return;
     PieceWalk at(first, stride, ds.total_chunks);
     for (int64_t i = first; i < total; i += stride) {
@@ -217,7 +238,8 @@ __global__ __launch_bounds__(kBlock) void k_gather_rows(const int64_t *slots, co
                                                          int64_t row_stride_bytes, VEC *out)
 {
     const int64_t total = listed(count_dev, cap) * chunks;
-    const int64_t first = (int64_t)blockIdx.x * kBlock + threadIdx.x, stride = (int64_t)gridDim.x * kBlock;
+    const Share share(total);
+    const int64_t first = share.first, stride = share.stride;
     if (first >= total) return;
     PieceWalk at(first, stride, chunks);
     for (int64_t i = first; i < total; i += kPieces * stride) {
@@ -232,8 +254,7 @@ __global__ __launch_bounds__(kBlock) void k_gather_rows(const int64_t *slots, co
         }
 #pragma unroll
         for (int u = 0; u < kPieces; ++u)
-            v[u] = __builtin_nontemporal_load(
-                reinterpret_cast<const VEC *>(rows + (s[u] >= 0 ? row_of(mod, s[u]) : 0) * row_stride_bytes) + c[u]);
+            v[u] = __builtin_nontemporal_load(reinterpret_cast<const VEC *>(rows + (s[u] >= 0 ? row_of(mod, s[u]) : 0) * row_stride_bytes) + c[u]);
 #pragma unroll
         for (int u = 0; u < kPieces; ++u)
             if (i + u * stride < total) out[i + u * stride] = s[u] >= 0 ? v[u] : VEC(0);
@@ -251,7 +272,8 @@ __global__ __launch_bounds__(kBlock) void k_apply_delta_rows(int64_t num_slots, 
                                                               int64_t row_stride_bytes, const VEC *delta_rows)
 {
     const int64_t total = listed(count_dev, cap) * chunks;
-    const int64_t first = (int64_t)blockIdx.x * kBlock + threadIdx.x, stride = (int64_t)gridDim.x * kBlock;
+    const Share share(total);
+    const int64_t first = share.first, stride = share.stride;
     if (first >= total) return;
     PieceWalk at(first, stride, chunks);
     for (int64_t i = first; i < total; i += kPieces * stride) {

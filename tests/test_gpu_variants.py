@@ -222,6 +222,51 @@ def test_delta_round_trip_at_edges(slots, rows, dim, layout):
     t.close()
 
 
+# ---- row movers: a list's pieces go to as many workgroups as have work, of a grid sized for its capacity
+@pytest.mark.parametrize("dim", [1, 5, 64])
+@pytest.mark.parametrize("count,cap", [(0, 1), (1, 1), (63, 64), (64, 100_000), (65, 65), (1_025, 600_000), (262_145, 262_145),
+                                       (524_289, 524_289), (524_289, 2_000_000)])
+def test_row_movers_share_out_their_pieces(count, cap, dim):
+    """Rows of 4, 20 and 256 bytes (pieces of 4 and 16): lists of a few pieces, of a workgroup's share and one more, of all
+    that the largest grid takes in one turn and more, each with room for more entries than there are."""
+    rng = rng_for(912)
+    rows_n, other_n = 600_011, 600_000
+    slots = torch.full((cap,), -1, dtype=torch.int64, device="cuda")
+    at = torch.from_numpy(rng.permutation(rows_n)[:count]).cuda()          # distinct; a third of them wrap around
+    slots[:count] = torch.where(at % 3 == 0, at + rows_n, at)
+    slots[count // 2: count // 2 + (count > 9)] = -1                       # one entry that names no slot
+    valid = slots[:count] >= 0
+    at = at[valid]
+    n = torch.tensor([count], dtype=torch.int64, device="cuda")
+    src = torch.from_numpy(wl.embedding_pattern(rows_n, dim, np.float32)).cuda()
+    out = torch.full((cap, dim), 7.0, device="cuda")
+    mp.mpzch_gather_rows(slots, n, src, out)
+    want = torch.full((cap, dim), 7.0, device="cuda")
+    want[:count] = torch.where(valid[:, None], src[slots[:count].clamp(min=0) % rows_n], torch.zeros((), device="cuda"))
+    assert torch.equal(out, want)
+    ident, dst = torch.full((2 * rows_n,), -1, dtype=torch.int64, device="cuda"), torch.zeros_like(src)
+    mp.mpzch_apply_delta(ident, slots, slots + 5, n, dst, out)
+    want = torch.zeros_like(src)
+    want[at] = src[at]
+    assert torch.equal(dst, want)
+    named = slots[:count][valid]
+    want = torch.full_like(ident, -1)
+    want[named] = named + 5
+    assert torch.equal(ident, want)
+    a, b = src.clone(), torch.full((other_n, 8), 3.0, device="cuda")
+    init = torch.arange(dim, dtype=torch.float32, device="cuda")
+    mp.mpzch_reset_rows_multi(slots, n, [a, b], [init, None])
+    want = src.clone()
+    want[at] = init
+    assert torch.equal(a, want)
+    other = torch.full((other_n, 8), 3.0, device="cuda")
+    other[named % other_n] = 0.0
+    assert torch.equal(b, other)
+    a = src.clone()
+    mp.mpzch_reset_rows(slots, n, a, init)
+    assert torch.equal(a, want)
+
+
 # ---- LRU claims: one group of lanes per claimant, listed per workgroup where every wavefront has one chunk
 @pytest.mark.parametrize("layout", ["separate", "records"])
 @pytest.mark.parametrize("slots,probe", [(3, 8), (700, 1), (900, 8), (3_001, 9), (3_001, 16), (5_003, 31), (5_003, 33), (5_003, 64),
