@@ -698,13 +698,13 @@ RowGeom row_geom(const void *rows, int64_t row_bytes, int64_t row_stride_bytes, 
     return g;
 }
 // (the number of rows lives on the device: the grid is sized for the capacity of the list and bounded, the kernels stride.
-// Four times as many workgroups as 256 compute units hold at a time: they even the ends out, and those without work cost
-// nothing that shows.  2 M rows of 256 bytes, 2 048 / 8 192 workgroups, us: gather + apply 552 / 532, two tensors reset
-// 258 / 211; 128 bytes 314 / 304, 133 / 113.)
-int row_grid(int64_t items, int64_t per_block = kBlock * kPieces)
+// `most`: 2 048 workgroups, eight on each of 256 compute units, are all that run at a time.  The reset of one tensor is
+// as fast with them as with more (0.6 M rows of 256 bytes 34 / 33 us with 8 192), and those without work cost a short list
+// time.  Where the last ones would end late the kernel's bound is a multiple of it.)
+int row_grid(int64_t items, int64_t per_block = kBlock, int64_t most = 2048)
 {
     int64_t want = (items + per_block - 1) / per_block;
-    if (want > 8192) want = 8192;
+    if (want > most) want = most;
     if (want < 1) want = 1;
     return (int)want;
 }
@@ -961,7 +961,7 @@ mpzch_status_t mpzch_reset_rows_multi(const int64_t *slots, const int64_t *num_s
     if (slots_cap == 0) return MPZCH_OK;
     if (!slots) return MPZCH_ERR_INVALID_ARG;
     hipStream_t s = (hipStream_t)stream;
-    const int grid = row_grid(slots_cap * total, kBlock * kPiecesMulti);
+    const int grid = row_grid(slots_cap * total, kBlock, kMultiBlocks);
     if (wide) hipLaunchKernelGGL((k_reset_rows_multi<u32x4>), dim3(grid), dim3(kBlock), 0, s, slots, num_slots_dev, slots_cap, ds);
     else hipLaunchKernelGGL((k_reset_rows_multi<uint32_t>), dim3(grid), dim3(kBlock), 0, s, slots, num_slots_dev, slots_cap, ds);
     LAUNCH_CHECK();
@@ -978,7 +978,7 @@ mpzch_status_t mpzch_gather_rows(const int64_t *slots, const int64_t *count_dev,
     if (cap == 0) return MPZCH_OK;
     if (!slots) return MPZCH_ERR_INVALID_ARG;
     hipStream_t s = (hipStream_t)stream;
-    const int grid = row_grid(cap * g.chunks);
+    const int grid = row_grid(cap * g.chunks, kBlock * kPieces, kMoverBlocks);
     if (g.wide)
         hipLaunchKernelGGL((k_gather_rows<u32x4>), dim3(grid), dim3(kBlock), 0, s, slots, count_dev, cap, (const char *)rows,
                            row_mod(num_rows), (int32_t)g.chunks, row_stride_bytes, (u32x4 *)out_rows);
@@ -1083,7 +1083,7 @@ mpzch_status_t mpzch_apply_delta(int64_t *identities, int64_t num_slots,
     if (!slots || !ids) return MPZCH_ERR_INVALID_ARG;
     hipStream_t s = (hipStream_t)stream;
     if (rows) {
-        const int grid = row_grid(cap * g.chunks);
+        const int grid = row_grid(cap * g.chunks, kBlock * kPieces, kMoverBlocks);
         if (g.wide)
             hipLaunchKernelGGL((k_apply_delta_rows<u32x4>), dim3(grid), dim3(kBlock), 0, s, num_slots, slots, count_dev, cap,
                                (char *)rows, row_mod(num_rows), (int32_t)g.chunks, row_stride_bytes, (const u32x4 *)delta_rows);
@@ -1093,7 +1093,7 @@ mpzch_status_t mpzch_apply_delta(int64_t *identities, int64_t num_slots,
                                (const uint32_t *)delta_rows);
         LAUNCH_CHECK();
     }
-    hipLaunchKernelGGL(k_apply_delta_ids, dim3(row_grid(cap, kBlock)), dim3(kBlock), 0, s, identities, num_slots, slots, ids,
+    hipLaunchKernelGGL(k_apply_delta_ids, dim3(row_grid(cap)), dim3(kBlock), 0, s, identities, num_slots, slots, ids,
                        count_dev, cap);
     LAUNCH_CHECK();
     return MPZCH_OK;

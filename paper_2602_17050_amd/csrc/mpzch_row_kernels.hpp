@@ -32,14 +32,17 @@ __device__ __forceinline__ int64_t row_of(const RowMod &m, int64_t slot)
 // half a line: 0.6 M rows of 64 bytes 20 -> 23, and gather + apply 59 -> 50.)
 constexpr int kPieces = 4;
 
-// How the pieces of a list are shared out: to as many workgroups as have `each` for each thread, of those that the grid has
-// (it is sized for the list's capacity).  A thread with fewer than kPieces reads the first one again for what is missing,
-// which with one each took 5.9 -> 7.4 us for 28 000 rows of 256 bytes.
+// How gather and apply share out the pieces of a list: to as many workgroups as have kPieces for each thread, of those that
+// the grid has (it is sized for the list's capacity).  A thread with fewer reads the first one again for what is missing:
+// with one each the gather of 28 000 rows of 256 bytes took 7.4 instead of 5.9 us.  Up to four times as many workgroups as
+// run at a time, or the last ones end late: gather + apply of 2 M rows of 256 bytes 552 -> 532 us, of 128 bytes 314 -> 304.
+// (The resets have no second access to fill with, and the strides that depend on the count cost them more.)
+constexpr int64_t kMoverBlocks = 8192;
 struct Share {
     int64_t first, stride;
-    __device__ __forceinline__ explicit Share(int64_t total, int each = kPieces)
+    __device__ __forceinline__ explicit Share(int64_t total)
     {
-        const int64_t need = (total + kBlock * each - 1) / (kBlock * each);
+        const int64_t need = (total + kBlock * kPieces - 1) / (kBlock * kPieces);
         const int64_t blocks = need < (int64_t)gridDim.x ? need : (int64_t)gridDim.x;
         stride = blocks * kBlock;
         first = (int64_t)blockIdx.x < blocks ? (int64_t)blockIdx.x * kBlock + threadIdx.x : total;
@@ -81,8 +84,7 @@ __global__ __launch_bounds__(kBlock) void k_reset_rows(const int64_t *slots, con
                                                         int64_t row_stride_bytes, const VEC *init_row)
 {
     const int64_t total = listed(count_dev, cap) * chunks_per_row;
-    const Share share(total);
-    const int64_t first = share.first, stride = share.stride;
+    const int64_t first = (int64_t)blockIdx.x * kBlock + threadIdx.x, stride = (int64_t)gridDim.x * kBlock;
     if (first >= total) return;
     PieceWalk at(first, stride, chunks_per_row);
     for (int64_t i = first; i < total; i += kPieces * stride) {
@@ -106,11 +108,11 @@ __global__ __launch_bounds__(kBlock) void k_reset_rows(const int64_t *slots, con
     }
 }
 
-// The same for several tensors at once (embedding weights and optimizer state, Sec. 3.4).  One piece at a time per thread
-// and a grid of up to 8 192 workgroups: with 2 048 the last of them end late (two tensors, 0.6 M rows of 256 bytes 81 ->
-// 67 us, of 64 bytes 27.5 -> 24.0); four pieces under way gain nothing beside that.  Short lists do not use them all (28 000
-// rows of 256 bytes, 3 500 workgroups 7.3 us, half of them 6.4).
-constexpr int kPiecesMulti = 2;
+// The same for several tensors at once (embedding weights and optimizer state, Sec. 3.4).  One piece at a time per thread.
+// Grid of up to 4 096 workgroups: with 2 048 the last ones end late (two tensors, 0.6 M rows of 256 bytes 81 -> 71 us, of
+// 64 bytes 27.5 -> 24.9; 8 192 give 67 and 24.0, but cost a short list in a large area 0.5); four pieces under way gain
+// nothing beside that.
+constexpr int64_t kMultiBlocks = 4096;
 struct RowsDesc {
     char *rows;
     const void *init_row;
@@ -130,8 +132,7 @@ __global__ __launch_bounds__(kBlock) void k_reset_rows_multi(const int64_t *slot
                                                               RowsDescs ds)
 {
     const int64_t total = listed(count_dev, cap) * ds.total_chunks;
-    const Share share(total, kPiecesMulti);
-    const int64_t first = share.first, stride = share.stride;
+    const int64_t first = (int64_t)blockIdx.x * kBlock + threadIdx.x, stride = (int64_t)gridDim.x * kBlock;
     if (first >= total) return;
     PieceWalk at(first, stride, ds.total_chunks);
     for (int64_t i = first; i < total; i += stride) {
