@@ -29,8 +29,22 @@ __device__ __forceinline__ int64_t row_of(const RowMod &m, int64_t slot)
 // delta of 0.6 M rows of 256 bytes out of 50 M slots of records, collect + gather + apply rows + apply ids, us: 243 + 60 +
 // 64 + 29 before; non-temporal scan alone 131 + 106 + 76 + 29; rows read that way 131 + 79 + 89 + 32; rows written that
 // way too 130 + 65 + 57 + 17; the payload as well 131 + 71 + 75 + 11.  (The gather alone is slower for it where a row is
-// half a line: 0.6 M rows of 64 bytes 20 -> 23, and gather + apply 59 -> 50.)
+// half a line: 0.6 M rows of 64 bytes 20 -> 23, and gather + apply 59 -> 50.)  Pieces of 4 bytes go through the caches,
+// which put lines together from them: gather + apply of 0.6 M rows of 20 bytes non-temporally 67, plainly 57; 2 M rows
+// 241 and 181; 2 M rows of 132 bytes 605 and 519.
 constexpr int kPieces = 4;
+template <typename VEC>
+__device__ __forceinline__ VEC load_piece(const VEC *at)
+{
+    if constexpr (sizeof(VEC) == 16) return __builtin_nontemporal_load(at);
+    else return *at;
+}
+template <typename VEC>
+__device__ __forceinline__ void store_piece(VEC v, VEC *at)
+{
+    if constexpr (sizeof(VEC) == 16) __builtin_nontemporal_store(v, at);
+    else *at = v;
+}
 
 // How gather and apply share out the pieces of a list: to as many workgroups as have kPieces for each thread, of those that
 // the grid has (it is sized for the list's capacity).  A thread with fewer reads the first one again for what is missing:
@@ -255,7 +269,7 @@ __global__ __launch_bounds__(kBlock) void k_gather_rows(const int64_t *slots, co
         }
 #pragma unroll
         for (int u = 0; u < kPieces; ++u)
-            v[u] = __builtin_nontemporal_load(reinterpret_cast<const VEC *>(rows + (s[u] >= 0 ? row_of(mod, s[u]) : 0) * row_stride_bytes) + c[u]);
+            v[u] = load_piece(reinterpret_cast<const VEC *>(rows + (s[u] >= 0 ? row_of(mod, s[u]) : 0) * row_stride_bytes) + c[u]);
 #pragma unroll
         for (int u = 0; u < kPieces; ++u)
             if (i + u * stride < total) out[i + u * stride] = s[u] >= 0 ? v[u] : VEC(0);
@@ -293,7 +307,7 @@ __global__ __launch_bounds__(kBlock) void k_apply_delta_rows(int64_t num_slots, 
 #pragma unroll
         for (int u = 0; u < kPieces; ++u)
             if (s[u] >= 0 && s[u] < num_slots)
-                __builtin_nontemporal_store(v[u], reinterpret_cast<VEC *>(rows + row_of(mod, s[u]) * row_stride_bytes) + c[u]);
+                store_piece(v[u], reinterpret_cast<VEC *>(rows + row_of(mod, s[u]) * row_stride_bytes) + c[u]);
     }
 }
 
