@@ -31,7 +31,7 @@ __device__ __forceinline__ int64_t row_of(const RowMod &m, int64_t slot)
 // way too 130 + 65 + 57 + 17; the payload as well 131 + 71 + 75 + 11.  (The gather alone is slower for it where a row is
 // half a line: 0.6 M rows of 64 bytes 20 -> 23, and gather + apply 59 -> 50.)  Pieces of 4 bytes go through the caches,
 // which put lines together from them: gather + apply of 0.6 M rows of 20 bytes non-temporally 67, plainly 57; 2 M rows
-// 241 and 181; 2 M rows of 132 bytes 605 and 519.
+// 241 and 181; 2 M rows of 132 bytes 605 and 519.  (In a table of 600 MB the other way round: 0.6 M rows of 20 bytes 73, 83.)
 constexpr int kPieces = 4;
 template <typename VEC>
 __device__ __forceinline__ VEC load_piece(const VEC *at)
