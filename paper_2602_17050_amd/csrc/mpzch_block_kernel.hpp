@@ -2,7 +2,7 @@
 //
 // Three launches cost the host some 12 us and the GPU two waits of 1.6 us between kernels, which is most of a step of
 // a thousand ids.  One workgroup of up to 1 024 threads has barriers instead of launches, and what the phases hand to
-// each other (scratch set, places, counters, evicted rows) stays in LDS, so the call needs no scratch memory.  The
+// each other (scratch set, claims, places, counters, evicted rows) stays in LDS, so the call needs no scratch memory.  The
 // phases are those of mpzch_chunk_kernels.hpp.  Remap with row reset, us per call, against three launches: 64 to 512
 // positions 14 to 17.5 -> 7 to 9, 1 024 positions 13.8 to 17.7 -> 7.0 to 12.4; with two positions per thread (2 048) the
 // one compute unit took as long as three launches do (10.8 to 21.8 against 13.8 to 19.2), so the line is drawn at 1 024.
@@ -22,6 +22,8 @@ struct OneBlockArea {
     int64_t row[kOneBlock];                                  // rows to reset
     uint16_t claimant[kOneBlock];                            // first occurrences of the missed ids
     uint32_t set[2 * kOneBlock];
+    uint64_t claim_slot[2 * kOneBlock];                      // claims: address of the slot's identity (0: free entry)
+    int64_t claim_tag[2 * kOneBlock];                        // and the best claim of it so far (0: none)
     uint32_t place[kOneBlock];
     uint32_t count[kStatCount];                              // (probe lengths of 1 024 positions fit 32 bits)
     MergeArea<kOneBlock, 2 * kOneBlock> merge;
@@ -41,7 +43,11 @@ __global__ __launch_bounds__(kOneBlock) void k_remap_block(Params p)
     const int64_t id = in ? p.ids[t] : -1;
     const bool valid = in && id >= 0;
     const int64_t home = home_slot(id, d.seed, d.N);
-    for (int i = t; i < 2 * threads; i += threads) s.set[i] = kSetEmpty;
+    for (int i = t; i < 2 * threads; i += threads) {
+        s.set[i] = kSetEmpty;
+        s.claim_slot[i] = 0;
+        s.claim_tag[i] = 0;
+    }
     if (t < kStatCount) s.count[t] = 0;
     s.id[t] = id;
     s.place[t] = 0;
@@ -95,6 +101,26 @@ __global__ __launch_bounds__(kOneBlock) void k_remap_block(Params p)
     // every id that was resident has been refreshed, every first occurrence is elected
     __syncthreads();
 
+    // A claim is an atomic minimum of the claimant's tag, as in the table, but on an entry of a map in LDS: all claimants of
+    // the call are in this workgroup, and the table keeps what it held until every claim stands.  (Claims are made one after
+    // the other, each waiting for the one before.  8 steps of 1 024 positions on 4 096 slots, the whole pass: 94.9 us with
+    // the claims in memory, 90.3 so.)  An entry comes with a claim that
+    // stands, if only until a better one, so there are no more entries than claimants: at most half of the map.
+    auto claim_in_map = [&](uint64_t address, int64_t tag, uint32_t occ) -> int64_t {
+        const uint32_t size = 2u * (uint32_t)threads;
+        uint32_t at = (uint32_t)__umul64hi((address >> 3) * 0x9E3779B97F4A7C15ull, (uint64_t)size);
+        for (;;) {
+            uint64_t holds = 0;
+            if (__hip_atomic_compare_exchange_strong(&s.claim_slot[at], &holds, address, __ATOMIC_RELAXED, __ATOMIC_RELAXED,
+                                                     __HIP_MEMORY_SCOPE_WORKGROUP) ||
+                holds == address)
+                break;
+            if (++at == size) at = 0;
+        }
+        const int64_t old = __hip_atomic_fetch_min(&s.claim_tag[at], tag, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+        return old != 0 ? old : occ ? 0 : -1;
+    };
+
     // claims.  (The one compute unit is busy with instructions, not waiting: the claimants are listed, so that they take
     // up as few wavefronts as they can.)
     const int32_t bound = expiry_bound(d, p.step);
@@ -120,7 +146,7 @@ __global__ __launch_bounds__(kOneBlock) void k_remap_block(Params p)
         const int m = blocks_shift(__popcll(am), d.P);
         const int row = claim_blocks<false, REC>(d, d, cl, am, m, bound, false, s.code[w], s.req[w]);
         if (cl.active)
-            claim_walk(d, cl, m, row, s.code[w], s.req[w],
+            claim_walk(d, cl, m, row, s.code[w], s.req[w], claim_in_map,
                        [&](uint32_t who, int32_t round, int64_t at, int64_t old) {
                            atomicMax(&s.place[who], (uint32_t)round + 1u);
                            outcome = old == -1 ? 1u : old >= 0 ? 2u : 0u;

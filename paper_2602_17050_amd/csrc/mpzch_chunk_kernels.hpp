@@ -296,7 +296,7 @@ __global__ __launch_bounds__(kBlock, 4) void k_allocate_chunk(Params p)
         const int row = claim_blocks<false, REC>(d, d, c, am, m, bound, aligned, s_code[w], s_req[w]);
         if (!later) c.active = c.active && first == (uint32_t)pos;      // else: a later copy of the id
         if (c.active)
-            claim_walk(d, c, m, row, s_code[w], s_req[w],
+            claim_walk(d, c, m, row, s_code[w], s_req[w], claim_in_table,
                        [&](uint32_t who, int32_t round, int64_t at, int64_t old) {
                            if (who == (uint32_t)pos) own = (uint32_t)round + 1u;
                            else note_place(p, who, (uint32_t)round + 1u);

@@ -1141,6 +1141,12 @@ struct Claimant {
     int64_t home;
 };
 
+// The claim as an atomic minimum of the tag into the identities word.
+__device__ __forceinline__ int64_t claim_in_table(uint64_t address, int64_t tag, uint32_t)
+{
+    return __hip_atomic_fetch_min((global_ptr<int64_t>)(uintptr_t)address, tag, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
 // One stage: reads the next 1 << m blocks of every active claimant's window (am: who is active) and leaves in s_code
 // what may be claimed, in rows `row` (returned) and following of 8 bytes each.  d: the table of this lane's
 // claimant; d0: any table of the call.
@@ -1217,9 +1223,11 @@ __device__ __forceinline__ int claim_blocks(const Tab &d, const Tab &d0, const C
 // round trip of its atomic and no other.  placed(pos, round, slot, old) is called for every claim that stands, old being
 // what the slot held before; lost(pos) for a claimant that has run out of slots.  On return c is the claimant to go on
 // with, if c.active.
-template <typename Placed, typename Lost>
+// claim(address of the identity, tag, whether the slot held an id when the call began) makes the claim and returns what the
+// slot held before.
+template <typename Claim, typename Placed, typename Lost>
 __device__ __forceinline__ void claim_walk(const Tab &d, Claimant &c, int m, int row, const uint8_t *s_code,
-                                           const ClaimReq *s_req, Placed placed, Lost lost)
+                                           const ClaimReq *s_req, Claim claim, Placed placed, Lost lost)
 {
     constexpr int G = kAllocG;
     constexpr uint64_t kOnes = 0x0101010101010101ull;
@@ -1235,9 +1243,9 @@ __device__ __forceinline__ void claim_walk(const Tab &d, Claimant &c, int m, int
             x &= x - 1;
             const int32_t round = c.q + k;                           // c.q: the round of the block's first slot
             if (round >= d.P) break;
-            const int64_t mine = make_tag((uint32_t)round, c.pos, (uint32_t)(word >> (bit + 1)) & 1u);
-            const int64_t old = __hip_atomic_fetch_min((global_ptr<int64_t>)(uintptr_t)(a + ((uint64_t)k << (3 + d.sh))), mine,
-                                                       __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            const uint32_t occ = (uint32_t)(word >> (bit + 1)) & 1u;
+            const int64_t mine = make_tag((uint32_t)round, c.pos, occ);
+            const int64_t old = claim(a + ((uint64_t)k << (3 + d.sh)), mine, occ);
             if (is_tag(old) && old < mine) continue;                 // a better claim got there first
             const int64_t slot = wrap(c.home + round, d.N);
             placed(c.pos, round, slot, old);
@@ -1320,7 +1328,7 @@ __device__ __forceinline__ void allocate_body(const Params &p, int64_t vblock, i
                 const int m = later ? blocks_shift(__popcll(am), !MULTI ? d0.P : seg_one ? seg_d.P : 64) : 0;
                 const int row = claim_blocks<MULTI, REC>(d, d0, c, am, m, bound, aligned, s_code, s_req);
                 if (c.active)
-                    claim_walk(d, c, m, row, s_code, s_req,
+                    claim_walk(d, c, m, row, s_code, s_req, claim_in_table,
                                [&](uint32_t who, int32_t round, int64_t, int64_t) {
                                    const uint32_t at = round < (int32_t)kHintUnknown ? (uint32_t)round : kHintUnknown;
                                    if (who == pos) hint = at;

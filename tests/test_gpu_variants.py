@@ -319,3 +319,17 @@ def test_lookups_around_the_largest_short_one(slots, probe, layout):
         mp.mpzch_lookup_gather(t.g.handle, t.g.identities, torch.from_numpy(q).cuda(), rows, out)
         assert np.array_equal(out.cpu().numpy(), rows_np[so % slots]), n
     t.close()
+
+
+# ---- one workgroup makes its claims in a map in LDS of twice as many entries as it has threads: every position new, the
+# claimants on as many different slots as there are of them, or all on a few windows
+@pytest.mark.parametrize("layout", ["separate", "records"])
+@pytest.mark.parametrize("evict", [True, "expiry", False])
+@pytest.mark.parametrize("n", [1, 63, 64, 65, 500, 1_024])
+def test_claims_of_one_workgroup(n, evict, layout):
+    rng = rng_for(911 + n)
+    t = Pair(30_011, 40, 1, evict, 29, layout=layout)
+    for step in range(6):
+        homes = rng.integers(0, 30_011, size=n) if step % 2 else (30_000 + rng.integers(0, max(1, n // 30), size=n)) % 30_011
+        t.step(ids_at(homes, 30_011, 29, rng), 2 * step)
+    t.close()
