@@ -33,7 +33,7 @@ template <bool REC>
 __global__ __launch_bounds__(kOneBlock) void k_remap_block(Params p)
 {
     __shared__ OneBlockArea s;
-    const int lane = lane_id(), w = threadIdx.x / kWave, t = threadIdx.x, threads = blockDim.x;
+    const int lane = lane_id(), w = wave_id(), t = threadIdx.x, threads = blockDim.x;
     const int n = (int)p.n;
     const Tab d = view(p.t0);
     ProbeReq *const s_probe = reinterpret_cast<ProbeReq *>(s.req[w]);
@@ -56,12 +56,13 @@ __global__ __launch_bounds__(kOneBlock) void k_remap_block(Params p)
     // Pass 1.  (Blocks of the next 8 slots: round trips count here, not lines.)
     bool fresh = false;
     int q = 0;
-    int res = probe_first<false, REC, false>(d, id, home, first_slot_step(d), s_probe, s.code[w], p.step, &fresh, &q);
+    int res = probe_first<false, REC, false>(d, id, home, first_lane_bytes(d), s_probe, s.code[w], p.step, &fresh, &q);
+    int left = d.P - 1;
     for (;;) {
         const bool need = valid && res == kProbeGoOn && q < d.P;
         if (!__any(need)) break;
         bool f = false;
-        const int got = probe_more<false, REC>(d, id, home, q, need, s_probe, s.code[w], p.step, &f);
+        const int got = probe_more<false, REC>(d, id, home, q, left, need, s_probe, s.code[w], p.step, &f);
         if (need) { res = got; fresh = f; }
     }
     const bool hit = valid && res >= 0, miss = valid && res < 0;

@@ -165,7 +165,7 @@ __global__ __launch_bounds__(kBlock << SHIFT, 4) void k_discover_chunk(Params p)
     __shared__ uint32_t s_red[WAVES][5];
     __shared__ MergeArea<THREADS, 2 * kBlock> s_merge;
 
-    const int lane = lane_id(), w = threadIdx.x / kWave;
+    const int lane = lane_id(), w = wave_id();
     const int64_t pos = (int64_t)blockIdx.x * kBlock + w * PER + lane;
     const bool in = lane < PER && pos < p.n;
     const Tab d = view(p.t0);
@@ -176,17 +176,18 @@ __global__ __launch_bounds__(kBlock << SHIFT, 4) void k_discover_chunk(Params p)
     int res = kProbeGoOn, q = 0;
     if constexpr (SHIFT == 0) {
         // first block: the aligned one, or in a table that the caches hold the 8 slots from the home slot on (k_allocate)
-        const uint32_t step = first_slot_step(d);
+        const uint32_t lane_bytes = first_lane_bytes(d);
         if ((d.N << (3 + d.sh)) > kCachedTableBytes)
-            res = probe_first<false, REC, true>(d, id, home, step, s_req[w], s_code[w], p.step, &fresh, &q);
+            res = probe_first<false, REC, true>(d, id, home, lane_bytes, s_req[w], s_code[w], p.step, &fresh, &q);
         else
-            res = probe_first<false, REC, false>(d, id, home, step, s_req[w], s_code[w], p.step, &fresh, &q);
+            res = probe_first<false, REC, false>(d, id, home, lane_bytes, s_req[w], s_code[w], p.step, &fresh, &q);
     }
+    int left = SHIFT == 0 ? d.P - 1 : d.P;
     for (;;) {
         const bool need = valid && res == kProbeGoOn && q < d.P;
         if (!__any(need)) break;
         bool f = false;
-        const int got = probe_more<false, REC>(d, id, home, q, need, s_req[w], s_code[w], p.step, &f);
+        const int got = probe_more<false, REC>(d, id, home, q, left, need, s_req[w], s_code[w], p.step, &f);
         if (need) { res = got; fresh = f; }
     }
     const bool hit = valid && res >= 0, miss = valid && res < 0;

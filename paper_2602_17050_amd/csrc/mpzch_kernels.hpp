@@ -171,6 +171,14 @@ __device__ __forceinline__ int64_t shfl64(int64_t v, int src)
 }
 
 __device__ __forceinline__ int lane_id() { return threadIdx.x & (kWave - 1); }
+// This wavefront's number in the workgroup, in a scalar register: what follows from it (segments, chunks, loop ends) then
+// costs scalar instructions, and the loops are branches instead of masks.
+__device__ __forceinline__ int wave_id() { return __builtin_amdgcn_readfirstlane((int)(threadIdx.x / kWave)); }
+// how many of the lanes below this one are in the mask
+__device__ __forceinline__ int lanes_below(uint64_t mask)
+{
+    return (int)__builtin_amdgcn_mbcnt_hi((uint32_t)(mask >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)mask, 0u));
+}
 
 // table owning position pos (largest f with offsets[f] <= pos)
 __device__ __forceinline__ int find_table(const int64_t *offsets, int num_tables, int64_t pos)
@@ -432,166 +440,190 @@ __device__ __forceinline__ int probe_absent(int empty_round) { return kProbeAbse
 // slots of the window read until the search ended: up to and including the first empty one
 __device__ __forceinline__ int absent_len(int code) { return -code - 1; }
 
-// What the lane that holds an id leaves in LDS for the lanes that load for it: the id, and `where`
-// = address of the identity of the first slot to read (bits 0..47: device addresses have no more)
-// with, for probe_more, in bit 48 + r whether round q + r exists (r < G).
+// What the lane that holds an id leaves in LDS for the lanes that load for it: the id, and the address of the identity of
+// the first slot to read.
 struct alignas(16) ProbeReq {
     int64_t id;
     uint64_t where;
 };
-constexpr int kWhereAddrBits = 48;
+constexpr int kWhereAddrBits = 48;     // (device addresses have no more)
 
-// the loads of one pass: lane r of a group reads slot number k(r) behind the first one, where k counts the rounds
-// that exist below its own -- its own slot when its round exists, else the one after the last: a valid address in or next
-// to the line that is fetched anyway.  Slots past the end of the table go on at slot 0.
+// The reads of one pass: 64 blocks of 8 slots, 1 << m of them side by side for each request; 8 lanes read one block, and
+// lane_bytes is how far this lane's slot lies from its request's first one.  rows: how many of the blocks anybody asks for.
+// What was seen goes to s_code, a byte per slot in the order of requests and slots.
 // NT: the loads are marked non-temporal (see k_discover_streaming).  REC: a table of records, read with the
 // metadata (12 bytes per lane, the same line): what comes back besides the id is the slot's metadata.
-template <int G, bool NT, bool REC>
-__device__ __forceinline__ void probe_loads(const Tab &d, const ProbeReq *s_req, int64_t (&v)[G], int32_t (&m)[G])
+//
+// The blocks are read as they lie and nothing is asked per slot: whoever made the request chose a first slot from which
+// all of them are in the table, and its own lane knows which bytes are rounds of its window.  (A lookup spends more than
+// half of its time issuing instructions.  1 M ids, windows of 32 slots, 80 % load: 856 -> 578 vector instructions per
+// wavefront of two chunks, 21.4 -> 19.5 us; 10 K values over 26 tables 5.6 -> 5.1.)
+template <int T, bool NT, bool REC>
+__device__ __forceinline__ void probe_rows(const ProbeReq *req, int next, uint8_t *s_code, uint32_t lane_bytes, int32_t fresh_meta)
 {
-    constexpr int IPI = kWave / G;
-    const int lane = lane_id();
-    const int g = lane / G, r = lane % G;
-    const uint32_t below = (1u << r) - 1u;
-    const int sh3 = 3 + d.sh;
-    const uint64_t table_bytes = (uint64_t)d.N << sh3;
-    const uint64_t table_end = (uint64_t)(uintptr_t)(int64_t *)d.I + table_bytes;
+    int64_t v[T];
+    int32_t meta[T];
+    // (the compiler would start what the forms have in common before it branches to one of them, and wait there)
+    asm volatile("" ::"i"(T) : "memory");
 #pragma unroll
-    for (int t = 0; t < G; ++t) {
-        const uint64_t where = s_req[t * IPI + g].where;
-        const uint32_t k = (uint32_t)__popc((uint32_t)(where >> kWhereAddrBits) & below);
-        uint64_t a = (where & ((1ull << kWhereAddrBits) - 1ull)) + (uint64_t)(k << sh3);
-        if (a >= table_end) a -= table_bytes;
+    for (int t = 0; t < T; ++t) {
+        const uint64_t a = req[t * next].where + lane_bytes;
         if constexpr (REC) {
             const u32x3 rec = *(global_ptr<u32x3>)(uintptr_t)a;
             v[t] = (int64_t)(((uint64_t)rec.y << 32) | rec.x);
-            m[t] = (int32_t)rec.z;
+            meta[t] = (int32_t)rec.z;
         } else if constexpr (NT) {
             v[t] = __builtin_nontemporal_load((global_ptr<int64_t>)(uintptr_t)a);
         } else {
             v[t] = *(global_ptr<int64_t>)(uintptr_t)a;
         }
     }
+    __builtin_amdgcn_sched_barrier(0);          // (the ids are read now, not kept meanwhile)
+#pragma unroll
+    for (int t = 0; t < T; ++t) {
+        const bool same = v[t] == req[t * next].id;
+        // (only an empty slot has a high word of all ones: ids are not negative, and the rounds of tags stay below 2^21)
+        const uint32_t empty = __builtin_elementwise_sub_sat((uint32_t)((uint64_t)v[t] >> 32), 0xFFFFFFFDu);       // 2 or 0
+        uint32_t hit = 1;
+        if constexpr (REC) hit = meta[t] == fresh_meta ? 5u : 1u;
+        s_code[t * kWave] = (uint8_t)(same ? hit : empty);
+    }
 }
 
-// probe_first's slot_step (tables of fewer than 8 slots have no block to read: every lane reads slot 0)
-__device__ __forceinline__ uint32_t first_slot_step(const Tab &d)
+// (Which of the 64 blocks anybody asks for: the last few searches of a wavefront ask for a quarter of them.)
+template <bool NT, bool REC>
+__device__ __forceinline__ void probe_blocks(const ProbeReq *s_req, uint8_t *s_code, int m, int rows, uint32_t lane_bytes,
+                                             int32_t fresh_meta)
 {
-    return d.N >= kFirstG ? (uint32_t)(lane_id() % kFirstG) << (3 + d.sh) : 0u;
+    const int lane = lane_id();
+    const ProbeReq *const req = s_req + ((lane / 8) >> m);
+    const int next = 8 >> m;
+    if (rows > 32) probe_rows<8, NT, REC>(req, next, s_code + lane, lane_bytes, fresh_meta);
+    else if (rows > 16) probe_rows<4, NT, REC>(req, next, s_code + lane, lane_bytes, fresh_meta);
+    else probe_rows<2, NT, REC>(req, next, s_code + lane, lane_bytes, fresh_meta);
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+}
+
+// probe_first's lane_bytes (tables of fewer than 8 slots have no block to read: the lanes past the last slot read that one)
+__device__ __forceinline__ uint32_t first_lane_bytes(const Tab &d)
+{
+    const int r = lane_id() % kFirstG;
+    return (uint32_t)((int64_t)r < d.N ? r : (int)d.N - 1) << (3 + d.sh);
 }
 
 // The first pass: the aligned block of 8 slots that holds the home slot or, ALIGNED not set, the 8 slots from the home slot
 // on.  d is wave-uniform; s_req, s_code: this wavefront's own areas of LDS; next: the round to go on with; fresh: whether
-// the record of a hit holds fresh_meta already.  The lanes that load read the block as it lies, eight slots
-// from its first one on (slot_step: how far this lane's slot lies from it, in bytes), and only the id's own lane knows
-// which of them are its rounds: two instructions per load instead of fifteen.  An id whose block reaches out of the table
-// leaves everything to the later passes.  (With the
+// the record of a hit holds fresh_meta already.  A block that reaches out of the table is moved to its edge.  (With the
 // tables of a group looked at one at a time, see discover_body: 41 M values over 26 tables 961 -> 882 us; lookup of 1 M ids
 // 19.8 -> 18.4 us.)
 template <bool NT, bool REC, bool ALIGNED = true>
-__device__ __forceinline__ int probe_first(const Tab &d, int64_t id, int64_t home, uint32_t slot_step, ProbeReq *s_req,
+__device__ __forceinline__ int probe_first(const Tab &d, int64_t id, int64_t home, uint32_t lane_bytes, ProbeReq *s_req,
                                            uint8_t *s_code, int32_t fresh_meta, bool *fresh, int *next)
 {
-    constexpr int G = kFirstG, IPI = kWave / G;
+    constexpr int G = kFirstG;
     const int lane = lane_id();
-    const int g = lane / G;
-    const int o = ALIGNED ? block_offset(d, home, G) : 0;
-    const bool here = home >= o && home - o + G <= d.N;
-    s_req[lane] = ProbeReq{id, (uint64_t)(uintptr_t)(int64_t *)id_at(d, here ? home - o : 0)};
-    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-    int64_t v[G];
-    int32_t m[G];
-#pragma unroll
-    for (int t = 0; t < G; ++t) {
-        const uint64_t a = s_req[t * IPI + g].where + slot_step;
-        if constexpr (REC) {
-            const u32x3 rec = *(global_ptr<u32x3>)(uintptr_t)a;
-            v[t] = (int64_t)(((uint64_t)rec.y << 32) | rec.x);
-            m[t] = (int32_t)rec.z;
-        } else if constexpr (NT) {
-            v[t] = __builtin_nontemporal_load((global_ptr<int64_t>)(uintptr_t)a);
-        } else {
-            v[t] = *(global_ptr<int64_t>)(uintptr_t)a;
-        }
+    const int64_t last = d.N > G ? d.N - G : 0;
+    int64_t first = home;
+    if constexpr (ALIGNED) {
+        first -= block_offset(d, home, G);
+        first = first > 0 ? first : 0;
     }
-    __builtin_amdgcn_sched_barrier(0);          // (the ids are read again now, not kept meanwhile)
-#pragma unroll
-    for (int t = 0; t < G; ++t) {
-        const int64_t gid = s_req[t * IPI + g].id;
-        uint8_t code = v[t] == gid ? 1 : (v[t] == -1 ? 2 : 0);
-        if constexpr (REC) code = v[t] == gid ? (m[t] == fresh_meta ? 5 : 1) : (v[t] == -1 ? 2 : 0);
-        s_code[t * kWave + lane] = code;        // = byte (slot of the block) of id t * IPI + g
-    }
+    first = first < last ? first : last;
+    const int o = (int)(home - first);
+    s_req[lane] = ProbeReq{id, (uint64_t)(uintptr_t)(int64_t *)id_at(d, first)};
     __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    probe_blocks<NT, REC>(s_req, s_code, 0, kWave, lane_bytes, fresh_meta);
     const uint64_t x = *reinterpret_cast<const uint64_t *>(s_code + lane * G) >> (8 * o);
     const int bit = __ffsll((unsigned long long)x) - 1;
     const int round = bit >> 3;
-    const int count = d.P < G - o ? d.P : G - o;
+    const int there = (d.N < G ? (int)d.N : G) - o;
+    const int count = d.P < there ? d.P : there;
     if constexpr (REC) *fresh = x != 0 && ((x >> (bit & 63)) & 4ull) != 0;
-    *next = here ? G - o : 0;
+    *next = count;
     int found = (bit & 1) ? probe_absent(round) : round;
     if (x == 0 || round >= count) found = count == d.P ? probe_absent(d.P - 1) : kProbeGoOn;   // (or: the whole window was read)
     __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");    // the areas are written again by the next pass
-    return here ? found : kProbeGoOn;
+    return found;
 }
 
-// How many blocks of 8 slots each of `count` lanes gets in one pass over 64 blocks, as a shift; no more than windows of
-// P slots have use for.
-__device__ __forceinline__ int blocks_shift(int count, int P)
+// How many blocks of 8 slots each of `count` lanes gets in one pass over 64 blocks, as a shift; no more than `left` rounds
+// have use for.
+__device__ __forceinline__ int blocks_shift(int count, int left)
 {
     const int m = count <= 8 ? 3 : count <= 16 ? 2 : count <= 32 ? 1 : 0;
-    const int most = P <= 8 ? 0 : P <= 16 ? 1 : P <= 32 ? 2 : 3;
+    const int most = left <= 8 ? 0 : left <= 16 ? 1 : left <= 32 ? 2 : 3;
     return m < most ? m : most;
 }
 
 // A later pass: rounds q, q + 1, ... of the lanes with `need` set (the others' arguments are ignored).  The 64 blocks of
 // 8 slots that one pass reads are shared out among those lanes: the fewer are left, the more of its window each one
 // sees per round trip (8 slots, up to 64 when 8 lanes or fewer are left; a window at 95 % load is often longer than
-// 8 slots).  q is moved on past the slots that were looked at.
+// 8 slots).  q is moved on past the slots that were looked at; left: how many rounds any of the lanes has left, as far as
+// is known (blocks past the end of every window are lines read for nothing).  The slots of one request lie side by side: a window that
+// goes on at the table's start does so in the next pass.
 template <bool NT = false, bool REC = false>
-__device__ __forceinline__ int probe_more(const Tab &d, int64_t id, int64_t home, int &q, bool need, ProbeReq *s_req,
-                                          uint8_t *s_code, int32_t fresh_meta = 0, bool *fresh = nullptr)
+__device__ __forceinline__ int probe_more(const Tab &d, int64_t id, int64_t home, int &q, int &left, bool need,
+                                          ProbeReq *s_req, uint8_t *s_code, int32_t fresh_meta = 0, bool *fresh = nullptr)
 {
-    constexpr int G = 8, IPI = kWave / G;
+    constexpr int G = 8;
     const int lane = lane_id();
-    const int g = lane / G;
     const uint64_t nm = __ballot(need);
-    const int m = blocks_shift(__popcll(nm), d.P);
-    const int row = __popcll(nm & ((1ull << lane) - 1ull)) << m;
-    s_req[lane] = ProbeReq{-1, (uint64_t)(uintptr_t)(int64_t *)d.I};        // blocks nobody asks for: slot 0
+    const int requests = uniform32(__popcll(nm));
+    int m = blocks_shift(requests, left);
+    if (d.N < 8 * G) m = d.N < 2 * G ? 0 : d.N < 4 * G ? (m < 1 ? m : 1) : (m < 2 ? m : 2);
+    const int width = d.N < G ? (int)d.N : G << m;                          // slots of a request
+    const int at = lanes_below(nm);
+    const int64_t slot = need ? wrap(home + q, d.N) : 0;
+    const int64_t last = d.N - width;
+    const int64_t first = slot < last ? slot : last;
+    const int o = (int)(slot - first);
+    const int count = d.P - q < width - o ? d.P - q : width - o;           // rounds among them
+    // (what nobody asks for: any slot that is there)
+    s_req[need ? at : requests + lane - at] = ProbeReq{id, (uint64_t)(uintptr_t)(int64_t *)id_at(d, first)};
     __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-    if (need) {
-        for (int j = 0; j < (1 << m); ++j) {
-            const int left = d.P - (q + G * j);                             // rounds from the block's first one on
-            const uint32_t rounds = left >= G ? 0xFFu : left > 0 ? (1u << left) - 1u : 0u;
-            const int64_t first_slot = left > 0 ? wrap(home + (q + G * j), d.N) : 0;
-            s_req[row + j] = ProbeReq{id, (uint64_t)(uintptr_t)(int64_t *)id_at(d, first_slot) | ((uint64_t)rounds << kWhereAddrBits)};
-        }
-    }
-    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-    int64_t v[G];
-    int32_t meta[G];
-    probe_loads<G, NT, REC>(d, s_req, v, meta);
-#pragma unroll
-    for (int t = 0; t < G; ++t) {
-        const int64_t gid = s_req[t * IPI + g].id;
-        uint8_t code = v[t] == gid ? 1 : (v[t] == -1 ? 2 : 0);
-        if constexpr (REC) code = v[t] == gid ? (meta[t] == fresh_meta ? 5 : 1) : (v[t] == -1 ? 2 : 0);
-        s_code[t * kWave + lane] = code;
-    }
-    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    const int r = lane & ((G << m) - 1);                                    // this lane's slot of its request
+    probe_blocks<NT, REC>(s_req, s_code, m, requests << m, (uint32_t)(r < width ? r : width - 1) << (3 + d.sh), fresh_meta);
+    const bool moved = __any(need && o != 0);
     int found = kProbeGoOn;
     if (need) {
-        for (int j = 0; j < (1 << m) && found == kProbeGoOn; ++j) {
-            const uint64_t x = *reinterpret_cast<const uint64_t *>(s_code + (row + j) * G);
-            const int bit = __ffsll((unsigned long long)x) - 1;
-            const int round = q + G * j + (bit >> 3);
-            if (x == 0 || round >= d.P) continue;
-            if constexpr (REC) *fresh = ((x >> bit) & 4ull) != 0;
-            found = (bit & 1) ? probe_absent(round) : round;
+        // the first byte that is not 0, from the o-th on
+        const uint8_t *const mine = s_code + (at << (m + 3));
+        uint64_t x = 0;
+        int from = 0;
+        auto see = [&](int j, int skip) {
+            uint64_t y = reinterpret_cast<const uint64_t *>(mine)[j];
+            if (skip > 0) y = skip < G ? y & (~0ull << (8 * skip)) : 0;
+            if (y) {
+                x = y;
+                from = G * j;
+            }
+        };
+        if (moved) {
+#pragma unroll 1
+            for (int j = (1 << m) - 1; j >= 0; --j) see(j, o - G * j);
+        } else {
+            if (m == 3) {
+                see(7, 0);
+                see(6, 0);
+                see(5, 0);
+                see(4, 0);
+            }
+            if (m >= 2) {
+                see(3, 0);
+                see(2, 0);
+            }
+            if (m >= 1) see(1, 0);
+            see(0, 0);
         }
-        q += G << m;
+        const int bit = __ffsll((unsigned long long)x) - 1;
+        const int k = from + (bit >> 3) - o;
+        if (x && k < count) {
+            if constexpr (REC) *fresh = ((x >> bit) & 4ull) != 0;
+            found = (bit & 1) ? probe_absent(q + k) : q + k;
+        }
+        q += count;
     }
+    left -= width;
     __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");    // the areas are written again by the next pass
     return found;
 }
@@ -701,7 +733,7 @@ __device__ __forceinline__ void discover_body(const Params &p)
     __shared__ TableDesc s_desc[MULTI ? kMaxTables : 1];
 
     const int lane = lane_id();
-    const int w = threadIdx.x / kWave;
+    const int w = wave_id();
     int block = blockIdx.x;
     if constexpr (MULTI && TRAIN) {
         // Which workgroup takes which part of the batch.  The dies take workgroups in turn; here each gets whole
@@ -808,12 +840,12 @@ __device__ __forceinline__ void discover_body(const Params &p)
             int dist = -1;
             bool fresh = false;
             int mlen = q0 < 0 ? -q0 : 0;                // > 0: the search has ended at an empty slot
-            int q = q0;
+            int q = q0, left = d.P - 1;
             for (;;) {
                 const bool need = have && dist < 0 && mlen == 0 && q < d.P;
                 if (!__any(need)) break;
                 bool got_fresh = false;
-                const int got = probe_more<NT, REC>(d, id, home, q, need, s_req[w], s_code[w], p.step, &got_fresh);
+                const int got = probe_more<NT, REC>(d, id, home, q, left, need, s_req[w], s_code[w], p.step, &got_fresh);
                 if (need) {
                     if (got >= 0) { dist = got; fresh = got_fresh; }
                     else if (got <= kProbeAbsent) mlen = absent_len(got);   // an empty slot ends the search
@@ -823,7 +855,7 @@ __device__ __forceinline__ void discover_body(const Params &p)
             const bool miss = have && dist < 0;
             const uint64_t mb = __ballot(miss);
             if (miss && TRAIN) {
-                const int at = nmiss + __popcll(mb & ((1ull << lane) - 1ull));      // slots already consumed
+                const int at = nmiss + lanes_below(mb);      // slots already consumed
                 s_pos[w][at] = pos;
                 s_id[w][at] = id;
             }
@@ -886,10 +918,10 @@ __device__ __forceinline__ void discover_body(const Params &p)
                 const bool mine = todo && (!multi || pos < t_hi);
                 const bool valid = mine && id >= 0;
                 const int64_t home = mine ? home_slot(id, d.seed, d.N) : 0;
-                const uint32_t slot_step = first_slot_step(d);
+                const uint32_t lane_bytes = first_lane_bytes(d);
                 bool fresh = false;
                 int next = 0;
-                const int res = probe_first<NT, REC>(d, id, home, slot_step, s_req[w], s_code[w], p.step, &fresh, &next);
+                const int res = probe_first<NT, REC>(d, id, home, lane_bytes, s_req[w], s_code[w], p.step, &fresh, &next);
                 const bool hit = valid && res >= 0;
                 finish_hit(d, hit, pos, home, res, false, fresh);
                 if (COUNT) {
@@ -915,7 +947,7 @@ __device__ __forceinline__ void discover_body(const Params &p)
                 const bool park = valid && (res == kProbeGoOn || (TRAIN && res <= kProbeAbsent));
                 const uint64_t pb = __ballot(park);
                 if (park) {
-                    const int at = staged + __popcll(pb & ((1ull << lane) - 1ull));
+                    const int at = staged + lanes_below(pb);
                     s_pos[w][at] = (uint32_t)pos;
                     s_id[w][at] = id;
                     s_q[w][at] = res <= kProbeAbsent ? -absent_len(res) : next;
@@ -1031,7 +1063,7 @@ __global__ __launch_bounds__(kBlock, 4) void k_lookup_short(Params p)
     __shared__ ProbeReq s_req[kWavesPerBlock][kWave];
     __shared__ __attribute__((aligned(16))) uint8_t s_code[kWavesPerBlock][kWave * kFirstG];
     __shared__ TableDesc s_desc[MULTI ? kMaxTables : 1];
-    const int lane = lane_id(), w = threadIdx.x / kWave;
+    const int lane = lane_id(), w = wave_id();
     const int per = kWave >> p.short_shift;                      // ids of a wavefront
     const int64_t pos = ((int64_t)blockIdx.x * kWavesPerBlock + w) * per + lane;
     bool todo = lane < per && pos < p.n;
@@ -1058,11 +1090,11 @@ __global__ __launch_bounds__(kBlock, 4) void k_lookup_short(Params p)
         }
         const bool valid = mine && id >= 0;
         const int64_t home = home_slot(id, d.seed, d.N);
-        int res = kProbeGoOn, q = 0;
+        int res = kProbeGoOn, q = 0, left = d.P;
         for (;;) {
             const bool need = valid && res == kProbeGoOn && q < d.P;
             if (!__any(need)) break;
-            const int got = probe_more<false, false>(d, id, home, q, need, s_req[w], s_code[w]);
+            const int got = probe_more<false, false>(d, id, home, q, left, need, s_req[w], s_code[w]);
             if (need) res = got;
         }
         const bool hit = valid && res >= 0;

@@ -333,3 +333,33 @@ def test_claims_of_one_workgroup(n, evict, layout):
         homes = rng.integers(0, 30_011, size=n) if step % 2 else (30_000 + rng.integers(0, max(1, n // 30), size=n)) % 30_011
         t.step(ids_at(homes, 30_011, 29, rng), 2 * step)
     t.close()
+
+
+# ---- the blocks of a probe pass at the edges of small tables (fewer slots than a request is wide; requests moved back from
+# the table's end; windows that go on at its start) and of identities that are not aligned to a block
+@pytest.mark.parametrize("layout", ["separate", "records"])
+@pytest.mark.parametrize("slots", [1, 2, 7, 8, 9, 15, 16, 17, 31, 33, 63, 64, 65, 203])
+def test_probe_blocks_at_the_edges_of_small_tables(slots, layout):
+    rng = rng_for(912 + slots)
+    for probe in (1, 5, 8, 13, 32, 64):
+        t = Pair(slots, probe, 1, True, 31, layout=layout)
+        sizes = [1, max(1, slots // 2), min(1_000, 5 * slots), 1_100] + ([530_000] if slots in (9, 65) and probe == 13 else [])
+        for step, n in enumerate(sizes):
+            ids = ids_at(rng.integers(0, slots, size=min(n, 3_000)), slots, 31, rng)
+            ids = np.concatenate([ids, ids[rng.integers(0, ids.size, size=n - ids.size)]])
+            t.step(ids, 2 * step)
+            q = np.concatenate([ids[:2_000], ids_at(rng.integers(0, slots, size=70), slots, 31, rng)])
+            so, fo = t.lookup(q)
+            if layout == "separate":
+                for shift in (1, 3, 6):
+                    moved = torch.empty(slots + 8, dtype=torch.int64, device="cuda")[shift: shift + slots]
+                    moved.copy_(t.g.identities)
+                    qg = torch.from_numpy(q).cuda()
+                    for count in (q.size, 300_000):                 # a short lookup, and one of whole chunks
+                        many = qg.repeat(-(-count // q.size))[:count].contiguous()
+                        out = torch.empty_like(many)
+                        found = torch.empty(count, dtype=torch.uint8, device="cuda")
+                        mp.mpzch_lookup(t.g.handle, moved, many, out, found)
+                        assert np.array_equal(out.cpu().numpy(), np.resize(so, count)), (shift, count)
+                        assert np.array_equal(found.cpu().numpy(), np.resize(fo, count)), (shift, count)
+        t.close()
