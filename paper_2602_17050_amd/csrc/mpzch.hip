@@ -444,7 +444,7 @@ mpzch_status_t launch_remap_chunks(Timing &tm, const Params &p, int32_t max_p_lr
     else hipLaunchKernelGGL((k_allocate_chunk<false>), dim3(grid), dim3(kBlock), 0, s, p);
     LAUNCH_CHECK();
     if (!tm.end(s) || !tm.begin(KFinalize, s)) return MPZCH_ERR_HIP;
-    hipLaunchKernelGGL(k_finalize_chunk, dim3(grid), dim3(kBlock), 0, s, p);
+    hipLaunchKernelGGL(k_finalize_chunk, dim3(kPublishTasks + grid), dim3(kBlock), 0, s, p);
     LAUNCH_CHECK();
     if (!tm.end(s)) return MPZCH_ERR_HIP;
     return MPZCH_OK;

@@ -84,7 +84,7 @@ __device__ __forceinline__ uint32_t wave_sum32(uint32_t x)
 }
 
 // counters of one workgroup, three words: positions (hit, miss, invalid), probe lengths (hits, misses), outcomes
-// (distinct ids, inserts, evictions)
+// (distinct ids, inserts, evictions); the first ones of all workgroups, then the second ones, then the third ones
 __device__ __forceinline__ uint64_t pack3(uint32_t a, uint32_t b, uint32_t c)
 {
     return (uint64_t)a | ((uint64_t)b << 16) | ((uint64_t)c << 32);
@@ -224,8 +224,8 @@ __global__ __launch_bounds__(kBlock << SHIFT, 4) void k_discover_chunk(Params p)
             uint32_t t[5] = {0, 0, 0, 0, 0};
             for (int i = 0; i < WAVES; ++i)
                 for (int k = 0; k < 5; ++k) t[k] += s_red[i][k];
-            p.wg_words[3 * blockIdx.x] = pack3(t[0], t[1], t[2]);
-            p.wg_words[3 * blockIdx.x + 1] = (uint64_t)t[3] | ((uint64_t)t[4] << 32);
+            p.wg_words[blockIdx.x] = pack3(t[0], t[1], t[2]);
+            p.wg_words[gridDim.x + blockIdx.x] = (uint64_t)t[3] | ((uint64_t)t[4] << 32);
         }
     }
 }
@@ -252,7 +252,7 @@ __device__ __forceinline__ void leave_outcomes(const Params &p, bool agent, bool
         uint32_t t[3] = {0, 0, 0};
         for (int i = 0; i < WAVES; ++i)
             for (int k = 0; k < 3; ++k) t[k] += s_red[i][k];
-        p.wg_words[3 * blockIdx.x + 2] = pack3(t[0], t[1], t[2]);
+        p.wg_words[2 * gridDim.x + blockIdx.x] = pack3(t[0], t[1], t[2]);
     }
 }
 
@@ -402,13 +402,17 @@ __device__ __forceinline__ unsigned long long block_sum(unsigned long long x, un
     return v;
 }
 
-// The call's counters, from the words of all workgroups: three tasks, taken by the first workgroups.
-__device__ __forceinline__ void publish_words(const Params &p, int task, unsigned long long *s_sum)
+// The call's counters, from the words of all `groups` workgroups: three tasks, each the work of a workgroup of its own in
+// front of the others: at the end of the first three it was the last 1.7 us of the kernel.  Together with the counts of
+// the workgroups before being requested at the start: 51 calls of 65 536 positions 1 057 -> 1 027 us, 12 of 262 144
+// 806 -> 796.
+constexpr int kPublishTasks = 3;
+__device__ __forceinline__ void publish_words(const Params &p, int task, int groups, unsigned long long *s_sum)
 {
     if (task < 2 && !p.out_stats) return;
     unsigned long long a = 0, b = 0, c = 0;
-    for (int i = threadIdx.x; i < (int)gridDim.x; i += kBlock) {
-        const uint64_t v = p.wg_words[3 * i + task];
+    for (int i = threadIdx.x; i < groups; i += kBlock) {
+        const uint64_t v = p.wg_words[task * groups + i];
         if (task == 1) {
             a += (uint32_t)v;
             b += v >> 32;
@@ -444,9 +448,15 @@ __global__ __launch_bounds__(kBlock, 8) void k_finalize_chunk(Params p)
 {
     __shared__ int64_t s_row[kBlock];
     __shared__ unsigned long long s_sum[kWavesPerBlock];
+    __shared__ uint32_t s_base[kWavesPerBlock];
     __shared__ MergeArea<kBlock, 2 * kBlock> s_merge;
 
-    const int64_t pos = (int64_t)blockIdx.x * kBlock + threadIdx.x;
+    const int groups = (int)gridDim.x - kPublishTasks, group = (int)blockIdx.x - kPublishTasks;
+    if (group < 0) {
+        publish_words(p, (int)blockIdx.x, groups, s_sum);
+        return;
+    }
+    const int64_t pos = (int64_t)group * kBlock + threadIdx.x;
     const bool in = pos < p.n;
     const Tab d = view(p.t0);
     const uint32_t word = in ? p.list[pos] : kNoEntry;
@@ -456,17 +466,40 @@ __global__ __launch_bounds__(kBlock, 8) void k_finalize_chunk(Params p)
     // a time)
     static_assert(kChunkSetEntries == 4, "cleared as one vector of four");
     if (in) reinterpret_cast<u32x4 *>(p.set_slot)[pos] = u32x4(kSetEmpty);
-    const int evicted = (int)unpack3(p.wg_words[3 * blockIdx.x + 2], 2);
-    const bool have = word != kNoEntry;
-    bool refresh = false;
+    // what the evicted slots of this workgroup need, requested now: the slots, and the counts of the workgroups before
+    const uint64_t *const outcomes = p.wg_words + 2 * groups;
+    const int evicted = (int)unpack3(outcomes[group], 2);
+    constexpr int kMostBefore = (int)(kChunkMaxBatch / kBlock / kBlock);
+    uint64_t before[kMostBefore];
+#pragma unroll
+    for (int k = 0; k < kMostBefore; ++k) {
+        before[k] = 0;
+        if (d.evict != 0 && k * kBlock < group) {
+            const int i = k * kBlock + (int)threadIdx.x;
+            before[k] = outcomes[i < group ? i : group];
+            if (i >= group) before[k] = 0;
+        }
+    }
+    const int64_t evicted_slot = d.evict != 0 && in ? p.evicted[pos] : 0;      // (of the threads below `evicted`)
+    const bool have = word != kNoEntry, agent = have && (word & kOwnPlace) != 0;
+    uint32_t place = word & ~kOwnPlace;
+    if (have && !agent) {
+        moved = p.place[word];
+        place = p.list[word] & ~kOwnPlace;
+    }
+    // (meanwhile: where this workgroup's part of the evicted list begins, and the rows to reset)
+    if (evicted > 0) {
+        uint32_t base = 0;
+#pragma unroll
+        for (int k = 0; k < kMostBefore; ++k) base += unpack3(before[k], 2);
+        base = wave_sum32(base);
+        if (lane_id() == 0) s_base[wave_id()] = base;
+        if (p.r_rows && (int)threadIdx.x < evicted)
+            s_row[threadIdx.x] = evicted_slot >= p.g_num_rows ? evicted_slot % p.g_num_rows : evicted_slot;
+    }
+    const bool refresh = agent || (have && p.ttls && d.evict == 3);
     int64_t slot = 0;
     if (have) {
-        const bool agent = (word & kOwnPlace) != 0;
-        uint32_t place = word & ~kOwnPlace;
-        if (!agent) {
-            moved = p.place[word];
-            place = p.list[word] & ~kOwnPlace;
-        }
         place = moved > place ? moved : place;
         const bool placed = place != 0 && place != kPlaceNone;
         const int64_t home = home_slot(id, d.seed, d.N);
@@ -475,31 +508,24 @@ __global__ __launch_bounds__(kBlock, 8) void k_finalize_chunk(Params p)
         // the claim becomes the id, metadata gets its value (Algorithm 1, Pass 2); without a claim: Case 3, the home
         // slot's metadata is refreshed; with per-feature retention a later copy may ask for a later expiry step
         if (agent && placed) *id_at(d, slot) = id;
-        refresh = agent || (p.ttls && d.evict == 3);
         p.out_slots[pos] = slot;
     }
     store_meta_block(d, refresh, slot, refresh ? meta_value(p, d, pos) : 0, s_merge);
     if (evicted > 0) {
-        // where this workgroup's part of the list begins: the evictions of the workgroups before
-        unsigned long long base = 0;
-        for (int i = threadIdx.x; i < (int)blockIdx.x; i += kBlock) base += unpack3(p.wg_words[3 * i + 2], 2);
-        base = block_sum(base, s_sum);
-        if ((int)threadIdx.x < evicted) {
-            const int64_t s = p.evicted[(int64_t)blockIdx.x * kBlock + threadIdx.x];
-            const int64_t at = (int64_t)base + threadIdx.x;
-            if (at < p.t0.ev_cap) p.out_evicted[at] = s;
-            if (p.r_rows) s_row[threadIdx.x] = s >= p.g_num_rows ? s % p.g_num_rows : s;
-        }
+        __syncthreads();
+        uint32_t base = 0;
+#pragma unroll
+        for (int i = 0; i < kWavesPerBlock; ++i) base += s_base[i];
+        const int64_t at = (int64_t)base + threadIdx.x;
+        if ((int)threadIdx.x < evicted && at < p.t0.ev_cap) p.out_evicted[at] = evicted_slot;
         if (p.r_rows) {
-            __syncthreads();
             // every wavefront resets a quarter of the rows
-            const int per = (evicted + kWavesPerBlock - 1) / kWavesPerBlock, w = threadIdx.x / kWave;
+            const int per = (evicted + kWavesPerBlock - 1) / kWavesPerBlock, w = wave_id();
             const int lo = w * per < evicted ? w * per : evicted;
             const int hi = lo + per < evicted ? lo + per : evicted;
             reset_staged_rows(p, s_row + lo, hi - lo);
         }
     }
-    for (int task = blockIdx.x; task < 3; task += gridDim.x) publish_words(p, task, s_sum);
 }
 
 }  // namespace mpzch
