@@ -288,19 +288,21 @@ int lookup_grid(int64_t n, int num_cus)
     return grid_for(n, two ? 2 * kBlock : kBlock, num_cus, 16);
 }
 
-template <bool TRAIN>
 mpzch_status_t launch_discover(const Params &p, int grid, hipStream_t s)
 {
-    if (TRAIN) {
-        if (p.num_tables > 1 && p.all_records) hipLaunchKernelGGL(k_discover_tables_records, dim3(grid), dim3(kBlock), 0, s, p);
-        else if (p.num_tables > 1) hipLaunchKernelGGL(k_discover_tables, dim3(grid), dim3(kBlock), 0, s, p);
-        else if (p.t0.sh) hipLaunchKernelGGL(k_discover_records, dim3(grid), dim3(kBlock), 0, s, p);
-        else if (p.t0.N >= kStreamingSlots) hipLaunchKernelGGL(k_discover_streaming, dim3(grid), dim3(kBlock), 0, s, p);
-        else hipLaunchKernelGGL(k_discover, dim3(grid), dim3(kBlock), 0, s, p);
-    } else {
-        if (p.num_tables > 1) hipLaunchKernelGGL(k_lookup_tables, dim3(grid), dim3(kBlock), 0, s, p);
-        else hipLaunchKernelGGL(k_lookup, dim3(grid), dim3(kBlock), 0, s, p);
-    }
+    if (p.num_tables > 1 && p.all_records) hipLaunchKernelGGL(k_discover_tables_records, dim3(grid), dim3(kBlock), 0, s, p);
+    else if (p.num_tables > 1) hipLaunchKernelGGL(k_discover_tables, dim3(grid), dim3(kBlock), 0, s, p);
+    else if (p.t0.sh) hipLaunchKernelGGL(k_discover_records, dim3(grid), dim3(kBlock), 0, s, p);
+    else if (p.t0.N >= kStreamingSlots) hipLaunchKernelGGL(k_discover_streaming, dim3(grid), dim3(kBlock), 0, s, p);
+    else hipLaunchKernelGGL(k_discover, dim3(grid), dim3(kBlock), 0, s, p);
+    LAUNCH_CHECK();
+    return MPZCH_OK;
+}
+
+mpzch_status_t launch_lookup(const Params &p, int grid, hipStream_t s)
+{
+    if (p.num_tables > 1) hipLaunchKernelGGL(k_lookup_tables, dim3(grid), dim3(kBlock), 0, s, (lookup_args<true, false>(p, p.seg_chunks)));
+    else hipLaunchKernelGGL(k_lookup, dim3(grid), dim3(kBlock), 0, s, (lookup_args<false, false>(p, p.seg_chunks)));
     LAUNCH_CHECK();
     return MPZCH_OK;
 }
@@ -316,8 +318,10 @@ mpzch_status_t launch_lookup_short(const Params &p, hipStream_t s)
 {
     const int per_block = kBlock >> p.short_shift;
     const int grid = (int)((p.n + per_block - 1) / per_block);
-    if (p.num_tables > 1) hipLaunchKernelGGL((k_lookup_short<true, GATHER>), dim3(grid), dim3(kBlock), 0, s, p);
-    else hipLaunchKernelGGL((k_lookup_short<false, GATHER>), dim3(grid), dim3(kBlock), 0, s, p);
+    if (p.num_tables > 1)
+        hipLaunchKernelGGL((k_lookup_short<true, GATHER>), dim3(grid), dim3(kBlock), 0, s, (lookup_args<true, GATHER>(p, p.short_shift)));
+    else
+        hipLaunchKernelGGL((k_lookup_short<false, GATHER>), dim3(grid), dim3(kBlock), 0, s, (lookup_args<false, GATHER>(p, p.short_shift)));
     LAUNCH_CHECK();
     return MPZCH_OK;
 }
@@ -481,7 +485,7 @@ mpzch_status_t launch_remap(Scratch &sc, Timing &tm, Params p, int32_t max_p_lru
     // per compute unit; of the form for several tables, with 66 registers, one is resident at a time.)
     const int g_grp = grid_for((int64_t)p.num_segs, kFinalizeWaves, sc.num_cus, 2);
 
-    TIMED(tm, KDiscover, s, (launch_discover<true>(p, g_disc, s)));
+    TIMED(tm, KDiscover, s, launch_discover(p, g_disc, s));
     TIMED(tm, KAllocate, s, launch_allocate(max_p_lru, p, sc.num_cus, s));
     TIMED(tm, KFinalize, s, launch_finalize(p, g_grp, s));
     return MPZCH_OK;
@@ -869,7 +873,7 @@ mpzch_status_t mpzch_lookup(const mpzch_table_t *t, const int64_t *identities,
     const int grid = lookup_grid(n, num_cus);
     p.num_segs = grid * kWavesPerBlock;
     p.seg_chunks = (int32_t)(((n + kWave - 1) / kWave + p.num_segs - 1) / p.num_segs);
-    TIMED(t->tm, KLookup, s, (launch_discover<false>(p, grid, s)));
+    TIMED(t->tm, KLookup, s, launch_lookup(p, grid, s));
     return MPZCH_OK;
 }
 
@@ -1035,7 +1039,7 @@ mpzch_status_t mpzch_lookup_gather(const mpzch_table_t *t, const int64_t *identi
     p.num_segs = grid * kWavesPerBlock;
     p.seg_chunks = (int32_t)(((n + kWave - 1) / kWave + p.num_segs - 1) / p.num_segs);
     if (!t->tm.begin(KLookup, s)) return MPZCH_ERR_HIP;
-    hipLaunchKernelGGL(k_lookup_gather, dim3(grid), dim3(kBlock), 0, s, p);
+    hipLaunchKernelGGL(k_lookup_gather, dim3(grid), dim3(kBlock), 0, s, (lookup_args<false, true>(p, p.seg_chunks)));
     LAUNCH_CHECK();
     if (!t->tm.end(s)) return MPZCH_ERR_HIP;
     return MPZCH_OK;
@@ -1243,7 +1247,7 @@ mpzch_status_t mpzch_lookup_jagged(mpzch_group_t *g, const int64_t *const *ident
     const int grid = lookup_grid(total_values, g->sc.num_cus);
     p.num_segs = grid * kWavesPerBlock;
     p.seg_chunks = (int32_t)(((total_values + kWave - 1) / kWave + p.num_segs - 1) / p.num_segs);
-    TIMED(g->tm, KLookup, s, (launch_discover<false>(p, grid, s)));
+    TIMED(g->tm, KLookup, s, launch_lookup(p, grid, s));
     return MPZCH_OK;
 }
 
