@@ -318,10 +318,14 @@ mpzch_status_t launch_lookup_short(const Params &p, hipStream_t s)
 {
     const int per_block = kBlock >> p.short_shift;
     const int grid = (int)((p.n + per_block - 1) / per_block);
-    if (p.num_tables > 1)
-        hipLaunchKernelGGL((k_lookup_short<true, GATHER>), dim3(grid), dim3(kBlock), 0, s, (lookup_args<true, GATHER>(p, p.short_shift)));
-    else
-        hipLaunchKernelGGL((k_lookup_short<false, GATHER>), dim3(grid), dim3(kBlock), 0, s, (lookup_args<false, GATHER>(p, p.short_shift)));
+    if constexpr (!GATHER) {
+        if (p.num_tables > 1) {
+            hipLaunchKernelGGL((k_lookup_short<true, false>), dim3(grid), dim3(kBlock), 0, s, (lookup_args<true, false>(p, p.short_shift)));
+            LAUNCH_CHECK();
+            return MPZCH_OK;
+        }
+    }
+    hipLaunchKernelGGL((k_lookup_short<false, GATHER>), dim3(grid), dim3(kBlock), 0, s, (lookup_args<false, GATHER>(p, p.short_shift)));
     LAUNCH_CHECK();
     return MPZCH_OK;
 }

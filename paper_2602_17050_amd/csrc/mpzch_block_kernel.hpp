@@ -62,7 +62,7 @@ __global__ __launch_bounds__(kOneBlock) void k_remap_block(Params p)
         const bool need = valid && res == kProbeGoOn && q < d.P;
         if (!__any(need)) break;
         bool f = false;
-        const int got = probe_more<false, REC>(d, id, home, q, left, need, s_probe, s.code[w], p.step, &f);
+        const int got = probe_more<false, REC>(d, d.sh, slots_up_to_widest(d), id, home, q, left, need, s_probe, s.code[w], p.step, &f);
         if (need) { res = got; fresh = f; }
     }
     const bool hit = valid && res >= 0, miss = valid && res < 0;

@@ -187,7 +187,7 @@ __global__ __launch_bounds__(kBlock << SHIFT, 4) void k_discover_chunk(Params p)
         const bool need = valid && res == kProbeGoOn && q < d.P;
         if (!__any(need)) break;
         bool f = false;
-        const int got = probe_more<false, REC>(d, id, home, q, left, need, s_req[w], s_code[w], p.step, &f);
+        const int got = probe_more<false, REC>(d, d.sh, slots_up_to_widest(d), id, home, q, left, need, s_req[w], s_code[w], p.step, &f);
         if (need) { res = got; fresh = f; }
     }
     const bool hit = valid && res >= 0, miss = valid && res < 0;

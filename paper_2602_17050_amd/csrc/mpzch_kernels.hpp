@@ -337,6 +337,12 @@ __device__ __forceinline__ Tab view(const TableDesc &d)
 // registers (a descriptor loaded from memory arrives in vector registers: the kernels also store to
 // global memory, so the load cannot be a scalar one).
 __device__ __forceinline__ int32_t uniform32(int32_t v) { return __builtin_amdgcn_readfirstlane(v); }
+__device__ __forceinline__ int64_t readlane64(int64_t v, int lane)
+{
+    const uint32_t lo = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(uint64_t)v, lane);
+    const uint32_t hi = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)((uint64_t)v >> 32), lane);
+    return (int64_t)(((uint64_t)hi << 32) | lo);
+}
 __device__ __forceinline__ int64_t uniform64(int64_t v)
 {
     const uint32_t lo = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)(uint64_t)v);
@@ -643,29 +649,37 @@ __device__ __forceinline__ int blocks_shift(int count, int left)
 // sees per round trip (8 slots, up to 64 when 8 lanes or fewer are left; a window at 95 % load is often longer than
 // 8 slots).  q is moved on past the slots that were looked at; left: how many rounds any of the lanes has left, as far as
 // is known (blocks past the end of every window are lines read for nothing).  The slots of one request lie side by side: a window that
-// goes on at the table's start does so in the next pass.
+// goes on at the table's start does so in the next pass.  The lanes may be of several tables, d being each one's own, if
+// these have kWidest slots or more; sh: the layout, the same for all of them; slots: the table's slots, or kWidest if it
+// has more.
+constexpr int kWidest = 64;
+__device__ __forceinline__ int slots_up_to_widest(const Tab &d) { return d.N < kWidest ? (int)d.N : kWidest; }
 template <bool NT = false, bool REC = false>
-__device__ __forceinline__ int probe_more(const Tab &d, int64_t id, int64_t home, int &q, int &left, bool need,
-                                          ProbeReq *s_req, uint8_t *s_code, int32_t fresh_meta = 0, bool *fresh = nullptr)
+__device__ __forceinline__ int probe_more(const Tab &d, int sh, int slots, int64_t id, int64_t home, int &q, int &left,
+                                          bool need, ProbeReq *s_req, uint8_t *s_code, int32_t fresh_meta = 0,
+                                          bool *fresh = nullptr)
 {
     constexpr int G = 8;
     const int lane = lane_id();
     const uint64_t nm = __ballot(need);
     const int requests = uniform32(__popcll(nm));
     int m = blocks_shift(requests, left);
-    if (d.N < 8 * G) m = d.N < 2 * G ? 0 : d.N < 4 * G ? (m < 1 ? m : 1) : (m < 2 ? m : 2);
-    const int width = d.N < G ? (int)d.N : G << m;                          // slots of a request
+    if (slots < kWidest) m = slots < 2 * G ? 0 : slots < 4 * G ? (m < 1 ? m : 1) : (m < 2 ? m : 2);
+    const int width = slots < G ? slots : G << m;                           // slots of a request
     const int at = lanes_below(nm);
-    const int64_t slot = need ? wrap(home + q, d.N) : 0;
+    const int64_t slot = wrap(home + q, d.N);
     const int64_t last = d.N - width;
     const int64_t first = slot < last ? slot : last;
     const int o = (int)(slot - first);
     const int count = d.P - q < width - o ? d.P - q : width - o;           // rounds among them
-    // (what nobody asks for: any slot that is there)
-    s_req[need ? at : requests + lane - at] = ProbeReq{id, (uint64_t)(uintptr_t)(int64_t *)id_at(d, first)};
+    // What nobody asks for is read where the first of them reads.  (Not in this lane's own table: it may be one of those
+    // with fewer slots than a request is wide.)
+    const uint64_t where = (uint64_t)(uintptr_t)(int64_t *)(d.I + (first << sh));
+    const uint64_t there = (uint64_t)readlane64((int64_t)where, __ffsll((unsigned long long)nm) - 1);
+    s_req[need ? at : requests + lane - at] = ProbeReq{id, need ? where : there};
     __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
     const int r = lane & ((G << m) - 1);                                    // this lane's slot of its request
-    probe_blocks<NT, REC>(s_req, s_code, m, requests << m, (uint32_t)(r < width ? r : width - 1) << (3 + d.sh), fresh_meta);
+    probe_blocks<NT, REC>(s_req, s_code, m, requests << m, (uint32_t)(r < width ? r : width - 1) << (3 + sh), fresh_meta);
     const bool moved = __any(need && o != 0);
     int found = kProbeGoOn;
     if (need) {
@@ -928,7 +942,7 @@ __device__ __forceinline__ void discover_body(const Params &p)
                 const bool need = have && dist < 0 && mlen == 0 && q < d.P;
                 if (!__any(need)) break;
                 bool got_fresh = false;
-                const int got = probe_more<NT, REC>(d, id, home, q, left, need, s_req[w], s_code[w], p.step, &got_fresh);
+                const int got = probe_more<NT, REC>(d, d.sh, slots_up_to_widest(d), id, home, q, left, need, s_req[w], s_code[w], p.step, &got_fresh);
                 if (need) {
                     if (got >= 0) { dist = got; fresh = got_fresh; }
                     else if (got <= kProbeAbsent) mlen = absent_len(got);   // an empty slot ends the search
@@ -1140,6 +1154,9 @@ __global__ __launch_bounds__(kBlock, 4) void k_lookup_tables(LookupArgs<true, fa
 constexpr int64_t kShortBlocks = (int64_t)1 << 18;
 constexpr int window_shift(int P) { return P <= 8 ? 0 : P <= 16 ? 1 : P <= 32 ? 2 : 3; }
 
+// Several tables: a wavefront's ids are looked up together whatever their tables, each lane with its own (tables of one
+// layout at a time, and those of fewer slots than a request is wide one by one).  One table after the other was a chain
+// of its own for each, 1.1 us: 26 ids over 26 tables 32 -> 4 us, 10 K values over them 5.1 -> 3.8.
 template <bool MULTI, bool GATHER>
 __global__ __launch_bounds__(kBlock, 4) void k_lookup_short(LookupArgs<MULTI, GATHER> a)
 {
@@ -1149,36 +1166,43 @@ __global__ __launch_bounds__(kBlock, 4) void k_lookup_short(LookupArgs<MULTI, GA
     __shared__ TableDesc s_desc[MULTI ? kMaxTables : 1];
     const int lane = lane_id(), w = wave_id();
     const int per = kWave >> p.short_shift;                      // ids of a wavefront
-    const int64_t pos = ((int64_t)blockIdx.x * kWavesPerBlock + w) * per + lane;
+    const int64_t pos0 = ((int64_t)blockIdx.x * kWavesPerBlock + w) * per, pos = pos0 + lane;
     bool todo = lane < per && pos < p.n;
     const int64_t id = todo ? p.ids[pos] : -1;
-    int64_t lane_offset = 0;
     Tab d = view(p.t0);
+    int f = 0;
     if constexpr (MULTI) {
-        lane_offset = table_offsets(p.offsets, p.num_tables);
+        const int64_t lane_offset = table_offsets(p.offsets, p.num_tables);
         const uint64_t *src = reinterpret_cast<const uint64_t *>(p.descs);
         uint64_t *dst = reinterpret_cast<uint64_t *>(s_desc);
         for (int i = threadIdx.x; i < p.num_tables * (int)(sizeof(TableDesc) / 8); i += kBlock) dst[i] = src[i];
         __syncthreads();
+        f = find_table_wave(lane_offset, pos0);
+        for (int k = f + 1; k < p.num_tables; ++k) {
+            const int64_t begin = readlane64(lane_offset, k);
+            if (begin >= pos0 + per) break;
+            if (begin <= pos) f = k;
+        }
+        d = view(s_desc[f]);
     }
-    // one table after the other where the ids straddle a feature boundary
+    const int64_t home = home_slot(id, d.seed, d.N);
     while (__any(todo)) {
         bool mine = todo;
+        int sh = d.sh, slots = slots_up_to_widest(d);
         if constexpr (MULTI) {
-            const int64_t upos = pos - lane + __ffsll((unsigned long long)__ballot(todo)) - 1;
-            const int f = find_table_wave(lane_offset, upos);
-            int64_t hi = shfl64(lane_offset, (f + 1) & (kWave - 1));
-            if (f == p.num_tables - 1 || hi <= upos) hi = f == p.num_tables - 1 ? p.n : upos + 1;     // (finite whatever the offsets hold)
-            mine = todo && pos < hi;
-            d = uniform(view(s_desc[f]));
+            const int head = __ffsll((unsigned long long)__ballot(todo)) - 1;
+            sh = __builtin_amdgcn_readlane(d.sh, head);
+            const int of_head = __builtin_amdgcn_readlane(slots, head);
+            mine = todo && (of_head < kWidest ? f == __builtin_amdgcn_readlane(f, head) : slots == kWidest && d.sh == sh);
+            slots = of_head;
         }
         const bool valid = mine && id >= 0;
-        const int64_t home = home_slot(id, d.seed, d.N);
-        int res = kProbeGoOn, q = 0, left = d.P;
+        int res = kProbeGoOn, q = 0;
+        int left = p.short_shift == 3 ? 1 << 30 : kFirstG << p.short_shift;
         for (;;) {
             const bool need = valid && res == kProbeGoOn && q < d.P;
             if (!__any(need)) break;
-            const int got = probe_more<false, false>(d, id, home, q, left, need, s_req[w], s_code[w]);
+            const int got = probe_more<false, false>(d, sh, slots, id, home, q, left, need, s_req[w], s_code[w]);
             if (need) res = got;
         }
         const bool hit = valid && res >= 0;

@@ -327,3 +327,24 @@ def test_jagged_row_reset_in_one_launch():
     assert sts[4]["evictions"] == 0                                   # eviction off: its rows stay as they were
     assert np.array_equal(jp.emb_o[4], wl.embedding_pattern(300, 4, np.float32))
     jp.close()
+
+
+# A wavefront of a short lookup looks up ids of several tables together: both layouts, tables of fewer slots than a request
+# is wide, windows of every length, empty features and features of one value, more features than a wavefront has ids.
+@pytest.mark.parametrize("tables,longest", [(2, 8), (7, 16), (26, 32), (64, 300), (64, 64)])
+def test_short_lookups_across_features(tables, longest):
+    rng = np.random.Generator(np.random.Philox(key=9130 + tables + longest))
+    sizes = [1, 3, 7, 8, 40, 63, 64, 65, 1_000, 5_003, 200_003]
+    specs = [wl.TableSpec(sizes[int(rng.integers(0, len(sizes)))], longest if f == 0 else int(rng.integers(1, longest + 1)), 1,
+                          True, 700 + f) for f in range(tables)]
+    jp = JaggedPair(specs, records=tuple(f for f in range(tables) if rng.random() < 0.4))
+    counts = [int(rng.integers(1, 2 * min(s.num_slots, 2_000) + 2)) for s in specs]
+    fill = np.concatenate([wl.rank_to_id(rng.integers(0, 3 * s.num_slots, size=c)) for s, c in zip(specs, counts)]).astype(np.int64)
+    jp.step(fill, np.concatenate([[0], np.cumsum(counts)]).astype(np.int64), 1)
+    for most in (1, 2, 5, 90):
+        counts = [int(rng.integers(0, most + 1)) for _ in specs]
+        counts[int(rng.integers(0, tables))] = most
+        values = np.concatenate([wl.rank_to_id(rng.integers(0, 3 * s.num_slots, size=c)) for s, c in zip(specs, counts)]).astype(np.int64)
+        values[rng.random(values.size) < 0.05] = -7
+        jp.lookup(values, np.concatenate([[0], np.cumsum(counts)]).astype(np.int64))
+    jp.close()
