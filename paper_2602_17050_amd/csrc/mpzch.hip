@@ -486,7 +486,7 @@ mpzch_status_t launch_remap(Scratch &sc, Timing &tm, Params p, int32_t max_p_lru
     p.num_segs = g_disc * kWavesPerBlock;
     p.seg_chunks = (int32_t)((num_chunks + p.num_segs - 1) / p.num_segs);
     // the other kernels walk the segments' miss lists, one segment per wavefront pass.  (Two workgroups of 16 wavefronts
-    // per compute unit; of the form for several tables, with 66 registers, one is resident at a time.)
+    // per compute unit.)
     const int g_grp = grid_for((int64_t)p.num_segs, kFinalizeWaves, sc.num_cus, 2);
 
     TIMED(tm, KDiscover, s, launch_discover(p, g_disc, s));

@@ -1980,7 +1980,7 @@ __device__ __forceinline__ bool finalize_epilogue(const Params &p, FinalizeState
         const unsigned long long vals[3] = {fs.st_ins, fs.st_evi, fs.st_col};
         block_stat_add(p, idx, vals, 3, fs.st_table, s_red, s_tab);
     }
-    if (multi && total > 0 && !same) flush_evicted(p, s_ev[w], s_row[w], fs.ev_cnt, fs.ev_table);
+    if (multi && total > 0 && !same) flush_evicted(p, s_ev[w], s_row[0], fs.ev_cnt, fs.ev_table);
     const bool reserve = total > 0 && (same || !multi);
     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
     __syncthreads();
@@ -2021,7 +2021,7 @@ template <bool MULTI>
 __device__ __forceinline__ void finalize_body(const Params &p)
 {
     __shared__ int64_t s_ev[kFinalizeWaves][kEvBuf];
-    __shared__ int64_t s_row[kFinalizeWaves][kEvBuf];              // fused row reset: the rows of the staged slots
+    __shared__ int64_t s_row[MULTI ? 1 : kFinalizeWaves][kEvBuf];  // fused row reset (one table): the rows of the staged slots
     __shared__ unsigned long long s_red[kFinalizeWaves][kStatCount];
     __shared__ unsigned long long s_bins[MULTI ? kMaxTables : 1][kStatCount];
     __shared__ int s_cnt[kFinalizeWaves];
@@ -2140,7 +2140,7 @@ __device__ __forceinline__ void finalize_body(const Params &p)
                 }
                 p.out_slots[pos] = s_final;
             }
-            finalize_account<MULTI>(p, fs, s_ev[w], s_row[w], agent, outcome, s_final, f, want_stats);
+            finalize_account<MULTI>(p, fs, s_ev[w], s_row[MULTI ? 0 : w], agent, outcome, s_final, f, want_stats);
         }
     }
     if constexpr (!MULTI) {
@@ -2152,14 +2152,15 @@ __device__ __forceinline__ void finalize_body(const Params &p)
     if (last) publish_counters<kFinalizeBlock>(p, s_bins);
 }
 
-// The single-table form is held to 8 wavefronts per SIMD (50 registers, 66 KB of LDS for 16 wavefronts): its 8 192
-// wavefronts, each a chain of three round trips, then run in one go.  (The form for several tables has 66 registers, seven
-// wavefronts per SIMD, so that one workgroup of 16 is resident per compute unit and the grid runs in two turns.)  A batch of 4 M positions, 10 % of them new, with
+// Held to 8 wavefronts per SIMD (one table: 50 registers and 66 KB of LDS for 16 wavefronts, several: 63 and 40 KB), so that
+// the 8 192 wavefronts, each a chain of three round trips, run in one go.  (Several tables with 66 registers and the rows'
+// buffer that only one table has use for: one workgroup per compute unit and two turns, 41 M values over 26 tables 152 -> 145
+// us.)  A batch of 4 M positions, 10 % of them new, with
 // the row reset: 56 -> 46 us by the ids in the miss lists (a line read for each of them before), one store for id and
 // metadata of a record, and rows reset before the workgroup's barrier instead of behind it; 41 M values over 26 tables
 // 242 -> 178 us.
 template <bool MULTI>
-__global__ __launch_bounds__(kFinalizeBlock, MULTI ? 4 : 8) void k_finalize(Params p)
+__global__ __launch_bounds__(kFinalizeBlock, 8) void k_finalize(Params p)
 {
     finalize_body<MULTI>(p);
 }
