@@ -144,10 +144,9 @@ __global__ __launch_bounds__(kOneBlock) void k_remap_block(Params p)
     for (;;) {
         const uint64_t am = __ballot(cl.active);
         if (!am) break;
-        const int m = blocks_shift(__popcll(am), d.P);
-        const int row = claim_blocks<false, REC>(d, d, cl, am, m, bound, false, s.code[w], s.req[w]);
+        const ClaimStage st = claim_blocks<REC>(d, cl, am, blocks_shift(uniform32(__popcll(am)), d.P), bound, false, s.code[w], s.req[w]);
         if (cl.active)
-            claim_walk(d, cl, m, row, s.code[w], s.req[w], claim_in_map,
+            claim_walk(d, cl, st, s.code[w], s.req[w], claim_in_map,
                        [&](uint32_t who, int32_t round, int64_t at, int64_t old) {
                            atomicMax(&s.place[who], (uint32_t)round + 1u);
                            outcome = old == -1 ? 1u : old >= 0 ? 2u : 0u;

@@ -268,7 +268,7 @@ __global__ __launch_bounds__(kBlock, 4) void k_allocate_chunk(Params p)
     __shared__ ClaimReq s_req[kWavesPerBlock][kWave];
     __shared__ uint32_t s_red[kWavesPerBlock][3];
 
-    const int w = threadIdx.x / kWave;
+    const int w = wave_id();
     const int64_t pos = (int64_t)blockIdx.x * kBlock + threadIdx.x;
     const bool in = pos < p.n;
     const Tab d = view(p.t0);
@@ -293,11 +293,11 @@ __global__ __launch_bounds__(kBlock, 4) void k_allocate_chunk(Params p)
     for (bool later = false;; later = true) {
         const uint64_t am = __ballot(c.active);
         if (!am) break;
-        const int m = later || !aligned ? blocks_shift(__popcll(am), d.P) : 0;
-        const int row = claim_blocks<false, REC>(d, d, c, am, m, bound, aligned, s_code[w], s_req[w]);
+        const ClaimStage st = claim_blocks<REC>(d, c, am, later || !aligned ? blocks_shift(uniform32(__popcll(am)), d.P) : 0, bound,
+                                                aligned && !later, s_code[w], s_req[w]);
         if (!later) c.active = c.active && first == (uint32_t)pos;      // else: a later copy of the id
         if (c.active)
-            claim_walk(d, c, m, row, s_code[w], s_req[w], claim_in_table,
+            claim_walk(d, c, st, s_code[w], s_req[w], claim_in_table,
                        [&](uint32_t who, int32_t round, int64_t at, int64_t old) {
                            if (who == (uint32_t)pos) own = (uint32_t)round + 1u;
                            else note_place(p, who, (uint32_t)round + 1u);

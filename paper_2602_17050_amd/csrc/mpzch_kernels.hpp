@@ -1246,16 +1246,13 @@ constexpr uint32_t kHintUnknown = 0xFD;    // placed, but not at a round that fi
 // that position itself, kAgentEntry | hint.
 constexpr uint32_t kAgentEntry = 0x80000000u;
 
-// What the lanes that load a block of a claimant's window need to know: the address of the identity of its first
-// slot (bits 0..47; bits 48..51: how many slots to look at, bit 52: records), the address of that slot's metadata, the
-// value below which metadata is expired, and the claim: the claimant's position and the round of the block's first slot.
+// What a claimant's lane leaves in LDS for the lanes that load for it: the address of the identity of the first slot to
+// read, that slot's number, and the claim: the claimant's position and the round that the first slot would be for it.
 struct alignas(16) ClaimReq {
-    uint64_t first;
-    uint64_t meta;
-    int32_t bound;
+    uint64_t where;
+    int64_t slot;
+    int32_t round;
     uint32_t pos;
-    uint32_t round;
-    uint32_t unused;
 };
 
 // The TTL test of Sec. 3.4 on a slot that holds an id: expired <=> metadata < bound
@@ -1266,7 +1263,7 @@ __device__ __forceinline__ int32_t expiry_bound(const Tab &d, int32_t step)
     return (int32_t)0x80000000;
 }
 
-// Blocks.  They are aligned: a claimant placed in the block of its home slot -- nearly every one, in a table with room
+// Blocks.  The first one is aligned: a claimant placed in the block of its home slot -- nearly every one, in a table with room
 // or with expired ids -- costs the memory system one line (8 slots counted from the home slot straddle two in seven
 // of eight cases; 1 B slots of records, 345 K claimants: 51.5 -> 37 us).  In a table that the memory-side cache holds,
 // lines are cheap and round trips are what counts: there a block is simply the next 8 slots.
@@ -1287,119 +1284,147 @@ __device__ __forceinline__ int64_t claim_in_table(uint64_t address, int64_t tag,
     return __hip_atomic_fetch_min((global_ptr<int64_t>)(uintptr_t)address, tag, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
-// One stage: reads the next 1 << m blocks of every active claimant's window (am: who is active) and leaves in s_code
-// what may be claimed, in rows `row` (returned) and following of 8 bytes each.  d: the table of this lane's
-// claimant; d0: any table of the call.
-template <bool MULTI, bool REC>
-__device__ __forceinline__ int claim_blocks(const Tab &d, const Tab &d0, const Claimant &c, uint64_t am, int m, int32_t bound,
-                                            bool aligned, uint8_t *s_code, ClaimReq *s_req)
+// The loads of one stage, T for each lane.  As in probe_rows every lane adds a constant to its request's address and nothing
+// is asked per slot (51 calls of 65 536 positions 1 026 -> 1 006 us, 12 of 262 144 792 -> 775, 8 of 1 024 90 -> 85).  What the
+// claimant's lane needs to know of a slot goes to s_code, one byte: 1 = it may be claimed (empty, holds an expired id, or a
+// worse claim), 2 = it held an id when the call began, 4 = it is claimed already.
+template <int T, bool REC>
+__device__ __forceinline__ void claim_rows(const Tab &d, const ClaimReq *req, int next, uint8_t *s_code, int slot_of_request, bool in,
+                                           int32_t bound)
 {
-    constexpr int G = kAllocG;
-    constexpr int APL = kWave / G;                   // blocks served by one load instruction
-    constexpr int NT = kWave / APL;                  // load instructions per stage
-    const int lane = lane_id();
-    const int g = lane / G, r = lane % G;
-    const int row = m == 0 ? lane : __popcll(am & ((1ull << lane) - 1ull)) << m;
-    if (m > 0 || !c.active)
-        s_req[lane] = ClaimReq{(uint64_t)(uintptr_t)(int64_t *)d.I, (uint64_t)(uintptr_t)(int32_t *)d.M, bound, 0, 0, 0};
-    if (m > 0) __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-    if (c.active) {
-        int qj = c.q;
-        for (int j = 0; j < (1 << m); ++j) {
-            // the slots from round qj on that lie in one block, in the window and before the table's end
-            const int64_t s0 = qj < d.P ? wrap(c.home + qj, d.N) : 0;
-            int count = aligned ? G - block_offset(d, s0, G) : G;
-            if (count > d.P - qj) count = d.P - qj;
-            if ((int64_t)count > d.N - s0) count = (int)(d.N - s0);
-            s_req[row + j] = ClaimReq{(uint64_t)(uintptr_t)(int64_t *)id_at(d, s0) | ((uint64_t)(uint32_t)count << kWhereAddrBits) |
-                                          ((uint64_t)(uint32_t)d.sh << (kWhereAddrBits + 4)),
-                                      (uint64_t)(uintptr_t)(int32_t *)meta_at(d, s0), bound, c.pos, (uint32_t)qj, 0};
-            qj += count;
-        }
-    }
-    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-    int64_t vi[NT];
-    int32_t vm[NT];
+    int64_t v[T];
+    int32_t meta[T];
+    const uint32_t id_bytes = (uint32_t)slot_of_request << (3 + d.sh);
+    asm volatile("" ::"i"(T) : "memory");          // (see probe_rows)
 #pragma unroll
-    for (int t = 0; t < NT; ++t) {
-        const ClaimReq &rq = s_req[t * APL + g];
-        const uint64_t first_slot = rq.first;
-        // lanes without a slot to look at read the block's first one
-        const uint64_t k = r < (int)((first_slot >> kWhereAddrBits) & 15u) ? (uint64_t)r : 0ull;
-        const uint64_t a = first_slot & ((1ull << kWhereAddrBits) - 1ull);
+    for (int t = 0; t < T; ++t) {
+        const uint64_t a = req[t * next].where + id_bytes;
         if constexpr (REC) {
-            const u32x3 rec = *(global_ptr<u32x3>)(uintptr_t)(a + k * 16);
-            vi[t] = (int64_t)(((uint64_t)rec.y << 32) | rec.x);
-            vm[t] = (int32_t)rec.z;
+            const u32x3 rec = *(global_ptr<u32x3>)(uintptr_t)a;
+            v[t] = (int64_t)(((uint64_t)rec.y << 32) | rec.x);
+            meta[t] = (int32_t)rec.z;
         } else {
-            const int sh = MULTI ? (int)(first_slot >> (kWhereAddrBits + 4)) & 1 : d0.sh;
-            vi[t] = *(global_ptr<int64_t>)(uintptr_t)(a + (k << (3 + sh)));
-            vm[t] = 0;
-            if (MULTI || d0.evict != 0) vm[t] = *(global_ptr<int32_t>)(uintptr_t)(rq.meta + (k << (2 + 2 * sh)));
+            v[t] = *(global_ptr<int64_t>)(uintptr_t)a;
         }
     }
-    // what the claimant's lane needs to know of a slot, one byte: 1 = it may be claimed (empty, holds an
-    // expired id, or a worse claim), 2 = it held an id when the call began, 4 = it is claimed already
+    if constexpr (!REC) {
 #pragma unroll
-    for (int t = 0; t < NT; ++t) {
-        const ClaimReq &rq = s_req[t * APL + g];
-        const int64_t v = vi[t];
-        uint32_t occ = v >= 0 ? 1u : 0u;
-        bool cand = v < 0 || vm[t] < (MULTI ? rq.bound : bound);
-        if (is_tag(v)) {
-            occ = tag_occ(v);
-            cand = v > make_tag(rq.round + (uint32_t)r, rq.pos, occ);
+        for (int t = 0; t < T; ++t) meta[t] = 0;
+        if (d.evict != 0) {
+#pragma unroll
+            for (int t = 0; t < T; ++t) meta[t] = *meta_at(d, req[t * next].slot + slot_of_request);
         }
-        const bool in = r < (int)((rq.first >> kWhereAddrBits) & 15u);
-        s_code[(t * APL + g) * G + r] = (uint8_t)(in ? (cand ? 1u : 0u) | (occ << 1) | (is_tag(v) ? 4u : 0u) : 0u);
     }
-    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-    return row;
+    uint32_t code[T];
+    uint64_t tags = 0;
+#pragma unroll
+    for (int t = 0; t < T; ++t) {
+        code[t] = v[t] < 0 ? 1u : meta[t] < bound ? 3u : 2u;
+        tags |= __ballot(is_tag(v[t]));
+    }
+    if (tags) {                                    // (hardly ever in the first stage)
+#pragma unroll
+        for (int t = 0; t < T; ++t) {
+            const uint32_t occ = tag_occ(v[t]);
+            const bool worse = v[t] > make_tag((uint32_t)(req[t * next].round + slot_of_request), req[t * next].pos, occ);
+            if (is_tag(v[t])) code[t] = 4u | (occ << 1) | (worse ? 1u : 0u);
+        }
+    }
+#pragma unroll
+    for (int t = 0; t < T; ++t) s_code[t * kWave] = in ? (uint8_t)code[t] : (uint8_t)0;
 }
 
-// The claimant's lane walks the blocks of the stage and claims.  A claimant that it displaces is carried on at once, from
-// the next slot of the same blocks (its next round is that slot: displaced at round r of slot s its home is s - r, and
-// what the block says of empty and expired slots holds for it too; claimed ones it tries) -- a displacement costs the
+// One stage: reads the next slots of every active claimant's window (am: who is active), 8 << m of them side by side, the
+// first ones from the claimant's next round on or, with `aligned`, in the aligned block that holds it.  d is wave-uniform.
+// What may be claimed goes to s_code, a byte per slot, 8 << m for each claimant in the order of the lanes.
+struct ClaimStage {
+    int m;                                           // 8 << m slots per claimant
+    int width;                                       // of these, how many there are (all but in tables of fewer than 8 slots)
+    int at;                                          // number of this lane's claimant
+    int skip;                                        // its first slot is the skip-th that was read
+};
+template <bool REC>
+__device__ __forceinline__ ClaimStage claim_blocks(const Tab &d, const Claimant &c, uint64_t am, int m, int32_t bound, bool aligned,
+                                                   uint8_t *s_code, ClaimReq *s_req)
+{
+    constexpr int G = kAllocG;
+    const int lane = lane_id();
+    const int slots = slots_up_to_widest(d);
+    if (slots < kWidest) m = slots < 2 * G ? 0 : slots < 4 * G ? (m < 1 ? m : 1) : (m < 2 ? m : 2);
+    ClaimStage st;
+    st.m = m;
+    st.width = slots < G ? slots : G << m;
+    st.at = lanes_below(am);
+    const int claimants = uniform32(__popcll(am));
+    const int64_t slot = c.active ? wrap(c.home + c.q, d.N) : 0;
+    const int64_t last = d.N - st.width;
+    int64_t first = slot;
+    if (aligned) {
+        first -= block_offset(d, slot, G);
+        first = first > 0 ? first : 0;
+    }
+    first = first < last ? first : last;
+    st.skip = (int)(slot - first);
+    const ClaimReq rq{(uint64_t)(uintptr_t)(int64_t *)id_at(d, first), first, c.q - st.skip, c.pos};
+    s_req[c.active ? st.at : claimants + lane - st.at] = rq;        // (what nobody asks for: slots that are there)
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    const int r = lane & ((G << m) - 1), rows = claimants << m;
+    const bool in = r < st.width;
+    const ClaimReq *const req = s_req + ((lane / G) >> m);
+    const int next = kWave / G >> m, k = in ? r : st.width - 1;
+    if (rows > 32) claim_rows<8, REC>(d, req, next, s_code + lane, k, in, bound);
+    else if (rows > 16) claim_rows<4, REC>(d, req, next, s_code + lane, k, in, bound);
+    else claim_rows<2, REC>(d, req, next, s_code + lane, k, in, bound);
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    return st;
+}
+
+// The claimant's lane walks the slots of the stage and claims.  A claimant that it displaces is carried on at once, from
+// the next slot of the same stage (its next round is that slot: displaced at round r of slot s its home is s - r, and
+// what was read of empty and expired slots holds for it too; claimed ones it tries) -- a displacement costs the
 // round trip of its atomic and no other.  placed(pos, round, slot, old) is called for every claim that stands, old being
 // what the slot held before; lost(pos) for a claimant that has run out of slots.  On return c is the claimant to go on
 // with, if c.active.
 // claim(address of the identity, tag, whether the slot held an id when the call began) makes the claim and returns what the
 // slot held before.
 template <typename Claim, typename Placed, typename Lost>
-__device__ __forceinline__ void claim_walk(const Tab &d, Claimant &c, int m, int row, const uint8_t *s_code,
+__device__ __forceinline__ void claim_walk(const Tab &d, Claimant &c, const ClaimStage &st, const uint8_t *s_code,
                                            const ClaimReq *s_req, Claim claim, Placed placed, Lost lost)
 {
     constexpr int G = kAllocG;
     constexpr uint64_t kOnes = 0x0101010101010101ull;
+    const uint8_t *const mine = s_code + (st.at << (st.m + 3));
+    const uint64_t where = s_req[st.at].where;
     bool carried = false;
-    for (int j = 0; j < (1 << m); ++j) {
-        const uint64_t word = *reinterpret_cast<const uint64_t *>(s_code + (row + j) * G);
-        const uint64_t rq = s_req[row + j].first;
-        const uint64_t a = rq & ((1ull << kWhereAddrBits) - 1ull);
+    int32_t round0 = c.q - st.skip;                                  // the round that the first slot read is for the claimant
+    int skip = st.skip;
+    for (int j = 0; j < (1 << st.m); ++j, skip -= G) {
+        const uint64_t word = reinterpret_cast<const uint64_t *>(mine)[j];
         uint64_t x = (carried ? word | (word >> 2) : word) & kOnes;
+        if (skip > 0) x = skip < G ? x & (~0ull << (8 * skip)) : 0;
         while (x) {
             const int bit = __ffsll((unsigned long long)x) - 1;
-            const int k = bit >> 3;
+            const int k = G * j + (bit >> 3);
             x &= x - 1;
-            const int32_t round = c.q + k;                           // c.q: the round of the block's first slot
+            const int32_t round = round0 + k;
             if (round >= d.P) break;
             const uint32_t occ = (uint32_t)(word >> (bit + 1)) & 1u;
-            const int64_t mine = make_tag((uint32_t)round, c.pos, occ);
-            const int64_t old = claim(a + ((uint64_t)k << (3 + d.sh)), mine, occ);
-            if (is_tag(old) && old < mine) continue;                 // a better claim got there first
+            const int64_t mine_tag = make_tag((uint32_t)round, c.pos, occ);
+            const int64_t old = claim(where + ((uint64_t)k << (3 + d.sh)), mine_tag, occ);
+            if (is_tag(old) && old < mine_tag) continue;             // a better claim got there first
             const int64_t slot = wrap(c.home + round, d.N);
             placed(c.pos, round, slot, old);
             if (!is_tag(old)) { c.active = false; return; }
             c.pos = tag_pos(old);
             c.home = slot - (int64_t)tag_round(old);
             if (c.home < 0) c.home += d.N;
-            c.q = (int32_t)tag_round(old) - k;
+            round0 = (int32_t)tag_round(old) - k;
             carried = true;
             x = ((word | (word >> 2)) & kOnes) & ~((1ull << bit) | ((1ull << bit) - 1ull));
         }
-        c.q += (int)(rq >> kWhereAddrBits) & 15;
-        if (c.q >= d.P) break;
+        if (round0 + G * (j + 1) >= d.P) break;
     }
+    c.q = round0 + st.width;
     if (c.q >= d.P) {
         c.active = false;
         lost(c.pos);
@@ -1407,7 +1432,8 @@ __device__ __forceinline__ void claim_walk(const Tab &d, Claimant &c, int m, int
 }
 
 // One wavefront serves the segments vblock, vblock + vgrid, ...; s_code and s_req are its own areas of LDS.  REC: every
-// table of the call is kept as records (identity and metadata come with one load).
+// table of the call is kept as records (identity and metadata come with one load).  Several tables: the claimants of one
+// table at a time (nearly always all of them: a segment is a few thousand positions, a feature's share many times that).
 template <bool MULTI, bool REC>
 __device__ __forceinline__ void allocate_body(const Params &p, int64_t vblock, int64_t vgrid,
                                               uint8_t *s_code, ClaimReq *s_req)
@@ -1433,52 +1459,64 @@ __device__ __forceinline__ void allocate_body(const Params &p, int64_t vblock, i
             const int64_t id = p.list_id[idx];
             if (j0 >= cnt) break;
             const bool have = j0 + lane < cnt;
-            bool agent = false;
             uint32_t first = 0;
-            int f = 0;
-            Tab d = d0;
+            int f = seg_f;
             if (have) {
                 first = p.set_slot[e];
-                agent = first == pos;                         // else: a later copy of the id
-                if (MULTI && agent) {
-                    if (seg_one) {
-                        f = seg_f;
-                        d = seg_d;
-                    } else {
-                        f = find_table(p.offsets, p.num_tables, (int64_t)pos);
-                        d = view(p.descs[f]);
+                if (MULTI && !seg_one) f = find_table(p.offsets, p.num_tables, (int64_t)pos);
+            }
+            const bool elected = have && first == pos;        // else: a later copy of the id
+            if (have && !elected) p.first_of[idx] = first;
+            bool todo = elected;
+            while (__any(todo)) {
+                Tab d = seg_d;
+                bool agent = todo;
+                if constexpr (MULTI) {
+                    if (!seg_one) {
+                        const int of_head = __builtin_amdgcn_readlane(f, __ffsll((unsigned long long)__ballot(todo)) - 1);
+                        agent = todo && f == of_head;
+                        d = uniform(view(p.descs[of_head]));
                     }
-                    if (d.evict == 2) agent = false;          // claimants of LRU tables are served by k_allocate_lru
+                    todo = todo && !agent;
+                    // claimants of LRU tables are served by k_allocate_lru
+                    if (d.evict == 2) {
+                        if (agent) p.first_of[idx] = first;
+                        continue;
+                    }
+                } else {
+                    todo = false;
+                }
+                const int32_t bound = expiry_bound(d, p.step);
+                const bool aligned = (d.N << (3 + d.sh)) > kCachedTableBytes;
+                uint32_t hint = kHintUnplaced;
+                // the claimant this lane carries
+                Claimant c;
+                c.active = agent;
+                c.pos = pos;
+                c.q = 0;
+                c.home = home_slot(id, d.seed, d.N);
+                for (bool later = false;; later = true) {
+                    const uint64_t am = __ballot(c.active);
+                    if (!am) break;
+                    // the 64 blocks of a stage are shared out among the claimants that are left (but one block each is
+                    // what nearly every claimant needs at first)
+                    const ClaimStage st = claim_blocks<REC>(d, c, am, later ? blocks_shift(uniform32(__popcll(am)), d.P) : 0, bound,
+                                                            aligned && !later, s_code, s_req);
+                    if (c.active)
+                        claim_walk(d, c, st, s_code, s_req, claim_in_table,
+                                   [&](uint32_t who, int32_t round, int64_t, int64_t) {
+                                       const uint32_t at = round < (int32_t)kHintUnknown ? (uint32_t)round : kHintUnknown;
+                                       if (who == pos) hint = at;
+                                       else p.hint[who] = (uint8_t)at;
+                                   },
+                                   [](uint32_t) {});
+                    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");   // s_code and s_req are written again
+                }
+                if (agent) {
+                    p.hint[pos] = (uint8_t)hint;              // for the copies of the id
+                    p.first_of[idx] = kAgentEntry | hint;
                 }
             }
-            const int32_t bound = expiry_bound(d, p.step);
-            const bool aligned = (d.N << (3 + d.sh)) > kCachedTableBytes;
-            uint32_t hint = kHintUnplaced;
-            // the claimant this lane carries
-            Claimant c;
-            c.active = agent;
-            c.pos = pos;
-            c.q = 0;
-            c.home = home_slot(id, d.seed, d.N);
-            for (bool later = false;; later = true) {
-                const uint64_t am = __ballot(c.active);
-                if (!am) break;
-                // the 64 blocks of a stage are shared out among the claimants that are left (but one block each is
-                // what nearly every claimant needs at first)
-                const int m = later ? blocks_shift(__popcll(am), !MULTI ? d0.P : seg_one ? seg_d.P : 64) : 0;
-                const int row = claim_blocks<MULTI, REC>(d, d0, c, am, m, bound, aligned, s_code, s_req);
-                if (c.active)
-                    claim_walk(d, c, m, row, s_code, s_req, claim_in_table,
-                               [&](uint32_t who, int32_t round, int64_t, int64_t) {
-                                   const uint32_t at = round < (int32_t)kHintUnknown ? (uint32_t)round : kHintUnknown;
-                                   if (who == pos) hint = at;
-                                   else p.hint[who] = (uint8_t)at;
-                               },
-                               [](uint32_t) {});
-                __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");   // s_code and s_req are written again
-            }
-            if (agent) p.hint[pos] = (uint8_t)hint;           // for the copies of the id
-            if (have) p.first_of[idx] = agent ? (kAgentEntry | hint) : first;
             __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
         }
     }
