@@ -42,7 +42,8 @@ __global__ __launch_bounds__(kOneBlock) void k_remap_block(Params p)
     const uint32_t pos = (uint32_t)t;
     const int64_t id = in ? p.ids[t] : -1;
     const bool valid = in && id >= 0;
-    const int64_t home = home_slot(id, d.seed, d.N);
+    const uint64_t hash = hash_of(id, d.seed);
+    const int64_t home = home_of(hash, d.N);
     for (int i = t; i < 2 * threads; i += threads) {
         s.set[i] = kSetEmpty;
         s.claim_slot[i] = 0;
@@ -70,7 +71,7 @@ __global__ __launch_bounds__(kOneBlock) void k_remap_block(Params p)
     uint32_t e = kNoEntry;
     if (miss) {
         const uint32_t size = 2u * (uint32_t)threads;
-        uint32_t at = (uint32_t)__umul64hi(mix64((uint64_t)id ^ kSetSeed), (uint64_t)size);
+        uint32_t at = __umulhi((uint32_t)hash, size);
         for (;;) {
             uint32_t expected = kSetEmpty;
             if (__hip_atomic_compare_exchange_strong(&s.set[at], &expected, pos, __ATOMIC_RELAXED, __ATOMIC_RELAXED,
@@ -109,7 +110,7 @@ __global__ __launch_bounds__(kOneBlock) void k_remap_block(Params p)
     // stands, if only until a better one, so there are no more entries than claimants: at most half of the map.
     auto claim_in_map = [&](uint64_t address, int64_t tag, uint32_t occ) -> int64_t {
         const uint32_t size = 2u * (uint32_t)threads;
-        uint32_t at = (uint32_t)__umul64hi((address >> 3) * 0x9E3779B97F4A7C15ull, (uint64_t)size);
+        uint32_t at = __umulhi((uint32_t)(address >> 3) * 0x9E3779B1u, size);
         for (;;) {
             uint64_t holds = 0;
             if (__hip_atomic_compare_exchange_strong(&s.claim_slot[at], &holds, address, __ATOMIC_RELAXED, __ATOMIC_RELAXED,

@@ -33,7 +33,9 @@ constexpr uint32_t kOwnPlace = 0x80000000u;      // list[pos] of the first occur
 
 // Scratch set of these calls: an entry is the batch position with 12 bits of the id's hash above it, so that two ids that
 // meet in one entry tell each other apart without a look at the batch (a round trip per collision; with every
-// id missed and half of the set full, that was 8 of 40 us for 262 144 ids).  Otherwise as set_insert.
+// id missed and half of the set full, that was 8 of 40 us for 262 144 ids).  Otherwise as set_insert.  The hash is the one
+// that gave the home slot: that takes its highest bits, an entry its low word and the 12 bits above.  (Three hashes per
+// position before: 51 calls of 65 536 positions 1 006 -> 996 us, 8 of 1 024 85 -> 83.)
 //
 // Four entries per position: the GPU performs 27 G atomics/s on memory that its 256 MB cache holds, as it does this set of
 // 8 MB at most (17 to 18 G/s on gigabytes), so where every id is missed the lanes of all wavefronts queue 10 us for their
@@ -44,12 +46,11 @@ constexpr int64_t kChunkMaxBatch = (int64_t)1 << 19;
 constexpr int kChunkPosBits = 20;
 constexpr uint32_t kChunkPosMask = (1u << kChunkPosBits) - 1u;
 
-__device__ __forceinline__ uint32_t set_insert_chunk(const Params &p, int64_t id, uint32_t pos)
+__device__ __forceinline__ uint32_t set_insert_chunk(const Params &p, int64_t id, uint64_t hash, uint32_t pos)
 {
-    const uint64_t h = mix64((uint64_t)id ^ kSetSeed);
     const uint32_t size = (uint32_t)kChunkSetEntries * (uint32_t)p.n;
-    const uint32_t mine = ((uint32_t)h << kChunkPosBits) | pos;
-    uint32_t e = (uint32_t)__umul64hi(h, (uint64_t)size);
+    const uint32_t mine = ((uint32_t)(hash >> 32) << kChunkPosBits) | pos;
+    uint32_t e = __umulhi((uint32_t)hash, size);
     for (;;) {
         uint32_t expected = kSetEmpty;
         if (__hip_atomic_compare_exchange_strong(&p.set_slot[e], &expected, mine, __ATOMIC_RELAXED, __ATOMIC_RELAXED,
@@ -130,10 +131,11 @@ __device__ __forceinline__ void store_meta_block(const Tab &d, bool active, int6
 // LDS) enter it once, with the smallest of their positions: an id that is new and popular at once -- the first batch of a
 // table, of a feature -- otherwise has thousands of atomics on one word, 12 ns each (65 536 positions, the most popular id
 // a fourteenth of them: 67 -> 27 us; over the workgroup instead, 14 us, but the barriers cost every other call 0.7).
-__device__ __forceinline__ uint32_t set_insert_wave(const Params &p, bool miss, int64_t id, uint32_t pos, MetaMerge *s_m)
+__device__ __forceinline__ uint32_t set_insert_wave(const Params &p, bool miss, int64_t id, uint64_t hash, uint32_t pos,
+                                                    MetaMerge *s_m)
 {
     const int lane = lane_id();
-    const int cell = (int)((uint32_t)(mix64((uint64_t)id) >> 58));
+    const int cell = (int)(hash >> 44) & (kWave - 1);
     s_m[lane].slot = miss ? id : -1;
     s_m[lane].value = (int32_t)pos;
     if (miss) s_m[cell].winner = (uint32_t)lane;
@@ -148,7 +150,7 @@ __device__ __forceinline__ uint32_t set_insert_wave(const Params &p, bool miss, 
     }
     __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
     uint32_t e = kNoEntry;
-    if (miss && from == lane) e = set_insert_chunk(p, id, (uint32_t)s_m[lane].value);
+    if (miss && from == lane) e = set_insert_chunk(p, id, hash, (uint32_t)s_m[lane].value);
     return (uint32_t)__shfl((int)e, from);
 }
 
@@ -171,7 +173,8 @@ __global__ __launch_bounds__(kBlock << SHIFT, 4) void k_discover_chunk(Params p)
     const Tab d = view(p.t0);
     const int64_t id = in ? p.ids[pos] : -1;
     const bool valid = in && id >= 0;
-    const int64_t home = home_slot(id, d.seed, d.N);
+    const uint64_t hash = hash_of(id, d.seed);
+    const int64_t home = home_of(hash, d.N);
     bool fresh = false;
     int res = kProbeGoOn, q = 0;
     if constexpr (SHIFT == 0) {
@@ -191,7 +194,7 @@ __global__ __launch_bounds__(kBlock << SHIFT, 4) void k_discover_chunk(Params p)
         if (need) { res = got; fresh = f; }
     }
     const bool hit = valid && res >= 0, miss = valid && res < 0;
-    const uint32_t e = set_insert_wave(p, miss, id, (uint32_t)pos, reinterpret_cast<MetaMerge *>(s_req[w]));
+    const uint32_t e = set_insert_wave(p, miss, id, hash, (uint32_t)pos, reinterpret_cast<MetaMerge *>(s_req[w]));
     const int64_t slot = hit ? wrap(home + res, d.N) : home;
     store_meta_block(d, hit && !(REC && fresh && d.evict != 3), slot, hit ? meta_value(p, d, pos) : 0, s_merge);
     if (in) {

@@ -227,10 +227,9 @@ __device__ __forceinline__ uint64_t mix64(uint64_t x)
     return z ^ (z >> 31);
 }
 
-__device__ __forceinline__ int64_t home_slot(int64_t id, uint64_t seed, int64_t n_slots)
-{
-    return (int64_t)__umul64hi(mix64((uint64_t)id ^ seed), (uint64_t)n_slots);
-}
+__device__ __forceinline__ uint64_t hash_of(int64_t id, uint64_t seed) { return mix64((uint64_t)id ^ seed); }
+__device__ __forceinline__ int64_t home_of(uint64_t hash, int64_t n_slots) { return (int64_t)__umul64hi(hash, (uint64_t)n_slots); }
+__device__ __forceinline__ int64_t home_slot(int64_t id, uint64_t seed, int64_t n_slots) { return home_of(hash_of(id, seed), n_slots); }
 
 // Claim tags live in the identities word while a call is in flight.  They are below every
 // valid id and below the empty marker, and a smaller tag is a better claim.
