@@ -6,7 +6,8 @@
 // phases are those of mpzch_chunk_kernels.hpp.  Remap with row reset, us per call, against three launches: 64 to 512
 // positions 14 to 17.5 -> 7 to 9, 1 024 positions 13.8 to 17.7 -> 7.0 to 12.4; with two positions per thread (2 048) the
 // one compute unit took as long as three launches do (10.8 to 21.8 against 13.8 to 19.2), so the line is drawn at 1 024.
-// The claimants listed and the first look without index arithmetic: the tiny 8-step pass 97.8 -> 93.2 us.
+// (Claimants listed, so that they take up as few wavefronts as they can, 83.9 against 82.6 us for the 8-step pass: a list
+// costs a barrier, and a stage of few claimants loads only the rows they ask for.)
 #pragma once
 #include "mpzch_chunk_kernels.hpp"
 
@@ -20,7 +21,6 @@ struct OneBlockArea {
     alignas(16) uint8_t code[kOneBlockWaves][kWave * kAllocG];
     int64_t id[kOneBlock];
     int64_t row[kOneBlock];                                  // rows to reset
-    uint16_t claimant[kOneBlock];                            // first occurrences of the missed ids
     uint32_t set[2 * kOneBlock];
     uint64_t claim_slot[2 * kOneBlock];                      // claims: address of the slot's identity (0: free entry)
     int64_t claim_tag[2 * kOneBlock];                        // and the best claim of it so far (0: none)
@@ -123,25 +123,17 @@ __global__ __launch_bounds__(kOneBlock) void k_remap_block(Params p)
         return old != 0 ? old : occ ? 0 : -1;
     };
 
-    // claims.  (The one compute unit is busy with instructions, not waiting: the claimants are listed, so that they take
-    // up as few wavefronts as they can.)
+    // claims
     const int32_t bound = expiry_bound(d, p.step);
     const uint32_t first = e != kNoEntry ? s.set[e] : kNoEntry;
     uint32_t outcome = 0;                                    // 1 = this lane's last claim was an insert, 2 = an eviction
     int64_t claimed = 0;
-    {
-        const uint64_t am = __ballot(first == pos);
-        uint32_t at = 0;
-        if (lane == 0 && am) at = atomicAdd(&s.count[kDistinctMiss], (uint32_t)__popcll(am));
-        at = (uint32_t)__builtin_amdgcn_readfirstlane((int)at);
-        if (first == pos) s.claimant[at + (uint32_t)__popcll(am & ((1ull << lane) - 1ull))] = (uint16_t)pos;
-    }
-    __syncthreads();
     Claimant cl;
-    cl.active = t < (int)s.count[kDistinctMiss];
-    cl.pos = cl.active ? s.claimant[t] : 0u;
+    cl.active = first == pos;
+    cl.pos = pos;
     cl.q = 0;
-    cl.home = cl.active ? home_slot(s.id[cl.pos], d.seed, d.N) : 0;
+    cl.home = home;
+    const uint32_t distinct = (uint32_t)__popcll(__ballot(cl.active));
     for (;;) {
         const uint64_t am = __ballot(cl.active);
         if (!am) break;
@@ -159,6 +151,7 @@ __global__ __launch_bounds__(kOneBlock) void k_remap_block(Params p)
     const uint64_t em = __ballot(outcome == 2u);
     const uint32_t ins = (uint32_t)__popcll(__ballot(outcome == 1u));
     uint32_t base = 0;
+    if (lane == 0 && distinct) atomicAdd(&s.count[kDistinctMiss], distinct);
     if (lane == 0 && ins) atomicAdd(&s.count[kInserts], ins);
     if (lane == 0 && em) base = atomicAdd(&s.count[kEvictions], (uint32_t)__popcll(em));
     base = (uint32_t)__builtin_amdgcn_readfirstlane((int)base);
