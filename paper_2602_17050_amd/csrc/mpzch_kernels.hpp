@@ -44,7 +44,6 @@ constexpr int kBlock = 256;
 constexpr int kWavesPerBlock = kBlock / kWave;
 constexpr int kMaxTables = 64;
 constexpr int kStatCount = 9;
-constexpr int kStage = 256;            // undecided positions parked per wavefront before they are resolved
 constexpr int kEvBuf = 256;            // evicted slots staged per wavefront before a flush
 
 enum Stat { kHitPos = 0, kMissPos, kDistinctMiss, kInserts, kEvictions, kCollisions, kInvalidPos, kHitProbeSum, kMissProbeSum };
@@ -819,6 +818,12 @@ __device__ __forceinline__ void gather_wave(const Params &p, bool active, int64_
 template <bool TRAIN, bool MULTI, bool GATHER, bool COUNT = TRAIN, bool NT = false, bool REC = false>
 __device__ __forceinline__ void discover_body(const Params &p)
 {
+    // undecided positions parked per wavefront before they are resolved.  (A lookup's wavefront has two chunks as a rule; with
+    // room for 256 in 22 KB of LDS, and one register more than 64, seven of its workgroups were resident on a compute unit and
+    // the last twelfth of 1 M ids waited for another's end: 15.8 -> 15.0 us, 19.2 -> 18.4 on batches that the caches do not
+    // hold.  With the gather, which has the waiting to do elsewhere, the larger area is the better one: 1.5 M rows of
+    // 128 bytes 85.4 against 87.0.)
+    constexpr int kStage = TRAIN || GATHER ? 256 : 128;
     __shared__ uint32_t s_pos[kWavesPerBlock][kStage];
     __shared__ int32_t s_q[kWavesPerBlock][kStage];      // >= 0: next round to look at; < 0: absent, -(slots read)
     __shared__ int64_t s_id[kWavesPerBlock][kStage];
@@ -1082,11 +1087,11 @@ __device__ __forceinline__ void discover_body(const Params &p)
     }
 }
 
-// The kernels around the one body.  At least four wavefronts per SIMD are asked for (128 registers); with the 84 to 93
-// that training on one table needs five are resident, with the 116 and 125 of a group four, and of the lookups (64 and 72)
-// the seven that their LDS leaves room for.  The pass is bound by memory, and measured within 2 % of its best from three
-// to six wavefronts for both table layouts; fewer hide the latency of the loads less well, more only add to the queues of
-// the memory system.
+// The kernels around the one body.  At least four wavefronts per SIMD are asked for (128 registers); with the 71 to 74
+// registers that training on one table needs six are resident, with the 80 and 98 of a group six and five (41 M values over
+// 26 tables as records, the whole step: held to four 1 221 us, five 1 173, six, with spills, 1 375), of the lookups seven, and
+// of the plain one, held to 64 registers, eight.  Training is bound by memory, and measured within 2 % of its best from three
+// to six wavefronts for both table layouts.
 __global__ __launch_bounds__(kBlock, 4) void k_discover(Params p)
 {
     discover_body<true, false, false>(p);
@@ -1110,7 +1115,7 @@ __global__ __launch_bounds__(kBlock, 4) void k_discover_records(Params p)
     discover_body<true, false, false, true, false, true>(p);
 }
 
-__global__ __launch_bounds__(kBlock, 4) void k_lookup(LookupArgs<false, false> a)
+__global__ __launch_bounds__(kBlock, 8) void k_lookup(LookupArgs<false, false> a)
 {
     discover_body<false, false, false>(lookup_params(a));
 }
