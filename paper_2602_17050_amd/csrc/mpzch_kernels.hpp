@@ -851,11 +851,13 @@ __device__ __forceinline__ void discover_body(const Params &p)
             block = (j / per * kDies + block % kDies) * per + j % per;
         }
     }
-    const int64_t seg = (int64_t)block * kWavesPerBlock + w;            // this wavefront's segment
-    const int64_t num_chunks = (p.n + kWave - 1) / kWave;
-    const int64_t c_begin = seg * p.seg_chunks;
-    const int64_t c_end = c_begin + p.seg_chunks < num_chunks ? c_begin + p.seg_chunks : num_chunks;
-    const int64_t seg_base = c_begin * kWave;
+    // (positions are below 2^30: 32 bits, of which the scalar unit compares any two)
+    const int n = (int)p.n;
+    const int seg = block * kWavesPerBlock + w;                         // this wavefront's segment
+    const int num_chunks = (n + kWave - 1) / kWave;
+    const int c_begin = seg * p.seg_chunks;
+    const int c_end = c_begin + p.seg_chunks < num_chunks ? c_begin + p.seg_chunks : num_chunks;
+    const int64_t seg_base = (int64_t)c_begin * kWave;
     constexpr bool multi = MULTI;
     const bool want_stats = COUNT && p.out_stats != nullptr;
 
@@ -871,10 +873,15 @@ __device__ __forceinline__ void discover_body(const Params &p)
     // ids: from then on a change of table waits for no memory.  A request of 10 K values over 26 tables, one chunk
     // per wavefront, took 11 us, five of them for the search and the descriptor.)
     int t_f = 0;
-    int64_t t_lo = 0, t_hi = 0;
+    int t_lo = 0, t_hi = 0;
     Tab t_d = view(p.t0);
     // the ids of the next chunk are requested while the current one is probed
-    int64_t id_next = (c_begin < c_end && c_begin * kWave + lane < p.n) ? p.ids[c_begin * kWave + lane] : -1;
+    auto ids_of = [&](int chunk) {
+        int64_t id = -1;
+        if (chunk < c_end && lane < n - chunk * kWave) id = (p.ids + (int64_t)chunk * kWave)[lane];
+        return id;
+    };
+    int64_t id_next = ids_of(c_begin);
     int64_t lane_offset = 0;
     if constexpr (multi) {
         lane_offset = table_offsets(p.offsets, p.num_tables);
@@ -905,8 +912,8 @@ __device__ __forceinline__ void discover_body(const Params &p)
         if (hi <= upos) hi = upos + 1;
         if (lo > upos) lo = upos;
         if (lo < 0) lo = 0;
-        t_lo = uniform64(lo);
-        t_hi = uniform64(hi);
+        t_lo = uniform32((int)lo);
+        t_hi = uniform32((int)hi);
         t_d = uniform(view(s_desc[t_f]));
     };
     // a position whose id is resident at `dist` probes from home
@@ -991,21 +998,23 @@ __device__ __forceinline__ void discover_body(const Params &p)
     // One step looks at the lanes of the present chunk that belong to one table (all of them unless the chunk straddles a
     // feature boundary); parked ids are resolved when the stage is full, when the next lanes belong to another table and
     // at the end.  (One place each for the two, or the code is there several times over and needs more registers.)
-    int64_t c = c_begin, id = -1;
+    int c = c_begin;
+    int64_t id = -1;
     bool todo = false;                           // lanes of chunk c that have not been looked at
     bool fetch = true, done = c_begin >= c_end;
+    // The first ids are waited for here: a wait inside the loop would be one for everything under way, among it the stores
+    // of the chunk before.
+    asm volatile("" : "+v"(id_next));
     for (;;) {
         bool resolve = done;
         if (!done) {
-            const int64_t pos = c * kWave + lane;
+            const int pos = c * kWave + lane;
             if (fetch) {
                 id = id_next;
-                id_next = (c + 1 < c_end && pos + kWave < p.n) ? p.ids[pos + kWave] : -1;
-                todo = pos < p.n;
-                fetch = false;
+                todo = pos < n;
             }
             if (multi) {
-                const int64_t upos = c * kWave + __ffsll((unsigned long long)__ballot(todo)) - 1;
+                const int upos = c * kWave + __ffsll((unsigned long long)__ballot(todo)) - 1;
                 if (upos < t_lo || upos >= t_hi) {
                     resolve = staged > 0;        // what is parked belongs to the table that is left
                     if (!resolve) {
@@ -1019,6 +1028,9 @@ __device__ __forceinline__ void discover_body(const Params &p)
                 const bool mine = todo && (!multi || pos < t_hi);
                 const bool valid = mine && id >= 0;
                 const int64_t home = mine ? home_slot(id, d.seed, d.N) : 0;
+                // (behind the hash, or the hash waits for this load too)
+                if (fetch) id_next = ids_of(c + 1);
+                fetch = false;
                 const uint32_t lane_bytes = first_lane_bytes(d);
                 bool fresh = false;
                 int next = 0;
@@ -1041,8 +1053,9 @@ __device__ __forceinline__ void discover_body(const Params &p)
                 const int64_t slot = hit ? wrap(home + res, d.N) : home;
                 if (mine) {
                     // (non-temporal: the outputs are not read by this call; nine in ten are final here)
-                    if (!GATHER || p.out_slots) __builtin_nontemporal_store(slot, &p.out_slots[pos]);
-                    if (!TRAIN && p.out_found) p.out_found[pos] = hit ? 1 : 0;
+                    const int64_t base = (int64_t)c * kWave;
+                    if (!GATHER || p.out_slots) __builtin_nontemporal_store(slot, &(p.out_slots + base)[lane]);
+                    if (!TRAIN && p.out_found) (p.out_found + base)[lane] = hit ? 1 : 0;
                 }
                 // not found so far: parked when its window goes on, or (training) to be listed as a miss
                 const bool park = valid && (res == kProbeGoOn || (TRAIN && res <= kProbeAbsent));
