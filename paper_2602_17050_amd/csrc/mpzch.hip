@@ -143,6 +143,7 @@ struct Scratch {
     uint32_t *seg_cnt = nullptr;
     uint32_t *set_slot = nullptr;
     Control *ctl = nullptr;
+    uint8_t *again = nullptr;
     Control *lookup_ctl = nullptr; // counter block of counting lookups while there is no scratch area
     bool dirty = false;            // a launch sequence was cut short: set and counters must be cleared before use
     bool owned = true;             // base came from hipMalloc (false: it points into the file-scope scratch array)
@@ -157,9 +158,10 @@ struct Scratch {
     }
 
     // Where each array sits inside an area that serves batches of up to n positions: 29 bytes per
-    // position (37 for the first kChunkMaxBatch) and a few small fixed areas.
+    // position (38 for the first kChunkMaxBatch) and a few small fixed areas.  What a call leaves empty: the set from o_set
+    // to o_ctl (ones), counters and notes from there on (zeros).
     struct Layout {
-        size_t o_list, o_ent, o_first, o_list_id, o_hint, o_seg, o_set, o_ctl, total;
+        size_t o_list, o_ent, o_first, o_list_id, o_hint, o_seg, o_set, o_ctl, o_again, total;
     };
     static int64_t set_entries(int64_t n)
     {
@@ -179,7 +181,8 @@ struct Scratch {
         L.o_seg = L.o_hint + align_up((size_t)n + kWave);
         L.o_set = L.o_seg + align_up(4 * max_blocks * kWavesPerBlock);
         L.o_ctl = L.o_set + align_up(4 * (size_t)set_entries(n));
-        L.total = L.o_ctl + align_up(sizeof(Control));
+        L.o_again = L.o_ctl + align_up(sizeof(Control));
+        L.total = L.o_again + align_up((size_t)(n < kChunkMaxBatch ? n : kChunkMaxBatch));
         return L;
     }
     void bind(char *area, const Layout &L, int64_t n)
@@ -193,6 +196,7 @@ struct Scratch {
         seg_cnt = (uint32_t *)(base + L.o_seg);
         set_slot = (uint32_t *)(base + L.o_set);
         ctl = (Control *)(base + L.o_ctl);
+        again = (uint8_t *)(base + L.o_again);
         cap_n = n;
     }
 
@@ -422,7 +426,8 @@ mpzch_status_t run_remap(Scratch &sc, Timing &tm, const Params &p, int32_t max_p
     if (one_block(p)) return launch_remap_block(tm, p, s);        // uses no scratch
     if (sc.dirty) {
         TRY(fill32((int32_t *)sc.set_slot, Scratch::set_entries(sc.cap_n), -1, s));
-        TRY(fill64((int64_t *)sc.ctl, (int64_t)(sizeof(Control) / sizeof(int64_t)), 0, s));
+        const Scratch::Layout L = Scratch::layout_for(sc.cap_n, sc.num_cus);
+        TRY(fill64((int64_t *)sc.ctl, (int64_t)((L.total - L.o_ctl) / sizeof(int64_t)), 0, s));
     }
     sc.dirty = true;
     const mpzch_status_t st = launch_remap(sc, tm, p, max_p_lru, s);
@@ -471,6 +476,7 @@ mpzch_status_t launch_remap(Scratch &sc, Timing &tm, Params p, int32_t max_p_lru
     p.ctl = sc.ctl;
 
     p.place = sc.first_of;
+    p.again = sc.again;
     p.wg_words = (uint64_t *)sc.seg_cnt;
 
     // one table, and no wavefront of Pass 1 has more than one chunk

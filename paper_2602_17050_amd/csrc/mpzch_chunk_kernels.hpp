@@ -24,6 +24,7 @@
 namespace mpzch {
 
 constexpr uint32_t kNoEntry = 0xFFFFFFFFu;       // ent[pos]: the position did not miss
+constexpr uint32_t kEntered = 0x80000000u;       // ... with the entry: this position was the first to be entered there
 // Where a claimant ends up: round + 1 (under the LRU policy choice << 16 | round + 1), 0: nowhere so far, kPlaceNone:
 // displaced and out of slots.
 constexpr uint32_t kPlaceNone = 0x7FFFFFFEu;      // (with kOwnPlace it is not kNoEntry)
@@ -41,6 +42,10 @@ constexpr uint32_t kOwnPlace = 0x80000000u;      // list[pos] of the first occur
 // 8 MB at most (17 to 18 G/s on gigabytes), so where every id is missed the lanes of all wavefronts queue 10 us for their
 // first one, and every collision queues again (262 144 ids,
 // Pass 1: 36 -> 24 us; two entries per position and 1.5 atomics per id took 27 of 36).
+//
+// Who is the first of its id is known without a look at the entry where nobody else has met it: whoever does leaves a note
+// (again) under the position that stands there.  (262 144 new ids: a random read less for each, 12 calls 772 -> 749 us;
+// 51 calls of 65 536 positions 998 -> 986.)
 constexpr int kChunkSetEntries = 4;              // per position
 constexpr int64_t kChunkMaxBatch = (int64_t)1 << 19;
 constexpr int kChunkPosBits = 20;
@@ -55,10 +60,11 @@ __device__ __forceinline__ uint32_t set_insert_chunk(const Params &p, int64_t id
         uint32_t expected = kSetEmpty;
         if (__hip_atomic_compare_exchange_strong(&p.set_slot[e], &expected, mine, __ATOMIC_RELAXED, __ATOMIC_RELAXED,
                                                  __HIP_MEMORY_SCOPE_AGENT))
-            break;                                            // first of its id so far
+            return e | kEntered;                              // first of its id so far
         if (((expected ^ mine) & ~kChunkPosMask) == 0) {
             const uint32_t other = expected & kChunkPosMask;
             if ((int64_t)other < p.n && p.ids[other] == id) {
+                p.again[other] = 1;
                 if (mine < expected) __hip_atomic_fetch_min(&p.set_slot[e], mine, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
                 break;
             }
@@ -150,8 +156,17 @@ __device__ __forceinline__ uint32_t set_insert_wave(const Params &p, bool miss, 
     }
     __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
     uint32_t e = kNoEntry;
-    if (miss && from == lane) e = set_insert_chunk(p, id, hash, (uint32_t)s_m[lane].value);
-    return (uint32_t)__shfl((int)e, from);
+    const uint32_t entered = (uint32_t)s_m[from].value;
+    if (miss && from == lane) e = set_insert_chunk(p, id, hash, entered);
+    e = (uint32_t)__shfl((int)e, from);
+    return miss && entered != pos ? e & ~kEntered : e;
+}
+
+// The first position of the id that was entered at ent[pos] (`again`: the note under pos).
+__device__ __forceinline__ uint32_t first_occurrence(const Params &p, uint32_t pos, uint32_t ent, uint8_t again)
+{
+    if ((ent & kEntered) && !again) return pos;
+    return p.set_slot[ent & ~kEntered] & kChunkPosMask;
 }
 
 // SHIFT 1: a wavefront takes 32 positions, so that one pass holds the whole windows of up to 16 slots (see k_lookup_short;
@@ -278,9 +293,10 @@ __global__ __launch_bounds__(kBlock, 4) void k_allocate_chunk(Params p)
     const uint32_t e = in ? p.ent[pos] : kNoEntry;
     const int64_t id = in ? p.ids[pos] : -1;
     uint32_t start = in ? (uint32_t)p.hint[pos] : kStartNever;   // (anything where the position did not miss)
+    const uint8_t again = in ? p.again[pos] : 0;
     const bool have = e != kNoEntry;
     uint32_t first = 0;
-    if (have) first = p.set_slot[e] & kChunkPosMask;
+    if (have) first = first_occurrence(p, (uint32_t)pos, e, again);
     else start = kStartNever;
 
     Claimant c;
@@ -339,9 +355,10 @@ __global__ __launch_bounds__(kLruBlock, 8) void k_allocate_lru_chunk(Params p)
     const bool in = (int)threadIdx.x < kBlock && pos < p.n;
     const uint32_t e = in ? p.ent[pos] : kNoEntry;
     const int64_t id = in ? p.ids[pos] : -1;
+    const uint8_t again = in ? p.again[pos] : 0;
     const bool have = e != kNoEntry;
     uint32_t first = 0;
-    if (have) first = p.set_slot[e] & kChunkPosMask;
+    if (have) first = first_occurrence(p, (uint32_t)pos, e, again);
     const bool agent = have && first == (uint32_t)pos;
     if (in && !agent) p.list[pos] = have ? first : kNoEntry;
     const uint64_t am = __ballot(agent);
@@ -468,7 +485,10 @@ __global__ __launch_bounds__(kBlock, 8) void k_finalize_chunk(Params p)
     // the scratch set is left empty again (all of it, in one coalesced store, instead of the entries that were used, one at
     // a time)
     static_assert(kChunkSetEntries == 4, "cleared as one vector of four");
-    if (in) reinterpret_cast<u32x4 *>(p.set_slot)[pos] = u32x4(kSetEmpty);
+    if (in) {
+        reinterpret_cast<u32x4 *>(p.set_slot)[pos] = u32x4(kSetEmpty);
+        p.again[pos] = 0;
+    }
     // what the evicted slots of this workgroup need, requested now: the slots, and the counts of the workgroups before
     const uint64_t *const outcomes = p.wg_words + 2 * groups;
     const int evicted = (int)unpack3(outcomes[group], 2);

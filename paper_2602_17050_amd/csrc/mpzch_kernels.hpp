@@ -105,6 +105,7 @@ struct Params {
     // one chunk per wavefront (mpzch_chunk_kernels.hpp): by batch position, where the claim of the id elected there
     // ended up; by workgroup, the slots evicted by its claimants; and three words of counters per workgroup
     uint32_t *place;
+    uint8_t *again;                // ... by batch position: another wavefront has met the id that was entered for it
     int64_t *evicted;
     uint64_t *wg_words;
     int32_t seg_chunks;
