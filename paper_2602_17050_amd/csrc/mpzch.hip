@@ -338,23 +338,23 @@ mpzch_status_t launch_lookup_short(const Params &p, hipStream_t s)
 template <bool MULTI, bool REC>
 void launch_allocate_lru(int32_t max_p_lru, const Params &p, int grid, hipStream_t s)
 {
-    // a group of 8, 16, 32 or 64 lanes per claimant, whichever holds its window; the whole wavefront
+    // 8 lanes per claimant, with 1, 2, 4 or 8 slots each, whichever holds its window; the whole wavefront
     // with several slots per lane for longer probe ranges
     if (max_p_lru > kWave) hipLaunchKernelGGL((k_allocate_lru_long<MULTI>), dim3(grid), dim3(kWave), 0, s, p);
-    else if (max_p_lru <= 8) hipLaunchKernelGGL((k_allocate_lru<8, MULTI, REC>), dim3(grid), dim3(kWave), 0, s, p);
-    else if (max_p_lru <= 16) hipLaunchKernelGGL((k_allocate_lru<16, MULTI, REC>), dim3(grid), dim3(kWave), 0, s, p);
-    else if (max_p_lru <= 32) hipLaunchKernelGGL((k_allocate_lru<32, MULTI, REC>), dim3(grid), dim3(kWave), 0, s, p);
-    else hipLaunchKernelGGL((k_allocate_lru<64, MULTI, REC>), dim3(grid), dim3(kWave), 0, s, p);
+    else if (max_p_lru <= 8) hipLaunchKernelGGL((k_allocate_lru<1, MULTI, REC>), dim3(grid), dim3(kWave), 0, s, p);
+    else if (max_p_lru <= 16) hipLaunchKernelGGL((k_allocate_lru<2, MULTI, REC>), dim3(grid), dim3(kWave), 0, s, p);
+    else if (max_p_lru <= 32) hipLaunchKernelGGL((k_allocate_lru<4, MULTI, REC>), dim3(grid), dim3(kWave), 0, s, p);
+    else hipLaunchKernelGGL((k_allocate_lru<8, MULTI, REC>), dim3(grid), dim3(kWave), 0, s, p);
 }
 
 // the same where every wavefront has one chunk (max_p_lru <= 64)
 template <bool REC>
 void launch_allocate_lru_chunk(int32_t max_p_lru, const Params &p, int grid, hipStream_t s)
 {
-    if (max_p_lru <= 8) hipLaunchKernelGGL((k_allocate_lru_chunk<8, REC>), dim3(grid), dim3(kLruBlock), 0, s, p);
-    else if (max_p_lru <= 16) hipLaunchKernelGGL((k_allocate_lru_chunk<16, REC>), dim3(grid), dim3(kLruBlock), 0, s, p);
-    else if (max_p_lru <= 32) hipLaunchKernelGGL((k_allocate_lru_chunk<32, REC>), dim3(grid), dim3(kLruBlock), 0, s, p);
-    else hipLaunchKernelGGL((k_allocate_lru_chunk<64, REC>), dim3(grid), dim3(kLruBlock), 0, s, p);
+    if (max_p_lru <= 8) hipLaunchKernelGGL((k_allocate_lru_chunk<1, REC>), dim3(grid), dim3(kBlock), 0, s, p);
+    else if (max_p_lru <= 16) hipLaunchKernelGGL((k_allocate_lru_chunk<2, REC>), dim3(grid), dim3(kBlock), 0, s, p);
+    else if (max_p_lru <= 32) hipLaunchKernelGGL((k_allocate_lru_chunk<4, REC>), dim3(grid), dim3(kBlock), 0, s, p);
+    else hipLaunchKernelGGL((k_allocate_lru_chunk<8, REC>), dim3(grid), dim3(kBlock), 0, s, p);
 }
 
 mpzch_status_t launch_allocate(int32_t max_p_lru, const Params &p, int num_cus, hipStream_t s)

@@ -335,24 +335,23 @@ __global__ __launch_bounds__(kBlock, 4) void k_allocate_chunk(Params p)
     leave_outcomes<kWavesPerBlock>(p, have && first == (uint32_t)pos, inserted, evicted, slot, s_red);
 }
 
-// The claims under the LRU policy (max_probe <= G <= 64).  The workgroup first lists its claimants, so that its 512 / G
+// The claims under the LRU policy (max_probe <= 8 T <= 64).  The workgroup first lists its claimants, so that its 32
 // groups of lanes get them evenly: a wavefront of 64 positions has a handful, which it would serve one or two at a time
 // (300 007 positions, 10 % of them claimants with windows of 32 slots: 43 -> 16 us).
-constexpr int kLruBlock = 512;
-template <int G, bool REC>
-__global__ __launch_bounds__(kLruBlock, 8) void k_allocate_lru_chunk(Params p)
+template <int T, bool REC>
+__global__ __launch_bounds__(kBlock, T == 8 ? 4 : 6) void k_allocate_lru_chunk(Params p)
 {
-    constexpr int WAVES = kLruBlock / kWave, GROUPS = kLruBlock / G;
+    constexpr int G = kLruG, WAVES = kWavesPerBlock, GROUPS = kBlock / G;
     __shared__ int64_t s_home[kBlock];
     __shared__ int64_t s_slot[kBlock];               // of the claimant's chain of claims: the slot not claimed before
     __shared__ uint32_t s_pos[kBlock];
     __shared__ uint32_t s_own[kBlock];               // its place
     __shared__ uint8_t s_outcome[kBlock];            // 0: none, 1: it was empty, 2: it held an id
     __shared__ uint32_t s_red[WAVES][3];
-    const int lane = lane_id(), w = threadIdx.x / kWave;
+    const int lane = lane_id(), w = wave_id();
     const Tab d = view(p.t0);
     const int64_t pos = (int64_t)blockIdx.x * kBlock + threadIdx.x;
-    const bool in = (int)threadIdx.x < kBlock && pos < p.n;
+    const bool in = pos < p.n;
     const uint32_t e = in ? p.ent[pos] : kNoEntry;
     const int64_t id = in ? p.ids[pos] : -1;
     const uint8_t again = in ? p.again[pos] : 0;
@@ -379,13 +378,13 @@ __global__ __launch_bounds__(kLruBlock, 8) void k_allocate_lru_chunk(Params p)
     const int g = (int)threadIdx.x / G;
     int i = g;
     int64_t home = i < count ? s_home[i] : 0;
-    LruSlot x = load_lru_slot<G, REC>(d, i < count, home);
+    LruSlots<T> x = load_lru_slots<T, REC>(d, i < count, home);
     for (; __any(i < count); i += GROUPS) {
         // the window of the next claimant is requested before this one is served
         const bool more = i + GROUPS < count;
         const int64_t home2 = more ? s_home[i + GROUPS] : 0;
-        const LruSlot x2 = load_lru_slot<G, REC>(d, more, home2);
-        claim_group_lru<G, REC>(p, d, i < count, i < count ? s_pos[i] : 0u, home, x,
+        const LruSlots<T> x2 = load_lru_slots<T, REC>(d, more, home2);
+        claim_group_lru<T, REC>(p, d, i < count, i < count ? s_pos[i] : 0u, home, x,
                                 [&](uint32_t who, int32_t choice, int32_t round, int64_t slot, int64_t old) {
                                     if (lane % G != 0) return;
                                     const uint32_t place = (uint32_t)choice << 16 | (uint32_t)(round + 1);

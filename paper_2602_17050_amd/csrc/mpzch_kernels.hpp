@@ -1555,102 +1555,118 @@ __global__ __launch_bounds__(kWave, MULTI ? 5 : 7) void k_allocate(Params p)
 // oldest first -- follows from the state at the start of allocation, which stays readable while
 // claims are in flight: a tag keeps the was-occupied bit and metadata is not written before
 // k_finalize.  The tag's round field carries the CHOICE number, so a slot ends with the claimant
-// of the lowest (choice, position).  A group of G lanes serves one claimant, one lane per slot of
-// its window (max_probe <= G <= 64; longer ranges: claim_wave_lru_long), so a wavefront works on
-// 64 / G claimants at a time; a displaced claimant is carried on by the group that displaced it, from its next choice.
+// of the lowest (choice, position).  A group of 8 lanes serves one claimant, lane r holding the slots of rounds r, 8 + r, ...
+// of its window (T of them, max_probe <= 8 T <= 64; longer ranges: claim_wave_lru_long), so a wavefront works on
+// 8 claimants at a time; a displaced claimant is carried on by the group that displaced it, from its next choice.
 //
-// A claimant is a chain of two round trips, window and atomic, and with windows requested ahead what counts is the
+// A claimant is a chain of two round trips, window and atomic, some 2 us, and what counts is how many of them are under way
+// (with one lane per slot of the window, two claimants to a wavefront for windows of 32 slots, calls of 300 007
+// positions took 53.5 instead of 50.2 us, with windows of 64 of 400 000 78 instead of 72) and the
 // number of instructions in between: the list is not ranked, its next choice is drawn when it is needed, which for nearly
 // every claimant is once (2 M positions, windows of 32, 220 K claimants: ranked by two shuffles per slot of the window
 // more than twice as long, ranked through LDS 78, drawn 56 us).
+constexpr int kLruG = 8;
+constexpr int kLruGroups = kWave / kLruG;
 
-// What a lane of a claimant's group has read of its slot of the window.
-struct LruSlot {
-    int64_t v;
-    int32_t m;
+// What a lane of a claimant's group has read of its slots of the window.
+template <int T>
+struct LruSlots {
+    int64_t v[T];
+    int32_t m[T];
 };
-template <int G, bool REC>
-__device__ __forceinline__ LruSlot load_lru_slot(const Tab &d, bool active, int64_t home)
+template <int T, bool REC>
+__device__ __forceinline__ LruSlots<T> load_lru_slots(const Tab &d, bool active, int64_t home)
 {
-    const int r = lane_id() % G;
-    // (a lane without a slot reads one that is there)
-    const int64_t s = active && r < d.P ? wrap(home + r, d.N) : 0;
-    LruSlot x;
-    if constexpr (REC) {
-        const u32x3 rec = *(global_ptr<u32x3>)id_at(d, s);
-        x.v = (int64_t)(((uint64_t)rec.y << 32) | rec.x);
-        x.m = (int32_t)rec.z;
-    } else {
-        x.v = *id_at(d, s);
-        x.m = *meta_at(d, s);
+    const int r = lane_id() % kLruG;
+    LruSlots<T> x;
+#pragma unroll
+    for (int t = 0; t < T; ++t) {
+        // (a lane without a slot reads one that is there)
+        const int round = kLruG * t + r;
+        const int64_t s = active && round < d.P ? wrap(home + round, d.N) : 0;
+        if constexpr (REC) {
+            const u32x3 rec = *(global_ptr<u32x3>)id_at(d, s);
+            x.v[t] = (int64_t)(((uint64_t)rec.y << 32) | rec.x);
+            x.m[t] = (int32_t)rec.z;
+        } else {
+            x.v[t] = *id_at(d, s);
+            x.m[t] = *meta_at(d, s);
+        }
     }
     return x;
 }
 
-// Minimum over the G lanes of a group, in every lane of it.
+// Minimum over the 8 lanes of a group, in every lane of it.
 template <int CTRL>
 __device__ __forceinline__ int32_t min_with(int32_t x)
 {
     const int32_t y = __builtin_amdgcn_update_dpp(x, x, CTRL, 0xF, 0xF, false);
     return y < x ? y : x;
 }
-template <int G>
 __device__ __forceinline__ int32_t group_min(int32_t x)
 {
     x = min_with<0xB1>(x);                           // quad_perm 1 0 3 2
     x = min_with<0x4E>(x);                           // quad_perm 2 3 0 1
-    x = min_with<0x141>(x);                          // row_half_mirror: 8 lanes
-    if constexpr (G >= 16) x = min_with<0x140>(x);   // row_mirror: 16 lanes
-    for (int o = 16; o < G; o <<= 1) {
-        const int32_t y = __shfl_xor(x, o);
-        x = y < x ? y : x;
-    }
-    return x;
+    return min_with<0x141>(x);                       // row_half_mirror: 8 lanes
 }
 
 // active, cpos and home are uniform within a group, x: what its lanes have read of the window.  placed(pos, choice, round,
 // slot, old) is called for every claim that stands, old being what the slot held before; lost(pos) for a claimant that
 // has run out of slots; both by all lanes of the group.
-template <int G, bool REC, typename Placed, typename Lost>
+template <int T, bool REC, typename Placed, typename Lost>
 __device__ __forceinline__ void claim_group_lru(const Params &p, const Tab &d, bool active, uint32_t cpos, int64_t home,
-                                                LruSlot x, Placed placed, Lost lost)
+                                                LruSlots<T> x, Placed placed, Lost lost)
 {
+    constexpr int32_t kNone = 0x7FFFFFFF;
     const int lane = lane_id();
-    const int r = lane % G, gbase = lane - r;
-    const uint64_t gmask = G == kWave ? ~0ull : ((1ull << (G % kWave)) - 1ull) << gbase;
+    const int r = lane % kLruG, gbase = lane - r;
     int32_t choice = 0;
     while (__any(active)) {
-        const bool in = active && r < d.P;
-        const bool occ = is_tag(x.v) ? tag_occ(x.v) != 0 : x.v >= 0;      // the slot held an id when the call began
-        // what has not been drawn yet
-        uint64_t empties = __ballot(in && !occ) & gmask;
-        bool evictable = in && occ && x.m != p.step;
+        uint32_t empties = 0, evictable = 0;         // bit t: the slot of round 8 t + r is empty / may be evicted and has not been drawn
+#pragma unroll
+        for (int t = 0; t < T; ++t) {
+            const bool in = active && kLruG * t + r < d.P;
+            const bool occ = is_tag(x.v[t]) ? tag_occ(x.v[t]) != 0 : x.v[t] >= 0;     // it held an id when the call began
+            if (in && !occ) empties |= 1u << t;
+            if (in && occ && x.m[t] != p.step) evictable |= 1u << t;
+        }
         int32_t drawn = 0;
         int64_t displaced = 0;
         bool trying = active;
         while (__any(trying)) {
-            const int32_t oldest = group_min<G>(evictable ? x.m : 0x7FFFFFFF);
-            const uint64_t oldests = __ballot(evictable && x.m == oldest) & gmask;
-            const uint64_t from = empties ? empties : oldests;
-            const bool was_empty = empties != 0;
-            if (trying && !from) {
+            // the first empty slot; without one the oldest time stamp's first round
+            const int32_t empty = group_min(empties ? kLruG * (__ffs(empties) - 1) + r : kNone);
+            int32_t oldest = kNone;
+#pragma unroll
+            for (int t = 0; t < T; ++t)
+                if ((evictable >> t & 1u) && x.m[t] < oldest) oldest = x.m[t];
+            oldest = group_min(oldest);
+            int32_t old_round = kNone;
+#pragma unroll
+            for (int t = T - 1; t >= 0; --t)
+                if ((evictable >> t & 1u) && x.m[t] == oldest) old_round = kLruG * t + r;
+            old_round = group_min(old_round);
+            const bool was_empty = empty != kNone;
+            const int32_t round = was_empty ? empty : old_round;
+            if (trying && round == kNone) {
                 lost(cpos);
                 trying = false;
             }
             if (!trying) continue;
-            const int who = __ffsll((unsigned long long)from) - 1;
-            empties &= empties - 1;                                     // (0 stays 0)
-            if (!was_empty && lane == who) evictable = false;
+            if (round % kLruG == r) {
+                empties &= ~(1u << (round / kLruG));
+                evictable &= ~(1u << (round / kLruG));
+            }
             if (drawn++ < choice) continue;
             const int64_t mine = make_tag((uint32_t)choice, cpos, was_empty ? 0u : 1u);
-            const int64_t s = wrap(home + (who - gbase), d.N);
+            const int64_t s = wrap(home + round, d.N);
             int64_t old = 0;
-            if (lane == who) old = __hip_atomic_fetch_min(id_at(d, s), mine, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            old = shfl64(old, who);
+            if (r == 0) old = __hip_atomic_fetch_min(id_at(d, s), mine, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            old = shfl64(old, gbase);
             if (is_tag(old) && old < mine) {
                 ++choice;                                               // a better claim holds this slot
             } else {
-                placed(cpos, choice, who - gbase, s, old);
+                placed(cpos, choice, round, s, old);
                 displaced = is_tag(old) ? old : 0;
                 trying = false;
             }
@@ -1661,7 +1677,7 @@ __device__ __forceinline__ void claim_group_lru(const Params &p, const Tab &d, b
             choice = (int32_t)tag_round(displaced) + 1;
             home = home_slot(p.ids[cpos], d.seed, d.N);
         }
-        if (__any(active)) x = load_lru_slot<G, REC>(d, active, home);
+        if (__any(active)) x = load_lru_slots<T, REC>(d, active, home);
     }
 }
 
@@ -1669,10 +1685,10 @@ __device__ __forceinline__ void claim_group_lru(const Params &p, const Tab &d, b
 // written the hints of every list entry and skipped the claimants of LRU tables; here only those
 // claimants are served and only their hints are written.  The windows of the next claimants are requested before the
 // present ones are served.
-template <int G, bool MULTI, bool REC>
-__global__ __launch_bounds__(kWave, MULTI ? 5 : 8) void k_allocate_lru(Params p)
+template <int T, bool MULTI, bool REC>
+__global__ __launch_bounds__(kWave, MULTI ? (T == 8 ? 3 : 4) : T == 8 ? 4 : 5) void k_allocate_lru(Params p)
 {
-    constexpr int NG = kWave / G;
+    constexpr int G = kLruG, NG = kLruGroups;
     const int lane = threadIdx.x;
     const int g = lane / G;
     const Tab d0 = view(MULTI ? p.descs[0] : p.t0);
@@ -1711,7 +1727,7 @@ __global__ __launch_bounds__(kWave, MULTI ? 5 : 8) void k_allocate_lru(Params p)
             const int f1 = __shfl(f, src >= 0 ? src : lane);
             Tab d = d0;
             if (MULTI && src >= 0) d = view(p.descs[f1]);
-            LruSlot x = load_lru_slot<G, REC>(d, src >= 0, chome);
+            LruSlots<T> x = load_lru_slots<T, REC>(d, src >= 0, chome);
             while (__any(src >= 0)) {
                 const int src2 = next_bits<G>(am, g);
                 const uint32_t cpos2 = __shfl(pos, src2 >= 0 ? src2 : lane);
@@ -1719,9 +1735,9 @@ __global__ __launch_bounds__(kWave, MULTI ? 5 : 8) void k_allocate_lru(Params p)
                 const int f2 = __shfl(f, src2 >= 0 ? src2 : lane);
                 Tab d2 = d0;
                 if (MULTI && src2 >= 0) d2 = view(p.descs[f2]);
-                const LruSlot x2 = load_lru_slot<G, REC>(d2, src2 >= 0, chome2);
+                const LruSlots<T> x2 = load_lru_slots<T, REC>(d2, src2 >= 0, chome2);
                 int32_t fr = -1;
-                claim_group_lru<G, REC>(p, d, src >= 0, cpos, chome, x,
+                claim_group_lru<T, REC>(p, d, src >= 0, cpos, chome, x,
                                         [&](uint32_t who, int32_t, int32_t round, int64_t, int64_t) {
                                             if (who == cpos) fr = round;
                                         },
