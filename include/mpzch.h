@@ -137,7 +137,7 @@ mpzch_status_t mpzch_create_with_layout(int64_t num_slots, int32_t max_probe, mp
 mpzch_status_t mpzch_destroy(mpzch_table_t *t);
 
 /*
- * Optional: allocate scratch for batches of up to max_n positions now (29 bytes per
+ * Optional: allocate scratch for batches of up to max_n positions now (30 bytes per
  * position, 38 for the first 524 288) so that later remap calls allocate nothing.  Synchronises the device when it
  * has to grow the scratch.  Errors: INVALID_ARG (max_n < 0 or > MPZCH_MAX_BATCH), ALLOC.
  * With enough scratch reserved and kernel timing off, mpzch_remap, mpzch_remap_feature_ttl,

@@ -143,7 +143,7 @@ struct Scratch {
     uint32_t *seg_cnt = nullptr;
     uint32_t *set_slot = nullptr;
     Control *ctl = nullptr;
-    uint8_t *again = nullptr;
+    uint8_t *note = nullptr;
     Control *lookup_ctl = nullptr; // counter block of counting lookups while there is no scratch area
     bool dirty = false;            // a launch sequence was cut short: set and counters must be cleared before use
     bool owned = true;             // base came from hipMalloc (false: it points into the file-scope scratch array)
@@ -157,11 +157,11 @@ struct Scratch {
         return device_cus(&num_cus);
     }
 
-    // Where each array sits inside an area that serves batches of up to n positions: 29 bytes per
+    // Where each array sits inside an area that serves batches of up to n positions: 30 bytes per
     // position (38 for the first kChunkMaxBatch) and a few small fixed areas.  What a call leaves empty: the set from o_set
     // to o_ctl (ones), counters and notes from there on (zeros).
     struct Layout {
-        size_t o_list, o_ent, o_first, o_list_id, o_hint, o_seg, o_set, o_ctl, o_again, total;
+        size_t o_list, o_ent, o_first, o_list_id, o_hint, o_seg, o_set, o_ctl, o_note, total;
     };
     static int64_t set_entries(int64_t n)
     {
@@ -181,8 +181,8 @@ struct Scratch {
         L.o_seg = L.o_hint + align_up((size_t)n + kWave);
         L.o_set = L.o_seg + align_up(4 * max_blocks * kWavesPerBlock);
         L.o_ctl = L.o_set + align_up(4 * (size_t)set_entries(n));
-        L.o_again = L.o_ctl + align_up(sizeof(Control));
-        L.total = L.o_again + align_up((size_t)(n < kChunkMaxBatch ? n : kChunkMaxBatch));
+        L.o_note = L.o_ctl + align_up(sizeof(Control));
+        L.total = L.o_note + align_up((size_t)n);
         return L;
     }
     void bind(char *area, const Layout &L, int64_t n)
@@ -196,7 +196,7 @@ struct Scratch {
         seg_cnt = (uint32_t *)(base + L.o_seg);
         set_slot = (uint32_t *)(base + L.o_set);
         ctl = (Control *)(base + L.o_ctl);
-        again = (uint8_t *)(base + L.o_again);
+        note = (uint8_t *)(base + L.o_note);
         cap_n = n;
     }
 
@@ -478,7 +478,7 @@ mpzch_status_t launch_remap(Scratch &sc, Timing &tm, Params p, int32_t max_p_lru
     p.ctl = sc.ctl;
 
     p.place = sc.first_of;
-    p.again = sc.again;
+    p.note = sc.note;
     p.wg_words = (uint64_t *)sc.seg_cnt;
 
     // one table, and no wavefront of Pass 1 has more than one chunk

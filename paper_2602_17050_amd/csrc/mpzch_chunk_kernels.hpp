@@ -24,7 +24,7 @@
 namespace mpzch {
 
 constexpr uint32_t kNoEntry = 0xFFFFFFFFu;       // ent[pos]: the position did not miss
-constexpr uint32_t kEntered = 0x80000000u;       // ... with the entry: this position was the first to be entered there
+                                                 // (with the entry: kEntered)
 // Where a claimant ends up: round + 1 (under the LRU policy choice << 16 | round + 1), 0: nowhere so far, kPlaceNone:
 // displaced and out of slots.
 constexpr uint32_t kPlaceNone = 0x7FFFFFFEu;      // (with kOwnPlace it is not kNoEntry)
@@ -42,10 +42,7 @@ constexpr uint32_t kOwnPlace = 0x80000000u;      // list[pos] of the first occur
 // 8 MB at most (17 to 18 G/s on gigabytes), so where every id is missed the lanes of all wavefronts queue 10 us for their
 // first one, and every collision queues again (262 144 ids,
 // Pass 1: 36 -> 24 us; two entries per position and 1.5 atomics per id took 27 of 36).
-//
-// Who is the first of its id is known without a look at the entry where nobody else has met it: whoever does leaves a note
-// (again) under the position that stands there.  (262 144 new ids: a random read less for each, 12 calls 772 -> 749 us;
-// 51 calls of 65 536 positions 998 -> 986.)
+// (With the notes of set_insert: 12 calls of 262 144 new ids 772 -> 749 us, 51 of 65 536 positions 998 -> 986.)
 constexpr int kChunkSetEntries = 4;              // per position
 constexpr int64_t kChunkMaxBatch = (int64_t)1 << 19;
 constexpr int kChunkPosBits = 20;
@@ -64,7 +61,7 @@ __device__ __forceinline__ uint32_t set_insert_chunk(const Params &p, int64_t id
         if (((expected ^ mine) & ~kChunkPosMask) == 0) {
             const uint32_t other = expected & kChunkPosMask;
             if ((int64_t)other < p.n && p.ids[other] == id) {
-                p.again[other] = 1;
+                p.note[other] = 1;
                 if (mine < expected) __hip_atomic_fetch_min(&p.set_slot[e], mine, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
                 break;
             }
@@ -133,39 +130,21 @@ __device__ __forceinline__ void store_meta_block(const Tab &d, bool active, int6
     if (store) __hip_atomic_fetch_max(meta_at(d, slot), s_m.value[t], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
-// set_insert_chunk for the lanes with `miss` set.  Copies of one id within the wavefront (those that find each other in
-// LDS) enter it once, with the smallest of their positions: an id that is new and popular at once -- the first batch of a
-// table, of a feature -- otherwise has thousands of atomics on one word, 12 ns each (65 536 positions, the most popular id
-// a fourteenth of them: 67 -> 27 us; over the workgroup instead, 14 us, but the barriers cost every other call 0.7).
+// set_insert_chunk for the lanes with `miss` set.
 __device__ __forceinline__ uint32_t set_insert_wave(const Params &p, bool miss, int64_t id, uint64_t hash, uint32_t pos,
                                                     MetaMerge *s_m)
 {
-    const int lane = lane_id();
-    const int cell = (int)(hash >> 44) & (kWave - 1);
-    s_m[lane].slot = miss ? id : -1;
-    s_m[lane].value = (int32_t)pos;
-    if (miss) s_m[cell].winner = (uint32_t)lane;
-    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-    int from = lane;
-    if (miss) {
-        const int o = (int)s_m[cell].winner;
-        if (o != lane && s_m[o].slot == id) {
-            __hip_atomic_fetch_min(&s_m[o].value, (int32_t)pos, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
-            from = o;
-        }
-    }
-    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-    uint32_t e = kNoEntry;
-    const uint32_t entered = (uint32_t)s_m[from].value;
-    if (miss && from == lane) e = set_insert_chunk(p, id, hash, entered);
+    uint32_t e = kNoEntry, first = pos;
+    const int from = merge_copies(miss, id, (int)(hash >> 44) & (kWave - 1), first, s_m);
+    if (miss && from == lane_id()) e = set_insert_chunk(p, id, hash, first);
     e = (uint32_t)__shfl((int)e, from);
-    return miss && entered != pos ? e & ~kEntered : e;
+    return miss && first != pos ? e & ~kEntered : e;
 }
 
-// The first position of the id that was entered at ent[pos] (`again`: the note under pos).
-__device__ __forceinline__ uint32_t first_occurrence(const Params &p, uint32_t pos, uint32_t ent, uint8_t again)
+// The first position of the id that was entered at ent[pos].
+__device__ __forceinline__ uint32_t first_occurrence(const Params &p, uint32_t pos, uint32_t ent, uint8_t note)
 {
-    if ((ent & kEntered) && !again) return pos;
+    if (entered_alone(ent, note)) return pos;
     return p.set_slot[ent & ~kEntered] & kChunkPosMask;
 }
 
@@ -293,10 +272,10 @@ __global__ __launch_bounds__(kBlock, 4) void k_allocate_chunk(Params p)
     const uint32_t e = in ? p.ent[pos] : kNoEntry;
     const int64_t id = in ? p.ids[pos] : -1;
     uint32_t start = in ? (uint32_t)p.hint[pos] : kStartNever;   // (anything where the position did not miss)
-    const uint8_t again = in ? p.again[pos] : 0;
+    const uint8_t note = in ? p.note[pos] : 0;
     const bool have = e != kNoEntry;
     uint32_t first = 0;
-    if (have) first = first_occurrence(p, (uint32_t)pos, e, again);
+    if (have) first = first_occurrence(p, (uint32_t)pos, e, note);
     else start = kStartNever;
 
     Claimant c;
@@ -354,10 +333,10 @@ __global__ __launch_bounds__(kBlock, T == 8 ? 4 : 6) void k_allocate_lru_chunk(P
     const bool in = pos < p.n;
     const uint32_t e = in ? p.ent[pos] : kNoEntry;
     const int64_t id = in ? p.ids[pos] : -1;
-    const uint8_t again = in ? p.again[pos] : 0;
+    const uint8_t note = in ? p.note[pos] : 0;
     const bool have = e != kNoEntry;
     uint32_t first = 0;
-    if (have) first = first_occurrence(p, (uint32_t)pos, e, again);
+    if (have) first = first_occurrence(p, (uint32_t)pos, e, note);
     const bool agent = have && first == (uint32_t)pos;
     if (in && !agent) p.list[pos] = have ? first : kNoEntry;
     const uint64_t am = __ballot(agent);
@@ -486,7 +465,7 @@ __global__ __launch_bounds__(kBlock, 8) void k_finalize_chunk(Params p)
     static_assert(kChunkSetEntries == 4, "cleared as one vector of four");
     if (in) {
         reinterpret_cast<u32x4 *>(p.set_slot)[pos] = u32x4(kSetEmpty);
-        p.again[pos] = 0;
+        p.note[pos] = 0;
     }
     // what the evicted slots of this workgroup need, requested now: the slots, and the counts of the workgroups before
     const uint64_t *const outcomes = p.wg_words + 2 * groups;

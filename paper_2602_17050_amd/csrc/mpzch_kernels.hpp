@@ -105,7 +105,8 @@ struct Params {
     // one chunk per wavefront (mpzch_chunk_kernels.hpp): by batch position, where the claim of the id elected there
     // ended up; by workgroup, the slots evicted by its claimants; and three words of counters per workgroup
     uint32_t *place;
-    uint8_t *again;                // ... by batch position: another wavefront has met the id that was entered for it
+    uint8_t *note;                 // ... by batch position, 0 between calls: 1 = somebody else has met the id that was entered
+                                   // in the scratch set for it (also where lists are kept, of one table)
     int64_t *evicted;
     uint64_t *wg_words;
     int32_t seg_chunks;
@@ -394,17 +395,23 @@ constexpr uint32_t kSetEmpty = 0xFFFFFFFFu;
 // probe sequence with one compare-and-swap, or, on meeting an entry of the same id, lower it to
 // min(entry, pos).  An entry never changes the id it stands for, so concurrent inserts agree.
 // size >= 2 * (number of inserts into the region), so the unbounded probe always ends.
-// Returns the entry index.
-__device__ __forceinline__ uint32_t set_insert(const Params &p, int64_t id, uint32_t pos, uint64_t base, uint64_t size)
+// Returns the entry index, with kEntered if pos was the first to stand there.  NOTE: whoever meets an entry of its id leaves a
+// note under the position that stands there, so that who comes first need not be read back where there is no note, and with
+// k_allocate's notes of displaced claims k_finalize need not look at the table (a random read less in each, for each missed
+// id: 2.5 M positions, 10 % of them new, on 400 M slots 208 -> 203 us, on 50 M 194 -> 188; 5 %, on 300 M, 165 -> 161).
+constexpr uint32_t kEntered = 0x80000000u;       // (entries are below 2^31)
+template <bool NOTE>
+__device__ __forceinline__ uint32_t set_insert(const Params &p, int64_t id, uint64_t hash, uint32_t pos, uint64_t base, uint64_t size)
 {
-    uint64_t e = base + __umul64hi(mix64((uint64_t)id ^ kSetSeed), size);
+    uint64_t e = base + __umul64hi(hash, size);
     const uint64_t end = base + size;
     for (;;) {
         uint32_t expected = kSetEmpty;
         if (__hip_atomic_compare_exchange_strong(&p.set_slot[e], &expected, pos, __ATOMIC_RELAXED, __ATOMIC_RELAXED,
                                                  __HIP_MEMORY_SCOPE_AGENT))
-            break;                                            // first of its id so far
+            return NOTE ? (uint32_t)e | kEntered : (uint32_t)e;   // first of its id so far
         if ((int64_t)expected < p.n && p.ids[expected] == id) {   // (an entry is always a position of this batch)
+            if constexpr (NOTE) p.note[expected] = 1;
             if (pos < expected) __hip_atomic_fetch_min(&p.set_slot[e], pos, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
             break;
         }
@@ -412,6 +419,9 @@ __device__ __forceinline__ uint32_t set_insert(const Params &p, int64_t id, uint
     }
     return (uint32_t)e;
 }
+
+// Is it certain that nobody else has the id that was entered at `ent`?
+__device__ __forceinline__ bool entered_alone(uint32_t ent, uint8_t note) { return (ent & kEntered) && !note; }
 
 // ------------------------------------------------------------------ small wavefront helpers
 __device__ __forceinline__ unsigned long long wave_sum(unsigned long long x)
@@ -761,6 +771,32 @@ __device__ __forceinline__ void store_meta_wave(const Tab &d, bool active, int64
     __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
 }
 
+// Copies of one id within the wavefront (those that find each other in LDS) enter the scratch set once, with the smallest
+// of their positions: an id that is new and popular at once -- the first batch of a table, of a feature -- otherwise has
+// thousands of atomics on one word, 12 ns each (65 536 positions, the most popular id a fourteenth of them: 67 -> 27 us; over
+// the workgroup instead, 14 us, but the barriers cost every other call 0.7).
+// miss: the lanes with an id to enter; cell: bits of its hash.  Returns the lane that enters it, and the position in `pos`.
+__device__ __forceinline__ int merge_copies(bool miss, int64_t id, int cell, uint32_t &pos, MetaMerge *s_m)
+{
+    const int lane = lane_id();
+    s_m[lane].slot = miss ? id : -1;
+    s_m[lane].value = (int32_t)pos;
+    if (miss) s_m[cell].winner = (uint32_t)lane;
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    int from = lane;
+    if (miss) {
+        const int o = (int)s_m[cell].winner;
+        if (o != lane && s_m[o].slot == id) {
+            __hip_atomic_fetch_min(&s_m[o].value, (int32_t)pos, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+            from = o;
+        }
+    }
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    pos = (uint32_t)s_m[from].value;
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    return from;
+}
+
 // out[pos, :] <- rows[slot mod num_rows, :] for the positions of the active lanes (Sec. 3.7: the lookup
 // fused with the embedding gather).  The 64 rows are copied by the whole wavefront, consecutive lanes
 // moving consecutive 16-byte (or 4-byte) pieces of a row, several loads in flight per lane.
@@ -982,13 +1018,31 @@ __device__ __forceinline__ void discover_body(const Params &p)
             // the region of the scratch set that serves this table: twice as many entries as the table has positions, so
             // that it can never fill up
             const uint64_t sb = multi ? 2ull * (uint64_t)t_lo : 0, ss = 2ull * (uint64_t)(multi ? t_hi - t_lo : p.n);
-            for (int j = lane; j < nmiss; j += kWave) {
-                const uint32_t pos = s_pos[w][j];
-                const int64_t id = s_id[w][j];
-                const uint32_t e = set_insert(p, id, pos, sb, ss);
-                p.list[seg_base + flushed + j] = pos;
-                p.ent[seg_base + flushed + j] = e;
-                p.list_id[seg_base + flushed + j] = id;
+            // (The copies of an id are merged and leave notes with one table only.  In groups, with batches of 320 K values of
+            // which the new ones are popular, Pass 1 took 21 instead of 17 us with the notes.)
+            constexpr bool NOTE = !MULTI;
+            for (int j0 = 0; j0 < nmiss; j0 += kWave) {
+                const int j = j0 + lane;
+                const bool miss = j < nmiss;
+                const uint32_t pos = miss ? s_pos[w][j] : 0;
+                const int64_t id = miss ? s_id[w][j] : -1;
+                const uint64_t hash = mix64((uint64_t)id ^ kSetSeed);
+                uint32_t e = 0;
+                if constexpr (NOTE) {
+                    uint32_t first = pos;
+                    const int from = merge_copies(miss, id, (int)hash & (kWave - 1), first, reinterpret_cast<MetaMerge *>(s_req[w]));
+                    if (miss && from == lane) e = set_insert<NOTE>(p, id, hash, first, sb, ss);
+                    e = (uint32_t)__shfl((int)e, from);
+                    if (miss && from != lane) p.note[first] = 1;
+                    if (first != pos) e &= ~kEntered;
+                } else if (miss) {
+                    e = set_insert<NOTE>(p, id, hash, pos, sb, ss);
+                }
+                if (miss) {
+                    p.list[seg_base + flushed + j] = pos;
+                    p.ent[seg_base + flushed + j] = e;
+                    p.list_id[seg_base + flushed + j] = id;
+                }
             }
             flushed += nmiss;
         }
@@ -1261,8 +1315,11 @@ constexpr uint32_t kHintUnplaced = 0xFE;   // ran out of slots: falls back to ho
 constexpr uint32_t kHintUnknown = 0xFD;    // placed, but not at a round that fits the hint: search the window
 
 // What k_allocate leaves in first_of for k_finalize: the position of the first occurrence of the entry's id, or, for
-// that position itself, kAgentEntry | hint.
+// that position itself, kAgentEntry | hint, with kAgentOcc if the slot there held an id.  With one table that stands
+// unless a note says that the claim was displaced (or kAgentLook that nobody would have left one).
 constexpr uint32_t kAgentEntry = 0x80000000u;
+constexpr uint32_t kAgentOcc = 0x100u;
+constexpr uint32_t kAgentLook = 0x200u;
 
 // What a claimant's lane leaves in LDS for the lanes that load for it: the address of the identity of the first slot to
 // read, that slot's number, and the claim: the claimant's position and the round that the first slot would be for it.
@@ -1478,9 +1535,18 @@ __device__ __forceinline__ void allocate_body(const Params &p, int64_t vblock, i
             if (j0 >= cnt) break;
             const bool have = j0 + lane < cnt;
             uint32_t first = 0;
+            bool alone = false;
             int f = seg_f;
             if (have) {
-                first = p.set_slot[e];
+                if constexpr (MULTI) {
+                    first = p.set_slot[e];
+                } else {
+                    const uint8_t note = p.note[pos];
+                    first = pos;
+                    if (!(e & kEntered)) first = p.set_slot[e];       // (under way together with the note)
+                    alone = entered_alone(e, note);
+                    if ((e & kEntered) && note) first = p.set_slot[e & ~kEntered];
+                }
                 if (MULTI && !seg_one) f = find_table(p.offsets, p.num_tables, (int64_t)pos);
             }
             const bool elected = have && first == pos;        // else: a later copy of the id
@@ -1506,7 +1572,7 @@ __device__ __forceinline__ void allocate_body(const Params &p, int64_t vblock, i
                 }
                 const int32_t bound = expiry_bound(d, p.step);
                 const bool aligned = (d.N << (3 + d.sh)) > kCachedTableBytes;
-                uint32_t hint = kHintUnplaced;
+                uint32_t hint = kHintUnplaced, occ = 0;
                 // the claimant this lane carries
                 Claimant c;
                 c.active = agent;
@@ -1522,17 +1588,22 @@ __device__ __forceinline__ void allocate_body(const Params &p, int64_t vblock, i
                                                             aligned && !later, s_code, s_req);
                     if (c.active)
                         claim_walk(d, c, st, s_code, s_req, claim_in_table,
-                                   [&](uint32_t who, int32_t round, int64_t, int64_t) {
+                                   [&](uint32_t who, int32_t round, int64_t, int64_t old) {
                                        const uint32_t at = round < (int32_t)kHintUnknown ? (uint32_t)round : kHintUnknown;
-                                       if (who == pos) hint = at;
-                                       else p.hint[who] = (uint8_t)at;
+                                       if (who == pos) {
+                                           hint = at;
+                                           occ = (is_tag(old) ? tag_occ(old) != 0 : old >= 0) ? kAgentOcc : 0u;
+                                       } else {
+                                           p.hint[who] = (uint8_t)at;
+                                       }
+                                       if (!MULTI && is_tag(old)) p.note[tag_pos(old)] = 1;
                                    },
                                    [](uint32_t) {});
                     __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");   // s_code and s_req are written again
                 }
                 if (agent) {
-                    p.hint[pos] = (uint8_t)hint;              // for the copies of the id
-                    p.first_of[idx] = kAgentEntry | hint;
+                    if (!alone) p.hint[pos] = (uint8_t)hint;  // for the copies of the id
+                    p.first_of[idx] = kAgentEntry | (MULTI ? 0u : occ) | hint;
                 }
             }
             __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
@@ -1705,7 +1776,7 @@ __global__ __launch_bounds__(kWave, MULTI ? (T == 8 ? 3 : 4) : T == 8 ? 4 : 5) v
             int f = 0;
             if (have) {
                 pos = p.list[idx];
-                e = p.ent[idx];
+                e = p.ent[idx] & ~kEntered;
                 const int64_t id = p.list_id[idx];
                 first = p.set_slot[e];
                 agent = first == pos;
@@ -1756,7 +1827,7 @@ __global__ __launch_bounds__(kWave, MULTI ? (T == 8 ? 3 : 4) : T == 8 ? 4 : 5) v
                 x = x2;
             }
             if (agent) p.hint[pos] = (uint8_t)hint;
-            if (agent) p.first_of[idx] = kAgentEntry | hint;
+            if (agent) p.first_of[idx] = kAgentEntry | kAgentLook | hint;
             else if (!MULTI && have) p.first_of[idx] = first;     // (several tables: k_allocate has written it)
         }
     }
@@ -1883,7 +1954,7 @@ __global__ __launch_bounds__(kWave) void k_allocate_lru_long(Params p)
             int f = 0;
             if (have) {
                 pos = p.list[idx];
-                e = p.ent[idx];
+                e = p.ent[idx] & ~kEntered;
                 first = p.set_slot[e];
                 agent = first == pos;
                 if (MULTI && agent) {
@@ -1904,7 +1975,7 @@ __global__ __launch_bounds__(kWave) void k_allocate_lru_long(Params p)
                     hint = fr < 0 ? kHintUnplaced : (fr < (int32_t)kHintUnknown ? (uint32_t)fr : kHintUnknown);
             }
             if (agent) p.hint[pos] = (uint8_t)hint;
-            if (agent) p.first_of[idx] = kAgentEntry | hint;
+            if (agent) p.first_of[idx] = kAgentEntry | kAgentLook | hint;
             else if (!MULTI && have) p.first_of[idx] = first;     // (several tables: k_allocate has written it)
         }
     }
@@ -2083,10 +2154,10 @@ __device__ __forceinline__ bool finalize_epilogue(const Params &p, FinalizeState
 }
 
 // Every entry of the miss lists -- the elected position of an id (its agent) and the other copies of
-// the id alike -- finds the slot that carries the agent's claim: where k_allocate left it (the hint,
-// kept under the agent's batch position, which every copy knows), else by a search of the window by
-// the whole wavefront (a claimant displaced after its hint was written).  A copy may find the claim
-// tag or, when the agent has been quicker, already the id.  The agent turns the tag into the id,
+// the id alike -- finds the slot that carries the agent's claim.  With one table the agent knows where it is unless a note
+// says that it was displaced or has copies; else it and its copies look where k_allocate left the claim (the hint, kept
+// under the agent's batch position, which every copy knows), and the whole wavefront searches the window of a claimant
+// displaced after its hint was written.  A copy may find the claim tag or, when the agent has been quicker, already the id.  The agent turns the tag into the id,
 // writes the metadata and accounts for the outcome; every entry stores its output slot.  Entries
 // without a claim fall back to the home slot (Case 3).
 template <bool MULTI>
@@ -2138,12 +2209,17 @@ __device__ __forceinline__ void finalize_body(const Params &p)
             auto is_claim_of = [](int64_t v, uint32_t fst, int64_t cid) {
                 return is_tag(v) ? tag_pos(v) == fst : v == cid;
             };
-            bool search = false;
+            bool search = false, sure = false;
             if (have) {
                 agent = (word & kAgentEntry) != 0;
                 first = agent ? pos : word;
+                if constexpr (!MULTI) {
+                    const uint8_t note = p.note[pos];
+                    if (note) p.note[pos] = 0;                 // no note is left behind
+                    sure = agent && !note && !(word & kAgentLook);
+                }
                 h = agent ? word & 0xFFu : (uint32_t)p.hint[first];
-                p.set_slot[e] = kSetEmpty;                     // the scratch set is left empty again
+                p.set_slot[e & ~kEntered] = kSetEmpty;         // the scratch set is left empty again
                 if (multi) {
                     if (seg_one) {
                         f = seg_f;
@@ -2154,7 +2230,10 @@ __device__ __forceinline__ void finalize_body(const Params &p)
                     }
                 }
                 home = home_slot(id, d.seed, d.N);
-                if (h < kHintUnknown) {
+                if (sure && h < kHintUnknown) {
+                    at = (int)h;
+                    occ = (word & kAgentOcc) ? 1u : 0u;
+                } else if (h < kHintUnknown) {
                     const int64_t v = *id_at(d, wrap(home + (int)h, d.N));
                     if (is_claim_of(v, first, id)) { at = (int)h; occ = tag_occ(v); }
                 }

@@ -363,3 +363,20 @@ def test_probe_blocks_at_the_edges_of_small_tables(slots, layout):
                         assert np.array_equal(out.cpu().numpy(), np.resize(so, count)), (shift, count)
                         assert np.array_equal(found.cpu().numpy(), np.resize(fo, count)), (shift, count)
         t.close()
+
+
+# ---- lists of one table: new ids alone, with copies in their own wavefront and in others, and with displaced claims (the
+# positions stand in any order, so that many a first occurrence comes after a copy; the last table is too small for all)
+@pytest.mark.parametrize("layout", ["separate", "records"])
+@pytest.mark.parametrize("policy", [True, "expiry", False, "lru"])
+@pytest.mark.parametrize("slots,copies", [(2_000_003, 1), (700_001, 3), (90_001, 2)])
+def test_lists_with_copies_and_displaced_claims(slots, copies, policy, layout):
+    rng = rng_for(913 + slots)
+    t = Pair(slots, 12, 1, policy, 37, layout=layout)
+    n = 524_289
+    for step in range(3):
+        ids = rng.integers(0, 1 << 50, size=n // copies)
+        ids = np.concatenate([ids, ids[rng.integers(0, ids.size, size=n - ids.size)], np.repeat(ids[:40], 64)])
+        near = rng.random(ids.size) < 0.5
+        t.step(np.where(near, ids, rng.permutation(ids)), 3 * step)
+    t.close()
