@@ -1032,7 +1032,7 @@ mpzch_status_t mpzch_lookup_gather(const mpzch_table_t *t, const int64_t *identi
         TIMED(t->tm, KLookup, s, launch_lookup_short<true>(p, s));
         return MPZCH_OK;
     }
-    // Seven workgroups of this kernel are resident on a compute unit (22.5 KB of LDS, 72 registers): of eight per unit the
+    // Seven workgroups of this kernel are resident on a compute unit (22.5 KB of LDS, 68 registers): of eight per unit the
     // last starts when another ends.  Where every wavefront has several chunks anyway, four per unit run in one go and
     // have lines enough under way.  Eight / four per unit, us, rows of 256 bytes: 0.7 M ids 67 / 68, 1 M 103 / 98, 2 M
     // 205 / 194, 4 M 417 / 381 (seven: 67, 104, 205, 389, for a wavefront more or less has one chunk more); rows of 64 bytes

@@ -1155,10 +1155,10 @@ __device__ __forceinline__ void discover_body(const Params &p)
     }
 }
 
-// The kernels around the one body.  At least four wavefronts per SIMD are asked for (128 registers); with the 71 to 74
-// registers that training on one table needs six are resident, with the 80 and 98 of a group six and five (41 M values over
-// 26 tables as records, the whole step: held to four 1 221 us, five 1 173, six, with spills, 1 375), of the lookups seven, and
-// of the plain one, held to 64 registers, eight.  Training is bound by memory, and measured within 2 % of its best from three
+// The kernels around the one body.  At least four wavefronts per SIMD are asked for (128 registers); with the 70 to 78
+// registers that training on one table needs six are resident, with the 80 and 96 of a group six and five (41 M values over
+// 26 tables as records, the whole step: held to four 1 221 us, five 1 173, six, with spills, 1 375), of the lookup with gather
+// seven, of the plain ones, held to 64 registers, eight.  Training is bound by memory, and measured within 2 % of its best from three
 // to six wavefronts for both table layouts.
 __global__ __launch_bounds__(kBlock, 4) void k_discover(Params p)
 {
@@ -2303,12 +2303,13 @@ __device__ __forceinline__ void finalize_body(const Params &p)
     if (last) publish_counters<kFinalizeBlock>(p, s_bins);
 }
 
-// Held to 8 wavefronts per SIMD (one table: 50 registers and 66 KB of LDS for 16 wavefronts, several: 63 and 40 KB), so that
+// Held to 8 wavefronts per SIMD (one table: 51 registers and 66 KB of LDS for 16 wavefronts, several: 63 and 40 KB), so that
 // the 8 192 wavefronts, each a chain of three round trips, run in one go.  (Several tables with 66 registers and the rows'
 // buffer that only one table has use for: one workgroup per compute unit and two turns, 41 M values over 26 tables 152 -> 145
 // us.)  A batch of 4 M positions, 10 % of them new, with
 // the row reset: 56 -> 46 us by the ids in the miss lists (a line read for each of them before), one store for id and
-// metadata of a record, and rows reset before the workgroup's barrier instead of behind it; 41 M values over 26 tables
+// metadata of a record, and rows reset before the workgroup's barrier instead of behind it, 45.5 -> 41 us by the claims that
+// need no look; 41 M values over 26 tables
 // 242 -> 178 us.
 template <bool MULTI>
 __global__ __launch_bounds__(kFinalizeBlock, 8) void k_finalize(Params p)

@@ -47,25 +47,33 @@ __device__ __forceinline__ void store_piece(VEC v, VEC *at)
 }
 
 // How gather and apply share out the pieces of a list: to as many workgroups as have kPieces for each thread, of those that
-// the grid has (it is sized for the list's capacity).  A thread with fewer reads the first one again for what is missing:
-// with one each the gather of 28 000 rows of 256 bytes took 7.4 instead of 5.9 us.  Up to four times as many workgroups as
-// run at a time, or the last ones end late: gather + apply of 2 M rows of 256 bytes 552 -> 532 us, of 128 bytes 314 -> 304.
+// the grid has (it is sized for the list's capacity), and in as many turns for all of them alike.  A thread with fewer reads
+// the first one again for what is missing: with one each the gather of 28 000 rows of 256 bytes took 7.4 instead of 5.9 us.
+// Up to four times as many workgroups as run at a time, or the last ones end late: gather + apply of 2 M rows of 256 bytes
+// 552 -> 532 us, of 128 bytes 314 -> 304.  More of them would be there for short lists in large areas, too (1 000 rows of
+// 256 bytes, room for 2 M: 10 -> 20 us with four times as many).
+// What a workgroup moves in one turn lies side by side, so that all that are under way work on one stretch of the list,
+// instead of each on four that are a turn apart: gather + apply of 0.6 M rows of 256 bytes 99 -> 96 us, 2 M 519 -> 497, 4 M
+// 1 046 -> 953, 1 M of 512 bytes 484 -> 462, of 64 bytes the same.
 // (The resets have no second access to fill with, and the strides that depend on the count cost them more.)
 constexpr int64_t kMoverBlocks = 8192;
 struct Share {
-    int64_t first, stride;
+    int64_t first, turn;         // this thread's first piece; from one turn to the next
     __device__ __forceinline__ explicit Share(int64_t total)
     {
-        const int64_t need = (total + kBlock * kPieces - 1) / (kBlock * kPieces);
-        const int64_t blocks = need < (int64_t)gridDim.x ? need : (int64_t)gridDim.x;
-        stride = blocks * kBlock;
-        first = (int64_t)blockIdx.x < blocks ? (int64_t)blockIdx.x * kBlock + threadIdx.x : total;
+        // (32 bits: 2^32 times 1 024 pieces of four bytes are more than the GPU's memory)
+        const uint32_t need = (uint32_t)((total + kBlock * kPieces - 1) / (kBlock * kPieces));
+        const uint32_t turns = need > gridDim.x ? (need + gridDim.x - 1) / gridDim.x : 1;
+        const int64_t blocks = turns > 1 ? (need + turns - 1) / turns : need;
+        turn = blocks * kBlock * kPieces;
+        first = (int64_t)blockIdx.x < blocks ? (int64_t)blockIdx.x * kBlock * kPieces + threadIdx.x : total;
     }
 };
 struct PieceWalk {
     int64_t k, dk;               // row
     uint32_t c, dc, chunks;      // piece of it
-    // (first and stride are numbers of threads of a grid: 32 bits, which a division takes a tenth of the time of 64)
+    // (first and stride are numbers of threads of a grid, or of their pieces in a turn: 32 bits, which a division takes a tenth
+    // of the time of 64)
     __device__ __forceinline__ PieceWalk(uint32_t first, uint32_t stride, int32_t chunks_per_row)
     {
         chunks = (uint32_t)chunks_per_row;
@@ -74,6 +82,15 @@ struct PieceWalk {
         c = first - q * chunks;
         dk = dq;
         dc = stride - dq * chunks;
+    }
+    // the same place, to go on by one workgroup's threads
+    __device__ __forceinline__ PieceWalk by_block() const
+    {
+        PieceWalk w = *this;
+        const uint32_t q = (uint32_t)kBlock / chunks;
+        w.dk = q;
+        w.dc = (uint32_t)kBlock - q * chunks;
+        return w;
     }
     __device__ __forceinline__ void next()
     {
@@ -264,16 +281,16 @@ __global__ __launch_bounds__(kBlock) void k_gather_rows(const int64_t *slots, co
 {
     const int64_t total = listed(count_dev, cap) * chunks;
     const Share share(total);
-    const int64_t first = share.first, stride = share.stride;
-    if (first >= total) return;
-    PieceWalk at((uint32_t)first, (uint32_t)stride, chunks);
-    for (int64_t i = first; i < total; i += kPieces * stride) {
+    if (share.first >= total) return;
+    PieceWalk turn((uint32_t)share.first, (uint32_t)share.turn, chunks);
+    for (int64_t i = share.first; i < total; i += share.turn, turn.next()) {
+        PieceWalk at = turn.by_block();
         int64_t s[kPieces];
         uint32_t c[kPieces];
         VEC v[kPieces];
 #pragma unroll
         for (int u = 0; u < kPieces; ++u) {
-            s[u] = slots[i + u * stride < total ? at.k : 0];
+            s[u] = slots[i + u * kBlock < total ? at.k : 0];
             c[u] = at.c;
             at.next();
         }
@@ -282,7 +299,7 @@ __global__ __launch_bounds__(kBlock) void k_gather_rows(const int64_t *slots, co
             v[u] = load_piece(reinterpret_cast<const VEC *>(rows + (s[u] >= 0 ? row_of(mod, s[u]) : 0) * row_stride_bytes) + c[u]);
 #pragma unroll
         for (int u = 0; u < kPieces; ++u)
-            if (i + u * stride < total) out[i + u * stride] = s[u] >= 0 ? v[u] : VEC(0);
+            if (i + u * kBlock < total) out[i + u * kBlock] = s[u] >= 0 ? v[u] : VEC(0);
     }
 }
 
@@ -298,18 +315,18 @@ __global__ __launch_bounds__(kBlock) void k_apply_delta_rows(int64_t num_slots, 
 {
     const int64_t total = listed(count_dev, cap) * chunks;
     const Share share(total);
-    const int64_t first = share.first, stride = share.stride;
-    if (first >= total) return;
-    PieceWalk at((uint32_t)first, (uint32_t)stride, chunks);
-    for (int64_t i = first; i < total; i += kPieces * stride) {
+    if (share.first >= total) return;
+    PieceWalk turn((uint32_t)share.first, (uint32_t)share.turn, chunks);
+    for (int64_t i = share.first; i < total; i += share.turn, turn.next()) {
+        PieceWalk at = turn.by_block();
         int64_t s[kPieces];
         uint32_t c[kPieces];
         VEC v[kPieces];
 #pragma unroll
         for (int u = 0; u < kPieces; ++u) {
-            const bool in = i + u * stride < total;
+            const bool in = i + u * kBlock < total;
             s[u] = slots[in ? at.k : 0];
-            v[u] = delta_rows[in ? i + u * stride : 0];
+            v[u] = delta_rows[in ? i + u * kBlock : 0];
             if (!in) s[u] = -1;
             c[u] = at.c;
             at.next();

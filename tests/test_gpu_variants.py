@@ -267,6 +267,30 @@ def test_row_movers_share_out_their_pieces(count, cap, dim):
     assert torch.equal(a, want)
 
 
+# ---- gather and apply in two and three turns of the largest grid (8 192 workgroups of 1 024 pieces), the last one ragged
+@pytest.mark.parametrize("dim,pieces", [(5, 5), (12, 3), (64, 16)])
+@pytest.mark.parametrize("turns", [1, 2])
+def test_row_movers_take_turns(turns, dim, pieces):
+    count = turns * 8_192 * 1_024 // pieces + 77
+    rows_n = count + 11
+    gen = torch.Generator(device="cuda").manual_seed(914)
+    slots = torch.randperm(rows_n, generator=gen, device="cuda")[:count]
+    slots[count // 3] = -1
+    valid = slots >= 0
+    n = torch.tensor([count], dtype=torch.int64, device="cuda")
+    src = torch.arange(rows_n * dim, dtype=torch.int32, device="cuda").view(torch.float32).reshape(rows_n, dim)
+    out = torch.full((count, dim), 7.0, device="cuda")
+    mp.mpzch_gather_rows(slots, n, src, out)
+    want = torch.where(valid[:, None], src[slots.clamp(min=0)], torch.zeros((), device="cuda"))
+    assert torch.equal(out.view(torch.int32), want.view(torch.int32))
+    ident, dst = torch.full((rows_n,), -1, dtype=torch.int64, device="cuda"), torch.zeros_like(src)
+    mp.mpzch_apply_delta(ident, slots, slots + 5, n, dst, out)
+    want = torch.zeros_like(src)
+    want[slots[valid]] = src[slots[valid]]
+    assert torch.equal(dst.view(torch.int32), want.view(torch.int32))
+    del want
+
+
 # ---- LRU claims: one group of lanes per claimant, listed per workgroup where every wavefront has one chunk
 @pytest.mark.parametrize("layout", ["separate", "records"])
 @pytest.mark.parametrize("slots,probe", [(3, 8), (700, 1), (900, 8), (3_001, 9), (3_001, 16), (5_003, 31), (5_003, 33), (5_003, 64),
