@@ -1681,55 +1681,80 @@ __device__ __forceinline__ int32_t group_min(int32_t x)
     return min_with<0x141>(x);                       // row_half_mirror: 8 lanes
 }
 
+// The slots of a window as a mask, bit 8 t + r for lane r's slot t; its union over the 8 lanes of a group, in every lane.
+template <int T>
+using LruMask = std::conditional_t<(T <= 4), uint32_t, uint64_t>;
+template <int CTRL>
+__device__ __forceinline__ uint32_t or_with(uint32_t x)
+{
+    return x | (uint32_t)__builtin_amdgcn_update_dpp((int)x, (int)x, CTRL, 0xF, 0xF, false);
+}
+__device__ __forceinline__ uint32_t group_or(uint32_t x) { return or_with<0x141>(or_with<0x4E>(or_with<0xB1>(x))); }
+__device__ __forceinline__ uint64_t group_or(uint64_t x)
+{
+    return (uint64_t)group_or((uint32_t)(x >> 32)) << 32 | group_or((uint32_t)x);
+}
+
 // active, cpos and home are uniform within a group, x: what its lanes have read of the window.  placed(pos, choice, round,
 // slot, old) is called for every claim that stands, old being what the slot held before; lost(pos) for a claimant that
 // has run out of slots; both by all lanes of the group.
+//
+// The list is drawn class by class: the empty slots, then those of the oldest time stamp, of the next one and so on.  A class is
+// a mask that all lanes of the group hold, so its choices, and the first `choice` ones that a displaced claimant has behind
+// it, cost no exchange between lanes.  (Each choice drawn by three minima over the group, from the first one again for every
+// displaced claimant: 12 547 positions on 6 964 slots, windows of 32, 140 -> 99 us; calls of 300 007 on 60 M slots 11.15 -> 10.95.)
 template <int T, bool REC, typename Placed, typename Lost>
 __device__ __forceinline__ void claim_group_lru(const Params &p, const Tab &d, bool active, uint32_t cpos, int64_t home,
                                                 LruSlots<T> x, Placed placed, Lost lost)
 {
-    constexpr int32_t kNone = 0x7FFFFFFF;
+    using Mask = LruMask<T>;
+    constexpr int32_t kNone = 0x7FFFFFFF, kEmpties = -0x7FFFFFFF - 1;
     const int lane = lane_id();
     const int r = lane % kLruG, gbase = lane - r;
     int32_t choice = 0;
     while (__any(active)) {
-        uint32_t empties = 0, evictable = 0;         // bit t: the slot of round 8 t + r is empty / may be evicted and has not been drawn
+        Mask empties = 0;
+        uint32_t evictable = 0;                      // bit t: the slot of round 8 t + r may be evicted
 #pragma unroll
         for (int t = 0; t < T; ++t) {
             const bool in = active && kLruG * t + r < d.P;
             const bool occ = is_tag(x.v[t]) ? tag_occ(x.v[t]) != 0 : x.v[t] >= 0;     // it held an id when the call began
-            if (in && !occ) empties |= 1u << t;
+            if (in && !occ) empties |= (Mask)1 << (kLruG * t + r);
             if (in && occ && x.m[t] != p.step) evictable |= 1u << t;
         }
-        int32_t drawn = 0;
+        Mask left = group_or(empties);               // of the present class: the slots that have not been drawn
+        int32_t stamp = kEmpties;                    // ... and its time stamp
+        int32_t skip = choice;
         int64_t displaced = 0;
         bool trying = active;
-        while (__any(trying)) {
-            // the first empty slot; without one the oldest time stamp's first round
-            const int32_t empty = group_min(empties ? kLruG * (__ffs(empties) - 1) + r : kNone);
-            int32_t oldest = kNone;
+        while (trying) {                             // (whole groups)
+            bool none = false;
+            for (;;) {
+                const int32_t count = sizeof(Mask) == 4 ? __popc((uint32_t)left) : __popcll(left);
+                if (skip < count) break;
+                skip -= count;
+                int32_t next = kNone;
 #pragma unroll
-            for (int t = 0; t < T; ++t)
-                if ((evictable >> t & 1u) && x.m[t] < oldest) oldest = x.m[t];
-            oldest = group_min(oldest);
-            int32_t old_round = kNone;
+                for (int t = 0; t < T; ++t)
+                    if ((evictable >> t & 1u) && x.m[t] > stamp && x.m[t] < next) next = x.m[t];
+                next = group_min(next);
+                none = next == kNone;
+                if (none) break;
+                stamp = next;
+                left = 0;
 #pragma unroll
-            for (int t = T - 1; t >= 0; --t)
-                if ((evictable >> t & 1u) && x.m[t] == oldest) old_round = kLruG * t + r;
-            old_round = group_min(old_round);
-            const bool was_empty = empty != kNone;
-            const int32_t round = was_empty ? empty : old_round;
-            if (trying && round == kNone) {
+                for (int t = 0; t < T; ++t)
+                    if ((evictable >> t & 1u) && x.m[t] == next) left |= (Mask)1 << (kLruG * t + r);
+                left = group_or(left);
+            }
+            if (none) {
                 lost(cpos);
-                trying = false;
+                break;
             }
-            if (!trying) continue;
-            if (round % kLruG == r) {
-                empties &= ~(1u << (round / kLruG));
-                evictable &= ~(1u << (round / kLruG));
-            }
-            if (drawn++ < choice) continue;
-            const int64_t mine = make_tag((uint32_t)choice, cpos, was_empty ? 0u : 1u);
+            for (; skip > 0; --skip) left &= left - 1;
+            const int32_t round = __ffsll((unsigned long long)left) - 1;
+            left &= left - 1;
+            const int64_t mine = make_tag((uint32_t)choice, cpos, stamp == kEmpties ? 0u : 1u);
             const int64_t s = wrap(home + round, d.N);
             int64_t old = 0;
             if (r == 0) old = __hip_atomic_fetch_min(id_at(d, s), mine, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
