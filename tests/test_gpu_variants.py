@@ -404,3 +404,19 @@ def test_lists_with_copies_and_displaced_claims(slots, copies, policy, layout):
         near = rng.random(ids.size) < 0.5
         t.step(np.where(near, ids, rng.permutation(ids)), 3 * step)
     t.close()
+
+
+# ---- whether the scratch set is read back or the notes decide, on both sides of the lines and with few and many misses
+@pytest.mark.parametrize("evict", [True, False])
+@pytest.mark.parametrize("n", [32_768, 32_769, 131_072, 131_073])
+def test_first_occurrences_read_back_or_noted(n, evict):
+    rng = rng_for(915)
+    t = Pair(3 * n, 24, 1, evict, 41, layout="records")
+    old = rng.integers(0, 1 << 50, size=n)
+    for step, share in enumerate([1.0, 0.4, 0.7]):
+        new = rng.integers(0, 1 << 50, size=n)
+        ids = np.where(rng.random(n) < share, new, old)
+        ids[rng.random(n) < 0.1] = ids[0]
+        t.step(rng.permutation(np.concatenate([ids[: n // 2], ids[rng.integers(0, n, size=n - n // 2)]])), step)
+        old = ids
+    t.close()
