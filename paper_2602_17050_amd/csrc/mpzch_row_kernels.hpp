@@ -83,14 +83,16 @@ struct PieceWalk {
         dk = dq;
         dc = stride - dq * chunks;
     }
-    // the same place, to go on by one workgroup's threads
-    __device__ __forceinline__ PieceWalk by_block() const
+    // (one division, where there is another turn: lists of one turn are short)
+    __device__ __forceinline__ void skip(uint32_t pieces)
     {
-        PieceWalk w = *this;
-        const uint32_t q = (uint32_t)kBlock / chunks;
-        w.dk = q;
-        w.dc = (uint32_t)kBlock - q * chunks;
-        return w;
+        const uint32_t q = pieces / chunks;
+        k += q;
+        c += pieces - q * chunks;
+        if (c >= chunks) {
+            c -= chunks;
+            ++k;
+        }
     }
     __device__ __forceinline__ void next()
     {
@@ -282,9 +284,8 @@ __global__ __launch_bounds__(kBlock) void k_gather_rows(const int64_t *slots, co
     const int64_t total = listed(count_dev, cap) * chunks;
     const Share share(total);
     if (share.first >= total) return;
-    PieceWalk turn((uint32_t)share.first, (uint32_t)share.turn, chunks);
-    for (int64_t i = share.first; i < total; i += share.turn, turn.next()) {
-        PieceWalk at = turn.by_block();
+    PieceWalk at((uint32_t)share.first, kBlock, chunks);
+    for (int64_t i = share.first; i < total; i += share.turn) {
         int64_t s[kPieces];
         uint32_t c[kPieces];
         VEC v[kPieces];
@@ -300,6 +301,7 @@ __global__ __launch_bounds__(kBlock) void k_gather_rows(const int64_t *slots, co
 #pragma unroll
         for (int u = 0; u < kPieces; ++u)
             if (i + u * kBlock < total) out[i + u * kBlock] = s[u] >= 0 ? v[u] : VEC(0);
+        if (i + share.turn < total) at.skip((uint32_t)share.turn - kBlock * kPieces);
     }
 }
 
@@ -316,9 +318,8 @@ __global__ __launch_bounds__(kBlock) void k_apply_delta_rows(int64_t num_slots, 
     const int64_t total = listed(count_dev, cap) * chunks;
     const Share share(total);
     if (share.first >= total) return;
-    PieceWalk turn((uint32_t)share.first, (uint32_t)share.turn, chunks);
-    for (int64_t i = share.first; i < total; i += share.turn, turn.next()) {
-        PieceWalk at = turn.by_block();
+    PieceWalk at((uint32_t)share.first, kBlock, chunks);
+    for (int64_t i = share.first; i < total; i += share.turn) {
         int64_t s[kPieces];
         uint32_t c[kPieces];
         VEC v[kPieces];
@@ -335,6 +336,7 @@ __global__ __launch_bounds__(kBlock) void k_apply_delta_rows(int64_t num_slots, 
         for (int u = 0; u < kPieces; ++u)
             if (s[u] >= 0 && s[u] < num_slots)
                 store_piece(v[u], reinterpret_cast<VEC *>(rows + row_of(mod, s[u]) * row_stride_bytes) + c[u]);
+        if (i + share.turn < total) at.skip((uint32_t)share.turn - kBlock * kPieces);
     }
 }
 
