@@ -3,6 +3,7 @@ header declares, and rejects bad arguments before touching a device."""
 import ctypes
 import os
 import re
+import subprocess
 
 import pytest
 
@@ -117,3 +118,20 @@ def test_group_create_validates_arguments(binding):
 def test_missing_library_fails_loudly(binding, tmp_path):
     with pytest.raises(FileNotFoundError):
         binding.load_library(str(tmp_path / "libmpzch.so"))
+
+
+# A kernel's arguments are passed on as its parameters' types: a wrong pointer or a number that would lose bits must not
+# compile (syntax only, host side)
+@pytest.mark.parametrize("args,ok", [("(int32_t *)nullptr, (int64_t)5, (int32_t)7", True),
+                                     ("(int32_t *)nullptr, (int64_t)5, (int64_t)7", False),
+                                     ("(int64_t *)nullptr, (int64_t)5, (int32_t)7", False),
+                                     ("(const int32_t *)nullptr, (int64_t)5, (int32_t)7", False)])
+def test_launch_takes_only_arguments_that_fit(tmp_path, args, ok):
+    from paper_2602_17050_amd import build
+    src = tmp_path / "probe.hip"
+    src.write_text('#include "mpzch.hip"\n'
+                   f"static mpzch_status_t probe() {{ return launch(k_fill32, 1, 64, hipStream_t(nullptr), {args}); }}\n"
+                   "void *probe_used = (void *)probe;\n")
+    r = subprocess.run([build.hipcc(), "--offload-arch=gfx950", "-std=c++17", "--offload-host-only", "-fsyntax-only",
+                        "-I", os.path.dirname(build.SRC), "-x", "hip", str(src)], capture_output=True, text=True)
+    assert (r.returncode == 0) == ok, r.stderr[-2000:]
