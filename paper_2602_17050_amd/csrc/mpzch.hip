@@ -448,8 +448,24 @@ mpzch_status_t launch_discover_chunk(const Params &p, int grid, hipStream_t s)
     return MPZCH_OK;
 }
 
+// Calls of so many workgroups of 256 positions read the scratch set back (k_allocate_chunk says why).  Measured on 256 compute
+// units, loads of new ids by the notes alone / with the set read back, us, two calls into a table that ends 0.4 full, windows of
+// 16 slots, records: 50 K ids 60.3 / 60.0, 57 K 69.2 / 63.5, 66 K 75.4 / 64.7, 100 K 93.2 / 77.3, 131 K 105.7 / 88.5, 145 K 87.4 /
+// 91.1, 200 K 105.9 / 110.9; one call, 0.2 full, 30.5 / 31.0, 34.8 / 33.5, 40.1 / 35.0, 48.1 / 40.2, 53.0 / 46.1, 45.7 / 47.5, 53.9 /
+// 56.0; eight calls, 0.95 full, 222 / 225, 243 / 235, 283 / 252, 324 / 286, 373 / 341, 344 / 350, 406 / 425; windows of 64 and
+// two tensors have the same lines.  (Below 50 K the read costs what it is, 1 to 2 %.)
+constexpr bool read_back_groups(int64_t groups, int num_cus) { return 8 * groups > 7 * (int64_t)num_cus && groups <= 2 * (int64_t)num_cus; }
+
+template <bool REC>
+mpzch_status_t launch_allocate_chunk(const Params &p, int grid, int num_cus, hipStream_t s)
+{
+    if (read_back_groups(grid, num_cus)) TRY(launch(k_allocate_chunk<REC, true>, grid, kBlock, s, p));
+    else TRY(launch(k_allocate_chunk<REC, false>, grid, kBlock, s, p));
+    return MPZCH_OK;
+}
+
 // One chunk per wavefront (mpzch_chunk_kernels.hpp): grid = workgroups of 256 positions.
-mpzch_status_t launch_remap_chunks(Timing &tm, const Params &p, int32_t max_p_lru, int grid, hipStream_t s)
+mpzch_status_t launch_remap_chunks(Timing &tm, const Params &p, int32_t max_p_lru, int grid, int num_cus, hipStream_t s)
 {
     const bool rec = p.t0.sh != 0;
     if (!tm.begin(KDiscover, s)) return MPZCH_ERR_HIP;
@@ -458,8 +474,8 @@ mpzch_status_t launch_remap_chunks(Timing &tm, const Params &p, int32_t max_p_lr
     if (!tm.end(s) || !tm.begin(KAllocate, s)) return MPZCH_ERR_HIP;
     if (max_p_lru > 0 && rec) TRY(launch_allocate_lru_chunk<true>(max_p_lru, p, grid, s));
     else if (max_p_lru > 0) TRY(launch_allocate_lru_chunk<false>(max_p_lru, p, grid, s));
-    else if (rec) TRY(launch(k_allocate_chunk<true>, grid, kBlock, s, p));
-    else TRY(launch(k_allocate_chunk<false>, grid, kBlock, s, p));
+    else if (rec) TRY(launch_allocate_chunk<true>(p, grid, num_cus, s));
+    else TRY(launch_allocate_chunk<false>(p, grid, num_cus, s));
     if (!tm.end(s) || !tm.begin(KFinalize, s)) return MPZCH_ERR_HIP;
     TRY(launch(k_finalize_chunk, kPublishTasks + grid, kBlock, s, p));
     if (!tm.end(s)) return MPZCH_ERR_HIP;
@@ -487,7 +503,7 @@ mpzch_status_t launch_remap(Scratch &sc, Timing &tm, Params p, int32_t max_p_lru
     // (the LRU policy with windows of more than 64 slots gives a claimant the whole wavefront)
     if (p.num_tables == 1 && max_p_lru <= kWave && groups <= (int64_t)sc.num_cus * discover_blocks_per_cu() &&
         p.n <= kChunkMaxBatch)
-        return launch_remap_chunks(tm, p, max_p_lru, (int)groups, s);
+        return launch_remap_chunks(tm, p, max_p_lru, (int)groups, sc.num_cus, s);
 
     const int64_t num_chunks = (p.n + kWave - 1) / kWave;
     // k_discover: every wavefront owns one segment of seg_chunks 64-position chunks

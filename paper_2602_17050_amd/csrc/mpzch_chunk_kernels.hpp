@@ -258,15 +258,13 @@ __device__ __forceinline__ void note_place(const Params &p, uint32_t pos, uint32
     __hip_atomic_fetch_max(&p.place[pos], place, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
-// Between these numbers of positions (half a workgroup and two per compute unit) a wavefront of which most have missed reads the
-// set back for all of them, notes or not: such calls' claimants otherwise read their windows all at the same time, before any
-// claim stands, and meet in the claims instead.  Loads into tables of five times as many slots, two calls, us, by the notes /
-// read back: 66 K ids 69 / 61, 100 K 85 / 77, 131 K 99 / 85, 200 K 106 / 109, 262 K 124 / 125; twelve steps of 20 011 positions
-// 317 / 319.
-constexpr int64_t kReadBackLeast = (int64_t)1 << 15;
-constexpr int64_t kReadBackMost = (int64_t)1 << 17;
-
-template <bool REC>
+// READ_BACK: a wavefront of which most have missed reads the set back for all of them, notes or not: calls of about one to two
+// workgroups per compute unit (read_back_groups).  There the claims of all wavefronts, if they read their
+// windows at once, go out within a microsecond or two, and the atomics then run at 9 instead of 27 G/s: 131 000 new ids in a
+// table of five times as many slots, the same 151 K atomics either way (0.3 % apart), of which each wavefront waits 15 us for
+// its first and k_allocate_chunk takes 22.7 us (14 to 28); with the set read in front 17.7.  From 145 000 ids on the wait is 5.5
+// us without it.  Why a burst of that length is slow, and longer ones are not, is not known.
+template <bool REC, bool READ_BACK>
 __global__ __launch_bounds__(kBlock, 4) void k_allocate_chunk(Params p)
 {
     __shared__ __attribute__((aligned(16))) uint8_t s_code[kWavesPerBlock][kWave * kAllocG];
@@ -283,7 +281,7 @@ __global__ __launch_bounds__(kBlock, 4) void k_allocate_chunk(Params p)
     const uint8_t note = in ? p.note[pos] : 0;
     const bool have = e != kNoEntry;
     uint32_t first = 0;
-    const bool read_back = p.n > kReadBackLeast && p.n <= kReadBackMost && __popcll(__ballot(have)) > kWave / 2;
+    const bool read_back = READ_BACK && __popcll(__ballot(have)) > kWave / 2;
     if (have) first = first_occurrence(p, (uint32_t)pos, e, read_back ? 1 : note);
     else start = kStartNever;
 

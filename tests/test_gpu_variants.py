@@ -408,7 +408,7 @@ def test_lists_with_copies_and_displaced_claims(slots, copies, policy, layout):
 
 # ---- whether the scratch set is read back or the notes decide, on both sides of the lines and with few and many misses
 @pytest.mark.parametrize("evict", [True, False])
-@pytest.mark.parametrize("n", [32_768, 32_769, 131_072, 131_073])
+@pytest.mark.parametrize("n", [32_768, 32_769, 57_344, 57_345, 131_072, 131_073])
 def test_first_occurrences_read_back_or_noted(n, evict):
     rng = rng_for(915)
     t = Pair(3 * n, 24, 1, evict, 41, layout="records")
