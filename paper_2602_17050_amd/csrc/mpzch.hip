@@ -541,7 +541,8 @@ bool records_ok(const int64_t *identities, const int32_t *metadata)
 {
     return !((uintptr_t)identities & 15) && (const void *)metadata == (const void *)((const int32_t *)identities + 2);
 }
-// the kernels keep the address of a slot in 48 bits (device addresses have no more)
+// no device address of this GPU has more than 48 bits: a pointer that cannot be one is refused here instead of faulting in a
+// kernel
 bool addresses_ok(const TableCfg &c, const int64_t *identities)
 {
     const uint64_t bytes = (uint64_t)c.num_slots << (c.layout == MPZCH_LAYOUT_RECORDS ? 4 : 3);

@@ -544,7 +544,6 @@ struct alignas(16) ProbeReq {
     int64_t id;
     uint64_t where;
 };
-constexpr int kWhereAddrBits = 48;     // (device addresses have no more)
 
 // The reads of one pass: 64 blocks of 8 slots, 1 << m of them side by side for each request; 8 lanes read one block, and
 // lane_bytes is how far this lane's slot lies from its request's first one.  rows: how many of the blocks anybody asks for.

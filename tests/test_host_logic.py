@@ -64,7 +64,7 @@ def test_create_validates_arguments_without_a_gpu(binding):
 
 def test_entry_points_reject_bad_arguments_before_touching_the_gpu(binding):
     """Checks that run before the first HIP call: NULL handles and required pointers, sizes out of range, a slot
-    count beyond MPZCH_MAX_SLOTS, a table that would reach past the 48 bits the kernels keep of an address."""
+    count beyond MPZCH_MAX_SLOTS, a table that would reach past the 48 bits that a device address has."""
     b = binding
     lib = b.load_library()
     vp = ctypes.c_void_p
