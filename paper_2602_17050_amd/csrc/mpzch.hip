@@ -360,14 +360,35 @@ mpzch_status_t launch_allocate_lru(int32_t max_p_lru, const Params &p, int grid,
     return MPZCH_OK;
 }
 
-// the same where every wavefront has one chunk (max_p_lru <= 64)
-template <bool REC>
-mpzch_status_t launch_allocate_lru_chunk(int32_t max_p_lru, const Params &p, int grid, hipStream_t s)
+// The same where every wavefront has one chunk (max_p_lru <= 64).  Threads that serve the up to 256 claimants of a workgroup:
+// 1 024 while there is one workgroup per compute unit, 512 up to two, with windows of up to 16 slots (48 and 57 registers)
+// up to five, and 256 beyond, where more of them only keep other workgroups out.  Full tables, ten steps of mostly claimants that
+// contend, us, 256 / 512 / 1 024 threads: 15 194 positions, windows of 8, 485 / 366 / 345, of 16 720 / 524 / 470, of 32
+// 1 205 / 830 / 730, of 64 2 220 / - / 1 320; 100 000 positions, of 8 543 / 424 / -, of 64 2 260 / 1 590 / -; 200 000, of 8
+// 517 / 456 / -, 300 000 604 / 582 / -, 400 000 660 / 647 / -.  Steps of which a tenth are claimants, on 30 M slots: 65 000
+// positions 21.5 / 21.4 / 21.6 (8), 25.0 / 25.7 / 25.1 (32); 200 000, 30.7 / 29.8 / 33.1 (8), 38.1 / 41.8 / - (32); 300 000,
+// 39.7 / 40.5 / - (8); 500 000, 56.1 / 57.9 / - (8).
+template <int T>
+constexpr int lru_chunk_threads(int grid, int num_cus)
 {
-    if (max_p_lru <= 8) TRY(launch(k_allocate_lru_chunk<1, REC>, grid, kBlock, s, p));
-    else if (max_p_lru <= 16) TRY(launch(k_allocate_lru_chunk<2, REC>, grid, kBlock, s, p));
-    else if (max_p_lru <= 32) TRY(launch(k_allocate_lru_chunk<4, REC>, grid, kBlock, s, p));
-    else TRY(launch(k_allocate_lru_chunk<8, REC>, grid, kBlock, s, p));
+    return grid <= num_cus ? 4 * kBlock : grid <= (T <= 2 ? 5 : 2) * num_cus ? 2 * kBlock : kBlock;
+}
+template <int T, bool REC>
+mpzch_status_t launch_allocate_lru_chunk(const Params &p, int grid, int num_cus, hipStream_t s)
+{
+    const int threads = lru_chunk_threads<T>(grid, num_cus);
+    if (threads == 4 * kBlock) TRY(launch(k_allocate_lru_chunk<T, REC, 4 * kBlock>, grid, threads, s, p));
+    else if (threads == 2 * kBlock) TRY(launch(k_allocate_lru_chunk<T, REC, 2 * kBlock>, grid, threads, s, p));
+    else TRY(launch(k_allocate_lru_chunk<T, REC, kBlock>, grid, threads, s, p));
+    return MPZCH_OK;
+}
+template <bool REC>
+mpzch_status_t launch_allocate_lru_chunk(int32_t max_p_lru, const Params &p, int grid, int num_cus, hipStream_t s)
+{
+    if (max_p_lru <= 8) TRY(launch_allocate_lru_chunk<1, REC>(p, grid, num_cus, s));
+    else if (max_p_lru <= 16) TRY(launch_allocate_lru_chunk<2, REC>(p, grid, num_cus, s));
+    else if (max_p_lru <= 32) TRY(launch_allocate_lru_chunk<4, REC>(p, grid, num_cus, s));
+    else TRY(launch_allocate_lru_chunk<8, REC>(p, grid, num_cus, s));
     return MPZCH_OK;
 }
 
@@ -472,8 +493,8 @@ mpzch_status_t launch_remap_chunks(Timing &tm, const Params &p, int32_t max_p_lr
     if (window_shift(p.t0.P) == 1 && 2 * p.n <= kShortBlocks) TRY(launch_discover_chunk<1>(p, grid, s));
     else TRY(launch_discover_chunk<0>(p, grid, s));
     if (!tm.end(s) || !tm.begin(KAllocate, s)) return MPZCH_ERR_HIP;
-    if (max_p_lru > 0 && rec) TRY(launch_allocate_lru_chunk<true>(max_p_lru, p, grid, s));
-    else if (max_p_lru > 0) TRY(launch_allocate_lru_chunk<false>(max_p_lru, p, grid, s));
+    if (max_p_lru > 0 && rec) TRY(launch_allocate_lru_chunk<true>(max_p_lru, p, grid, num_cus, s));
+    else if (max_p_lru > 0) TRY(launch_allocate_lru_chunk<false>(max_p_lru, p, grid, num_cus, s));
     else if (rec) TRY(launch_allocate_chunk<true>(p, grid, num_cus, s));
     else TRY(launch_allocate_chunk<false>(p, grid, num_cus, s));
     if (!tm.end(s) || !tm.begin(KFinalize, s)) return MPZCH_ERR_HIP;

@@ -321,13 +321,14 @@ __global__ __launch_bounds__(kBlock, 4) void k_allocate_chunk(Params p)
     leave_outcomes<kWavesPerBlock>(p, have && first == (uint32_t)pos, inserted, evicted, slot, s_red);
 }
 
-// The claims under the LRU policy (max_probe <= 8 T <= 64).  The workgroup first lists its claimants, so that its 32
-// groups of lanes get them evenly: a wavefront of 64 positions has a handful, which it would serve one or two at a time
-// (300 007 positions, 10 % of them claimants with windows of 32 slots: 43 -> 16 us).
-template <int T, bool REC>
-__global__ __launch_bounds__(kBlock, T == 8 ? 4 : 6) void k_allocate_lru_chunk(Params p)
+// The claims under the LRU policy (max_probe <= 8 T <= 64).  The workgroup first lists its claimants, so that its groups of
+// 8 lanes get them evenly: a wavefront of 64 positions has a handful, which it would serve one or two at a time
+// (300 007 positions, 10 % of them claimants with windows of 32 slots: 43 -> 16 us).  Claimants beyond the groups wait for
+// the first ones' chains, so the workgroup is as large as the compute unit has room for (lru_chunk_threads).
+template <int T, bool REC, int THREADS>
+__global__ __launch_bounds__(THREADS, T == 8 || THREADS > kBlock ? 4 : 6) void k_allocate_lru_chunk(Params p)
 {
-    constexpr int G = kLruG, WAVES = kWavesPerBlock, GROUPS = kBlock / G;
+    constexpr int G = kLruG, WAVES = THREADS / kWave, GROUPS = THREADS / G;
     __shared__ int64_t s_home[kBlock];
     __shared__ int64_t s_slot[kBlock];               // of the claimant's chain of claims: the slot not claimed before
     __shared__ uint32_t s_pos[kBlock];
@@ -337,7 +338,7 @@ __global__ __launch_bounds__(kBlock, T == 8 ? 4 : 6) void k_allocate_lru_chunk(P
     const int lane = lane_id(), w = wave_id();
     const Tab d = view(p.t0);
     const int64_t pos = (int64_t)blockIdx.x * kBlock + threadIdx.x;
-    const bool in = pos < p.n;
+    const bool in = (int)threadIdx.x < kBlock && pos < p.n;
     const uint32_t e = in ? p.ent[pos] : kNoEntry;
     const int64_t id = in ? p.ids[pos] : -1;
     const uint8_t note = in ? p.note[pos] : 0;

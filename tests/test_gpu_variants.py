@@ -308,6 +308,19 @@ def test_lru_claims(slots, probe, layout):
     t.close()
 
 
+# ---- LRU claims by workgroups of 1 024, 512 and 256 threads: on both sides of each line, few claimants and mostly claimants
+@pytest.mark.parametrize("more", [0, 1])
+@pytest.mark.parametrize("groups,probe", [(1, 5), (1, 16), (1, 29), (1, 64), (2, 5), (2, 16), (2, 29), (2, 64), (5, 5), (5, 16)])
+def test_lru_claims_around_the_lines_of_their_workgroups(groups, probe, more):
+    rng = rng_for(916)
+    n = groups * torch.cuda.get_device_properties(0).multi_processor_count * 256 + more
+    slots = n // 3
+    t = Pair(slots, probe, 0, "lru", 43, layout="records" if more else "separate")
+    for step, universe in enumerate([2 * slots, 2 * slots, slots // 2]):
+        t.step(rng.integers(0, universe, size=n), step)
+    t.close()
+
+
 # ---- ids that are new and popular at once: copies enter the scratch set once per wavefront
 @pytest.mark.parametrize("evict", [True, "lru", False])
 @pytest.mark.parametrize("n", [1_025, 4_111, 65_536])
