@@ -1702,6 +1702,8 @@ __device__ __forceinline__ uint64_t group_or(uint64_t x)
 // a mask that all lanes of the group hold, so its choices, and the first `choice` ones that a displaced claimant has behind
 // it, cost no exchange between lanes.  (Each choice drawn by three minima over the group, from the first one again for every
 // displaced claimant: 12 547 positions on 6 964 slots, windows of 32, 140 -> 99 us; calls of 300 007 on 60 M slots 11.15 -> 10.95.)
+// The wavefront goes through the loops as one: a branch for each group cost windows of 8, which hardly need the classes, what
+// they gave (360 000 claimants 56.3 -> 53.9).
 template <int T, bool REC, typename Placed, typename Lost>
 __device__ __forceinline__ void claim_group_lru(const Params &p, const Tab &d, bool active, uint32_t cpos, int64_t home,
                                                 LruSlots<T> x, Placed placed, Lost lost)
@@ -1726,30 +1728,33 @@ __device__ __forceinline__ void claim_group_lru(const Params &p, const Tab &d, b
         int32_t skip = choice;
         int64_t displaced = 0;
         bool trying = active;
-        while (trying) {                             // (whole groups)
-            bool none = false;
+        while (__any(trying)) {
+            // on to the class of the present choice
             for (;;) {
                 const int32_t count = sizeof(Mask) == 4 ? __popc((uint32_t)left) : __popcll(left);
-                if (skip < count) break;
-                skip -= count;
+                const bool used_up = trying && skip >= count;
+                if (!__any(used_up)) break;
                 int32_t next = kNone;
 #pragma unroll
                 for (int t = 0; t < T; ++t)
                     if ((evictable >> t & 1u) && x.m[t] > stamp && x.m[t] < next) next = x.m[t];
                 next = group_min(next);
-                none = next == kNone;
-                if (none) break;
-                stamp = next;
-                left = 0;
+                Mask members = 0;
 #pragma unroll
                 for (int t = 0; t < T; ++t)
-                    if ((evictable >> t & 1u) && x.m[t] == next) left |= (Mask)1 << (kLruG * t + r);
-                left = group_or(left);
+                    if ((evictable >> t & 1u) && x.m[t] == next) members |= (Mask)1 << (kLruG * t + r);
+                members = group_or(members);
+                if (used_up) {
+                    skip -= count;
+                    stamp = next;
+                    left = members;
+                    if (next == kNone) {
+                        lost(cpos);
+                        trying = false;
+                    }
+                }
             }
-            if (none) {
-                lost(cpos);
-                break;
-            }
+            if (!trying) continue;
             for (; skip > 0; --skip) left &= left - 1;
             const int32_t round = __ffsll((unsigned long long)left) - 1;
             left &= left - 1;
@@ -1780,8 +1785,12 @@ __device__ __forceinline__ void claim_group_lru(const Params &p, const Tab &d, b
 // written the hints of every list entry and skipped the claimants of LRU tables; here only those
 // claimants are served and only their hints are written.  The windows of the next claimants are requested before the
 // present ones are served.
+//
+// The 8 192 wavefronts of a long call are to run in one go where the registers allow it, with windows of up to 8 slots: 64
+// vector registers, and no more than 80 scalar ones, for each wavefront gets 16 more than it uses (with 92 seven of
+// eight were resident: 3 M positions, 360 000 claimants, 53.9 -> 48.4 us).
 template <int T, bool MULTI, bool REC>
-__global__ __launch_bounds__(kWave, MULTI ? (T == 8 ? 3 : 4) : T == 8 ? 4 : 5) void k_allocate_lru(Params p)
+__global__ __launch_bounds__(kWave, MULTI ? (T == 8 ? 3 : 4) : T == 8 ? 4 : T == 1 ? 8 : 5) void k_allocate_lru(Params p)
 {
     constexpr int G = kLruG, NG = kLruGroups;
     const int lane = threadIdx.x;
