@@ -415,8 +415,9 @@ mpzch_status_t launch_allocate(int32_t max_p_lru, const Params &p, int num_cus, 
 
 mpzch_status_t launch_finalize(const Params &p, int grid, hipStream_t s)
 {
-    if (p.num_tables > 1) TRY(launch(k_finalize<true>, grid, kFinalizeBlock, s, p));
-    else TRY(launch(k_finalize<false>, grid, kFinalizeBlock, s, p));
+    if (p.num_tables > 1) TRY(launch(k_finalize<true, false>, grid, kFinalizeBlock, s, p));
+    else if (p.t0.evict == 2) TRY(launch(k_finalize<false, false>, grid, kFinalizeBlock, s, p));
+    else TRY(launch(k_finalize<false, true>, grid, kFinalizeBlock, s, p));
     return MPZCH_OK;
 }
 

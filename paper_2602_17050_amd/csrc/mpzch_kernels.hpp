@@ -398,10 +398,16 @@ constexpr uint32_t kSetEmpty = 0xFFFFFFFFu;
 // Returns the entry index, with kEntered if pos was the first to stand there.  NOTE: whoever meets an entry of its id leaves a
 // note under the position that stands there, so that who comes first need not be read back where there is no note, and with
 // k_allocate's notes of displaced claims k_finalize need not look at the table (a random read less in each, for each missed
-// id: 2.5 M positions, 10 % of them new, on 400 M slots 208 -> 203 us, on 50 M 194 -> 188; 5 %, on 300 M, 165 -> 161).
+// id: 2.5 M positions, 10 % of them new, on 400 M slots 208 -> 203 us, on 50 M 194 -> 188; 5 %, on 300 M, 165 -> 161).  New
+// ids that are popular: nobody loses by notes and merging together.  2.5 M positions on 50 M slots, a call and the add
+// that moves its ids, us, neither / notes alone / both: new ids 10 % of the positions, each once 194 / 191 / 191; each ten
+// times 155.5 / 157 / 157; drawn by a power law 173 / 173 / 162; the most popular a tenth of the new positions 208 / 206 /
+// 177, of all 895 / 890 / 203; all positions new, by a power law (a table's first batch), 1 472 / 1 469 / 620.  600 000
+// positions: within 1 % but for the last, 253 / 252 / 110.
 constexpr uint32_t kEntered = 0x80000000u;       // (entries are below 2^31)
 template <bool NOTE>
-__device__ __forceinline__ uint32_t set_insert(const Params &p, int64_t id, uint64_t hash, uint32_t pos, uint64_t base, uint64_t size)
+__device__ __forceinline__ uint32_t set_insert(const Params &p, int64_t id, uint64_t hash, uint32_t pos, uint64_t base, uint64_t size,
+                                               bool notes = NOTE)
 {
     uint64_t e = base + __umul64hi(hash, size);
     const uint64_t end = base + size;
@@ -411,7 +417,7 @@ __device__ __forceinline__ uint32_t set_insert(const Params &p, int64_t id, uint
                                                  __HIP_MEMORY_SCOPE_AGENT))
             return NOTE ? (uint32_t)e | kEntered : (uint32_t)e;   // first of its id so far
         if ((int64_t)expected < p.n && p.ids[expected] == id) {   // (an entry is always a position of this batch)
-            if constexpr (NOTE) p.note[expected] = 1;
+            if (NOTE && notes) p.note[expected] = 1;
             if (pos < expected) __hip_atomic_fetch_min(&p.set_slot[e], pos, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
             break;
         }
@@ -1018,8 +1024,11 @@ __device__ __forceinline__ void discover_body(const Params &p)
             // that it can never fill up
             const uint64_t sb = multi ? 2ull * (uint64_t)t_lo : 0, ss = 2ull * (uint64_t)(multi ? t_hi - t_lo : p.n);
             // (The copies of an id are merged and leave notes with one table only.  In groups, with batches of 320 K values of
-            // which the new ones are popular, Pass 1 took 21 instead of 17 us with the notes.)
+            // which the new ones are popular, Pass 1 took 21 instead of 17 us with both.  No notes for an LRU table either: its
+            // claims read the set and its finalize looks, whatever they say; read and cleared they cost finalize 3 of 40 us for
+            // 360 000 new ids.)
             constexpr bool NOTE = !MULTI;
+            const bool notes = d.evict != 2;
             for (int j0 = 0; j0 < nmiss; j0 += kWave) {
                 const int j = j0 + lane;
                 const bool miss = j < nmiss;
@@ -1030,9 +1039,9 @@ __device__ __forceinline__ void discover_body(const Params &p)
                 if constexpr (NOTE) {
                     uint32_t first = pos;
                     const int from = merge_copies(miss, id, (int)hash & (kWave - 1), first, reinterpret_cast<MetaMerge *>(s_req[w]));
-                    if (miss && from == lane) e = set_insert<NOTE>(p, id, hash, first, sb, ss);
+                    if (miss && from == lane) e = set_insert<NOTE>(p, id, hash, first, sb, ss, notes);
                     e = (uint32_t)__shfl((int)e, from);
-                    if (miss && from != lane) p.note[first] = 1;
+                    if (miss && from != lane && notes) p.note[first] = 1;
                     if (first != pos) e &= ~kEntered;
                 } else if (miss) {
                     e = set_insert<NOTE>(p, id, hash, pos, sb, ss);
@@ -1314,11 +1323,10 @@ constexpr uint32_t kHintUnplaced = 0xFE;   // ran out of slots: falls back to ho
 constexpr uint32_t kHintUnknown = 0xFD;    // placed, but not at a round that fits the hint: search the window
 
 // What k_allocate leaves in first_of for k_finalize: the position of the first occurrence of the entry's id, or, for
-// that position itself, kAgentEntry | hint, with kAgentOcc if the slot there held an id.  With one table that stands
-// unless a note says that the claim was displaced (or kAgentLook that nobody would have left one).
+// that position itself, kAgentEntry | hint, with kAgentOcc if the slot there held an id.  With one table, not LRU, that stands
+// unless a note says that the claim was displaced.
 constexpr uint32_t kAgentEntry = 0x80000000u;
 constexpr uint32_t kAgentOcc = 0x100u;
-constexpr uint32_t kAgentLook = 0x200u;
 
 // What a claimant's lane leaves in LDS for the lanes that load for it: the address of the identity of the first slot to
 // read, that slot's number, and the claim: the claimant's position and the round that the first slot would be for it.
@@ -1860,7 +1868,7 @@ __global__ __launch_bounds__(kWave, MULTI ? (T == 8 ? 3 : 4) : T == 8 ? 4 : T ==
                 x = x2;
             }
             if (agent) p.hint[pos] = (uint8_t)hint;
-            if (agent) p.first_of[idx] = kAgentEntry | kAgentLook | hint;
+            if (agent) p.first_of[idx] = kAgentEntry | hint;
             else if (!MULTI && have) p.first_of[idx] = first;     // (several tables: k_allocate has written it)
         }
     }
@@ -2008,7 +2016,7 @@ __global__ __launch_bounds__(kWave) void k_allocate_lru_long(Params p)
                     hint = fr < 0 ? kHintUnplaced : (fr < (int32_t)kHintUnknown ? (uint32_t)fr : kHintUnknown);
             }
             if (agent) p.hint[pos] = (uint8_t)hint;
-            if (agent) p.first_of[idx] = kAgentEntry | kAgentLook | hint;
+            if (agent) p.first_of[idx] = kAgentEntry | hint;
             else if (!MULTI && have) p.first_of[idx] = first;     // (several tables: k_allocate has written it)
         }
     }
@@ -2187,13 +2195,14 @@ __device__ __forceinline__ bool finalize_epilogue(const Params &p, FinalizeState
 }
 
 // Every entry of the miss lists -- the elected position of an id (its agent) and the other copies of
-// the id alike -- finds the slot that carries the agent's claim.  With one table the agent knows where it is unless a note
-// says that it was displaced or has copies; else it and its copies look where k_allocate left the claim (the hint, kept
+// the id alike -- finds the slot that carries the agent's claim.  With one table (not LRU) the agent knows where it is unless a
+// note says that it was displaced or has copies; else it and its copies look where k_allocate left the claim (the hint, kept
 // under the agent's batch position, which every copy knows), and the whole wavefront searches the window of a claimant
 // displaced after its hint was written.  A copy may find the claim tag or, when the agent has been quicker, already the id.  The agent turns the tag into the id,
 // writes the metadata and accounts for the outcome; every entry stores its output slot.  Entries
 // without a claim fall back to the home slot (Case 3).
-template <bool MULTI>
+// NOTES: one table, not LRU (see set_insert).
+template <bool MULTI, bool NOTES>
 __device__ __forceinline__ void finalize_body(const Params &p)
 {
     __shared__ int64_t s_ev[kFinalizeWaves][kEvBuf];
@@ -2246,10 +2255,10 @@ __device__ __forceinline__ void finalize_body(const Params &p)
             if (have) {
                 agent = (word & kAgentEntry) != 0;
                 first = agent ? pos : word;
-                if constexpr (!MULTI) {
+                if constexpr (NOTES) {
                     const uint8_t note = p.note[pos];
                     if (note) p.note[pos] = 0;                 // no note is left behind
-                    sure = agent && !note && !(word & kAgentLook);
+                    sure = agent && !note;
                 }
                 h = agent ? word & 0xFFu : (uint32_t)p.hint[first];
                 p.set_slot[e & ~kEntered] = kSetEmpty;         // the scratch set is left empty again
@@ -2336,7 +2345,8 @@ __device__ __forceinline__ void finalize_body(const Params &p)
     if (last) publish_counters<kFinalizeBlock>(p, s_bins);
 }
 
-// Held to 8 wavefronts per SIMD (one table: 51 registers and 66 KB of LDS for 16 wavefronts, several: 63 and 40 KB), so that
+// Held to 8 wavefronts per SIMD (one table: 51 vector registers and 66 KB of LDS for 16 wavefronts, several: 63 and 40 KB; no
+// vector register goes to memory, 86 to 89 scalar ones are kept in lanes of vector registers), so that
 // the 8 192 wavefronts, each a chain of three round trips, run in one go.  (Several tables with 66 registers and the rows'
 // buffer that only one table has use for: one workgroup per compute unit and two turns, 41 M values over 26 tables 152 -> 145
 // us.)  A batch of 4 M positions, 10 % of them new, with
@@ -2344,10 +2354,10 @@ __device__ __forceinline__ void finalize_body(const Params &p)
 // metadata of a record, and rows reset before the workgroup's barrier instead of behind it, 45.5 -> 41 us by the claims that
 // need no look; 41 M values over 26 tables
 // 242 -> 178 us.
-template <bool MULTI>
+template <bool MULTI, bool NOTES>
 __global__ __launch_bounds__(kFinalizeBlock, 8) void k_finalize(Params p)
 {
-    finalize_body<MULTI>(p);
+    finalize_body<MULTI, NOTES>(p);
 }
 
 // ------------------------------------------------------------------ fills and row reset
