@@ -507,6 +507,7 @@ __global__ __launch_bounds__(kBlock, 8) void k_finalize_chunk(Params p)
             s_row[threadIdx.x] = evicted_slot >= p.g_num_rows ? evicted_slot % p.g_num_rows : evicted_slot;
     }
     const bool refresh = agent || (have && p.ttls && d.evict == 3);
+    bool moves_in = false;
     int64_t slot = 0;
     if (have) {
         place = moved > place ? moved : place;
@@ -516,10 +517,14 @@ __global__ __launch_bounds__(kBlock, 8) void k_finalize_chunk(Params p)
         slot = placed ? wrap(home + (int64_t)(place - 1u), d.N) : home;
         // the claim becomes the id, metadata gets its value (Algorithm 1, Pass 2); without a claim: Case 3, the home
         // slot's metadata is refreshed; with per-feature retention a later copy may ask for a later expiry step
-        if (agent && placed) *id_at(d, slot) = id;
+        if (agent && placed) {
+            if (d.evict != 3) *id_at(d, slot) = id;
+            else moves_in = true;
+        }
         p.out_slots[pos] = slot;
     }
     store_meta_block(d, refresh, slot, refresh ? meta_value(p, d, pos) : 0, s_merge);
+    if (moves_in) *id_at(d, slot) = id;              // (expiry steps: see store_meta)
     if (evicted > 0) {
         __syncthreads();
         uint32_t base = 0;
