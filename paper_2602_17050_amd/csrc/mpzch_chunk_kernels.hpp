@@ -282,7 +282,10 @@ __global__ __launch_bounds__(kBlock, 4) void k_allocate_chunk(Params p)
     const bool have = e != kNoEntry;
     uint32_t first = 0;
     const bool read_back = READ_BACK && __popcll(__ballot(have)) > kWave / 2;
-    if (have) first = first_occurrence(p, (uint32_t)pos, e, read_back ? 1 : note);
+    // (looked at here: compared in the branch that reads it, calls of 262 144 and 400 000 new ids 23.5 -> 24.1 and 31.4 -> 32.2)
+    uint32_t met = read_back ? 1u : note;
+    asm volatile("" : "+v"(met));
+    if (have) first = first_occurrence(p, (uint32_t)pos, e, (uint8_t)met);
     else start = kStartNever;
 
     Claimant c;
