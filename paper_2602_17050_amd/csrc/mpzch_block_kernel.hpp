@@ -163,18 +163,16 @@ __global__ __launch_bounds__(kOneBlock) void k_remap_block(Params p)
     // every claim stands
     __syncthreads();
 
-    bool refresh = false, claims = false;                    // (claims: this lane's id moves into its slot)
+    bool refresh = false;
     if (first != kNoEntry) {
         const uint32_t place = s.place[first];
         const bool placed = place != 0 && place != kPlaceNone, agent = first == pos;
         if (placed) slot = wrap(home + (int64_t)(place - 1u), d.N);
-        claims = agent && placed;
+        if (agent && placed) *id_at(d, slot) = id;
         refresh = agent || (p.ttls && d.evict == 3);
     }
-    if (claims && d.evict != 3) *id_at(d, slot) = id;
     if (in) p.out_slots[pos] = slot;
     store_meta_block(d, refresh, slot, refresh ? meta_value(p, d, pos) : 0, s.merge);
-    if (claims && d.evict == 3) *id_at(d, slot) = id;        // (see store_meta)
     const int evicted = (int)s.count[kEvictions];
     if (p.r_rows && evicted > 0) {
         const int waves = (threads + kWave - 1) / kWave, per = (evicted + waves - 1) / waves;
