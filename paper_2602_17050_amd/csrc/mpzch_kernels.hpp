@@ -1721,22 +1721,21 @@ __device__ __forceinline__ void claim_group_lru(const Params &p, const Tab &d, b
                                                 LruSlots<T> x, Placed placed, Lost lost)
 {
     using Mask = LruMask<T>;
-    constexpr int32_t kNone = 0x7FFFFFFF, kEmpties = -0x7FFFFFFF - 1;
     const int lane = lane_id();
     const int r = lane % kLruG, gbase = lane - r;
     int32_t choice = 0;
     while (__any(active)) {
         Mask empties = 0;
-        uint32_t evictable = 0;                      // bit t: the slot of round 8 t + r may be evicted
+        Mask evictable = 0;                          // bit 8 t: the slot of round 8 t + r may be evicted and has not been drawn
 #pragma unroll
         for (int t = 0; t < T; ++t) {
             const bool in = active && kLruG * t + r < d.P;
             const bool occ = is_tag(x.v[t]) ? tag_occ(x.v[t]) != 0 : x.v[t] >= 0;     // it held an id when the call began
             if (in && !occ) empties |= (Mask)1 << (kLruG * t + r);
-            if (in && occ && x.m[t] != p.step) evictable |= 1u << t;
+            if (in && occ && x.m[t] != p.step) evictable |= (Mask)1 << (kLruG * t);
         }
         Mask left = group_or(empties);               // of the present class: the slots that have not been drawn
-        int32_t stamp = kEmpties;                    // ... and its time stamp
+        uint32_t class_occ = 0;                      // ... whether they held ids
         int32_t skip = choice;
         int64_t displaced = 0;
         bool trying = active;
@@ -1746,21 +1745,23 @@ __device__ __forceinline__ void claim_group_lru(const Params &p, const Tab &d, b
                 const int32_t count = sizeof(Mask) == 4 ? __popc((uint32_t)left) : __popcll(left);
                 const bool used_up = trying && skip >= count;
                 if (!__any(used_up)) break;
-                int32_t next = kNone;
+                // (metadata is the caller's: any value may be a time stamp, so a class is told by its members)
+                int32_t next = 0x7FFFFFFF;
 #pragma unroll
                 for (int t = 0; t < T; ++t)
-                    if ((evictable >> t & 1u) && x.m[t] > stamp && x.m[t] < next) next = x.m[t];
+                    if ((evictable >> (kLruG * t) & 1u) && x.m[t] < next) next = x.m[t];
                 next = group_min(next);
                 Mask members = 0;
 #pragma unroll
                 for (int t = 0; t < T; ++t)
-                    if ((evictable >> t & 1u) && x.m[t] == next) members |= (Mask)1 << (kLruG * t + r);
-                members = group_or(members);
+                    if (x.m[t] == next) members |= (Mask)1 << (kLruG * t);
+                members = group_or((members & evictable) << r);
                 if (used_up) {
                     skip -= count;
-                    stamp = next;
+                    class_occ = 1;
+                    evictable &= ~(members >> r);
                     left = members;
-                    if (next == kNone) {
+                    if (!members) {
                         lost(cpos);
                         trying = false;
                     }
@@ -1770,7 +1771,7 @@ __device__ __forceinline__ void claim_group_lru(const Params &p, const Tab &d, b
             for (; skip > 0; --skip) left &= left - 1;
             const int32_t round = __ffsll((unsigned long long)left) - 1;
             left &= left - 1;
-            const int64_t mine = make_tag((uint32_t)choice, cpos, stamp == kEmpties ? 0u : 1u);
+            const int64_t mine = make_tag((uint32_t)choice, cpos, class_occ);
             const int64_t s = wrap(home + round, d.N);
             int64_t old = 0;
             if (r == 0) old = __hip_atomic_fetch_min(id_at(d, s), mine, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);

@@ -67,3 +67,35 @@ def test_lru_one_million_slots_with_row_reset():
     p.check_state()
     assert p.o.check_state()[0] == 0
     p.close()
+
+
+@pytest.mark.parametrize("probe", [5, 16, 29, 64, 65])
+@pytest.mark.parametrize("slots,batch", [(900, 2_000), (150_001, 530_000)])
+def test_lru_any_time_stamp(slots, batch, probe):
+    """An entry is evictable by whatever its time stamp is: the largest step there is, and what a caller has written."""
+    rng = np.random.Generator(np.random.Philox(key=917 + probe))
+    p = Pair(slots, probe, 0, "lru", 47, layout="records" if probe % 2 else "separate")
+    evictions = []
+    for k, step in enumerate((2**31 - 1, 3, 2**31 - 1, 0, 2**31 - 2)):
+        if k == 3:
+            for stamp, at in ((-2**31, slice(0, slots, 3)), (2**31 - 1, slice(1, slots, 3))):
+                p.g.metadata[at] = stamp
+                p.o.metadata[at] = stamp
+        ids = rng.integers(k * batch, (k + 2) * batch, size=batch)
+        evictions.append(p.step(ids, step).stats["evictions"])
+    assert min(evictions[1:]) > slots // 4
+    p.close()
+
+
+def test_lru_any_time_stamp_in_groups():
+    from test_gpu_jagged import JaggedPair
+    rng = np.random.Generator(np.random.Philox(key=918))
+    specs = [wl.TableSpec(900, probe, 0, "lru", 71 + probe) for probe in (5, 16, 29, 64)]
+    jp = JaggedPair(specs, (1, 3))
+    offsets = np.arange(0, 2_000 * (len(specs) + 1), 2_000, dtype=np.int64)
+    for k, step in enumerate((2**31 - 1, 3, 2**31 - 1, 0)):
+        vals = rng.integers(k * 2_000, (k + 2) * 2_000, size=2_000 * len(specs))
+        got = jp.step(vals, offsets, step)
+        assert k == 0 or min(s["evictions"] for s in got) > 200
+    jp.check_state()
+    jp.close()
