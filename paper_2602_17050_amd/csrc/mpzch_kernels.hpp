@@ -1027,10 +1027,12 @@ __device__ __forceinline__ void discover_body(const Params &p)
             // the region of the scratch set that serves this table: twice as many entries as the table has positions, so
             // that it can never fill up
             const uint64_t sb = multi ? 2ull * (uint64_t)t_lo : 0, ss = 2ull * (uint64_t)(multi ? t_hi - t_lo : p.n);
-            // (The copies of an id are merged and leave notes with one table only.  In groups, with batches of 320 K values of
+            // (The copies of an id are merged, but leave notes with one table only: in groups, with batches of 320 K values of
             // which the new ones are popular, Pass 1 took 21 instead of 17 us with both.  No notes for an LRU table either: its
             // claims read the set and its finalize looks, whatever they say; read and cleared they cost finalize 3 of 40 us for
-            // 360 000 new ids.)
+            // 360 000 new ids.  Merged or not, groups, whole steps, new ids popular: 26 x 12 000 values 64.1 / 52.6 us, 8 x
+            // 100 000 254 / 88, 4 x 1 M 2 066 / 512, the less so the faster Pass 1 reaches the atomics; new ids rare, 26 x 12 000
+            // to 41 M values, the same to 0.6 %.)
             constexpr bool NOTE = !MULTI;
             const bool notes = d.evict != 2;
             for (int j0 = 0; j0 < nmiss; j0 += kWave) {
@@ -1039,16 +1041,13 @@ __device__ __forceinline__ void discover_body(const Params &p)
                 const uint32_t pos = miss ? s_pos[w][j] : 0;
                 const int64_t id = miss ? s_id[w][j] : -1;
                 const uint64_t hash = mix64((uint64_t)id ^ kSetSeed);
-                uint32_t e = 0;
+                uint32_t e = 0, first = pos;
+                const int from = merge_copies(miss, id, (int)hash & (kWave - 1), first, reinterpret_cast<MetaMerge *>(s_req[w]));
+                if (miss && from == lane) e = set_insert<NOTE>(p, id, hash, first, sb, ss, notes);
+                e = (uint32_t)__shfl((int)e, from);
                 if constexpr (NOTE) {
-                    uint32_t first = pos;
-                    const int from = merge_copies(miss, id, (int)hash & (kWave - 1), first, reinterpret_cast<MetaMerge *>(s_req[w]));
-                    if (miss && from == lane) e = set_insert<NOTE>(p, id, hash, first, sb, ss, notes);
-                    e = (uint32_t)__shfl((int)e, from);
                     if (miss && from != lane && notes) p.note[first] = 1;
                     if (first != pos) e &= ~kEntered;
-                } else if (miss) {
-                    e = set_insert<NOTE>(p, id, hash, pos, sb, ss);
                 }
                 if (miss) {
                     p.list[seg_base + flushed + j] = pos;

@@ -433,3 +433,28 @@ def test_first_occurrences_read_back_or_noted(n, evict):
         t.step(rng.permutation(np.concatenate([ids[: n // 2], ids[rng.integers(0, n, size=n - n // 2)]])), step)
         old = ids
     t.close()
+
+
+# ---- the same in groups: copies are merged within a wavefront and a table, features end inside wavefronts, the same ids are
+# new in several of them, and of the copies the one that asks for the latest expiry step counts
+@pytest.mark.parametrize("records", [(0, 1, 2, 3, 4), (1, 3)])
+@pytest.mark.parametrize("n", [37, 700, 66_000])
+def test_new_ids_with_many_copies_in_groups(n, records):
+    from test_gpu_jagged import JaggedPair
+    rng = rng_for(919)
+    specs = [wl.TableSpec(2_003, 16, 1, True, 81), wl.TableSpec(300, 8, 0, "lru", 82), wl.TableSpec(1_501, 24, 2, "expiry", 83),
+             wl.TableSpec(5, 3, 1, True, 84), wl.TableSpec(4_000, 16, 0, False, 85)]
+    jp = JaggedPair(specs, records)
+    for step in range(4):
+        counts = n + np.array([0, 1, -5, 30, 7])
+        hot = rng.integers(0, 1 << 40, size=5)
+        vals = []
+        for c in counts:
+            v = np.where(rng.random(c) < 0.7, hot[rng.integers(0, 5, size=c)], rng.integers(0, 1 << 40, size=c))
+            v[: c // 3] = hot[0]
+            vals.append(v[rng.permutation(c)])
+        vals = np.concatenate(vals)
+        offsets = np.concatenate([[0], np.cumsum(counts)]).astype(np.int64)
+        jp.step(vals, offsets, 2 * step, None if step % 2 else rng.integers(0, 6, size=len(vals)).astype(np.int32))
+    jp.check_state()
+    jp.close()
