@@ -563,14 +563,20 @@ struct alignas(16) ProbeReq {
 //
 // The blocks are read as they lie and nothing is asked per slot: whoever made the request chose a first slot from which
 // all of them are in the table, and its own lane knows which bytes are rounds of its window.  (A lookup spends more than
-// half of its time issuing instructions.  1 M ids, windows of 32 slots, 80 % load: 856 -> 578 vector instructions per
+// half of its time issuing instructions.  1 M ids, windows of 32 slots, 80 % load: 903 -> 554 vector instructions per
 // wavefront of two chunks, 21.4 -> 19.5 us; 10 K values over 26 tables 5.6 -> 5.1.)
+//
+// The forms for 8, 4 and 2 rows are copies of one loop of loads behind a wave-uniform branch.  An earlier lookup built that way,
+// with nothing to hold the copies apart, gave wrong and varying results on tables of 100 M slots, for a reason that was not
+// found, and right ones with a scheduling barrier behind the branch.  The two barriers below therefore stay, whatever their
+// effect on the speed: with them every form, in the assembly of each kernel, issues its own loads behind the branch and
+// waits for the last of them before the last byte is stored.
 template <int T, bool NT, bool REC>
 __device__ __forceinline__ void probe_rows(const ProbeReq *req, int next, uint8_t *s_code, uint32_t lane_bytes, int32_t fresh_meta)
 {
     int64_t v[T];
     int32_t meta[T];
-    // (the compiler would start what the forms have in common before it branches to one of them, and wait there)
+    // (without: the compiler starts what the forms have in common before it branches to one of them, and waits there)
     asm volatile("" ::"i"(T) : "memory");
 #pragma unroll
     for (int t = 0; t < T; ++t) {
