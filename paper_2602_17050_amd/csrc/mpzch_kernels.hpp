@@ -2237,7 +2237,8 @@ __device__ __forceinline__ void finalize_body(const Params &p)
         const uint32_t cnt = p.seg_cnt[seg];
         const int64_t seg_base = seg * p.seg_chunks * kWave;
         int seg_f = 0;
-        Tab seg_d = view(p.t0);
+        Tab seg_d{};
+        if (!multi) seg_d = view(p.t0);
         bool seg_one = true;
         if (multi) seg_one = segment_table(p, lane_offset, seg_base, p.seg_chunks * kWave, seg_f, seg_d);
         if (seg_base >= p.n) break;                            // segments past the batch hold nothing
@@ -2254,7 +2255,7 @@ __device__ __forceinline__ void finalize_body(const Params &p)
             uint32_t first = 0, h = kHintUnplaced;
             int outcome = 2, f = 0;
             int64_t s_final = 0, home = 0;
-            Tab d = view(p.t0);
+            Tab d = seg_d;
             int at = -1;
             uint32_t occ = 0;
             // does slot value v carry the claim of the id whose first occurrence is `fst`?
@@ -2275,7 +2276,6 @@ __device__ __forceinline__ void finalize_body(const Params &p)
                 if (multi) {
                     if (seg_one) {
                         f = seg_f;
-                        d = seg_d;
                     } else {
                         f = find_table(p.offsets, p.num_tables, (int64_t)pos);
                         d = view(p.descs[f]);
@@ -2300,7 +2300,7 @@ __device__ __forceinline__ void finalize_body(const Params &p)
                 const uint32_t cfirst = __shfl(first, src);
                 const int64_t cid = shfl64(id, src);
                 const int64_t chome = shfl64(home, src);
-                Tab dw = view(p.t0);
+                Tab dw = seg_d;
                 if (multi) dw = uniform(view(p.descs[__shfl(f, src)]));
                 int found_round = -1;
                 uint32_t found_occ = 0;
@@ -2355,8 +2355,8 @@ __device__ __forceinline__ void finalize_body(const Params &p)
     if (last) publish_counters<kFinalizeBlock>(p, s_bins);
 }
 
-// Held to 8 wavefronts per SIMD (one table: 51 vector registers and 66 KB of LDS for 16 wavefronts, several: 63 and 40 KB; no
-// vector register goes to memory, 86 to 89 scalar ones are kept in lanes of vector registers), so that
+// WAVES = 8 wavefronts per SIMD (one table: 51 vector registers and 66 KB of LDS for 16 wavefronts, several: 63 and 40 KB; no
+// vector register goes to memory, 81 to 88 scalar ones are kept in lanes of vector registers), so that
 // the 8 192 wavefronts, each a chain of three round trips, run in one go.  (Several tables with 66 registers and the rows'
 // buffer that only one table has use for: one workgroup per compute unit and two turns, 41 M values over 26 tables 152 -> 145
 // us.)  A batch of 4 M positions, 10 % of them new, with
@@ -2364,8 +2364,10 @@ __device__ __forceinline__ void finalize_body(const Params &p)
 // metadata of a record, and rows reset before the workgroup's barrier instead of behind it, 45.5 -> 41 us by the claims that
 // need no look; 41 M values over 26 tables
 // 242 -> 178 us.
-template <bool MULTI, bool NOTES>
-__global__ __launch_bounds__(kFinalizeBlock, 8) void k_finalize(Params p)
+// WAVES = 4, several tables: twice the scalar registers, 49 kept in vector lanes, which is time that the chain of a small call
+// sees: steps of 600 values over 2 tables 35.6 -> 34.8 us, 10 400 over 26 41.4 -> 40.6.
+template <bool MULTI, bool NOTES, int WAVES = 8>
+__global__ __launch_bounds__(kFinalizeBlock, WAVES) void k_finalize(Params p)
 {
     finalize_body<MULTI, NOTES>(p);
 }

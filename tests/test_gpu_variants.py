@@ -458,3 +458,19 @@ def test_new_ids_with_many_copies_in_groups(n, records):
         jp.step(vals, offsets, 2 * step, None if step % 2 else rng.integers(0, 6, size=len(vals)).astype(np.int32))
     jp.check_state()
     jp.close()
+
+
+# ---- groups on both sides of the line at which a second workgroup of the last kernel comes to a compute unit
+@pytest.mark.parametrize("more", [0, 1])
+def test_groups_around_the_line_of_the_last_kernel(more):
+    from test_gpu_jagged import JaggedPair
+    rng = rng_for(920)
+    n = torch.cuda.get_device_properties(0).multi_processor_count * 16 * 64 + more
+    specs = [wl.TableSpec(30_011, 16, 1, True, 91), wl.TableSpec(9_001, 8, 0, "lru", 92), wl.TableSpec(25_000, 24, 2, "expiry", 93)]
+    jp = JaggedPair(specs, (0, 2))
+    offsets = np.array([0, n // 2 + 7, n // 2 + n // 5, n], dtype=np.int64)
+    for step in (0, 3):
+        vals = np.concatenate([wl.zipf_ids(rng, int(c), 1.05, 3 * s.num_slots) + step for c, s in zip(np.diff(offsets), specs)])
+        jp.step(vals, offsets, step)
+    jp.check_state()
+    jp.close()
