@@ -501,7 +501,7 @@ mpzch_status_t launch_remap_chunks(Timing &tm, const Params &p, int32_t max_p_lr
     else if (rec) TRY(launch_allocate_chunk<true>(p, grid, num_cus, s));
     else TRY(launch_allocate_chunk<false>(p, grid, num_cus, s));
     if (!tm.end(s) || !tm.begin(KFinalize, s)) return MPZCH_ERR_HIP;
-    TRY(launch(k_finalize_chunk, kPublishTasks + grid, kBlock, s, p));
+    TRY(launch(k_finalize_chunk, kPublishGroups + grid, kBlock, s, p));
     if (!tm.end(s)) return MPZCH_ERR_HIP;
     return MPZCH_OK;
 }

@@ -43,6 +43,7 @@ constexpr int kWave = 64;
 constexpr int kBlock = 256;
 constexpr int kWavesPerBlock = kBlock / kWave;
 constexpr int kMaxTables = 64;
+constexpr int kDies = 8;               // the dies of the GPU, each with an L2 of its own, take the workgroups of a launch in turn
 constexpr int kStatCount = 9;
 constexpr int kEvBuf = 256;            // evicted slots staged per wavefront before a flush
 
@@ -897,7 +898,7 @@ __device__ __forceinline__ void discover_body(const Params &p)
         // 992 / 937, 1 603 / 1 513.  The line at 16 chunks per wavefront is a cautious one: 4.1 M values 171 / 164 and
         // 186 / 183.  Not for lookups, which do not write the lines they share: 12.2 M values 152 / 159, 16.2 M 201 / 210,
         // 41.6 M 495 / 494.
-        constexpr int kDies = 8, kParts = 16;
+        constexpr int kParts = 16;
         if (p.seg_chunks >= 16 && gridDim.x % kParts == 0) {
             const int per = (int)gridDim.x / kParts, j = block / kDies;
             block = (j / per * kDies + block % kDies) * per + j % per;
