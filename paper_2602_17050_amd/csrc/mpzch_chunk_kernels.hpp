@@ -72,7 +72,8 @@ __device__ __forceinline__ uint32_t set_insert_chunk(const Params &p, int64_t id
 }
 
 // hint[pos] of a missed position: the first round at which its id may find a slot to claim, as far as Pass 1 can tell
-// (without eviction: the first empty slot), at most kStartMax; kStartNever: there is none in its window.
+// (without eviction: the first empty slot), at most kStartMax; kStartNever: there is none in its window.  (Of the others 0: a
+// line that is written as a whole need not be fetched.)
 constexpr uint32_t kStartMax = 0xFE, kStartNever = 0xFF;
 
 // Sum over the wavefront of 32-bit values whose total fits 32 bits, in every lane.
@@ -195,10 +196,8 @@ __global__ __launch_bounds__(kBlock << SHIFT, 4) void k_discover_chunk(Params p)
         p.out_slots[pos] = slot;
         p.ent[pos] = e;
         p.place[pos] = 0;
-    }
-    if (miss) {
         uint32_t start = 0;
-        if (d.evict == 0) {
+        if (d.evict == 0 && miss) {
             const uint32_t r = (uint32_t)(absent_len(res) - 1);
             start = res > kProbeAbsent ? kStartNever : r < kStartMax ? r : kStartMax;
         }
@@ -275,10 +274,13 @@ __global__ __launch_bounds__(kBlock, 4) void k_allocate_chunk(Params p)
     const int64_t pos = (int64_t)blockIdx.x * kBlock + threadIdx.x;
     const bool in = pos < p.n;
     const Tab d = view(p.t0);
-    const uint32_t e = in ? p.ent[pos] : kNoEntry;
-    const int64_t id = in ? p.ids[pos] : -1;
-    uint32_t start = in ? (uint32_t)p.hint[pos] : kStartNever;   // (anything where the position did not miss)
-    const uint8_t note = in ? p.note[pos] : 0;
+    const int64_t from = in ? pos : 0;               // (no branch between the loads)
+    args_now(p.ent, p.ids, p.hint, p.note, p.set_slot, p.list, p.step, d.I, d.M, d.N, d.seed, d.P, d.ttl, d.evict, d.sh);
+    uint32_t e = p.ent[from];
+    const int64_t id = p.ids[from];
+    uint32_t start = (uint32_t)p.hint[from];         // (anything where the position did not miss)
+    const uint8_t note = p.note[from];
+    if (!in) e = kNoEntry;
     const bool have = e != kNoEntry;
     uint32_t first = 0;
     const bool read_back = READ_BACK && __popcll(__ballot(have)) > kWave / 2;
@@ -475,31 +477,31 @@ __global__ __launch_bounds__(kBlock, 8) void k_finalize_chunk(Params p)
     const int64_t pos = (int64_t)group * kBlock + threadIdx.x;
     const bool in = pos < p.n;
     const Tab d = view(p.t0);
-    const uint32_t word = in ? p.list[pos] : kNoEntry;
-    const int64_t id = in ? p.ids[pos] : -1;
-    uint32_t moved = in ? p.place[pos] : 0;
-    // the scratch set is left empty again (all of it, in one coalesced store, instead of the entries that were used, one at
-    // a time)
-    static_assert(kChunkSetEntries == 4, "cleared as one vector of four");
-    if (in) {
-        reinterpret_cast<u32x4 *>(p.set_slot)[pos] = u32x4(kSetEmpty);
-        p.note[pos] = 0;
-    }
-    // what the evicted slots of this workgroup need, requested now: the slots, and the counts of the workgroups before
+    // Nothing is asked between the loads and nothing is done with one before the last of them has been requested: two round
+    // trips, this workgroup's words and then, for copies, those of their first occurrences.  (A choice or a scalar made right
+    // behind a load waits for it, and for all stores before it: the counts of the workgroups before were a chain of their own,
+    // one to eight round trips long.  With k_allocate_chunk's loads likewise: 51 calls of 65 536 positions 972 -> 926 us, 12 of
+    // 20 011 with expiry steps 321 -> 309, 12 of 262 144 new ids 753 -> 731.)
+    const int64_t at = in ? pos : 0;
+    args_now(p.list, p.ids, p.place, p.set_slot, p.note, p.wg_words, p.evicted, p.out_slots, p.r_rows, p.ttls, p.step, p.g_num_rows, d.I, d.M, d.N,
+             d.seed, d.evict, d.sh);
+    uint32_t word = p.list[at];
+    const int64_t id = p.ids[at];
+    uint32_t moved = p.place[at];
+    // what the evicted slots of this workgroup need, requested now: the slots, and the counts of the workgroups before (the
+    // upper halves of their words)
     const uint64_t *const outcomes = p.wg_words + 2 * groups;
-    const int evicted = (int)unpack3(outcomes[group], 2);
+    uint32_t evicted_word = reinterpret_cast<const uint32_t *>(outcomes)[2 * group + 1];
     constexpr int kMostBefore = (int)(kChunkMaxBatch / kBlock / kBlock);
-    uint64_t before[kMostBefore];
+    uint32_t before[kMostBefore];
 #pragma unroll
     for (int k = 0; k < kMostBefore; ++k) {
         before[k] = 0;
-        if (d.evict != 0 && k * kBlock < group) {
-            const int i = k * kBlock + (int)threadIdx.x;
-            before[k] = outcomes[i < group ? i : group];
-            if (i >= group) before[k] = 0;
-        }
+        const int i = k * kBlock + (int)threadIdx.x;
+        if (d.evict != 0 && k * kBlock < group) before[k] = reinterpret_cast<const uint32_t *>(outcomes)[2 * (i < group ? i : group) + 1];
     }
-    const int64_t evicted_slot = d.evict != 0 && in ? p.evicted[pos] : 0;      // (of the threads below `evicted`)
+    const int64_t evicted_slot = d.evict != 0 ? p.evicted[at] : 0;     // (of the threads below `evicted`)
+    if (!in) word = kNoEntry;
     const bool have = word != kNoEntry, agent = have && (word & kOwnPlace) != 0;
     uint32_t place = word & ~kOwnPlace;
     if (have && !agent) {
@@ -507,10 +509,15 @@ __global__ __launch_bounds__(kBlock, 8) void k_finalize_chunk(Params p)
         place = p.list[word] & ~kOwnPlace;
     }
     // (meanwhile: where this workgroup's part of the evicted list begins, and the rows to reset)
+    asm volatile("" : "+v"(evicted_word));           // (a scalar from here on: made one right behind the load it waits for it)
+    const int evicted = uniform32((int)(evicted_word & 0xFFFFu));
     if (evicted > 0) {
         uint32_t base = 0;
 #pragma unroll
-        for (int k = 0; k < kMostBefore; ++k) base += unpack3(before[k], 2);
+        for (int k = 0; k < kMostBefore; ++k) {
+            asm volatile("" : "+v"(before[k]));      // (selected here: a choice right behind a load waits for it)
+            if (k * kBlock + (int)threadIdx.x < group) base += before[k] & 0xFFFFu;
+        }
         base = wave_sum32(base);
         if (lane_id() == 0) s_base[wave_id()] = base;
         if (p.r_rows && (int)threadIdx.x < evicted)
@@ -532,6 +539,13 @@ __global__ __launch_bounds__(kBlock, 8) void k_finalize_chunk(Params p)
             else moves_in = true;
         }
         p.out_slots[pos] = slot;
+    }
+    // the scratch set is left empty again (all of it, in one coalesced store, instead of the entries that were used, one at
+    // a time; behind all loads, none of which then waits for it)
+    static_assert(kChunkSetEntries == 4, "cleared as one vector of four");
+    if (in) {
+        reinterpret_cast<u32x4 *>(p.set_slot)[pos] = u32x4(kSetEmpty);
+        p.note[pos] = 0;
     }
     store_meta_block(d, refresh, slot, refresh ? meta_value(p, d, pos) : 0, s_merge);
     if (moves_in) *id_at(d, slot) = id;              // (expiry steps: see store_meta)

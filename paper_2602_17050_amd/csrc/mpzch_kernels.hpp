@@ -309,6 +309,13 @@ struct Tab {
     int32_t sh;
 };
 
+// The arguments that the kernel is about to use are requested together, here.  (Else each where its first use is, and a row of
+// loads becomes a chain of as many scalar loads, each waited for.)
+template <typename T>
+__device__ __forceinline__ void wait_for_scalar(T x) { asm volatile("" ::"s"(x)); }
+template <typename... T>
+__device__ __forceinline__ void args_now(T... args) { (wait_for_scalar(args), ...); }
+
 // Where slot s lives.  Two dense tensors (sh = 0): I[s], M[s].  One tensor of 16-byte records (sh = 1): the id of
 // slot s is the int64 at I + 2 s, its metadata the int32 at M + 4 s -- the line that a probe fetches then also
 // holds the metadata word that a hit refreshes.
