@@ -464,11 +464,11 @@ mpzch_status_t run_remap(Scratch &sc, Timing &tm, const Params &p, int32_t max_p
     return st;
 }
 
-template <int SHIFT>
+template <int SHIFT, bool EVEN>
 mpzch_status_t launch_discover_chunk(const Params &p, int grid, hipStream_t s)
 {
-    if (p.t0.sh) TRY(launch(k_discover_chunk<true, SHIFT>, grid, kBlock << SHIFT, s, p));
-    else TRY(launch(k_discover_chunk<false, SHIFT>, grid, kBlock << SHIFT, s, p));
+    if (p.t0.sh) TRY(launch(k_discover_chunk<true, SHIFT, EVEN>, grid, kBlock << SHIFT, s, p));
+    else TRY(launch(k_discover_chunk<false, SHIFT, EVEN>, grid, kBlock << SHIFT, s, p));
     return MPZCH_OK;
 }
 
@@ -488,13 +488,26 @@ mpzch_status_t launch_allocate_chunk(const Params &p, int grid, int num_cus, hip
     return MPZCH_OK;
 }
 
+// Calls whose first looks go before the later ones (k_discover_chunk): more than three workgroups per compute unit, all of
+// them resident with room to spare (records need more registers: up to five; those beyond start when others end, and come last
+// anyway), windows of up to 32 slots.  Whole steps without / with, 60 M slots, us, in this order TTL at 0.7 with windows of 16, at 0.95
+// of 32, LRU at 0.95 of 32, at 0.9 of 8.  Two tensors: 200 K positions 32.9 / 32.8, 34.5 / 33.7, 39.6 / 38.9, 33.3 / 32.7; 400 K 52.8 /
+// 51.8, 55.7 / 54.1, 65.1 / 62.1, 53.3 / 51.9.  Records: 150 K 27.1 / 27.4, 28.4 / 28.4, 39.1 / 39.1 and, of 16, LRU, 200 K 31.7 / 31.6, 33.6 /
+// 33.7, 41.6 / 40.7, 32.6 / 32.7; 250 K 36.0 / 35.7, 38.4 / 38.2, 46.8 / 45.3, 37.4 / 36.8; 400 K 51.1 / 49.5, 53.3 / 55.4, 65.4 / 67.5, 51.1 /
+// 51.0.  Windows of 64: 300 K, LRU, 71.4 / 72.0, 12 loads of 262 144 ids 733 / 738.
+constexpr bool even_looks(int64_t groups, int num_cus, bool records, int32_t P)
+{
+    return P <= 32 && groups > 3 * (int64_t)num_cus && groups <= (records ? 5 : 8) * (int64_t)num_cus;
+}
+
 // One chunk per wavefront (mpzch_chunk_kernels.hpp): grid = workgroups of 256 positions.
 mpzch_status_t launch_remap_chunks(Timing &tm, const Params &p, int32_t max_p_lru, int grid, int num_cus, hipStream_t s)
 {
     const bool rec = p.t0.sh != 0;
     if (!tm.begin(KDiscover, s)) return MPZCH_ERR_HIP;
-    if (window_shift(p.t0.P) == 1 && 2 * p.n <= kShortBlocks) TRY(launch_discover_chunk<1>(p, grid, s));
-    else TRY(launch_discover_chunk<0>(p, grid, s));
+    if (window_shift(p.t0.P) == 1 && 2 * p.n <= kShortBlocks) TRY(launch_discover_chunk<1, false>(p, grid, s));
+    else if (even_looks(grid, num_cus, rec, p.t0.P)) TRY(launch_discover_chunk<0, true>(p, grid, s));
+    else TRY(launch_discover_chunk<0, false>(p, grid, s));
     if (!tm.end(s) || !tm.begin(KAllocate, s)) return MPZCH_ERR_HIP;
     if (max_p_lru > 0 && rec) TRY(launch_allocate_lru_chunk<true>(max_p_lru, p, grid, num_cus, s));
     else if (max_p_lru > 0) TRY(launch_allocate_lru_chunk<false>(max_p_lru, p, grid, num_cus, s));

@@ -153,7 +153,12 @@ __device__ __forceinline__ uint32_t first_occurrence(const Params &p, uint32_t p
 // while the call has no more than kShortBlocks blocks), and the workgroup's 256 positions have 512 threads.  65 536
 // positions per step, the 50-step pass 1 078 -> 1 056 us.  Longer windows gain nothing by it: what a look less saves, the
 // barriers of 1 024 threads and the copies of an id that no longer meet in one wavefront cost.
-template <bool REC, int SHIFT>
+//
+// EVEN: where there are several workgroups per compute unit its memory pipe has more requests than it takes at a time, and the
+// older wavefronts go first, with all their looks, so that the youngest come to their first one when the others are
+// through (300 007 positions, windows of 32 slots at 95 % load: the first look is there after 2 to 15 us) and their
+// chain of looks ends the call, alone.  With a priority that falls from look to look they end together.  even_looks says when.
+template <bool REC, int SHIFT, bool EVEN>
 __global__ __launch_bounds__(kBlock << SHIFT, 4) void k_discover_chunk(Params p)
 {
     constexpr int THREADS = kBlock << SHIFT, WAVES = THREADS / kWave, PER = kWave >> SHIFT;
@@ -172,6 +177,7 @@ __global__ __launch_bounds__(kBlock << SHIFT, 4) void k_discover_chunk(Params p)
     const int64_t home = home_of(hash, d.N);
     bool fresh = false;
     int res = kProbeGoOn, q = 0;
+    if constexpr (EVEN) __builtin_amdgcn_s_setprio(3);
     if constexpr (SHIFT == 0) {
         // first block: the aligned one, or in a table that the caches hold the 8 slots from the home slot on (k_allocate)
         const uint32_t lane_bytes = first_lane_bytes(d);
@@ -180,14 +186,20 @@ __global__ __launch_bounds__(kBlock << SHIFT, 4) void k_discover_chunk(Params p)
         else
             res = probe_first<false, REC, false>(d, id, home, lane_bytes, s_req[w], s_code[w], p.step, &fresh, &q);
     }
+    if constexpr (EVEN) __builtin_amdgcn_s_setprio(2);
     int left = SHIFT == 0 ? d.P - 1 : d.P;
-    for (;;) {
+    for (bool second = true;; second = false) {
         const bool need = valid && res == kProbeGoOn && q < d.P;
         if (!__any(need)) break;
         bool f = false;
         const int got = probe_more<false, REC>(d, d.sh, slots_up_to_widest(d), id, home, q, left, need, s_req[w], s_code[w], p.step, &f);
         if (need) { res = got; fresh = f; }
+        if constexpr (EVEN) {
+            if (second) __builtin_amdgcn_s_setprio(1);
+            else __builtin_amdgcn_s_setprio(0);
+        }
     }
+    if constexpr (EVEN) __builtin_amdgcn_s_setprio(3);
     const bool hit = valid && res >= 0, miss = valid && res < 0;
     const uint32_t e = set_insert_wave(p, miss, id, hash, (uint32_t)pos, reinterpret_cast<MetaMerge *>(s_req[w]));
     const int64_t slot = hit ? wrap(home + res, d.N) : home;

@@ -164,6 +164,20 @@ def test_batches_around_the_largest_one_chunk_call(n):
     t.close()
 
 
+# ---- one-chunk calls whose first looks go before the later ones: on both sides of each line
+@pytest.mark.parametrize("evict", [True, "lru"])
+@pytest.mark.parametrize("groups,layout", [(3, "separate"), (3, "records"), (5, "records")])
+def test_calls_around_the_lines_of_even_looks(groups, layout, evict):
+    """Crowded windows, so that most ids take several looks; n at the line and one position beyond it."""
+    rng = rng_for(917)
+    n = groups * torch.cuda.get_device_properties(0).multi_processor_count * 256
+    slots = n // 2
+    t = Pair(slots, 29, 1, evict, 47, layout=layout)
+    for step, more in enumerate([0, 1, 0, 1]):
+        t.step(rng.integers(0, 2 * slots, size=n + more), step)
+    t.close()
+
+
 # ---- expiry steps: the copies of a popular id agree on their maximum in LDS before they store it
 @pytest.mark.parametrize("layout", ["separate", "records"])
 @pytest.mark.parametrize("n", [3, 64, 100, 257, 20_011, 530_000])
