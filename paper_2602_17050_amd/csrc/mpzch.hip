@@ -416,10 +416,10 @@ mpzch_status_t launch_allocate(int32_t max_p_lru, const Params &p, int num_cus, 
 // Groups of at most one workgroup of k_finalize per compute unit have no use for a second one beside it (k_finalize: WAVES).
 mpzch_status_t launch_finalize(const Params &p, int grid, int num_cus, hipStream_t s)
 {
-    if (p.num_tables > 1 && grid <= num_cus) TRY(launch(k_finalize<true, false, 4>, grid, kFinalizeBlock, s, p));
-    else if (p.num_tables > 1) TRY(launch(k_finalize<true, false>, grid, kFinalizeBlock, s, p));
-    else if (p.t0.evict == 2) TRY(launch(k_finalize<false, false>, grid, kFinalizeBlock, s, p));
-    else TRY(launch(k_finalize<false, true>, grid, kFinalizeBlock, s, p));
+    if (p.num_tables > 1 && grid <= num_cus) TRY(launch(k_finalize<true, false, 4>, kFinalizeExtra + grid, kFinalizeBlock, s, p));
+    else if (p.num_tables > 1) TRY(launch(k_finalize<true, false>, kFinalizeExtra + grid, kFinalizeBlock, s, p));
+    else if (p.t0.evict == 2) TRY(launch(k_finalize<false, false>, kFinalizeExtra + grid, kFinalizeBlock, s, p));
+    else TRY(launch(k_finalize<false, true>, kFinalizeExtra + grid, kFinalizeBlock, s, p));
     return MPZCH_OK;
 }
 

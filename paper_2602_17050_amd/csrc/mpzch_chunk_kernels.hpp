@@ -3,10 +3,10 @@
 //
 // Such a call is bound by latency: every kernel is a chain of dependent round trips to memory (0.6 to 1 us each),
 // and the kernels wait for each other.  The kernels of mpzch_kernels.hpp compact the missed positions into lists, add
-// their counters to shared words and let the workgroup that finishes last publish them; none of that pays here.
+// their counters to shared words and reserve their parts of the evicted list by atomics; none of that pays here.
 // In these kernels lane L of wavefront W works on position 64 W + L in all three phases, what one phase leaves for the
 // next is stored by position, and counters are stored per workgroup and summed by the last kernel: no shared
-// counter, no arrival word, no list.
+// counter, no reservation, no list.
 //   k_discover_chunk   Pass 1; the whole window of every id is looked at in registers (nothing is parked); missed
 //                      ids enter the scratch set.
 //   k_allocate_chunk   claims.  The first block of every window is requested together with the election of the
@@ -75,18 +75,6 @@ __device__ __forceinline__ uint32_t set_insert_chunk(const Params &p, int64_t id
 // (without eviction: the first empty slot), at most kStartMax; kStartNever: there is none in its window.  (Of the others 0: a
 // line that is written as a whole need not be fetched.)
 constexpr uint32_t kStartMax = 0xFE, kStartNever = 0xFF;
-
-// Sum over the wavefront of 32-bit values whose total fits 32 bits, in every lane.
-__device__ __forceinline__ uint32_t wave_sum32(uint32_t x)
-{
-    x += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x111, 0xF, 0xF, false);      // row_shr:1
-    x += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x112, 0xF, 0xF, false);      // row_shr:2
-    x += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x114, 0xF, 0xF, false);      // row_shr:4
-    x += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x118, 0xF, 0xF, false);      // row_shr:8
-    x += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x142, 0xA, 0xF, false);      // row_bcast:15
-    x += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x143, 0xC, 0xF, false);      // row_bcast:31
-    return (uint32_t)__builtin_amdgcn_readlane((int)x, kWave - 1);
-}
 
 // counters of one workgroup, three words: positions (hit, miss, invalid), probe lengths (hits, misses), outcomes
 // (distinct ids, inserts, evictions); the first ones of all workgroups, then the second ones, then the third ones

@@ -17,11 +17,11 @@
 //                with the claimant of the lowest (round, position); a claimant that is
 //                displaced is carried on by the displacing lane from its next round.  The
 //                fixed point is the unique stable assignment, the same one a sequential
-//                round-major / position-minor sweep produces.
+//                round-major / position-minor sweep produces.  The outcomes are counted here.
 //   k_finalize   every listed position finds the slot that carries its id's claim; the elected one
 //                replaces the tag by the id, sets the metadata and reports evicted slots; ids
 //                without a claim fall back to home.  The scratch set entries that were used are
-//                emptied again; the workgroup that finishes last publishes the call's counters.
+//                emptied again; a workgroup of its own publishes the call's counters meanwhile.
 // k_allocate / k_finalize work with one lane per claimant.  Tables under the LRU policy allocate in
 // k_allocate_lru (a group of lanes per claimant) or k_allocate_lru_long (probe ranges beyond 64 slots).
 //
@@ -66,24 +66,22 @@ struct TableDesc {
 // Counters of one call.  Every workgroup adds its partial counts once, into one of kBins copies of the
 // counters chosen by its index: an atomic on ONE address costs about 12 ns whatever it adds, so a
 // few thousand workgroups on one address would take longer than the kernel, spread over kBins addresses
-// they vanish in it.  The workgroup of k_finalize that finishes last sums the copies, publishes the
-// totals and clears the block: it is all zero between calls (so a captured launch sequence can be replayed).
+// they vanish in it.  Pass 1 and the allocation count; a workgroup of k_finalize sums the copies, publishes the
+// totals and clears them (publish_counters), while the others work: the counters are zero between calls (so a captured
+// launch sequence can be replayed).
 constexpr int kBins = 16;
+// One table: k_allocate's wavefronts, workgroups of one, have this many times as many copies, the other tables' counters.
+constexpr int kSpread = 8;
 struct Control {
-    unsigned long long num_evicted[kMaxTables];
+    unsigned long long num_evicted[kMaxTables];       // k_finalize: how much of the evicted lists is taken (cleared by the allocation)
     unsigned long long stats[kBins][kMaxTables][kStatCount];
-    unsigned long long done;       // workgroups that have finished (k_finalize: counted in the bits from kArriveShift up)
+    unsigned long long done;       // counting lookups: workgroups that have finished
 };
-// k_finalize reports in by adding kArriveOne to `done`.  With one table the same atomic also reserves the
-// workgroup's part of the evicted list, whose length is kept in the low bits of `done` (num_evicted[0]
-// stays unused): one round trip to one address at the end of a workgroup instead of two to two.
-// Workgroups of 16 wavefronts: at 12 ns each the arrivals of 2 048 workgroups of four took 25 us, however little
+// Workgroups of 16 wavefronts: at 12 ns each the reservations of 2 048 workgroups of four took 25 us, however little
 // there was to do (batch of 700 K positions 35 -> 19 us).
 constexpr int kFinalizeBlock = 1024;
 constexpr int kFinalizeWaves = kFinalizeBlock / kWave;
-constexpr int kArriveShift = 40;
-constexpr unsigned long long kArriveOne = 1ull << kArriveShift;
-constexpr unsigned long long kEvictedMask = kArriveOne - 1ull;
+constexpr int kFinalizeExtra = 1;      // workgroups of k_finalize beside those that walk the lists
 
 struct Params {
     const int64_t *ids;
@@ -468,6 +466,18 @@ __device__ __forceinline__ int next_bits(uint64_t &amask, int g)
     return b;
 }
 
+// Sum over the wavefront of 32-bit values whose total fits 32 bits, in every lane.
+__device__ __forceinline__ uint32_t wave_sum32(uint32_t x)
+{
+    x += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x111, 0xF, 0xF, false);      // row_shr:1
+    x += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x112, 0xF, 0xF, false);      // row_shr:2
+    x += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x114, 0xF, 0xF, false);      // row_shr:4
+    x += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x118, 0xF, 0xF, false);      // row_shr:8
+    x += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x142, 0xA, 0xF, false);      // row_bcast:15
+    x += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x143, 0xC, 0xF, false);      // row_bcast:31
+    return (uint32_t)__builtin_amdgcn_readlane((int)x, kWave - 1);
+}
+
 __device__ __forceinline__ unsigned long long *stat_word(const Params &p, int table, int k)
 {
     return &p.ctl->stats[blockIdx.x % kBins][table][k];
@@ -502,40 +512,97 @@ __device__ __forceinline__ void block_stat_add(const Params &p, const int *idx, 
     }
 }
 
-// Sums the kBins copies of the call's counters, writes out_num_evicted / out_stats and clears the block.
-// Run by the workgroup that finishes last (of k_finalize; of a counting lookup).
+// Sums the copies of the call's counters, writes out_num_evicted / out_stats and clears them.  Run by a workgroup of
+// k_finalize of its own; of a counting lookup by the one that finishes last.
 template <int THREADS>
-__device__ __forceinline__ void publish_counters(const Params &p, unsigned long long (*s_bins)[kStatCount])
+__device__ __forceinline__ void publish_counters(const Params &p, unsigned long long (*s_sum)[kStatCount])
 {
-    if (p.out_num_evicted) {
-        if (p.num_tables > 1) {
-            for (int i = threadIdx.x; i < p.num_tables; i += THREADS)
-                p.out_num_evicted[i] =
-                    (int64_t)__hip_atomic_load(&p.ctl->num_evicted[i], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        } else if (threadIdx.x == 0) {
-            p.out_num_evicted[0] =
-                (int64_t)(__hip_atomic_load(&p.ctl->done, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) & kEvictedMask);
+    const bool multi = p.num_tables > 1;
+    const int tables = multi ? p.num_tables : 1, words = (multi ? p.num_tables : kSpread) * kStatCount;
+    unsigned long long *const sum = &s_sum[0][0];
+    for (int i = threadIdx.x; i < tables * kStatCount; i += THREADS) sum[i] = 0;
+    __syncthreads();
+    for (int k = threadIdx.x; k < words; k += THREADS) {
+        // (all copies requested at once)
+        unsigned long long *const at = &p.ctl->stats[0][0][0] + k;
+        constexpr int kNext = kMaxTables * kStatCount;
+        unsigned long long v[kBins], total = 0;
+#pragma unroll
+        for (int b = 0; b < kBins; ++b) v[b] = __hip_atomic_load(at + b * kNext, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+#pragma unroll
+        for (int b = 0; b < kBins; ++b) {
+            total += v[b];
+            if (v[b]) at[b * kNext] = 0;
         }
-    }
-    if (p.out_stats) {
-        const int nbins = p.num_tables * kStatCount;
-        for (int i = threadIdx.x; i < nbins; i += THREADS) {
-            unsigned long long v = 0;
-            for (int b = 0; b < kBins; ++b)
-                v += __hip_atomic_load(&p.ctl->stats[b][i / kStatCount][i % kStatCount], __ATOMIC_RELAXED,
-                                       __HIP_MEMORY_SCOPE_AGENT);
-            s_bins[i / kStatCount][i % kStatCount] = v;
-        }
-        __syncthreads();
-        for (int t = threadIdx.x; t < p.num_tables; t += THREADS)
-            s_bins[t][kDistinctMiss] = s_bins[t][kInserts] + s_bins[t][kEvictions] + s_bins[t][kCollisions];
-        __syncthreads();
-        for (int i = threadIdx.x; i < nbins; i += THREADS)
-            p.out_stats[i] = (int64_t)s_bins[i / kStatCount][i % kStatCount];
+        if (total) atomicAdd(&sum[multi ? k : k % kStatCount], total);
     }
     __syncthreads();
-    unsigned long long *z = reinterpret_cast<unsigned long long *>(p.ctl);
-    for (int i = threadIdx.x; i < (int)(sizeof(Control) / sizeof(unsigned long long)); i += THREADS) z[i] = 0ull;
+    for (int i = threadIdx.x; i < tables * kStatCount; i += THREADS) {
+        const unsigned long long *const t = s_sum[i / kStatCount];
+        const int k = i % kStatCount;
+        if (p.out_stats) p.out_stats[i] = (int64_t)(k == kCollisions ? t[kDistinctMiss] - t[kInserts] - t[kEvictions] : t[k]);
+        if (p.out_num_evicted && k == kEvictions) p.out_num_evicted[i / kStatCount] = (int64_t)t[k];
+    }
+}
+
+// The outcomes of the claimants that a wavefront of the allocation has served, of one table at a time.  A claim that meets a slot
+// nobody has claimed yet is an insert or an eviction whatever displacements follow, so they are known when the claims stand.
+// (In LDS, a word per lane: these kernels have no register left.)
+struct Outcomes {
+    uint32_t *agents;                                // LDS, kWave words each
+    uint32_t *placed;                                // inserts and, 16 bits up, evictions
+    int table;
+};
+struct OutcomeArea {
+    uint32_t agents[kWave];
+    uint32_t placed[kWave];
+};
+// (the kernels of the allocation also clear what k_finalize counts in: it is all zero for it, whatever it left behind)
+__device__ __forceinline__ Outcomes no_outcomes(const Params &p, OutcomeArea &s)
+{
+    static_assert(kMaxTables == kWave, "a word per lane");
+    if (blockIdx.x == 0) p.ctl->num_evicted[lane_id()] = 0;
+    s.agents[lane_id()] = 0;
+    s.placed[lane_id()] = 0;
+    return Outcomes{s.agents, s.placed, 0};
+}
+// (a wavefront has at most 2^30 positions / 8 192 segments, or 2^17, and a lane an eighth of them)
+__device__ __forceinline__ void count_placed(Outcomes &o, int64_t old)
+{
+    if (!is_tag(old))
+        __hip_atomic_fetch_add(&o.placed[lane_id()], old == -1 ? 1u : 1u << 16, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WAVEFRONT);
+}
+__device__ __forceinline__ void count_agent(Outcomes &o)
+{
+    __hip_atomic_fetch_add(&o.agents[lane_id()], 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WAVEFRONT);
+}
+// counts: whether what this lane has counted is to be added (one lane of those that serve a claimant)
+template <bool MULTI>
+__device__ __forceinline__ void add_outcomes(const Params &p, Outcomes &o, bool counts)
+{
+    static_assert(kInserts == kDistinctMiss + 1 && kEvictions == kDistinctMiss + 2, "three words side by side");
+    const int lane = lane_id();
+    const uint32_t a = counts ? o.agents[lane] : 0u, placed = counts ? o.placed[lane] : 0u, i = placed & 0xFFFFu, e = placed >> 16;
+    if (!__any(a)) return;
+    uint32_t v;
+    if (!__any((a | i | e) >> 4)) {                  // up to 15 each, as nearly always: one sum of three times ten bits
+        v = wave_sum32(a | i << 10 | e << 20) >> (10 * (lane < 3 ? lane : 0)) & 0x3FFu;
+    } else {
+        const uint32_t agents = wave_sum32(a), inserts = wave_sum32(i), evictions = wave_sum32(e);
+        v = lane == 0 ? agents : lane == 1 ? inserts : evictions;
+    }
+    if (lane < 3 && v)
+        atomicAdd(stat_word(p, MULTI ? o.table : (int)(blockIdx.x / kBins) % kSpread, kDistinctMiss + lane), (unsigned long long)v);
+}
+// what follows is counted for table f (the same in all lanes)
+template <bool MULTI>
+__device__ __forceinline__ void count_for(const Params &p, Outcomes &o, int f, bool counts)
+{
+    if (!MULTI || f == o.table) return;
+    add_outcomes<MULTI>(p, o, counts);
+    o.agents[lane_id()] = 0;
+    o.placed[lane_id()] = 0;
+    o.table = f;
 }
 
 // ------------------------------------------------------------------ Pass 1 (discovery)
@@ -1169,14 +1236,17 @@ __device__ __forceinline__ void discover_body(const Params &p)
         block_stat_add(p, idx, vals, 5, t_f, s_red, s_tab);
     }
     if constexpr (COUNT && !TRAIN) {
-        // a counting lookup publishes its own counters (see finalize_body for the training remap)
+        // a counting lookup publishes its own counters (see k_finalize for the training remap)
         __shared__ unsigned long long s_bins[kMaxTables][kStatCount];
         __shared__ bool s_last;
         __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
         __syncthreads();
         if (threadIdx.x == 0) s_last = atomicAdd(&p.ctl->done, 1ull) == (unsigned long long)(gridDim.x - 1);
         __syncthreads();
-        if (s_last) publish_counters<kBlock>(p, s_bins);
+        if (s_last) {
+            publish_counters<kBlock>(p, s_bins);
+            if (threadIdx.x == 0) p.ctl->done = 0;
+        }
     }
 }
 
@@ -1535,15 +1605,16 @@ __device__ __forceinline__ void claim_walk(const Tab &d, Claimant &c, const Clai
 // table at a time (nearly always all of them: a segment is a few thousand positions, a feature's share many times that).
 template <bool MULTI, bool REC>
 __device__ __forceinline__ void allocate_body(const Params &p, int64_t vblock, int64_t vgrid,
-                                              uint8_t *s_code, ClaimReq *s_req)
+                                              uint8_t *s_code, ClaimReq *s_req, OutcomeArea &s_outcomes)
 {
     const int lane = lane_id();
     const Tab d0 = view(p.t0);
     const int64_t lane_offset = MULTI ? table_offsets(p.offsets, p.num_tables) : 0;
+    Outcomes outcomes = no_outcomes(p, s_outcomes);
     for (int64_t seg = vblock; seg < p.num_segs; seg += vgrid) {
         const uint32_t cnt = p.seg_cnt[seg];
         const int64_t seg_base = seg * p.seg_chunks * kWave;
-        if (seg_base >= p.n) break;                           // segments past the batch hold nothing
+        if ((int32_t)seg_base >= (int32_t)p.n) break;                           // segments past the batch hold nothing
         int seg_f = 0;
         Tab seg_d = d0;
         bool seg_one = true;
@@ -1579,11 +1650,12 @@ __device__ __forceinline__ void allocate_body(const Params &p, int64_t vblock, i
             while (__any(todo)) {
                 Tab d = seg_d;
                 bool agent = todo;
+                int of_table = seg_f;
                 if constexpr (MULTI) {
                     if (!seg_one) {
-                        const int of_head = __builtin_amdgcn_readlane(f, __ffsll((unsigned long long)__ballot(todo)) - 1);
-                        agent = todo && f == of_head;
-                        d = uniform(view(p.descs[of_head]));
+                        of_table = __builtin_amdgcn_readlane(f, __ffsll((unsigned long long)__ballot(todo)) - 1);
+                        agent = todo && f == of_table;
+                        d = uniform(view(p.descs[of_table]));
                     }
                     todo = todo && !agent;
                     // claimants of LRU tables are served by k_allocate_lru
@@ -1594,9 +1666,11 @@ __device__ __forceinline__ void allocate_body(const Params &p, int64_t vblock, i
                 } else {
                     todo = false;
                 }
+                if constexpr (MULTI) count_for<MULTI>(p, outcomes, of_table, true);
+                if (agent) count_agent(outcomes);
                 const int32_t bound = expiry_bound(d, p.step);
                 const bool aligned = (d.N << (3 + d.sh)) > kCachedTableBytes;
-                uint32_t hint = kHintUnplaced, occ = 0;
+                uint32_t hint = kHintUnplaced;        // (and kAgentOcc)
                 // the claimant this lane carries
                 Claimant c;
                 c.active = agent;
@@ -1615,11 +1689,11 @@ __device__ __forceinline__ void allocate_body(const Params &p, int64_t vblock, i
                                    [&](uint32_t who, int32_t round, int64_t, int64_t old) {
                                        const uint32_t at = round < (int32_t)kHintUnknown ? (uint32_t)round : kHintUnknown;
                                        if (who == pos) {
-                                           hint = at;
-                                           occ = (is_tag(old) ? tag_occ(old) != 0 : old >= 0) ? kAgentOcc : 0u;
+                                           hint = at | ((is_tag(old) ? tag_occ(old) != 0 : old >= 0) ? kAgentOcc : 0u);
                                        } else {
                                            p.hint[who] = (uint8_t)at;
                                        }
+                                       count_placed(outcomes, old);
                                        if (!MULTI && is_tag(old)) p.note[tag_pos(old)] = 1;
                                    },
                                    [](uint32_t) {});
@@ -1627,12 +1701,13 @@ __device__ __forceinline__ void allocate_body(const Params &p, int64_t vblock, i
                 }
                 if (agent) {
                     if (!alone) p.hint[pos] = (uint8_t)hint;  // for the copies of the id
-                    p.first_of[idx] = kAgentEntry | (MULTI ? 0u : occ) | hint;
+                    p.first_of[idx] = kAgentEntry | (MULTI ? hint & 0xFFu : hint);
                 }
             }
             __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
         }
     }
+    add_outcomes<MULTI>(p, outcomes, true);
 }
 
 template <bool MULTI, bool REC>
@@ -1640,7 +1715,8 @@ __global__ __launch_bounds__(kWave, MULTI ? 5 : 7) void k_allocate(Params p)
 {
     __shared__ __attribute__((aligned(16))) uint8_t s_code[kWave * kAllocG];
     __shared__ ClaimReq s_req[kWave];
-    allocate_body<MULTI, REC>(p, blockIdx.x, gridDim.x, s_code, s_req);
+    __shared__ OutcomeArea s_outcomes;
+    allocate_body<MULTI, REC>(p, blockIdx.x, gridDim.x, s_code, s_req, s_outcomes);
 }
 
 // ------------------------------------------------------------------ allocation, LRU policy
@@ -1822,12 +1898,14 @@ __global__ __launch_bounds__(kWave, MULTI ? (T == 8 ? 3 : 4) : T == 8 ? 4 : T ==
     const int lane = threadIdx.x;
     const int g = lane / G;
     const Tab d0 = view(MULTI ? p.descs[0] : p.t0);
+    __shared__ OutcomeArea s_outcomes;
+    Outcomes outcomes = no_outcomes(p, s_outcomes);
     for (int64_t seg = blockIdx.x; seg < p.num_segs; seg += gridDim.x) {
-        const uint32_t cnt = p.seg_cnt[seg];
+        const uint32_t cnt = (uint32_t)uniform32((int)p.seg_cnt[seg]);
         const int64_t seg_base = seg * p.seg_chunks * kWave;
-        if (seg_base >= p.n) break;
+        if ((int32_t)seg_base >= (int32_t)p.n) break;
         for (uint32_t j0 = 0; j0 < cnt; j0 += kWave) {
-            const int64_t idx = seg_base + j0 + lane;
+            const uint32_t idx = (uint32_t)seg_base + j0 + (uint32_t)lane;
             const bool have = j0 + lane < cnt;
             uint32_t pos = 0, e = 0, first = 0;
             int64_t home = 0;
@@ -1854,9 +1932,9 @@ __global__ __launch_bounds__(kWave, MULTI ? (T == 8 ? 3 : 4) : T == 8 ? 4 : T ==
             int src = next_bits<G>(am, g);
             uint32_t cpos = __shfl(pos, src >= 0 ? src : lane);
             int64_t chome = shfl64(home, src >= 0 ? src : lane);
-            const int f1 = __shfl(f, src >= 0 ? src : lane);
+            int fc = __shfl(f, src >= 0 ? src : lane);
             Tab d = d0;
-            if (MULTI && src >= 0) d = view(p.descs[f1]);
+            if (MULTI && src >= 0) d = view(p.descs[fc]);
             LruSlots<T> x = load_lru_slots<T, REC>(d, src >= 0, chome);
             while (__any(src >= 0)) {
                 const int src2 = next_bits<G>(am, g);
@@ -1867,9 +1945,17 @@ __global__ __launch_bounds__(kWave, MULTI ? (T == 8 ? 3 : 4) : T == 8 ? 4 : T ==
                 if (MULTI && src2 >= 0) d2 = view(p.descs[f2]);
                 const LruSlots<T> x2 = load_lru_slots<T, REC>(d2, src2 >= 0, chome2);
                 int32_t fr = -1;
+                bool counted = src >= 0;             // (else: of a table beside the one that is counted for, at a feature's end)
+                if constexpr (MULTI) {
+                    count_for<MULTI>(p, outcomes, __builtin_amdgcn_readlane(fc, __ffsll((unsigned long long)__ballot(counted)) - 1), lane % G == 0);
+                    counted = counted && fc == outcomes.table;
+                }
+                if (counted) count_agent(outcomes);
                 claim_group_lru<T, REC>(p, d, src >= 0, cpos, chome, x,
-                                        [&](uint32_t who, int32_t, int32_t round, int64_t, int64_t) {
+                                        [&](uint32_t who, int32_t, int32_t round, int64_t, int64_t old) {
                                             if (who == cpos) fr = round;
+                                            if (!MULTI || counted) count_placed(outcomes, old);
+                                            else if (lane % G == 0 && !is_tag(old)) atomicAdd(stat_word(p, fc, old == -1 ? kInserts : kEvictions), 1ull);
                                         },
                                         [](uint32_t) {});
                 // the outcome goes to the lane that holds the claimant's list entry
@@ -1878,6 +1964,10 @@ __global__ __launch_bounds__(kWave, MULTI ? (T == 8 ? 3 : 4) : T == 8 ? 4 : T ==
                     const int sk = __shfl(src, k * G);
                     const int32_t frk = __shfl(fr, k * G);
                     if (lane == sk) hint = frk < 0 ? kHintUnplaced : (uint32_t)frk;
+                }
+                if constexpr (MULTI) {
+                    if (src >= 0 && !counted && lane % G == 0) atomicAdd(stat_word(p, fc, kDistinctMiss), 1ull);
+                    fc = f2;
                 }
                 src = src2;
                 cpos = cpos2;
@@ -1890,6 +1980,7 @@ __global__ __launch_bounds__(kWave, MULTI ? (T == 8 ? 3 : 4) : T == 8 ? 4 : T ==
             else if (!MULTI && have) p.first_of[idx] = first;     // (several tables: k_allocate has written it)
         }
     }
+    add_outcomes<MULTI>(p, outcomes, lane % G == 0);
 }
 
 // LRU for probe ranges of 65 .. 1 024 slots: the whole wavefront serves one claimant, a lane holds
@@ -1910,7 +2001,7 @@ __device__ __forceinline__ uint64_t wave_min64(uint64_t x)
     return x;
 }
 
-__device__ __forceinline__ int32_t claim_wave_lru_long(const Params &p, const Tab &d, uint32_t cpos, int32_t choice)
+__device__ __forceinline__ int32_t claim_wave_lru_long(const Params &p, const Tab &d, uint32_t cpos, int32_t choice, Outcomes &outcomes)
 {
     const int lane = lane_id();
     const int C = (d.P + kWave - 1) / kWave;             // <= kLruLongSlots (checked when the table is created)
@@ -1986,6 +2077,7 @@ __device__ __forceinline__ int32_t claim_wave_lru_long(const Params &p, const Ta
             if (is_tag(old) && old < mine) continue;                    // a better claim holds this slot
             placed = true;
             displaced = is_tag(old) ? old : 0;
+            count_placed(outcomes, old);
             if (is_first) first_round = round;
         }
         is_first = false;
@@ -2001,10 +2093,12 @@ __global__ __launch_bounds__(kWave) void k_allocate_lru_long(Params p)
 {
     const int lane = threadIdx.x;
     const Tab d0 = view(MULTI ? p.descs[0] : p.t0);
+    __shared__ OutcomeArea s_outcomes;
+    Outcomes outcomes = no_outcomes(p, s_outcomes);
     for (int64_t seg = blockIdx.x; seg < p.num_segs; seg += gridDim.x) {
         const uint32_t cnt = p.seg_cnt[seg];
         const int64_t seg_base = seg * p.seg_chunks * kWave;
-        if (seg_base >= p.n) break;
+        if ((int32_t)seg_base >= (int32_t)p.n) break;
         for (uint32_t j0 = 0; j0 < cnt; j0 += kWave) {
             const int64_t idx = seg_base + j0 + lane;
             const bool have = j0 + lane < cnt;
@@ -2029,7 +2123,9 @@ __global__ __launch_bounds__(kWave) void k_allocate_lru_long(Params p)
                 const uint32_t cpos = __shfl(pos, src);
                 const int fs = __shfl(f, src);
                 const Tab d = MULTI ? view(p.descs[fs]) : d0;
-                const int32_t fr = claim_wave_lru_long(p, d, cpos, 0);
+                count_for<MULTI>(p, outcomes, fs, lane == 0);
+                count_agent(outcomes);
+                const int32_t fr = claim_wave_lru_long(p, d, cpos, 0, outcomes);
                 if (lane == src)
                     hint = fr < 0 ? kHintUnplaced : (fr < (int32_t)kHintUnknown ? (uint32_t)fr : kHintUnknown);
             }
@@ -2038,6 +2134,7 @@ __global__ __launch_bounds__(kWave) void k_allocate_lru_long(Params p)
             else if (!MULTI && have) p.first_of[idx] = first;     // (several tables: k_allocate has written it)
         }
     }
+    add_outcomes<MULTI>(p, outcomes, lane == 0);
 }
 
 // ------------------------------------------------------------------ finalize
@@ -2074,9 +2171,7 @@ __device__ __forceinline__ void flush_evicted(const Params &p, const int64_t *bu
     reset_staged_rows(p, rows_buf, count);
     const int lane = lane_id();
     unsigned long long base = 0;
-    if (lane == 0)
-        base = p.num_tables > 1 ? atomicAdd(&p.ctl->num_evicted[table], (unsigned long long)count)
-                                : atomicAdd(&p.ctl->done, (unsigned long long)count) & kEvictedMask;
+    if (lane == 0) base = atomicAdd(&p.ctl->num_evicted[table], (unsigned long long)count);
     base = (unsigned long long)shfl64((int64_t)base, 0);
     // (separate statements: a choice between the descriptor in the kernel arguments and one in global memory,
     // written as one expression, is compiled into loads through a generic pointer)
@@ -2093,79 +2188,42 @@ __device__ __forceinline__ void flush_evicted(const Params &p, const int64_t *bu
     count = 0;
 }
 
-// Book-keeping shared by both forms of k_finalize: counters for one table at a time in
-// registers, evicted slots staged per wavefront in LDS.
-struct FinalizeState {
-    int ev_cnt = 0, ev_table = 0;                       // (all members are the same in every lane)
-    unsigned long long st_ins = 0, st_evi = 0, st_col = 0;
-    int st_table = 0;
+// Evicted slots staged per wavefront in LDS (all members are the same in every lane).
+struct Staged {
+    int count = 0, table = 0;
 };
 
-// Called by all lanes of the wavefront.  `done` lanes finished a claimant of table f with
-// outcome 0 = insert, 1 = eviction of slot s, 2 = collision.
-template <bool MULTI>
-__device__ __forceinline__ void finalize_account(const Params &p, FinalizeState &fs, int64_t *s_ev_w, int64_t *s_row_w,
-                                                 bool done, int outcome, int64_t s, int f, bool want_stats)
+// Called by all lanes of the wavefront.  `evicted` lanes hold an evicted slot s of table f.
+__device__ __forceinline__ void stage_evicted(const Params &p, Staged &st, int64_t *s_ev_w, int64_t *s_row_w, bool evicted, int64_t s, int f)
 {
     const int lane = lane_id();
-    if (want_stats) {
-        const uint64_t dm = __ballot(done);
-        if (MULTI && dm) {
-            const int f0 = __shfl(f, __ffsll((unsigned long long)dm) - 1);
-            if (f0 != fs.st_table) {
-                // rare (feature boundary): hand the counters over through atomics
-                if (lane == 0) {
-                    if (fs.st_ins) atomicAdd(stat_word(p, fs.st_table, kInserts), fs.st_ins);
-                    if (fs.st_evi) atomicAdd(stat_word(p, fs.st_table, kEvictions), fs.st_evi);
-                    if (fs.st_col) atomicAdd(stat_word(p, fs.st_table, kCollisions), fs.st_col);
-                }
-                fs.st_ins = fs.st_evi = fs.st_col = 0;
-                fs.st_table = f0;
-            }
-            if (done && f != f0)
-                atomicAdd(stat_word(p, f, outcome == 0 ? kInserts : outcome == 1 ? kEvictions : kCollisions), 1ull);
-        }
-        const bool counted = done && (!MULTI || f == fs.st_table);
-        fs.st_ins += __popcll(__ballot(counted && outcome == 0));
-        fs.st_evi += __popcll(__ballot(counted && outcome == 1));
-        fs.st_col += __popcll(__ballot(counted && outcome == 2));
-    }
-    // stage evicted slots in LDS; all entries of the buffer belong to one table
-    uint64_t evm = __ballot(done && outcome == 1);
+    // all entries of the buffer belong to one table
+    uint64_t evm = __ballot(evicted);
     while (evm) {
         const int tf = __shfl(f, __ffsll((unsigned long long)evm) - 1);
-        const bool sel = done && outcome == 1 && f == tf;
+        const bool sel = evicted && f == tf;
         const uint64_t selm = __ballot(sel);
         const int add = __popcll(selm);
-        if ((fs.ev_cnt > 0 && tf != fs.ev_table) || fs.ev_cnt + add > kEvBuf)
-            flush_evicted(p, s_ev_w, s_row_w, fs.ev_cnt, fs.ev_table);
-        fs.ev_table = tf;
+        if ((st.count > 0 && tf != st.table) || st.count + add > kEvBuf) flush_evicted(p, s_ev_w, s_row_w, st.count, st.table);
+        st.table = tf;
         if (sel) {
-            const int at = fs.ev_cnt + __popcll(selm & ((1ull << lane) - 1ull));
+            const int at = st.count + __popcll(selm & ((1ull << lane) - 1ull));
             s_ev_w[at] = s;
             if (p.r_rows) s_row_w[at] = s >= p.g_num_rows ? s % p.g_num_rows : s;
         }
-        fs.ev_cnt += add;
+        st.count += add;
         evm &= ~selm;
     }
 }
 
-// End of k_finalize, reached by all threads: the workgroup adds its counters to its copy of the call's
-// counters, reserves its part of the evicted list (one reservation when all its wavefronts staged for
-// the same table) and reports in; returns true in the workgroup that reported in last.  Everything that
-// workgroup will read -- evicted counts and counter copies -- was added with device-scope atomics,
-// which are performed where all dies see them; a workgroup waits until its own have been acknowledged
-// before it reports in.  (A device-scope release fence here would also write back the die's whole L2,
-// once per workgroup.)
-__device__ __forceinline__ bool finalize_epilogue(const Params &p, FinalizeState &fs, int64_t (*s_ev)[kEvBuf],
-                                                  int64_t (*s_row)[kEvBuf], int *s_cnt, int (&s_tab)[kFinalizeWaves],
-                                                  unsigned long long *s_base, bool *s_last,
-                                                  unsigned long long (&s_red)[kFinalizeWaves][kStatCount], bool want_stats)
+// End of k_finalize, reached by all threads: the workgroup reserves its part of the evicted list (one reservation when all its
+// wavefronts staged for the same table) and writes it.
+__device__ __forceinline__ void list_evicted(const Params &p, Staged &st, int64_t (*s_ev)[kEvBuf], int64_t (*s_row)[kEvBuf],
+                                             int *s_cnt, int (&s_tab)[kFinalizeWaves], unsigned long long *s_base)
 {
     const int lane = lane_id(), w = threadIdx.x / kWave;
-    const bool multi = p.num_tables > 1;
     __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-    if (lane == 0) { s_cnt[w] = fs.ev_cnt; s_tab[w] = fs.ev_table; }
+    if (lane == 0) { s_cnt[w] = st.count; s_tab[w] = st.table; }
     __syncthreads();
     int total = 0, before = 0, tab = -1;
     bool same = true;
@@ -2176,40 +2234,21 @@ __device__ __forceinline__ bool finalize_epilogue(const Params &p, FinalizeState
         if (i < w) before += s_cnt[i];
         total += s_cnt[i];
     }
-    __syncthreads();                                              // s_tab is used again by block_stat_add
-    if (want_stats) {
-        const int idx[3] = {kInserts, kEvictions, kCollisions};
-        const unsigned long long vals[3] = {fs.st_ins, fs.st_evi, fs.st_col};
-        block_stat_add(p, idx, vals, 3, fs.st_table, s_red, s_tab);
+    if (total == 0) return;
+    if (!same) {
+        flush_evicted(p, s_ev[w], s_row[0], st.count, st.table);
+        return;
     }
-    if (multi && total > 0 && !same) flush_evicted(p, s_ev[w], s_row[0], fs.ev_cnt, fs.ev_table);
-    const bool reserve = total > 0 && (same || !multi);
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
+    if (threadIdx.x == 0) *s_base = atomicAdd(&p.ctl->num_evicted[tab], (unsigned long long)total);
     __syncthreads();
-    if (threadIdx.x == 0) {
-        unsigned long long arrived;
-        if (multi) {
-            // the reservation is acknowledged (its result is used) before the workgroup reports in
-            if (reserve) *s_base = atomicAdd(&p.ctl->num_evicted[tab], (unsigned long long)total);
-            arrived = atomicAdd(&p.ctl->done, kArriveOne);
-        } else {
-            arrived = atomicAdd(&p.ctl->done, kArriveOne + (unsigned long long)total);
-            *s_base = arrived & kEvictedMask;
-        }
-        *s_last = (arrived >> kArriveShift) == (unsigned long long)(gridDim.x - 1);
+    const int64_t base = (int64_t)*s_base + before;
+    int64_t ev_begin = p.t0.ev_begin, ev_cap = p.t0.ev_cap;
+    if (p.num_tables > 1) {
+        ev_begin = p.descs[tab].ev_begin;
+        ev_cap = p.descs[tab].ev_cap;
     }
-    __syncthreads();
-    if (reserve) {
-        const int64_t base = (int64_t)*s_base + before;
-        int64_t ev_begin = p.t0.ev_begin, ev_cap = p.t0.ev_cap;
-        if (multi) {
-            ev_begin = p.descs[tab].ev_begin;
-            ev_cap = p.descs[tab].ev_cap;
-        }
-        for (int i = lane; i < fs.ev_cnt; i += kWave)
-            if (base + i < ev_cap) p.out_evicted[ev_begin + base + i] = s_ev[w][i];
-    }
-    return *s_last;
+    for (int i = lane; i < st.count; i += kWave)
+        if (base + i < ev_cap) p.out_evicted[ev_begin + base + i] = s_ev[w][i];
 }
 
 // Every entry of the miss lists -- the elected position of an id (its agent) and the other copies of
@@ -2217,7 +2256,7 @@ __device__ __forceinline__ bool finalize_epilogue(const Params &p, FinalizeState
 // note says that it was displaced or has copies; else it and its copies look where k_allocate left the claim (the hint, kept
 // under the agent's batch position, which every copy knows), and the whole wavefront searches the window of a claimant
 // displaced after its hint was written.  A copy may find the claim tag or, when the agent has been quicker, already the id.  The agent turns the tag into the id,
-// writes the metadata and accounts for the outcome; every entry stores its output slot.  Entries
+// writes the metadata and lists the slot that it evicted; every entry stores its output slot.  Entries
 // without a claim fall back to the home slot (Case 3).
 // NOTES: one table, not LRU (see set_insert).
 template <bool MULTI, bool NOTES>
@@ -2225,20 +2264,26 @@ __device__ __forceinline__ void finalize_body(const Params &p)
 {
     __shared__ int64_t s_ev[kFinalizeWaves][kEvBuf];
     __shared__ int64_t s_row[MULTI ? 1 : kFinalizeWaves][kEvBuf];  // fused row reset (one table): the rows of the staged slots
-    __shared__ unsigned long long s_red[kFinalizeWaves][kStatCount];
-    __shared__ unsigned long long s_bins[MULTI ? kMaxTables : 1][kStatCount];
+    __shared__ unsigned long long s_sum[MULTI ? kMaxTables : 1][kStatCount];
     __shared__ int s_cnt[kFinalizeWaves];
     __shared__ int s_tab[kFinalizeWaves];
     __shared__ unsigned long long s_base;
-    __shared__ bool s_last;
 
+    // The call's counters, complete since the allocation, are the work of a workgroup of its own, the last one, which starts when
+    // another has ended where all compute units are full.  (Outcomes counted here, by workgroups that reported in and of which the
+    // last summed the counters and cleared 74 KB, ended the kernel 7 us after its last list entry, now 2.4; the allocation takes
+    // 0.5 longer for it.  600 K positions on two tensors, k_finalize 19.7 -> 15.8 us, the step 80.4 -> 76.8; 4 tables with 20 K
+    // values 42.0 -> 38.3; 500 M slots, 2 M positions, k_finalize 23.4 -> 20.0.)
+    if (blockIdx.x == gridDim.x - kFinalizeExtra) {
+        publish_counters<kFinalizeBlock>(p, s_sum);
+        return;
+    }
     const int lane = lane_id();
     const int w = threadIdx.x / kWave;
     const int64_t wave_global = ((int64_t)blockIdx.x * kFinalizeBlock + threadIdx.x) / kWave;
-    const int64_t num_waves = (int64_t)gridDim.x * kFinalizeWaves;
+    const int64_t num_waves = (int64_t)(gridDim.x - kFinalizeExtra) * kFinalizeWaves;
     constexpr bool multi = MULTI;
-    const bool want_stats = p.out_stats != nullptr;
-    FinalizeState fs;
+    Staged staged;
     const int64_t lane_offset = multi ? table_offsets(p.offsets, p.num_tables) : 0;
 
     for (int64_t seg = wave_global; seg < p.num_segs; seg += num_waves) {
@@ -2249,7 +2294,7 @@ __device__ __forceinline__ void finalize_body(const Params &p)
         if (!multi) seg_d = view(p.t0);
         bool seg_one = true;
         if (multi) seg_one = segment_table(p, lane_offset, seg_base, p.seg_chunks * kWave, seg_f, seg_d);
-        if (seg_base >= p.n) break;                            // segments past the batch hold nothing
+        if ((int32_t)seg_base >= (int32_t)p.n) break;                            // segments past the batch hold nothing
         for (uint32_t j0 = 0; j0 == 0 || j0 < cnt; j0 += kWave) {
             // (as in k_allocate, the first entries are requested before the count is known)
             const int64_t idx = seg_base + j0 + lane;
@@ -2351,20 +2396,18 @@ __device__ __forceinline__ void finalize_body(const Params &p)
                 }
                 p.out_slots[pos] = s_final;
             }
-            finalize_account<MULTI>(p, fs, s_ev[w], s_row[MULTI ? 0 : w], agent, outcome, s_final, f, want_stats);
+            stage_evicted(p, staged, s_ev[w], s_row[MULTI ? 0 : w], agent && outcome == 1, s_final, f);
         }
     }
     if constexpr (!MULTI) {
         __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-        reset_staged_rows(p, s_row[w], fs.ev_cnt);
+        reset_staged_rows(p, s_row[w], staged.count);
     }
-    // the workgroup that finishes last publishes the call's counters
-    const bool last = finalize_epilogue(p, fs, s_ev, s_row, s_cnt, s_tab, &s_base, &s_last, s_red, want_stats);
-    if (last) publish_counters<kFinalizeBlock>(p, s_bins);
+    list_evicted(p, staged, s_ev, s_row, s_cnt, s_tab, &s_base);
 }
 
-// WAVES = 8 wavefronts per SIMD (one table: 51 vector registers and 66 KB of LDS for 16 wavefronts, several: 63 and 40 KB; no
-// vector register goes to memory, 81 to 88 scalar ones are kept in lanes of vector registers), so that
+// WAVES = 8 wavefronts per SIMD (one table: 46 vector registers and 66 KB of LDS for 16 wavefronts, several: 56 and 40 KB; no
+// vector register goes to memory, 67 to 78 scalar ones are kept in lanes of vector registers), so that
 // the 8 192 wavefronts, each a chain of three round trips, run in one go.  (Several tables with 66 registers and the rows'
 // buffer that only one table has use for: one workgroup per compute unit and two turns, 41 M values over 26 tables 152 -> 145
 // us.)  A batch of 4 M positions, 10 % of them new, with
@@ -2372,7 +2415,7 @@ __device__ __forceinline__ void finalize_body(const Params &p)
 // metadata of a record, and rows reset before the workgroup's barrier instead of behind it, 45.5 -> 41 us by the claims that
 // need no look; 41 M values over 26 tables
 // 242 -> 178 us.
-// WAVES = 4, several tables: twice the scalar registers, 49 kept in vector lanes, which is time that the chain of a small call
+// WAVES = 4, several tables: more scalar registers, 40 kept in vector lanes, which is time that the chain of a small call
 // sees: steps of 600 values over 2 tables 35.6 -> 34.8 us, 10 400 over 26 41.4 -> 40.6.
 template <bool MULTI, bool NOTES, int WAVES = 8>
 __global__ __launch_bounds__(kFinalizeBlock, WAVES) void k_finalize(Params p)

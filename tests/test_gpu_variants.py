@@ -4,6 +4,7 @@ import numpy as np
 import pytest
 import torch
 
+import oracle
 from paper_2602_17050_amd import binding as mp
 from paper_2602_17050_amd import workloads as wl
 from gpu_common import Pair
@@ -431,6 +432,56 @@ def test_lists_with_copies_and_displaced_claims(slots, copies, policy, layout):
         near = rng.random(ids.size) < 0.5
         t.step(np.where(near, ids, rng.permutation(ids)), 3 * step)
     t.close()
+
+
+# ---- where lists are kept the allocation counts the outcomes and a workgroup of the last kernel publishes them: every kernel of
+# the allocation, calls with and without statistics and counting lookups in turn (what one leaves behind the next would show)
+@pytest.mark.parametrize("layout", ["separate", "records"])
+@pytest.mark.parametrize("policy,probe,n", [(True, 12, 524_289), ("expiry", 24, 524_353), ("lru", 7, 524_289), ("lru", 15, 524_289),
+                                            ("lru", 30, 524_290), ("lru", 60, 524_289), ("lru", 70, 1), ("lru", 70, 700), ("lru", 300, 9_000)])
+def test_counters_of_lists(policy, probe, n, layout):
+    rng = rng_for(921)
+    slots = n // 2 + probe
+    t = Pair(slots, probe, 1, policy, 43, layout=layout)
+    evicted = torch.empty(n, dtype=torch.int64, device="cuda")
+    count = torch.empty(1, dtype=torch.int64, device="cuda")
+    for step in range(4):
+        ids = rng.integers(-1, 3 * slots, size=n)
+        if step == 2:
+            g = torch.from_numpy(ids).cuda()
+            mp.mpzch_remap(t.g.handle, t.g.identities, t.g.metadata, g, 2 * step, torch.empty_like(g), evicted, count, None)
+            r = t.o.remap(ids, 2 * step)
+            assert np.array_equal(np.sort(evicted[: int(count)].cpu().numpy()), np.sort(r.evicted))
+            t.check_state()
+        else:
+            t.step(ids, 2 * step)
+        t.lookup(ids[:5_000])
+    t.close()
+
+
+@pytest.mark.parametrize("kinds", [(True, "lru", False), ("lru", "lru", "expiry")])
+@pytest.mark.parametrize("probe", [8, 61, 70])
+def test_counters_of_groups(probe, kinds):
+    """Features of a handful of values: a wavefront has claimants of many tables, at each of its steps of others."""
+    from test_gpu_jagged import JaggedPair
+    rng = rng_for(922)
+    specs = [wl.TableSpec(40 + 3 * f, probe, 1, kinds[f % 3], 60 + f) for f in range(64)]
+    jp = JaggedPair(specs, range(0, 64, 2))
+    for step in range(4):
+        counts = rng.integers(0, 30, size=64) if step else np.full(64, 3)
+        offsets = np.concatenate([[0], np.cumsum(counts)]).astype(np.int64)
+        vals = rng.integers(-1, 400, size=int(offsets[-1]))
+        if step == 2:
+            v = torch.from_numpy(vals).cuda()
+            evicted, count = torch.empty_like(v), torch.empty(64, dtype=torch.int64, device="cuda")
+            mp.mpzch_remap_jagged(jp.group, jp.I, jp.M, v, torch.from_numpy(offsets).cuda(), 2 * step, torch.empty_like(v), evicted,
+                                  offsets.tolist(), count, None)
+            _, evs, _ = oracle.remap_jagged(jp.o, vals, offsets, 2 * step, None)
+            assert count.tolist() == [len(e) for e in evs]
+        else:
+            jp.step(vals, offsets, 2 * step)
+        jp.check_state()
+    jp.close()
 
 
 # ---- whether the scratch set is read back or the notes decide, on both sides of the lines and with few and many misses
