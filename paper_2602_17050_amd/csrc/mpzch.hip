@@ -308,9 +308,12 @@ int lookup_grid(int64_t n, int num_cus)
     return grid_for(n, two ? 2 * kBlock : kBlock, num_cus, 16);
 }
 
+// (k_discover_tables_chunk as far as it reaches, up to 524 288 values on 256 compute units: it is the faster one there too.)
 mpzch_status_t launch_discover(const Params &p, int grid, hipStream_t s)
 {
-    if (p.num_tables > 1 && p.all_records) TRY(launch(k_discover_tables_records, grid, kBlock, s, p));
+    if (p.num_tables > 1 && p.seg_chunks == 1 && p.all_records) TRY(launch(k_discover_tables_chunk<true>, grid, kBlock, s, p));
+    else if (p.num_tables > 1 && p.seg_chunks == 1) TRY(launch(k_discover_tables_chunk<false>, grid, kBlock, s, p));
+    else if (p.num_tables > 1 && p.all_records) TRY(launch(k_discover_tables_records, grid, kBlock, s, p));
     else if (p.num_tables > 1) TRY(launch(k_discover_tables, grid, kBlock, s, p));
     else if (p.t0.sh) TRY(launch(k_discover_records, grid, kBlock, s, p));
     else if (p.t0.N >= kStreamingSlots) TRY(launch(k_discover_streaming, grid, kBlock, s, p));

@@ -7,7 +7,8 @@
 //                the few ids whose window continues are parked in LDS and scanned 8 slots at
 //                a time.  Hits store metadata = step and the output slot.  (k_lookup is the
 //                same body without writes, k_discover_tables / k_lookup_tables the bodies for
-//                several tables, k_discover_records the one for a table of 16-byte records.)  Each
+//                several tables, k_discover_records the one for a table of 16-byte records,
+//                k_discover_tables_chunk a shorter one for groups of small batches.)  Each
 //                wavefront owns a contiguous range of positions (a segment) and appends the
 //                positions that missed to its segment's list; at the end it enters them into a
 //                scratch hash set that elects, per distinct missed id, the position of its first
@@ -866,17 +867,20 @@ __device__ __forceinline__ void store_meta_wave(const Tab &d, bool active, int64
 // thousands of atomics on one word, 12 ns each (65 536 positions, the most popular id a fourteenth of them: 67 -> 27 us; over
 // the workgroup instead, 14 us, but the barriers cost every other call 0.7).
 // miss: the lanes with an id to enter; cell: bits of its hash.  Returns the lane that enters it, and the position in `pos`.
-__device__ __forceinline__ int merge_copies(bool miss, int64_t id, int cell, uint32_t &pos, MetaMerge *s_m)
+// TABLES: the lanes may be of several tables, f being each one's own; s_f: the wavefront's area for them.
+template <bool TABLES = false>
+__device__ __forceinline__ int merge_copies(bool miss, int64_t id, int cell, uint32_t &pos, MetaMerge *s_m, uint8_t *s_f = nullptr, int f = 0)
 {
     const int lane = lane_id();
     s_m[lane].slot = miss ? id : -1;
     s_m[lane].value = (int32_t)pos;
     if (miss) s_m[cell].winner = (uint32_t)lane;
+    if constexpr (TABLES) s_f[lane] = (uint8_t)f;
     __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
     int from = lane;
     if (miss) {
         const int o = (int)s_m[cell].winner;
-        if (o != lane && s_m[o].slot == id) {
+        if (o != lane && s_m[o].slot == id && (!TABLES || s_f[o] == f)) {
             __hip_atomic_fetch_min(&s_m[o].value, (int32_t)pos, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
             from = o;
         }
@@ -1380,6 +1384,122 @@ __global__ __launch_bounds__(kBlock, 4) void k_lookup_short(LookupArgs<MULTI, GA
         }
         if constexpr (GATHER) gather_wave(p, mine, pos, slot);
         todo = todo && !mine;
+    }
+}
+
+// store_meta_wave where the lanes may be of several tables, d being each one's own: what is shared is told by its address.
+__device__ __forceinline__ void store_meta_tables(const Tab &d, bool active, int64_t slot, int32_t value, MetaMerge *s_m)
+{
+    if (active && d.evict != 3) *meta_at(d, slot) = value;
+    const bool latest = active && d.evict == 3;
+    if (!__any(latest)) return;
+    const int lane = lane_id();
+    const int64_t key = latest ? (int64_t)(uintptr_t)meta_at(d, slot) : -1;
+    const int cell = (int)((uint32_t)(key >> 2) * 0x9E3779B1u >> 26);
+    s_m[lane].slot = key;
+    s_m[lane].value = value;
+    if (latest) s_m[cell].winner = (uint32_t)lane;
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    bool store = latest;
+    if (latest) {
+        const uint32_t o = s_m[cell].winner;
+        if (o != (uint32_t)lane && s_m[o].slot == key) {
+            __hip_atomic_fetch_max(&s_m[o].value, value, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+            store = false;
+        }
+    }
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    if (store) __hip_atomic_fetch_max(meta_at(d, slot), s_m[lane].value, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+}
+
+// Pass 1 of a group where every wavefront has one chunk: its positions are looked at together whatever their tables, as in
+// k_lookup_short, and nothing is parked, so a chunk in which features end is no longer a chain than another.  Bound by that
+// chain: descriptors and ids, looks, set, stores.  Whole steps, k_discover_tables* / this, us: 4 tables with 20 K values 38.3 /
+// 33.8, 26 with 320 K 56.3 / 51.4, 26 x 400 values 40.1 / 34.7, 8 x 60 000 on two tensors each 60.0 / 55.2, of four policies
+// 101.4 / 85.9 (8 slots), 116.2 / 97.0 (64).
+template <bool REC>
+__global__ __launch_bounds__(kBlock, 4) void k_discover_tables_chunk(Params p)
+{
+    __shared__ ProbeReq s_req[kWavesPerBlock][kWave];
+    __shared__ __attribute__((aligned(16))) uint8_t s_code[kWavesPerBlock][kWave * kFirstG];
+    __shared__ uint8_t s_table[kWavesPerBlock][kWave];
+    __shared__ TableDesc s_desc[kMaxTables];
+    const int lane = lane_id(), w = wave_id();
+    const int seg = (int)blockIdx.x * kWavesPerBlock + w;
+    const int pos0 = seg * kWave, pos = pos0 + lane, n = (int)p.n;
+    const bool in = pos < n;
+    const int64_t id = in ? p.ids[pos] : -1;
+    const int64_t lane_offset = table_offsets(p.offsets, p.num_tables);
+    const uint64_t *src = reinterpret_cast<const uint64_t *>(p.descs);
+    uint64_t *dst = reinterpret_cast<uint64_t *>(s_desc);
+    for (int i = threadIdx.x; i < p.num_tables * (int)(sizeof(TableDesc) / 8); i += kBlock) dst[i] = src[i];
+    __syncthreads();
+    int f = find_table_wave(lane_offset, pos0);
+    for (int k = f + 1; k < p.num_tables; ++k) {
+        const int64_t begin = readlane64(lane_offset, k);
+        if (begin >= pos0 + kWave) break;
+        if (begin <= pos) f = k;
+    }
+    const Tab d = view(s_desc[f]);
+    const int64_t home = home_slot(id, d.seed, d.N);
+    const bool valid = in && id >= 0;
+    int res = kProbeGoOn;
+    bool fresh = false, todo = valid;
+    while (__any(todo)) {
+        // the lanes whose tables are of one layout, or of one table of fewer slots than a request is wide
+        const int head = __ffsll((unsigned long long)__ballot(todo)) - 1;
+        const int widest = slots_up_to_widest(d), slots = __builtin_amdgcn_readlane(widest, head);
+        const int sh = __builtin_amdgcn_readlane(d.sh, head), f_head = __builtin_amdgcn_readlane(f, head);
+        const bool mine = todo && (slots < kWidest ? f == f_head : widest == kWidest && d.sh == sh);
+        int q = 0, left = __any(mine && f != f_head) ? 1 << 30 : __builtin_amdgcn_readlane(d.P, head);
+        for (;;) {
+            const bool need = mine && res == kProbeGoOn && q < d.P;
+            if (!__any(need)) break;
+            bool got_fresh = false;
+            const int got = probe_more<false, REC>(d, sh, slots, id, home, q, left, need, s_req[w], s_code[w], p.step, &got_fresh);
+            if (need) { res = got; fresh = got_fresh; }
+        }
+        todo = todo && !mine;
+    }
+    const bool hit = valid && res >= 0, miss = valid && res < 0;
+    MetaMerge *const s_m = reinterpret_cast<MetaMerge *>(s_req[w]);
+    const int64_t slot = hit ? wrap(home + res, d.N) : home;
+    if (in) __builtin_nontemporal_store(slot, &p.out_slots[pos]);      // (of a missed id: rewritten by k_finalize)
+    const uint64_t mb = __ballot(miss);
+    if (mb) {
+        // the region of the scratch set that serves the table, and the clamps: see discover_body
+        int64_t lo = shfl64(lane_offset, f), hi = shfl64(lane_offset, (f + 1) & (kWave - 1));
+        if (f == p.num_tables - 1 || hi > n) hi = n;
+        if (hi <= pos) hi = pos + 1;
+        if (lo > pos) lo = pos;
+        if (lo < 0) lo = 0;
+        const uint64_t hash = mix64((uint64_t)id ^ kSetSeed);
+        uint32_t e = 0, first = (uint32_t)pos;
+        const int from = merge_copies<true>(miss, id, ((int)hash + f) & (kWave - 1), first, s_m, s_table[w], f);
+        if (miss && from == lane) e = set_insert<false>(p, id, hash, first, 2ull * (uint64_t)lo, 2ull * (uint64_t)(hi - lo));
+        e = (uint32_t)__shfl((int)e, from);
+        if (miss) {
+            const int at = pos0 + lanes_below(mb);
+            p.list[at] = (uint32_t)pos;
+            p.ent[at] = e;
+            p.list_id[at] = id;
+        }
+    }
+    if (lane == 0 && seg < p.num_segs) p.seg_cnt[seg] = (uint32_t)__popcll(mb);
+    store_meta_tables(d, hit && !(REC && fresh && d.evict != 3), slot, hit ? meta_value(p, d, pos) : 0, s_m);
+    if (!p.out_stats) return;
+    for (uint64_t m = __ballot(in); m;) {
+        const int t = __builtin_amdgcn_readlane(f, __ffsll((unsigned long long)m) - 1);
+        const uint64_t of_table = __ballot(in && f == t);
+        const uint32_t hits = (uint32_t)__popcll(__ballot(hit) & of_table), misses = (uint32_t)__popcll(mb & of_table);
+        const uint32_t hit_len = wave_sum32(hit && f == t ? (uint32_t)res + 1u : 0u);
+        const uint32_t miss_len = wave_sum32(miss && f == t ? (uint32_t)(res <= kProbeAbsent ? absent_len(res) : d.P) : 0u);
+        const uint32_t invalid = (uint32_t)__popcll(of_table) - hits - misses;
+        const uint32_t v = lane == kHitPos ? hits : lane == kMissPos ? misses : lane == kInvalidPos ? invalid
+                         : lane == kHitProbeSum ? hit_len : lane == kMissProbeSum ? miss_len : 0u;
+        if (v) atomicAdd(stat_word(p, t, lane), (unsigned long long)v);
+        m &= ~of_table;
     }
 }
 

@@ -539,3 +539,23 @@ def test_groups_around_the_line_of_the_last_kernel(more):
         jp.step(vals, offsets, step)
     jp.check_state()
     jp.close()
+
+
+# ---- groups on both sides of the line at which a wavefront of Pass 1 comes to have a second chunk: features end inside of
+# wavefronts, the same ids are new in all of them, tables of fewer slots than a request is wide, windows around the block sizes
+@pytest.mark.parametrize("records", [range(6), (1, 2, 4)], ids=["records", "mixed"])
+@pytest.mark.parametrize("more", [0, 1])
+def test_groups_around_the_line_of_one_chunk(more, records):
+    from test_gpu_jagged import JaggedPair
+    rng = rng_for(923)
+    n = torch.cuda.get_device_properties(0).multi_processor_count * 8 * 256 + more
+    specs = [wl.TableSpec(120_011, 16, 1, True, 101), wl.TableSpec(50, 64, 1, True, 102), wl.TableSpec(90_001, 9, 0, "lru", 103),
+             wl.TableSpec(5, 8, 2, "expiry", 104), wl.TableSpec(150_000, 24, 2, "expiry", 105), wl.TableSpec(80_000, 65, 0, False, 106)]
+    jp = JaggedPair(specs, records)
+    offsets = np.array([0, n // 3 + 7, n // 3 + 40, n // 2 + 1, n // 2 + 20, n - n // 5, n], dtype=np.int64)
+    for step in (0, 3):
+        vals = np.concatenate([wl.zipf_ids(rng, int(c), 1.05, 300_000) + 1_000 * step for c in np.diff(offsets)])
+        vals[rng.random(n) < 0.01] = -1
+        jp.step(vals, offsets, step, None if step else rng.integers(0, 6, size=n).astype(np.int32))
+    jp.check_state()
+    jp.close()
