@@ -106,7 +106,8 @@ struct Params {
     // ended up; by workgroup, the slots evicted by its claimants; and three words of counters per workgroup
     uint32_t *place;
     uint8_t *note;                 // ... by batch position, 0 between calls: 1 = somebody else has met the id that was entered
-                                   // in the scratch set for it (also where lists are kept, of one table)
+                                   // in the scratch set for it (also where lists are kept, of one table; of groups: that the
+                                   // claim made there was displaced)
     int64_t *evicted;
     uint64_t *wg_words;
     int32_t seg_chunks;
@@ -1530,7 +1531,7 @@ constexpr uint32_t kHintUnplaced = 0xFE;   // ran out of slots: falls back to ho
 constexpr uint32_t kHintUnknown = 0xFD;    // placed, but not at a round that fits the hint: search the window
 
 // What k_allocate leaves in first_of for k_finalize: the position of the first occurrence of the entry's id, or, for
-// that position itself, kAgentEntry | hint, with kAgentOcc if the slot there held an id.  With one table, not LRU, that stands
+// that position itself, kAgentEntry | hint, with kAgentOcc if the slot there held an id.  Of tables that are not LRU that stands
 // unless a note says that the claim was displaced.
 constexpr uint32_t kAgentEntry = 0x80000000u;
 constexpr uint32_t kAgentOcc = 0x100u;
@@ -1814,14 +1815,14 @@ __device__ __forceinline__ void allocate_body(const Params &p, int64_t vblock, i
                                            p.hint[who] = (uint8_t)at;
                                        }
                                        count_placed(outcomes, old);
-                                       if (!MULTI && is_tag(old)) p.note[tag_pos(old)] = 1;
+                                       if (is_tag(old)) p.note[tag_pos(old)] = 1;
                                    },
                                    [](uint32_t) {});
                     __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");   // s_code and s_req are written again
                 }
                 if (agent) {
                     if (!alone) p.hint[pos] = (uint8_t)hint;  // for the copies of the id
-                    p.first_of[idx] = kAgentEntry | (MULTI ? hint & 0xFFu : hint);
+                    p.first_of[idx] = kAgentEntry | hint;
                 }
             }
             __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
@@ -2372,13 +2373,15 @@ __device__ __forceinline__ void list_evicted(const Params &p, Staged &st, int64_
 }
 
 // Every entry of the miss lists -- the elected position of an id (its agent) and the other copies of
-// the id alike -- finds the slot that carries the agent's claim.  With one table (not LRU) the agent knows where it is unless a
-// note says that it was displaced or has copies; else it and its copies look where k_allocate left the claim (the hint, kept
+// the id alike -- finds the slot that carries the agent's claim.  The agent of a table that is not LRU knows where it is unless a
+// note says that it was displaced (or, with one table, has copies); else it and its copies look where k_allocate left the claim (the hint, kept
 // under the agent's batch position, which every copy knows), and the whole wavefront searches the window of a claimant
 // displaced after its hint was written.  A copy may find the claim tag or, when the agent has been quicker, already the id.  The agent turns the tag into the id,
 // writes the metadata and lists the slot that it evicted; every entry stores its output slot.  Entries
 // without a claim fall back to the home slot (Case 3).
-// NOTES: one table, not LRU (see set_insert).
+// NOTES: one table, not LRU (see set_insert).  Groups have notes of displaced claims alone: the claim is looked at by few, and a
+// random line less is read for each (same tables, both builds in turn, whole steps: 26 x 400 000 values, 10 % of them new, records 670 ->
+// 660 us, two tensors 822 -> 813; 8 x 500 000 239 -> 237, 271 -> 269; 26 x 12 000 the same).
 template <bool MULTI, bool NOTES>
 __device__ __forceinline__ void finalize_body(const Params &p)
 {
@@ -2439,11 +2442,6 @@ __device__ __forceinline__ void finalize_body(const Params &p)
             if (have) {
                 agent = (word & kAgentEntry) != 0;
                 first = agent ? pos : word;
-                if constexpr (NOTES) {
-                    const uint8_t note = p.note[pos];
-                    if (note) p.note[pos] = 0;                 // no note is left behind
-                    sure = agent && !note;
-                }
                 h = agent ? word & 0xFFu : (uint32_t)p.hint[first];
                 p.set_slot[e & ~kEntered] = kSetEmpty;         // the scratch set is left empty again
                 if (multi) {
@@ -2453,6 +2451,11 @@ __device__ __forceinline__ void finalize_body(const Params &p)
                         f = find_table(p.offsets, p.num_tables, (int64_t)pos);
                         d = view(p.descs[f]);
                     }
+                }
+                if (MULTI ? d.evict != 2 : NOTES) {
+                    const uint8_t note = p.note[pos];
+                    if (note) p.note[pos] = 0;                 // no note is left behind
+                    sure = agent && !note;
                 }
                 home = home_slot(id, d.seed, d.N);
                 if (sure && h < kHintUnknown) {

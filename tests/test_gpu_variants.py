@@ -559,3 +559,22 @@ def test_groups_around_the_line_of_one_chunk(more, records):
         jp.step(vals, offsets, step, None if step else rng.integers(0, 6, size=n).astype(np.int32))
     jp.check_state()
     jp.close()
+
+
+# ---- claims of groups stand without a look at the table unless a note says that they were displaced: crowded windows, where most
+# are, LRU tables (no notes) among the others, copies of new ids, the next call with the notes that this one must not leave behind
+@pytest.mark.parametrize("records", [range(5), (0, 3)], ids=["records", "mixed"])
+@pytest.mark.parametrize("n", [3_000, 90_001, 1_300_003])
+def test_groups_with_displaced_claims(n, records):
+    from test_gpu_jagged import JaggedPair
+    rng = rng_for(925)
+    per = n // 12
+    specs = [wl.TableSpec(per, 24, 1, True, 111), wl.TableSpec(per, 16, 0, "lru", 112), wl.TableSpec(per + 1, 64, 2, "expiry", 113),
+             wl.TableSpec(per, 7, 0, False, 114), wl.TableSpec(per, 260, 1, True, 115)]
+    jp = JaggedPair(specs, records)
+    offsets = np.array([0, n // 5, n // 5 + n // 4, n // 2 + 3, n - n // 7, n], dtype=np.int64)
+    for step in (0, 2, 4):
+        vals = np.concatenate([rng.integers(0, 2 * per, size=int(c)) + step * per // 2 for c in np.diff(offsets)])
+        jp.step(vals, offsets, step, rng.integers(0, 4, size=n).astype(np.int32) if step == 2 else None)
+        jp.check_state()
+    jp.close()
