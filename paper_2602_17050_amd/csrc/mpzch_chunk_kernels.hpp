@@ -344,9 +344,12 @@ __global__ __launch_bounds__(THREADS, T == 8 || THREADS > kBlock ? 4 : 6) void k
     const Tab d = view(p.t0);
     const int64_t pos = (int64_t)blockIdx.x * kBlock + threadIdx.x;
     const bool in = (int)threadIdx.x < kBlock && pos < p.n;
-    const uint32_t e = in ? p.ent[pos] : kNoEntry;
-    const int64_t id = in ? p.ids[pos] : -1;
-    const uint8_t note = in ? p.note[pos] : 0;
+    const int64_t from = in ? pos : 0;               // (no branch between the loads, see k_finalize_chunk: 20 011 positions 24.7 -> 24.3 us)
+    args_now(p.ent, p.ids, p.note, p.set_slot, p.list, p.place, p.evicted, p.wg_words, p.step, d.I, d.M, d.N, d.seed, d.P, d.sh);
+    uint32_t e = p.ent[from];
+    const int64_t id = p.ids[from];
+    const uint8_t note = p.note[from];
+    if (!in) e = kNoEntry;
     const bool have = e != kNoEntry;
     uint32_t first = 0;
     if (have) first = first_occurrence(p, (uint32_t)pos, e, note);
