@@ -467,11 +467,11 @@ mpzch_status_t run_remap(Scratch &sc, Timing &tm, const Params &p, int32_t max_p
     return st;
 }
 
-template <int SHIFT, bool EVEN>
+template <int SHIFT, bool EVEN, bool OVERLAP>
 mpzch_status_t launch_discover_chunk(const Params &p, int grid, hipStream_t s)
 {
-    if (p.t0.sh) TRY(launch(k_discover_chunk<true, SHIFT, EVEN>, grid, kBlock << SHIFT, s, p));
-    else TRY(launch(k_discover_chunk<false, SHIFT, EVEN>, grid, kBlock << SHIFT, s, p));
+    if (p.t0.sh) TRY(launch(k_discover_chunk<true, SHIFT, EVEN, OVERLAP>, grid, kBlock << SHIFT, s, p));
+    else TRY(launch(k_discover_chunk<false, SHIFT, EVEN, OVERLAP>, grid, kBlock << SHIFT, s, p));
     return MPZCH_OK;
 }
 
@@ -503,14 +503,21 @@ constexpr bool even_looks(int64_t groups, int num_cus, bool records, int32_t P)
     return P <= 32 && groups > 3 * (int64_t)num_cus && groups <= (records ? 5 : 8) * (int64_t)num_cus;
 }
 
+// Calls whose stores go out while the compare-and-swap of the scratch set is under way (k_discover_chunk): up to four workgroups per
+// compute unit, of records two.  Beyond, the stores of the others are in the way of it.  Whole calls, behind / beside it, TTL,
+// windows of 64 unless said, us: two tensors 200 K positions 27.3 / 27.1, 262 144 30.9 / 30.7, 300 007 33.3 / 33.8; 262 144 new ids 55.4 / 54.9;
+// records 100 K (of 32) 21.6 / 21.3, 150 K (of 32, expiry steps) 28.4 / 28.7, 200 K 30.9 / 31.0, 230 K 33.0 / 33.3.
+constexpr bool overlap_insert(int64_t groups, int num_cus, bool records) { return groups <= (records ? 2 : 4) * (int64_t)num_cus; }
+
 // One chunk per wavefront (mpzch_chunk_kernels.hpp): grid = workgroups of 256 positions.
 mpzch_status_t launch_remap_chunks(Timing &tm, const Params &p, int32_t max_p_lru, int grid, int num_cus, hipStream_t s)
 {
     const bool rec = p.t0.sh != 0;
     if (!tm.begin(KDiscover, s)) return MPZCH_ERR_HIP;
-    if (window_shift(p.t0.P) == 1 && 2 * p.n <= kShortBlocks) TRY(launch_discover_chunk<1, false>(p, grid, s));
-    else if (even_looks(grid, num_cus, rec, p.t0.P)) TRY(launch_discover_chunk<0, true>(p, grid, s));
-    else TRY(launch_discover_chunk<0, false>(p, grid, s));
+    if (window_shift(p.t0.P) == 1 && 2 * p.n <= kShortBlocks) TRY((launch_discover_chunk<1, false, true>(p, grid, s)));
+    else if (even_looks(grid, num_cus, rec, p.t0.P)) TRY((launch_discover_chunk<0, true, false>(p, grid, s)));
+    else if (overlap_insert(grid, num_cus, rec)) TRY((launch_discover_chunk<0, false, true>(p, grid, s)));
+    else TRY((launch_discover_chunk<0, false, false>(p, grid, s)));
     if (!tm.end(s) || !tm.begin(KAllocate, s)) return MPZCH_ERR_HIP;
     if (max_p_lru > 0 && rec) TRY(launch_allocate_lru_chunk<true>(max_p_lru, p, grid, num_cus, s));
     else if (max_p_lru > 0) TRY(launch_allocate_lru_chunk<false>(max_p_lru, p, grid, num_cus, s));

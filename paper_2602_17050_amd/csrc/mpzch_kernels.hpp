@@ -378,6 +378,17 @@ __device__ __forceinline__ int32_t meta_value(const Params &p, const Tab &d, int
     if (d.evict != 3) return p.step;
     return p.step + (p.ttls ? p.ttls[pos] : d.ttl);
 }
+// The same in two parts, for kernels that request the duration ahead.
+__device__ __forceinline__ int32_t duration_of(const Params &p, const Tab &d, int64_t pos)
+{
+    int32_t t = d.ttl;
+    if (d.evict == 3 && p.ttls) t = p.ttls[pos];
+    return t;
+}
+__device__ __forceinline__ int32_t metadata_for(const Params &p, const Tab &d, int32_t duration)
+{
+    return d.evict == 3 ? p.step + duration : p.step;
+}
 
 // Metadata write on behalf of one batch position.  With last-seen metadata every writer of a call
 // stores the same step.  With per-feature expiry times (Sec. 3.4, second paragraph) the writers of one

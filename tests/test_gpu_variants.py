@@ -578,3 +578,18 @@ def test_groups_with_displaced_claims(n, records):
         jp.step(vals, offsets, step, rng.integers(0, 4, size=n).astype(np.int32) if step == 2 else None)
         jp.check_state()
     jp.close()
+
+
+# ---- one-chunk calls whose stores go out beside the scratch set's compare-and-swap: on both sides of each line, with new ids whose
+# copies meet within a wavefront and across workgroups, and durations per position
+@pytest.mark.parametrize("evict", [True, "expiry", False])
+@pytest.mark.parametrize("groups,layout", [(4, "separate"), (2, "records")])
+def test_calls_around_the_lines_of_overlapped_inserts(groups, layout, evict):
+    rng = rng_for(927)
+    n = groups * torch.cuda.get_device_properties(0).multi_processor_count * 256
+    t = Pair(n, 41, 1, evict, 49, layout=layout)
+    for step, more in enumerate([0, 1, 0]):
+        ids = wl.zipf_ids(rng, n + more, 1.05, 2 * n) + step * n // 2
+        ids[: n // 8] = rng.integers(4 * n, 4 * n + 50, size=n // 8) + 100 * step
+        t.step(ids, 2 * step, ttls=rng.integers(0, 5, size=n + more).astype(np.int32) if evict == "expiry" else None)
+    t.close()
