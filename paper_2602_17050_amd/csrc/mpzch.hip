@@ -308,11 +308,22 @@ int lookup_grid(int64_t n, int num_cus)
     return grid_for(n, two ? 2 * kBlock : kBlock, num_cus, 16);
 }
 
+// Calls whose stores go out while the compare-and-swap of the scratch set is under way (k_discover_chunk): up to four workgroups per
+// compute unit, of records two.  Beyond, the stores of the others are in the way of it.  Whole calls, behind / beside it, TTL,
+// windows of 64 unless said, us: two tensors 200 K positions 27.3 / 27.1, 262 144 30.9 / 30.7, 300 007 33.3 / 33.8; 262 144 new ids 55.4 / 54.9;
+// records 100 K (of 32) 21.6 / 21.3, 150 K (of 32, expiry steps) 28.4 / 28.7, 200 K 30.9 / 31.0, 230 K 33.0 / 33.3.
+constexpr bool overlap_insert(int64_t groups, int num_cus, bool records) { return groups <= (records ? 2 : 4) * (int64_t)num_cus; }
+
 // (k_discover_tables_chunk as far as it reaches, up to 524 288 values on 256 compute units: it is the faster one there too.)
-mpzch_status_t launch_discover(const Params &p, int grid, hipStream_t s)
+mpzch_status_t launch_discover(const Params &p, int grid, int num_cus, hipStream_t s)
 {
-    if (p.num_tables > 1 && p.seg_chunks == 1 && p.all_records) TRY(launch(k_discover_tables_chunk<true>, grid, kBlock, s, p));
-    else if (p.num_tables > 1 && p.seg_chunks == 1) TRY(launch(k_discover_tables_chunk<false>, grid, kBlock, s, p));
+    if (p.num_tables > 1 && p.seg_chunks == 1) {
+        const bool overlap = overlap_insert(grid, num_cus, false);
+        if (p.all_records && overlap) TRY(launch(k_discover_tables_chunk<true, true>, grid, kBlock, s, p));
+        else if (p.all_records) TRY(launch(k_discover_tables_chunk<true, false>, grid, kBlock, s, p));
+        else if (overlap) TRY(launch(k_discover_tables_chunk<false, true>, grid, kBlock, s, p));
+        else TRY(launch(k_discover_tables_chunk<false, false>, grid, kBlock, s, p));
+    }
     else if (p.num_tables > 1 && p.all_records) TRY(launch(k_discover_tables_records, grid, kBlock, s, p));
     else if (p.num_tables > 1) TRY(launch(k_discover_tables, grid, kBlock, s, p));
     else if (p.t0.sh) TRY(launch(k_discover_records, grid, kBlock, s, p));
@@ -503,12 +514,6 @@ constexpr bool even_looks(int64_t groups, int num_cus, bool records, int32_t P)
     return P <= 32 && groups > 3 * (int64_t)num_cus && groups <= (records ? 5 : 8) * (int64_t)num_cus;
 }
 
-// Calls whose stores go out while the compare-and-swap of the scratch set is under way (k_discover_chunk): up to four workgroups per
-// compute unit, of records two.  Beyond, the stores of the others are in the way of it.  Whole calls, behind / beside it, TTL,
-// windows of 64 unless said, us: two tensors 200 K positions 27.3 / 27.1, 262 144 30.9 / 30.7, 300 007 33.3 / 33.8; 262 144 new ids 55.4 / 54.9;
-// records 100 K (of 32) 21.6 / 21.3, 150 K (of 32, expiry steps) 28.4 / 28.7, 200 K 30.9 / 31.0, 230 K 33.0 / 33.3.
-constexpr bool overlap_insert(int64_t groups, int num_cus, bool records) { return groups <= (records ? 2 : 4) * (int64_t)num_cus; }
-
 // One chunk per wavefront (mpzch_chunk_kernels.hpp): grid = workgroups of 256 positions.
 mpzch_status_t launch_remap_chunks(Timing &tm, const Params &p, int32_t max_p_lru, int grid, int num_cus, hipStream_t s)
 {
@@ -561,7 +566,7 @@ mpzch_status_t launch_remap(Scratch &sc, Timing &tm, Params p, int32_t max_p_lru
     // per compute unit.)
     const int g_grp = grid_for((int64_t)p.num_segs, kFinalizeWaves, sc.num_cus, 2);
 
-    TIMED(tm, KDiscover, s, launch_discover(p, g_disc, s));
+    TIMED(tm, KDiscover, s, launch_discover(p, g_disc, sc.num_cus, s));
     TIMED(tm, KAllocate, s, launch_allocate(max_p_lru, p, sc.num_cus, s));
     TIMED(tm, KFinalize, s, launch_finalize(p, g_grp, sc.num_cus, s));
     return MPZCH_OK;

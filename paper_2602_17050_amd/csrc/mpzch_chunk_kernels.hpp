@@ -57,12 +57,6 @@ struct SetInsert {
     uint32_t first;                  // the lowest position among the copies of the id in this wavefront
     int from;                        // the lane that enters the id
 };
-__device__ __forceinline__ uint32_t try_entry(const Params &p, uint32_t e, uint32_t mine)
-{
-    uint32_t seen = kSetEmpty;
-    __hip_atomic_compare_exchange_strong(&p.set_slot[e], &seen, mine, __ATOMIC_RELAXED, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    return seen;
-}
 // for the lanes with `miss` set
 __device__ __forceinline__ SetInsert begin_insert(const Params &p, bool miss, int64_t id, uint64_t hash, uint32_t pos, MetaMerge *s_m)
 {

@@ -428,25 +428,35 @@ constexpr uint32_t kSetEmpty = 0xFFFFFFFFu;
 // 177, of all 895 / 890 / 203; all positions new, by a power law (a table's first batch), 1 472 / 1 469 / 620.  600 000
 // positions: within 1 % but for the last, 253 / 252 / 110.
 constexpr uint32_t kEntered = 0x80000000u;       // (entries are below 2^31)
+// one entry: what was there (kSetEmpty: `mine` is there now)
+__device__ __forceinline__ uint32_t try_entry(const Params &p, uint64_t e, uint32_t mine)
+{
+    uint32_t seen = kSetEmpty;
+    __hip_atomic_compare_exchange_strong(&p.set_slot[e], &seen, mine, __ATOMIC_RELAXED, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    return seen;
+}
+// the rest of it, entry e having been tried
+template <bool NOTE>
+__device__ __forceinline__ uint32_t set_insert_from(const Params &p, int64_t id, uint32_t pos, uint64_t e, uint32_t seen, uint64_t base,
+                                                    uint64_t end, bool notes = NOTE)
+{
+    while (seen != kSetEmpty) {
+        if ((int64_t)seen < p.n && p.ids[seen] == id) {           // (an entry is always a position of this batch)
+            if (NOTE && notes) p.note[seen] = 1;
+            if (pos < seen) __hip_atomic_fetch_min(&p.set_slot[e], pos, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            return (uint32_t)e;
+        }
+        if (++e == end) e = base;
+        seen = try_entry(p, e, pos);
+    }
+    return NOTE ? (uint32_t)e | kEntered : (uint32_t)e;           // first of its id so far
+}
 template <bool NOTE>
 __device__ __forceinline__ uint32_t set_insert(const Params &p, int64_t id, uint64_t hash, uint32_t pos, uint64_t base, uint64_t size,
                                                bool notes = NOTE)
 {
-    uint64_t e = base + __umul64hi(hash, size);
-    const uint64_t end = base + size;
-    for (;;) {
-        uint32_t expected = kSetEmpty;
-        if (__hip_atomic_compare_exchange_strong(&p.set_slot[e], &expected, pos, __ATOMIC_RELAXED, __ATOMIC_RELAXED,
-                                                 __HIP_MEMORY_SCOPE_AGENT))
-            return NOTE ? (uint32_t)e | kEntered : (uint32_t)e;   // first of its id so far
-        if ((int64_t)expected < p.n && p.ids[expected] == id) {   // (an entry is always a position of this batch)
-            if (NOTE && notes) p.note[expected] = 1;
-            if (pos < expected) __hip_atomic_fetch_min(&p.set_slot[e], pos, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            break;
-        }
-        if (++e == end) e = base;
-    }
-    return (uint32_t)e;
+    const uint64_t e = base + __umul64hi(hash, size);
+    return set_insert_from<NOTE>(p, id, pos, e, try_entry(p, e, pos), base, base + size, notes);
 }
 
 // Is it certain that nobody else has the id that was entered at `ent`?
@@ -1430,7 +1440,10 @@ __device__ __forceinline__ void store_meta_tables(const Tab &d, bool active, int
 // chain: descriptors and ids, looks, set, stores.  Whole steps, k_discover_tables* / this, us: 4 tables with 20 K values 38.3 /
 // 33.8, 26 with 320 K 56.3 / 51.4, 26 x 400 values 40.1 / 34.7, 8 x 60 000 on two tensors each 60.0 / 55.2, of four policies
 // 101.4 / 85.9 (8 slots), 116.2 / 97.0 (64).
-template <bool REC>
+// OVERLAP: what else there is to store goes out beside the scratch set's compare-and-swap, as in k_discover_chunk: 2 x 300 values
+// 22.9 -> 22.4 us, 4 x 5 000 25.1 -> 24.7, 26 x 6 000 32.8 -> 32.5 (records), 31.5 -> 31.0; 26 x 12 000 the same, 26 x 19 000 59.6 -> 60.0,
+// 55.6 -> 56.1, which is beyond the line that launch_discover draws.
+template <bool REC, bool OVERLAP>
 __global__ __launch_bounds__(kBlock, 4) void k_discover_tables_chunk(Params p)
 {
     __shared__ ProbeReq s_req[kWavesPerBlock][kWave];
@@ -1479,6 +1492,9 @@ __global__ __launch_bounds__(kBlock, 4) void k_discover_tables_chunk(Params p)
     const int64_t slot = hit ? wrap(home + res, d.N) : home;
     if (in) __builtin_nontemporal_store(slot, &p.out_slots[pos]);      // (of a missed id: rewritten by k_finalize)
     const uint64_t mb = __ballot(miss);
+    uint64_t base = 0, end = 0, entry = 0;
+    uint32_t first = (uint32_t)pos, seen = kSetEmpty;
+    int from = lane;
     if (mb) {
         // the region of the scratch set that serves the table, and the clamps: see discover_body
         int64_t lo = shfl64(lane_offset, f), hi = shfl64(lane_offset, (f + 1) & (kWave - 1));
@@ -1487,21 +1503,28 @@ __global__ __launch_bounds__(kBlock, 4) void k_discover_tables_chunk(Params p)
         if (lo > pos) lo = pos;
         if (lo < 0) lo = 0;
         const uint64_t hash = mix64((uint64_t)id ^ kSetSeed);
-        uint32_t e = 0, first = (uint32_t)pos;
-        const int from = merge_copies<true>(miss, id, ((int)hash + f) & (kWave - 1), first, s_m, s_table[w], f);
-        if (miss && from == lane) e = set_insert<false>(p, id, hash, first, 2ull * (uint64_t)lo, 2ull * (uint64_t)(hi - lo));
-        e = (uint32_t)__shfl((int)e, from);
+        base = 2ull * (uint64_t)lo;
+        end = 2ull * (uint64_t)hi;
+        entry = base + __umul64hi(hash, end - base);
+        from = merge_copies<true>(miss, id, ((int)hash + f) & (kWave - 1), first, s_m, s_table[w], f);
+        if (miss && from == lane) seen = try_entry(p, entry, first);
         if (miss) {
             const int at = pos0 + lanes_below(mb);
             p.list[at] = (uint32_t)pos;
-            p.ent[at] = e;
             p.list_id[at] = id;
         }
     }
+    auto finish = [&]() {
+        if (!mb) return;
+        uint32_t e = 0;
+        if (miss && from == lane) e = set_insert_from<false>(p, id, first, entry, seen, base, end);
+        e = (uint32_t)__shfl((int)e, from);
+        if (miss) p.ent[pos0 + lanes_below(mb)] = e;
+    };
+    if constexpr (!OVERLAP) finish();
     if (lane == 0 && seg < p.num_segs) p.seg_cnt[seg] = (uint32_t)__popcll(mb);
     store_meta_tables(d, hit && !(REC && fresh && d.evict != 3), slot, hit ? meta_value(p, d, pos) : 0, s_m);
-    if (!p.out_stats) return;
-    for (uint64_t m = __ballot(in); m;) {
+    for (uint64_t m = p.out_stats ? __ballot(in) : 0; m;) {
         const int t = __builtin_amdgcn_readlane(f, __ffsll((unsigned long long)m) - 1);
         const uint64_t of_table = __ballot(in && f == t);
         const uint32_t hits = (uint32_t)__popcll(__ballot(hit) & of_table), misses = (uint32_t)__popcll(mb & of_table);
@@ -1513,6 +1536,7 @@ __global__ __launch_bounds__(kBlock, 4) void k_discover_tables_chunk(Params p)
         if (v) atomicAdd(stat_word(p, t, lane), (unsigned long long)v);
         m &= ~of_table;
     }
+    if constexpr (OVERLAP) finish();
 }
 
 // Several tables: the table of a whole segment of positions [seg_base, seg_base + seg_len), when one

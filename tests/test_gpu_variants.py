@@ -541,14 +541,14 @@ def test_groups_around_the_line_of_the_last_kernel(more):
     jp.close()
 
 
-# ---- groups on both sides of the line at which a wavefront of Pass 1 comes to have a second chunk: features end inside of
+# ---- groups on both sides of the lines at which a wavefront of Pass 1 comes to have a second chunk, and of overlapped inserts: features end inside of
 # wavefronts, the same ids are new in all of them, tables of fewer slots than a request is wide, windows around the block sizes
 @pytest.mark.parametrize("records", [range(6), (1, 2, 4)], ids=["records", "mixed"])
-@pytest.mark.parametrize("more", [0, 1])
-def test_groups_around_the_line_of_one_chunk(more, records):
+@pytest.mark.parametrize("chunks,more", [(8, 0), (8, 1), (4, 0), (4, 1)])
+def test_groups_around_the_line_of_one_chunk(chunks, more, records):
     from test_gpu_jagged import JaggedPair
     rng = rng_for(923)
-    n = torch.cuda.get_device_properties(0).multi_processor_count * 8 * 256 + more
+    n = torch.cuda.get_device_properties(0).multi_processor_count * chunks * 256 + more
     specs = [wl.TableSpec(120_011, 16, 1, True, 101), wl.TableSpec(50, 64, 1, True, 102), wl.TableSpec(90_001, 9, 0, "lru", 103),
              wl.TableSpec(5, 8, 2, "expiry", 104), wl.TableSpec(150_000, 24, 2, "expiry", 105), wl.TableSpec(80_000, 65, 0, False, 106)]
     jp = JaggedPair(specs, records)
