@@ -570,34 +570,40 @@ __device__ __forceinline__ void publish_counters(const Params &p, unsigned long 
 
 // The outcomes of the claimants that a wavefront of the allocation has served, of one table at a time.  A claim that meets a slot
 // nobody has claimed yet is an insert or an eviction whatever displacements follow, so they are known when the claims stand.
-// (In LDS, a word per lane: these kernels have no register left.)
-struct Outcomes {
-    uint32_t *agents;                                // LDS, kWave words each
-    uint32_t *placed;                                // inserts and, 16 bits up, evictions
-    int table;
-};
+// (In LDS, words per lane: these kernels have no register left.)
 struct OutcomeArea {
     uint32_t agents[kWave];
-    uint32_t placed[kWave];
+    uint32_t placed[2][kWave];                       // inserts, evictions
 };
+struct Outcomes {
+    OutcomeArea *area;
+    int table;
+};
+__device__ __forceinline__ void clear_outcomes(OutcomeArea &s)
+{
+    const int lane = lane_id();
+    s.agents[lane] = 0;
+    s.placed[0][lane] = 0;
+    s.placed[1][lane] = 0;
+}
 // (the kernels of the allocation also clear what k_finalize counts in: it is all zero for it, whatever it left behind)
 __device__ __forceinline__ Outcomes no_outcomes(const Params &p, OutcomeArea &s)
 {
     static_assert(kMaxTables == kWave, "a word per lane");
     if (blockIdx.x == 0) p.ctl->num_evicted[lane_id()] = 0;
-    s.agents[lane_id()] = 0;
-    s.placed[lane_id()] = 0;
-    return Outcomes{s.agents, s.placed, 0};
+    clear_outcomes(s);
+    return Outcomes{&s, 0};
 }
-// (a wavefront has at most 2^30 positions / 8 192 segments, or 2^17, and a lane an eighth of them)
+// A word counts positions of the call, 2^30 of them at most, and add_outcomes' sums do, whichever lanes serve a claimant (one in
+// k_allocate, eight in k_allocate_lru, all of them in k_allocate_lru_long) and however few wavefronts share a call.
+static_assert(MPZCH_MAX_BATCH <= UINT32_MAX, "outcomes are counted in 32 bits");
 __device__ __forceinline__ void count_placed(Outcomes &o, int64_t old)
 {
-    if (!is_tag(old))
-        __hip_atomic_fetch_add(&o.placed[lane_id()], old == -1 ? 1u : 1u << 16, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WAVEFRONT);
+    if (!is_tag(old)) __hip_atomic_fetch_add(&o.area->placed[old != -1][lane_id()], 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WAVEFRONT);
 }
 __device__ __forceinline__ void count_agent(Outcomes &o)
 {
-    __hip_atomic_fetch_add(&o.agents[lane_id()], 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WAVEFRONT);
+    __hip_atomic_fetch_add(&o.area->agents[lane_id()], 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WAVEFRONT);
 }
 // counts: whether what this lane has counted is to be added (one lane of those that serve a claimant)
 template <bool MULTI>
@@ -605,7 +611,7 @@ __device__ __forceinline__ void add_outcomes(const Params &p, Outcomes &o, bool 
 {
     static_assert(kInserts == kDistinctMiss + 1 && kEvictions == kDistinctMiss + 2, "three words side by side");
     const int lane = lane_id();
-    const uint32_t a = counts ? o.agents[lane] : 0u, placed = counts ? o.placed[lane] : 0u, i = placed & 0xFFFFu, e = placed >> 16;
+    const uint32_t a = counts ? o.area->agents[lane] : 0u, i = counts ? o.area->placed[0][lane] : 0u, e = counts ? o.area->placed[1][lane] : 0u;
     if (!__any(a)) return;
     uint32_t v;
     if (!__any((a | i | e) >> 4)) {                  // up to 15 each, as nearly always: one sum of three times ten bits
@@ -623,8 +629,7 @@ __device__ __forceinline__ void count_for(const Params &p, Outcomes &o, int f, b
 {
     if (!MULTI || f == o.table) return;
     add_outcomes<MULTI>(p, o, counts);
-    o.agents[lane_id()] = 0;
-    o.placed[lane_id()] = 0;
+    clear_outcomes(*o.area);
     o.table = f;
 }
 

@@ -416,3 +416,31 @@ def test_maximum_batch_in_one_call():
     assert np.array_equal(out[pos_t].cpu().numpy(), so)
     assert fo.mean() > 0.97
     g.close()
+
+
+def test_more_than_65536_outcomes_per_wavefront():
+    """2^29 + 2^24 new ids in one call of a table under the LRU policy with a window beyond 64 slots: each of the 8 192 wavefronts
+    of the allocation serves 67 584 claimants, and its first lane counts the outcomes of all of them.  The counters are compared
+    with the table: too many for the oracle to replay."""
+    n = (1 << 29) + (1 << 24)
+    num_slots, max_probe, seed = (1 << 30) + 7, 70, 0x5EED0051
+    g = mp.MpzchTable(num_slots, max_probe, mp.EVICT_LRU, 0, seed)
+    ids = torch.empty(n, dtype=torch.int64, device="cuda")
+    chunk = 1 << 26
+    for lo in range(0, n, chunk):
+        ids[lo:min(lo + chunk, n)] = wl.distinct_ids_device(lo, min(lo + chunk, n), ids.device, salt=7)
+    say("outcomes: remap of", n, "new ids")
+    out = g.remap(ids, 1)
+    torch.cuda.synchronize()
+    st = g.stats_dict()
+    say("outcomes:", st)
+    assert st["hit_pos"] == 0 and st["invalid_pos"] == 0 and st["miss_pos"] == n and st["distinct_miss"] == n
+    occupied = int((g.identities >= 0).sum().item())
+    assert int((g.identities < -1).sum().item()) == 0
+    assert st["inserts"] == occupied and st["evictions"] == 0 and st["collisions"] == n - occupied
+    assert int(g.num_evicted.item()) == 0
+    # every id is in its slot but the counted ones (at half load a uniform hash leaves 1 of 150 M ids without a slot in windows of
+    # 64, see test_table1_cells_at_full_scale: some 4 here)
+    homeless = sum(int((g.identities[out[lo:lo + chunk]] != ids[lo:lo + chunk]).sum()) for lo in range(0, n, chunk))
+    assert homeless == st["collisions"] < 40
+    g.close()
