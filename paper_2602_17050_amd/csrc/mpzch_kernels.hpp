@@ -568,69 +568,72 @@ __device__ __forceinline__ void publish_counters(const Params &p, unsigned long 
     }
 }
 
-// The outcomes of the claimants that a wavefront of the allocation has served, of one table at a time.  A claim that meets a slot
-// nobody has claimed yet is an insert or an eviction whatever displacements follow, so they are known when the claims stand.
-// (In LDS, words per lane: these kernels have no register left.)
-struct OutcomeArea {
-    uint32_t agents[kWave];
-    uint32_t placed[2][kWave];                       // inserts, evictions
-};
+// The outcomes of the claimants that a wavefront of the allocation has served.  A claim that meets a slot nobody has claimed yet is
+// an insert or an eviction whatever displacements follow, and it ends the chain of the lane or group that carries it: so the
+// lane that holds a claimant's list entry knows one outcome when its chain has ended, keeps it with the claimant's hint, which it holds
+// anyway, and the wavefront counts a chunk's by ballot.  (Counted where a claim stands, in words of the lanes in LDS, they cost the
+// claims registers, a wavefront per SIMD in LRU groups.  Before any were counted here / so counted / now, both builds in turn on the same
+// tables, us, windows of 16 unless said: the allocation of 26 x 400 000 values, LRU, 250 / 263 / 251, of 64 541 / 556 / 543; whole steps 924 /
+// 937 / 922, 1 762 / 1 778 / 1 764; 8 x 100 000, LRU, of 100, 490 / 511 / 485, of 8 90 / 91 / 87; TTL 26 x 20 000 74 / 68 / 68.)
+// A word counts positions of the call, MPZCH_MAX_BATCH of them at most, however many a wavefront gets.
 struct Outcomes {
-    OutcomeArea *area;
-    int table;
+    uint32_t word[3][kMaxTables];                    // ids, inserts, evictions
 };
-__device__ __forceinline__ void clear_outcomes(OutcomeArea &s)
-{
-    const int lane = lane_id();
-    s.agents[lane] = 0;
-    s.placed[0][lane] = 0;
-    s.placed[1][lane] = 0;
-}
-// (the kernels of the allocation also clear what k_finalize counts in: it is all zero for it, whatever it left behind)
-__device__ __forceinline__ Outcomes no_outcomes(const Params &p, OutcomeArea &s)
-{
-    static_assert(kMaxTables == kWave, "a word per lane");
-    if (blockIdx.x == 0) p.ctl->num_evicted[lane_id()] = 0;
-    clear_outcomes(s);
-    return Outcomes{&s, 0};
-}
-// A word counts positions of the call, 2^30 of them at most, and add_outcomes' sums do, whichever lanes serve a claimant (one in
-// k_allocate, eight in k_allocate_lru, all of them in k_allocate_lru_long) and however few wavefronts share a call.
 static_assert(MPZCH_MAX_BATCH <= UINT32_MAX, "outcomes are counted in 32 bits");
-__device__ __forceinline__ void count_placed(Outcomes &o, int64_t old)
+static_assert(kMaxTables == kWave, "a lane per table");
+static_assert(kInserts == kDistinctMiss + 1 && kEvictions == kDistinctMiss + 2, "three counters side by side");
+constexpr uint32_t kOutcomeInsert = 0x200u, kOutcomeEvict = 0x400u;      // (above what first_of takes of a hint)
+__device__ __forceinline__ uint32_t outcome_of(int64_t old) { return is_tag(old) ? 0u : old == -1 ? kOutcomeInsert : kOutcomeEvict; }
+
+// (the kernels of the allocation also clear what k_finalize counts in: it is all zero for it, whatever it left behind)
+__device__ __forceinline__ void clear_outcomes(const Params &p, Outcomes &o)
 {
-    if (!is_tag(old)) __hip_atomic_fetch_add(&o.area->placed[old != -1][lane_id()], 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WAVEFRONT);
-}
-__device__ __forceinline__ void count_agent(Outcomes &o)
-{
-    __hip_atomic_fetch_add(&o.area->agents[lane_id()], 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WAVEFRONT);
-}
-// counts: whether what this lane has counted is to be added (one lane of those that serve a claimant)
-template <bool MULTI>
-__device__ __forceinline__ void add_outcomes(const Params &p, Outcomes &o, bool counts)
-{
-    static_assert(kInserts == kDistinctMiss + 1 && kEvictions == kDistinctMiss + 2, "three words side by side");
     const int lane = lane_id();
-    const uint32_t a = counts ? o.area->agents[lane] : 0u, i = counts ? o.area->placed[0][lane] : 0u, e = counts ? o.area->placed[1][lane] : 0u;
-    if (!__any(a)) return;
-    uint32_t v;
-    if (!__any((a | i | e) >> 4)) {                  // up to 15 each, as nearly always: one sum of three times ten bits
-        v = wave_sum32(a | i << 10 | e << 20) >> (10 * (lane < 3 ? lane : 0)) & 0x3FFu;
-    } else {
-        const uint32_t agents = wave_sum32(a), inserts = wave_sum32(i), evictions = wave_sum32(e);
-        v = lane == 0 ? agents : lane == 1 ? inserts : evictions;
-    }
-    if (lane < 3 && v)
-        atomicAdd(stat_word(p, MULTI ? o.table : (int)(blockIdx.x / kBins) % kSpread, kDistinctMiss + lane), (unsigned long long)v);
+    if (blockIdx.x == 0) p.ctl->num_evicted[lane] = 0;
+    for (int k = 0; k < 3; ++k) o.word[k][lane] = 0;
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
 }
-// what follows is counted for table f (the same in all lanes)
-template <bool MULTI>
-__device__ __forceinline__ void count_for(const Params &p, Outcomes &o, int f, bool counts)
+// Claimants of table t (the same in all lanes), hint: theirs and its outcome.
+__device__ __forceinline__ void count_outcomes(Outcomes &o, bool agent, uint32_t hint, int t)
 {
-    if (!MULTI || f == o.table) return;
-    add_outcomes<MULTI>(p, o, counts);
-    clear_outcomes(*o.area);
-    o.table = f;
+    int lane = lane_id();
+    asm volatile("" : "+v"(lane));                   // (compared here: the masks would else be kept, or spilled, through the loops of claims)
+    const uint64_t agents = __ballot(agent);
+    const uint32_t ids = (uint32_t)__popcll(agents), inserts = (uint32_t)__popcll(__ballot((hint & kOutcomeInsert) != 0) & agents),
+                   evictions = (uint32_t)__popcll(__ballot((hint & kOutcomeEvict) != 0) & agents);
+    if (lane < 3)
+        __hip_atomic_fetch_add(&o.word[lane][t], lane == 0 ? ids : lane == 1 ? inserts : evictions, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WAVEFRONT);
+}
+// Claimants of several tables, f being each one's own.
+template <bool MULTI>
+__device__ __forceinline__ void count_outcomes_of(Outcomes &o, bool agent, uint32_t hint, int f)
+{
+    if constexpr (MULTI) {
+        for (uint64_t m = __ballot(agent); m;) {
+            const int t = __builtin_amdgcn_readlane(f, __ffsll((unsigned long long)m) - 1);
+            const bool of_table = agent && f == t;
+            count_outcomes(o, of_table, hint, t);
+            m &= ~__ballot(of_table);
+        }
+    } else {
+        count_outcomes(o, agent, hint, 0);
+    }
+}
+template <bool MULTI>
+__device__ __forceinline__ void add_outcomes(const Params &p, Outcomes &o)
+{
+    const int lane = lane_id();
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    if constexpr (MULTI) {
+        if (o.word[0][lane] == 0) return;
+        for (int k = 0; k < 3; ++k) {
+            const uint32_t v = o.word[k][lane];
+            if (v) atomicAdd(stat_word(p, lane, kDistinctMiss + k), (unsigned long long)v);
+        }
+    } else if (lane < 3) {
+        const uint32_t v = o.word[lane][0];
+        if (v) atomicAdd(stat_word(p, (int)(blockIdx.x / kBins) % kSpread, kDistinctMiss + lane), (unsigned long long)v);
+    }
 }
 
 // ------------------------------------------------------------------ Pass 1 (discovery)
@@ -1571,7 +1574,7 @@ constexpr uint32_t kHintUnplaced = 0xFE;   // ran out of slots: falls back to ho
 constexpr uint32_t kHintUnknown = 0xFD;    // placed, but not at a round that fits the hint: search the window
 
 // What k_allocate leaves in first_of for k_finalize: the position of the first occurrence of the entry's id, or, for
-// that position itself, kAgentEntry | hint, with kAgentOcc if the slot there held an id.  Of tables that are not LRU that stands
+// that position itself, kAgentEntry | hint, with kAgentOcc if the slot there held an id (and the outcome, which is counted already).  Of tables that are not LRU that stands
 // unless a note says that the claim was displaced.
 constexpr uint32_t kAgentEntry = 0x80000000u;
 constexpr uint32_t kAgentOcc = 0x100u;
@@ -1766,12 +1769,12 @@ __device__ __forceinline__ void claim_walk(const Tab &d, Claimant &c, const Clai
 // table at a time (nearly always all of them: a segment is a few thousand positions, a feature's share many times that).
 template <bool MULTI, bool REC>
 __device__ __forceinline__ void allocate_body(const Params &p, int64_t vblock, int64_t vgrid,
-                                              uint8_t *s_code, ClaimReq *s_req, OutcomeArea &s_outcomes)
+                                              uint8_t *s_code, ClaimReq *s_req, Outcomes &outcomes)
 {
     const int lane = lane_id();
     const Tab d0 = view(p.t0);
     const int64_t lane_offset = MULTI ? table_offsets(p.offsets, p.num_tables) : 0;
-    Outcomes outcomes = no_outcomes(p, s_outcomes);
+    clear_outcomes(p, outcomes);
     for (int64_t seg = vblock; seg < p.num_segs; seg += vgrid) {
         const uint32_t cnt = p.seg_cnt[seg];
         const int64_t seg_base = seg * p.seg_chunks * kWave;
@@ -1827,11 +1830,9 @@ __device__ __forceinline__ void allocate_body(const Params &p, int64_t vblock, i
                 } else {
                     todo = false;
                 }
-                if constexpr (MULTI) count_for<MULTI>(p, outcomes, of_table, true);
-                if (agent) count_agent(outcomes);
                 const int32_t bound = expiry_bound(d, p.step);
                 const bool aligned = (d.N << (3 + d.sh)) > kCachedTableBytes;
-                uint32_t hint = kHintUnplaced;        // (and kAgentOcc)
+                uint32_t hint = kHintUnplaced;        // (and kAgentOcc, and the outcome)
                 // the claimant this lane carries
                 Claimant c;
                 c.active = agent;
@@ -1854,12 +1855,13 @@ __device__ __forceinline__ void allocate_body(const Params &p, int64_t vblock, i
                                        } else {
                                            p.hint[who] = (uint8_t)at;
                                        }
-                                       count_placed(outcomes, old);
+                                       hint |= outcome_of(old);
                                        if (is_tag(old)) p.note[tag_pos(old)] = 1;
                                    },
                                    [](uint32_t) {});
                     __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");   // s_code and s_req are written again
                 }
+                count_outcomes(outcomes, agent, hint, MULTI ? of_table : 0);
                 if (agent) {
                     if (!alone) p.hint[pos] = (uint8_t)hint;  // for the copies of the id
                     p.first_of[idx] = kAgentEntry | hint;
@@ -1868,7 +1870,7 @@ __device__ __forceinline__ void allocate_body(const Params &p, int64_t vblock, i
             __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
         }
     }
-    add_outcomes<MULTI>(p, outcomes, true);
+    add_outcomes<MULTI>(p, outcomes);
 }
 
 template <bool MULTI, bool REC>
@@ -1876,7 +1878,7 @@ __global__ __launch_bounds__(kWave, MULTI ? 5 : 7) void k_allocate(Params p)
 {
     __shared__ __attribute__((aligned(16))) uint8_t s_code[kWave * kAllocG];
     __shared__ ClaimReq s_req[kWave];
-    __shared__ OutcomeArea s_outcomes;
+    __shared__ Outcomes s_outcomes;
     allocate_body<MULTI, REC>(p, blockIdx.x, gridDim.x, s_code, s_req, s_outcomes);
 }
 
@@ -2059,8 +2061,8 @@ __global__ __launch_bounds__(kWave, MULTI ? (T == 8 ? 3 : 4) : T == 8 ? 4 : T ==
     const int lane = threadIdx.x;
     const int g = lane / G;
     const Tab d0 = view(MULTI ? p.descs[0] : p.t0);
-    __shared__ OutcomeArea s_outcomes;
-    Outcomes outcomes = no_outcomes(p, s_outcomes);
+    __shared__ Outcomes outcomes;
+    clear_outcomes(p, outcomes);
     for (int64_t seg = blockIdx.x; seg < p.num_segs; seg += gridDim.x) {
         const uint32_t cnt = (uint32_t)uniform32((int)p.seg_cnt[seg]);
         const int64_t seg_base = seg * p.seg_chunks * kWave;
@@ -2093,9 +2095,9 @@ __global__ __launch_bounds__(kWave, MULTI ? (T == 8 ? 3 : 4) : T == 8 ? 4 : T ==
             int src = next_bits<G>(am, g);
             uint32_t cpos = __shfl(pos, src >= 0 ? src : lane);
             int64_t chome = shfl64(home, src >= 0 ? src : lane);
-            int fc = __shfl(f, src >= 0 ? src : lane);
+            const int f1 = __shfl(f, src >= 0 ? src : lane);
             Tab d = d0;
-            if (MULTI && src >= 0) d = view(p.descs[fc]);
+            if (MULTI && src >= 0) d = view(p.descs[f1]);
             LruSlots<T> x = load_lru_slots<T, REC>(d, src >= 0, chome);
             while (__any(src >= 0)) {
                 const int src2 = next_bits<G>(am, g);
@@ -2105,30 +2107,19 @@ __global__ __launch_bounds__(kWave, MULTI ? (T == 8 ? 3 : 4) : T == 8 ? 4 : T ==
                 Tab d2 = d0;
                 if (MULTI && src2 >= 0) d2 = view(p.descs[f2]);
                 const LruSlots<T> x2 = load_lru_slots<T, REC>(d2, src2 >= 0, chome2);
-                int32_t fr = -1;
-                bool counted = src >= 0;             // (else: of a table beside the one that is counted for, at a feature's end)
-                if constexpr (MULTI) {
-                    count_for<MULTI>(p, outcomes, __builtin_amdgcn_readlane(fc, __ffsll((unsigned long long)__ballot(counted)) - 1), lane % G == 0);
-                    counted = counted && fc == outcomes.table;
-                }
-                if (counted) count_agent(outcomes);
+                uint32_t fr = kHintUnplaced;         // (and the outcome)
                 claim_group_lru<T, REC>(p, d, src >= 0, cpos, chome, x,
                                         [&](uint32_t who, int32_t, int32_t round, int64_t, int64_t old) {
-                                            if (who == cpos) fr = round;
-                                            if (!MULTI || counted) count_placed(outcomes, old);
-                                            else if (lane % G == 0 && !is_tag(old)) atomicAdd(stat_word(p, fc, old == -1 ? kInserts : kEvictions), 1ull);
+                                            if (who == cpos) fr = (uint32_t)round;
+                                            fr |= outcome_of(old);
                                         },
                                         [](uint32_t) {});
                 // the outcome goes to the lane that holds the claimant's list entry
 #pragma unroll
                 for (int k = 0; k < NG; ++k) {
                     const int sk = __shfl(src, k * G);
-                    const int32_t frk = __shfl(fr, k * G);
-                    if (lane == sk) hint = frk < 0 ? kHintUnplaced : (uint32_t)frk;
-                }
-                if constexpr (MULTI) {
-                    if (src >= 0 && !counted && lane % G == 0) atomicAdd(stat_word(p, fc, kDistinctMiss), 1ull);
-                    fc = f2;
+                    const uint32_t frk = __shfl(fr, k * G);
+                    if (lane == sk) hint = frk;
                 }
                 src = src2;
                 cpos = cpos2;
@@ -2136,12 +2127,13 @@ __global__ __launch_bounds__(kWave, MULTI ? (T == 8 ? 3 : 4) : T == 8 ? 4 : T ==
                 d = d2;
                 x = x2;
             }
+            count_outcomes_of<MULTI>(outcomes, agent, hint, f);
             if (agent) p.hint[pos] = (uint8_t)hint;
             if (agent) p.first_of[idx] = kAgentEntry | hint;
             else if (!MULTI && have) p.first_of[idx] = first;     // (several tables: k_allocate has written it)
         }
     }
-    add_outcomes<MULTI>(p, outcomes, lane % G == 0);
+    add_outcomes<MULTI>(p, outcomes);
 }
 
 // LRU for probe ranges of 65 .. 1 024 slots: the whole wavefront serves one claimant, a lane holds
@@ -2162,7 +2154,7 @@ __device__ __forceinline__ uint64_t wave_min64(uint64_t x)
     return x;
 }
 
-__device__ __forceinline__ int32_t claim_wave_lru_long(const Params &p, const Tab &d, uint32_t cpos, int32_t choice, Outcomes &outcomes)
+__device__ __forceinline__ int32_t claim_wave_lru_long(const Params &p, const Tab &d, uint32_t cpos, int32_t choice, uint32_t &outcome)
 {
     const int lane = lane_id();
     const int C = (d.P + kWave - 1) / kWave;             // <= kLruLongSlots (checked when the table is created)
@@ -2238,7 +2230,7 @@ __device__ __forceinline__ int32_t claim_wave_lru_long(const Params &p, const Ta
             if (is_tag(old) && old < mine) continue;                    // a better claim holds this slot
             placed = true;
             displaced = is_tag(old) ? old : 0;
-            count_placed(outcomes, old);
+            outcome = outcome_of(old);
             if (is_first) first_round = round;
         }
         is_first = false;
@@ -2254,8 +2246,8 @@ __global__ __launch_bounds__(kWave) void k_allocate_lru_long(Params p)
 {
     const int lane = threadIdx.x;
     const Tab d0 = view(MULTI ? p.descs[0] : p.t0);
-    __shared__ OutcomeArea s_outcomes;
-    Outcomes outcomes = no_outcomes(p, s_outcomes);
+    __shared__ Outcomes outcomes;
+    clear_outcomes(p, outcomes);
     for (int64_t seg = blockIdx.x; seg < p.num_segs; seg += gridDim.x) {
         const uint32_t cnt = p.seg_cnt[seg];
         const int64_t seg_base = seg * p.seg_chunks * kWave;
@@ -2284,18 +2276,18 @@ __global__ __launch_bounds__(kWave) void k_allocate_lru_long(Params p)
                 const uint32_t cpos = __shfl(pos, src);
                 const int fs = __shfl(f, src);
                 const Tab d = MULTI ? view(p.descs[fs]) : d0;
-                count_for<MULTI>(p, outcomes, fs, lane == 0);
-                count_agent(outcomes);
-                const int32_t fr = claim_wave_lru_long(p, d, cpos, 0, outcomes);
+                uint32_t outcome = 0;
+                const int32_t fr = claim_wave_lru_long(p, d, cpos, 0, outcome);
                 if (lane == src)
-                    hint = fr < 0 ? kHintUnplaced : (fr < (int32_t)kHintUnknown ? (uint32_t)fr : kHintUnknown);
+                    hint = (fr < 0 ? kHintUnplaced : (fr < (int32_t)kHintUnknown ? (uint32_t)fr : kHintUnknown)) | outcome;
             }
+            count_outcomes_of<MULTI>(outcomes, agent, hint, f);
             if (agent) p.hint[pos] = (uint8_t)hint;
             if (agent) p.first_of[idx] = kAgentEntry | hint;
             else if (!MULTI && have) p.first_of[idx] = first;     // (several tables: k_allocate has written it)
         }
     }
-    add_outcomes<MULTI>(p, outcomes, lane == 0);
+    add_outcomes<MULTI>(p, outcomes);
 }
 
 // ------------------------------------------------------------------ finalize

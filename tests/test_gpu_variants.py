@@ -459,6 +459,28 @@ def test_counters_of_lists(policy, probe, n, layout):
     t.close()
 
 
+# ---- ... and calls of many claimants per lane (16 outcomes and more are added in another way), from 2^24 positions on over two
+# segments per wavefront.  All ids new: into an empty table, then over those of the first call.  The counters are compared with
+# what the call has changed in the table.
+@pytest.mark.parametrize("n", [9_000_000, (1 << 24) + 65])
+@pytest.mark.parametrize("policy,probe,layout", [(mp.EVICT_TTL, 12, "records"), (mp.EVICT_TTL, 12, "separate"), (mp.EVICT_LRU, 7, "records"),
+                                                 (mp.EVICT_LRU, 15, "separate"), (mp.EVICT_LRU, 30, "records"), (mp.EVICT_LRU, 60, "separate")])
+def test_counters_of_long_lists(policy, probe, layout, n):
+    g = mp.MpzchTable(n + n // 8, probe, policy, 1, 53, layout=mp.LAYOUT_RECORDS if layout == "records" else mp.LAYOUT_SEPARATE)
+    for call in range(2):
+        before = g.identities.clone()
+        g.remap(wl.distinct_ids_device(call * n, (call + 1) * n, "cuda", salt=3), 5 * call)
+        st = g.stats_dict()
+        inserted, changed = (before == -1) & (g.identities >= 0), (before >= 0) & (g.identities != before)
+        assert int((g.identities < -1).sum()) == 0
+        assert st["miss_pos"] == st["distinct_miss"] == n and st["hit_pos"] == st["invalid_pos"] == 0
+        assert st["inserts"] == int(inserted.sum()) and st["evictions"] == int(changed.sum()) == int(g.num_evicted)
+        assert st["collisions"] == n - st["inserts"] - st["evictions"]
+        assert torch.equal(torch.sort(g.evicted).values, torch.nonzero(changed).flatten())
+        assert st["inserts"] > n // 2 if call == 0 else st["evictions"] > n // 2
+    g.close()
+
+
 @pytest.mark.parametrize("kinds", [(True, "lru", False), ("lru", "lru", "expiry")])
 @pytest.mark.parametrize("probe", [8, 61, 70])
 def test_counters_of_groups(probe, kinds):
