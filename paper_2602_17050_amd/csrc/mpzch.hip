@@ -314,10 +314,35 @@ int lookup_grid(int64_t n, int num_cus)
 // records 100 K (of 32) 21.6 / 21.3, 150 K (of 32, expiry steps) 28.4 / 28.7, 200 K 30.9 / 31.0, 230 K 33.0 / 33.3.
 constexpr bool overlap_insert(int64_t groups, int num_cus, bool records) { return groups <= (records ? 2 : 4) * (int64_t)num_cus; }
 
-// (k_discover_tables_chunk as far as it reaches, up to 524 288 values on 256 compute units: it is the faster one there too.)
-mpzch_status_t launch_discover(const Params &p, int grid, int num_cus, hipStream_t s)
+// The longest windows, min(max_probe, num_slots), of the tables involved: of those under the LRU policy and of the others; 0 where
+// there is none.
+struct Windows {
+    int32_t lru, other;
+};
+Windows windows_of(const TableDesc &d) { return d.evict == 2 ? Windows{d.P, 0} : Windows{0, d.P}; }
+Windows longest(Windows a, Windows b) { return {a.lru > b.lru ? a.lru : b.lru, a.other > b.other ? a.other : b.other}; }
+
+// Groups with one chunk per wavefront (up to 524 288 values on 256 compute units) run k_discover_tables_chunk where searches end
+// early.  It looks from the home slot on, so every look of 8 slots of records is two lines, where k_discover_tables_records, whose
+// first look is an aligned block, goes on with one each: long searches cost it more than the round trip that it saves, and the more
+// so the more wavefronts share the memory.  How long they are the windows tell: an absent id's search ends at an empty slot, and LRU tables
+// have none once they are full.  26 tables at 95 % load or full, Pass 1 of this / of the other kernels, by workgroups per compute
+// unit (1, 2, 3, 4, 6, 8).  Records, LRU, windows of 32: 0.69 0.82 0.87 0.93 0.92 1.00, of 64: 0.79 0.82 0.93 1.03 1.03 1.12, of 256: 0.89 0.93
+// 1.00 1.16 1.11 1.21; TTL, of 128: 0.81 0.88 0.86 0.91 0.95 0.99, of 256: 0.81 0.85 0.86 0.92 0.95 1.03, of 512: 0.76 0.82 0.95 0.97 0.98
+// 1.05.  Two tensors (8 slots are half a line), LRU, of 100: 0.79 0.79 0.82 0.83 0.90 0.99, of 256: 0.87 0.90 0.90 0.96 0.96 1.05; TTL, of
+// 512: 0.77 0.81 0.95 0.93 0.89 0.91.  Windows of 1 000, whole steps of 1.6 workgroups 0.95 to 1.03, of 4 1.04 to 1.08.
+constexpr bool tables_by_chunk(int64_t groups, int num_cus, bool records, Windows w)
 {
-    if (p.num_tables > 1 && p.seg_chunks == 1) {
+    int per_cu = 8;
+    if (records && w.lru > 32) per_cu = 3;
+    else if (w.lru > 100 || (records && w.other > 128)) per_cu = 6;
+    if (w.other > 512 || w.lru > 512) per_cu = 2;
+    return groups <= (int64_t)per_cu * num_cus;
+}
+
+mpzch_status_t launch_discover(const Params &p, int grid, int num_cus, Windows windows, hipStream_t s)
+{
+    if (p.num_tables > 1 && p.seg_chunks == 1 && tables_by_chunk(grid, num_cus, p.all_records, windows)) {
         const bool overlap = overlap_insert(grid, num_cus, false);
         if (p.all_records && overlap) TRY(launch(k_discover_tables_chunk<true, true>, grid, kBlock, s, p));
         else if (p.all_records) TRY(launch(k_discover_tables_chunk<true, false>, grid, kBlock, s, p));
@@ -360,7 +385,7 @@ mpzch_status_t launch_lookup_short(const Params &p, hipStream_t s)
     return MPZCH_OK;
 }
 
-// max_p_lru: largest min(max_probe, num_slots) of the LRU tables involved, 0 when there is none
+// max_p_lru: Windows::lru
 template <bool MULTI, bool REC>
 mpzch_status_t launch_allocate_lru(int32_t max_p_lru, const Params &p, int grid, hipStream_t s)
 {
@@ -460,11 +485,11 @@ mpzch_status_t launch_remap_block(Timing &tm, const Params &p, hipStream_t s)
 }
 
 // The launch sequence of one training remap (single table or group).
-mpzch_status_t launch_remap(Scratch &sc, Timing &tm, Params p, int32_t max_p_lru, hipStream_t s);
+mpzch_status_t launch_remap(Scratch &sc, Timing &tm, Params p, Windows windows, hipStream_t s);
 
 // Every call leaves the scratch set empty and the counter block zeroed -- unless its launch
 // sequence was cut short by a HIP error; the next call then clears both before it starts.
-mpzch_status_t run_remap(Scratch &sc, Timing &tm, const Params &p, int32_t max_p_lru, hipStream_t s)
+mpzch_status_t run_remap(Scratch &sc, Timing &tm, const Params &p, Windows windows, hipStream_t s)
 {
     if (one_block(p)) return launch_remap_block(tm, p, s);        // uses no scratch
     if (sc.dirty) {
@@ -473,7 +498,7 @@ mpzch_status_t run_remap(Scratch &sc, Timing &tm, const Params &p, int32_t max_p
         TRY(fill64((int64_t *)sc.ctl, (int64_t)((L.total - L.o_ctl) / sizeof(int64_t)), 0, s));
     }
     sc.dirty = true;
-    const mpzch_status_t st = launch_remap(sc, tm, p, max_p_lru, s);
+    const mpzch_status_t st = launch_remap(sc, tm, p, windows, s);
     if (st == MPZCH_OK) sc.dirty = false;
     return st;
 }
@@ -534,7 +559,7 @@ mpzch_status_t launch_remap_chunks(Timing &tm, const Params &p, int32_t max_p_lr
     return MPZCH_OK;
 }
 
-mpzch_status_t launch_remap(Scratch &sc, Timing &tm, Params p, int32_t max_p_lru, hipStream_t s)
+mpzch_status_t launch_remap(Scratch &sc, Timing &tm, Params p, Windows windows, hipStream_t s)
 {
     p.list = sc.list;
     p.ent = sc.ent;
@@ -553,9 +578,9 @@ mpzch_status_t launch_remap(Scratch &sc, Timing &tm, Params p, int32_t max_p_lru
     // one table, and no wavefront of Pass 1 has more than one chunk
     const int64_t groups = (p.n + kBlock - 1) / kBlock;
     // (the LRU policy with windows of more than 64 slots gives a claimant the whole wavefront)
-    if (p.num_tables == 1 && max_p_lru <= kWave && groups <= (int64_t)sc.num_cus * discover_blocks_per_cu() &&
+    if (p.num_tables == 1 && windows.lru <= kWave && groups <= (int64_t)sc.num_cus * discover_blocks_per_cu() &&
         p.n <= kChunkMaxBatch)
-        return launch_remap_chunks(tm, p, max_p_lru, (int)groups, sc.num_cus, s);
+        return launch_remap_chunks(tm, p, windows.lru, (int)groups, sc.num_cus, s);
 
     const int64_t num_chunks = (p.n + kWave - 1) / kWave;
     // k_discover: every wavefront owns one segment of seg_chunks 64-position chunks
@@ -566,8 +591,8 @@ mpzch_status_t launch_remap(Scratch &sc, Timing &tm, Params p, int32_t max_p_lru
     // per compute unit.)
     const int g_grp = grid_for((int64_t)p.num_segs, kFinalizeWaves, sc.num_cus, 2);
 
-    TIMED(tm, KDiscover, s, launch_discover(p, g_disc, sc.num_cus, s));
-    TIMED(tm, KAllocate, s, launch_allocate(max_p_lru, p, sc.num_cus, s));
+    TIMED(tm, KDiscover, s, launch_discover(p, g_disc, sc.num_cus, windows, s));
+    TIMED(tm, KAllocate, s, launch_allocate(windows.lru, p, sc.num_cus, s));
     TIMED(tm, KFinalize, s, launch_finalize(p, g_grp, sc.num_cus, s));
     return MPZCH_OK;
 }
@@ -847,7 +872,7 @@ mpzch_status_t remap_one(mpzch_table_t *t, int64_t *identities, int32_t *metadat
         for (int b = 0; b < 31; ++b)
             if (g.chunks == ((int64_t)1 << b)) p.g_shift = b;
     }
-    return run_remap(t->sc, t->tm, p, p.t0.evict == 2 ? p.t0.P : 0, s);
+    return run_remap(t->sc, t->tm, p, windows_of(p.t0), s);
 }
 }  // namespace
 
@@ -922,7 +947,7 @@ mpzch_status_t mpzch_remap_noalloc(const mpzch_table_t *t, int64_t *identities, 
     p.out_num_evicted = out_num_evicted;
     p.out_stats = out_stats;
     Timing off;                                  // never enabled: records nothing, creates no event
-    return run_remap(*sc, off, p, p.t0.evict == 2 ? p.t0.P : 0, s);
+    return run_remap(*sc, off, p, windows_of(p.t0), s);
 }
 
 mpzch_status_t mpzch_lookup(const mpzch_table_t *t, const int64_t *identities,
@@ -1221,7 +1246,7 @@ mpzch_status_t mpzch_remap_jagged_feature_ttl(mpzch_group_t *g, int64_t *const *
         for (int f = 0; f < T; ++f) any = any || g->cfgs[f].kind == MPZCH_EVICT_TTL_EXPIRY;
         if (!any) return MPZCH_ERR_INVALID_ARG;          // no table of the group uses retention times
     }
-    int32_t max_p_lru = 0;
+    Windows windows{0, 0};
     bool all_records = true;
     std::vector<TableDesc> descs((size_t)T);
     for (int f = 0; f < T; ++f) {
@@ -1232,7 +1257,7 @@ mpzch_status_t mpzch_remap_jagged_feature_ttl(mpzch_group_t *g, int64_t *const *
         if (cap > 0 && !out_evicted_slots) return MPZCH_ERR_INVALID_ARG;
         descs[f] = make_desc(g->cfgs[f], identities[f], metadata[f], evicted_offsets[f], cap);
         all_records = all_records && descs[f].sh == 1;
-        if (descs[f].evict == 2 && descs[f].P > max_p_lru) max_p_lru = descs[f].P;
+        windows = longest(windows, windows_of(descs[f]));
     }
     hipStream_t s = (hipStream_t)stream;
     if (total_values == 0) {
@@ -1262,7 +1287,7 @@ mpzch_status_t mpzch_remap_jagged_feature_ttl(mpzch_group_t *g, int64_t *const *
         p.out_evicted = out_evicted_slots + p.t0.ev_begin;
         p.t0.ev_begin = 0;
     }
-    return run_remap(g->sc, g->tm, p, max_p_lru, s);
+    return run_remap(g->sc, g->tm, p, windows, s);
 }
 
 mpzch_status_t mpzch_remap_jagged(mpzch_group_t *g, int64_t *const *identities, int32_t *const *metadata,

@@ -583,6 +583,25 @@ def test_groups_around_the_line_of_one_chunk(chunks, more, records):
     jp.close()
 
 
+# ---- groups on both sides of the lines that their longest windows draw for the same kernel (searches that go on beyond its widest
+# look, in full tables)
+@pytest.mark.parametrize("more", [0, 1])
+@pytest.mark.parametrize("chunks,policy,probe,records", [(3, "lru", 33, range(3)), (6, True, 129, range(3)), (6, "lru", 101, (1,)),
+                                                         (2, False, 513, range(3)), (2, "lru", 600, ())])
+def test_groups_around_the_lines_of_long_windows(chunks, policy, probe, records, more):
+    from test_gpu_jagged import JaggedPair
+    rng = rng_for(929)
+    n = torch.cuda.get_device_properties(0).multi_processor_count * chunks * 256 + more
+    specs = [wl.TableSpec(n // 2, 16, 1, True, 121), wl.TableSpec(2_003, probe, 1, policy, 122), wl.TableSpec(n // 3, 24, 2, "expiry", 123)]
+    jp = JaggedPair(specs, records)
+    offsets = np.array([0, n // 2 + 5, n // 2 + 3_009, n], dtype=np.int64)
+    for step in (0, 1, 3):
+        vals = np.concatenate([rng.integers(0, 2 * specs[f].num_slots, size=int(c)) + step * 400 for f, c in enumerate(np.diff(offsets))])
+        jp.step(vals, offsets, step)
+    jp.check_state()
+    jp.close()
+
+
 # ---- claims of groups stand without a look at the table unless a note says that they were displaced: crowded windows, where most
 # are, LRU tables (no notes) among the others, copies of new ids, the next call with the notes that this one must not leave behind
 @pytest.mark.parametrize("records", [range(5), (0, 3)], ids=["records", "mixed"])
