@@ -487,8 +487,9 @@ mpzch_status_t launch_remap_block(Timing &tm, const Params &p, hipStream_t s)
 // The launch sequence of one training remap (single table or group).
 mpzch_status_t launch_remap(Scratch &sc, Timing &tm, Params p, Windows windows, hipStream_t s);
 
-// Every call leaves the scratch set empty and the counter block zeroed -- unless its launch
-// sequence was cut short by a HIP error; the next call then clears both before it starts.
+// Every call leaves the scratch set and the notes empty and, of the counter block, `stats` and `done` zero -- unless its launch
+// sequence was cut short by a HIP error; the next call then clears all of it before it starts.  num_evicted is left as it is: it is
+// k_finalize's alone, and the kernels of the allocation, which run before every k_finalize, clear it (clear_outcomes).
 mpzch_status_t run_remap(Scratch &sc, Timing &tm, const Params &p, Windows windows, hipStream_t s)
 {
     if (one_block(p)) return launch_remap_block(tm, p, s);        // uses no scratch

@@ -48,9 +48,8 @@ constexpr int64_t kChunkMaxBatch = (int64_t)1 << 19;
 constexpr int kChunkPosBits = 20;
 constexpr uint32_t kChunkPosMask = (1u << kChunkPosBits) - 1u;
 
-//
-// In two halves: begin_insert requests the first compare-and-swap, and what the kernel has to store besides goes out while that
-// is under way (OVERLAP of k_discover_chunk).
+// A missed id enters it in two halves: begin_insert requests the first compare-and-swap, and what the kernel has to store besides goes
+// out while that is under way (OVERLAP of k_discover_chunk).
 struct SetInsert {
     uint32_t mine, e;                // what is entered, and where next
     uint32_t seen;                   // what was there

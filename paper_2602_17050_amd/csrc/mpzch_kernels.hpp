@@ -1778,7 +1778,7 @@ __device__ __forceinline__ void allocate_body(const Params &p, int64_t vblock, i
     for (int64_t seg = vblock; seg < p.num_segs; seg += vgrid) {
         const uint32_t cnt = p.seg_cnt[seg];
         const int64_t seg_base = seg * p.seg_chunks * kWave;
-        if ((int32_t)seg_base >= (int32_t)p.n) break;                           // segments past the batch hold nothing
+        if ((int32_t)seg_base >= (int32_t)p.n) break;         // segments past the batch hold nothing
         int seg_f = 0;
         Tab seg_d = d0;
         bool seg_one = true;
@@ -2449,7 +2449,7 @@ __device__ __forceinline__ void finalize_body(const Params &p)
         if (!multi) seg_d = view(p.t0);
         bool seg_one = true;
         if (multi) seg_one = segment_table(p, lane_offset, seg_base, p.seg_chunks * kWave, seg_f, seg_d);
-        if ((int32_t)seg_base >= (int32_t)p.n) break;                            // segments past the batch hold nothing
+        if ((int32_t)seg_base >= (int32_t)p.n) break;         // segments past the batch hold nothing
         for (uint32_t j0 = 0; j0 == 0 || j0 < cnt; j0 += kWave) {
             // (as in k_allocate, the first entries are requested before the count is known)
             const int64_t idx = seg_base + j0 + lane;

@@ -420,8 +420,8 @@ def test_maximum_batch_in_one_call():
 
 def test_more_than_65536_outcomes_per_wavefront():
     """2^29 + 2^24 new ids in one call of a table under the LRU policy with a window beyond 64 slots: each of the 8 192 wavefronts
-    of the allocation serves 67 584 claimants, and its first lane counts the outcomes of all of them.  The counters are compared
-    with the table: too many for the oracle to replay."""
+    of the allocation serves 67 584 claimants and counts their outcomes, more than 16 bits hold.  The counters are compared with the
+    table: too many for the oracle to replay."""
     n = (1 << 29) + (1 << 24)
     num_slots, max_probe, seed = (1 << 30) + 7, 70, 0x5EED0051
     g = mp.MpzchTable(num_slots, max_probe, mp.EVICT_LRU, 0, seed)

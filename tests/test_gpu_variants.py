@@ -459,8 +459,7 @@ def test_counters_of_lists(policy, probe, n, layout):
     t.close()
 
 
-# ---- ... and calls of many claimants per lane (16 outcomes and more are added in another way), from 2^24 positions on over two
-# segments per wavefront.  All ids new: into an empty table, then over those of the first call.  The counters are compared with
+# ---- ... and calls of many chunks per wavefront, whose outcomes add up, from 2^24 positions on over two segments.  All ids new: into an empty table, then over those of the first call.  The counters are compared with
 # what the call has changed in the table.
 @pytest.mark.parametrize("n", [9_000_000, (1 << 24) + 65])
 @pytest.mark.parametrize("policy,probe,layout", [(mp.EVICT_TTL, 12, "records"), (mp.EVICT_TTL, 12, "separate"), (mp.EVICT_LRU, 7, "records"),
