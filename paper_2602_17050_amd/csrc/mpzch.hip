@@ -528,16 +528,25 @@ mpzch_status_t launch_allocate_chunk(const Params &p, int grid, int num_cus, hip
     return MPZCH_OK;
 }
 
-// Calls whose first looks go before the later ones (k_discover_chunk): more than three workgroups per compute unit, all of
-// them resident with room to spare (records need more registers: up to five; those beyond start when others end, and come last
-// anyway), windows of up to 32 slots.  Whole steps without / with, 60 M slots, us, in this order TTL at 0.7 with windows of 16, at 0.95
-// of 32, LRU at 0.95 of 32, at 0.9 of 8.  Two tensors: 200 K positions 32.9 / 32.8, 34.5 / 33.7, 39.6 / 38.9, 33.3 / 32.7; 400 K 52.8 /
-// 51.8, 55.7 / 54.1, 65.1 / 62.1, 53.3 / 51.9.  Records: 150 K 27.1 / 27.4, 28.4 / 28.4, 39.1 / 39.1 and, of 16, LRU, 200 K 31.7 / 31.6, 33.6 /
-// 33.7, 41.6 / 40.7, 32.6 / 32.7; 250 K 36.0 / 35.7, 38.4 / 38.2, 46.8 / 45.3, 37.4 / 36.8; 400 K 51.1 / 49.5, 53.3 / 55.4, 65.4 / 67.5, 51.1 /
-// 51.0.  Windows of 64: 300 K, LRU, 71.4 / 72.0, 12 loads of 262 144 ids 733 / 738.
-constexpr bool even_looks(int64_t groups, int num_cus, bool records, int32_t P)
+// Calls whose first looks go before the later ones (k_discover_chunk): windows of up to 32 slots, more than three workgroups per
+// compute unit, and no more than leave the even end something to give.  In a table that the memory-side cache holds looks are
+// short: up to four.  Beyond the cache five, of records, which need more registers, four; under the LRU policy, whose full windows make
+// long chains of looks, six and five.  Whole steps without / with, us, of 200 K 230 K 262 144 300 007 400 K positions, each table as two
+// tensors and as records:
+//   150 M slots, TTL, 70 % load, of 16   34.9/34.2 38.5/37.7 40.2/39.7 44.6/44.9 55.5/57.3   34.2/33.8 36.6/36.7 39.7/40.5 43.3/44.8 55.0/58.9
+//   60 M slots, TTL, 95 %, of 32         48.3/47.6 54.2/52.9 59.4/58.8 69.7/72.1 96.1/103.8  51.5/50.6 55.8/54.5 61.7/61.1 70.3/70.0 93.5/97.1
+//   60 M slots, LRU, 95 %, of 32         34.6/32.9 37.3/36.2 38.8/36.7 42.9/41.8 52.7/51.5   35.1/34.2 37.2/37.0 41.0/40.0 45.6/44.2 53.9/54.6
+//   20 M slots, TTL, 95 %, of 32         58.3/60.0 65.6/67.7 72.9/78.4 83.7/92.2 120/132     (records: beyond the cache)
+//   20 M slots, LRU, 95 %, of 32         32.7/31.9 35.5/34.4 36.9/36.1 41.1/40.9 49.5/50.3
+// and of 210 K 262 144 300 007 400 K 520 K, tables of 200 (beyond the cache), 50 and 16 (in it) slots a position:
+//   200, TTL, 95 %, of 32                37.1/35.5 40.3/38.3 45.2/43.8 56.6/55.3 68.6/68.9   37.8/37.4 41.9/41.5 46.6/46.5 58.8/60.2 71.2/74.5
+//   50, LRU, full, of 32                 35.4/34.7 40.5/40.9 44.1/44.5 57.8/63.0 71.8/79.9   41.2/40.8 46.6/47.4 52.8/55.7 63.1/65.8 77.5/78.8
+//   16, LRU, full, of 16                 31.2/30.6 34.6/34.6 38.2/38.7 44.7/45.5 52.7/54.4   33.5/33.0 37.4/37.3 42.3/42.5 50.5/50.7 60.7/62.1
+constexpr bool even_looks(int64_t groups, int num_cus, const TableDesc &t)
 {
-    return P <= 32 && groups > 3 * (int64_t)num_cus && groups <= (records ? 5 : 8) * (int64_t)num_cus;
+    const bool cached = (t.N << (3 + t.sh)) <= kCachedTableBytes;
+    const int most = cached ? 4 : 5 - (t.sh ? 1 : 0) + (t.evict == 2 ? 1 : 0);
+    return t.P <= 32 && groups > 3 * (int64_t)num_cus && groups <= (int64_t)most * num_cus;
 }
 
 // One chunk per wavefront (mpzch_chunk_kernels.hpp): grid = workgroups of 256 positions.
@@ -546,7 +555,7 @@ mpzch_status_t launch_remap_chunks(Timing &tm, const Params &p, int32_t max_p_lr
     const bool rec = p.t0.sh != 0;
     if (!tm.begin(KDiscover, s)) return MPZCH_ERR_HIP;
     if (window_shift(p.t0.P) == 1 && 2 * p.n <= kShortBlocks) TRY((launch_discover_chunk<1, false, true>(p, grid, s)));
-    else if (even_looks(grid, num_cus, rec, p.t0.P)) TRY((launch_discover_chunk<0, true, false>(p, grid, s)));
+    else if (even_looks(grid, num_cus, p.t0)) TRY((launch_discover_chunk<0, true, false>(p, grid, s)));
     else if (overlap_insert(grid, num_cus, rec)) TRY((launch_discover_chunk<0, false, true>(p, grid, s)));
     else TRY((launch_discover_chunk<0, false, false>(p, grid, s)));
     if (!tm.end(s) || !tm.begin(KAllocate, s)) return MPZCH_ERR_HIP;

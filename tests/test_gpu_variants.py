@@ -165,9 +165,9 @@ def test_batches_around_the_largest_one_chunk_call(n):
     t.close()
 
 
-# ---- one-chunk calls whose first looks go before the later ones: on both sides of each line
+# ---- one-chunk calls whose first looks go before the later ones, in tables that the memory-side cache holds: on both sides of each line
 @pytest.mark.parametrize("evict", [True, "lru"])
-@pytest.mark.parametrize("groups,layout", [(3, "separate"), (3, "records"), (5, "records")])
+@pytest.mark.parametrize("groups,layout", [(3, "separate"), (4, "separate"), (3, "records"), (4, "records"), (5, "records")])
 def test_calls_around_the_lines_of_even_looks(groups, layout, evict):
     """Crowded windows, so that most ids take several looks; n at the line and one position beyond it."""
     rng = rng_for(917)
@@ -176,6 +176,37 @@ def test_calls_around_the_lines_of_even_looks(groups, layout, evict):
     t = Pair(slots, 29, 1, evict, 47, layout=layout)
     for step, more in enumerate([0, 1, 0, 1]):
         t.step(rng.integers(0, 2 * slots, size=n + more), step)
+    t.close()
+
+
+def ids_with_home(rng, count, lo, hi, num_slots, seed):
+    """Distinct ids >= 0 whose home slots, by the hash of the library, are spread over [lo, hi): the hash undone."""
+    want = np.empty(0, dtype=np.int64)
+    while want.size < count:
+        home = rng.integers(lo, hi, size=3 * count).astype(np.float64) + rng.random(3 * count) * 0.9 + 0.05
+        x = (home / num_slots * 2.0 ** 64).astype(np.uint64)
+        unxor = lambda x, s: x ^ (x >> np.uint64(s)) ^ (x >> np.uint64(2 * s))
+        x = unxor(x, 31) * np.uint64(pow(0x94D049BB133111EB, -1, 1 << 64))
+        x = unxor(x, 27) * np.uint64(pow(0xBF58476D1CE4E5B9, -1, 1 << 64))
+        x = ((unxor(x, 30) - np.uint64(0x9E3779B97F4A7C15)) ^ np.uint64(seed)).view(np.int64)
+        want = np.unique(np.concatenate([want, x[x >= 0]]))
+    want = rng.permutation(want)[:count]
+    assert all(lo <= oracle.home(int(i), seed, num_slots) < hi for i in want[:100])
+    return want
+
+
+# ---- the same in tables that the cache does not hold
+@pytest.mark.parametrize("groups,layout,evict", [(3, "separate", True), (5, "separate", "expiry"), (6, "separate", "lru"),
+                                                 (3, "records", "lru"), (4, "records", True), (5, "records", "lru")])
+def test_calls_around_the_lines_of_even_looks_beyond_the_cache(groups, layout, evict):
+    """Ids whose home slots lie in a small part of the table, so that its windows are crowded and most ids take several looks."""
+    rng = rng_for(931)
+    n = groups * torch.cuda.get_device_properties(0).multi_processor_count * 256
+    slots = 34_000_003 if layout == "separate" else 17_000_003
+    pool = ids_with_home(rng, n, 1_000, 1_000 + n // 2, slots, 59)
+    t = Pair(slots, 29, 1, evict, 59, layout=layout)
+    for step, more in enumerate([0, 1, 0, 1]):
+        t.step(rng.choice(pool, size=n + more), step, check_state=step == 3)
     t.close()
 
 
