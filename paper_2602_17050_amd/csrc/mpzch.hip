@@ -326,17 +326,22 @@ Windows longest(Windows a, Windows b) { return {a.lru > b.lru ? a.lru : b.lru, a
 // early.  It looks from the home slot on, so every look of 8 slots of records is two lines, where k_discover_tables_records, whose
 // first look is an aligned block, goes on with one each: long searches cost it more than the round trip that it saves, and the more
 // so the more wavefronts share the memory.  How long they are the windows tell: an absent id's search ends at an empty slot, and LRU tables
-// have none once they are full.  26 tables at 95 % load or full, Pass 1 of this / of the other kernels, by workgroups per compute
-// unit (1, 2, 3, 4, 6, 8).  Records, LRU, windows of 32: 0.69 0.82 0.87 0.93 0.92 1.00, of 64: 0.79 0.82 0.93 1.03 1.03 1.12, of 256: 0.89 0.93
-// 1.00 1.16 1.11 1.21; TTL, of 128: 0.81 0.88 0.86 0.91 0.95 0.99, of 256: 0.81 0.85 0.86 0.92 0.95 1.03, of 512: 0.76 0.82 0.95 0.97 0.98
-// 1.05.  Two tensors (8 slots are half a line), LRU, of 100: 0.79 0.79 0.82 0.83 0.90 0.99, of 256: 0.87 0.90 0.90 0.96 0.96 1.05; TTL, of
-// 512: 0.77 0.81 0.95 0.93 0.89 0.91.  Windows of 1 000, whole steps of 1.6 workgroups 0.95 to 1.03, of 4 1.04 to 1.08.
+// have none once they are full.  26 tables, Pass 1 of this over that of the other kernels, by workgroups per compute unit
+// (1, 2, 3, 4, 6, 8); TTL at 95 % load, LRU full, 4 slots a value, in brackets 8:
+//   records      LRU, of 32     0.69 0.82 0.87 0.93 0.92 1.00       of 64   0.79 0.82 0.93 1.03 1.03 1.12
+//                of 110       (0.83 0.84 1.03 1.12 1.15 1.18)       of 520 (0.93 0.98 1.10 1.20 1.18 1.26)
+//                TTL, of 128    0.81 0.88 0.86 0.91 0.95 0.99       of 256  0.81 0.85 0.86 0.92 0.95 1.03
+//                of 520       (0.77 0.81 0.96 1.00 1.02 1.05)       of 1 000, whole steps (0.86 0.95 0.90 0.99 1.00 1.03)
+//   two tensors  LRU, of 100    0.79 0.79 0.82 0.83 0.90 0.99       of 200 (0.83 0.86 0.86 1.02 1.02 1.15)
+//   (8 slots are of 520       (0.88 0.94 0.94 1.07 1.05 1.17)
+//   half a line) TTL, of 520  (0.74 0.81 0.96 0.97 0.94 0.94)       of 1 000, whole steps (0.86 0.96 0.88 0.95 0.90 0.95)
+// (Eviction off counts as the others: its tables are full only when they are too small for their ids, and then windows of 520 take whole
+// steps 0.85 0.93 1.11 1.15 1.15 1.17 over records, 0.86 0.86 0.95 1.12 1.05 1.12 over two tensors; half full they gain like the others.)
 constexpr bool tables_by_chunk(int64_t groups, int num_cus, bool records, Windows w)
 {
     int per_cu = 8;
-    if (records && w.lru > 32) per_cu = 3;
-    else if (w.lru > 100 || (records && w.other > 128)) per_cu = 6;
-    if (w.other > 512 || w.lru > 512) per_cu = 2;
+    if (records) per_cu = w.lru > 64 ? 2 : w.lru > 32 ? 3 : w.other > 128 ? 6 : 8;
+    else if (w.lru > 100) per_cu = w.lru > 256 ? 3 : 6;
     return groups <= (int64_t)per_cu * num_cus;
 }
 

@@ -616,8 +616,8 @@ def test_groups_around_the_line_of_one_chunk(chunks, more, records):
 # ---- groups on both sides of the lines that their longest windows draw for the same kernel (searches that go on beyond its widest
 # look, in full tables)
 @pytest.mark.parametrize("more", [0, 1])
-@pytest.mark.parametrize("chunks,policy,probe,records", [(3, "lru", 33, range(3)), (6, True, 129, range(3)), (6, "lru", 101, (1,)),
-                                                         (2, False, 513, range(3)), (2, "lru", 600, ())])
+@pytest.mark.parametrize("chunks,policy,probe,records", [(3, "lru", 33, range(3)), (2, "lru", 65, range(3)), (6, True, 129, range(3)), (6, "lru", 101, (1,)),
+                                                         (6, False, 513, range(3)), (3, "lru", 600, ())])
 def test_groups_around_the_lines_of_long_windows(chunks, policy, probe, records, more):
     from test_gpu_jagged import JaggedPair
     rng = rng_for(929)
