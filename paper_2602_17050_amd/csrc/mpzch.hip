@@ -574,6 +574,15 @@ mpzch_status_t launch_remap_chunks(Timing &tm, const Params &p, int32_t max_p_lr
     return MPZCH_OK;
 }
 
+// Where the first try of the scratch set is made (set_insert), as a shift.  Calls, everywhere / front half / quarter / eighth, us: 41.6 M
+// values over 26 tables 1 282 / 1 272 / 1 259 / 1 250, 22 M 645 / 639 / 639, 11 M 364.5 / 364.1 / 363.7, 5.6 M 230.0 / 230.3 / 230.3, 2.8 M
+// 142.8 / 143.2 / 143.9, 1.4 M 92.0 / 92.8 / 93.5 (a set that the caches hold: there the second try is what it costs).  One table, a
+// tenth of the ids new: 4 M positions on 1 B slots 295 / 291 / 288 / 287, 2.4 M under LRU 281 / 278 / 277 / 277, 2 M on 500 M 173.0 / 171.8 /
+// 171.6 / 171.6, 1.4 M 121.7 / 122.0 / 121.7 / 121.9.  All positions new: 1 M 218 / 207 / 219 / 235, 4 M 938 / 893 / 932 / 981, 16 M
+// 3 792 / 3 599 / 3 711 / 3 935, nine tenths of 26 x 1.6 M 12 552 / 12 430 / 12 498 / 12 734: first tries meet, and of the parts that gain
+// otherwise the quarter is the smallest that costs these nothing.
+constexpr int front_shift(int64_t n, bool group) { return n >= (group ? (int64_t)1 << 23 : (int64_t)1 << 21) ? 2 : 0; }
+
 mpzch_status_t launch_remap(Scratch &sc, Timing &tm, Params p, Windows windows, hipStream_t s)
 {
     p.list = sc.list;
@@ -602,6 +611,7 @@ mpzch_status_t launch_remap(Scratch &sc, Timing &tm, Params p, Windows windows, 
     const int g_disc = grid_for(p.n, kBlock, sc.num_cus, train_blocks_per_cu(p.n));
     p.num_segs = g_disc * kWavesPerBlock;
     p.seg_chunks = (int32_t)((num_chunks + p.num_segs - 1) / p.num_segs);
+    p.front_shift = front_shift(p.n, p.num_tables > 1);
     // the other kernels walk the segments' miss lists, one segment per wavefront pass.  (Two workgroups of 16 wavefronts
     // per compute unit.)
     const int g_grp = grid_for((int64_t)p.num_segs, kFinalizeWaves, sc.num_cus, 2);

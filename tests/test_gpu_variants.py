@@ -664,3 +664,36 @@ def test_calls_around_the_lines_of_overlapped_inserts(groups, layout, evict):
         ids[: n // 8] = rng.integers(4 * n, 4 * n + 50, size=n // 8) + 100 * step
         t.step(ids, 2 * step, ttls=rng.integers(0, 5, size=n + more).astype(np.int32) if evict == "expiry" else None)
     t.close()
+
+
+# ---- the two parts of a feature's region of the scratch set (long calls): features of so few positions that the front part has no entry,
+# one or two, each all new, with copies and without; in the last one nearly all positions are new, so that both parts fill up
+@pytest.mark.parametrize("layout", ["separate", "records"])
+def test_parts_of_the_scratch_set_in_groups(layout):
+    from test_gpu_jagged import JaggedPair
+    rng = rng_for(931)
+    counts = np.array([1, 2, 3, 4, 5, 8, 9, 17, 1 << 23])
+    specs = [wl.TableSpec(40, 8, 1, "lru" if f == 4 else True, 130 + f) for f in range(8)] + [wl.TableSpec(2_000_003, 8, 1, True, 139)]
+    jp = JaggedPair(specs, range(9) if layout == "records" else ())
+    offsets = np.concatenate([[0], np.cumsum(counts)]).astype(np.int64)
+    for step, distinct in ((0, 3), (3, 1 << 40)):
+        vals = rng.integers(0, distinct, size=counts.sum()) + step * distinct
+        vals[offsets[8]:] = rng.integers(0, 1 << 40, size=counts[8])
+        vals[offsets[8] + 5:: 3] = vals[offsets[8]: -5: 3]
+        jp.step(vals, offsets, step)
+    jp.check_state()
+    jp.close()
+
+
+# ---- ... and of one table, on both sides of the line
+@pytest.mark.parametrize("layout", ["separate", "records"])
+@pytest.mark.parametrize("evict", [True, "lru"])
+@pytest.mark.parametrize("n", [(1 << 21) - 1, 1 << 21])
+def test_parts_of_the_scratch_set(n, evict, layout):
+    rng = rng_for(933)
+    t = Pair(700_001, 8, 1, evict, 53, layout=layout)
+    for step in (0, 3):
+        ids = rng.integers(0, 1 << 40, size=n)
+        ids[1000::2] = ids[:-1000:2]
+        t.step(ids, step)
+    t.close()
