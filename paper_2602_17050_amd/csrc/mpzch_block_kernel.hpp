@@ -143,14 +143,13 @@ __global__ __launch_bounds__(kOneBlock) void k_remap_block(Params p)
         const uint64_t am = __ballot(cl.active);
         if (!am) break;
         const ClaimStage st = claim_blocks<REC>(d, cl, am, blocks_shift(uniform32(__popcll(am)), d.P), bound, false, s.code[w], s.req[w]);
-        if (cl.active)
-            claim_walk(d, cl, st, s.code[w], s.req[w], claim_in_map,
-                       [&](uint32_t who, int32_t round, int64_t at, int64_t old) {
-                           atomicMax(&s.place[who], (uint32_t)round + 1u);
-                           outcome = old == -1 ? 1u : old >= 0 ? 2u : 0u;
-                           claimed = at;
-                       },
-                       [&](uint32_t who) { atomicMax(&s.place[who], kPlaceNone); });
+        claim_walk<32>(d, cl, st, s.code[w], s.req[w], claim_in_map,
+                   [&](uint32_t who, int32_t round, int64_t at, int64_t old) {
+                       atomicMax(&s.place[who], (uint32_t)round + 1u);
+                       outcome = old == -1 ? 1u : old >= 0 ? 2u : 0u;
+                       claimed = at;
+                   },
+                   [&](uint32_t who) { atomicMax(&s.place[who], kPlaceNone); });
         __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
     }
     const uint64_t em = __ballot(outcome == 2u);

@@ -322,7 +322,7 @@ __global__ __launch_bounds__(kBlock, 4) void k_allocate_chunk(Params p)
     c.q = (int32_t)start;
     const int32_t bound = expiry_bound(d, p.step);
     const bool aligned = (d.N << (3 + d.sh)) > kCachedTableBytes;
-    bool inserted = false, evicted = false;
+    int64_t was = (int64_t)kTagBase;                // what the slot of the lane's last claim held
     int64_t slot = 0;
     uint32_t own = 0;
     for (bool later = false;; later = true) {
@@ -331,24 +331,22 @@ __global__ __launch_bounds__(kBlock, 4) void k_allocate_chunk(Params p)
         const ClaimStage st = claim_blocks<REC>(d, c, am, later || !aligned ? blocks_shift(uniform32(__popcll(am)), d.P) : 0, bound,
                                                 aligned && !later, s_code[w], s_req[w]);
         if (!later) c.active = c.active && first == (uint32_t)pos;      // else: a later copy of the id
-        if (c.active)
-            claim_walk(d, c, st, s_code[w], s_req[w], claim_in_table,
-                       [&](uint32_t who, int32_t round, int64_t at, int64_t old) {
-                           if (who == (uint32_t)pos) own = (uint32_t)round + 1u;
-                           else note_place(p, who, (uint32_t)round + 1u);
-                           inserted = old == -1;     // (a lane's last claim: only it meets a slot not claimed before)
-                           evicted = old >= 0;
-                           slot = at;
-                       },
-                       // (also for the lane's own: its chain may come back to it, in a table hardly longer than a window)
-                       [&](uint32_t who) {
-                           if (who == (uint32_t)pos) own = kPlaceNone;
-                           else note_place(p, who, kPlaceNone);
-                       });
+        claim_walk<16>(d, c, st, s_code[w], s_req[w], claim_in_table,
+                   [&](uint32_t who, int32_t round, int64_t at, int64_t old) {
+                       if (who == (uint32_t)pos) own = (uint32_t)round + 1u;
+                       else note_place(p, who, (uint32_t)round + 1u);
+                       was = old;
+                       slot = at;
+                   },
+                   // (also for the lane's own: its chain may come back to it, in a table hardly longer than a window)
+                   [&](uint32_t who) {
+                       if (who == (uint32_t)pos) own = kPlaceNone;
+                       else note_place(p, who, kPlaceNone);
+                   });
         __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");   // s_code and s_req are written again
     }
     if (in) p.list[pos] = !have ? kNoEntry : first == (uint32_t)pos ? kOwnPlace | own : first;
-    leave_outcomes<kWavesPerBlock>(p, have && first == (uint32_t)pos, inserted, evicted, slot, s_red);
+    leave_outcomes<kWavesPerBlock>(p, have && first == (uint32_t)pos, was == -1, was >= 0, slot, s_red);
 }
 
 // The claims under the LRU policy (max_probe <= 8 T <= 64).  The workgroup first lists its claimants, so that its groups of

@@ -1744,48 +1744,85 @@ __device__ __forceinline__ ClaimStage claim_blocks(const Tab &d, const Claimant 
 // with, if c.active.
 // claim(address of the identity, tag, whether the slot held an id when the call began) makes the claim and returns what the
 // slot held before.
-template <typename Claim, typename Placed, typename Lost>
+//
+// Reached by all lanes, who walk in step: one claim each, whichever word of the stage they are at, and what becomes of a lane is a
+// number that it carries.  A claim is a round trip and what lies between two of them, which was a third of it: a loop per
+// word and lane that ended in five places kept its lanes and their outcomes in masks, some 60 scalar instructions each time around, and
+// those that had come to the next word waited for the others.  And where windows are longer than LEAVE slots (0: never) the walk ends
+// when, after its first claims, more lanes wait for the next stage than walk: those go on there too, with what others have claimed
+// meanwhile.  Before / in step / and left early, us: 12 calls of 262 144 new ids 722 / 704 / 686, two of 126 000 and 83 000 into a table of
+// 238 000 slots, windows of 256, 163 / 149 / 137, four of 30 000 into 120 000, of 512, 262 / 251 / 202; 51 steps of 65 536 positions 907 /
+// 881, 12 of 20 011 309 / 298, 12 of 50 000 on 100 000 slots of records, windows of 32, 411 / 394 / 378; one workgroup, 12 steps of 1 024
+// 147 / 141.  (The lists of long calls gain nothing by either, crowded ones lose by the second: 600 000 positions on 3 M slots 167.0 /
+// 165.3 / 169.7.)
+template <int LEAVE, typename Claim, typename Placed, typename Lost>
 __device__ __forceinline__ void claim_walk(const Tab &d, Claimant &c, const ClaimStage &st, const uint8_t *s_code,
                                            const ClaimReq *s_req, Claim claim, Placed placed, Lost lost)
 {
     constexpr int G = kAllocG;
     constexpr uint64_t kOnes = 0x0101010101010101ull;
-    const uint8_t *const mine = s_code + (st.at << (st.m + 3));
-    const uint64_t where = s_req[st.at].where;
-    bool carried = false;
+    enum : uint32_t { kDone, kWalks, kWaits, kLost };                // kWaits: for the next stage
+    uint32_t state = c.active ? kWalks : kDone;
+    const int at = c.active ? st.at : 0;
+    const uint8_t *const mine = s_code + (at << (st.m + 3));
+    const uint64_t where = s_req[at].where;
+    uint32_t carried = 0;                                            // all ones: of a displaced claimant, claimed slots are tried
     int32_t round0 = c.q - st.skip;                                  // the round that the first slot read is for the claimant
-    int skip = st.skip;
-    for (int j = 0; j < (1 << st.m); ++j, skip -= G) {
-        const uint64_t word = reinterpret_cast<const uint64_t *>(mine)[j];
-        uint64_t x = (carried ? word | (word >> 2) : word) & kOnes;
-        if (skip > 0) x = skip < G ? x & (~0ull << (8 * skip)) : 0;
-        while (x) {
-            const int bit = __ffsll((unsigned long long)x) - 1;
-            const int k = G * j + (bit >> 3);
-            x &= x - 1;
-            const int32_t round = round0 + k;
-            if (round >= d.P) break;
-            const uint32_t occ = (uint32_t)(word >> (bit + 1)) & 1u;
-            const int64_t mine_tag = make_tag((uint32_t)round, c.pos, occ);
-            const int64_t old = claim(where + ((uint64_t)k << (3 + d.sh)), mine_tag, occ);
-            if (is_tag(old) && old < mine_tag) continue;             // a better claim got there first
-            const int64_t slot = wrap(c.home + round, d.N);
-            placed(c.pos, round, slot, old);
-            if (!is_tag(old)) { c.active = false; return; }
+    int j = 0, skip = st.skip;
+    bool claims = false;                                             // (nobody leaves before the stage's first claims)
+    uint64_t word = reinterpret_cast<const uint64_t *>(mine)[0], x = word & kOnes;
+    if (skip > 0) x = skip < G ? x & (~0ull << (8 * skip)) : 0;
+    for (;;) {
+        if (__any(state == kWalks && x == 0)) {
+            while (state == kWalks && x == 0) {
+                ++j;
+                if (j == (1 << st.m) || round0 + G * j >= d.P) {
+                    c.q = round0 + st.width;                         // (beyond the window's end if the second is why)
+                    state = c.q >= d.P ? kLost : kWaits;
+                } else {
+                    skip -= G;
+                    word = reinterpret_cast<const uint64_t *>(mine)[j];
+                    x = (word | (word >> 2 & ((uint64_t)carried << 32 | carried))) & kOnes;
+                    if (skip > 0) x = skip < G ? x & (~0ull << (8 * skip)) : 0;
+                }
+            }
+        }
+        const uint64_t walking = __ballot(state == kWalks);
+        if (!walking) break;
+        if (LEAVE != 0 && d.P > LEAVE && claims) {
+            if (__popcll(__ballot(state == kWaits)) > __popcll(walking)) break;
+        }
+        claims = true;
+        const int bit = __ffsll((unsigned long long)x) - 1;
+        const int k = G * j + (bit >> 3);
+        const int32_t round = round0 + k;
+        const uint32_t occ = (uint32_t)(word >> ((bit + 1) & 63)) & 1u;
+        const int64_t tag = make_tag((uint32_t)round, c.pos, occ);
+        const bool tries = state == kWalks && round < d.P;
+        int64_t old = 0;
+        if (tries) old = claim(where + ((uint32_t)k << (3 + d.sh)), tag, occ);
+        const bool stands = tries && old >= tag;                     // (else a better claim got there first)
+        const bool displaces = stands && is_tag(old);
+        const int64_t slot = wrap(c.home + round, d.N);
+        if (stands) placed(c.pos, round, slot, old);
+        x &= x - 1;
+        if (state == kWalks && !tries) state = kLost;
+        if (stands && !displaces) state = kDone;
+        if (displaces) {
             c.pos = tag_pos(old);
             c.home = slot - (int64_t)tag_round(old);
             if (c.home < 0) c.home += d.N;
             round0 = (int32_t)tag_round(old) - k;
-            carried = true;
+            carried = ~0u;
             x = ((word | (word >> 2)) & kOnes) & ~((1ull << bit) | ((1ull << bit) - 1ull));
         }
-        if (round0 + G * (j + 1) >= d.P) break;
     }
-    c.q = round0 + st.width;
-    if (c.q >= d.P) {
-        c.active = false;
-        lost(c.pos);
+    if (state == kWalks) {
+        c.q = round0 + G * j + ((__ffsll((unsigned long long)x) - 1) >> 3);
+        if (c.q >= d.P) state = kLost;
     }
+    if (state == kLost) lost(c.pos);
+    c.active = state == kWalks || state == kWaits;
 }
 
 // One wavefront serves the segments vblock, vblock + vgrid, ...; s_code and s_req are its own areas of LDS.  REC: every
@@ -1870,19 +1907,18 @@ __device__ __forceinline__ void allocate_body(const Params &p, int64_t vblock, i
                     // what nearly every claimant needs at first)
                     const ClaimStage st = claim_blocks<REC>(d, c, am, later ? blocks_shift(uniform32(__popcll(am)), d.P) : 0, bound,
                                                             aligned && !later, s_code, s_req);
-                    if (c.active)
-                        claim_walk(d, c, st, s_code, s_req, claim_in_table,
-                                   [&](uint32_t who, int32_t round, int64_t, int64_t old) {
-                                       const uint32_t at = round < (int32_t)kHintUnknown ? (uint32_t)round : kHintUnknown;
-                                       if (who == pos) {
-                                           hint = at | ((is_tag(old) ? tag_occ(old) != 0 : old >= 0) ? kAgentOcc : 0u);
-                                       } else {
-                                           p.hint[who] = (uint8_t)at;
-                                       }
-                                       hint |= outcome_of(old);
-                                       if (is_tag(old)) p.note[tag_pos(old)] = 1;
-                                   },
-                                   [](uint32_t) {});
+                    claim_walk<0>(d, c, st, s_code, s_req, claim_in_table,
+                               [&](uint32_t who, int32_t round, int64_t, int64_t old) {
+                                   const uint32_t at = round < (int32_t)kHintUnknown ? (uint32_t)round : kHintUnknown;
+                                   if (who == pos) {
+                                       hint = at | ((is_tag(old) ? tag_occ(old) != 0 : old >= 0) ? kAgentOcc : 0u);
+                                   } else {
+                                       p.hint[who] = (uint8_t)at;
+                                   }
+                                   hint |= outcome_of(old);
+                                   if (is_tag(old)) p.note[tag_pos(old)] = 1;
+                               },
+                               [](uint32_t) {});
                     __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");   // s_code and s_req are written again
                 }
                 count_outcomes(outcomes, agent, hint, MULTI ? of_table : 0);
@@ -1898,7 +1934,7 @@ __device__ __forceinline__ void allocate_body(const Params &p, int64_t vblock, i
 }
 
 template <bool MULTI, bool REC>
-__global__ __launch_bounds__(kWave, MULTI ? 5 : 7) void k_allocate(Params p)
+__global__ __launch_bounds__(kWave, MULTI ? 5 : REC ? 7 : 6) void k_allocate(Params p)
 {
     __shared__ __attribute__((aligned(16))) uint8_t s_code[kWave * kAllocG];
     __shared__ ClaimReq s_req[kWave];

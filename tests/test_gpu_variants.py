@@ -141,6 +141,24 @@ def test_crowded_windows(slots, probe, layout, evict):
     t.close()
 
 
+# ---- the walk of claims in step: lanes leave a stage before its window is through only in windows of more than 16 slots (one chunk per
+# wavefront) or 32 (one workgroup), never in the lists of long calls; windows a slot to either side of those lines, of less than a
+# stage, of several, and longer than the table, with far more ids than slots, so that lanes end in every way in one wavefront
+@pytest.mark.parametrize("layout", ["separate", "records"])
+@pytest.mark.parametrize("n", [900, 5_000, 524_289])
+@pytest.mark.parametrize("probe", [16, 17, 32, 33, 65, 200])
+def test_walks_left_early(n, probe, layout):
+    rng = rng_for(990 + probe + n)
+    for slots, evict in [(7, True), (n // 6, True), (n // 6, False), (n // 2, "expiry")]:
+        if n > 500_000 and slots == 7:
+            continue
+        t = Pair(slots, probe, 1, evict, 5, layout=layout)
+        for step in range(3):
+            t.step(rng.integers(0, 1 << 60, size=n), 2 * step)
+        t.check_state()
+        t.close()
+
+
 # ---- one workgroup up to 1 024 positions, one chunk per wavefront up to 256 x 8 workgroups of 256 positions (256 compute units); lists beyond that
 @pytest.mark.parametrize("layout", ["separate", "records"])
 @pytest.mark.parametrize("evict,fused", [(True, True), (True, False), ("expiry", False), (False, False)])
