@@ -402,7 +402,7 @@ __global__ __launch_bounds__(THREADS, T == 8 || THREADS > kBlock ? 4 : 6) void k
         const bool more = i + GROUPS < count;
         const int64_t home2 = more ? s_home[i + GROUPS] : 0;
         const LruSlots<T> x2 = load_lru_slots<T, REC>(d, more, home2);
-        claim_group_lru<T, REC>(p, d, i < count, i < count ? s_pos[i] : 0u, home, x,
+        claim_group_lru<T, REC, true>(p, d, i < count, i < count ? s_pos[i] : 0u, home, x,
                                 [&](uint32_t who, int32_t choice, int32_t round, int64_t slot, int64_t old) {
                                     if (lane % G != 0) return;
                                     const uint32_t place = (uint32_t)choice << 16 | (uint32_t)(round + 1);

@@ -248,6 +248,16 @@ __device__ __forceinline__ uint32_t tag_pos(int64_t v) { return (uint32_t)(((uin
 __device__ __forceinline__ uint32_t tag_round(int64_t v) { return (uint32_t)(((uint64_t)v & ~kTagBase) >> kTagRoundShift); }
 __device__ __forceinline__ uint32_t tag_occ(int64_t v) { return (uint32_t)((uint64_t)v & 1u); }
 
+// Under the LRU policy claims rank by the number of the choice.  The round, which tells a displaced claimant's home slot, is kept
+// below the position (choices and rounds are below 1 024, positions below 2^30).
+__device__ __forceinline__ int64_t make_lru_tag(uint32_t choice, uint32_t pos, uint32_t round, uint32_t was_occupied)
+{
+    return (int64_t)(kTagBase | ((uint64_t)choice << 44) | ((uint64_t)pos << 12) | (round << 1 | was_occupied));
+}
+__device__ __forceinline__ uint32_t lru_tag_pos(int64_t v) { return (uint32_t)((uint64_t)v >> 12); }
+__device__ __forceinline__ uint32_t lru_tag_choice(int64_t v) { return (uint32_t)((uint64_t)v >> 44) & 0x7FFFFu; }
+__device__ __forceinline__ uint32_t lru_tag_round(int64_t v) { return (uint32_t)v >> 1 & 0x7FFu; }
+
 __device__ __forceinline__ int64_t shfl64(int64_t v, int src)
 {
     int lo = __shfl((int)(uint32_t)(uint64_t)v, src);
@@ -1948,7 +1958,7 @@ __global__ __launch_bounds__(kWave, MULTI ? 5 : REC ? 7 : 6) void k_allocate(Par
 // the current step.  Its preference list -- empty slots in probe order, then evictable slots
 // oldest first -- follows from the state at the start of allocation, which stays readable while
 // claims are in flight: a tag keeps the was-occupied bit and metadata is not written before
-// k_finalize.  The tag's round field carries the CHOICE number, so a slot ends with the claimant
+// k_finalize.  The tag ranks by the CHOICE number (make_lru_tag), so a slot ends with the claimant
 // of the lowest (choice, position).  A group of 8 lanes serves one claimant, lane r holding the slots of rounds r, 8 + r, ...
 // of its window (T of them, max_probe <= 8 T <= 64; longer ranges: claim_wave_lru_long), so a wavefront works on
 // 8 claimants at a time; a displaced claimant is carried on by the group that displaced it, from its next choice.
@@ -2026,9 +2036,16 @@ __device__ __forceinline__ uint64_t group_or(uint64_t x)
 // a mask that all lanes of the group hold, so its choices, and the first `choice` ones that a displaced claimant has behind
 // it, cost no exchange between lanes.  (Each choice drawn by three minima over the group, from the first one again for every
 // displaced claimant: 12 547 positions on 6 964 slots, windows of 32, 140 -> 99 us; calls of 300 007 on 60 M slots 11.15 -> 10.95.)
+//
+// A displaced claimant's home slot comes with its tag: by its id it was a round trip of the three that carry a claimant on.  SEEN: a slot that
+// was read with a better claim than the claimant's first choice would make is passed over, since claims only get better; the atomic
+// that it would lose is another round trip.  Before / home from the tag / and passed over, us: 12 steps under LRU of 684 positions 251.6 /
+// 247.0 / 245.7, of 5 000 on 20 000 slots, windows of 32, 373 / 361 / 358, of 20 011 on 12 000 609 / 588 / 558, of 12 000 on 8 000, of 64,
+// 1 049 / 1 024 / 889; where few are displaced the same to 0.4 %.  (Not in the lists of long calls, where few claims meet and windows of 64
+// have no registers left for it.)
 // The wavefront goes through the loops as one: a branch for each group cost windows of 8, which hardly need the classes, what
 // they gave (360 000 claimants 56.3 -> 53.9).
-template <int T, bool REC, typename Placed, typename Lost>
+template <int T, bool REC, bool SEEN, typename Placed, typename Lost>
 __device__ __forceinline__ void claim_group_lru(const Params &p, const Tab &d, bool active, uint32_t cpos, int64_t home,
                                                 LruSlots<T> x, Placed placed, Lost lost)
 {
@@ -2047,6 +2064,14 @@ __device__ __forceinline__ void claim_group_lru(const Params &p, const Tab &d, b
             if (in && occ && x.m[t] != p.step) evictable |= (Mask)1 << (kLruG * t);
         }
         Mask left = group_or(empties);               // of the present class: the slots that have not been drawn
+        Mask beaten = 0;                             // SEEN: the slots that were read with a better claim
+        if constexpr (SEEN) {
+            const int64_t best = make_lru_tag((uint32_t)choice, cpos, 0, 0);
+#pragma unroll
+            for (int t = 0; t < T; ++t)
+                if (is_tag(x.v[t]) && x.v[t] < best) beaten |= (Mask)1 << (kLruG * t + r);
+            if (__any(beaten != 0)) beaten = group_or(beaten);
+        }
         uint32_t class_occ = 0;                      // ... whether they held ids
         int32_t skip = choice;
         int64_t displaced = 0;
@@ -2054,8 +2079,16 @@ __device__ __forceinline__ void claim_group_lru(const Params &p, const Tab &d, b
         while (__any(trying)) {
             // on to the class of the present choice
             for (;;) {
-                const int32_t count = sizeof(Mask) == 4 ? __popc((uint32_t)left) : __popcll(left);
-                const bool used_up = trying && skip >= count;
+                int32_t count = sizeof(Mask) == 4 ? __popc((uint32_t)left) : __popcll(left);
+                bool used_up = trying && skip >= count;
+                if (SEEN && trying && !used_up) {
+                    for (; skip > 0; --skip) left &= left - 1;
+                    if (!(left & ~beaten)) {
+                        choice += sizeof(Mask) == 4 ? __popc((uint32_t)left) : __popcll(left);
+                        count = 0;
+                        used_up = true;
+                    }
+                }
                 if (!__any(used_up)) break;
                 // (metadata is the caller's: any value may be a time stamp, so a class is told by its members)
                 int32_t next = 0x7FFFFFFF;
@@ -2080,10 +2113,13 @@ __device__ __forceinline__ void claim_group_lru(const Params &p, const Tab &d, b
                 }
             }
             if (!trying) continue;
-            for (; skip > 0; --skip) left &= left - 1;
-            const int32_t round = __ffsll((unsigned long long)left) - 1;
-            left &= left - 1;
-            const int64_t mine = make_tag((uint32_t)choice, cpos, class_occ);
+            if (!SEEN)
+                for (; skip > 0; --skip) left &= left - 1;
+            const Mask open = left & ~beaten, below = (open & (0 - open)) - 1;
+            const int32_t round = __ffsll((unsigned long long)open) - 1;
+            if (SEEN) choice += sizeof(Mask) == 4 ? __popc((uint32_t)(left & below)) : __popcll(left & below);
+            left &= ~(below << 1 | 1);
+            const int64_t mine = make_lru_tag((uint32_t)choice, cpos, (uint32_t)round, class_occ);
             const int64_t s = wrap(home + round, d.N);
             int64_t old = 0;
             if (r == 0) old = __hip_atomic_fetch_min(id_at(d, s), mine, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
@@ -2093,14 +2129,16 @@ __device__ __forceinline__ void claim_group_lru(const Params &p, const Tab &d, b
             } else {
                 placed(cpos, choice, round, s, old);
                 displaced = is_tag(old) ? old : 0;
+                home = s;
                 trying = false;
             }
         }
         active = active && displaced != 0;
         if (active) {
-            cpos = tag_pos(displaced);                                   // same table: same slot
-            choice = (int32_t)tag_round(displaced) + 1;
-            home = home_slot(p.ids[cpos], d.seed, d.N);
+            cpos = lru_tag_pos(displaced);                               // same table: same slot
+            choice = (int32_t)lru_tag_choice(displaced) + 1;
+            home -= (int64_t)lru_tag_round(displaced);
+            if (home < 0) home += d.N;
         }
         if (__any(active)) x = load_lru_slots<T, REC>(d, active, home);
     }
@@ -2168,7 +2206,7 @@ __global__ __launch_bounds__(kWave, MULTI ? (T == 8 ? 3 : 4) : T == 8 ? 4 : T ==
                 if (MULTI && src2 >= 0) d2 = view(p.descs[f2]);
                 const LruSlots<T> x2 = load_lru_slots<T, REC>(d2, src2 >= 0, chome2);
                 uint32_t fr = kHintUnplaced;         // (and the outcome)
-                claim_group_lru<T, REC>(p, d, src >= 0, cpos, chome, x,
+                claim_group_lru<T, REC, false>(p, d, src >= 0, cpos, chome, x,
                                         [&](uint32_t who, int32_t, int32_t round, int64_t, int64_t old) {
                                             if (who == cpos) fr = (uint32_t)round;
                                             fr |= outcome_of(old);
@@ -2220,8 +2258,8 @@ __device__ __forceinline__ int32_t claim_wave_lru_long(const Params &p, const Ta
     const int C = (d.P + kWave - 1) / kWave;             // <= kLruLongSlots (checked when the table is created)
     int32_t first_round = -1;
     bool is_first = true;
+    int64_t home = home_slot(p.ids[cpos], d.seed, d.N);
     for (;;) {
-        const int64_t home = home_slot(p.ids[cpos], d.seed, d.N);
         uint32_t emp = 0, evi = 0;                        // bit c: the slot of round c * 64 + lane is empty / evictable
         int32_t m[kLruLongSlots];
 #pragma unroll
@@ -2281,7 +2319,7 @@ __device__ __forceinline__ int32_t claim_wave_lru_long(const Params &p, const Ta
             const int who = round % kWave;
             int64_t old = 0, mine = 0;
             if (lane == who) {
-                mine = make_tag((uint32_t)choice, cpos, occ);
+                mine = make_lru_tag((uint32_t)choice, cpos, (uint32_t)round, occ);
                 old = __hip_atomic_fetch_min(id_at(d, wrap(home + round, d.N)), mine, __ATOMIC_RELAXED,
                                              __HIP_MEMORY_SCOPE_AGENT);
             }
@@ -2292,11 +2330,13 @@ __device__ __forceinline__ int32_t claim_wave_lru_long(const Params &p, const Ta
             displaced = is_tag(old) ? old : 0;
             outcome = outcome_of(old);
             if (is_first) first_round = round;
+            home = wrap(home + round, d.N) - (int64_t)lru_tag_round(old);
+            if (home < 0) home += d.N;
         }
         is_first = false;
         if (!placed || !displaced) break;
-        cpos = tag_pos(displaced);                                       // same table: same slot
-        choice = (int32_t)tag_round(displaced) + 1;
+        cpos = lru_tag_pos(displaced);                                   // same table: same slot
+        choice = (int32_t)lru_tag_choice(displaced) + 1;
     }
     return first_round;
 }
@@ -2527,8 +2567,8 @@ __device__ __forceinline__ void finalize_body(const Params &p)
             int at = -1;
             uint32_t occ = 0;
             // does slot value v carry the claim of the id whose first occurrence is `fst`?
-            auto is_claim_of = [](int64_t v, uint32_t fst, int64_t cid) {
-                return is_tag(v) ? tag_pos(v) == fst : v == cid;
+            auto is_claim_of = [](int64_t v, uint32_t fst, int64_t cid, bool lru) {
+                return is_tag(v) ? (lru ? lru_tag_pos(v) : tag_pos(v)) == fst : v == cid;
             };
             bool search = false, sure = false;
             if (have) {
@@ -2555,7 +2595,7 @@ __device__ __forceinline__ void finalize_body(const Params &p)
                     occ = (word & kAgentOcc) ? 1u : 0u;
                 } else if (h < kHintUnknown) {
                     const int64_t v = *id_at(d, wrap(home + (int)h, d.N));
-                    if (is_claim_of(v, first, id)) { at = (int)h; occ = tag_occ(v); }
+                    if (is_claim_of(v, first, id, d.evict == 2)) { at = (int)h; occ = tag_occ(v); }
                 }
                 search = at < 0 && h != kHintUnplaced;
             }
@@ -2578,7 +2618,7 @@ __device__ __forceinline__ void finalize_body(const Params &p)
                     uint32_t o = 0;
                     if (round < dw.P) {
                         const int64_t v = *id_at(dw, wrap(chome + round, dw.N));
-                        mine = is_claim_of(v, cfirst, cid);
+                        mine = is_claim_of(v, cfirst, cid, dw.evict == 2);
                         o = tag_occ(v);
                     }
                     const uint64_t mb = __ballot(mine);

@@ -372,6 +372,26 @@ def test_lru_claims(slots, probe, layout):
     t.close()
 
 
+# displaced claimants whose home slots come from their tags (around the end of the table, in tables hardly longer than a window)
+# and slots that are passed over because they were read with a better claim: whole classes of them, in masks of 32 and 64 slots; one chunk
+# per wavefront, and lists
+@pytest.mark.parametrize("layout", ["separate", "records"])
+@pytest.mark.parametrize("probe", [7, 8, 9, 31, 32, 33, 63, 64])
+@pytest.mark.parametrize("slots,n", [(65, 300), (700, 1_500), (9_000, 12_000), (400_000, 524_289)])
+def test_lru_crowded(slots, n, probe, layout):
+    rng = rng_for(1_004 + slots + probe)
+    t = Pair(slots, probe, 0, "lru", 5, layout=layout)
+    for step in range(4):
+        ids = rng.integers(0, 1 << 60, size=n)
+        if n < 100_000:
+            at = rng.random(n) < 0.5
+            ids[at] = ids_at((slots - 3 + rng.integers(0, 9, size=int(at.sum()))) % slots, slots, 5, rng)   # homes around the end
+        t.step(ids, step + 1)
+        t.step(ids[: n // 3 + 1], step + 1)
+    t.check_state()
+    t.close()
+
+
 # ---- LRU claims by workgroups of 1 024, 512 and 256 threads: on both sides of each line, few claimants and mostly claimants
 @pytest.mark.parametrize("more", [0, 1])
 @pytest.mark.parametrize("groups,probe", [(1, 5), (1, 16), (1, 29), (1, 64), (2, 5), (2, 16), (2, 29), (2, 64), (5, 5), (5, 16)])
