@@ -509,12 +509,18 @@ mpzch_status_t run_remap(Scratch &sc, Timing &tm, const Params &p, Windows windo
     return st;
 }
 
-template <int SHIFT, bool EVEN, bool OVERLAP>
+template <int SHIFT, bool EVEN, bool OVERLAP, bool ALIGNED>
 mpzch_status_t launch_discover_chunk(const Params &p, int grid, hipStream_t s)
 {
-    if (p.t0.sh) TRY(launch(k_discover_chunk<true, SHIFT, EVEN, OVERLAP>, grid, kBlock << SHIFT, s, p));
-    else TRY(launch(k_discover_chunk<false, SHIFT, EVEN, OVERLAP>, grid, kBlock << SHIFT, s, p));
+    if (p.t0.sh) TRY(launch(k_discover_chunk<true, SHIFT, EVEN, OVERLAP, ALIGNED>, grid, kBlock << SHIFT, s, p));
+    else TRY(launch(k_discover_chunk<false, SHIFT, EVEN, OVERLAP, ALIGNED>, grid, kBlock << SHIFT, s, p));
     return MPZCH_OK;
+}
+template <bool EVEN, bool OVERLAP>
+mpzch_status_t launch_discover_chunk(const Params &p, int grid, bool aligned, hipStream_t s)
+{
+    if (aligned) return launch_discover_chunk<0, EVEN, OVERLAP, true>(p, grid, s);
+    return launch_discover_chunk<0, EVEN, OVERLAP, false>(p, grid, s);
 }
 
 // Calls of so many workgroups of 256 positions read the scratch set back (k_allocate_chunk says why).  Measured on 256 compute
@@ -554,15 +560,38 @@ constexpr bool even_looks(int64_t groups, int num_cus, const TableDesc &t)
     return t.P <= 32 && groups > 3 * (int64_t)num_cus && groups <= (int64_t)most * num_cus;
 }
 
+// Calls whose windows of 9 to 16 slots are read whole (SHIFT 1 of k_discover_chunk): up to one workgroup for two compute units.  Of records
+// that is three lines an id, where a first look reads one or two, and beyond it is their number that counts: 65 536 ids were 196 K lines,
+// 3.4 us of the kernel's 6.8.  Sessions of ten steps on six slots a position, whole windows / two looks, us: 2 000 positions of two tensors 177
+// / 183, of records 175 / 183, 9 000 188 / 191, 187 / 192, 20 000 203 / 205, 203 / 207, 40 000 227 / 226, 225 / 224, 65 000 285 / 276, 284 /
+// 273; six steps of 100 000 on 1 M slots 452 / 403, 444 / 395.
+constexpr bool whole_windows(int64_t groups, int num_cus, int32_t max_probe) { return window_shift(max_probe) == 1 && 2 * groups <= num_cus; }
+
+// One-chunk calls whose first look is at the aligned block that holds the home slot: one line an id, and a second look where the id is
+// not in its part of the window.  In tables beyond the memory-side cache all of them (see k_allocate).  Otherwise the 8 slots from the home slot
+// on, which are two lines of records and one and a half of two tensors, decide more of the ids, and only calls with enough
+// workgroups for the lines to count do better without: from one per compute unit on over records, from two and a half over two tensors.
+// From the home slot on / aligned, us: records, 51 steps of 65 536 positions, windows of 16, 883 / 860; sessions of eight steps on 1 M slots,
+// windows of 16, 48 000 positions 351 / 350, 66 000 367 / 366, 80 000 408 / 400, of 24 361 / 363, 376 / 378, 388 / 389, of 64 406 / 406, 425 /
+// 422, 434 / 433; of six, of 16, 200 000 515 / 502, of 32 453 / 443; new ids into 3 M slots, 262 144 a call 315 / 305, 200 000, of 64, 759 /
+// 733.  Two tensors, of 16, 131 000 482 / 482, new ids, 160 000 a call 357 / 353, 200 000 340 / 338, 262 144, of 64, 683 / 677.  (Windows of up to 8 slots, which a
+// look from the home slot on decides: 66 000 366 / 373, 131 000 452 / 456.)
+constexpr bool aligned_first(int64_t groups, int num_cus, const TableDesc &t)
+{
+    if ((t.N << (3 + t.sh)) > kCachedTableBytes) return true;
+    return t.P > 8 && 2 * groups >= (t.sh ? 2 : 5) * (int64_t)num_cus;
+}
+
 // One chunk per wavefront (mpzch_chunk_kernels.hpp): grid = workgroups of 256 positions.
 mpzch_status_t launch_remap_chunks(Timing &tm, const Params &p, int32_t max_p_lru, int grid, int num_cus, hipStream_t s)
 {
     const bool rec = p.t0.sh != 0;
+    const bool aligned = aligned_first(grid, num_cus, p.t0);
     if (!tm.begin(KDiscover, s)) return MPZCH_ERR_HIP;
-    if (window_shift(p.t0.P) == 1 && 2 * p.n <= kShortBlocks) TRY((launch_discover_chunk<1, false, true>(p, grid, s)));
-    else if (even_looks(grid, num_cus, p.t0)) TRY((launch_discover_chunk<0, true, false>(p, grid, s)));
-    else if (overlap_insert(grid, num_cus, rec)) TRY((launch_discover_chunk<0, false, true>(p, grid, s)));
-    else TRY((launch_discover_chunk<0, false, false>(p, grid, s)));
+    if (whole_windows(grid, num_cus, p.t0.P)) TRY((launch_discover_chunk<1, false, true, false>(p, grid, s)));
+    else if (even_looks(grid, num_cus, p.t0)) TRY((launch_discover_chunk<true, false>(p, grid, aligned, s)));
+    else if (overlap_insert(grid, num_cus, rec)) TRY((launch_discover_chunk<false, true>(p, grid, aligned, s)));
+    else TRY((launch_discover_chunk<false, false>(p, grid, aligned, s)));
     if (!tm.end(s) || !tm.begin(KAllocate, s)) return MPZCH_ERR_HIP;
     if (max_p_lru > 0 && rec) TRY(launch_allocate_lru_chunk<true>(max_p_lru, p, grid, num_cus, s));
     else if (max_p_lru > 0) TRY(launch_allocate_lru_chunk<false>(max_p_lru, p, grid, num_cus, s));

@@ -149,10 +149,13 @@ __device__ __forceinline__ uint32_t first_occurrence(const Params &p, uint32_t p
     return p.set_slot[ent & ~kEntered] & kChunkPosMask;
 }
 
-// SHIFT 1: a wavefront takes 32 positions, so that one pass holds the whole windows of up to 16 slots (see k_lookup_short;
-// while the call has no more than kShortBlocks blocks), and the workgroup's 256 positions have 512 threads.  65 536
-// positions per step, the 50-step pass 1 078 -> 1 056 us.  Longer windows gain nothing by it: what a look less saves, the
-// barriers of 1 024 threads and the copies of an id that no longer meet in one wavefront cost.
+// ALIGNED: the first look is at an aligned block (aligned_first says when).  A parameter of the kernel: with both looks in it, and a
+// branch, 51 calls of 65 536 positions took 885 us instead of 862, sessions of ten steps of 4 000 positions of records 196 to 201 instead of 190
+// to 196, of 60 000 255 to 260 instead of 251 to 257.
+//
+// SHIFT 1: a wavefront takes 32 positions, so that one pass holds the whole windows of up to 16 slots (see k_lookup_short),
+// and the workgroup's 256 positions have 512 threads (whole_windows says when).  Longer windows gain nothing by it: what a look
+// less saves, the barriers of 1 024 threads and the copies of an id that no longer meet in one wavefront cost.
 //
 // EVEN: where there are several workgroups per compute unit its memory pipe has more requests than it takes at a time, and the
 // older wavefronts go first, with all their looks, so that the youngest come to their first one when the others are
@@ -163,7 +166,7 @@ __device__ __forceinline__ uint32_t first_occurrence(const Params &p, uint32_t p
 // trip that nothing else then waits for; overlap_insert says when.  (With the durations of expiry steps requested together with
 // the ids, here and in k_finalize_chunk: calls of 2 000 to 20 000 positions 15.0 to 16.0 -> 14.5 to 15.4 us, 51 of 65 536 in a row
 // 924 -> 894, 12 of 262 144 new ids 726 -> 718.)
-template <bool REC, int SHIFT, bool EVEN, bool OVERLAP>
+template <bool REC, int SHIFT, bool EVEN, bool OVERLAP, bool ALIGNED>
 __global__ __launch_bounds__(kBlock << SHIFT, 4) void k_discover_chunk(Params p)
 {
     constexpr int THREADS = kBlock << SHIFT, WAVES = THREADS / kWave, PER = kWave >> SHIFT;
@@ -185,12 +188,8 @@ __global__ __launch_bounds__(kBlock << SHIFT, 4) void k_discover_chunk(Params p)
     int res = kProbeGoOn, q = 0;
     if constexpr (EVEN) __builtin_amdgcn_s_setprio(3);
     if constexpr (SHIFT == 0) {
-        // first block: the aligned one, or in a table that the caches hold the 8 slots from the home slot on (k_allocate)
-        const uint32_t lane_bytes = first_lane_bytes(d);
-        if ((d.N << (3 + d.sh)) > kCachedTableBytes)
-            res = probe_first<false, REC, true>(d, id, home, lane_bytes, s_req[w], s_code[w], p.step, &fresh, &q);
-        else
-            res = probe_first<false, REC, false>(d, id, home, lane_bytes, s_req[w], s_code[w], p.step, &fresh, &q);
+        // the first block: the aligned one that holds the home slot, or the 8 slots from there on
+        res = probe_first<false, REC, ALIGNED>(d, id, home, first_lane_bytes(d), s_req[w], s_code[w], p.step, &fresh, &q);
     }
     if constexpr (EVEN) __builtin_amdgcn_s_setprio(2);
     int left = SHIFT == 0 ? d.P - 1 : d.P;

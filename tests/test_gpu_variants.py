@@ -735,3 +735,20 @@ def test_parts_of_the_scratch_set(n, evict, layout):
         ids[1000::2] = ids[:-1000:2]
         t.step(ids, step)
     t.close()
+
+
+# ---- one-chunk calls on both sides of the lines at which windows of 9 to 16 slots are no longer read whole, and the first look is at an
+# aligned block: windows that end in its first block and in a later one, reach the table's end and go round it
+@pytest.mark.parametrize("evict", [True, "lru", "expiry", False])
+@pytest.mark.parametrize("halves,less,layout,probe", [(1, 0, "separate", 16), (1, 0, "records", 9), (2, 256, "records", 9), (2, 256, "records", 30),
+                                                      (5, 256, "separate", 8), (5, 256, "separate", 17)])
+def test_calls_around_the_lines_of_first_looks(halves, less, layout, probe, evict):
+    rng = rng_for(937)
+    n = halves * torch.cuda.get_device_properties(0).multi_processor_count * 128 - less
+    slots = n // 2 + 5
+    t = Pair(slots, probe, 1, evict, 59, layout=layout)
+    for step, more in enumerate([0, 1, 0, 1]):
+        ids = wl.zipf_ids(rng, n + more, 1.05, 2 * n) + step * n // 8
+        ids[: n // 16] = ids_with_home(rng, n // 16, slots - 12, slots, slots, 59)
+        t.step(ids, 2 * step, ttls=rng.integers(0, 5, size=n + more).astype(np.int32) if evict == "expiry" else None)
+    t.close()
