@@ -509,18 +509,18 @@ mpzch_status_t run_remap(Scratch &sc, Timing &tm, const Params &p, Windows windo
     return st;
 }
 
-template <int SHIFT, bool EVEN, bool OVERLAP, bool ALIGNED>
+template <int SHIFT, bool EVEN, bool OVERLAP, bool ALIGNED, bool LOOKS>
 mpzch_status_t launch_discover_chunk(const Params &p, int grid, hipStream_t s)
 {
-    if (p.t0.sh) TRY(launch(k_discover_chunk<true, SHIFT, EVEN, OVERLAP, ALIGNED>, grid, kBlock << SHIFT, s, p));
-    else TRY(launch(k_discover_chunk<false, SHIFT, EVEN, OVERLAP, ALIGNED>, grid, kBlock << SHIFT, s, p));
+    if (p.t0.sh) TRY(launch(k_discover_chunk<true, SHIFT, EVEN, OVERLAP, ALIGNED, LOOKS>, grid, kBlock << SHIFT, s, p));
+    else TRY(launch(k_discover_chunk<false, SHIFT, EVEN, OVERLAP, ALIGNED, LOOKS>, grid, kBlock << SHIFT, s, p));
     return MPZCH_OK;
 }
-template <bool EVEN, bool OVERLAP>
+template <bool EVEN, bool OVERLAP, bool LOOKS>
 mpzch_status_t launch_discover_chunk(const Params &p, int grid, bool aligned, hipStream_t s)
 {
-    if (aligned) return launch_discover_chunk<0, EVEN, OVERLAP, true>(p, grid, s);
-    return launch_discover_chunk<0, EVEN, OVERLAP, false>(p, grid, s);
+    if (aligned) return launch_discover_chunk<0, EVEN, OVERLAP, true, LOOKS>(p, grid, s);
+    return launch_discover_chunk<0, EVEN, OVERLAP, false, LOOKS>(p, grid, s);
 }
 
 // Calls of so many workgroups of 256 positions read the scratch set back (k_allocate_chunk says why).  Measured on 256 compute
@@ -588,10 +588,11 @@ mpzch_status_t launch_remap_chunks(Timing &tm, const Params &p, int32_t max_p_lr
     const bool rec = p.t0.sh != 0;
     const bool aligned = aligned_first(grid, num_cus, p.t0);
     if (!tm.begin(KDiscover, s)) return MPZCH_ERR_HIP;
-    if (whole_windows(grid, num_cus, p.t0.P)) TRY((launch_discover_chunk<1, false, true, false>(p, grid, s)));
-    else if (even_looks(grid, num_cus, p.t0)) TRY((launch_discover_chunk<true, false>(p, grid, aligned, s)));
-    else if (overlap_insert(grid, num_cus, rec)) TRY((launch_discover_chunk<false, true>(p, grid, aligned, s)));
-    else TRY((launch_discover_chunk<false, false>(p, grid, aligned, s)));
+    if (whole_windows(grid, num_cus, p.t0.P)) TRY((launch_discover_chunk<1, false, true, false, false>(p, grid, s)));
+    else if (even_looks(grid, num_cus, p.t0)) TRY((launch_discover_chunk<true, false, true>(p, grid, aligned, s)));
+    else if (grid < num_cus) TRY((launch_discover_chunk<false, true, false>(p, grid, aligned, s)));
+    else if (overlap_insert(grid, num_cus, rec)) TRY((launch_discover_chunk<false, true, true>(p, grid, aligned, s)));
+    else TRY((launch_discover_chunk<false, false, true>(p, grid, aligned, s)));
     if (!tm.end(s) || !tm.begin(KAllocate, s)) return MPZCH_ERR_HIP;
     if (max_p_lru > 0 && rec) TRY(launch_allocate_lru_chunk<true>(max_p_lru, p, grid, num_cus, s));
     else if (max_p_lru > 0) TRY(launch_allocate_lru_chunk<false>(max_p_lru, p, grid, num_cus, s));

@@ -68,9 +68,38 @@ __device__ __forceinline__ SetInsert begin_insert(const Params &p, bool miss, in
     if (miss && x.from == lane_id()) x.seen = try_entry(p, x.e, x.mine);
     return x;
 }
+// The entry to try after e, which another id holds: the next one that was empty, or had the hash bits of `mine`, when looked at.  (What
+// was seen of an entry that an id holds stays true: none is given up or handed on during the call.)
+__device__ __forceinline__ uint32_t next_entry(const Params &p, uint32_t e, uint32_t size, uint32_t mine)
+{
+    for (;;) {
+        if (++e == size) e = 0;
+        const uint32_t g = e & ~3u, h = g + 4 == size ? 0 : g + 4;       // (size is a multiple of four)
+        const u32x4 a = *reinterpret_cast<const u32x4 *>(p.set_slot + g), b = *reinterpret_cast<const u32x4 *>(p.set_slot + h);
+        uint32_t stop = 0;
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+            if (a[k] == kSetEmpty || ((a[k] ^ mine) & ~kChunkPosMask) == 0) stop |= 1u << k;
+            if (b[k] == kSetEmpty || ((b[k] ^ mine) & ~kChunkPosMask) == 0) stop |= 16u << k;
+        }
+        stop &= ~0u << (e & 3);
+        if (stop) {
+            const uint32_t k = (uint32_t)__ffs((int)stop) - 1u;
+            return k < 4 ? g + k : h + k - 4;
+        }
+        e = h + 3;
+    }
+}
+// LOOKS: after a collision a wavefront most of which has missed looks at the entries that follow and goes on at the first that may serve.
+// Where all ids are new the last entries of a call are a quarter full, and the last wavefronts had chains of eleven compare-and-swaps, a
+// round trip each; so they are three trips long.  Where few are new the one after the next is nearly always free, and the look is one
+// more, so calls of less than a workgroup per compute unit do without.  Loads of new ids, us: 12 calls of 262 144 677 / 662, 15 of 100 000 429 /
+// 422, 6 of 262 144 into records 304 / 298, of 233 000 133 / 130.  (In all calls and wavefronts: sessions 1 to 3 % longer.)
+template <bool LOOKS>
 __device__ __forceinline__ uint32_t finish_insert(const Params &p, bool miss, int64_t id, uint32_t pos, const SetInsert &x)
 {
     uint32_t ent = kNoEntry;
+    const bool many = LOOKS && __popcll(__ballot(miss)) > kWave / 2;
     if (miss && x.from == lane_id()) {
         const uint32_t size = (uint32_t)kChunkSetEntries * (uint32_t)p.n;
         uint32_t e = x.e, seen = x.seen;
@@ -85,7 +114,8 @@ __device__ __forceinline__ uint32_t finish_insert(const Params &p, bool miss, in
                     break;
                 }
             }
-            if (++e == size) e = 0;
+            if (LOOKS && many) e = next_entry(p, e, size, x.mine);
+            else if (++e == size) e = 0;
             seen = try_entry(p, e, x.mine);
         }
         ent |= e;
@@ -166,7 +196,7 @@ __device__ __forceinline__ uint32_t first_occurrence(const Params &p, uint32_t p
 // trip that nothing else then waits for; overlap_insert says when.  (With the durations of expiry steps requested together with
 // the ids, here and in k_finalize_chunk: calls of 2 000 to 20 000 positions 15.0 to 16.0 -> 14.5 to 15.4 us, 51 of 65 536 in a row
 // 924 -> 894, 12 of 262 144 new ids 726 -> 718.)
-template <bool REC, int SHIFT, bool EVEN, bool OVERLAP, bool ALIGNED>
+template <bool REC, int SHIFT, bool EVEN, bool OVERLAP, bool ALIGNED, bool LOOKS>
 __global__ __launch_bounds__(kBlock << SHIFT, 4) void k_discover_chunk(Params p)
 {
     constexpr int THREADS = kBlock << SHIFT, WAVES = THREADS / kWave, PER = kWave >> SHIFT;
@@ -209,7 +239,7 @@ __global__ __launch_bounds__(kBlock << SHIFT, 4) void k_discover_chunk(Params p)
     asm volatile("" : "+v"(duration));               // (not added to before: made right behind the load, the sum waits for it)
     const SetInsert insert = begin_insert(p, miss, id, hash, (uint32_t)pos, reinterpret_cast<MetaMerge *>(s_req[w]));
     uint32_t e = kNoEntry;
-    if constexpr (!OVERLAP) e = finish_insert(p, miss, id, (uint32_t)pos, insert);
+    if constexpr (!OVERLAP) e = finish_insert<LOOKS>(p, miss, id, (uint32_t)pos, insert);
     const int64_t slot = hit ? wrap(home + res, d.N) : home;
     store_meta_block(d, hit && !(REC && fresh && d.evict != 3), slot, metadata_for(p, d, duration), s_merge);
     if (in) {
@@ -245,7 +275,7 @@ __global__ __launch_bounds__(kBlock << SHIFT, 4) void k_discover_chunk(Params p)
         }
     }
     if constexpr (OVERLAP) {
-        e = finish_insert(p, miss, id, (uint32_t)pos, insert);
+        e = finish_insert<LOOKS>(p, miss, id, (uint32_t)pos, insert);
         if (in) p.ent[pos] = e;
     }
 }

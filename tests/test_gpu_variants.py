@@ -752,3 +752,18 @@ def test_calls_around_the_lines_of_first_looks(halves, less, layout, probe, evic
         ids[: n // 16] = ids_with_home(rng, n // 16, slots - 12, slots, slots, 59)
         t.step(ids, 2 * step, ttls=rng.integers(0, 5, size=n + more).astype(np.int32) if evict == "expiry" else None)
     t.close()
+
+
+# ---- ... and at which a wavefront looks at the scratch set after a collision: all ids new, copies of them a workgroup and half a call away
+@pytest.mark.parametrize("layout,evict", [("separate", False), ("records", True), ("records", "expiry"), ("separate", "lru")])
+@pytest.mark.parametrize("more", [-256, -255, 0, 37])
+def test_collisions_of_new_ids(layout, evict, more):
+    rng = rng_for(941)
+    n = torch.cuda.get_device_properties(0).multi_processor_count * 256 + more
+    t = Pair(2 * n, 24, 0, evict, 61, layout=layout)
+    for step in (0, 2, 4):
+        ids = rng.integers(0, 1 << 40, size=n)
+        ids[n // 2::3] = ids[: n - n // 2: 3]
+        ids[300::7] = ids[:-300:7]
+        t.step(ids, step)
+    t.close()
