@@ -1435,7 +1435,8 @@ mpzch_status_t mpzch_reset_rows_jagged(mpzch_group_t *g, const int64_t *evicted_
     hipStream_t s = (hipStream_t)stream;
     TRY(g->sc.query_device());
     TRY(g->rows.put(descs, s));
-    TRY(launch(k_reset_rows_jagged, g->sc.num_cus * 8, kBlock, s, evicted_slots, num_evicted, g->rows.dev, T));
+    // (eight workgroups per compute unit: 10 400 values over 26 tables, the whole step, 36.7 us against 35.6 with two; 41.6 M the same with four)
+    TRY(launch(k_reset_rows_jagged, g->sc.num_cus * 4, kBlock, s, evicted_slots, num_evicted, g->rows.dev, T));
     return MPZCH_OK;
 }
 

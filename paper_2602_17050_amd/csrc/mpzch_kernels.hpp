@@ -1581,15 +1581,28 @@ __global__ __launch_bounds__(kBlock, 4) void k_discover_tables_chunk(Params p)
     if constexpr (OVERLAP) finish();
 }
 
+// find_table for a position of a segment that begins in table f, without a look at the memory: one comparison for every table that begins
+// before the segment's `end`.  (In k_allocate_lru the lanes' offsets cost more registers than the search costs time: 8 x 100 000 values in LRU
+// tables of records 664 -> 691 us for six steps.)
+__device__ __forceinline__ int find_table_from(int64_t lane_offset, int num_tables, int f, int64_t end, int64_t pos)
+{
+    for (int k = f + 1; k < num_tables; ++k) {
+        const int64_t begin = readlane64(lane_offset, k);
+        if (begin >= end) break;
+        if (begin <= pos) f = k;
+    }
+    return f;
+}
+
 // Several tables: the table of a whole segment of positions [seg_base, seg_base + seg_len), when one
 // table owns them all (the rule: a segment is a few thousand positions, a feature's share of the
 // batch many times that).  Its number and descriptor are then wave-uniform and read once per segment
 // instead of once per lane and list entry.  Returns false when the segment straddles a boundary.
 __device__ __forceinline__ bool segment_table(const Params &p, int64_t lane_offset, int64_t seg_base, int64_t seg_len,
-                                              int &f, Tab &d)
+                                              int &f, Tab &d, const TableDesc *descs)
 {
     f = find_table_wave(lane_offset, seg_base);
-    d = uniform(view(p.descs[f]));
+    d = uniform(view(descs[f]));
     return f == p.num_tables - 1 || uniform64(seg_base) + seg_len <= uniform64(shfl64(lane_offset, (f + 1) & (kWave - 1)));
 }
 
@@ -1835,16 +1848,29 @@ __device__ __forceinline__ void claim_walk(const Tab &d, Claimant &c, const Clai
     c.active = state == kWalks || state == kWaits;
 }
 
+// The descriptors of a group, in LDS: to be reached by all `threads` of the workgroup.  (Segments of short features belong to several tables, one after
+// the other, and each change waited for a descriptor, each position for a search through the offsets in memory, each list of
+// evicted slots for its place.  With the lanes' offsets and a copy of the descriptors, whole steps, us: 26 tables with 10 400 values 36.5 -> 35.4, with
+// 320 K 50.2 -> 49.0, 4 with 20 K 32.7 -> 32.4, 26 with 1.1 M 74.5 -> 73.4, 41.6 M values the same.)
+__device__ __forceinline__ void copy_descs(const Params &p, TableDesc *s_desc, int threads)
+{
+    const uint64_t *src = reinterpret_cast<const uint64_t *>(p.descs);
+    uint64_t *dst = reinterpret_cast<uint64_t *>(s_desc);
+    for (int i = threadIdx.x; i < p.num_tables * (int)(sizeof(TableDesc) / 8); i += threads) dst[i] = src[i];
+    __syncthreads();
+}
+
 // One wavefront serves the segments vblock, vblock + vgrid, ...; s_code and s_req are its own areas of LDS.  REC: every
 // table of the call is kept as records (identity and metadata come with one load).  Several tables: the claimants of one
 // table at a time (nearly always all of them: a segment is a few thousand positions, a feature's share many times that).
 template <bool MULTI, bool REC>
 __device__ __forceinline__ void allocate_body(const Params &p, int64_t vblock, int64_t vgrid,
-                                              uint8_t *s_code, ClaimReq *s_req, Outcomes &outcomes)
+                                              uint8_t *s_code, ClaimReq *s_req, Outcomes &outcomes, TableDesc *s_desc)
 {
     const int lane = lane_id();
     const Tab d0 = view(p.t0);
     const int64_t lane_offset = MULTI ? table_offsets(p.offsets, p.num_tables) : 0;
+    if constexpr (MULTI) copy_descs(p, s_desc, kWave);
     clear_outcomes(p, outcomes);
     for (int64_t seg = vblock; seg < p.num_segs; seg += vgrid) {
         const uint32_t cnt = p.seg_cnt[seg];
@@ -1853,7 +1879,7 @@ __device__ __forceinline__ void allocate_body(const Params &p, int64_t vblock, i
         int seg_f = 0;
         Tab seg_d = d0;
         bool seg_one = true;
-        if constexpr (MULTI) seg_one = segment_table(p, lane_offset, seg_base, p.seg_chunks * kWave, seg_f, seg_d);
+        if constexpr (MULTI) seg_one = segment_table(p, lane_offset, seg_base, p.seg_chunks * kWave, seg_f, seg_d, s_desc);
         for (uint32_t j0 = 0; j0 == 0 || j0 < cnt; j0 += kWave) {
             // the first entries are requested before the count is known: the count is at most the
             // number of positions of the segment and the arrays have room for n + 128 entries, so
@@ -1867,6 +1893,7 @@ __device__ __forceinline__ void allocate_body(const Params &p, int64_t vblock, i
             uint32_t first = 0;
             bool alone = false;
             int f = seg_f;
+            if (MULTI && !seg_one) f = find_table_from(lane_offset, p.num_tables, seg_f, seg_base + p.seg_chunks * kWave, (int64_t)pos);
             if (have) {
                 if constexpr (MULTI) {
                     first = p.set_slot[e];
@@ -1877,7 +1904,6 @@ __device__ __forceinline__ void allocate_body(const Params &p, int64_t vblock, i
                     alone = entered_alone(e, note);
                     if ((e & kEntered) && note) first = p.set_slot[e & ~kEntered];
                 }
-                if (MULTI && !seg_one) f = find_table(p.offsets, p.num_tables, (int64_t)pos);
             }
             const bool elected = have && first == pos;        // else: a later copy of the id
             if (have && !elected) p.first_of[idx] = first;
@@ -1890,7 +1916,7 @@ __device__ __forceinline__ void allocate_body(const Params &p, int64_t vblock, i
                     if (!seg_one) {
                         of_table = __builtin_amdgcn_readlane(f, __ffsll((unsigned long long)__ballot(todo)) - 1);
                         agent = todo && f == of_table;
-                        d = uniform(view(p.descs[of_table]));
+                        d = uniform(view(s_desc[of_table]));
                     }
                     todo = todo && !agent;
                     // claimants of LRU tables are served by k_allocate_lru
@@ -1949,7 +1975,8 @@ __global__ __launch_bounds__(kWave, MULTI ? 5 : REC ? 7 : 6) void k_allocate(Par
     __shared__ __attribute__((aligned(16))) uint8_t s_code[kWave * kAllocG];
     __shared__ ClaimReq s_req[kWave];
     __shared__ Outcomes s_outcomes;
-    allocate_body<MULTI, REC>(p, blockIdx.x, gridDim.x, s_code, s_req, s_outcomes);
+    __shared__ TableDesc s_desc[MULTI ? kMaxTables : 1];
+    allocate_body<MULTI, REC>(p, blockIdx.x, gridDim.x, s_code, s_req, s_outcomes, s_desc);
 }
 
 // ------------------------------------------------------------------ allocation, LRU policy
@@ -2417,7 +2444,7 @@ __device__ __forceinline__ void reset_staged_rows(const Params &p, const int64_t
 
 // Appends the staged evicted slots of one wavefront to table `table`'s list (and resets their rows).
 __device__ __forceinline__ void flush_evicted(const Params &p, const int64_t *buf, const int64_t *rows_buf, int &count,
-                                              int table)
+                                              int table, const TableDesc *s_desc)
 {
     if (count == 0) return;
     __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
@@ -2430,8 +2457,8 @@ __device__ __forceinline__ void flush_evicted(const Params &p, const int64_t *bu
     // written as one expression, is compiled into loads through a generic pointer)
     int64_t ev_begin = p.t0.ev_begin, ev_cap = p.t0.ev_cap;
     if (p.num_tables > 1) {
-        ev_begin = p.descs[table].ev_begin;
-        ev_cap = p.descs[table].ev_cap;
+        ev_begin = s_desc[table].ev_begin;
+        ev_cap = s_desc[table].ev_cap;
     }
     for (int i = lane; i < count; i += kWave) {
         const int64_t at = (int64_t)base + i;
@@ -2447,7 +2474,7 @@ struct Staged {
 };
 
 // Called by all lanes of the wavefront.  `evicted` lanes hold an evicted slot s of table f.
-__device__ __forceinline__ void stage_evicted(const Params &p, Staged &st, int64_t *s_ev_w, int64_t *s_row_w, bool evicted, int64_t s, int f)
+__device__ __forceinline__ void stage_evicted(const Params &p, Staged &st, int64_t *s_ev_w, int64_t *s_row_w, bool evicted, int64_t s, int f, const TableDesc *s_desc)
 {
     const int lane = lane_id();
     // all entries of the buffer belong to one table
@@ -2457,7 +2484,7 @@ __device__ __forceinline__ void stage_evicted(const Params &p, Staged &st, int64
         const bool sel = evicted && f == tf;
         const uint64_t selm = __ballot(sel);
         const int add = __popcll(selm);
-        if ((st.count > 0 && tf != st.table) || st.count + add > kEvBuf) flush_evicted(p, s_ev_w, s_row_w, st.count, st.table);
+        if ((st.count > 0 && tf != st.table) || st.count + add > kEvBuf) flush_evicted(p, s_ev_w, s_row_w, st.count, st.table, s_desc);
         st.table = tf;
         if (sel) {
             const int at = st.count + __popcll(selm & ((1ull << lane) - 1ull));
@@ -2472,7 +2499,7 @@ __device__ __forceinline__ void stage_evicted(const Params &p, Staged &st, int64
 // End of k_finalize, reached by all threads: the workgroup reserves its part of the evicted list (one reservation when all its
 // wavefronts staged for the same table) and writes it.
 __device__ __forceinline__ void list_evicted(const Params &p, Staged &st, int64_t (*s_ev)[kEvBuf], int64_t (*s_row)[kEvBuf],
-                                             int *s_cnt, int (&s_tab)[kFinalizeWaves], unsigned long long *s_base)
+                                             int *s_cnt, int (&s_tab)[kFinalizeWaves], unsigned long long *s_base, const TableDesc *s_desc)
 {
     const int lane = lane_id(), w = threadIdx.x / kWave;
     __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
@@ -2489,7 +2516,7 @@ __device__ __forceinline__ void list_evicted(const Params &p, Staged &st, int64_
     }
     if (total == 0) return;
     if (!same) {
-        flush_evicted(p, s_ev[w], s_row[0], st.count, st.table);
+        flush_evicted(p, s_ev[w], s_row[0], st.count, st.table, s_desc);
         return;
     }
     if (threadIdx.x == 0) *s_base = atomicAdd(&p.ctl->num_evicted[tab], (unsigned long long)total);
@@ -2497,8 +2524,8 @@ __device__ __forceinline__ void list_evicted(const Params &p, Staged &st, int64_
     const int64_t base = (int64_t)*s_base + before;
     int64_t ev_begin = p.t0.ev_begin, ev_cap = p.t0.ev_cap;
     if (p.num_tables > 1) {
-        ev_begin = p.descs[tab].ev_begin;
-        ev_cap = p.descs[tab].ev_cap;
+        ev_begin = s_desc[tab].ev_begin;
+        ev_cap = s_desc[tab].ev_cap;
     }
     for (int i = lane; i < st.count; i += kWave)
         if (base + i < ev_cap) p.out_evicted[ev_begin + base + i] = s_ev[w][i];
@@ -2540,6 +2567,8 @@ __device__ __forceinline__ void finalize_body(const Params &p)
     constexpr bool multi = MULTI;
     Staged staged;
     const int64_t lane_offset = multi ? table_offsets(p.offsets, p.num_tables) : 0;
+    __shared__ TableDesc s_desc[MULTI ? kMaxTables : 1];
+    if constexpr (MULTI) copy_descs(p, s_desc, kFinalizeBlock);
 
     for (int64_t seg = wave_global; seg < p.num_segs; seg += num_waves) {
         const uint32_t cnt = p.seg_cnt[seg];
@@ -2548,7 +2577,7 @@ __device__ __forceinline__ void finalize_body(const Params &p)
         Tab seg_d{};
         if (!multi) seg_d = view(p.t0);
         bool seg_one = true;
-        if (multi) seg_one = segment_table(p, lane_offset, seg_base, p.seg_chunks * kWave, seg_f, seg_d);
+        if (multi) seg_one = segment_table(p, lane_offset, seg_base, p.seg_chunks * kWave, seg_f, seg_d, s_desc);
         if ((int32_t)seg_base >= (int32_t)p.n) break;         // segments past the batch hold nothing
         for (uint32_t j0 = 0; j0 == 0 || j0 < cnt; j0 += kWave) {
             // (as in k_allocate, the first entries are requested before the count is known)
@@ -2571,6 +2600,7 @@ __device__ __forceinline__ void finalize_body(const Params &p)
                 return is_tag(v) ? (lru ? lru_tag_pos(v) : tag_pos(v)) == fst : v == cid;
             };
             bool search = false, sure = false;
+            if (multi && !seg_one) f = find_table_from(lane_offset, p.num_tables, seg_f, seg_base + p.seg_chunks * kWave, (int64_t)pos);
             if (have) {
                 agent = (word & kAgentEntry) != 0;
                 first = agent ? pos : word;
@@ -2580,8 +2610,7 @@ __device__ __forceinline__ void finalize_body(const Params &p)
                     if (seg_one) {
                         f = seg_f;
                     } else {
-                        f = find_table(p.offsets, p.num_tables, (int64_t)pos);
-                        d = view(p.descs[f]);
+                        d = view(s_desc[f]);
                     }
                 }
                 if (MULTI ? d.evict != 2 : NOTES) {
@@ -2651,14 +2680,14 @@ __device__ __forceinline__ void finalize_body(const Params &p)
                 }
                 __builtin_nontemporal_store(s_final, &p.out_slots[pos]);             // (see finish_hit in discover_body)
             }
-            stage_evicted(p, staged, s_ev[w], s_row[MULTI ? 0 : w], agent && outcome == 1, s_final, f);
+            stage_evicted(p, staged, s_ev[w], s_row[MULTI ? 0 : w], agent && outcome == 1, s_final, f, s_desc);
         }
     }
     if constexpr (!MULTI) {
         __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
         reset_staged_rows(p, s_row[w], staged.count);
     }
-    list_evicted(p, staged, s_ev, s_row, s_cnt, s_tab, &s_base);
+    list_evicted(p, staged, s_ev, s_row, s_cnt, s_tab, &s_base, s_desc);
 }
 
 // WAVES = 8 wavefronts per SIMD (one table: 46 vector registers and 66 KB of LDS for 16 wavefronts, several: 56 and 40 KB; no

@@ -767,3 +767,22 @@ def test_collisions_of_new_ids(layout, evict, more):
         ids[300::7] = ids[:-300:7]
         t.step(ids, step)
     t.close()
+
+
+# ---- groups whose segments hold the ends of several features: one, two and more of them in a chunk of 64 values, empty ones between, evicted
+# slots of many tables in a workgroup
+@pytest.mark.parametrize("layout", ["separate", "records"])
+@pytest.mark.parametrize("per,empty", [(1, 0), (31, 3), (64, 0), (150, 2), (64 * 16 + 1, 1)])
+def test_segments_of_several_features(per, empty, layout):
+    from test_gpu_jagged import JaggedPair
+    rng = rng_for(947)
+    kinds = [True, "lru", "expiry", False]
+    specs = [wl.TableSpec(max(9, 2 * per), 8, 0, kinds[f % 4], 150 + f) for f in range(40)]
+    jp = JaggedPair(specs, range(40) if layout == "records" else ())
+    for step in range(4):
+        counts = rng.integers(per // 2, per + 1, size=40)
+        counts[rng.permutation(40)[: 5 * empty]] = 0
+        vals = rng.integers(0, 6 * per + 1, size=counts.sum()) + step * per
+        jp.step(vals, np.concatenate([[0], np.cumsum(counts)]).astype(np.int64), 2 * step)
+    jp.check_state()
+    jp.close()
