@@ -417,23 +417,36 @@ constexpr int lru_chunk_threads(int grid, int num_cus)
 {
     return grid <= num_cus ? 4 * kBlock : grid <= (T <= 2 ? 5 : 2) * num_cus ? 2 * kBlock : kBlock;
 }
-template <int T, bool REC>
+// Calls whose LRU claims pass over slots that were read with a better claim (SEEN of claim_group_lru): up to four slots of the table for a
+// position.  With more of them claims hardly meet, and the look for better ones costs each claimant some twenty instructions more.
+// Steps at 95 % load, a tenth of the ids new, with / without, us: 70 000 positions, one slot for a position 97.6 / 123.1, two 57.4 / 60.1, a little over
+// four 34.4 / 33.7, eight 26.5 / 26.2, 64 26.9 / 26.5; 200 000 149 / 186, 78.8 / 82.4, 48.1 / 47.2, 33.7 / 33.3, 39.3 / 38.1; 400 000 210 / 252, 112 / 116,
+// 68.4 / 67.9, 49.4 / 49.2, 65.4 / 64.5.  (Twelve steps of 5 000 on 20 000 slots, the table filling up, 358 / 361.)
+constexpr bool crowded_lru(const Params &p) { return p.t0.N <= 4 * p.n; }
+
+template <int T, bool REC, bool SEEN>
 mpzch_status_t launch_allocate_lru_chunk(const Params &p, int grid, int num_cus, hipStream_t s)
 {
     const int threads = lru_chunk_threads<T>(grid, num_cus);
-    if (threads == 4 * kBlock) TRY(launch(k_allocate_lru_chunk<T, REC, 4 * kBlock>, grid, threads, s, p));
-    else if (threads == 2 * kBlock) TRY(launch(k_allocate_lru_chunk<T, REC, 2 * kBlock>, grid, threads, s, p));
-    else TRY(launch(k_allocate_lru_chunk<T, REC, kBlock>, grid, threads, s, p));
+    if (threads == 4 * kBlock) TRY(launch(k_allocate_lru_chunk<T, REC, SEEN, 4 * kBlock>, grid, threads, s, p));
+    else if (threads == 2 * kBlock) TRY(launch(k_allocate_lru_chunk<T, REC, SEEN, 2 * kBlock>, grid, threads, s, p));
+    else TRY(launch(k_allocate_lru_chunk<T, REC, SEEN, kBlock>, grid, threads, s, p));
+    return MPZCH_OK;
+}
+template <bool REC, bool SEEN>
+mpzch_status_t launch_allocate_lru_chunk(int32_t max_p_lru, const Params &p, int grid, int num_cus, hipStream_t s)
+{
+    if (max_p_lru <= 8) TRY((launch_allocate_lru_chunk<1, REC, SEEN>(p, grid, num_cus, s)));
+    else if (max_p_lru <= 16) TRY((launch_allocate_lru_chunk<2, REC, SEEN>(p, grid, num_cus, s)));
+    else if (max_p_lru <= 32) TRY((launch_allocate_lru_chunk<4, REC, SEEN>(p, grid, num_cus, s)));
+    else TRY((launch_allocate_lru_chunk<8, REC, SEEN>(p, grid, num_cus, s)));
     return MPZCH_OK;
 }
 template <bool REC>
 mpzch_status_t launch_allocate_lru_chunk(int32_t max_p_lru, const Params &p, int grid, int num_cus, hipStream_t s)
 {
-    if (max_p_lru <= 8) TRY(launch_allocate_lru_chunk<1, REC>(p, grid, num_cus, s));
-    else if (max_p_lru <= 16) TRY(launch_allocate_lru_chunk<2, REC>(p, grid, num_cus, s));
-    else if (max_p_lru <= 32) TRY(launch_allocate_lru_chunk<4, REC>(p, grid, num_cus, s));
-    else TRY(launch_allocate_lru_chunk<8, REC>(p, grid, num_cus, s));
-    return MPZCH_OK;
+    if (crowded_lru(p)) return launch_allocate_lru_chunk<REC, true>(max_p_lru, p, grid, num_cus, s);
+    return launch_allocate_lru_chunk<REC, false>(max_p_lru, p, grid, num_cus, s);
 }
 
 mpzch_status_t launch_allocate(int32_t max_p_lru, const Params &p, int num_cus, hipStream_t s)

@@ -381,8 +381,8 @@ __global__ __launch_bounds__(kBlock, 4) void k_allocate_chunk(Params p)
 // The claims under the LRU policy (max_probe <= 8 T <= 64).  The workgroup first lists its claimants, so that its groups of
 // 8 lanes get them evenly: a wavefront of 64 positions has a handful, which it would serve one or two at a time
 // (300 007 positions, 10 % of them claimants with windows of 32 slots: 43 -> 16 us).  Claimants beyond the groups wait for
-// the first ones' chains, so the workgroup is as large as the compute unit has room for (lru_chunk_threads).
-template <int T, bool REC, int THREADS>
+// the first ones' chains, so the workgroup is as large as the compute unit has room for (lru_chunk_threads).  SEEN: crowded_lru.
+template <int T, bool REC, bool SEEN, int THREADS>
 __global__ __launch_bounds__(THREADS, T == 8 || THREADS > kBlock ? 4 : 6) void k_allocate_lru_chunk(Params p)
 {
     constexpr int G = kLruG, WAVES = THREADS / kWave, GROUPS = THREADS / G;
@@ -431,7 +431,7 @@ __global__ __launch_bounds__(THREADS, T == 8 || THREADS > kBlock ? 4 : 6) void k
         const bool more = i + GROUPS < count;
         const int64_t home2 = more ? s_home[i + GROUPS] : 0;
         const LruSlots<T> x2 = load_lru_slots<T, REC>(d, more, home2);
-        claim_group_lru<T, REC, true>(p, d, i < count, i < count ? s_pos[i] : 0u, home, x,
+        claim_group_lru<T, REC, SEEN>(p, d, i < count, i < count ? s_pos[i] : 0u, home, x,
                                 [&](uint32_t who, int32_t choice, int32_t round, int64_t slot, int64_t old) {
                                     if (lane % G != 0) return;
                                     const uint32_t place = (uint32_t)choice << 16 | (uint32_t)(round + 1);

@@ -2068,8 +2068,8 @@ __device__ __forceinline__ uint64_t group_or(uint64_t x)
 // was read with a better claim than the claimant's first choice would make is passed over, since claims only get better; the atomic
 // that it would lose is another round trip.  Before / home from the tag / and passed over, us: 12 steps under LRU of 684 positions 251.6 /
 // 247.0 / 245.7, of 5 000 on 20 000 slots, windows of 32, 373 / 361 / 358, of 20 011 on 12 000 609 / 588 / 558, of 12 000 on 8 000, of 64,
-// 1 049 / 1 024 / 889; where few are displaced the same to 0.4 %.  (Not in the lists of long calls, where few claims meet and windows of 64
-// have no registers left for it.)
+// 1 049 / 1 024 / 889.  (Where few are displaced it costs 1 to 2 %: crowded_lru.  Not in the lists of long calls, where few claims meet and
+// windows of 64 have no registers left for it.)
 // The wavefront goes through the loops as one: a branch for each group cost windows of 8, which hardly need the classes, what
 // they gave (360 000 claimants 56.3 -> 53.9).
 template <int T, bool REC, bool SEEN, typename Placed, typename Lost>

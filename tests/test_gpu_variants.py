@@ -392,6 +392,22 @@ def test_lru_crowded(slots, n, probe, layout):
     t.close()
 
 
+# ... and on both sides of four slots for a position, beyond which no slot is passed over: few windows' homes, so that claims meet there too
+@pytest.mark.parametrize("layout", ["separate", "records"])
+@pytest.mark.parametrize("probe", [8, 9, 32, 64])
+@pytest.mark.parametrize("n", [600, 40_000, 140_000])
+def test_lru_four_slots_a_position(n, probe, layout):
+    rng = rng_for(1_017 + n + probe)
+    for slots in (4 * n, 4 * n + 1):
+        t = Pair(slots, probe, 0, "lru", 5, layout=layout)
+        for step in range(3):
+            ids = rng.integers(0, 1 << 60, size=n)
+            ids[: n // 8] = ids_with_home(rng, n // 8, slots - 40, slots, slots, 5)
+            t.step(ids, step + 1)
+        t.check_state()
+        t.close()
+
+
 # ---- LRU claims by workgroups of 1 024, 512 and 256 threads: on both sides of each line, few claimants and mostly claimants
 @pytest.mark.parametrize("more", [0, 1])
 @pytest.mark.parametrize("groups,probe", [(1, 5), (1, 16), (1, 29), (1, 64), (2, 5), (2, 16), (2, 29), (2, 64), (5, 5), (5, 16)])
