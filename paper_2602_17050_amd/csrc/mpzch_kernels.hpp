@@ -2285,8 +2285,11 @@ __device__ __forceinline__ int32_t claim_wave_lru_long(const Params &p, const Ta
     const int C = (d.P + kWave - 1) / kWave;             // <= kLruLongSlots (checked when the table is created)
     int32_t first_round = -1;
     bool is_first = true;
-    int64_t home = home_slot(p.ids[cpos], d.seed, d.N);
     for (;;) {
+        // (Of a displaced claimant too, by its id: the home slot from its tag, as in claim_group_lru, has to be kept through the loop of
+        // choices, and the claim itself took longer.  One table, windows of 100, by the id / from the tag, us: 300 000 positions of records
+        // 168 / 180, 700 000 325 / 350, of two tensors 289 / 312; of 1 024, 40 000 positions 280 / 294.  Groups the same either way.)
+        const int64_t home = home_slot(p.ids[cpos], d.seed, d.N);
         uint32_t emp = 0, evi = 0;                        // bit c: the slot of round c * 64 + lane is empty / evictable
         int32_t m[kLruLongSlots];
 #pragma unroll
@@ -2357,8 +2360,6 @@ __device__ __forceinline__ int32_t claim_wave_lru_long(const Params &p, const Ta
             displaced = is_tag(old) ? old : 0;
             outcome = outcome_of(old);
             if (is_first) first_round = round;
-            home = wrap(home + round, d.N) - (int64_t)lru_tag_round(old);
-            if (home < 0) home += d.N;
         }
         is_first = false;
         if (!placed || !displaced) break;
