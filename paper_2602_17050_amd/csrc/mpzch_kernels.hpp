@@ -249,14 +249,17 @@ __device__ __forceinline__ uint32_t tag_round(int64_t v) { return (uint32_t)(((u
 __device__ __forceinline__ uint32_t tag_occ(int64_t v) { return (uint32_t)((uint64_t)v & 1u); }
 
 // Under the LRU policy claims rank by the number of the choice.  The round, which tells a displaced claimant's home slot, is kept
-// below the position (choices and rounds are below 1 024, positions below 2^30).
+// below the position.
+constexpr int kLruRoundBits = 11, kLruPosShift = 1 + kLruRoundBits, kLruChoiceShift = kLruPosShift + 32;
+static_assert(MPZCH_MAX_PROBE_LRU <= 1 << kLruRoundBits, "rounds (and choices, of which a window has no more) fit an LRU claim tag");
+static_assert(MPZCH_MAX_BATCH <= (int64_t)1 << 32, "positions fit an LRU claim tag");
 __device__ __forceinline__ int64_t make_lru_tag(uint32_t choice, uint32_t pos, uint32_t round, uint32_t was_occupied)
 {
-    return (int64_t)(kTagBase | ((uint64_t)choice << 44) | ((uint64_t)pos << 12) | (round << 1 | was_occupied));
+    return (int64_t)(kTagBase | ((uint64_t)choice << kLruChoiceShift) | ((uint64_t)pos << kLruPosShift) | (round << 1 | was_occupied));
 }
-__device__ __forceinline__ uint32_t lru_tag_pos(int64_t v) { return (uint32_t)((uint64_t)v >> 12); }
-__device__ __forceinline__ uint32_t lru_tag_choice(int64_t v) { return (uint32_t)((uint64_t)v >> 44) & 0x7FFFFu; }
-__device__ __forceinline__ uint32_t lru_tag_round(int64_t v) { return (uint32_t)v >> 1 & 0x7FFu; }
+__device__ __forceinline__ uint32_t lru_tag_pos(int64_t v) { return (uint32_t)((uint64_t)v >> kLruPosShift); }
+__device__ __forceinline__ uint32_t lru_tag_choice(int64_t v) { return (uint32_t)(((uint64_t)v & ~kTagBase) >> kLruChoiceShift); }
+__device__ __forceinline__ uint32_t lru_tag_round(int64_t v) { return (uint32_t)v >> 1 & ((1u << kLruRoundBits) - 1u); }
 
 __device__ __forceinline__ int64_t shfl64(int64_t v, int src)
 {

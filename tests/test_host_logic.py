@@ -135,3 +135,20 @@ def test_launch_takes_only_arguments_that_fit(tmp_path, args, ok):
     r = subprocess.run([build.hipcc(), "--offload-arch=gfx950", "-std=c++17", "--offload-host-only", "-fsyntax-only",
                         "-I", os.path.dirname(build.SRC), "-x", "hip", str(src)], capture_output=True, text=True)
     assert (r.returncode == 0) == ok, r.stderr[-2000:]
+
+
+# The fields of an LRU claim tag are as wide as the limits of the header need: with a wider limit the library must not compile
+# (syntax only, host side)
+@pytest.mark.parametrize("limit,value,message", [("MPZCH_MAX_PROBE_LRU", "1024", ""), ("MPZCH_MAX_PROBE_LRU", "2049", "rounds"),
+                                                 ("MPZCH_MAX_BATCH", "((int64_t)1 << 32) + 1", "positions")])
+def test_lru_claim_tag_is_as_wide_as_the_limits(tmp_path, limit, value, message):
+    from paper_2602_17050_amd import build
+    src = tmp_path / "probe.hip"
+    header = os.path.join(os.path.dirname(build.SRC), "..", "..", "include", "mpzch.h")
+    src.write_text(f'#include "{header}"\n#undef {limit}\n#define {limit} ({value})\n#include "mpzch.hip"\n')
+    r = subprocess.run([build.hipcc(), "--offload-arch=gfx950", "-std=c++17", "--offload-host-only", "-fsyntax-only",
+                        "-I", os.path.dirname(build.SRC), "-x", "hip", str(src)], capture_output=True, text=True)
+    if not message:
+        assert r.returncode == 0, r.stderr[-2000:]
+    else:
+        assert r.returncode != 0 and any("static assertion" in x and message in x and "LRU claim tag" in x for x in r.stderr.splitlines()), r.stderr[-2000:]
