@@ -578,7 +578,21 @@ constexpr bool even_looks(int64_t groups, int num_cus, const TableDesc &t)
 // 3.4 us of the kernel's 6.8.  Sessions of ten steps on six slots a position, whole windows / two looks, us: 2 000 positions of two tensors 177
 // / 183, of records 175 / 183, 9 000 188 / 191, 187 / 192, 20 000 203 / 205, 203 / 207, 40 000 227 / 226, 225 / 224, 65 000 285 / 276, 284 /
 // 273; six steps of 100 000 on 1 M slots 452 / 403, 444 / 395.
-constexpr bool whole_windows(int64_t groups, int num_cus, int32_t max_probe) { return window_shift(max_probe) == 1 && 2 * groups <= num_cus; }
+// Up to one workgroup per compute unit where the lines are fewer or nearly every absent id needs its whole window: tables of two tensors
+// that the memory-side cache holds and the L2 does not, unless eviction is off, and, beyond that cache, LRU tables, which are full.  Steps
+// in steady state, windows of 16, whole / two looks, 36 000, 45 000, 55 000 and 65 536 positions, us: LRU, 80 M slots as two tensors 19.4 / 20.6,
+// 20.1 / 21.3, 20.9 / 21.9, 21.6 / 22.6, as records 19.8 / 20.9, 20.7 / 21.6, 21.7 / 22.2, 22.5 / 23.1; two tensors, 20 M slots, TTL 17.9 / 18.5,
+// 18.4 / 19.1, 19.3 / 19.6, 19.5 / 19.8; sessions on 2.1 M slots 628 / 631, 637 / 643, 650 / 655, 662 / 667.  On the other sides: TTL, 80 M slots as
+// records 18.8 / 18.6, 19.8 / 19.2, 20.7 / 19.7, 21.6 / 20.3, as two tensors, of 65 536, 20.8 / 20.7; sessions on 1 M slots, 50 000 positions, 330 / 324, on
+// 300 000 448 / 371; loads of new ids into 3 M 231 / 229, 242 / 241, 264 / 259, 287 / 279; LRU, windows of 9, 80 M slots as records, of 50 000, 20.6 /
+// 20.2; 72 000 positions, LRU, 80 M slots as two tensors 22.7 / 22.9, as records 24.2 / 23.2.
+constexpr int64_t kL2Slots = (int64_t)1 << 21;
+constexpr bool whole_windows(int64_t groups, int num_cus, const TableDesc &t)
+{
+    if (window_shift(t.P) != 1 || groups > num_cus) return false;
+    const bool cached = (t.N << (3 + t.sh)) <= kCachedTableBytes;
+    return 2 * groups <= num_cus || (cached ? !t.sh && t.evict != 0 && t.N >= kL2Slots : t.evict == 2 && t.P > 9);
+}
 
 // One-chunk calls whose first look is at the aligned block that holds the home slot: one line an id, and a second look where the id is
 // not in its part of the window.  In tables beyond the memory-side cache all of them (see k_allocate).  Otherwise the 8 slots from the home slot
@@ -601,7 +615,7 @@ mpzch_status_t launch_remap_chunks(Timing &tm, const Params &p, int32_t max_p_lr
     const bool rec = p.t0.sh != 0;
     const bool aligned = aligned_first(grid, num_cus, p.t0);
     if (!tm.begin(KDiscover, s)) return MPZCH_ERR_HIP;
-    if (whole_windows(grid, num_cus, p.t0.P)) TRY((launch_discover_chunk<1, false, true, false, false>(p, grid, s)));
+    if (whole_windows(grid, num_cus, p.t0)) TRY((launch_discover_chunk<1, false, true, false, false>(p, grid, s)));
     else if (even_looks(grid, num_cus, p.t0)) TRY((launch_discover_chunk<true, false, true>(p, grid, aligned, s)));
     else if (grid < num_cus) TRY((launch_discover_chunk<false, true, false>(p, grid, aligned, s)));
     else if (overlap_insert(grid, num_cus, rec)) TRY((launch_discover_chunk<false, true, true>(p, grid, aligned, s)));

@@ -802,3 +802,22 @@ def test_segments_of_several_features(per, empty, layout):
         jp.step(vals, np.concatenate([[0], np.cumsum(counts)]).astype(np.int64), 2 * step)
     jp.check_state()
     jp.close()
+
+
+# ---- calls of up to one workgroup per compute unit whose windows of 9 to 16 slots are read whole, and those a position, a slot of the table or
+# of the window beyond: two tensors from 2^21 slots on, LRU tables of more than 256 MiB.  Homes at the table's end and in one region of it that
+# fills up, so that windows go round the end, and are full
+@pytest.mark.parametrize("layout,evict,slots,probe", [
+    ("separate", True, (1 << 21) - 1, 16), ("separate", True, 1 << 21, 16), ("separate", "expiry", 1 << 21, 9), ("separate", "lru", 1 << 21, 13),
+    ("separate", False, 1 << 21, 16), ("separate", "lru", (1 << 25) + 1, 10), ("separate", True, (1 << 25) + 1, 16), ("records", "lru", 1 << 24, 16),
+    ("records", "lru", (1 << 24) + 1, 16), ("records", "lru", (1 << 24) + 1, 9)])
+def test_calls_around_the_lines_of_whole_windows(layout, evict, slots, probe):
+    rng = rng_for(953 + probe)
+    n = torch.cuda.get_device_properties(0).multi_processor_count * 256
+    t = Pair(slots, probe, 1, evict, 67, layout=layout)
+    for step, more in enumerate([0, 1, 0, 1]):
+        ids = wl.zipf_ids(rng, n + more, 1.05, 2 * n) + step * n // 8
+        ids[: n // 2] = ids_with_home(rng, n // 2, 4_000, 4_000 + n // 2, slots, 67)
+        ids[n // 2: n // 2 + 2_000] = ids_with_home(rng, 2_000, slots - 700, slots, slots, 67)
+        t.step(ids, 2 * step + 1, check_state=step == 3, ttls=rng.integers(0, 5, size=n + more).astype(np.int32) if evict == "expiry" else None)
+    t.close()
