@@ -555,21 +555,21 @@ mpzch_status_t launch_allocate_chunk(const Params &p, int grid, int num_cus, hip
 // Calls whose first looks go before the later ones (k_discover_chunk): windows of up to 32 slots, more than three workgroups per
 // compute unit, and no more than leave the even end something to give.  In a table that the memory-side cache holds looks are
 // short: up to four.  Beyond the cache five, of records, which need more registers, four; under the LRU policy, whose full windows make
-// long chains of looks, six and five.  Whole steps without / with, us, of 200 K 230 K 262 144 300 007 400 K positions, each table as two
-// tensors and as records:
-//   150 M slots, TTL, 70 % load, of 16   34.9/34.2 38.5/37.7 40.2/39.7 44.6/44.9 55.5/57.3   34.2/33.8 36.6/36.7 39.7/40.5 43.3/44.8 55.0/58.9
-//   60 M slots, TTL, 95 %, of 32         48.3/47.6 54.2/52.9 59.4/58.8 69.7/72.1 96.1/103.8  51.5/50.6 55.8/54.5 61.7/61.1 70.3/70.0 93.5/97.1
-//   60 M slots, LRU, 95 %, of 32         34.6/32.9 37.3/36.2 38.8/36.7 42.9/41.8 52.7/51.5   35.1/34.2 37.2/37.0 41.0/40.0 45.6/44.2 53.9/54.6
-//   20 M slots, TTL, 95 %, of 32         58.3/60.0 65.6/67.7 72.9/78.4 83.7/92.2 120/132     (records: beyond the cache)
-//   20 M slots, LRU, 95 %, of 32         32.7/31.9 35.5/34.4 36.9/36.1 41.1/40.9 49.5/50.3
-// and of 210 K 262 144 300 007 400 K 520 K, tables of 200 (beyond the cache), 50 and 16 (in it) slots a position:
-//   200, TTL, 95 %, of 32                37.1/35.5 40.3/38.3 45.2/43.8 56.6/55.3 68.6/68.9   37.8/37.4 41.9/41.5 46.6/46.5 58.8/60.2 71.2/74.5
-//   50, LRU, full, of 32                 35.4/34.7 40.5/40.9 44.1/44.5 57.8/63.0 71.8/79.9   41.2/40.8 46.6/47.4 52.8/55.7 63.1/65.8 77.5/78.8
-//   16, LRU, full, of 16                 31.2/30.6 34.6/34.6 38.2/38.7 44.7/45.5 52.7/54.4   33.5/33.0 37.4/37.3 42.3/42.5 50.5/50.7 60.7/62.1
+// long chains of looks, one more, but over two tensors with windows of more than 16 slots.  Whole steps with a tenth of the ids new, without /
+// with, us, of 230 K 262 144 300 007 330 K 393 216 480 K positions, each table as two tensors and as records:
+//   60 M slots, TTL, 90 % load, of 16  42.8/41.7 45.2/43.2 48.0/46.5 50.5/47.4 58.2/53.7 65.8/62.5  41.5/40.5 44.2/42.1 47.0/45.6 49.8/46.8 57.3/53.0 65.1/63.5
+//   60 M slots, TTL, 90 %, of 32       43.2/41.6 45.6/43.1 48.4/46.4 50.7/47.5 58.5/54.2 66.4/64.1  41.9/40.6 44.4/41.5 47.2/45.3 49.6/47.6 57.3/54.9 65.0/66.0
+//   300 M slots, TTL, 95 %, of 24      43.1/41.8 46.1/43.8 48.4/46.4 50.7/47.5 58.1/54.3 65.8/63.2  41.8/41.7 44.7/43.4 47.3/45.3 49.6/48.4 57.2/57.5 64.9/67.3
+//   60 M slots, LRU, full, of 16       35.8/35.2 38.4/37.5 41.8/41.3 44.0/43.5 50.5/50.6 58.2/60.1  38.6/38.8 42.0/41.7 45.7/45.0 48.0/47.4 54.2/54.8 62.5/66.4
+//   300 M slots, LRU, full, of 24      38.2/37.1 41.1/39.5 44.9/45.0 47.3/48.0 54.0/57.0 63.0/67.8  41.4/41.0 45.0/44.2 49.0/49.9 51.9/54.4 59.3/63.0 68.7/73.5
+// (TTL tables would gain beyond their lines as well, but calls of new ids lose there: half of the ids new, 300 M slots as two tensors, 400 K
+// 68.6/70.6, 500 K 81.9/85.5, nearly all 97.2/102.4, 115.5/122.9, as records, 300 K, 73.2/76.1.)
+// In the cache (20 M slots as two tensors, 10 M as records), 262 144 positions: TTL, of 24, 43.3/42.2, records 39.1/39.3, LRU, of 32, 43.5/43.3,
+// records 48.9/48.5; sessions of eight steps of 200 000 on 2 M slots 450/438, records 421/421, loads of new ids 341/347, records 344/346.
 constexpr bool even_looks(int64_t groups, int num_cus, const TableDesc &t)
 {
     const bool cached = (t.N << (3 + t.sh)) <= kCachedTableBytes;
-    const int most = cached ? 4 : 5 - (t.sh ? 1 : 0) + (t.evict == 2 ? 1 : 0);
+    const int most = cached ? 4 : 5 - (t.sh ? 1 : 0) + (t.evict == 2 && (t.sh || t.P <= 16) ? 1 : 0);
     return t.P <= 32 && groups > 3 * (int64_t)num_cus && groups <= (int64_t)most * num_cus;
 }
 

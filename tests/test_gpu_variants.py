@@ -821,3 +821,18 @@ def test_calls_around_the_lines_of_whole_windows(layout, evict, slots, probe):
         ids[n // 2: n // 2 + 2_000] = ids_with_home(rng, 2_000, slots - 700, slots, slots, 67)
         t.step(ids, 2 * step + 1, check_state=step == 3, ttls=rng.integers(0, 5, size=n + more).astype(np.int32) if evict == "expiry" else None)
     t.close()
+
+
+# ---- the lines of even looks that windows draw: LRU tables over two tensors, of 16 slots and of one more
+@pytest.mark.parametrize("groups,probe", [(6, 16), (5, 17)])
+def test_calls_around_the_lines_of_even_looks_by_window(groups, probe):
+    rng = rng_for(957 + probe)
+    n = groups * torch.cuda.get_device_properties(0).multi_processor_count * 256
+    slots = (1 << 25) + 1
+    t = Pair(slots, probe, 1, "lru", 71)
+    for step, more in enumerate([0, 1, 0]):
+        ids = wl.zipf_ids(rng, n + more, 1.05, 2 * n) + step * n // 8
+        ids[: n // 2] = ids_with_home(rng, n // 2, 4_000, 4_000 + n // 2, slots, 71)
+        ids[n // 2: n // 2 + 2_000] = ids_with_home(rng, 2_000, slots - 700, slots, slots, 71)
+        t.step(ids, 2 * step + 1, check_state=step == 2)
+    t.close()
