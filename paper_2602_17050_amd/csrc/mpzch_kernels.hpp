@@ -1121,10 +1121,13 @@ __device__ __forceinline__ void discover_body(const Params &p)
         if (!active) return;
         if (COUNT) st_probe += (unsigned long long)(dist + 1);
         if (emit) {
-            // (non-temporal, as are the few that k_finalize rewrites: kept in the L2, such a word is a line of it that nobody reads.
-            // Both so, us: 41.6 M values over 26 tables 1 257 -> 1 234, 22 M 713 -> 692, 4 M over 8 154 -> 148, 1.2 M over 22 154 ->
-            // 143.5; one table, 0.84 M under LRU 116.9 -> 112, 4 M 288.3 -> 287.1; lookups of 1 M 13.8 -> 13.4, of 0.44 M over 15
-            // tables 14.1 -> 13.7.  Not in calls of one chunk: 51 of 65 536 positions 906 -> 923.)
+            // (Non-temporal, as are the few that k_finalize rewrites: kept in the L2, such a word is a line of it that the call does not read
+            // again.  Both so, us: 41.6 M values over 26 tables 1 266 -> 1 243, 22 M 720 -> 706, 5.6 M 240 -> 237, 1.2 M over 22 79.1 -> 78.3;
+            // one table, 3 M positions under LRU 304 -> 295, 4 M 290 -> 289, 0.54 M 61.2 -> 60.7; lookups of 1 M 13.4 -> 13.1, of 0.44 M 8.53 ->
+            // 8.41.  What the next kernel of the caller pays for it, the same with a copy of out_slots behind each call: groups 1 412 -> 1 387,
+            // 805 -> 793, 262.3 -> 261.9, 84.7 -> 83.9; one table 318 -> 312, 308.5 -> 310, 64.8 -> 64.4, but 2 M on 500 M slots 178.8 -> 181.1 and
+            // 2 M on 30 M 150.8 -> 152.2; lookups 18.2 -> 18.0, 11.24 -> 11.18, 4 M 64.5 -> 64.4.  With the rows gathered by them all are
+            // within 0.3 %, LRU 944 -> 937.  Not in calls of one chunk: 51 of 65 536 positions 906 -> 923.)
             if (!GATHER || p.out_slots) __builtin_nontemporal_store(slot, &p.out_slots[pos]);
             if (!TRAIN && p.out_found) p.out_found[pos] = 1;
         }
