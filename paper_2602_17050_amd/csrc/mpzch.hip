@@ -1462,7 +1462,9 @@ mpzch_status_t mpzch_reset_rows_jagged(mpzch_group_t *g, const int64_t *evicted_
     hipStream_t s = (hipStream_t)stream;
     TRY(g->sc.query_device());
     TRY(g->rows.put(descs, s));
-    // (eight workgroups per compute unit: 10 400 values over 26 tables, the whole step, 36.7 us against 35.6 with two; 41.6 M the same with four)
+    // (Two / four / eight workgroups per compute unit, whole steps over 26 tables, us: 10 400 values 33.6 / 33.7 / 33.8, 81 K 38.1 / 38.2 / 38.2,
+    // 0.64 M 61.2 / 61.4 / 61.5, 2.5 M 131.9 / 131.7 / 131.7, 10.4 M 371.1 / 371.2 / 370.5, 41.6 M 1 238 / 1 237 / 1 237: hardly any difference.  Four,
+    // so that rows of several segments are under way in a compute unit, and small steps do not start what they have no use for.)
     TRY(launch(k_reset_rows_jagged, g->sc.num_cus * 4, kBlock, s, evicted_slots, num_evicted, g->rows.dev, T));
     return MPZCH_OK;
 }

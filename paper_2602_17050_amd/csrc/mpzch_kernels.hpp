@@ -473,6 +473,9 @@ __device__ __forceinline__ uint32_t set_insert_from(const Params &p, int64_t id,
 // enough for a batch of new ids, but of nearly every batch a tenth or less is new, and spread over all of it each id is a line of its
 // own, fetched and written back three times (entered, read, emptied): 333 MB of them for 41.6 M values, more than the memory-side cache
 // holds.  (Three quarters have 1.5 entries for each position of the region, so the rest never fills up.)
+// The question whether there is a front costs the calls without one up to 0.3 %, groups up to 1 %: without / with it, us, one table, 0.54 M
+// positions 60.9 / 61.0, 1.2 M 95.2 / 95.3, 1.9 M 183.6 / 183.8; 26 tables, 0.33 M values 51.1 / 50.9, 0.64 M 63.4 / 63.8, 1.1 M 82.5 / 83.3, 2.5 M
+// 131.7 / 132.5, 5.6 M 238.5 / 239.4.  (Entries in 32 bits, which take back half of the scalar registers that it needs, are no faster.)
 template <bool NOTE>
 __device__ __forceinline__ uint32_t set_insert(const Params &p, int64_t id, uint64_t hash, uint32_t pos, uint64_t base, uint64_t size,
                                                bool notes = NOTE)
@@ -1975,6 +1978,9 @@ __device__ __forceinline__ void allocate_body(const Params &p, int64_t vblock, i
     add_outcomes<MULTI>(p, outcomes);
 }
 
+// Two tensors, one table: six wavefronts per SIMD, for the walk in step takes 73 registers.  At seven two go to memory; whole steps, seven / six, us:
+// 540 K positions on 20 M slots 59.6 / 59.0, 2 M on 500 M 170.2 / 169.0, 2.5 M on 30 M 247.2 / 245.3, 600 K on 5 M, half of them new, 207.9 / 206.5, 840 K and
+// 1.2 M, of which a tenth or a fifth is new, the same to 0.4 %.
 template <bool MULTI, bool REC>
 __global__ __launch_bounds__(kWave, MULTI ? 5 : REC ? 7 : 6) void k_allocate(Params p)
 {
@@ -2697,8 +2703,8 @@ __device__ __forceinline__ void finalize_body(const Params &p)
     list_evicted(p, staged, s_ev, s_row, s_cnt, s_tab, &s_base, s_desc);
 }
 
-// WAVES = 8 wavefronts per SIMD (one table: 46 vector registers and 66 KB of LDS for 16 wavefronts, several: 56 and 40 KB; no
-// vector register goes to memory, 67 to 78 scalar ones are kept in lanes of vector registers), so that
+// WAVES = 8 wavefronts per SIMD (one table: 47 vector registers and 66 KB of LDS for 16 wavefronts, several: 61 and 44 KB, 4 of them the
+// descriptors; no vector register goes to memory, 67 to 76 scalar ones are kept in lanes of vector registers), so that
 // the 8 192 wavefronts, each a chain of three round trips, run in one go.  (Several tables with 66 registers and the rows'
 // buffer that only one table has use for: one workgroup per compute unit and two turns, 41 M values over 26 tables 152 -> 145
 // us.)  A batch of 4 M positions, 10 % of them new, with
@@ -2706,7 +2712,7 @@ __device__ __forceinline__ void finalize_body(const Params &p)
 // metadata of a record, and rows reset before the workgroup's barrier instead of behind it, 45.5 -> 41 us by the claims that
 // need no look; 41 M values over 26 tables
 // 242 -> 178 us.
-// WAVES = 4, several tables: more scalar registers, 40 kept in vector lanes, which is time that the chain of a small call
+// WAVES = 4, several tables: more scalar registers, 38 kept in vector lanes, which is time that the chain of a small call
 // sees: steps of 600 values over 2 tables 35.6 -> 34.8 us, 10 400 over 26 41.4 -> 40.6.
 template <bool MULTI, bool NOTES, int WAVES = 8>
 __global__ __launch_bounds__(kFinalizeBlock, WAVES) void k_finalize(Params p)
