@@ -836,3 +836,50 @@ def test_calls_around_the_lines_of_even_looks_by_window(groups, probe):
         ids[n // 2: n // 2 + 2_000] = ids_with_home(rng, 2_000, slots - 700, slots, slots, 71)
         t.step(ids, 2 * step + 1, check_state=step == 2)
     t.close()
+
+
+def ids_of_hash(hashes, seed):
+    """The ids that the library's hash takes to `hashes` (uint64): the hash undone.  Some are negative."""
+    unxor = lambda x, s: x ^ (x >> np.uint64(s)) ^ (x >> np.uint64(2 * s))
+    with np.errstate(over="ignore"):
+        x = unxor(hashes, 31) * np.uint64(pow(0x94D049BB133111EB, -1, 1 << 64))
+        x = unxor(x, 27) * np.uint64(pow(0xBF58476D1CE4E5B9, -1, 1 << 64))
+        return ((unxor(x, 30) - np.uint64(0x9E3779B97F4A7C15)) ^ np.uint64(seed)).view(np.int64)
+
+
+# ---- a look at the scratch set that goes round its end: several dozen ids whose first tries are the last entries of it (four for each position, by the
+# low word of the hash), spread over wavefronts of new ids, with copies in other workgroups.  They fill the last eight entries and as many at the
+# front as are left of them, so that looks begin in each of the last entries, find the rest full, and go on for several steps behind the end
+@pytest.mark.parametrize("layout,evict", [("separate", False), ("records", True), ("records", "lru")])
+@pytest.mark.parametrize("more,crowd", [(0, 12), (37, 60), (64 * 129 + 1, 250)])
+def test_collisions_at_the_end_of_the_scratch_set(layout, evict, more, crowd):
+    rng = rng_for(961 + crowd)
+    n = torch.cuda.get_device_properties(0).multi_processor_count * 256 + more
+    size = 4 * n
+    t = Pair(2 * n, 24, 0, evict, 73, layout=layout)
+    for step in (0, 2):
+        ids = rng.integers(0, 1 << 40, size=n)
+        last = np.empty(0, dtype=np.int64)
+        while last.size < crowd:
+            entry = rng.integers(size - 8, size, size=4 * crowd)
+            low = np.array([-(-(int(e) << 32) // size) for e in entry], dtype=np.uint64)      # the first word that leads to the entry
+            high = rng.integers(0, 1 << 32, size=4 * crowd, dtype=np.uint64)
+            x = ids_of_hash(high << np.uint64(32) | low, 73)
+            last = np.unique(np.concatenate([last, x[x >= 0]]))
+        last = rng.permutation(last)[:crowd]
+        # (what the kernel makes of them)
+        low = np.array([(h * size) >> 32 for h in (oracle_hash(int(i), 73) & 0xFFFFFFFF for i in last)])
+        assert low.min() >= size - 8 and low.max() < size and len(np.unique(low)) > 4
+        at = rng.permutation(n)[: 3 * crowd]
+        ids[at] = np.tile(last, 3)
+        t.step(ids, step)
+    t.close()
+
+
+def oracle_hash(i, seed):
+    """SplitMix64's finalizer over (id xor seed) plus its increment, in whole numbers."""
+    m = (1 << 64) - 1
+    z = ((i ^ seed) + 0x9E3779B97F4A7C15) & m
+    z = (z ^ z >> 30) * 0xBF58476D1CE4E5B9 & m
+    z = (z ^ z >> 27) * 0x94D049BB133111EB & m
+    return z ^ z >> 31
