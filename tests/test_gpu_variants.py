@@ -851,7 +851,7 @@ def ids_of_hash(hashes, seed):
 # low word of the hash), spread over wavefronts of new ids, with copies in other workgroups.  They fill the last eight entries and as many at the
 # front as are left of them, so that looks begin in each of the last entries, find the rest full, and go on for several steps behind the end
 @pytest.mark.parametrize("layout,evict", [("separate", False), ("records", True), ("records", "lru")])
-@pytest.mark.parametrize("more,crowd", [(0, 12), (37, 60), (64 * 129 + 1, 250)])
+@pytest.mark.parametrize("more,crowd", [(0, 24), (37, 60), (64 * 129 + 1, 250)])
 def test_collisions_at_the_end_of_the_scratch_set(layout, evict, more, crowd):
     rng = rng_for(961 + crowd)
     n = torch.cuda.get_device_properties(0).multi_processor_count * 256 + more
