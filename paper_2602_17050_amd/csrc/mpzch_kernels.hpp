@@ -385,6 +385,31 @@ __device__ __forceinline__ Tab uniform(const Tab &d)
     return t;
 }
 
+// find_table for a position of a segment that begins in table f, without a look at the memory: one comparison for every table that begins
+// before the segment's `end`.  (In k_allocate_lru the lanes' offsets cost more registers than the search costs time: 8 x 100 000 values in LRU
+// tables of records 664 -> 691 us for six steps.)
+__device__ __forceinline__ int find_table_from(int64_t lane_offset, int num_tables, int f, int64_t end, int64_t pos)
+{
+    for (int k = f + 1; k < num_tables; ++k) {
+        const int64_t begin = readlane64(lane_offset, k);
+        if (begin >= end) break;
+        if (begin <= pos) f = k;
+    }
+    return f;
+}
+
+// The descriptors of a group, in LDS: to be reached by all `threads` of the workgroup.  (Segments of short features belong to several tables, one after
+// the other, and each change waited for a descriptor, each position for a search through the offsets in memory, each list of
+// evicted slots for its place.  With the lanes' offsets and a copy of the descriptors, whole steps, us: 26 tables with 10 400 values 36.5 -> 35.4, with
+// 320 K 50.2 -> 49.0, 4 with 20 K 32.7 -> 32.4, 26 with 1.1 M 74.5 -> 73.4, 41.6 M values the same.)
+__device__ __forceinline__ void copy_descs(const Params &p, TableDesc *s_desc, int threads)
+{
+    const uint64_t *src = reinterpret_cast<const uint64_t *>(p.descs);
+    uint64_t *dst = reinterpret_cast<uint64_t *>(s_desc);
+    for (int i = threadIdx.x; i < p.num_tables * (int)(sizeof(TableDesc) / 8); i += threads) dst[i] = src[i];
+    __syncthreads();
+}
+
 // Metadata written for the id at batch position pos: the step (last seen), or with per-feature TTL
 // (Sec. 3.4) the step after which the id is expired: now + duration of its feature.
 __device__ __forceinline__ int32_t meta_value(const Params &p, const Tab &d, int64_t pos)
@@ -1082,10 +1107,7 @@ __device__ __forceinline__ void discover_body(const Params &p)
     int64_t lane_offset = 0;
     if constexpr (multi) {
         lane_offset = table_offsets(p.offsets, p.num_tables);
-        const uint64_t *src = reinterpret_cast<const uint64_t *>(p.descs);
-        uint64_t *dst = reinterpret_cast<uint64_t *>(s_desc);
-        for (int i = threadIdx.x; i < p.num_tables * (int)(sizeof(TableDesc) / 8); i += kBlock) dst[i] = src[i];
-        __syncthreads();
+        copy_descs(p, s_desc, kBlock);
     }
     // hands the counters of the present table over (when the table changes inside this wavefront's range)
     auto hand_over = [&]() {
@@ -1417,16 +1439,8 @@ __global__ __launch_bounds__(kBlock, 4) void k_lookup_short(LookupArgs<MULTI, GA
     int f = 0;
     if constexpr (MULTI) {
         const int64_t lane_offset = table_offsets(p.offsets, p.num_tables);
-        const uint64_t *src = reinterpret_cast<const uint64_t *>(p.descs);
-        uint64_t *dst = reinterpret_cast<uint64_t *>(s_desc);
-        for (int i = threadIdx.x; i < p.num_tables * (int)(sizeof(TableDesc) / 8); i += kBlock) dst[i] = src[i];
-        __syncthreads();
-        f = find_table_wave(lane_offset, pos0);
-        for (int k = f + 1; k < p.num_tables; ++k) {
-            const int64_t begin = readlane64(lane_offset, k);
-            if (begin >= pos0 + per) break;
-            if (begin <= pos) f = k;
-        }
+        copy_descs(p, s_desc, kBlock);
+        f = find_table_from(lane_offset, p.num_tables, find_table_wave(lane_offset, pos0), pos0 + per, pos);
         d = view(s_desc[f]);
     }
     const int64_t home = home_slot(id, d.seed, d.N);
@@ -1507,16 +1521,8 @@ __global__ __launch_bounds__(kBlock, 4) void k_discover_tables_chunk(Params p)
     const bool in = pos < n;
     const int64_t id = in ? p.ids[pos] : -1;
     const int64_t lane_offset = table_offsets(p.offsets, p.num_tables);
-    const uint64_t *src = reinterpret_cast<const uint64_t *>(p.descs);
-    uint64_t *dst = reinterpret_cast<uint64_t *>(s_desc);
-    for (int i = threadIdx.x; i < p.num_tables * (int)(sizeof(TableDesc) / 8); i += kBlock) dst[i] = src[i];
-    __syncthreads();
-    int f = find_table_wave(lane_offset, pos0);
-    for (int k = f + 1; k < p.num_tables; ++k) {
-        const int64_t begin = readlane64(lane_offset, k);
-        if (begin >= pos0 + kWave) break;
-        if (begin <= pos) f = k;
-    }
+    copy_descs(p, s_desc, kBlock);
+    const int f = find_table_from(lane_offset, p.num_tables, find_table_wave(lane_offset, pos0), pos0 + kWave, pos);
     const Tab d = view(s_desc[f]);
     const int64_t home = home_slot(id, d.seed, d.N);
     const bool valid = in && id >= 0;
@@ -1588,19 +1594,6 @@ __global__ __launch_bounds__(kBlock, 4) void k_discover_tables_chunk(Params p)
         m &= ~of_table;
     }
     if constexpr (OVERLAP) finish();
-}
-
-// find_table for a position of a segment that begins in table f, without a look at the memory: one comparison for every table that begins
-// before the segment's `end`.  (In k_allocate_lru the lanes' offsets cost more registers than the search costs time: 8 x 100 000 values in LRU
-// tables of records 664 -> 691 us for six steps.)
-__device__ __forceinline__ int find_table_from(int64_t lane_offset, int num_tables, int f, int64_t end, int64_t pos)
-{
-    for (int k = f + 1; k < num_tables; ++k) {
-        const int64_t begin = readlane64(lane_offset, k);
-        if (begin >= end) break;
-        if (begin <= pos) f = k;
-    }
-    return f;
 }
 
 // Several tables: the table of a whole segment of positions [seg_base, seg_base + seg_len), when one
@@ -1855,18 +1848,6 @@ __device__ __forceinline__ void claim_walk(const Tab &d, Claimant &c, const Clai
     }
     if (state == kLost) lost(c.pos);
     c.active = state == kWalks || state == kWaits;
-}
-
-// The descriptors of a group, in LDS: to be reached by all `threads` of the workgroup.  (Segments of short features belong to several tables, one after
-// the other, and each change waited for a descriptor, each position for a search through the offsets in memory, each list of
-// evicted slots for its place.  With the lanes' offsets and a copy of the descriptors, whole steps, us: 26 tables with 10 400 values 36.5 -> 35.4, with
-// 320 K 50.2 -> 49.0, 4 with 20 K 32.7 -> 32.4, 26 with 1.1 M 74.5 -> 73.4, 41.6 M values the same.)
-__device__ __forceinline__ void copy_descs(const Params &p, TableDesc *s_desc, int threads)
-{
-    const uint64_t *src = reinterpret_cast<const uint64_t *>(p.descs);
-    uint64_t *dst = reinterpret_cast<uint64_t *>(s_desc);
-    for (int i = threadIdx.x; i < p.num_tables * (int)(sizeof(TableDesc) / 8); i += threads) dst[i] = src[i];
-    __syncthreads();
 }
 
 // One wavefront serves the segments vblock, vblock + vgrid, ...; s_code and s_req are its own areas of LDS.  REC: every
