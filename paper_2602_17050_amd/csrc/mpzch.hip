@@ -309,9 +309,16 @@ int lookup_grid(int64_t n, int num_cus)
 }
 
 // Calls whose stores go out while the compare-and-swap of the scratch set is under way (k_discover_chunk): up to four workgroups per
-// compute unit, of records two.  Beyond, the stores of the others are in the way of it.  Whole calls, behind / beside it, TTL,
-// windows of 64 unless said, us: two tensors 200 K positions 27.3 / 27.1, 262 144 30.9 / 30.7, 300 007 33.3 / 33.8; 262 144 new ids 55.4 / 54.9;
-// records 100 K (of 32) 21.6 / 21.3, 150 K (of 32, expiry steps) 28.4 / 28.7, 200 K 30.9 / 31.0, 230 K 33.0 / 33.3.
+// compute unit, of records two.  Beyond, the stores of the others are in the way of it.  Whole calls, behind / beside it, us, of 66 K 100 K 131 K
+// 150 K 200 K 240 K 262 144 300 007 positions; steps in steady state with a tenth of the ids new, sessions of 12 steps on 1 M slots, loads of new ids:
+//   records, 10 M slots, TTL, of 64   20.6/20.5 22.8/22.6 24.1/23.9 26.8/26.9 30.7/30.7 33.7/33.8 35.0/35.2 39.3/39.6
+//   records, 80 M slots, TTL, of 24   20.4/20.1 22.6/22.4 23.6/23.5 25.9/26.2 30.0/30.3 33.6/34.1 35.4/35.9 39.8/39.2
+//   records, sessions, TTL, of 64     250/249 288/285 319/317 348/346 397/397 438/436 471/467 518/520   loads 187/185 226/224 276/273 291/289 354/351 398/394 434/430
+//   tensors, 20 M slots, TTL, of 64   20.7/20.3 23.1/22.9 24.6/24.4 26.8/26.8 30.3/30.3 33.8/33.9 36.5/36.2 40.8/40.5
+//   tensors, 80 M slots, TTL, of 24   20.9/20.6 23.0/22.8 24.2/24.2 26.4/26.8 30.8/30.9 34.8/35.0 36.3/36.6 40.6/40.8
+//   tensors, sessions, TTL, of 64     247/244 291/288 322/318 351/349 402/400 443/442 470/470 515/516   loads 188/186 225/222 276/272 282/281 349/346 393/391 428/425
+// (Expiry steps, whose stores have barriers between them, lose where tables have room, sessions of 12 on 4 M slots, windows of 40, 66 K 567 / 573, 131 K
+// 678 / 684, records 568 / 577, 675 / 693, and gain where they are crowded, on 1 M, of 16, 131 K 596 / 580, 180 K 729 / 688, records 609 / 584.)
 constexpr bool overlap_insert(int64_t groups, int num_cus, bool records) { return groups <= (records ? 2 : 4) * (int64_t)num_cus; }
 
 // The longest windows, min(max_probe, num_slots), of the tables involved: of those under the LRU policy and of the others; 0 where
@@ -598,11 +605,17 @@ constexpr bool whole_windows(int64_t groups, int num_cus, const TableDesc &t)
 // not in its part of the window.  In tables beyond the memory-side cache all of them (see k_allocate).  Otherwise the 8 slots from the home slot
 // on, which are two lines of records and one and a half of two tensors, decide more of the ids, and only calls with enough
 // workgroups for the lines to count do better without: from one per compute unit on over records, from two and a half over two tensors.
-// From the home slot on / aligned, us: records, 51 steps of 65 536 positions, windows of 16, 883 / 860; sessions of eight steps on 1 M slots,
-// windows of 16, 48 000 positions 351 / 350, 66 000 367 / 366, 80 000 408 / 400, of 24 361 / 363, 376 / 378, 388 / 389, of 64 406 / 406, 425 /
-// 422, 434 / 433; of six, of 16, 200 000 515 / 502, of 32 453 / 443; new ids into 3 M slots, 262 144 a call 315 / 305, 200 000, of 64, 759 /
-// 733.  Two tensors, of 16, 131 000 482 / 482, new ids, 160 000 a call 357 / 353, 200 000 340 / 338, 262 144, of 64, 683 / 677.  (Windows of up to 8 slots, which a
-// look from the home slot on decides: 66 000 366 / 373, 131 000 452 / 456.)
+// From the home slot on / aligned, us, 49 K 57 K 65 536 72 K 80 K 100 K 131 K 160 K 200 K positions; steps in steady state, sessions of 12 steps on
+// 1 M slots, which the L2 holds, loads of new ids into 3 M:
+//   records, 10 M slots, TTL, of 24   20.8/18.6 20.6/19.0 20.2/19.4 21.6/19.9 21.5/20.2 22.8/21.2 24.7/23.0 27.2/25.0 30.1/27.2
+//   records, 10 M slots, LRU, of 16   22.1/20.9 22.1/21.6 22.8/22.7 23.0/22.9 23.6/23.3 25.0/24.6 27.8/27.0 30.8/29.8 34.4/32.0
+//   records, sessions, TTL, of 16     224/238 232/239 241/245 250/253 260/260 283/280 309/307 341/344 384/374
+//   ... of 24                         225/241 233/242 243/249 253/257 261/265 286/284 312/313 348/353 399/387
+//   records, loads, of 16             171/172 181/181 189/186 200/197 205/203 226/222 281/271 304/295 357/345
+//   tensors, from 100 K: 20 M slots, TTL, of 24, 22.4/21.4 24.0/23.3 26.1/25.1 29.2/27.9; LRU, of 16, 23.5/23.3 25.8/25.9 28.3/27.9 31.3/30.5; sessions, TTL, of 24, 289/287
+//   317/322 356/358 400/399; loads, of 16, 221/221 272/271 288/287 350/348
+// (Fuller sessions, filled to 0.3 before, gain from 65 536 records on: 51 steps of that many 883 / 860.)  Windows of up to 8 slots, which a look from the
+// home slot on decides, have it in all of them: sessions, records, 57 K 228 / 242, 72 K 248 / 249, 160 K 330 / 333.
 constexpr bool aligned_first(int64_t groups, int num_cus, const TableDesc &t)
 {
     if ((t.N << (3 + t.sh)) > kCachedTableBytes) return true;
