@@ -143,7 +143,7 @@ __global__ __launch_bounds__(kOneBlock) void k_remap_block(Params p)
         const uint64_t am = __ballot(cl.active);
         if (!am) break;
         const ClaimStage st = claim_blocks<REC>(d, cl, am, blocks_shift(uniform32(__popcll(am)), d.P), bound, false, s.code[w], s.req[w]);
-        claim_walk<32>(d, cl, st, s.code[w], s.req[w], claim_in_map,
+        claim_walk<32, 1>(d, cl, st, s.code[w], s.req[w], claim_in_map,
                    [&](uint32_t who, int32_t round, int64_t at, int64_t old) {
                        atomicMax(&s.place[who], (uint32_t)round + 1u);
                        outcome = old == -1 ? 1u : old >= 0 ? 2u : 0u;

@@ -360,7 +360,7 @@ __global__ __launch_bounds__(kBlock, 4) void k_allocate_chunk(Params p)
         const ClaimStage st = claim_blocks<REC>(d, c, am, later || !aligned ? blocks_shift(uniform32(__popcll(am)), d.P) : 0, bound,
                                                 aligned && !later, s_code[w], s_req[w]);
         if (!later) c.active = c.active && first == (uint32_t)pos;      // else: a later copy of the id
-        claim_walk<16>(d, c, st, s_code[w], s_req[w], claim_in_table,
+        claim_walk<16, 2>(d, c, st, s_code[w], s_req[w], claim_in_table,
                    [&](uint32_t who, int32_t round, int64_t at, int64_t old) {
                        if (who == (uint32_t)pos) own = (uint32_t)round + 1u;
                        else note_place(p, who, (uint32_t)round + 1u);

@@ -1774,13 +1774,18 @@ __device__ __forceinline__ ClaimStage claim_blocks(const Tab &d, const Claimant 
 // number that it carries.  A claim is a round trip and what lies between two of them, which was a third of it: a loop per
 // word and lane that ended in five places kept its lanes and their outcomes in masks, some 60 scalar instructions each time around, and
 // those that had come to the next word waited for the others.  And where windows are longer than LEAVE slots (0: never) the walk ends
-// when, after its first claims, more lanes wait for the next stage than walk: those go on there too, with what others have claimed
-// meanwhile.  Before / in step / and left early, us: 12 calls of 262 144 new ids 722 / 704 / 686, two of 126 000 and 83 000 into a table of
+// when, after its first claims, more than WAITS times as many lanes wait for the next stage as walk: those go on there too, with what others have
+// claimed meanwhile.  Before / in step / and left early, us: 12 calls of 262 144 new ids 722 / 704 / 686, two of 126 000 and 83 000 into a table of
 // 238 000 slots, windows of 256, 163 / 149 / 137, four of 30 000 into 120 000, of 512, 262 / 251 / 202; 51 steps of 65 536 positions 907 /
 // 881, 12 of 20 011 309 / 298, 12 of 50 000 on 100 000 slots of records, windows of 32, 411 / 394 / 378; one workgroup, 12 steps of 1 024
 // 147 / 141.  (The lists of long calls gain nothing by either, crowded ones lose by the second: 600 000 positions on 3 M slots 167.0 /
 // 165.3 / 169.7.)
-template <int LEAVE, typename Claim, typename Placed, typename Lost>
+// WAITS: one in calls of one workgroup, two in those of one chunk for each wavefront.  With more ids than slots most lanes walk to the end of their
+// windows, and what is read again for the others is lost.  Walks not in step / never left / left with one / two / four, us, 20 000 positions on 9 000 slots,
+// windows of 64, 207 / 204 / 212 / 209 / 207, 66 000 on 30 000 258 / 254 / 262 / 260 / 257; otherwise 5 000 on 20 000 217 / 194 / 194 / 192 / 194, 30 000 new
+// ids into 120 000, of 256, 210 / 192 / 172 / 169 / 172, 262 144 into 3 M, of 512, 1 111 / 1 007 / 954 / 954 / 964; one workgroup, 300 on 400, of 200, 845 / - /
+// 766 / 790 / 813.
+template <int LEAVE, int WAITS, typename Claim, typename Placed, typename Lost>
 __device__ __forceinline__ void claim_walk(const Tab &d, Claimant &c, const ClaimStage &st, const uint8_t *s_code,
                                            const ClaimReq *s_req, Claim claim, Placed placed, Lost lost)
 {
@@ -1815,7 +1820,7 @@ __device__ __forceinline__ void claim_walk(const Tab &d, Claimant &c, const Clai
         const uint64_t walking = __ballot(state == kWalks);
         if (!walking) break;
         if (LEAVE != 0 && d.P > LEAVE && claims) {
-            if (__popcll(__ballot(state == kWaits)) > __popcll(walking)) break;
+            if (__popcll(__ballot(state == kWaits)) > WAITS * __popcll(walking)) break;
         }
         claims = true;
         const int bit = __ffsll((unsigned long long)x) - 1;
@@ -1933,7 +1938,7 @@ __device__ __forceinline__ void allocate_body(const Params &p, int64_t vblock, i
                     // what nearly every claimant needs at first)
                     const ClaimStage st = claim_blocks<REC>(d, c, am, later ? blocks_shift(uniform32(__popcll(am)), d.P) : 0, bound,
                                                             aligned && !later, s_code, s_req);
-                    claim_walk<0>(d, c, st, s_code, s_req, claim_in_table,
+                    claim_walk<0, 0>(d, c, st, s_code, s_req, claim_in_table,
                                [&](uint32_t who, int32_t round, int64_t, int64_t old) {
                                    const uint32_t at = round < (int32_t)kHintUnknown ? (uint32_t)round : kHintUnknown;
                                    if (who == pos) {
