@@ -309,7 +309,7 @@ int lookup_grid(int64_t n, int num_cus)
 }
 
 // Calls whose stores go out while the compare-and-swap of the scratch set is under way (k_discover_chunk): up to four workgroups per
-// compute unit, of records two.  Beyond, the stores of the others are in the way of it.  Whole calls, behind / beside it, us, of 66 K 100 K 131 K
+// compute unit, of records two, of expiry steps three.  Beyond, the stores of the others are in the way of it.  Whole calls, behind / beside it, us, of 66 K 100 K 131 K
 // 150 K 200 K 240 K 262 144 300 007 positions; steps in steady state with a tenth of the ids new, sessions of 12 steps on 1 M slots, loads of new ids:
 //   records, 10 M slots, TTL, of 64   20.6/20.5 22.8/22.6 24.1/23.9 26.8/26.9 30.7/30.7 33.7/33.8 35.0/35.2 39.3/39.6
 //   records, 80 M slots, TTL, of 24   20.4/20.1 22.6/22.4 23.6/23.5 25.9/26.2 30.0/30.3 33.6/34.1 35.4/35.9 39.8/39.2
@@ -318,8 +318,12 @@ int lookup_grid(int64_t n, int num_cus)
 //   tensors, 80 M slots, TTL, of 24   20.9/20.6 23.0/22.8 24.2/24.2 26.4/26.8 30.8/30.9 34.8/35.0 36.3/36.6 40.6/40.8
 //   tensors, sessions, TTL, of 64     247/244 291/288 322/318 351/349 402/400 443/442 470/470 515/516   loads 188/186 225/222 276/272 282/281 349/346 393/391 428/425
 // (Expiry steps, whose stores have barriers between them, lose where tables have room, sessions of 12 on 4 M slots, windows of 40, 66 K 567 / 573, 131 K
-// 678 / 684, records 568 / 577, 675 / 693, and gain where they are crowded, on 1 M, of 16, 131 K 596 / 580, 180 K 729 / 688, records 609 / 584.)
-constexpr bool overlap_insert(int64_t groups, int num_cus, bool records) { return groups <= (records ? 2 : 4) * (int64_t)num_cus; }
+// 678 / 684, records 568 / 577, 675 / 693, and gain where they are crowded, on 1 M, of 16, 131 K 596 / 580, 180 K 729 / 688, records 609 / 584;
+// 262 144, windows of 40, on 1 M 762 / 766, on 4 M 911 / 927, of 64, on 1 M, 638 / 646.)
+constexpr bool overlap_insert(int64_t groups, int num_cus, bool records, bool expiry)
+{
+    return groups <= (records ? 2 : expiry ? 3 : 4) * (int64_t)num_cus;
+}
 
 // The longest windows, min(max_probe, num_slots), of the tables involved: of those under the LRU policy and of the others; 0 where
 // there is none.
@@ -355,7 +359,7 @@ constexpr bool tables_by_chunk(int64_t groups, int num_cus, bool records, Window
 mpzch_status_t launch_discover(const Params &p, int grid, int num_cus, Windows windows, hipStream_t s)
 {
     if (p.num_tables > 1 && p.seg_chunks == 1 && tables_by_chunk(grid, num_cus, p.all_records, windows)) {
-        const bool overlap = overlap_insert(grid, num_cus, false);
+        const bool overlap = overlap_insert(grid, num_cus, false, false);
         if (p.all_records && overlap) TRY(launch(k_discover_tables_chunk<true, true>, grid, kBlock, s, p));
         else if (p.all_records) TRY(launch(k_discover_tables_chunk<true, false>, grid, kBlock, s, p));
         else if (overlap) TRY(launch(k_discover_tables_chunk<false, true>, grid, kBlock, s, p));
@@ -536,11 +540,11 @@ mpzch_status_t launch_discover_chunk(const Params &p, int grid, hipStream_t s)
     else TRY(launch(k_discover_chunk<false, SHIFT, EVEN, OVERLAP, ALIGNED, LOOKS>, grid, kBlock << SHIFT, s, p));
     return MPZCH_OK;
 }
-template <bool EVEN, bool OVERLAP, bool LOOKS>
+template <bool OVERLAP, bool LOOKS>
 mpzch_status_t launch_discover_chunk(const Params &p, int grid, bool aligned, hipStream_t s)
 {
-    if (aligned) return launch_discover_chunk<0, EVEN, OVERLAP, true, LOOKS>(p, grid, s);
-    return launch_discover_chunk<0, EVEN, OVERLAP, false, LOOKS>(p, grid, s);
+    if (aligned) return launch_discover_chunk<0, false, OVERLAP, true, LOOKS>(p, grid, s);
+    return launch_discover_chunk<0, false, OVERLAP, false, LOOKS>(p, grid, s);
 }
 
 // Calls of so many workgroups of 256 positions read the scratch set back (k_allocate_chunk says why).  Measured on 256 compute
@@ -572,12 +576,13 @@ mpzch_status_t launch_allocate_chunk(const Params &p, int grid, int num_cus, hip
 // (TTL tables would gain beyond their lines as well, but calls of new ids lose there: half of the ids new, 300 M slots as two tensors, 400 K
 // 68.6/70.6, 500 K 81.9/85.5, nearly all 97.2/102.4, 115.5/122.9, as records, 300 K, 73.2/76.1.)
 // In the cache (20 M slots as two tensors, 10 M as records), 262 144 positions: TTL, of 24, 43.3/42.2, records 39.1/39.3, LRU, of 32, 43.5/43.3,
-// records 48.9/48.5; sessions of eight steps of 200 000 on 2 M slots 450/438, records 421/421, loads of new ids 341/347, records 344/346.
+// records 48.9/48.5; sessions of eight steps of 200 000 on 2 M slots 450/438, records 421/421, loads of new ids 341/347, records 344/346.  Windows of up to
+// 8 slots have no later looks there, all having been looked at from the home slot on: TTL, 200 000, 262 144, 27.4/27.5 32.4/32.6, records 28.6/28.9 32.6/32.8.
 constexpr bool even_looks(int64_t groups, int num_cus, const TableDesc &t)
 {
     const bool cached = (t.N << (3 + t.sh)) <= kCachedTableBytes;
     const int most = cached ? 4 : 5 - (t.sh ? 1 : 0) + (t.evict == 2 && (t.sh || t.P <= 16) ? 1 : 0);
-    return t.P <= 32 && groups > 3 * (int64_t)num_cus && groups <= (int64_t)most * num_cus;
+    return t.P <= 32 && !(cached && t.P <= 8) && groups > 3 * (int64_t)num_cus && groups <= (int64_t)most * num_cus;
 }
 
 // Calls whose windows of 9 to 16 slots are read whole (SHIFT 1 of k_discover_chunk): up to one workgroup for two compute units.  Of records
@@ -629,10 +634,10 @@ mpzch_status_t launch_remap_chunks(Timing &tm, const Params &p, int32_t max_p_lr
     const bool aligned = aligned_first(grid, num_cus, p.t0);
     if (!tm.begin(KDiscover, s)) return MPZCH_ERR_HIP;
     if (whole_windows(grid, num_cus, p.t0)) TRY((launch_discover_chunk<1, false, true, false, false>(p, grid, s)));
-    else if (even_looks(grid, num_cus, p.t0)) TRY((launch_discover_chunk<true, false, true>(p, grid, aligned, s)));
-    else if (grid < num_cus) TRY((launch_discover_chunk<false, true, false>(p, grid, aligned, s)));
-    else if (overlap_insert(grid, num_cus, rec)) TRY((launch_discover_chunk<false, true, true>(p, grid, aligned, s)));
-    else TRY((launch_discover_chunk<false, false, true>(p, grid, aligned, s)));
+    else if (even_looks(grid, num_cus, p.t0)) TRY((launch_discover_chunk<0, true, false, true, true>(p, grid, s)));     // (all of them are `aligned`)
+    else if (grid < num_cus) TRY((launch_discover_chunk<true, false>(p, grid, aligned, s)));
+    else if (overlap_insert(grid, num_cus, rec, p.t0.evict == 3)) TRY((launch_discover_chunk<true, true>(p, grid, aligned, s)));
+    else TRY((launch_discover_chunk<false, true>(p, grid, aligned, s)));
     if (!tm.end(s) || !tm.begin(KAllocate, s)) return MPZCH_ERR_HIP;
     if (max_p_lru > 0 && rec) TRY(launch_allocate_lru_chunk<true>(max_p_lru, p, grid, num_cus, s));
     else if (max_p_lru > 0) TRY(launch_allocate_lru_chunk<false>(max_p_lru, p, grid, num_cus, s));

@@ -708,7 +708,7 @@ def test_groups_with_displaced_claims(n, records):
 # ---- one-chunk calls whose stores go out beside the scratch set's compare-and-swap: on both sides of each line, with new ids whose
 # copies meet within a wavefront and across workgroups, and durations per position
 @pytest.mark.parametrize("evict", [True, "expiry", False])
-@pytest.mark.parametrize("groups,layout", [(4, "separate"), (2, "records")])
+@pytest.mark.parametrize("groups,layout", [(4, "separate"), (3, "separate"), (2, "records")])
 def test_calls_around_the_lines_of_overlapped_inserts(groups, layout, evict):
     rng = rng_for(927)
     n = groups * torch.cuda.get_device_properties(0).multi_processor_count * 256
@@ -823,18 +823,19 @@ def test_calls_around_the_lines_of_whole_windows(layout, evict, slots, probe):
     t.close()
 
 
-# ---- the lines of even looks that windows draw: LRU tables over two tensors, of 16 slots and of one more
-@pytest.mark.parametrize("groups,probe", [(6, 16), (5, 17)])
-def test_calls_around_the_lines_of_even_looks_by_window(groups, probe):
+# ---- the lines of even looks that windows draw: LRU tables over two tensors beyond the cache, of 16 slots and of one more; in the cache, of 8 and of one
+# more, every table
+@pytest.mark.parametrize("groups,probe,slots,layout,evict", [(6, 16, (1 << 25) + 1, "separate", "lru"), (5, 17, (1 << 25) + 1, "separate", "lru")] + [
+    (3, probe, 1 << 19, layout, evict) for probe in (8, 9) for layout in ("separate", "records") for evict in (True, "lru", "expiry", False)])
+def test_calls_around_the_lines_of_even_looks_by_window(groups, probe, slots, layout, evict):
     rng = rng_for(957 + probe)
     n = groups * torch.cuda.get_device_properties(0).multi_processor_count * 256
-    slots = (1 << 25) + 1
-    t = Pair(slots, probe, 1, "lru", 71)
+    t = Pair(slots, probe, 1, evict, 71, layout=layout)
     for step, more in enumerate([0, 1, 0]):
         ids = wl.zipf_ids(rng, n + more, 1.05, 2 * n) + step * n // 8
         ids[: n // 2] = ids_with_home(rng, n // 2, 4_000, 4_000 + n // 2, slots, 71)
         ids[n // 2: n // 2 + 2_000] = ids_with_home(rng, 2_000, slots - 700, slots, slots, 71)
-        t.step(ids, 2 * step + 1, check_state=step == 2)
+        t.step(ids, 2 * step + 1, check_state=step == 2, ttls=rng.integers(0, 5, size=n + more).astype(np.int32) if evict == "expiry" else None)
     t.close()
 
 
